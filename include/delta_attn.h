@@ -45,8 +45,10 @@ typedef enum {
 typedef enum { DA_F32 = 0, DA_BF16 = 1 } da_dtype;
 
 /* How scores outside the window are produced.  Both give the same real-number result.
- *   DA_SCORE_GATHER  Eq. 4 as written: a running score per query row, updated per key
- *                    column with only the surviving (channel, delta) entries.
+ *   DA_SCORE_GATHER  Eq. 4: a running score per query row, updated per key column.  fp32 inputs and head dims other
+ *                    than 64 / 128 add up the surviving (channel, delta) entries one by one; bf16 inputs with head
+ *                    dims 64 / 128 take each column's sum in its telescoped form (below) on the matrix cores, where a
+ *                    dense product costs a sixth of the surviving entries' multiply-adds on the vector ALU.
  *   DA_SCORE_REBASE  the telescoped form of Eq. 4: sum_{u<=j} dk(u) = k_hat(j), so the
  *                    score is the dense product q . k_hat(j) (no multiply is skipped). */
 typedef enum { DA_SCORE_GATHER = 0, DA_SCORE_REBASE = 1 } da_score_mode;
@@ -135,9 +137,7 @@ da_status delta_attn_prefill(const da_prefill_params *p, const void *Q, const vo
 /*
  * delta_attn_prefill for callers that cannot allocate device memory or bring a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same computation and same kernels as
- * delta_attn_prefill without a cache, masks and nnz bit-identical; outputs bit-identical too unless delta_attn_prefill
- * cuts a small launch along the keys (several work groups per row tile, merged afterwards) and the built-in buffer has
- * no room for the parts: this call then runs uncut and the outputs differ in rounding order only.  The scratch is a
+ * delta_attn_prefill without a cache, results bit-identical.  The scratch is a
  * buffer of DA_NOALLOC_SCRATCH_BYTES built into the library's device image (one copy per GPU, held until the process
  * ends), so the call itself allocates nothing.
  *   - Returns DA_ERR_WORKSPACE, with the two sizes in delta_attn_last_error(), when
@@ -165,13 +165,10 @@ da_status delta_attn_prefill_noalloc(const da_prefill_params *p, const void *Q, 
  *             a decode_window above max_seq counts as max_seq),
  *             at most 32 query heads per KV head; otherwise DA_ERR_UNSUPPORTED
  *   workspace device scratch of at least delta_attn_prefill_append_workspace_bytes(p, cache) (0 if the arguments
- *             are invalid), 256-byte aligned; it depends on p->seq_len and (through the key split
- *             of launches that do not fill the chip) on the cache length at the time of the call
+ *             are invalid), 256-byte aligned
  * The cache keeps the sequence so far as the plain arrays the prefill kernels read (keys, reference keys, values in
- * two orders, mask rows, and in DA_SCORE_GATHER mode the entry lists and gather plans of all key columns), with
- * max_seq rows of room: about 8 * head_dim + 4 * head_dim / 32 bytes per (KV head, row), 16 * head_dim + 8 in
- * gather mode.  The first call on a cache allocates them (hipMalloc + hipMemset, released by
- * delta_attn_cache_destroy; DA_ERR_HIP if that fails; make that call outside graph capture); a call that follows
+ * two orders, mask rows), with max_seq rows of room: about 8 * head_dim + 4 * head_dim / 32 bytes per (KV head, row).
+ * The first call on a cache allocates them (hipMalloc + hipMemset, released by delta_attn_cache_destroy; DA_ERR_HIP if that fails; make that call outside graph capture); a call that follows
  * another such call, or delta_attn_cache_reset, then only adds its own rows.  After decode steps or a one-shot
  * delta_attn_prefill into the cache the arrays are rebuilt from the cache by the next call, at a cost proportional to
  * the cache length.

@@ -19,12 +19,11 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline size_t elt_size(int dtype) { return dtype == DA_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t khat, chunk_out, ents, counts, nch8, plan, dense, vt, part, total;
-    int ksplit;   // work groups per tile of the attention launch (prefill_mfma_ksplit); `part` holds their results
+    size_t khat, chunk_out, ents, counts, vt, total;
 };
 
-// what prefill_mfma_ksplit reads, for a prefill of p's rows behind `cached` rows
-PrefillArgs split_args(const da_prefill_params *p, int64_t cached) {
+// what prefill_mfma_supported reads, for a prefill of p's rows behind `cached` rows
+PrefillArgs shape_args(const da_prefill_params *p, int64_t cached) {
     PrefillArgs a = {};
     a.dtype = p->dtype;
     a.B = p->batch;
@@ -32,11 +31,6 @@ PrefillArgs split_args(const da_prefill_params *p, int64_t cached) {
     a.Hkv = p->n_kv_heads;
     a.d = p->head_dim;
     a.n = (int)cached + p->seq_len;
-    a.q_off = (int)cached;
-    a.nq = p->seq_len;
-    a.ksplit = 1;
-    a.rebase = p->score_mode == DA_SCORE_REBASE;
-    a.fused = cached == 0 && prefill_mfma_supported(a) && (int64_t)p->seq_len * p->head_dim <= kFusedMaxElems;
     return a;
 }
 
@@ -56,8 +50,7 @@ da_status check_params(const da_prefill_params *p) {
     return DA_OK;
 }
 
-// split: cut the attention launch along the keys where that pays (more scratch); false: never
-WsLayout layout(const da_prefill_params *p, bool split = true) {
+WsLayout layout(const da_prefill_params *p) {
     const size_t units = (size_t)p->batch * p->n_kv_heads;
     const size_t rows = units * (size_t)p->seq_len;
     WsLayout w;
@@ -70,18 +63,8 @@ WsLayout layout(const da_prefill_params *p, bool split = true) {
     off += align_up(rows * p->head_dim * 8);   // EntryChunk storage: 8 bytes per possible entry
     w.counts = off;
     off += align_up(rows * sizeof(uint32_t));
-    w.nch8 = off;
-    off += align_up(units * (size_t)prefill_mfma_n_pad(p->seq_len));
-    w.plan = off;
-    off += align_up(units * (size_t)prefill_mfma_n_pad(p->seq_len) * 2);   // 8 waves x 8 bytes per block of 32 columns
-    w.dense = off;
-    off += align_up(units * (size_t)(prefill_mfma_n_pad(p->seq_len) / 32) * 4);
     w.vt = off;
     off += align_up(units * (size_t)p->head_dim * prefill_mfma_n_pad(p->seq_len) * 2);
-    const PrefillArgs a = split_args(p, 0);
-    w.ksplit = split ? prefill_mfma_ksplit(a) : 1;
-    w.part = off;
-    off += align_up(prefill_mfma_part_bytes(a, w.ksplit));
     w.total = off;
     return w;
 }
@@ -120,7 +103,7 @@ void *scratch_of_current_device() {
     return ptr_of[dev];
 }
 
-// the kernels read the workspace with 16-byte loads and 64-byte entry chunks; regions are carved at multiples of 256
+// the kernels read the workspace with 16-byte loads (generic path: 64-byte entry chunks); regions are carved at multiples of 256
 inline bool ws_aligned(const void *ws) { return ((uintptr_t)ws & (kAlign - 1)) == 0; }
 
 }  // namespace
@@ -204,8 +187,7 @@ da_status delta_attn_prefill_noalloc(const da_prefill_params *p, const void *Q, 
     da_status st = check_params(p);
     if (st != DA_OK) return st;
     if (!Q || !K || !V || !O || !mask_bits || !nnz) return DA_ERR_INVALID_ARG;
-    WsLayout w = layout(p);
-    if (w.total > kScratchBytes) w = layout(p, false);   // without the key split of small launches: less scratch
+    const WsLayout w = layout(p);
     if (w.total > kScratchBytes) {
         set_last_error("delta_attn_prefill_noalloc: these params need %zu bytes of scratch, the built-in buffer holds %zu",
                        w.total, kScratchBytes);
@@ -213,7 +195,7 @@ da_status delta_attn_prefill_noalloc(const da_prefill_params *p, const void *Q, 
     }
     void *ws = scratch_of_current_device();
     if (!ws) return DA_ERR_HIP;
-    // Nothing in the buffer has to start at zero: every region is written by the scan, compaction and re-order
+    // Nothing in the buffer has to start at zero: every region is written by the scan and re-order
     // kernels before the attention kernel reads it (the nnz counters, which do, are the caller's and are cleared by
     // a fill kernel on the stream).
     return prefill_checked(p, w, Q, K, V, O, mask_bits, nnz, nullptr, ws, (hipStream_t)hip_stream);
@@ -230,7 +212,6 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     void *khat = ws + w.khat;
     void *ents = ws + w.ents;
     uint32_t *counts = (uint32_t *)(ws + w.counts);
-    uint8_t *nch8 = (uint8_t *)(ws + w.nch8);
     const int units = p->batch * p->n_kv_heads;
 
     (void)hipGetLastError();   // do not inherit an earlier, unrelated error
@@ -241,7 +222,7 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.Hkv = p->n_kv_heads;
     a.Hq = p->n_q_heads;
     a.n = p->seq_len;
-    // Short prompts on the matrix-core kernel: one launch does everything (the scan, the compaction and the V
+    // Short prompts on the matrix-core kernel: one launch does everything (the scan and the V
     // re-order run inside the attention launch, once per work group); longer ones take a launch per stage.
     const bool fused = prefill_mfma_supported(a) && (int64_t)p->seq_len * p->head_dim <= kFusedMaxElems;
     // (the scan's first launch takes the V re-order of the matrix-core kernels along where it can)
@@ -253,11 +234,9 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
                           prefill_mfma_n_pad(p->seq_len));
         stage_end(kStageScan, s);
         if (!launch_ok("delta_scan")) return DA_ERR_HIP;
-        if (p->score_mode == DA_SCORE_GATHER || cache) {
+        if (p->score_mode == DA_SCORE_GATHER && !prefill_mfma_supported(a)) {
             stage_begin(kStageEmit, s);
-            launch_emit_entries(p->dtype, K, khat, mask_bits, ents, counts, nch8, ws + w.plan,
-                                (uint32_t *)(ws + w.dense), units, p->seq_len, prefill_mfma_n_pad(p->seq_len),
-                                p->head_dim, s);
+            launch_emit_entries(p->dtype, K, khat, mask_bits, ents, counts, units, p->seq_len, p->head_dim, s);
             stage_end(kStageEmit, s);
             if (!launch_ok("emit_entries")) return DA_ERR_HIP;
         }
@@ -285,12 +264,7 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.O = O;
     a.ents = ents;
     a.counts = counts;
-    a.nch8 = nch8;
-    a.ksplit = w.ksplit;
-    a.part = ws + w.part;
     a.vt_from = vt_in_scan ? prefill_mfma_n_pad(p->seq_len) / 32 : 0;   // (every block of V is in place already)
-    a.plan = ws + w.plan;
-    a.dense = (const uint32_t *)(ws + w.dense);
     stage_begin(kStageAttn, s);
     bool launched = true;
     if (prefill_mfma_supported(a))
@@ -302,7 +276,7 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     if (!launch_ok("prefill attention")) return DA_ERR_HIP;
     if (cache) {
         stage_begin(kStageCacheFill, s);
-        cache_fill_from_prefill(cache, p, K, V, khat, mask_bits, counts, nnz, s);
+        cache_fill_from_prefill(cache, p, K, V, khat, mask_bits, nnz, s);
         stage_end(kStageCacheFill, s);
         if (!launch_ok("cache_fill")) return DA_ERR_HIP;
     }
@@ -312,11 +286,10 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
 // workspace of delta_attn_prefill_append: what the scan of the new rows needs (the whole-sequence arrays live in the
 // cache, see da_prefix)
 struct AppendLayout {
-    size_t hnew, chunk_out, part, total;
-    int ksplit;
+    size_t hnew, chunk_out, total;
 };
 
-AppendLayout append_layout(const da_prefill_params *p, int64_t cached) {
+AppendLayout append_layout(const da_prefill_params *p) {
     const size_t units = (size_t)p->batch * p->n_kv_heads, d = p->head_dim, es = elt_size(p->dtype);
     const size_t m = p->seq_len;
     AppendLayout w;
@@ -325,17 +298,13 @@ AppendLayout append_layout(const da_prefill_params *p, int64_t cached) {
     off += align_up(units * m * d * es);
     w.chunk_out = off;
     off += align_up(2 * units * (size_t)delta_scan_num_chunks((int)m) * d * es);
-    const PrefillArgs a = split_args(p, cached);
-    w.ksplit = prefill_mfma_ksplit(a);
-    w.part = off;
-    off += align_up(prefill_mfma_part_bytes(a, w.ksplit));
     w.total = off;
     return w;
 }
 
 // The cache's whole-sequence arrays (da_prefix), allocated on first use and zero-filled (rows nothing has written yet
 // must hold finite numbers: the kernels load whole tiles and discard what lies past the sequence).
-da_status ensure_prefix(da_cache *c, bool gather) {
+da_status ensure_prefix(da_cache *c) {
     if (!c->pf) {
         c->pf = new (std::nothrow) da_prefix();
         if (!c->pf) return DA_ERR_HIP;
@@ -353,13 +322,6 @@ da_status ensure_prefix(da_cache *c, bool gather) {
     room(&f->v, units * ld * d * 2);
     room((void **)&f->m, units * ld * (d / 32) * 4);
     room(&f->vt, units * d * ld_pad * 2);
-    if (gather) {
-        room(&f->ents, units * ld * d * 8);
-        room((void **)&f->counts, units * ld * 4);
-        room((void **)&f->nch8, units * ld_pad);
-        room(&f->plan, units * ld_pad * 2);
-        room((void **)&f->dense, units * (ld_pad / 32) * 4);
-    }
     if (!ok) {
         (void)launch_ok("prefill_append: room for the cached sequence as plain arrays");   // records the error text
         return DA_ERR_HIP;
@@ -381,7 +343,7 @@ da_status check_append(const da_prefill_params *p, const da_cache *c) {
     // than the sequence is long
     const int64_t reach = p->window < c->len + p->seq_len ? p->window : c->len + p->seq_len;
     if (c->len > 0 && reach > c->Wd) return DA_ERR_UNSUPPORTED;
-    if (!prefill_mfma_supported(split_args(p, c->len))) return DA_ERR_UNSUPPORTED;   // (more tiles than a grid holds)
+    if (!prefill_mfma_supported(shape_args(p, c->len))) return DA_ERR_UNSUPPORTED;   // (more tiles than a grid holds)
     return DA_OK;
 }
 }  // namespace
@@ -390,7 +352,7 @@ extern "C" {
 
 size_t delta_attn_prefill_append_workspace_bytes(const da_prefill_params *p, const da_cache *cache) {
     if (check_append(p, cache) != DA_OK) return 0;
-    return append_layout(p, cache->len).total;
+    return append_layout(p).total;
 }
 
 da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, const void *K, const void *V, void *O,
@@ -400,27 +362,22 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     if (st != DA_OK) return st;
     if (!Q || !K || !V || !O || !mask_bits || !nnz) return DA_ERR_INVALID_ARG;
     const int t0 = (int)cache->len, m = p->seq_len, nk = t0 + m, d = p->head_dim;
-    const AppendLayout w = append_layout(p, t0);
+    const AppendLayout w = append_layout(p);
     if (!workspace || workspace_bytes < w.total || !ws_aligned(workspace)) return DA_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
     char *ws = (char *)workspace;
     const int units = p->batch * p->n_kv_heads;
-    const bool gather = p->score_mode == DA_SCORE_GATHER;
     (void)hipGetLastError();
-    st = ensure_prefix(cache, gather);
+    st = ensure_prefix(cache);
     if (st != DA_OK) return st;
     da_prefix *f = cache->pf;
     const int ld = cache->max_seq;
-    const int n_pad = prefill_mfma_n_pad(nk);
 
     // 1. the cached rows as plain arrays: kept from the previous piece, or (after decode steps or a one-shot prefill
     //    into this cache) unpacked from the cache; the new rows behind them
     const bool kept = f->rows == t0;
     f->rows = -1;                                   // in flux until this call has gone through
-    if (!kept) {
-        expand_cache_runs(cache, t0, ld, f->k, f->h, f->v, f->m, s);
-        f->ent_rows = 0;
-    }
+    if (!kept) expand_cache_runs(cache, t0, ld, f->k, f->h, f->v, f->m, s);
     // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis);
     //    the new rows (keys, values, reference keys, mask rows) go behind the cached ones
     stage_begin(kStageScan, s);
@@ -429,17 +386,7 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     launch_append_rows(K, V, ws + w.hnew, mask_bits, f->k, f->v, f->h, f->m, units, t0, m, ld, d, s);
     stage_end(kStageScan, s);
     if (!launch_ok("delta_scan")) return DA_ERR_HIP;
-    // 3. entry lists and plans of the key columns that do not have them yet, from the first block of 32 columns that
-    //    is new or was incomplete (cached columns from reference keys: where a bit is set they equal the key)
-    if (gather) {
-        const int64_t have = f->ent_rows < t0 ? f->ent_rows : t0;
-        stage_begin(kStageEmit, s);
-        launch_emit_entries(p->dtype, f->k, f->h, f->m, f->ents, f->counts, f->nch8, f->plan, f->dense, units, nk, n_pad,
-                            d, s, ld, (int)(have / 32));
-        stage_end(kStageEmit, s);
-        if (!launch_ok("emit_entries")) return DA_ERR_HIP;
-    }
-    // 4. attention of the new rows over all nk keys
+    // 3. attention of the new rows over all nk keys
     PrefillArgs a;
     a.dtype = p->dtype;
     a.B = p->batch;
@@ -451,8 +398,6 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     a.nq = m;
     a.ld = ld;
     a.vt_from = kept ? t0 / 32 : 0;
-    a.ksplit = w.ksplit;
-    a.part = ws + w.part;
     a.W = p->window;
     a.scale_log2 = score_scale(p->scale, d) * 1.4426950408889634f;
     a.rebase = p->score_mode == DA_SCORE_REBASE;
@@ -462,11 +407,6 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     a.V = f->v;
     a.Khat = f->h;
     a.O = O;
-    a.ents = f->ents;
-    a.counts = f->counts;
-    a.nch8 = f->nch8;
-    a.plan = f->plan;
-    a.dense = f->dense;
     a.fused = 0;
     a.mask_bits = nullptr;
     a.nnz = nullptr;
@@ -475,14 +415,13 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     launch_prefill_mfma(a, f->vt, s);                  // (supported: check_append has asked)
     stage_end(kStageAttn, s);
     if (!launch_ok("prefill_append attention")) return DA_ERR_HIP;
-    // 5. the new rows join the cache
+    // 4. the new rows join the cache
     stage_begin(kStageCacheFill, s);
     cache_fill_runs(cache, t0, nk, ld, f->k, V, f->h, f->m, nnz, s);
     stage_end(kStageCacheFill, s);
     if (!launch_ok("cache_fill")) return DA_ERR_HIP;
     cache->len = nk;
     f->rows = nk;
-    if (gather) f->ent_rows = nk;
     return DA_OK;
 }
 

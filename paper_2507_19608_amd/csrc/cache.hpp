@@ -10,22 +10,16 @@ constexpr int kChunk = 64;   // rows per decode chunk; one reference-key checkpo
 
 // What delta_attn_prefill_append keeps between its calls on one cache (Sec. III-C, a prompt processed in pieces):
 // the sequence so far as the plain arrays the prefill kernels read, so that a piece only adds its own rows instead
-// of unpacking and compacting the whole prefix again.  Device memory with max_seq rows of room per unit (row stride
-// max_seq, padded strides from prefill_mfma_n_pad(max_seq)), allocated by the first such call (the entry-list
-// arrays by the first one in gather mode), freed with the cache.  Host-side bookkeeping: kernels never see it.
+// of unpacking the whole prefix again.  Device memory with max_seq rows of room per unit (row stride
+// max_seq, padded strides from prefill_mfma_n_pad(max_seq)), allocated by the first such call, freed with the
+// cache.  Host-side bookkeeping: kernels never see it.
 struct da_prefix {
     void *k, *h, *v;      // [units][max_seq][d]     keys (raw where a window may need them, see expand_cache_kernel),
                           //                         reference keys, values
     uint32_t *m;          // [units][max_seq][d/32]  mask rows
     void *vt;             // V in matrix-core operand order (transpose_v_kernel)
-    void *ents;           // entry lists, counts, chunk counts, gather plan, re-based columns (emit_entries_kernel)
-    uint32_t *counts;
-    uint8_t *nch8;
-    void *plan;
-    uint32_t *dense;
     int64_t rows;         // k, h, v, m, vt describe rows 0 .. rows - 1 of the cached sequence; only trusted while
                           // rows == the cache's length (decode steps and one-shot prefills do not maintain them)
-    int64_t ent_rows;     // key columns 0 .. ent_rows - 1 have their entry lists and plans
 };
 
 struct da_cache {
@@ -81,7 +75,7 @@ inline bool cache_scale_matches(const da_cache *c, float scale) {
 }
 da_status cache_check_for_prefill(const da_cache *c, const da_prefill_params *p);
 void cache_fill_from_prefill(da_cache *c, const da_prefill_params *p, const void *K, const void *V,
-                             const void *Khat, const uint32_t *mask_bits, const uint32_t *counts,
+                             const void *Khat, const uint32_t *mask_bits,
                              const uint64_t *nnz, hipStream_t s);
 // column-run layout (fast == 1)
 // appends rows t0 .. n_k - 1 (t0 = rows already held) from whole-sequence arrays [units][ld][...] (ld >= n_k rows of

@@ -263,43 +263,19 @@ __global__ __launch_bounds__(64) void delta_scan_fixup_kernel(const T *__restric
 
 // One work group per block of 32 key columns, a wave per column at a time: ballot + prefix count turn the mask row into
 // a dense list of (channel, delta) pairs in EntryChunk form, padded with (0, 0.0f) to whole chunks and to at
-// least one chunk.  The chunks of column j of a unit start at chunk (unit * n + j) * d / 8;
-// counts holds the unpadded length, nch8 (stride n_pad per unit) the number of chunks.
-// plan (may be NULL): which of the block's columns each of the 8 waves of the matrix-core prefill kernel takes in its
-// gather loop, and in which pairs.  Full columns - lists that fill all d / 8 chunks, i.e. more than d - 8 surviving
-// entries: the whole-vector jumps of the key stream, and the basis row - can be left out of the gather: the running
-// score of Eq. 4 is then re-based at such a column from the dense product q . k_hat(j), which the telescoped sum makes
-// exact, on the matrix cores.  That costs a block a fixed amount (one K_hat Q^T tile) and saves the gather of each
-// full column, so it is done in blocks with at least kRouteMin full columns (measured break-even: about three), and
-// only if every reference key of the block fits fp16, the tile's operand format.  Re-based columns get chunk count 0
-// in the plan and their bit set in the block's word of `dense` ([units][n_pad / 32]).  The other
-// columns are ranked by chunk count (ties: lower index first), neighbours in that order form the 16 pairs (so the two
-// columns of a pair have nearly the same length), and every wave is dealt two pairs so that the four SIMDs carry
-// nearly equal numbers of gather steps (plan_block).  A wave's 8
-// bytes: the four column indices (first pair, longer column first; second pair), then their chunk counts; blocks that
-// reach past row n get zero counts and no dense bits (that kernel only gathers in blocks left of every row's window).
-// Which wave sums a column does not change the sum.
+// least one chunk.  The chunks of column j of a unit start at chunk (unit * n + j) * d / 8; counts holds the unpadded
+// length.
 template <typename T>
 __global__ __launch_bounds__(256) void emit_entries_kernel(const T *__restrict__ K, const T *__restrict__ Khat,
                                                            const uint32_t *__restrict__ mask_bits,
                                                            EntryChunk *__restrict__ ents, uint32_t *__restrict__ counts,
-                                                           uint8_t *__restrict__ nch8, uint8_t *__restrict__ plan,
-                                                           uint32_t *__restrict__ dense, int n, int ld, int ld_pad,
-                                                           int blk0, int d) {
-    constexpr int kCols = kPlanCols, kPlanWaves = kPlanWaveCount;
-    __shared__ uint32_t blk_cnt[kCols];
-    const int unit = blockIdx.y, blk = blk0 + blockIdx.x;
-    const int lane = threadIdx.x & 63;
-    const size_t row0 = (size_t)unit * ld;
+                                                           int n, int d) {
+    const int unit = blockIdx.y, lane = threadIdx.x & 63;
+    const size_t row0 = (size_t)unit * n;
     // the 4 waves take every 4th column of the block
+    const int first = (int)blockIdx.x * 32;
     emit_columns(K + row0 * d, Khat + row0 * d, mask_bits + row0 * (d >> 5), ents + row0 * (d / kGroup), counts + row0,
-                 nch8 + (size_t)unit * ld_pad, blk_cnt, n, d, lane, blk * kCols + (int)(threadIdx.x >> 6), 4,
-                 (blk + 1) * kCols, blk * kCols);
-    if (!plan) return;
-    __syncthreads();
-    if (threadIdx.x < kWave)                                  // the first wave; its lanes 0 .. 31 own a column each
-        plan_block(blk_cnt, plan + ((size_t)unit * (ld_pad / kCols) + blk) * kPlanWaves * 8,
-                   dense + (size_t)unit * (ld_pad / kCols) + blk, (blk + 1) * kCols <= n, d, threadIdx.x);
+                 n, d, lane, first + (int)(threadIdx.x >> 6), 4, first + 32);
 }
 
 __global__ void fill_u64_kernel(unsigned long long *p, unsigned long long v, int n) {
@@ -404,22 +380,15 @@ void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits
         scan_typed<bf16_t>(K, Khat, mask_bits, chunk_out, nnz, units, n, d, theta, init, s, V, Vt, n_pad);
 }
 
-// ld > 0: the arrays have ld rows of room per unit (padded strides from prefill_mfma_n_pad(ld)) of which n are valid,
-// and only the blocks of 32 columns from blk0 on are (re)written; ld == 0: the arrays are exactly n rows per unit.
 void launch_emit_entries(int dtype, const void *K, const void *Khat, const uint32_t *mask_bits, void *ents,
-                         uint32_t *counts, uint8_t *nch8, void *plan, uint32_t *dense, int units, int n, int n_pad,
-                         int d, hipStream_t s, int ld, int blk0) {
-    const int ld_pad = ld > 0 ? prefill_mfma_n_pad(ld) : n_pad;
-    if (ld <= 0) ld = n;
-    if (blk0 >= n_pad / 32) return;
-    dim3 grid(n_pad / 32 - blk0, units), block(256);
+                         uint32_t *counts, int units, int n, int d, hipStream_t s) {
+    dim3 grid((n + 31) / 32, units), block(256);
     if (dtype == 0)
         hipLaunchKernelGGL(emit_entries_kernel<float>, grid, block, 0, s, (const float *)K, (const float *)Khat,
-                           mask_bits, (EntryChunk *)ents, counts, nch8, (uint8_t *)plan, dense, n, ld, ld_pad, blk0, d);
+                           mask_bits, (EntryChunk *)ents, counts, n, d);
     else
         hipLaunchKernelGGL(emit_entries_kernel<bf16_t>, grid, block, 0, s, (const bf16_t *)K,
-                           (const bf16_t *)Khat, mask_bits, (EntryChunk *)ents, counts, nch8, (uint8_t *)plan, dense, n,
-                           ld, ld_pad, blk0, d);
+                           (const bf16_t *)Khat, mask_bits, (EntryChunk *)ents, counts, n, d);
 }
 
 }  // namespace da

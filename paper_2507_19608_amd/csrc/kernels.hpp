@@ -31,23 +31,18 @@ struct PrefillArgs {
     int dtype;            // 0 f32, 1 bf16
     int B, Hq, Hkv, d, n, W;   // n = number of key rows
     int q_off, nq;             // the query rows are positions q_off .. q_off + nq - 1 (q_off + nq == n)
-    int ld = 0;                // > 0 (matrix-core path only): K, V, Khat, ents, counts have ld >= n rows of room per
-                               // unit and nch8, plan, dense, vt the strides of prefill_mfma_n_pad(ld); 0: exactly n
+    int ld = 0;                // > 0 (matrix-core path only): K, V, Khat have ld >= n rows of room per unit and vt the
+                               // stride of prefill_mfma_n_pad(ld); 0: exactly n
     int vt_from = 0;           // blocks of 32 rows below this one are already in vt (V re-order of earlier rows kept)
-    int ksplit = 1;            // matrix-core path: work groups per tile (prefill_mfma_ksplit), each on a part of the keys
-    void *part = nullptr;      // ksplit > 1: prefill_mfma_part_bytes of scratch for the parts' results
     float scale_log2;     // score scale * log2(e)
-    int rebase;           // 1: outside scores from q . k_hat instead of the entry lists
+    int rebase;           // generic path: 1: outside scores from q . k_hat instead of the entry lists
     int sliding;          // 1: exact region is the band i - j < W instead of squares of side W
     const void *Q, *K, *V, *Khat;
     void *O;
-    const void *ents;     // EntryChunk lists, column (unit, j) at chunk (unit * n + j) * d / 8
+    const void *ents;     // generic path: EntryChunk lists, column (unit, j) at chunk (unit * n + j) * d / 8
     const uint32_t *counts;
-    const uint8_t *nch8;  // chunks per column, stride prefill_mfma_n_pad(n) per unit
-    const void *plan;     // gather mode: the column plan written by launch_emit_entries
-    const uint32_t *dense;   // gather mode: per unit and block of 32 columns, the columns re-based instead of gathered
-    // fused short-prompt launch (matrix-core kernel only): the attention launch itself runs the delta scan, the
-    // compaction and the V re-order; then K_hat, ents, counts, nch8, plan, dense are scratch it fills first
+    // fused short-prompt launch (matrix-core kernel only): the attention launch itself runs the delta scan and
+    // the V re-order; then K_hat and vt are scratch it fills first
     int fused;
     uint32_t *mask_bits;  // out (fused)
     uint64_t *nnz;        // out (fused)
@@ -72,11 +67,8 @@ bool delta_scan_takes_v(int dtype, int n, int d);
 void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *chunk_out, uint64_t *nnz,
                        int units, int n, int d, float theta, hipStream_t s, const void *init = nullptr,
                        const void *V = nullptr, void *Vt = nullptr, int n_pad = 0);
-// plan: NULL, or room for units * n_pad * 2 bytes: the gather loop's column plan; dense (used with plan): room for
-// units * n_pad / 32 words (see emit_entries_kernel)
 void launch_emit_entries(int dtype, const void *K, const void *Khat, const uint32_t *mask_bits, void *ents,
-                         uint32_t *counts, uint8_t *nch8, void *plan, uint32_t *dense, int units, int n, int n_pad,
-                         int d, hipStream_t s, int ld = 0, int blk0 = 0);
+                         uint32_t *counts, int units, int n, int d, hipStream_t s);
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, VALU only.  Returns false if
 // the head_dim has no instantiation.
 bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);
@@ -84,11 +76,6 @@ bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);
 bool prefill_mfma_supported(const PrefillArgs &a);
 int prefill_mfma_n_pad(int n);
 void launch_prefill_mfma(const PrefillArgs &a, void *vt, hipStream_t s);
-// Key-range split of the matrix-core launch (flash-decoding style, for launches that do not fill the chip): the
-// number of work groups per tile that pays for these arguments on the current device (1: none; reads B, Hq, Hkv, d,
-// nq, q_off, fused, dtype) and the scratch that many need.
-int prefill_mfma_ksplit(const PrefillArgs &a);
-size_t prefill_mfma_part_bytes(const PrefillArgs &a, int ksplit);
 // compute units of the current device (256 if it cannot be asked)
 int device_cu_count();
 

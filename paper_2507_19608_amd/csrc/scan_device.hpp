@@ -97,7 +97,7 @@ __device__ __forceinline__ float scan_rows(const T *__restrict__ Kp, T *__restri
 }
 
 // Compaction of one key column j of a unit by one wave: ballot + prefix count turn the mask row into a dense list of
-// (channel, delta) pairs in EntryChunk form (see emit_entries_kernel); blk_cnt[slot_in_block] receives the chunk count.
+// (channel, delta) pairs in EntryChunk form (see emit_entries_kernel).
 // In two steps, so that a wave can have the next column's inputs in flight while it works on this one (a column is
 // a short chain of dependent memory round trips; one column at a time is latency bound):
 //   load_column    every input of the column: the lane's mask word, key and previous reference key of each 64-channel
@@ -129,16 +129,11 @@ __device__ __forceinline__ void load_column(ColumnIn &in, const T *K0, const T *
 
 template <typename T>
 __device__ __forceinline__ void finish_column(const ColumnIn &in, EntryChunk *__restrict__ ents0,
-                                              uint32_t *__restrict__ counts0, uint8_t *__restrict__ nch0,
-                                              uint32_t *blk_cnt, int n, int d, int lane, int j, int slot_in_block) {
-    if (j >= n) {
-        if (lane == 0) blk_cnt[slot_in_block] = 0u;
-        return;
-    }
+                                              uint32_t *__restrict__ counts0, int n, int d, int lane, int j) {
+    if (j >= n) return;
     const size_t row = (size_t)j;
     EntryChunk *out = ents0 + row * (d / kGroup);
     uint32_t off = 0;
-    bool big = false;
 #pragma unroll
     for (int p = 0; p < kMaxPass; ++p) {
         if (p * kWave >= d) break;
@@ -151,10 +146,7 @@ __device__ __forceinline__ void finish_column(const ColumnIn &in, EntryChunk *__
             const float k = in.k[p];
             const float held = (j == 0) ? 0.f : in.held[p];
             delta = k - held;                                  // (row 0: the basis, delta = k)
-            const float now = (bit || j == 0) ? k : held;      // reference key after this row
-            big = big || !(fabsf(now) < 32768.f);
         }
-        big = __any(big);
         const uint64_t b = __ballot(bit);
         if (bit) {
             const uint32_t slot = off + lanes_below(b);
@@ -170,91 +162,20 @@ __device__ __forceinline__ void finish_column(const ColumnIn &in, EntryChunk *__
         out[slot / kGroup].chan[slot % kGroup] = 0u;
         out[slot / kGroup].delta[slot % kGroup] = 0.f;
     }
-    if (lane == 0) {
-        counts0[row] = off;
-        nch0[j] = (uint8_t)(padded / kGroup);
-        // bit 31: some reference key of this row is too large for (or not a number in) fp16, the format in which the
-        // matrix-core prefill kernel re-bases a column; such a column is gathered like any other
-        blk_cnt[slot_in_block] = (padded / kGroup) | (big ? 0x80000000u : 0u);
-    }
+    if (lane == 0) counts0[row] = off;
 }
 
-// Columns first, first + step, ... below end (end - first a multiple of step is not required) by one wave, the
-// inputs of column i + 1 requested before column i is compacted; the chunk count of column j goes to
-// blk_cnt[j - cnt_base].
 template <typename T>
 __device__ __forceinline__ void emit_columns(const T *K0, const T *H0, const uint32_t *M0, EntryChunk *__restrict__ ents0,
-                                             uint32_t *__restrict__ counts0, uint8_t *__restrict__ nch0,
-                                             uint32_t *blk_cnt, int n, int d, int lane, int first, int step, int end,
-                                             int cnt_base) {
+                                             uint32_t *__restrict__ counts0, int n, int d, int lane, int first, int step, int end) {
     if (first >= end) return;
     ColumnIn cur, nxt;
     load_column(cur, K0, H0, M0, n, d, lane, first);
     for (int j = first; j < end; j += step) {
         load_column(nxt, K0, H0, M0, n, d, lane, j + step);   // clamped to the last row; unused after the last column
-        finish_column<T>(cur, ents0, counts0, nch0, blk_cnt, n, d, lane, j, j - cnt_base);
+        finish_column<T>(cur, ents0, counts0, n, d, lane, j);
         cur = nxt;
     }
-}
-
-// The gather plan of one block of 32 key columns (see emit_entries_kernel), by the 64 lanes of one wave.
-//   blk_cnt  [32] chunk counts of the block's columns (bit 31: a reference key of that row does not fit fp16)
-//   plan_out the block's kPlanWaveCount x 8 bytes;  dense_out the block's word of re-based columns
-constexpr int kPlanCols = 32, kPlanWaveCount = 8;            // columns per block = the prefill kernel's key block
-constexpr int kRouteMin = 4;
-__device__ __forceinline__ void plan_block(const uint32_t *blk_cnt, uint8_t *plan_out, uint32_t *dense_out, bool whole,
-                                           int d, int lane) {
-    constexpr int kCols = kPlanCols, kPlanWaves = kPlanWaveCount;
-    const int c = lane & (kCols - 1);
-    auto chunks_of = [&](int col) { return blk_cnt[col] & 0x7fffffffu; };
-    const uint64_t full_cols = __ballot(lane < kCols && chunks_of(c) == (uint32_t)(d / kGroup));
-    const bool fits = whole && !__any((blk_cnt[c] >> 31) != 0u) && __popcll(full_cols) >= kRouteMin;
-    auto is_routed = [&](int col) { return fits && chunks_of(col) == (uint32_t)(d / kGroup); };
-    const bool routed = is_routed(c);
-    const uint64_t routed_cols = __ballot(routed && lane < kCols);
-    const uint32_t mine = routed ? 0u : chunks_of(c);
-    uint32_t rank = 0;
-    for (int o = 0; o < kCols; ++o) {
-        const uint32_t other = is_routed(o) ? 0u : chunks_of(o);
-        rank += (other > mine || (other == mine && o < c)) ? 1u : 0u;
-    }
-    if (!whole) rank = (uint32_t)c;
-    const uint32_t pair = rank >> 1;
-    // The pairs go, longest first, to the wave whose SIMD has the fewest gather steps so far (waves w and w + 4 of the
-    // 8 share a SIMD and its vector ALU; ties: the wave with fewer steps, then the lower index), two pairs per wave.
-    // A whole-vector jump of the key stream - a column of d / 8 chunks among columns a third as long - then lands on a
-    // SIMD whose other pairs are short.  (Dealt by rank alone, pairs w and 15 - w to wave w: 8.25 instead of 8.09 ms on
-    // the 8K workload; treating waves w and w ^ 1 as SIMD partners instead: 8.38 ms.)
-    // (lane w < 8 keeps wave w's tally; the choice is a minimum over those 8 lanes)
-    uint32_t steps_mine = 0, pairs_mine = 0;                 // of wave `lane & 7`
-    uint32_t wv = 0, nth = 0;                                // this lane's column: its wave, first or second pair there
-    for (int r = 0; r < kCols / 2; ++r) {
-        // steps of pair r = chunk count of its longer column, the one of rank 2 r
-        const uint64_t holder = __ballot(lane < kCols && rank == (uint32_t)(2 * r));
-        const uint32_t a = (uint32_t)__shfl((int)mine, (int)__builtin_ctzll(holder | (1ull << 63)));
-        const uint32_t partner = (uint32_t)__shfl_xor((int)steps_mine, kPlanWaves / 2);
-        uint32_t key = pairs_mine < 2u ? ((steps_mine + partner) << 16) | (steps_mine << 4) | (uint32_t)(lane & (kPlanWaves - 1))
-                                       : 0xffffffffu;
-#pragma unroll
-        for (int sft = 1; sft < kPlanWaves; sft <<= 1) key = min(key, (uint32_t)__shfl_xor((int)key, sft));
-        const uint32_t best = key & (uint32_t)(kPlanWaves - 1);
-        const uint32_t had = (uint32_t)__shfl((int)pairs_mine, (int)best);
-        if (pair == (uint32_t)r) {
-            wv = best;
-            nth = had;
-        }
-        if ((uint32_t)(lane & (kPlanWaves - 1)) == best) {
-            steps_mine += a;
-            pairs_mine += 1u;
-        }
-    }
-    const uint32_t slot = 2u * nth + (rank & 1u);
-    if (lane < kCols) {
-        uint8_t *out = plan_out + wv * 8;
-        out[slot] = (uint8_t)c;
-        out[4 + slot] = whole ? (uint8_t)mine : (uint8_t)0;
-    }
-    if (lane == 0) *dense_out = (uint32_t)routed_cols;
 }
 
 }  // namespace da
