@@ -19,7 +19,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline size_t elt_size(int dtype) { return dtype == DA_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t khat, chunk_out, ents, counts, vt, total;
+    size_t khat, chunk_out, scan_total, vt, total;
 };
 
 // what prefill_mfma_supported reads, for a prefill of p's rows behind `cached` rows
@@ -59,10 +59,10 @@ WsLayout layout(const da_prefill_params *p) {
     off += align_up(rows * p->head_dim * elt_size(p->dtype));
     w.chunk_out = off;
     off += align_up(2 * units * (size_t)delta_scan_num_chunks(p->seq_len) * p->head_dim * elt_size(p->dtype));
-    w.ents = off;
-    off += align_up(rows * p->head_dim * 8);   // EntryChunk storage: 8 bytes per possible entry
-    w.counts = off;
-    off += align_up(rows * sizeof(uint32_t));
+    w.scan_total = off;
+    // Room that no kernel uses: the size a caller asked for has always covered 8 bytes per key element and 4 per row
+    // here, and plans that were sized with it stay comparable.
+    off += align_up(rows * p->head_dim * 8) + align_up(rows * sizeof(uint32_t));
     w.vt = off;
     off += align_up(units * (size_t)p->head_dim * prefill_mfma_n_pad(p->seq_len) * 2);
     w.total = off;
@@ -103,7 +103,7 @@ void *scratch_of_current_device() {
     return ptr_of[dev];
 }
 
-// the kernels read the workspace with 16-byte loads (generic path: 64-byte entry chunks); regions are carved at multiples of 256
+// the kernels read the workspace with 16-byte loads; regions are carved at multiples of 256
 inline bool ws_aligned(const void *ws) { return ((uintptr_t)ws & (kAlign - 1)) == 0; }
 
 }  // namespace
@@ -149,7 +149,7 @@ size_t delta_attn_prefill_workspace_bytes(const da_prefill_params *p) {
 size_t delta_attn_delta_scan_workspace_bytes(const da_prefill_params *p) {
     if (check_params(p) != DA_OK) return 0;
     const WsLayout w = layout(p);
-    return w.ents;   // reference keys + per-chunk states: the first two regions of the prefill layout
+    return w.scan_total;   // reference keys + per-chunk states: the first two regions of the prefill layout
 }
 
 da_status delta_attn_delta_scan(const da_prefill_params *p, const void *K, uint32_t *mask_bits, uint64_t *nnz,
@@ -158,7 +158,7 @@ da_status delta_attn_delta_scan(const da_prefill_params *p, const void *K, uint3
     if (st != DA_OK) return st;
     if (!K || !mask_bits || !nnz) return DA_ERR_INVALID_ARG;
     const WsLayout w = layout(p);
-    if (!workspace || workspace_bytes < w.ents || !ws_aligned(workspace)) return DA_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < w.scan_total || !ws_aligned(workspace)) return DA_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)hip_stream;
     char *ws = (char *)workspace;
     (void)hipGetLastError();
@@ -210,8 +210,6 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
                           hipStream_t s) {
     char *ws = (char *)workspace;
     void *khat = ws + w.khat;
-    void *ents = ws + w.ents;
-    uint32_t *counts = (uint32_t *)(ws + w.counts);
     const int units = p->batch * p->n_kv_heads;
 
     (void)hipGetLastError();   // do not inherit an earlier, unrelated error
@@ -234,12 +232,6 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
                           prefill_mfma_n_pad(p->seq_len));
         stage_end(kStageScan, s);
         if (!launch_ok("delta_scan")) return DA_ERR_HIP;
-        if (p->score_mode == DA_SCORE_GATHER && !prefill_mfma_supported(a)) {
-            stage_begin(kStageEmit, s);
-            launch_emit_entries(p->dtype, K, khat, mask_bits, ents, counts, units, p->seq_len, p->head_dim, s);
-            stage_end(kStageEmit, s);
-            if (!launch_ok("emit_entries")) return DA_ERR_HIP;
-        }
     }
     a.fused = fused ? 1 : 0;
     a.mask_bits = mask_bits;
@@ -255,15 +247,12 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.nq = p->seq_len;
     a.W = p->window;
     a.scale_log2 = score_scale(p->scale, p->head_dim) * 1.4426950408889634f;
-    a.rebase = p->score_mode == DA_SCORE_REBASE;
     a.sliding = p->window_mode == DA_WINDOW_SLIDING;
     a.Q = Q;
     a.K = K;
     a.V = V;
     a.Khat = khat;
     a.O = O;
-    a.ents = ents;
-    a.counts = counts;
     a.vt_from = vt_in_scan ? prefill_mfma_n_pad(p->seq_len) / 32 : 0;   // (every block of V is in place already)
     stage_begin(kStageAttn, s);
     bool launched = true;
@@ -400,7 +389,6 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     a.vt_from = kept ? t0 / 32 : 0;
     a.W = p->window;
     a.scale_log2 = score_scale(p->scale, d) * 1.4426950408889634f;
-    a.rebase = p->score_mode == DA_SCORE_REBASE;
     a.sliding = p->window_mode == DA_WINDOW_SLIDING;
     a.Q = Q;
     a.K = f->k;

@@ -1,5 +1,4 @@
-// Delta matrix construction on the key matrix (Sec. II-C Eq. 2-3; Sec. III-A strategy 3) and
-// compaction of the surviving entries per key column.
+// Delta matrix construction on the key matrix (Sec. II-C Eq. 2-3; Sec. III-A strategy 3).
 #include "common.hpp"
 #include "kernels.hpp"
 #include "scan_device.hpp"
@@ -261,23 +260,6 @@ __global__ __launch_bounds__(64) void delta_scan_fixup_kernel(const T *__restric
     if (lane == 0 && adjust != 0) atomicAdd(nnz + unit, (unsigned long long)adjust);
 }
 
-// One work group per block of 32 key columns, a wave per column at a time: ballot + prefix count turn the mask row into
-// a dense list of (channel, delta) pairs in EntryChunk form, padded with (0, 0.0f) to whole chunks and to at
-// least one chunk.  The chunks of column j of a unit start at chunk (unit * n + j) * d / 8; counts holds the unpadded
-// length.
-template <typename T>
-__global__ __launch_bounds__(256) void emit_entries_kernel(const T *__restrict__ K, const T *__restrict__ Khat,
-                                                           const uint32_t *__restrict__ mask_bits,
-                                                           EntryChunk *__restrict__ ents, uint32_t *__restrict__ counts,
-                                                           int n, int d) {
-    const int unit = blockIdx.y, lane = threadIdx.x & 63;
-    const size_t row0 = (size_t)unit * n;
-    // the 4 waves take every 4th column of the block
-    const int first = (int)blockIdx.x * 32;
-    emit_columns(K + row0 * d, Khat + row0 * d, mask_bits + row0 * (d >> 5), ents + row0 * (d / kGroup), counts + row0,
-                 n, d, lane, first + (int)(threadIdx.x >> 6), 4, first + 32);
-}
-
 __global__ void fill_u64_kernel(unsigned long long *p, unsigned long long v, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -378,17 +360,6 @@ void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits
         scan_typed<float>(K, Khat, mask_bits, chunk_out, nnz, units, n, d, theta, init, s, nullptr, nullptr, 0);
     else
         scan_typed<bf16_t>(K, Khat, mask_bits, chunk_out, nnz, units, n, d, theta, init, s, V, Vt, n_pad);
-}
-
-void launch_emit_entries(int dtype, const void *K, const void *Khat, const uint32_t *mask_bits, void *ents,
-                         uint32_t *counts, int units, int n, int d, hipStream_t s) {
-    dim3 grid((n + 31) / 32, units), block(256);
-    if (dtype == 0)
-        hipLaunchKernelGGL(emit_entries_kernel<float>, grid, block, 0, s, (const float *)K, (const float *)Khat,
-                           mask_bits, (EntryChunk *)ents, counts, n, d);
-    else
-        hipLaunchKernelGGL(emit_entries_kernel<bf16_t>, grid, block, 0, s, (const bf16_t *)K,
-                           (const bf16_t *)Khat, mask_bits, (EntryChunk *)ents, counts, n, d);
 }
 
 }  // namespace da

@@ -35,12 +35,9 @@ struct PrefillArgs {
                                // stride of prefill_mfma_n_pad(ld); 0: exactly n
     int vt_from = 0;           // blocks of 32 rows below this one are already in vt (V re-order of earlier rows kept)
     float scale_log2;     // score scale * log2(e)
-    int rebase;           // generic path: 1: outside scores from q . k_hat instead of the entry lists
     int sliding;          // 1: exact region is the band i - j < W instead of squares of side W
     const void *Q, *K, *V, *Khat;
     void *O;
-    const void *ents;     // generic path: EntryChunk lists, column (unit, j) at chunk (unit * n + j) * d / 8
-    const uint32_t *counts;
     // fused short-prompt launch (matrix-core kernel only): the attention launch itself runs the delta scan and
     // the V re-order; then K_hat and vt are scratch it fills first
     int fused;
@@ -67,10 +64,8 @@ bool delta_scan_takes_v(int dtype, int n, int d);
 void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *chunk_out, uint64_t *nnz,
                        int units, int n, int d, float theta, hipStream_t s, const void *init = nullptr,
                        const void *V = nullptr, void *Vt = nullptr, int n_pad = 0);
-void launch_emit_entries(int dtype, const void *K, const void *Khat, const uint32_t *mask_bits, void *ents,
-                         uint32_t *counts, int units, int n, int d, hipStream_t s);
-// Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, VALU only.  Returns false if
-// the head_dim has no instantiation.
+// Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
+// no instantiation.  q_off, ld and the fused launch are not for it.
 bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);
 // Matrix-core path: bf16, head_dim 64 or 128.  vt is scratch for V^T: units * d * prefill_mfma_n_pad(n) bf16.
 bool prefill_mfma_supported(const PrefillArgs &a);

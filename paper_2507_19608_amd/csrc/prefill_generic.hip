@@ -1,15 +1,36 @@
-// Generic hybrid-attention prefill (Sec. III-B prefill stage; Eq. 4; Eq. 1): vector ALU only,
-// any head_dim that is a multiple of 32 up to 256, fp32 or bf16 inputs, fp32 arithmetic.
+// Hybrid-attention prefill (Sec. III-B prefill stage; Eq. 4; Eq. 1) in binary32 on the matrix cores
+// (v_mfma_f32_16x16x4): fp32 inputs, and bf16 inputs of head dims that prefill_mfma.hip has no kernel for.  Any head_dim
+// that is a multiple of 32 up to 256.
 //
-// One wave per 64 consecutive query rows of one query head; lane = query row.  Every key
-// column is wave-uniform, so its compacted (channel, delta) list, its raw key row and its value
-// row are read through the scalar path and broadcast; the per-row operand q_i[c] comes from a
-// transposed copy of the Q tile in LDS.  A row keeps its Eq. 4 running score in a register and
-// its softmax state lane-locally (no cross-lane reductions anywhere).
+// Scores left of the window are Eq. 4's running sum in telescoped form, q . k_hat(j); a block of keys that straddles
+// a window takes both products and a select per element.
+//
+// Work group = 16 * QT consecutive query rows of one query head; its 8 waves take the blocks of 32 keys in turn, each
+// with its own running (maximum, sum, output), and meet in LDS once at the end.  The calls this kernel sees are small
+// (a numerics user's single head of a few hundred rows), so what bounds it is how many waves there are and how long the
+// longest one walks: a wave per 64 rows that walked every key took 725 us on 256 rows of one head of 64 (4 waves on the
+// chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each, and the whole call
+// takes 28 us (scan included).
+//
+// Matrix-core layout (16x16x4, wave64): A lane l holds row l % 16, k = l / 16; B lane l column l % 16, same k; D lane l
+// column l % 16, rows 4 (l / 16) + r.  Scores are taken transposed (keys x query rows): a lane owns one query row, and
+// register r of a score tile is the B operand of a P V step whose k-th key is 4 k + r.  The contraction over channels runs
+// in the order that lets every operand be a 16-byte load of a row (step e of group s: channel 16 s + 4 (l / 16) + e), and
+// output tile e of a channel group covers the channels VW m + e, so that a lane loads and stores VW consecutive ones.
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace da {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned short u16x4;
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+constexpr int kWavesG = 8;       // waves of a work group, one block of keys each in turn
+constexpr int kKeys = 32;        // keys per block: two score tiles
 
 template <typename T>
 struct KArgs {
@@ -18,146 +39,232 @@ struct KArgs {
     const T *__restrict__ V;
     const T *__restrict__ Khat;
     T *__restrict__ O;
-    const EntryChunk *__restrict__ ents;
-    const uint32_t *__restrict__ counts;
-    int Hq, Hkv, n, W, rebase, sliding;
-    int q_off, nq;   // query rows are positions q_off .. q_off + nq - 1 of the n keys
+    int Hq, Hkv, n, W, sliding;
     float scale_log2;
 };
 
-template <typename T, int D>
-__global__ __launch_bounds__(64) void prefill_generic_kernel(KArgs<T> a) {
-    extern __shared__ __attribute__((aligned(16))) float qt[];   // [D][64]: qt[c * 64 + lane] = q_row(lane)[c]
-    const int lane = threadIdx.x;
-    const int tiles = (a.nq + 63) / 64;
-    const int tile = tiles - 1 - (int)blockIdx.x;   // longest rows first
-    const int i_first = a.q_off + tile * 64;        // position of the tile's first row
-    const int h = blockIdx.y, b = blockIdx.z;
-    const int g = a.Hq / a.Hkv;
-    const int unit = b * a.Hkv + h / g;
+__device__ __forceinline__ f32x4 load4(const float *p) { return *(const f32x4 *)p; }
+__device__ __forceinline__ f32x4 load4(const bf16_t *p) {
+    const u16x4 v = *(const u16x4 *)p;
+    return f32x4{bf16_to_f32(v[0]), bf16_to_f32(v[1]), bf16_to_f32(v[2]), bf16_to_f32(v[3])};
+}
+__device__ __forceinline__ f32x2 load2(const float *p) { return *(const f32x2 *)p; }
+__device__ __forceinline__ f32x2 load2(const bf16_t *p) {
+    const u16x2 v = *(const u16x2 *)p;
+    return f32x2{bf16_to_f32(v[0]), bf16_to_f32(v[1])};
+}
+
+template <typename T, int D, int QT>
+__global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> a) {
+    constexpr int VW = D % 64 == 0 ? 4 : 2;      // channels a lane loads and stores at a time
+    constexpr int CG = D / (16 * VW);            // channel groups of the output
+    constexpr int KS = D / 16;                   // 16-channel groups of the contraction
+    constexpr int kRowsG = 16 * QT;
+    extern __shared__ __attribute__((aligned(16))) float lds_g[];
+    float *ml = lds_g;                           // [wave][kRowsG][2] running maximum, sum
+    float *obuf = lds_g + kWavesG * kRowsG * 2;  // [wave][kRowsG][D + 4] outputs before the merge
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, lg = lane >> 4;
     const int n = a.n, W = a.W;
-    const int i = i_first + lane;
-    const bool valid = i < n;
-    const T *Qp = a.Q + ((size_t)(b * a.Hq + h) * a.nq) * D;
+    const int tile = (int)gridDim.x - 1 - (int)blockIdx.x;       // longest rows first
+    const int i0 = tile * kRowsG, i_last = min(n - 1, i0 + kRowsG - 1);
+    const int h = blockIdx.y, b = blockIdx.z;
+    const int unit = b * a.Hkv + h / (a.Hq / a.Hkv);
+    const T *Qp = a.Q + (size_t)(b * a.Hq + h) * n * D;
     const T *Kp = a.K + (size_t)unit * n * D;
     const T *Vp = a.V + (size_t)unit * n * D;
     const T *Hp = a.Khat + (size_t)unit * n * D;
-    const EntryChunk *Ep = a.ents + (size_t)unit * n * (D / kGroup);
-    const uint32_t *Cp = a.counts + (size_t)unit * n;
 
-    for (int c = 0; c < D; ++c) qt[c * 64 + lane] = valid ? load_f32(Qp, (size_t)(i - a.q_off) * D + c) : 0.f;
-    __syncthreads();
-
-    const int i_last = min(n - 1, i_first + 63);            // last row of the tile
     // first exact column of row r: start of its square, or of its band (monotone in r either way)
     auto win_start = [&](int r) { return a.sliding ? max(r - W + 1, 0) : (r / W) * W; };
-    const int win_first = win_start(i_first);               // window start of the tile's first row
-    const int win_last = win_start(i_last);                 // window start of its last row
-    const int my_win = valid ? win_start(i) : 0;
-
-    float o[D];
+    const int win_first = win_start(i0), win_last = win_start(i_last);
+    int my_i[QT], my_win[QT];
+    f32x4 q[QT][KS];
 #pragma unroll
-    for (int c = 0; c < D; ++c) o[c] = 0.f;
-    float m = -INFINITY, l = 0.f;
-    // Eq. 4 running score of this row (unscaled).  A column's update is summed in binary32, the running score over
-    // the columns in binary64: one add per column, and its rounding then does not grow with the prompt length
-    // (in binary32 it reached 1e-4 of the output scale at ~1500 columns with fp32 inputs).
-    double r = 0.0;
-
-    constexpr int TB = 16;
-    for (int jb = 0; jb <= i_last; jb += TB) {
-        float s[TB];
+    for (int t = 0; t < QT; ++t) {
+        my_i[t] = i0 + 16 * t + l16;
+        const int i = min(my_i[t], n - 1);
+        my_win[t] = win_start(i);
 #pragma unroll
-        for (int jj = 0; jj < TB; ++jj) {
-            const int j = jb + jj;   // wave-uniform
-            float sc = -INFINITY;
-            if (j <= i_last) {
-                float approx = 0.f;
-                if (j < win_last) {   // some row of the tile has this column outside its window
-                    if (a.rebase) {
-                        const T *hj = Hp + (size_t)j * D;
-                        for (int c = 0; c < D; ++c) approx = fmaf(qt[c * 64 + lane], load_f32(hj, c), approx);
-                    } else {
-                        const uint32_t cnt = Cp[j];
-                        const EntryChunk *e = Ep + (size_t)j * (D / kGroup);
-                        float upd = 0.f;
-                        for (uint32_t k = 0; k < cnt; k += kGroup) {
-                            const EntryChunk ch = e[k / kGroup];
-#pragma unroll
-                            for (int u = 0; u < kGroup; ++u) upd = fmaf(qt[ch.chan[u] * 64 + lane], ch.delta[u], upd);
-                        }
-                        r += (double)upd;
-                        approx = (float)r;
-                    }
-                }
-                float exact = 0.f;
-                if (j >= win_first) {  // some row of the tile has this column inside its window
-                    const T *kj = Kp + (size_t)j * D;
-                    for (int c = 0; c < D; ++c) exact = fmaf(qt[c * 64 + lane], load_f32(kj, c), exact);
-                }
-                const float pick = (j >= my_win) ? exact : approx;
-                if (valid && j <= i) sc = pick * a.scale_log2;
-            }
-            s[jj] = sc;
-        }
-        float bm = s[0];
-#pragma unroll
-        for (int jj = 1; jj < TB; ++jj) bm = fmaxf(bm, s[jj]);
-        const float m_new = fmaxf(m, bm);
-        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = exp2f(m - m_use);
-        l *= alpha;
-#pragma unroll
-        for (int c = 0; c < D; ++c) o[c] *= alpha;
-#pragma unroll
-        for (int jj = 0; jj < TB; ++jj) {
-            const int j = jb + jj;
-            if (j <= i_last) {
-                const float p = exp2f(s[jj] - m_use);
-                l += p;
-                const T *vj = Vp + (size_t)j * D;
-#pragma unroll
-                for (int c = 0; c < D; ++c) o[c] = fmaf(p, load_f32(vj, c), o[c]);
-            }
-        }
-        m = m_new;
+        for (int s = 0; s < KS; ++s) q[t][s] = load4(Qp + (size_t)i * D + 16 * s + 4 * lg);
     }
-    if (valid) {
-        const float inv = 1.f / l;
-        T *Op = a.O + ((size_t)(b * a.Hq + h) * a.nq + (i - a.q_off)) * D;
+
+    f32x4 o[QT][CG][VW];
+    float m[QT], l[QT];
 #pragma unroll
-        for (int c = 0; c < D; ++c) store_from_f32(Op, c, o[c] * inv);
+    for (int t = 0; t < QT; ++t) {
+        m[t] = -INFINITY;
+        l[t] = 0.f;
+#pragma unroll
+        for (int g = 0; g < CG; ++g)
+#pragma unroll
+            for (int e = 0; e < VW; ++e) o[t][g][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    for (int jb = wave * kKeys; jb <= i_last; jb += kWavesG * kKeys) {
+        // scores of the block: X = K, or K_hat where every row has the block left of its window
+        f32x4 s[QT][2];
+        auto scores = [&](const T *X, f32x4 (&acc)[QT][2]) {
+            const T *x0 = X + (size_t)min(jb + l16, n - 1) * D + 4 * lg;
+            const T *x1 = X + (size_t)min(jb + 16 + l16, n - 1) * D + 4 * lg;
+#pragma unroll
+            for (int t = 0; t < QT; ++t) acc[t][0] = acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int g = 0; g < KS; ++g) {
+                const f32x4 k0 = load4(x0 + 16 * g), k1 = load4(x1 + 16 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int t = 0; t < QT; ++t) {
+                        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(k0[e], q[t][g][e], acc[t][0], 0, 0, 0);
+                        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k1[e], q[t][g][e], acc[t][1], 0, 0, 0);
+                    }
+            }
+        };
+        const bool far = jb + kKeys <= win_first;
+        scores(far ? Hp : Kp, s);
+        if (!far && jb < win_last) {             // some row has part of the block left of its window
+            f32x4 sh[QT][2];
+            scores(Hp, sh);
+#pragma unroll
+            for (int t = 0; t < QT; ++t)
+#pragma unroll
+                for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        s[t][kt][r] = jb + 16 * kt + 4 * lg + r >= my_win[t] ? s[t][kt][r] : sh[t][kt][r];
+        }
+#pragma unroll
+        for (int t = 0; t < QT; ++t) {
+            float bm = -INFINITY;
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool seen = jb + 16 * kt + 4 * lg + r <= my_i[t];
+                    s[t][kt][r] = seen ? s[t][kt][r] * a.scale_log2 : -INFINITY;
+                    bm = fmaxf(bm, s[t][kt][r]);
+                }
+            bm = fmaxf(bm, __shfl_xor(bm, 16));
+            bm = fmaxf(bm, __shfl_xor(bm, 32));
+            const float m_new = fmaxf(m[t], bm);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // (a row that sees nothing of this wave's keys yet)
+            const float alpha = exp2f(m[t] - m_use);
+            m[t] = m_new;
+            l[t] *= alpha;
+#pragma unroll
+            for (int g = 0; g < CG; ++g)
+#pragma unroll
+                for (int e = 0; e < VW; ++e) o[t][g][e] *= alpha;
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    s[t][kt][r] = exp2f(s[t][kt][r] - m_use);
+                    l[t] += s[t][kt][r];
+                }
+        }
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const T *v = Vp + (size_t)min(jb + 16 * kt + 4 * lg + r, n - 1) * D + VW * l16;   // (p is 0 past the row)
+#pragma unroll
+                for (int g = 0; g < CG; ++g) {
+                    float vv[VW];
+                    if constexpr (VW == 4) {
+                        const f32x4 x = load4(v + 64 * g);
+                        for (int e = 0; e < 4; ++e) vv[e] = x[e];
+                    } else {
+                        const f32x2 x = load2(v + 32 * g);
+                        for (int e = 0; e < 2; ++e) vv[e] = x[e];
+                    }
+#pragma unroll
+                    for (int e = 0; e < VW; ++e)
+#pragma unroll
+                        for (int t = 0; t < QT; ++t)
+                            o[t][g][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], s[t][kt][r], o[t][g][e], 0, 0, 0);
+                }
+            }
+    }
+
+    // the waves' partial results meet: row maxima and sums first, then the outputs at the common maximum
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+        l[t] += __shfl_xor(l[t], 16);
+        l[t] += __shfl_xor(l[t], 32);
+        if (lg == 0) {
+            ml[(wave * kRowsG + 16 * t + l16) * 2] = m[t];
+            ml[(wave * kRowsG + 16 * t + l16) * 2 + 1] = l[t];
+        }
+#pragma unroll
+        for (int g = 0; g < CG; ++g)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float *dst = obuf + (size_t)(wave * kRowsG + 16 * t + l16) * (D + 4) + 16 * VW * g + VW * (4 * lg + r);
+#pragma unroll
+                for (int e = 0; e < VW; ++e) dst[e] = o[t][g][e][r];
+            }
+    }
+    __syncthreads();
+    for (int idx = threadIdx.x; idx < kRowsG * (D / 4); idx += 64 * kWavesG) {
+        const int row = idx / (D / 4), c = (idx % (D / 4)) * 4;
+        if (i0 + row >= n) continue;
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < kWavesG; ++w) M = fmaxf(M, ml[(w * kRowsG + row) * 2]);   // wave 0 has key 0: M is finite
+        float L = 0.f;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWavesG; ++w) {
+            const float f = exp2f(ml[(w * kRowsG + row) * 2] - M);
+            L = fmaf(f, ml[(w * kRowsG + row) * 2 + 1], L);
+            acc += f * *(const f32x4 *)(obuf + (size_t)(w * kRowsG + row) * (D + 4) + c);
+        }
+        const float inv = 1.f / L;
+        T *dst = a.O + ((size_t)(b * a.Hq + h) * n + i0 + row) * D + c;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) store_from_f32(dst, e, acc[e] * inv);
     }
 }
 
+template <typename T, int D, int QT>
+void launch_tiles(const PrefillArgs &p, const KArgs<T> &a, hipStream_t s) {
+    constexpr size_t lds = (size_t)kWavesG * 16 * QT * (D + 6) * sizeof(float);
+    static std::atomic<uint64_t> lds_set;   // per instantiation, one bit per device
+    ensure_dynamic_lds((const void *)prefill_generic_kernel<T, D, QT>, (int)lds, lds_set);
+    dim3 grid((p.n + 16 * QT - 1) / (16 * QT), p.Hq, p.B), block(64 * kWavesG);
+    hipLaunchKernelGGL((prefill_generic_kernel<T, D, QT>), grid, block, lds, s, a);
+}
+
 template <typename T, int D>
-static void launch_one(const PrefillArgs &p, hipStream_t s) {
+void launch_one(const PrefillArgs &p, hipStream_t s) {
     KArgs<T> a;
     a.Q = (const T *)p.Q;
     a.K = (const T *)p.K;
     a.V = (const T *)p.V;
     a.Khat = (const T *)p.Khat;
     a.O = (T *)p.O;
-    a.ents = (const EntryChunk *)p.ents;
-    a.counts = p.counts;
     a.Hq = p.Hq;
     a.Hkv = p.Hkv;
     a.n = p.n;
-    a.q_off = p.q_off;
-    a.nq = p.nq;
     a.W = p.W;
     a.sliding = p.sliding;
-    a.rebase = p.rebase;
     a.scale_log2 = p.scale_log2;
-    const size_t lds = (size_t)D * 64 * sizeof(float);
-    static std::atomic<uint64_t> lds_set;   // per instantiation, one bit per device
-    ensure_dynamic_lds((const void *)prefill_generic_kernel<T, D>, (int)lds, lds_set);
-    dim3 grid((p.nq + 63) / 64, p.Hq, p.B), block(64);
-    hipLaunchKernelGGL((prefill_generic_kernel<T, D>), grid, block, lds, s, a);
+    // 32 rows per work group halve the reads of K and V per row; they pay once 16-row work groups would outnumber
+    // the compute units anyway (their merge needs LDS that a larger head_dim does not leave)
+    if constexpr (D <= 128) {
+        if ((int64_t)((p.n + 15) / 16) * p.Hq * p.B > 2 * device_cu_count()) {
+            launch_tiles<T, D, 2>(p, a, s);
+            return;
+        }
+    }
+    launch_tiles<T, D, 1>(p, a, s);
 }
 
 template <typename T>
-static bool launch_by_dim(const PrefillArgs &p, hipStream_t s) {
+bool launch_by_dim(const PrefillArgs &p, hipStream_t s) {
     switch (p.d) {
         case 32: launch_one<T, 32>(p, s); return true;
         case 64: launch_one<T, 64>(p, s); return true;
@@ -170,6 +277,8 @@ static bool launch_by_dim(const PrefillArgs &p, hipStream_t s) {
         default: return false;
     }
 }
+
+}  // namespace
 
 bool launch_prefill_generic(const PrefillArgs &p, hipStream_t s) {
     return p.dtype == 0 ? launch_by_dim<float>(p, s) : launch_by_dim<bf16_t>(p, s);

@@ -1,5 +1,5 @@
-// Device code of the delta matrix construction (Sec. II-C Eq. 2-3; Sec. III-A strategy 3) and of the compaction of
-// surviving entries per key column, shared by the stand-alone kernels and by the fused short-prompt prefill kernel.
+// Device code of the delta matrix construction (Sec. II-C Eq. 2-3; Sec. III-A strategy 3), shared by the stand-alone
+// kernels and by the fused short-prompt prefill kernel.
 #pragma once
 #include "common.hpp"
 
@@ -94,88 +94,6 @@ __device__ __forceinline__ float scan_rows(const T *__restrict__ Kp, T *__restri
     }
     if (kFinal) *count = cnt;
     return held;
-}
-
-// Compaction of one key column j of a unit by one wave: ballot + prefix count turn the mask row into a dense list of
-// (channel, delta) pairs in EntryChunk form (see emit_entries_kernel).
-// In two steps, so that a wave can have the next column's inputs in flight while it works on this one (a column is
-// a short chain of dependent memory round trips; one column at a time is latency bound):
-//   load_column    every input of the column: the lane's mask word, key and previous reference key of each 64-channel
-//                  pass (all loads unconditional, indices clamped into the arrays)
-//   finish_column  the compaction proper
-// K0, H0, M0: row 0 of the unit's keys, reference keys and mask words (global memory or an LDS copy);
-// ents0, counts0, nch0: the unit's first entry chunk, count and chunk-count slot (global).
-constexpr int kMaxPass = 4;                                   // 64-channel passes of a column: head_dim <= 256
-struct ColumnIn {
-    float k[kMaxPass], held[kMaxPass];
-    uint32_t word[kMaxPass];
-};
-
-template <typename T>
-__device__ __forceinline__ void load_column(ColumnIn &in, const T *K0, const T *H0, const uint32_t *M0, int n, int d,
-                                            int lane, int j) {
-    const size_t row = (size_t)min(j, n - 1);                 // columns past the end are never finished
-    const T *Kp = K0 + row * d;
-    const T *Hprev = H0 + (row - (row > 0 ? 1 : 0)) * d;
-    const uint32_t *Mp = M0 + row * (d >> 5);
-#pragma unroll
-    for (int p = 0; p < kMaxPass; ++p) {
-        const int c = min(p * kWave + lane, d - 1);
-        in.word[p] = Mp[c >> 5];
-        in.k[p] = load_f32(Kp, c);
-        in.held[p] = load_f32(Hprev, c);
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ void finish_column(const ColumnIn &in, EntryChunk *__restrict__ ents0,
-                                              uint32_t *__restrict__ counts0, int n, int d, int lane, int j) {
-    if (j >= n) return;
-    const size_t row = (size_t)j;
-    EntryChunk *out = ents0 + row * (d / kGroup);
-    uint32_t off = 0;
-#pragma unroll
-    for (int p = 0; p < kMaxPass; ++p) {
-        if (p * kWave >= d) break;
-        const int c = p * kWave + lane;
-        const bool act = c < d;
-        bool bit = false;
-        float delta = 0.f;
-        if (act) {
-            bit = (in.word[p] >> (c & 31)) & 1u;
-            const float k = in.k[p];
-            const float held = (j == 0) ? 0.f : in.held[p];
-            delta = k - held;                                  // (row 0: the basis, delta = k)
-        }
-        const uint64_t b = __ballot(bit);
-        if (bit) {
-            const uint32_t slot = off + lanes_below(b);
-            out[slot / kGroup].chan[slot % kGroup] = (uint32_t)c;
-            out[slot / kGroup].delta[slot % kGroup] = delta;
-        }
-        off += __popcll(b);
-    }
-    uint32_t padded = (off + kGroup - 1) & ~(uint32_t)(kGroup - 1);
-    if (padded == 0) padded = kGroup;
-    if (off + lane < padded) {
-        const uint32_t slot = off + lane;
-        out[slot / kGroup].chan[slot % kGroup] = 0u;
-        out[slot / kGroup].delta[slot % kGroup] = 0.f;
-    }
-    if (lane == 0) counts0[row] = off;
-}
-
-template <typename T>
-__device__ __forceinline__ void emit_columns(const T *K0, const T *H0, const uint32_t *M0, EntryChunk *__restrict__ ents0,
-                                             uint32_t *__restrict__ counts0, int n, int d, int lane, int first, int step, int end) {
-    if (first >= end) return;
-    ColumnIn cur, nxt;
-    load_column(cur, K0, H0, M0, n, d, lane, first);
-    for (int j = first; j < end; j += step) {
-        load_column(nxt, K0, H0, M0, n, d, lane, j + step);   // clamped to the last row; unused after the last column
-        finish_column<T>(cur, ents0, counts0, n, d, lane, j);
-        cur = nxt;
-    }
 }
 
 }  // namespace da
