@@ -19,7 +19,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline size_t elt_size(int dtype) { return dtype == DA_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t khat, chunk_out, scan_total, vt, total;
+    size_t khat, scan, scan_total, vt, total;
 };
 
 // what prefill_mfma_supported reads, for a prefill of p's rows behind `cached` rows
@@ -57,8 +57,8 @@ WsLayout layout(const da_prefill_params *p) {
     size_t off = 0;
     w.khat = off;
     off += align_up(rows * p->head_dim * elt_size(p->dtype));
-    w.chunk_out = off;
-    off += align_up(2 * units * (size_t)delta_scan_num_chunks(p->seq_len) * p->head_dim * elt_size(p->dtype));
+    w.scan = off;
+    off += align_up(delta_scan_scratch_bytes(p->dtype, (int)units, p->seq_len, p->head_dim));
     w.scan_total = off;
     // Room that no kernel uses: the size a caller asked for has always covered 8 bytes per key element and 4 per row
     // here, and plans that were sized with it stay comparable.
@@ -162,7 +162,7 @@ da_status delta_attn_delta_scan(const da_prefill_params *p, const void *K, uint3
     hipStream_t s = (hipStream_t)hip_stream;
     char *ws = (char *)workspace;
     (void)hipGetLastError();
-    launch_delta_scan(p->dtype, K, k_hat ? k_hat : ws + w.khat, mask_bits, ws + w.chunk_out, nnz,
+    launch_delta_scan(p->dtype, K, k_hat ? k_hat : ws + w.khat, mask_bits, ws + w.scan, nnz,
                       p->batch * p->n_kv_heads, p->seq_len, p->head_dim, p->theta, s);
     return launch_ok("delta_scan") ? DA_OK : DA_ERR_HIP;
 }
@@ -223,13 +223,10 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     // Short prompts on the matrix-core kernel: one launch does everything (the scan and the V
     // re-order run inside the attention launch, once per work group); longer ones take a launch per stage.
     const bool fused = prefill_mfma_supported(a) && (int64_t)p->seq_len * p->head_dim <= kFusedMaxElems;
-    // (the scan's first launch takes the V re-order of the matrix-core kernels along where it can)
-    const bool vt_in_scan = !fused && prefill_mfma_supported(a) && delta_scan_takes_v(p->dtype, p->seq_len, p->head_dim);
     if (!fused) {
         stage_begin(kStageScan, s);
-        launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.chunk_out, nnz, units, p->seq_len, p->head_dim,
-                          p->theta, s, nullptr, vt_in_scan ? V : nullptr, vt_in_scan ? ws + w.vt : nullptr,
-                          prefill_mfma_n_pad(p->seq_len));
+        launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, nnz, units, p->seq_len, p->head_dim,
+                          p->theta, s);
         stage_end(kStageScan, s);
         if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     }
@@ -253,7 +250,7 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.V = V;
     a.Khat = khat;
     a.O = O;
-    a.vt_from = vt_in_scan ? prefill_mfma_n_pad(p->seq_len) / 32 : 0;   // (every block of V is in place already)
+    a.vt_from = 0;
     stage_begin(kStageAttn, s);
     bool launched = true;
     if (prefill_mfma_supported(a))
@@ -275,7 +272,7 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
 // workspace of delta_attn_prefill_append: what the scan of the new rows needs (the whole-sequence arrays live in the
 // cache, see da_prefix)
 struct AppendLayout {
-    size_t hnew, chunk_out, total;
+    size_t hnew, scan, total;
 };
 
 AppendLayout append_layout(const da_prefill_params *p) {
@@ -285,8 +282,8 @@ AppendLayout append_layout(const da_prefill_params *p) {
     size_t off = 0;
     w.hnew = off;
     off += align_up(units * m * d * es);
-    w.chunk_out = off;
-    off += align_up(2 * units * (size_t)delta_scan_num_chunks((int)m) * d * es);
+    w.scan = off;
+    off += align_up(delta_scan_scratch_bytes(p->dtype, (int)units, (int)m, (int)d));
     w.total = off;
     return w;
 }
@@ -370,7 +367,7 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis);
     //    the new rows (keys, values, reference keys, mask rows) go behind the cached ones
     stage_begin(kStageScan, s);
-    launch_delta_scan(p->dtype, K, ws + w.hnew, mask_bits, ws + w.chunk_out, nnz, units, m, d, p->theta, s,
+    launch_delta_scan(p->dtype, K, ws + w.hnew, mask_bits, ws + w.scan, nnz, units, m, d, p->theta, s,
                       t0 > 0 ? cache->khat : nullptr);
     launch_append_rows(K, V, ws + w.hnew, mask_bits, f->k, f->v, f->h, f->m, units, t0, m, ld, d, s);
     stage_end(kStageScan, s);

@@ -28,6 +28,10 @@ __device__ __forceinline__ float load_f32(const bf16_t *p, size_t i) { return bf
 __device__ __forceinline__ void store_from_f32(float *p, size_t i, float v) { p[i] = v; }
 __device__ __forceinline__ void store_from_f32(bf16_t *p, size_t i, float v) { p[i] = f32_to_bf16(v); }
 
+// v is a value of T's grid: its bits as they stand
+__device__ __forceinline__ void store_exact(float *p, size_t i, float v) { p[i] = v; }
+__device__ __forceinline__ void store_exact(bf16_t *p, size_t i, float v) { p[i] = (bf16_t)(__float_as_uint(v) >> 16); }
+
 // number of set bits of a 64-bit wave mask below this lane
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));

@@ -1,13 +1,13 @@
 // Delta matrix construction on the key matrix (Sec. II-C Eq. 2-3; Sec. III-A strategy 3).
 #include "common.hpp"
 #include "kernels.hpp"
-#include "scan_device.hpp"
-#include "vt_device.hpp"
 
 #include <stdarg.h>
 #include <stdio.h>
 
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 namespace da {
 
@@ -102,162 +102,341 @@ int timing_collect(double *ms_per_stage, int *calls_per_stage) {
     return n;
 }
 
-// The recurrence of Eq. 2-3 is sequential in t and is not an associative scan, but it forgets its
-// past every time a channel fires: from then on the held value is k(t) whatever it was before.
-// So time is cut into chunks that are scanned in parallel from a guessed incoming state:
+// The recurrence of Eq. 2-3 is sequential in t and is not an associative scan, but it forgets its past every time a
+// channel fires: from then on the held value is k(t) whatever it was before.  So time is cut into pieces that are walked in
+// parallel from a guessed incoming state, and pieces whose guess was wrong are walked again from the right one:
 //
-//   pass 1  (one wave per (unit, 64 channels, time chunk)): chunk 0 starts from the basis row (or, when the
-//           rows continue a sequence, from the reference key `init` carried over from it) and is exact.
-//           Chunk c > 0 starts from the guess "held = k(t0 - 1)" and records only its final held value.  That final value is already the true one for every channel that fired at
-//           least once inside the chunk at a row where the true chain fired too - nearly all.
-//   pass 2  same scan, but chunk c starts from pass 1's final value of chunk c - 1, and writes mask
-//           words, held keys, nnz and its own final values.
-//   pass 3  (one wave per (unit, 64 channels), chunks in order): carries the true held value along.
-//           Where it equals the value pass 2 started a chunk from, pass 2's results for the chunk
-//           are the true ones and nothing is touched; otherwise the chunk's rows are re-run from the
-//           true state until it meets pass 2's chain (both hold the same value), correcting mask
-//           words, held keys and nnz on the way.  Exact for any input.
+//   scan_segments_kernel  one work group per (unit, segment of S rows, group of channels); lane = channel, and the waves of
+//       64 channels cut the segment into runs of rows.  The segment's rows and up to `warm` rows before it are copied to LDS
+//       once (16-byte loads, every one in flight together: row by row from global memory the walk paid a memory round
+//       trip per batch of rows).  Every run first walks the rows before it from the guess "held = an earlier row", then its
+//       own rows, replacing each key in LDS by its reference key.  Runs then compare the value they started from with
+//       the value the run before ended on and walk again, in parallel, until all agree: after round i the first i + 1 runs
+//       are exact, and a run usually meets its old chain (both fire at the same row) after a few rows, so a round or
+//       two does it.  Reference keys leave LDS in 16-byte pieces.
+//   scan_settle_kernel    prompts of several segments: one work group per unit and 64 channels does the same between
+//       segments - compares every segment's start with its predecessor's end and walks what differs again - and adds
+//       up nnz.
 //
-// One lane per channel; the wave ballot of the threshold decision is the mask word itself.
-template <typename T, bool kFinal>
-__global__ __launch_bounds__(64) void delta_scan_chunks_kernel(const T *__restrict__ K, T *__restrict__ Khat,
-                                                               uint32_t *__restrict__ mask_bits,
-                                                               const T *__restrict__ guess_out,
-                                                               T *__restrict__ chunk_out,
-                                                               unsigned long long *__restrict__ nnz, int n, int d,
-                                                               int L, int nchunks, float theta,
-                                                               const T *__restrict__ init,
-                                                               const bf16_t *__restrict__ V = nullptr,
-                                                               bf16_t *__restrict__ Vt = nullptr, int n_pad = 0) {
-    const int unit = blockIdx.z, chunk = blockIdx.y;
-    const int lane = threadIdx.x;
-    // Work groups past the channel waves (the first pass has some when the launcher was given V) have nothing to do
-    // with the scan: each re-orders one block of 32 value rows - blocks (L / 32) chunk .. of the unit - for the
-    // matrix-core prefill kernels, which need that done before they start and would otherwise pay a launch of its own
-    // for it (in the first pass, so that what the later passes write is still in the caches when it is read again).
-    if ((int)blockIdx.x >= (d + kWave - 1) / kWave) {
-        const int blk = chunk * (L / kTB) + (int)blockIdx.x - (d + kWave - 1) / kWave;
-        if (kFinal || blk >= n_pad / kTB) return;
-        __shared__ bf16_t tile[kTB * (128 + 2)];
-        auto wave_sync = [] {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        };
-        if (d == 64)
-            transpose_v_block<64, kWave>(V + (size_t)unit * n * 64,
-                                         (u32x4 *)(Vt + (size_t)unit * 64 * n_pad) + (size_t)blk * (2 * 2 * 64), blk * kTB,
-                                         n, (bf16_t(*)[64 + 2]) tile, lane, wave_sync);
-        else
-            transpose_v_block<128, kWave>(V + (size_t)unit * n * 128,
-                                          (u32x4 *)(Vt + (size_t)unit * 128 * n_pad) + (size_t)blk * (2 * 4 * 64), blk * kTB,
-                                          n, (bf16_t(*)[128 + 2]) tile, lane, wave_sync);
-        return;
-    }
-    const int c = blockIdx.x * kWave + lane;
-    const bool active = c < d;
-    const T *Kp = K + (size_t)unit * n * d;
-    T *Hp = Khat + (size_t)unit * n * d;
-    uint32_t *Mp = mask_bits + (size_t)unit * n * (d >> 5);
-    const int t0 = chunk * L, t1 = min(n, t0 + L);
-    float start = 0.f;
-    if (chunk > 0 && active)
-        start = kFinal ? load_f32(guess_out, ((size_t)unit * nchunks + chunk - 1) * d + c)
-                       : load_f32(Kp, (size_t)(t0 - 1) * d + c);
-    unsigned long long cnt = 0;
-    const float held = scan_rows<T, kFinal>(Kp, Hp, Mp, d, c, lane, t0, t1, chunk == 0,
-                                            init ? init + (size_t)unit * d : nullptr, start, theta, &cnt);
-    if (active) store_from_f32(chunk_out, ((size_t)unit * nchunks + chunk) * d + c, held);
-    if (kFinal && lane == 0) atomicAdd(nnz + unit, cnt);
-    // (the first pass, when there is one, also clears the unit's counter for the final pass that follows it in the
-    // stream; a single-chunk scan has no first pass and its launcher clears the counters itself)
-    if (!kFinal && lane == 0 && blockIdx.x == 0 && chunk == 0) nnz[unit] = 0ull;
+// Exact for any input.  The wave ballot of the threshold decision is the mask word itself.
+// 4 x 5 x 8192 rows of 128 (86 MB in and out, 5 % jumps): 62 -> 39 us, of which copying the rows through LDS takes 20; with
+// 1 % jumps and chains that meet late 1247 -> 239 us; 5 x 4096 rows: 31 -> 21 us a call.
+constexpr int kScanLdsMax = 144 * 1024;    // a one-segment prompt: 128 KB of rows, their mask words, the runs' end values
+
+// lane L of (lo, hi) takes the two halves of a wave mask: two instructions, where comparing the lane number and selecting
+// twice takes five.  (s_nop: a mask that a vector compare has just written may be read two wait states later, which the
+// compiler does not look after inside asm.)
+template <int L>
+__device__ __forceinline__ void mask_to_lane(uint32_t &lo, uint32_t &hi, uint64_t mask) {
+    asm("s_nop 1\n\tv_writelane_b32 %0, %2, %4\n\tv_writelane_b32 %1, %3, %4"
+        : "+v"(lo), "+v"(hi)
+        : "s"((uint32_t)mask), "s"((uint32_t)(mask >> 32)), "n"(L));
 }
 
-template <typename T>
-__global__ __launch_bounds__(64) void delta_scan_fixup_kernel(const T *__restrict__ K, T *__restrict__ Khat,
-                                                              uint32_t *__restrict__ mask_bits,
-                                                              const T *__restrict__ out1,   // pass 1 final values
-                                                              const T *__restrict__ out2,   // pass 2 final values
-                                                              unsigned long long *__restrict__ nnz, int n, int d,
-                                                              int L, int nchunks, float theta) {
-    const int unit = blockIdx.y;
-    const int lane = threadIdx.x;
-    const int c = blockIdx.x * kWave + lane;
-    const bool active = c < d;
-    const int cs = active ? c : 0;
-    const int wpr = d >> 5;
-    const T *Kp = K + (size_t)unit * n * d;
-    T *Hp = Khat + (size_t)unit * n * d;
-    uint32_t *Mp = mask_bits + (size_t)unit * n * wpr;
-    const bool writer = active && ((lane & 31) == 0);
-    const int word = c >> 5;
-    const T *o1 = out1 + (size_t)unit * nchunks * d + cs;
-    const T *o2 = out2 + (size_t)unit * nchunks * d + cs;
+constexpr int U = 16;      // rows in a batch
 
-    float held = load_f32(o2, 0);   // chunk 0 is exact
-    long long adjust = 0;
-    constexpr int G = 4;            // chunks whose boundary values are fetched together
-    for (int cb = 1; cb < nchunks; cb += G) {
-        float g1[G], g2[G];
+// f(0), f(1), ... f(U - 1) with the index a constant
+template <typename F, int... I>
+__device__ __forceinline__ void for_batch_impl(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <typename F>
+__device__ __forceinline__ void for_batch(F f) {
+    for_batch_impl(f, std::make_integer_sequence<int, U>{});
+}
+
+// rows a .. b - 1 (LDS, this lane's channel, row stride d elements) in order: batch(t, k) for U rows from t on, then
+// single(t, k) for each of the rest.  Batches of U rows, the
+// next one's LDS reads issued before this one is worked on; keys are kept as stored until then (a conversion at the
+// read would wait for it), and a batch past the end re-reads the last U rows, so that no read hangs on a condition.
+template <typename T, typename Batch, typename Single>
+__device__ __forceinline__ void each_row(const T *rows, int d, int a, int b, Batch batch, Single single) {
+    auto fetch = [&](T (&k)[U], int t) {
+        const T *r = rows + min(t, b - U) * d;
 #pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int ch = min(cb + u, nchunks - 1);
-            g1[u] = load_f32(o1, (size_t)(ch - 1) * d);   // the value pass 2 started chunk ch from
-            g2[u] = load_f32(o2, (size_t)ch * d);         // the value pass 2 ended chunk ch with
-        }
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-            const int chunk = cb + u;
-            if (chunk < nchunks) {
-                float spec = g1[u];
-                bool synced = !active || (__float_as_uint(held) == __float_as_uint(spec));
-                if (__any(!synced)) {
-                    // Re-run the chunk's rows until every channel has met pass 2's chain.  The rows are fetched 16 at
-                    // a time, the next batch requested before this one is worked on (indices clamped to the chunk):
-                    // one row at a time the loop paid a full memory round trip per row.
-                    const int t1 = min(n, chunk * L + L);
-                    constexpr int U = 16;
-                    auto load_batch = [&](float (&k)[U], int tb) {
-#pragma unroll
-                        for (int r = 0; r < U; ++r) k[r] = load_f32(Kp, (size_t)min(tb + r, t1 - 1) * d + cs);
-                    };
-                    auto work_batch = [&](const float (&kk)[U], int tb) -> bool {   // true: nothing left to do
-#pragma unroll
-                        for (int r = 0; r < U; ++r) {
-                            const int t = tb + r;
-                            if (t >= t1 || !__any(!synced)) return true;
-                            const float k = kk[r];
-                            const bool fs = fabsf(k - spec) > theta;
-                            const bool ft = fabsf(k - held) > theta;
-                            spec = fs ? k : spec;
-                            if (!synced) {
-                                held = ft ? k : held;
-                                store_from_f32(Hp, (size_t)t * d + c, held);
-                            }
-                            const uint64_t bt = __ballot(synced ? fs : ft);
-                            const uint64_t bs = __ballot(fs);
-                            if (writer) Mp[(size_t)t * wpr + word] = (uint32_t)(bt >> (lane & 32));
-                            adjust += (long long)__popcll(bt) - (long long)__popcll(bs);
-                            synced = synced || (__float_as_uint(held) == __float_as_uint(spec));
-                        }
-                        return false;
-                    };
-                    float ka[U], kb[U];
-                    load_batch(ka, chunk * L);
-                    for (int tb = chunk * L; tb < t1; tb += 2 * U) {
-                        load_batch(kb, tb + U);
-                        if (work_batch(ka, tb)) break;
-                        load_batch(ka, tb + 2 * U);
-                        if (work_batch(kb, tb + U)) break;
-                    }
-                }
-                // a synced channel ends the chunk where pass 2's chain ended; an unsynced one walked all of it
-                held = synced ? g2[u] : held;
-            }
+        for (int u = 0; u < U; ++u) k[u] = r[u * d];
+    };
+    int t = a;
+    if (t + U <= b) {
+        T ka[U], kb[U];
+        fetch(ka, t);
+        while (true) {
+            fetch(kb, t + U);
+            batch(t, ka);
+            t += U;
+            if (t + U > b) break;
+            fetch(ka, t + U);
+            batch(t, kb);
+            t += U;
+            if (t + U > b) break;
         }
     }
-    if (lane == 0 && adjust != 0) atomicAdd(nnz + unit, (unsigned long long)adjust);
+    for (; t < b; ++t) single(t, rows[t * d]);
+}
+
+// the value held after rows a .. b - 1, from `held`; nothing is written
+template <typename T>
+__device__ __forceinline__ float walk(const T *rows, int d, int a, int b, float held, float theta) {
+    auto step = [&](T raw) {
+        const float k = to_f32(raw);
+        held = fabsf(k - held) > theta ? k : held;
+    };
+    each_row(
+        rows, d, a, b,
+        [&](int, const T (&k)[U]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) step(k[u]);
+        },
+        [&](int, T k) { step(k); });
+    return held;
+}
+
+// Walks rows t0 .. t1 - 1 again, from `held` instead of `spec` (where the recorded chain started), until the two chains meet
+// in every lane (one that has met its old chain writes what stands there already).  Kp: the keys, Hp: the reference keys
+// (this lane's channel, row strides d and dh elements), Mp: the two mask words of the wave's channels (row stride dm; `two`:
+// both exist).  Returns the value the rows end on (`end` is the recorded one); *adjust receives the change of the number of
+// fired entries.
+template <typename T>
+__device__ __forceinline__ float rewalk(const T *Kp, int d, T *Hp, int dh, uint32_t *Mp, int dm, bool two, int t0, int t1,
+                                        float spec, float held, float end, bool active, float theta, long long *adjust) {
+    const int lane = threadIdx.x & 63;
+    bool synced = !active || __float_as_uint(spec) == __float_as_uint(held);
+    auto fetch = [&](T (&k)[U], int tb) {                        // rows past the end are clamped and not worked on
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = Kp[(size_t)min(tb + u, t1 - 1) * d];
+    };
+    auto work = [&](const T (&kk)[U], int tb) {
+        uint32_t wlo = 0, whi = 0;
+        T *h = Hp + (size_t)tb * dh;
+        for_batch([&](auto u) {
+            const bool here = active && tb + u < t1;
+            const float k = to_f32(kk[u]);
+            const bool fs = here && fabsf(k - spec) > theta, ft = here && fabsf(k - held) > theta;
+            spec = fs ? k : spec;
+            held = ft ? k : held;
+            const uint64_t bt = __ballot(ft);
+            mask_to_lane<u>(wlo, whi, bt);
+            *adjust += (long long)__popcll(bt) - (long long)__popcll(__ballot(fs));
+            if (here) store_exact(h, (size_t)u * dh, held);
+        });
+        synced = synced || __float_as_uint(spec) == __float_as_uint(held);   // (chains that have met stay together)
+        if (lane < U && tb + lane < t1) {
+            uint32_t *m = Mp + (size_t)(tb + lane) * dm;
+            m[0] = wlo;
+            if (two) m[1] = whi;
+        }
+        return tb + U < t1 && __any(!synced);
+    };
+    T ka[U], kb[U];
+    fetch(ka, t0);
+    for (int tb = t0;; tb += 2 * U) {
+        fetch(kb, tb + U);
+        if (!work(ka, tb)) break;
+        fetch(ka, tb + 2 * U);
+        if (!work(kb, tb + U)) break;
+    }
+    return synced ? end : held;
+}
+
+// What a scan launch looks like.  `dl` channels per work group (all of them, or 64), `waves` waves.
+struct ScanPlan {
+    int S, nseg, warm;      // rows per segment, segments, rows walked before a segment
+    int dl, waves;
+    size_t lds;             // dynamic LDS bytes of scan_segments_kernel
+};
+
+template <typename T>
+struct ScanArgs {
+    const T *__restrict__ K;
+    T *__restrict__ Khat;
+    uint32_t *__restrict__ mask_bits;
+    T *starts, *ends;                    // [units][nseg][d] value every segment started from / ended on
+    uint32_t *counts;                    // [units][nseg][groups of 64 channels] fired entries
+    unsigned long long *nnz;
+    const T *init;
+    int n, d, S, nseg, warm, dl;
+    float theta;
+};
+
+template <typename T, int DL>   // channels per work group where known when compiling (LDS offsets become immediates), or 0
+__global__ __launch_bounds__(512) void scan_segments_kernel(ScanArgs<T> g) {
+    extern __shared__ __attribute__((aligned(16))) char lds_s[];
+    const int seg = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x, lane = tid & 63, threads = blockDim.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = g.n, d = g.d, ch0 = blockIdx.z * g.dl;
+    const int dl = DL ? DL : min(g.dl, d - ch0);                 // this work group's channels
+    const int wpr = d >> 5, wl = dl >> 5, CW = (dl + kWave - 1) / kWave, TW = (threads >> 6) / CW;
+    const int t0 = seg * g.S, t1 = min(n, t0 + g.S), lo = max(0, t0 - g.warm), rows = t1 - lo;
+    const float theta = g.theta;
+    T *R = (T *)lds_s;                                           // [rows][dl]: keys, then reference keys from row t0 on
+    uint32_t *M = (uint32_t *)(R + rows * dl);                   // [t1 - t0][wl] mask words
+    float *E = (float *)(M + (t1 - t0) * wl);                    // [TW][dl] value every run ended on
+    uint32_t *cnt = (uint32_t *)(E + TW * dl);                   // fired entries
+    const T *Kp = g.K + (size_t)unit * n * d + ch0;
+    const int ppr = dl * (int)sizeof(T) / 16, gpr = d * (int)sizeof(T) / 16;   // 16-byte pieces per row here / in memory
+    // 1. the rows into LDS
+    {
+        const uint4 *src = (const uint4 *)(Kp + (size_t)lo * d);
+        uint4 *dst = (uint4 *)R;
+        const int pieces = rows * ppr;
+        constexpr int kIn = 8;
+        for (int i0 = tid; i0 < pieces; i0 += kIn * threads) {
+            // (pieces past the end are the last one again, loaded and stored: under a condition the compiler would
+            // pull each load down to its store and wait for it there)
+            uint4 v[kIn];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) {
+                const int i = min(i0 + k * threads, pieces - 1);
+                v[k] = src[(size_t)(i / ppr) * gpr + i % ppr];
+            }
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) dst[min(i0 + k * threads, pieces - 1)] = v[k];
+        }
+        if (tid == 0) *cnt = 0;
+        if (g.nseg > 1 && seg == 0 && blockIdx.z == 0 && tid == 0) g.nnz[unit] = 0;   // (scan_settle_kernel adds to it)
+    }
+    __syncthreads();
+    // 2. this wave's run of rows a .. b - 1 (LDS rows) and the guess it starts from
+    const int run = wave / CW, c = (wave % CW) * kWave + lane;
+    constexpr bool kFull = DL > 0;                               // every wave has a run of 64 channels
+    const bool works = kFull || run < TW, active = kFull || (works && c < dl);
+    const int cs = kFull ? c : min(c, dl - 1), word = (wave % CW) * 2;
+    const int L = (t1 - t0 + TW - 1) / TW;
+    const int a = works ? min(t0 + run * L, t1) - lo : 0, b = works ? min(t0 + (run + 1) * L, t1) - lo : 0;
+    T *Rc = R + cs;
+    float start = 0.f;
+    if (a < b) {
+        // a run after the first warms up on half the rows: what it gets wrong is put right inside the work group
+        const int w = max(0, a - (run == 0 ? g.warm : g.warm / 2));
+        if (w == 0 && lo == 0 && g.init)
+            start = walk(Rc, dl, 0, a, load_f32(g.init, (size_t)unit * d + ch0 + cs), theta);
+        else if (a > 0)
+            start = walk(Rc, dl, w + 1, a, load_f32(Rc, (size_t)(w * dl)), theta);   // (row 0: the basis row, exact)
+    }
+    const bool basis = a == 0 && lo == 0 && !g.init;             // the run's first row is kept whole
+    __syncthreads();                                             // nobody needs the keys of another run any more
+    // 3. the run itself
+    float held = start;
+    uint32_t fired = 0;
+    auto row = [&](int t, T raw, bool first) -> uint64_t {       // returns the row's mask
+        const float k = to_f32(raw);
+        const bool fire = (kFull || active) && (first || fabsf(k - held) > theta);   // Eq. 2 in binary32
+        held = fire ? k : held;                                                      // Eq. 3
+        const uint64_t bal = __ballot(fire);
+        fired += __popcll(bal);
+        if (active) store_exact(Rc, (size_t)(t * dl), held);
+        return bal;
+    };
+    auto put_mask = [&](int t, uint32_t wlo, uint32_t whi) {
+        uint32_t *m = M + (lo + t - t0) * wl + word;
+        m[0] = wlo;
+        if (word + 1 < wl) m[1] = whi;
+    };
+    auto single = [&](int t, T raw, bool first) {
+        const uint64_t bal = row(t, raw, first);
+        if (lane == 0) put_mask(t, (uint32_t)bal, (uint32_t)(bal >> 32));
+    };
+    int from = a;
+    if (basis && a < b) single(from++, Rc[0], true);
+    each_row(
+        Rc, dl, from, b,
+        [&](int t, const T (&k)[U]) {
+            uint32_t wlo = 0, whi = 0;                           // lane u keeps the mask of row t + u
+            for_batch([&](auto u) { mask_to_lane<u>(wlo, whi, row(t + u, k[u], false)); });
+            if (lane < U) put_mask(t + lane, wlo, whi);
+        },
+        [&](int t, T k) { single(t, k, false); });
+    if (active) E[run * dl + c] = held;
+    __syncthreads();
+    // 4. runs whose guess was wrong, again
+    long long adjust = 0;
+    for (int round = 1; round < TW; ++round) {
+        float prev = start;
+        const bool follows = active && run > 0 && a < b;
+        if (follows) prev = E[(run - 1) * dl + c];
+        const bool wrong = follows && __float_as_uint(prev) != __float_as_uint(start);
+        if (!__syncthreads_or(wrong)) break;                     // (also: every run has read its predecessor's end)
+        if (__any(wrong)) {
+            held = rewalk(Kp + (size_t)lo * d + cs, d, Rc, dl, M + (lo - t0) * wl + word, wl, word + 1 < wl, a, b, start, prev,
+                          held, active, theta, &adjust);
+            start = prev;
+            if (active) E[run * dl + c] = held;
+        }
+        __syncthreads();
+    }
+    if (lane == 0 && a < b) atomicAdd(cnt, (uint32_t)((long long)fired + adjust));
+    // 5. out: reference keys, mask words, the segment's boundary values, nnz
+    if (g.nseg > 1 && active) {
+        const size_t at = ((size_t)unit * g.nseg + seg) * d + ch0 + c;
+        if (run == 0) store_exact(g.starts, at, start);
+        if (run == (t1 - t0 - 1) / L) store_exact(g.ends, at, held);     // the run that holds the segment's last row
+    }
+    __syncthreads();
+    {
+        uint4 *dst = (uint4 *)(g.Khat + ((size_t)unit * n + t0) * d + ch0);
+        const uint4 *src = (const uint4 *)(R + (t0 - lo) * dl);
+        for (int i = tid; i < (t1 - t0) * ppr; i += threads) dst[(size_t)(i / ppr) * gpr + i % ppr] = src[i];
+        uint32_t *mo = g.mask_bits + ((size_t)unit * n + t0) * wpr + (ch0 >> 5);
+        for (int i = tid; i < (t1 - t0) * wl; i += threads) mo[(size_t)(i / wl) * wpr + i % wl] = M[i];
+    }
+    if (tid == 0) {
+        if (g.nseg > 1)
+            g.counts[((size_t)unit * g.nseg + seg) * gridDim.z + blockIdx.z] = *cnt;
+        else
+            g.nnz[unit] = *cnt;
+    }
+}
+
+constexpr int kSettleWaves = 16;
+
+template <typename T>
+__global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_kernel(ScanArgs<T> g) {
+    __shared__ unsigned long long total;
+    const int group = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = g.n, d = g.d, nseg = g.nseg, wpr = d >> 5;
+    const int c = group * kWave + lane, cs = min(c, d - 1), word = group * 2;
+    const bool active = c < d;
+    const T *Kp = g.K + (size_t)unit * n * d + cs;
+    T *Hp = g.Khat + (size_t)unit * n * d + cs;
+    uint32_t *Mp = g.mask_bits + (size_t)unit * n * wpr + word;
+    T *sp = g.starts + (size_t)unit * nseg * d + cs, *ep = g.ends + (size_t)unit * nseg * d + cs;
+    if (tid == 0) total = 0;
+    unsigned long long sum = 0;
+    for (int s = tid; s < nseg; s += 64 * kSettleWaves) sum += g.counts[((size_t)unit * nseg + s) * gridDim.x + group];
+    long long adjust = 0;
+    for (int round = 0; round < nseg; ++round) {
+        bool again = false;
+        constexpr int G = 4;                                     // segments whose boundary values are fetched together
+        for (int sb = 1 + wave; sb < nseg; sb += G * kSettleWaves) {
+            float st[G], pe[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const size_t s = min(sb + u * kSettleWaves, nseg - 1);
+                st[u] = load_f32(sp, s * d);
+                pe[u] = load_f32(ep, (s - 1) * d);
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const int s = sb + u * kSettleWaves;
+                const bool wrong = s < nseg && active && __float_as_uint(st[u]) != __float_as_uint(pe[u]);
+                if (!__any(wrong)) continue;
+                again = true;
+                const float end = load_f32(ep, (size_t)s * d);
+                const float e = rewalk(Kp, d, Hp, d, Mp, wpr, word + 1 < wpr, s * g.S, min(n, s * g.S + g.S), st[u], pe[u],
+                                       end, active, g.theta, &adjust);
+                if (active) {
+                    store_exact(sp, (size_t)s * d, pe[u]);
+                    store_exact(ep, (size_t)s * d, e);
+                }
+            }
+        }
+        if (!__syncthreads_or(again)) break;
+    }
+    if (lane == 0) sum += (unsigned long long)adjust;
+    if (sum) atomicAdd(&total, sum);
+    __syncthreads();
+    if (tid == 0) atomicAdd(g.nnz + unit, total);
 }
 
 __global__ void fill_u64_kernel(unsigned long long *p, unsigned long long v, int n) {
@@ -321,45 +500,56 @@ void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s) {
                        (unsigned long long)v, n);
 }
 
-int delta_scan_chunk_len(int n) { return n >= 1024 ? 128 : 64; }
-int delta_scan_num_chunks(int n) { return (n + delta_scan_chunk_len(n) - 1) / delta_scan_chunk_len(n); }
+// A prompt whose rows fit into LDS is one segment: one work group of 8 waves per unit, one launch.  Longer ones are cut into
+// segments of 128 rows, 64 channels and 4 waves per work group: with the 128 rows before them 35 KB of LDS (bf16), so that
+// four work groups share a compute unit and cover each other's load, walk and store - or of 256 rows, which halves the rows
+// walked twice, where that still leaves every compute unit three work groups.
+static ScanPlan scan_plan(int dtype, int units, int n, int d) {
+    const int es = dtype == 0 ? 4 : 2;
+    ScanPlan p;
+    const bool one = (int64_t)n * d * es <= 128 * 1024;
+    p.warm = 128;
+    p.S = one ? n : (int64_t)units * ((d + 63) / 64) * (n / 256) >= 3 * device_cu_count() ? 256 : 128;
+    p.nseg = (n + p.S - 1) / p.S;
+    p.dl = one ? d : 64;
+    p.waves = one ? 8 : 4;
+    const int dl = p.dl < d ? p.dl : d, TW = p.waves / ((dl + kWave - 1) / kWave);
+    const size_t rows = one ? n : p.S + p.warm;
+    p.lds = rows * dl * es + (size_t)p.S * (dl / 32) * 4 + (size_t)TW * dl * 4 + 16;
+    return p;
+}
+
+size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d) {
+    const ScanPlan p = scan_plan(dtype, units, n, d);
+    const size_t segs = (size_t)units * p.nseg;
+    return p.nseg == 1 ? 0 : 2 * segs * d * (dtype == 0 ? 4 : 2) + segs * ((d + 63) / 64) * 4;
+}
 
 template <typename T>
-static void scan_typed(const void *K, void *Khat, uint32_t *mask_bits, void *chunk_out, uint64_t *nnz, int units,
-                       int n, int d, float theta, const void *init, hipStream_t s, const void *V, void *Vt, int n_pad) {
-    const int L = delta_scan_chunk_len(n), nchunks = delta_scan_num_chunks(n);
-    const int cw = (d + kWave - 1) / kWave;
-    T *out1 = (T *)chunk_out;
-    T *out2 = out1 + (size_t)units * nchunks * d;
-    if (nchunks > 1)
-        hipLaunchKernelGGL((delta_scan_chunks_kernel<T, false>), dim3(cw + (V ? L / kTB : 0), nchunks, units),
-                           dim3(kWave), 0, s, (const T *)K, (T *)Khat, mask_bits, (const T *)nullptr, out1,
-                           (unsigned long long *)nnz, n, d, L, nchunks, theta, (const T *)init, (const bf16_t *)V,
-                           (bf16_t *)Vt, n_pad);
-    hipLaunchKernelGGL((delta_scan_chunks_kernel<T, true>), dim3(cw, nchunks, units), dim3(kWave), 0, s,
-                       (const T *)K, (T *)Khat, mask_bits, (const T *)out1, out2, (unsigned long long *)nnz, n, d, L,
-                       nchunks, theta, (const T *)init);
-    if (nchunks > 1)
-        hipLaunchKernelGGL(delta_scan_fixup_kernel<T>, dim3(cw, units), dim3(kWave), 0, s, (const T *)K, (T *)Khat,
-                           mask_bits, (const T *)out1, (const T *)out2, (unsigned long long *)nnz, n, d, L, nchunks,
-                           theta);
+static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz,
+                       int units, int n, int d, float theta, const void *init, hipStream_t s) {
+    const size_t segs = (size_t)units * p.nseg;
+    T *starts = (T *)scratch;
+    const ScanArgs<T> a = {(const T *)K, (T *)Khat, mask_bits, starts, starts + segs * d, (uint32_t *)(starts + 2 * segs * d),
+                           (unsigned long long *)nnz, (const T *)init, n, d, p.S, p.nseg, p.warm, p.dl, theta};
+    const int groups = (d + p.dl - 1) / p.dl;
+    const int which = p.dl == 128 ? 2 : p.dl == 64 && d % 64 == 0 ? 1 : 0;
+    const auto kernel = which == 2 ? scan_segments_kernel<T, 128> : which == 1 ? scan_segments_kernel<T, 64> : scan_segments_kernel<T, 0>;
+    static std::atomic<uint64_t> lds_set[3];                     // per instantiation, one bit per device
+    ensure_dynamic_lds((const void *)kernel, kScanLdsMax, lds_set[which]);
+    hipLaunchKernelGGL(kernel, dim3(p.nseg, units, groups), dim3(64 * p.waves), p.lds, s, a);
+    if (p.nseg > 1)
+        hipLaunchKernelGGL(scan_settle_kernel<T>, dim3((d + 63) / 64, units), dim3(64 * kSettleWaves), 0, s, a);
 }
 
-// Khat [units][n][d] and chunk_out [2][units][delta_scan_num_chunks(n)][d] are required scratch/outputs.
-// init: NULL (row 0 is the basis row) or [units][d], the reference key the rows continue from.
-bool delta_scan_takes_v(int dtype, int n, int d) {
-    return dtype == 1 && (d == 64 || d == 128) && delta_scan_num_chunks(n) > 1;
-}
-
-void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *chunk_out, uint64_t *nnz,
-                       int units, int n, int d, float theta, hipStream_t s, const void *init, const void *V, void *Vt,
-                       int n_pad) {
-    if (delta_scan_num_chunks(n) <= 1) launch_fill_u64(nnz, 0, units, s);   // (else the first pass clears them)
-    if (!V || !Vt || !delta_scan_takes_v(dtype, n, d)) V = nullptr;
+// Khat [units][n][d] and scratch (delta_scan_scratch_bytes) are required scratch/outputs.
+void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz, int units,
+                       int n, int d, float theta, hipStream_t s, const void *init) {
+    const ScanPlan p = scan_plan(dtype, units, n, d);
     if (dtype == 0)
-        scan_typed<float>(K, Khat, mask_bits, chunk_out, nnz, units, n, d, theta, init, s, nullptr, nullptr, 0);
+        scan_typed<float>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, s);
     else
-        scan_typed<bf16_t>(K, Khat, mask_bits, chunk_out, nnz, units, n, d, theta, init, s, V, Vt, n_pad);
+        scan_typed<bf16_t>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, s);
 }
 
 }  // namespace da

@@ -56,14 +56,11 @@ void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s);
 // row t0 of the whole-sequence arrays [units][ld][...].
 void launch_append_rows(const void *K, const void *V, const void *H, const uint32_t *M, void *Kfull, void *Vfull,
                         void *Hfull, uint32_t *Mfull, int units, int t0, int m, int ld, int d, hipStream_t s);
-int delta_scan_num_chunks(int n);
-// V, Vt (both or neither; used only where delta_scan_takes_v() says so): the value rows [units][n][d] are re-ordered
-// into Vt [units][d][n_pad], the operand order of the matrix-core prefill kernels, by extra work groups of the scan's
-// first launch (they have nothing to do with the scan; it saves the prefill a launch).
-bool delta_scan_takes_v(int dtype, int n, int d);
-void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *chunk_out, uint64_t *nnz,
-                       int units, int n, int d, float theta, hipStream_t s, const void *init = nullptr,
-                       const void *V = nullptr, void *Vt = nullptr, int n_pad = 0);
+// scratch: delta_scan_scratch_bytes(); init: NULL (row 0 is the basis row), or [units][d], the reference key the rows
+// continue from
+size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d);
+void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz, int units,
+                       int n, int d, float theta, hipStream_t s, const void *init = nullptr);
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
 // no instantiation.  q_off, ld and the fused launch are not for it.
 bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);

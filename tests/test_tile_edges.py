@@ -28,3 +28,42 @@ def _walks(seed, B, Hq, Hkv, n, d, dtype):
 def test_binary32_products_kernel(window_mode, dtype, d, n, W, B, Hq):
     Q, K, V = _walks(301, B, Hq, 1, n, d, dtype)
     run_case(Q, K, V, 0.1 if dtype == "f32" else 0.2, W, dtype, da.DA_SCORE_GATHER, window_mode=window_mode)
+
+
+@pytest.mark.parametrize("dtype,d,sizes", [
+    ("bf16", 64, (1, 7, 8, 9, 1023, 1024, 1025, 1280)), ("bf16", 128, (5, 511, 512, 513, 640, 641)),
+    ("bf16", 32, (2048, 2049)), ("bf16", 96, (682, 683, 897)), ("bf16", 256, (256, 257, 321)), ("f32", 32, (1024, 1025)),
+    ("f32", 64, (512, 513, 769)), ("f32", 128, (255, 256, 257, 321)), ("f32", 160, (205, 300)), ("f32", 256, (128, 129, 193)),
+])
+def test_scan_segments(dtype, d, sizes):
+    """One segment or several, ragged last ones, runs of a few rows or none: bursty and slow keys, so that some guesses of
+    the time-parallel walk hold and some do not."""
+    import torch
+    import dense_form as df
+    from paper_2507_19608_amd import workloads as wl
+    from util import to_dev
+    for n in sizes:
+        rng = np.random.default_rng(n)
+        K = rand_walk(n + d, 2, 2, n, d, dtype, 0.02)
+        jump = rng.random((2, 2, n, 1)) < np.array([0.05, 0.002])[None, :, None, None]
+        K = wl.round_to_dtype(np.where(jump, rng.standard_normal((2, 2, n, d)), K), dtype)
+        Kd = to_dev(K, dtype)
+        for theta in (0.0, 0.07, 5.0):
+            bits, nnz, khat = da.delta_attn_delta_scan(Kd, theta, want_khat=True)
+            ref_khat, ref_mask = df.reference_keys(Kd, theta)
+            assert (df.unpack_bits(bits, d) == ref_mask).all(), (n, theta)
+            assert (nnz == ref_mask.sum(dim=(2, 3))).all(), (n, theta)
+            assert (khat.double() == ref_khat).all(), (n, theta)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("units", [64, 1100])
+def test_scan_of_many_short_rows(units):
+    """The 256-row segments that only launches of many units take, and the same rows in 128-row ones."""
+    import dense_form as df
+    from util import to_dev
+    Kd = to_dev(rand_walk(17, units, 1, 1100, 64, "bf16", 0.03), "bf16")
+    bits, nnz, khat = da.delta_attn_delta_scan(Kd, 0.1, want_khat=True)
+    ref_khat, ref_mask = df.reference_keys(Kd, 0.1)
+    assert (df.unpack_bits(bits, 64) == ref_mask).all() and (nnz == ref_mask.sum(dim=(2, 3))).all()
+    assert (khat.double() == ref_khat).all()
