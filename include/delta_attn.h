@@ -166,8 +166,8 @@ da_status delta_attn_prefill_noalloc(const da_prefill_params *p, const void *Q, 
  *             at most 32 query heads per KV head; otherwise DA_ERR_UNSUPPORTED
  *   workspace device scratch of at least delta_attn_prefill_append_workspace_bytes(p, cache) (0 if the arguments
  *             are invalid), 256-byte aligned
- * The cache keeps the sequence so far as the plain arrays the prefill kernels read (keys, reference keys, values in
- * two orders, mask rows), with max_seq rows of room: about 8 * head_dim + 4 * head_dim / 32 bytes per (KV head, row).
+ * The cache keeps the sequence so far as the plain arrays the prefill kernels read (keys, reference keys, values,
+ * mask rows), with max_seq rows of room: about 6 * head_dim + 4 * head_dim / 32 bytes per (KV head, row).
  * The first call on a cache allocates them (hipMalloc + hipMemset, released by delta_attn_cache_destroy; DA_ERR_HIP if that fails; make that call outside graph capture); a call that follows
  * another such call, or delta_attn_cache_reset, then only adds its own rows.  After decode steps or a one-shot
  * delta_attn_prefill into the cache the arrays are rebuilt from the cache by the next call, at a cost proportional to

@@ -19,7 +19,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline size_t elt_size(int dtype) { return dtype == DA_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t khat, scan, scan_total, vt, total;
+    size_t khat, scan, scan_total, total;
 };
 
 // what prefill_mfma_supported reads, for a prefill of p's rows behind `cached` rows
@@ -63,8 +63,6 @@ WsLayout layout(const da_prefill_params *p) {
     // Room that no kernel uses: the size a caller asked for has always covered 8 bytes per key element and 4 per row
     // here, and plans that were sized with it stay comparable.
     off += align_up(rows * p->head_dim * 8) + align_up(rows * sizeof(uint32_t));
-    w.vt = off;
-    off += align_up(units * (size_t)p->head_dim * prefill_mfma_n_pad(p->seq_len) * 2);
     w.total = off;
     return w;
 }
@@ -195,9 +193,8 @@ da_status delta_attn_prefill_noalloc(const da_prefill_params *p, const void *Q, 
     }
     void *ws = scratch_of_current_device();
     if (!ws) return DA_ERR_HIP;
-    // Nothing in the buffer has to start at zero: every region is written by the scan and re-order
-    // kernels before the attention kernel reads it (the nnz counters, which do, are the caller's and are cleared by
-    // a fill kernel on the stream).
+    // Nothing in the buffer has to start at zero: every region is written by the scan before the attention
+    // kernel reads it.
     return prefill_checked(p, w, Q, K, V, O, mask_bits, nnz, nullptr, ws, (hipStream_t)hip_stream);
 }
 
@@ -220,26 +217,10 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.Hkv = p->n_kv_heads;
     a.Hq = p->n_q_heads;
     a.n = p->seq_len;
-    // Short prompts on the matrix-core kernel: one launch does everything (the scan and the V
-    // re-order run inside the attention launch, once per work group); longer ones take a launch per stage.
-    const bool fused = prefill_mfma_supported(a) && (int64_t)p->seq_len * p->head_dim <= kFusedMaxElems;
-    if (!fused) {
-        stage_begin(kStageScan, s);
-        launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, nnz, units, p->seq_len, p->head_dim,
-                          p->theta, s);
-        stage_end(kStageScan, s);
-        if (!launch_ok("delta_scan")) return DA_ERR_HIP;
-    }
-    a.fused = fused ? 1 : 0;
-    a.mask_bits = mask_bits;
-    a.nnz = nnz;
-    a.theta = p->theta;
-    a.dtype = p->dtype;
-    a.B = p->batch;
-    a.Hq = p->n_q_heads;
-    a.Hkv = p->n_kv_heads;
-    a.d = p->head_dim;
-    a.n = p->seq_len;
+    stage_begin(kStageScan, s);
+    launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, nnz, units, p->seq_len, p->head_dim, p->theta, s);
+    stage_end(kStageScan, s);
+    if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     a.q_off = 0;
     a.nq = p->seq_len;
     a.W = p->window;
@@ -250,11 +231,10 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.V = V;
     a.Khat = khat;
     a.O = O;
-    a.vt_from = 0;
     stage_begin(kStageAttn, s);
     bool launched = true;
     if (prefill_mfma_supported(a))
-        launch_prefill_mfma(a, ws + w.vt, s);
+        launch_prefill_mfma(a, s);
     else
         launched = launch_prefill_generic(a, s);
     stage_end(kStageAttn, s);
@@ -297,7 +277,7 @@ da_status ensure_prefix(da_cache *c) {
         memset(c->pf, 0, sizeof(*c->pf));
     }
     da_prefix *f = c->pf;
-    const size_t units = (size_t)c->B * c->Hkv, d = c->d, ld = c->max_seq, ld_pad = prefill_mfma_n_pad(c->max_seq);
+    const size_t units = (size_t)c->B * c->Hkv, d = c->d, ld = c->max_seq;
     bool ok = true;
     auto room = [&](void **ptr, size_t bytes) {
         if (!ok || *ptr) return;
@@ -307,7 +287,6 @@ da_status ensure_prefix(da_cache *c) {
     room(&f->h, units * ld * d * 2);
     room(&f->v, units * ld * d * 2);
     room((void **)&f->m, units * ld * (d / 32) * 4);
-    room(&f->vt, units * d * ld_pad * 2);
     if (!ok) {
         (void)launch_ok("prefill_append: room for the cached sequence as plain arrays");   // records the error text
         return DA_ERR_HIP;
@@ -383,7 +362,6 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     a.q_off = t0;
     a.nq = m;
     a.ld = ld;
-    a.vt_from = kept ? t0 / 32 : 0;
     a.W = p->window;
     a.scale_log2 = score_scale(p->scale, d) * 1.4426950408889634f;
     a.sliding = p->window_mode == DA_WINDOW_SLIDING;
@@ -392,12 +370,8 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     a.V = f->v;
     a.Khat = f->h;
     a.O = O;
-    a.fused = 0;
-    a.mask_bits = nullptr;
-    a.nnz = nullptr;
-    a.theta = p->theta;
     stage_begin(kStageAttn, s);
-    launch_prefill_mfma(a, f->vt, s);                  // (supported: check_append has asked)
+    launch_prefill_mfma(a, s);                         // (supported: check_append has asked)
     stage_end(kStageAttn, s);
     if (!launch_ok("prefill_append attention")) return DA_ERR_HIP;
     // 4. the new rows join the cache

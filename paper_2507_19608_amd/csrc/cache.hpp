@@ -11,14 +11,13 @@ constexpr int kChunk = 64;   // rows per decode chunk; one reference-key checkpo
 // What delta_attn_prefill_append keeps between its calls on one cache (Sec. III-C, a prompt processed in pieces):
 // the sequence so far as the plain arrays the prefill kernels read, so that a piece only adds its own rows instead
 // of unpacking the whole prefix again.  Device memory with max_seq rows of room per unit (row stride
-// max_seq, padded strides from prefill_mfma_n_pad(max_seq)), allocated by the first such call, freed with the
+// max_seq), allocated by the first such call, freed with the
 // cache.  Host-side bookkeeping: kernels never see it.
 struct da_prefix {
     void *k, *h, *v;      // [units][max_seq][d]     keys (raw where a window may need them, see expand_cache_kernel),
                           //                         reference keys, values
     uint32_t *m;          // [units][max_seq][d/32]  mask rows
-    void *vt;             // V in matrix-core operand order (transpose_v_kernel)
-    int64_t rows;         // k, h, v, m, vt describe rows 0 .. rows - 1 of the cached sequence; only trusted while
+    int64_t rows;         // k, h, v, m describe rows 0 .. rows - 1 of the cached sequence; only trusted while
                           // rows == the cache's length (decode steps and one-shot prefills do not maintain them)
 };
 

@@ -649,7 +649,7 @@ void free_all(da_cache *c) {
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (da_prefix *f = c->pf) {
-        void *more[] = {f->k, f->h, f->v, f->m, f->vt};
+        void *more[] = {f->k, f->h, f->v, f->m};
         for (void *p : more)
             if (p) (void)hipFree(p);
         delete f;

@@ -31,24 +31,12 @@ struct PrefillArgs {
     int dtype;            // 0 f32, 1 bf16
     int B, Hq, Hkv, d, n, W;   // n = number of key rows
     int q_off, nq;             // the query rows are positions q_off .. q_off + nq - 1 (q_off + nq == n)
-    int ld = 0;                // > 0 (matrix-core path only): K, V, Khat have ld >= n rows of room per unit and vt the
-                               // stride of prefill_mfma_n_pad(ld); 0: exactly n
-    int vt_from = 0;           // blocks of 32 rows below this one are already in vt (V re-order of earlier rows kept)
+    int ld = 0;                // > 0 (matrix-core path only): K, V, Khat have ld >= n rows of room per unit; 0: exactly n
     float scale_log2;     // score scale * log2(e)
     int sliding;          // 1: exact region is the band i - j < W instead of squares of side W
     const void *Q, *K, *V, *Khat;
     void *O;
-    // fused short-prompt launch (matrix-core kernel only): the attention launch itself runs the delta scan and
-    // the V re-order; then K_hat and vt are scratch it fills first
-    int fused;
-    uint32_t *mask_bits;  // out (fused)
-    uint64_t *nnz;        // out (fused)
-    float theta;          // (fused)
 };
-
-// the fused launch is used for prompts of at most this many key elements per unit (seq_len * head_dim): their keys,
-// reference keys and mask words fit in LDS side by side
-constexpr int kFusedMaxElems = 32768;
 
 void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s);
 
@@ -62,12 +50,11 @@ size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d);
 void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz, int units,
                        int n, int d, float theta, hipStream_t s, const void *init = nullptr);
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
-// no instantiation.  q_off, ld and the fused launch are not for it.
+// no instantiation.  q_off and ld are not for it.
 bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);
-// Matrix-core path: bf16, head_dim 64 or 128.  vt is scratch for V^T: units * d * prefill_mfma_n_pad(n) bf16.
+// Matrix-core path: bf16, head_dim 64 or 128, K and V aligned to 16 bytes.
 bool prefill_mfma_supported(const PrefillArgs &a);
-int prefill_mfma_n_pad(int n);
-void launch_prefill_mfma(const PrefillArgs &a, void *vt, hipStream_t s);
+void launch_prefill_mfma(const PrefillArgs &a, hipStream_t s);
 // compute units of the current device (256 if it cannot be asked)
 int device_cu_count();
 

@@ -67,3 +67,44 @@ def test_scan_of_many_short_rows(units):
     ref_khat, ref_mask = df.reference_keys(Kd, 0.1)
     assert (df.unpack_bits(bits, 64) == ref_mask).all() and (nnz == ref_mask.sum(dim=(2, 3))).all()
     assert (khat.double() == ref_khat).all()
+
+
+@pytest.mark.parametrize("window_mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
+@pytest.mark.parametrize("d,n,W,B,Hq,Hkv", [
+    (64, 31, 7, 1, 4, 1), (128, 32, 64, 1, 8, 2), (64, 33, 1, 1, 1, 1), (128, 63, 20, 2, 4, 1), (64, 65, 32, 1, 8, 1),
+    (128, 129, 33, 1, 2, 1), (64, 255, 100, 1, 2, 2), (128, 257, 64, 1, 1, 1), (64, 449, 63, 1, 4, 2), (128, 321, 320, 1, 12, 6),
+    (64, 1000, 1000, 1, 4, 1),         # one window over everything
+])
+def test_matrix_core_tiles(window_mode, d, n, W, B, Hq, Hkv):
+    """Blocks that lie left of some rows' windows and inside others', tiles that end in the middle, waves without rows,
+    turns for which one of the two groups has no block."""
+    Q, K, V = _walks(401, B, Hq, Hkv, n, d, "bf16")
+    run_case(Q, K, V, 0.2, W, "bf16", da.DA_SCORE_GATHER, window_mode=window_mode)
+
+
+@pytest.mark.parametrize("window_mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
+@pytest.mark.parametrize("d,B,Hq,Hkv,n,W", [(64, 33, 32, 8, 300, 50), (128, 16, 20, 5, 900, 128), (64, 70, 8, 8, 520, 26),
+                                            (128, 24, 16, 2, 777, 64)])
+def test_whole_tiles_of_large_launches(window_mode, d, B, Hq, Hkv, n, W):
+    """The 256-row tiles that only launches of many tiles take: every output against the closed form, masks too."""
+    import torch
+    import dense_form as df
+    from util import to_dev
+    Q, K, V = (to_dev(x, "bf16") for x in _walks(501, B, Hq, Hkv, n, d, "bf16"))
+    O, bits, nnz = da.delta_attn_prefill(Q, K, V, 0.2, W, window_mode=window_mode)
+    khat, mask = df.reference_keys(K, 0.2)
+    assert (df.unpack_bits(bits, d) == mask).all() and (nnz == mask.sum(dim=(2, 3))).all()
+    assert torch.isfinite(O).all()
+    assert df.prefill_worst_error(Q, K, V, khat, W, window_mode == da.DA_WINDOW_SLIDING, [O]) <= 2e-2
+
+
+def test_unaligned_keys_take_the_kernel_that_allows_them():
+    """K and V one element off 16-byte alignment: same results within rounding."""
+    import torch
+    from util import to_dev
+    Q, K, V = (to_dev(x, "bf16") for x in _walks(601, 1, 4, 1, 200, 64, "bf16"))
+    off = [torch.cat((x.new_zeros(1), x.flatten()))[1:].view(x.shape) for x in (K, V)]
+    assert off[0].data_ptr() % 16 == 2
+    a, b = da.delta_attn_prefill(Q, K, V, 0.2, 16), da.delta_attn_prefill(Q, off[0], off[1], 0.2, 16)
+    assert torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
+    assert (a[0].float() - b[0].float()).abs().max().item() <= 2e-2
