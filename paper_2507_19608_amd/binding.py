@@ -130,11 +130,23 @@ def _check(st: int, where: str):
         raise DeltaAttnError(st, where)
 
 
+_torch_mod = None
+_raw_stream = None
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("delta_attn needs a GPU: there is no CPU path")
-    return torch
+    """torch, once a GPU has been seen (asked anew as long as there is none)."""
+    global _torch_mod, _raw_stream
+    if _torch_mod is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("delta_attn needs a GPU: there is no CPU path")
+        # The current stream's handle without a Stream object around it (2.5 us a call, a quarter of a decode step's host
+        # time); torch's own compiled code asks in this way, and without it the public call does.
+        of, device = (getattr(torch._C, f, None) for f in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        _raw_stream = (lambda: of(device())) if of and device else lambda: torch.cuda.current_stream().cuda_stream
+        _torch_mod = torch
+    return _torch_mod
 
 
 def _dtype_code(t) -> int:
@@ -147,7 +159,8 @@ def _dtype_code(t) -> int:
 
 
 def _stream() -> int:
-    return _torch().cuda.current_stream().cuda_stream
+    _torch()
+    return _raw_stream()
 
 
 def _ptr(t) -> Optional[int]:
@@ -184,6 +197,7 @@ class Cache:
         self.handle = h
         self.shape = (batch, n_q_heads, n_kv_heads, head_dim, max_seq)
         self.dtype = dtype
+        self._row_shapes = (batch, n_q_heads, head_dim), (batch, n_kv_heads, head_dim)   # of a decode step's q, and k and v
 
     def __len__(self):
         return int(lib().delta_attn_cache_length(self.handle))
@@ -231,6 +245,20 @@ class Cache:
 _hip = None
 
 
+def _qkv_params(Q, K, V, window, theta, scale, score_mode, window_mode):
+    """The parameters of a prefill call, its tensors checked (shapes read once: they are half of the checks' time)."""
+    for t, name in ((Q, "Q"), (K, "K"), (V, "V")):
+        if not (t.is_cuda and t.is_contiguous()):
+            _dev(t, name)
+    shape, dtype = K.shape, K.dtype
+    B, Hq, n, d = Q.shape
+    if V.shape != shape or len(shape) != 4 or shape[0] != B or shape[2] != n or shape[3] != d or Q.dtype != dtype \
+            or V.dtype != dtype:
+        raise ValueError("Q/K/V shapes or dtypes disagree")
+    return PrefillParams(B, Hq, shape[1], d, n, int(window), float(theta), float(scale), _dtype_code(K), int(score_mode),
+                         int(window_mode))
+
+
 def _hip_copy(dst: int, src: int, nbytes: int):
     """Device-to-device copy through the HIP runtime (plumbing for the cache accessors)."""
     global _hip
@@ -264,17 +292,11 @@ def delta_attn_prefill(Q, K, V, theta: float, window: int, scale: float = 0.0, s
     """Returns (O, mask_bits int32 [B, Hkv, n, d/32], nnz int64 [B, Hkv]).  Buffers may be passed in
     (workspace: uint8 tensor, out: (O, mask_bits, nnz)) so a timing loop allocates nothing."""
     torch = _torch()
-    for t, name in ((Q, "Q"), (K, "K"), (V, "V")):
-        _dev(t, name)
-    if K.shape != V.shape or Q.shape[0] != K.shape[0] or Q.shape[2:] != K.shape[2:] or Q.dtype != K.dtype \
-            or K.dtype != V.dtype:
-        raise ValueError("Q/K/V shapes or dtypes disagree")
-    p = make_params(Q, K, window, theta, scale, score_mode, window_mode)
-    need = delta_attn_prefill_workspace_bytes(p)
+    p = _qkv_params(Q, K, V, window, theta, scale, score_mode, window_mode)
     if workspace is None:
-        workspace = torch.empty(max(need, 1), dtype=torch.uint8, device=Q.device)
-    B, Hkv, n, d = K.shape
+        workspace = torch.empty(max(delta_attn_prefill_workspace_bytes(p), 1), dtype=torch.uint8, device=Q.device)
     if out is None:
+        B, Hkv, n, d = K.shape
         O = torch.empty_like(Q)
         mask = torch.empty((B, Hkv, n, d // 32), dtype=torch.int32, device=Q.device)
         nnz = torch.empty((B, Hkv), dtype=torch.int64, device=Q.device)
@@ -294,12 +316,9 @@ def delta_attn_prefill_noalloc(Q, K, V, theta: float, window: int, out, scale: f
                                score_mode: int = DA_SCORE_GATHER, window_mode: int = DA_WINDOW_BLOCK):
     """delta_attn_prefill on the library's built-in scratch: the call allocates nothing, so `out` = (O, mask_bits int32
     [B, Hkv, n, d/32], nnz int64 [B, Hkv]) must be passed in.  Returns `out`."""
-    for t, name in ((Q, "Q"), (K, "K"), (V, "V")) + tuple(zip(out, ("O", "mask_bits", "nnz"))):
+    for t, name in zip(out, ("O", "mask_bits", "nnz")):
         _dev(t, name)
-    if K.shape != V.shape or Q.shape[0] != K.shape[0] or Q.shape[2:] != K.shape[2:] or Q.dtype != K.dtype \
-            or K.dtype != V.dtype:
-        raise ValueError("Q/K/V shapes or dtypes disagree")
-    p = make_params(Q, K, window, theta, scale, score_mode, window_mode)
+    p = _qkv_params(Q, K, V, window, theta, scale, score_mode, window_mode)
     O, mask, nnz = out
     st = lib().delta_attn_prefill_noalloc(ctypes.byref(p), Q.data_ptr(), K.data_ptr(), V.data_ptr(), O.data_ptr(),
                                           mask.data_ptr(), nnz.data_ptr(), _stream())
@@ -312,12 +331,7 @@ def delta_attn_prefill_append(cache: Cache, Q, K, V, theta: float, window: int, 
     """Chunked prefill: the rows of Q, K, V continue the sequence the cache holds.  Returns
     (O, mask_bits int32 [B, Hkv, m, d/32], nnz int64 [B, Hkv]) of the new rows; the cache is extended."""
     torch = _torch()
-    for t, name in ((Q, "Q"), (K, "K"), (V, "V")):
-        _dev(t, name)
-    if K.shape != V.shape or Q.shape[0] != K.shape[0] or Q.shape[2:] != K.shape[2:] or Q.dtype != K.dtype \
-            or K.dtype != V.dtype:
-        raise ValueError("Q/K/V shapes or dtypes disagree")
-    p = make_params(Q, K, window, theta, scale, score_mode, window_mode)
+    p = _qkv_params(Q, K, V, window, theta, scale, score_mode, window_mode)
     need = int(lib().delta_attn_prefill_append_workspace_bytes(ctypes.byref(p), cache.handle))
     if need == 0:
         # let the call itself say why
@@ -336,20 +350,24 @@ def delta_attn_prefill_append(cache: Cache, Q, K, V, theta: float, window: int, 
 
 def delta_attn_decode(cache: Cache, q_new, k_new, v_new, out=None, mask_row=None):
     """One decode step.  q_new [B, Hq, d], k_new/v_new [B, Hkv, d].  Returns (o, mask_row)."""
-    torch = _torch()
+    _torch()
     for t, name in ((q_new, "q_new"), (k_new, "k_new"), (v_new, "v_new")):
-        _dev(t, name)
-    B, Hq, Hkv, d, _ = cache.shape
-    if tuple(q_new.shape) != (B, Hq, d) or tuple(k_new.shape) != (B, Hkv, d) or tuple(v_new.shape) != (B, Hkv, d) \
-            or q_new.dtype != cache.dtype or k_new.dtype != cache.dtype or v_new.dtype != cache.dtype:
+        if not (t.is_cuda and t.is_contiguous()):
+            _dev(t, name)
+    q_shape, kv_shape = cache._row_shapes
+    dtype = cache.dtype
+    if q_new.shape != q_shape or k_new.shape != kv_shape or v_new.shape != kv_shape \
+            or q_new.dtype != dtype or k_new.dtype != dtype or v_new.dtype != dtype:
         raise ValueError("decode tensors do not match the cache")
     if out is None:
-        out = torch.empty_like(q_new)
+        out = _torch_mod.empty_like(q_new)
     if mask_row is None:
-        mask_row = torch.empty((B, Hkv, d // 32), dtype=torch.int32, device=q_new.device)
-    st = lib().delta_attn_decode(cache.handle, q_new.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), out.data_ptr(),
-                                 mask_row.data_ptr(), _stream())
-    _check(st, "delta_attn_decode")
+        B, _, Hkv, d, _ = cache.shape
+        mask_row = _torch_mod.empty((B, Hkv, d // 32), dtype=_torch_mod.int32, device=q_new.device)
+    st = _lib.delta_attn_decode(cache.handle, q_new.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), out.data_ptr(),
+                                mask_row.data_ptr(), _raw_stream())
+    if st != DA_OK:
+        _check(st, "delta_attn_decode")
     return out, mask_row
 
 
