@@ -343,15 +343,18 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     const bool kept = f->rows == t0;
     f->rows = -1;                                   // in flux until this call has gone through
     if (!kept) expand_cache_runs(cache, t0, ld, f->k, f->h, f->v, f->m, s);
-    // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis);
-    //    the new rows (keys, values, reference keys, mask rows) go behind the cached ones
+    // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis)
     stage_begin(kStageScan, s);
     launch_delta_scan(p->dtype, K, ws + w.hnew, mask_bits, ws + w.scan, nnz, units, m, d, p->theta, s,
                       t0 > 0 ? cache->khat : nullptr);
-    launch_append_rows(K, V, ws + w.hnew, mask_bits, f->k, f->v, f->h, f->m, units, t0, m, ld, d, s);
     stage_end(kStageScan, s);
     if (!launch_ok("delta_scan")) return DA_ERR_HIP;
-    // 3. attention of the new rows over all nk keys
+    // 3. the new rows join the plain arrays and the cache
+    stage_begin(kStageCacheFill, s);
+    cache_fill_runs(cache, t0, nk, K, V, ws + w.hnew, mask_bits, nnz, f, s);
+    stage_end(kStageCacheFill, s);
+    if (!launch_ok("cache_fill")) return DA_ERR_HIP;
+    // 4. attention of the new rows over all nk keys
     PrefillArgs a;
     a.dtype = p->dtype;
     a.B = p->batch;
@@ -374,11 +377,6 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     launch_prefill_mfma(a, s);                         // (supported: check_append has asked)
     stage_end(kStageAttn, s);
     if (!launch_ok("prefill_append attention")) return DA_ERR_HIP;
-    // 4. the new rows join the cache
-    stage_begin(kStageCacheFill, s);
-    cache_fill_runs(cache, t0, nk, ld, f->k, V, f->h, f->m, nnz, s);
-    stage_end(kStageCacheFill, s);
-    if (!launch_ok("cache_fill")) return DA_ERR_HIP;
     cache->len = nk;
     f->rows = nk;
     return DA_OK;

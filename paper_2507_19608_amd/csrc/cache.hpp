@@ -30,7 +30,7 @@ struct da_cache {
     int nck;              // checkpoints per unit: max_seq / kChunk + 1
     int max_chunks;       // (max_seq + kChunk - 1) / kChunk
     int vrows;            // max_seq rounded up to a whole chunk (row capacity of V)
-    int plan_merge;       // launch plan of the column-run layout: -1 auto, 0 second launch, 1 merge in the kernel
+    int plan_merge;       // launch plan of the column-run layout: -1 auto, 0 spread over work groups, 1 one per unit
     int plan_slots;       // wave slots a launch is sized for, 0 = from the device
     int fast;             // 1: bf16, head_dim 64 or 128, decode window >= kChunk or >= max_seq, <= 32 query heads per KV
                           //    head: the column-run layout below
@@ -42,12 +42,12 @@ struct da_cache {
     //   column-run layout (fast == 1): written once per chunk, when its last row has arrived ("sealed"):
     //     for every channel in ascending order one run = the reference value held when the chunk starts,
     //     then the channel's surviving values in row order.  Rows of an unsealed chunk are always inside
-    //     the decode window (window >= kChunk, or the whole cache), where raw keys are used, so they need no run.  At head_dim
-    //     128 the runs of channels 64.. start at the next multiple of 8 elements.
+    //     the decode window (window >= kChunk, or the whole cache), where raw keys are used, so they need no run.  Every
+    //     64 channels have their own part of the room, kRunHalfRoom elements, with their column masks and starts in front.
     void *surv;           // [units][max_chunks][run_room_stride(d)]
     uint32_t *ccnt;       // [units][max_chunks]      row layout: elements stored in the chunk's room; column-run
-                          //                          layout: that in the low half, the start of the runs of
-                          //                          channels 64.. (head_dim 64: the same number) in the high half
+                          //                          layout: those of channels 0..63 in the low half, those of
+                          //                          channels 64.. in the high half
     void *ck;             // [units][nck][d]          ck[m] = reference key after row m*kChunk - 1 (m >= 1)
     void *khat;           // [units][d]               current reference key
     void *ring;           // [units][Wd][d]           raw key of position p at slot p % Wd
@@ -56,12 +56,14 @@ struct da_cache {
                           //            accumulator order (slot 8 k + i holds row 8 (i / 4) + 4 k + i % 4)
     uint64_t *nnz;        // [units]
     float *part;          // [B*Hq][max_chunks][d + 4] partial (o[d], m, l, 2 unused) rows of one decode step
+    uint32_t *arrived;    // [units] work groups of a unit that have left their partial rows (column-run layout); 0 between steps
     da_prefix *pf;        // host pointer, NULL until delta_attn_prefill_append has run on this cache
 };
 
-// elements of room per chunk for the surviving values: one per key element, one carried-in value per channel, and
-// the alignment gap of the column-run layout
-__host__ __device__ inline size_t run_room_stride(int d) { return (size_t)(kChunk + 1) * d + 8; }
+// Elements of room per chunk for the surviving values: one per key element and one carried-in value per channel; in the
+// column-run layout also, per 64 channels, their column masks and where their runs start (768 bytes, see decode_runs.hip).
+constexpr int kRunHalfRoom = 384 + (kChunk + 1) * 64;
+__host__ __device__ inline size_t run_room_stride(int d) { return (size_t)((d + 63) / 64) * kRunHalfRoom; }
 
 // floats per partial row: o[d], running maximum, running sum, padded to a 16-byte multiple
 __host__ __device__ inline int part_stride(int d) { return d + 4; }
@@ -77,15 +79,14 @@ void cache_fill_from_prefill(da_cache *c, const da_prefill_params *p, const void
                              const void *Khat, const uint32_t *mask_bits,
                              const uint64_t *nnz, hipStream_t s);
 // column-run layout (fast == 1)
-// appends rows t0 .. n_k - 1 (t0 = rows already held) from whole-sequence arrays [units][ld][...] (ld >= n_k rows of
-// room per unit)
-void cache_fill_runs(da_cache *c, int t0, int n_k, int ld, const void *Kfull, const void *Vnew, const void *Hfull,
-                     const uint32_t *Mfull, const uint64_t *nnz_new, hipStream_t s);
+// appends rows t0 .. n_k - 1 (t0 = rows already held), given as arrays of these rows alone [units][n_k - t0][...]; with
+// `full` they also join its plain arrays, which hold the rows before t0 (needed where t0 > 0)
+void cache_fill_runs(da_cache *c, int t0, int n_k, const void *Knew, const void *Vnew, const void *Hnew, const uint32_t *Mnew,
+                     const uint64_t *nnz_new, const da_prefix *full, hipStream_t s);
 // writes the cached rows 0 .. t0 - 1 out as whole-sequence arrays with ld >= t0 rows of room per unit
 void expand_cache_runs(da_cache *c, int t0, int ld, void *Kfull, void *Hfull, void *Vfull, uint32_t *Mfull,
                        hipStream_t s);
-// returns the number of partial rows written per head, 0 if the launch wrote the output itself
-int decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, void *o, uint32_t *mask_row, int t,
+void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, void *o, uint32_t *mask_row, int t,
                      float scale_log2, hipStream_t s);
 void seal_chunk_runs(da_cache *c, int chunk, hipStream_t s);
 }  // namespace da

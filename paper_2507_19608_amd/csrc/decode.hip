@@ -594,13 +594,8 @@ void decode_launch(da_cache *c, const void *q, const void *k, const void *v, voi
     const int nchunks = t / kChunk + 1;
     if (c->fast) {
         stage_begin(kStageChunk, s);
-        const int nparts = da::decode_step_runs(c, q, k, v, o, mask_row, t, sc, s);
+        da::decode_step_runs(c, q, k, v, o, mask_row, t, sc, s);
         stage_end(kStageChunk, s);
-        if (nparts > 0) {
-            stage_begin(kStageCombine, s);
-            launch_combine<T>(c, (T *)o, nparts, s);
-            stage_end(kStageCombine, s);
-        }
         if ((t + 1) % kChunk == 0) da::seal_chunk_runs(c, t / kChunk, s);
         return;
     }
@@ -645,7 +640,7 @@ void decode_launch(da_cache *c, const void *q, const void *k, const void *v, voi
 }
 
 void free_all(da_cache *c) {
-    void *ptrs[] = {c->mask, c->surv, c->ccnt, c->ck, c->khat, c->ring, c->V, c->nnz, c->part};
+    void *ptrs[] = {c->mask, c->surv, c->ccnt, c->ck, c->khat, c->ring, c->V, c->nnz, c->part, c->arrived};
     for (void *p : ptrs)
         if (p) (void)hipFree(p);
     if (da_prefix *f = c->pf) {
@@ -674,7 +669,7 @@ void cache_fill_from_prefill(da_cache *c, const da_prefill_params *p, const void
                              const uint64_t *nnz, hipStream_t s) {
     const int units = c->B * c->Hkv, n = p->seq_len;
     if (c->fast) {
-        da::cache_fill_runs(c, 0, n, n, K, V, Khat, mask_bits, nnz, s);
+        da::cache_fill_runs(c, 0, n, K, V, Khat, mask_bits, nnz, nullptr, s);
         c->len = n;
         return;
     }
@@ -743,6 +738,8 @@ da_status delta_attn_cache_create(da_cache **out, int32_t batch, int32_t n_q_hea
     ok = ok && hipMalloc((void **)&c->nnz, units * 8) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->part, (size_t)batch * n_q_heads * c->max_chunks * part_stride(d) * 4) == hipSuccess;
     if (ok) ok = hipMemset(c->nnz, 0, units * 8) == hipSuccess;
+    ok = ok && hipMalloc((void **)&c->arrived, units * 4) == hipSuccess;
+    if (ok) ok = hipMemset(c->arrived, 0, units * 4) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         free_all(c);

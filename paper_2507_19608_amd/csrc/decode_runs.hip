@@ -4,6 +4,8 @@
 // row has arrived, while its rows are still inside the decode window.
 #include <math.h>
 
+#include <algorithm>
+
 #include "cache.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
@@ -18,6 +20,9 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(16))) int i32x16;
 
 // V cache, column-run layout: 16 rows per channel, [unit][t / 16][channel][16].  Inside a group of 16 the
 // slot of row p is 8 k + i with k = (p / 4) % 2 and i = 4 (p / 8) + p % 4: the order in which the 32x32
@@ -32,138 +37,187 @@ __device__ __forceinline__ bf16_t *run_room(const da_cache &c, int unit, int chu
     return (bf16_t *)c.surv + ((size_t)unit * c.max_chunks + chunk) * run_room_stride(c.d);
 }
 
-// The runs of channels 64.. (head_dim 128) start at a multiple of 8 elements, so that the decode step can copy
-// either half of a chunk's runs with 16-byte pieces.
-__device__ __forceinline__ uint32_t second_half_start(uint32_t first_half_elems) { return (first_half_elems + 7u) & ~7u; }
+// A sealed chunk's room holds, per 64 channels (kHalfRoom elements apart): the column masks (64 x 8 bytes: bit r = the
+// channel's mask bit of row r), where each channel's run starts (64 x 4 bytes: byte offset from the head), then the runs.
+constexpr int kHead = 256 + 128;                             // elements of masks and starts
+constexpr int kHalfRoom = kRunHalfRoom;
+static_assert(kHalfRoom == kHead + (kChunk + 1) * 64 && kHalfRoom % 8 == 0, "16-byte pieces");
 
-// Seals chunk `chunk` of one unit (one wave): for every channel the run {reference value held when the
-// chunk starts, surviving values in row order}, runs stored one after another in channel order.
-// Mp: the chunk's kChunk mask rows; rowp(r): raw key row r of the chunk; heldp(ch): reference value of
-// channel ch before the chunk's first row.  lane = channel (mod 64).
-template <typename RowFn, typename HeldFn>
-__device__ void seal_chunk(const da_cache &c, int unit, int chunk, int lane, const uint32_t *__restrict__ Mp,
-                           RowFn rowp, HeldFn heldp) {
-    const int d = c.d, wpr = d >> 5;
-    bf16_t *room = run_room(c, unit, chunk);
-    uint32_t base = 0, half = 0;
-    for (int c0 = 0; c0 < d; c0 += kWave) {
-        const int ch = c0 + lane;
-        // rows in batches of 16: all loads of a batch are issued before anything is stored, so that their latency
-        // is paid once per batch, not once per row
-        uint64_t cm = 0;
-        for (int rb = 0; rb < kChunk; rb += 16) {
-            uint32_t w[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) w[u] = Mp[(size_t)(rb + u) * wpr + (ch >> 5)];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) cm |= (uint64_t)((w[u] >> (ch & 31)) & 1u) << (rb + u);
-        }
-        uint32_t total;
-        uint32_t p = base + wave_exclusive_scan((uint32_t)__popcll(cm) + 1u, &total);
-        room[p++] = heldp(ch);
-        for (int rb = 0; rb < kChunk; rb += 16) {
-            bf16_t kv[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) kv[u] = rowp(rb + u)[ch];
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if ((cm >> (rb + u)) & 1ull) room[p++] = kv[u];
-        }
-        base += total;
-        if (c0 == 0) {
-            half = base;                                     // elements of channels 0..63
-            if (d > kWave) base = second_half_start(base);
-        }
+// Seals 64 channels of one chunk, by one wave (lane = channel): head and runs - for every channel in ascending order
+// {reference value held before the chunk, then its surviving values in row order}.  From the chunk's keys (row stride d) and
+// mask rows in LDS into LDS; returns the number of elements.
+__device__ __forceinline__ uint32_t build_runs(const bf16_t *keys, int d, const uint32_t *mask, int wpr, bf16_t held, bf16_t *room) {
+    const int lane = threadIdx.x & (kWave - 1);
+    uint32_t lo = 0, hi = 0;                                     // the channel's mask bits of rows 0..31, 32..63
+#pragma unroll 16
+    for (int r = 0; r < 32; ++r) {
+        lo |= ((mask[r * wpr + (lane >> 5)] >> (lane & 31)) & 1u) << r;
+        hi |= ((mask[(r + 32) * wpr + (lane >> 5)] >> (lane & 31)) & 1u) << r;
     }
-    // low half: elements in the room (the gap included); high half: where the runs of channels 64.. start
-    if (lane == 0) c.ccnt[(size_t)unit * c.max_chunks + chunk] = base | ((d > kWave ? second_half_start(half) : base) << 16);
+    uint32_t total;
+    uint32_t p = kHead + wave_exclusive_scan((uint32_t)__popc(lo) + (uint32_t)__popc(hi) + 1u, &total);
+    ((uint32_t *)room)[2 * lane] = lo;
+    ((uint32_t *)room)[2 * lane + 1] = hi;
+    ((uint32_t *)room)[128 + lane] = 2u * p;
+    room[p++] = held;
+    for (int rb = 0; rb < kChunk; rb += 16) {                    // 16 keys at a time: reads first
+        bf16_t kv[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) kv[u] = keys[(rb + u) * d + lane];
+        const uint32_t bits = (rb < 32 ? lo : hi) >> (rb & 31);
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if ((bits >> u) & 1u) room[p++] = kv[u];
+    }
+    return kHead + total;
+}
+
+// sealed channels in LDS [D / 64][kHalfRoom] -> the chunk's room, 16-byte pieces (the last one may carry a few elements nobody
+// reads)
+template <int D, int NT>
+__device__ __forceinline__ void store_runs(const da_cache &c, int unit, int chunk, const bf16_t *runs, const uint32_t *len) {
+    for (int h = 0; h < D / 64; ++h) {
+        u32x4 *dst = (u32x4 *)(run_room(c, unit, chunk) + h * kHalfRoom);
+        const u32x4 *src = (const u32x4 *)(runs + h * kHalfRoom);
+        for (int i = threadIdx.x; i < (int)(len[h] + 7) / 8; i += NT) dst[i] = src[i];
+    }
+    if (threadIdx.x == 0) c.ccnt[(size_t)unit * c.max_chunks + chunk] = len[0] | (D > 64 ? len[1] << 16 : 0u);
 }
 
 // Seal from the raw-key ring: runs right after the step that appended the chunk's last row.
-__global__ __launch_bounds__(64) void seal_from_ring_kernel(da_cache c, int chunk) {
-    const int unit = blockIdx.x, lane = threadIdx.x;
-    const int d = c.d, r0 = chunk * kChunk;
-    const uint32_t *Mp = c.mask + ((size_t)unit * c.max_seq + r0) * (d >> 5);
-    const bf16_t *ring = (const bf16_t *)c.ring + (size_t)unit * c.Wd * d;
-    const bf16_t *ckp = (const bf16_t *)c.ck + ((size_t)unit * c.nck + chunk) * d;
-    seal_chunk(
-        c, unit, chunk, lane, Mp, [&](int r) { return ring + (size_t)((r0 + r) % c.Wd) * d; },
-        [&](int ch) { return chunk > 0 ? ckp[ch] : (bf16_t)0; });
+template <int D>
+__global__ __launch_bounds__(256) void seal_from_ring_kernel(da_cache c, int chunk) {
+    constexpr int WPR = D / 32, P = D / 8;                       // mask words, 16-byte pieces per row
+    __shared__ __attribute__((aligned(16))) bf16_t keys[kChunk * D];
+    __shared__ __attribute__((aligned(16))) bf16_t runs[(D / 64) * kHalfRoom];
+    __shared__ uint32_t mask[kChunk * WPR], len[2];
+    const int unit = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, r0 = chunk * kChunk;
+    const u32x4 *ring = (const u32x4 *)c.ring + (size_t)unit * c.Wd * P;
+    u32x4 kk[kChunk * P / 256];
+#pragma unroll
+    for (int i = 0; i < kChunk * P / 256; ++i) {
+        const int idx = tid + i * 256;
+        kk[i] = ring[(size_t)((r0 + idx / P) % c.Wd) * P + idx % P];
+    }
+    const uint32_t mw = tid < kChunk * WPR ? c.mask[((size_t)unit * c.max_seq + r0) * WPR + tid] : 0u;
+#pragma unroll
+    for (int i = 0; i < kChunk * P / 256; ++i) ((u32x4 *)keys)[tid + i * 256] = kk[i];
+    if (tid < kChunk * WPR) mask[tid] = mw;
+    __syncthreads();
+    if (wave < D / 64) {
+        const bf16_t held = chunk > 0 ? ((const bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * D + tid] : (bf16_t)0;
+        const uint32_t n = build_runs(keys + 64 * wave, D, mask + 2 * wave, WPR, held, runs + wave * kHalfRoom);
+        if ((tid & 63) == 0) len[wave] = n;
+    }
+    __syncthreads();
+    store_runs<D, 256>(c, unit, chunk, runs, len);
 }
 
-// Hand-off of prefilled rows to the cache (Sec. III-C): rows t0 .. n_k - 1 (t0 = rows the cache already
-// holds) are appended; two waves per (chunk that contains such a row, unit).  Kfull, Hfull, Mfull describe the
-// whole sequence [units][ld][...] (ld >= n_k rows of room per unit): keys (for rows the decode window no longer
-// holds raw, the reference key stands in - the two agree wherever a mask bit is set, which is all that is read),
-// reference keys, mask
-// rows; Vnew [units][n_k - t0][d] the new value rows.  With t0 = 0 these are the prefill's own arrays.
-__global__ __launch_bounds__(128) void cache_fill_runs_kernel(const bf16_t *__restrict__ Kfull,
-                                                             const bf16_t *__restrict__ Vnew,
-                                                             const bf16_t *__restrict__ Hfull,
-                                                             const uint32_t *__restrict__ Mfull,
-                                                             const uint64_t *__restrict__ nnz_new, da_cache c, int t0,
-                                                             int n_k, int ld) {
-    // two waves: wave 0 takes mask rows, raw-key ring, checkpoint, newest reference key and the chunk's runs; wave 1
-    // the value rows (two chains of dependent memory round trips side by side instead of one after the other)
-    const int chunk = blockIdx.x + t0 / kChunk, unit = blockIdx.y, lane = threadIdx.x & (kWave - 1);
-    const bool values = threadIdx.x >= kWave;
-    const int d = c.d, wpr = d >> 5, m = n_k - t0;
-    const int r0 = chunk * kChunk;
-    const int ra = max(r0, t0), rb = min(r0 + kChunk, n_k);          // new rows of this chunk
-    const uint32_t *Mp = Mfull + ((size_t)unit * ld + r0) * wpr;     // the chunk's mask rows, old ones included
-    const bf16_t *Kp = Kfull + ((size_t)unit * ld + r0) * d;
-    const bf16_t *Hp = Hfull + ((size_t)unit * ld + r0) * d;
-    const bf16_t *Vp = Vnew + (size_t)unit * m * d;
-    if (values) {
-        // V: 16 rows of one channel are contiguous.  A group that starts with a new row is written whole (32
-        // bytes per lane, consecutive lanes adjacent; rows past the end as zeros), one that starts with old
-        // rows only gets its new slots
-        for (int ch = lane; ch < d; ch += kWave) {
-            for (int g0 = r0; g0 < rb; g0 += 16) {
-                if (g0 + 16 <= ra) continue;
-                bf16_t *dst = (bf16_t *)c.V + (((size_t)unit * (c.vrows >> 4) + (g0 >> 4)) * d + ch) * 16;
-                if (g0 >= ra) {
-                    bf16_t v16[16];
+// Hand-off of prefilled rows to the cache (Sec. III-C): rows t0 .. n_k - 1 (t0 = rows the cache already holds) are appended,
+// one work group of 4 waves per (chunk that contains such a row, unit).  K, V, H [units][n_k - t0][D], M: the new rows - keys,
+// values, reference keys, mask rows.  `full` (chunked prefill): the whole sequence as plain arrays, [units][ld][...]; the new
+// rows are added to them, and the chunk's and its predecessor's old rows are read from them.  Without it t0 is 0.
+// The chunk's rows pass through LDS, whole lines in and out.  (A wave per chunk with a lane per channel that loaded and stored
+// two bytes at a time took 26 us on 1024 rows of 10 units of 128, and a kernel of its own the plain arrays; now 9 us
+// together.)
+struct FullRows {
+    bf16_t *k, *v, *h;
+    uint32_t *m;
+    int ld;
+};
+template <int D>
+__global__ __launch_bounds__(256) void cache_fill_runs_kernel(const bf16_t *__restrict__ Knew, const bf16_t *__restrict__ Vnew,
+                                                              const bf16_t *__restrict__ Hnew, const uint32_t *__restrict__ Mnew,
+                                                              const uint64_t *__restrict__ nnz_new, da_cache c, FullRows full,
+                                                              int t0, int n_k) {
+    constexpr int WPR = D / 32, P = D / 8, kIn = kChunk * P / 256;
+    __shared__ __attribute__((aligned(16))) bf16_t keys[kChunk * D];
+    __shared__ __attribute__((aligned(16))) bf16_t vals[kChunk * D];
+    __shared__ __attribute__((aligned(16))) bf16_t runs[(D / 64) * kHalfRoom];
+    __shared__ uint32_t mask[kChunk * WPR], len[2];
+    const int chunk = blockIdx.x + t0 / kChunk, unit = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int m = n_k - t0, r0 = chunk * kChunk;
+    const int ra = max(r0, t0), rb = min(r0 + kChunk, n_k);      // new rows of this chunk
+    const size_t new0 = (size_t)unit * m, full0 = (size_t)unit * full.ld, cache0 = (size_t)unit * c.max_seq;
+    // a row of an array: the new rows' own, or (rows before t0) the whole sequence's
+    auto piece = [&](const bf16_t *fresh, const bf16_t *old, int row, int p) {
+        return row >= t0 ? ((const u32x4 *)fresh)[(new0 + row - t0) * P + p] : ((const u32x4 *)old)[(full0 + row) * P + p];
+    };
+    auto held_of = [&](int row, int ch) { return row >= t0 ? Hnew[(new0 + row - t0) * D + ch] : full.h[(full0 + row) * D + ch]; };
+    // 1. keys (the chunk's old rows included), values and mask rows into LDS; new rows join the plain arrays
+    {
+        u32x4 kk[kIn], vv[kIn], hh[kIn];
 #pragma unroll
-                    for (int slot = 0; slot < 16; ++slot) {
-                        const int k = slot >> 3, i = slot & 7;
-                        const int row = g0 + 8 * (i >> 2) + 4 * k + (i & 3);
-                        const bf16_t v = Vp[(size_t)(min(row, rb - 1) - t0) * d + ch];   // clamped: no conditional load
-                        v16[slot] = row < rb ? v : (bf16_t)0;
-                    }
+        for (int i = 0; i < kIn; ++i) {                          // (rows past the end are the last one again)
+            const int idx = tid + i * 256, row = min(r0 + idx / P, rb - 1), p = idx % P;
+            kk[i] = piece(Knew, full.k, row, p);
+            vv[i] = ((const u32x4 *)Vnew)[(new0 + max(row, ra) - t0) * P + p];
+            hh[i] = ((const u32x4 *)Hnew)[(new0 + max(row, ra) - t0) * P + p];
+        }
+        uint32_t mw = 0;
+        const int mrow = min(r0 + tid / WPR, rb - 1);
+        if (tid < kChunk * WPR)
+            mw = mrow >= t0 ? Mnew[(new0 + mrow - t0) * WPR + tid % WPR] : full.m[(full0 + mrow) * WPR + tid % WPR];
 #pragma unroll
-                    for (int slot = 0; slot < 16; ++slot) dst[slot] = v16[slot];
-                } else {
-                    for (int row = ra; row < min(g0 + 16, rb); ++row)
-                        ((bf16_t *)c.V)[v16_index(unit, c.vrows, d, row, ch)] = Vp[(size_t)(row - t0) * d + ch];
+        for (int i = 0; i < kIn; ++i) {
+            const int idx = tid + i * 256, row = r0 + idx / P, p = idx % P;
+            ((u32x4 *)keys)[idx] = kk[i];
+            ((u32x4 *)vals)[idx] = vv[i];
+            if (row >= ra && row < rb) {
+                if (full.k) {
+                    ((u32x4 *)full.k)[(full0 + row) * P + p] = kk[i];
+                    ((u32x4 *)full.v)[(full0 + row) * P + p] = vv[i];
+                    ((u32x4 *)full.h)[(full0 + row) * P + p] = hh[i];
                 }
+                if (row >= n_k - c.Wd) ((u32x4 *)c.ring)[((size_t)unit * c.Wd + row % c.Wd) * P + p] = kk[i];
             }
         }
-        return;
-    }
-    uint32_t *Mc = c.mask + ((size_t)unit * c.max_seq + r0) * wpr;
-    for (int i = (ra - r0) * wpr + lane; i < (rb - r0) * wpr; i += kWave) Mc[i] = Mp[i];
-    if (lane == 0 && blockIdx.x == 0) c.nnz[unit] = (t0 == 0 ? 0ull : c.nnz[unit]) + nnz_new[unit];
-    for (int ch = lane; ch < d; ch += kWave) {
-        for (int rq = ra; rq < rb; rq += 16) {               // 16 rows at a time: loads first (clamped), then stores
-            bf16_t kk[16];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) kk[u] = Kp[(size_t)(min(rq + u, rb - 1) - r0) * d + ch];
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int row = rq + u;
-                if (row < rb && row >= n_k - c.Wd)
-                    ((bf16_t *)c.ring)[((size_t)unit * c.Wd + row % c.Wd) * d + ch] = kk[u];
+        if (tid < kChunk * WPR) {
+            const int row = r0 + tid / WPR;
+            mask[tid] = mw;
+            if (row >= ra && row < rb) {
+                c.mask[(cache0 + row) * WPR + tid % WPR] = mw;
+                if (full.k) full.m[(full0 + row) * WPR + tid % WPR] = mw;
             }
         }
-        if (chunk > 0 && r0 >= t0) ((bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * d + ch] = Hp[ch - d];
-        if (rb == n_k) ((bf16_t *)c.khat)[(size_t)unit * d + ch] = Hp[(size_t)(rb - 1 - r0) * d + ch];
     }
-    // chunks completed by these rows are sealed here (the run's first element comes from the reference keys)
-    if (rb - r0 == kChunk)
-        seal_chunk(
-            c, unit, chunk, lane, Mp, [&](int r) { return Kp + (size_t)r * d; },
-            [&](int ch) { return chunk > 0 ? Hp[ch - d] : (bf16_t)0; });
+    if (tid == 0 && blockIdx.x == 0) c.nnz[unit] = (t0 == 0 ? 0ull : c.nnz[unit]) + nnz_new[unit];
+    if (tid < D) {
+        if (chunk > 0 && r0 >= t0) ((bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * D + tid] = held_of(r0 - 1, tid);
+        if (rb == n_k) ((bf16_t *)c.khat)[(size_t)unit * D + tid] = held_of(n_k - 1, tid);
+    }
+    __syncthreads();
+    // 2. a chunk completed by these rows is sealed, by the first wave of every 64 channels; the others start on the values
+    const bool seals = rb - r0 == kChunk;
+    if (seals && wave < D / 64) {
+        const bf16_t held = chunk > 0 ? held_of(r0 - 1, 64 * wave + lane) : (bf16_t)0;
+        const uint32_t n = build_runs(keys + 64 * wave, D, mask + 2 * wave, WPR, held, runs + wave * kHalfRoom);
+        if (lane == 0) len[wave] = n;
+    }
+    // 3. values: 16 rows of one channel are contiguous, in slot order (v16_index).  A group that starts with a new row is
+    //    written whole (rows past the end as zeros), one that starts with old rows only gets its new slots
+    const int first = seals ? D / 64 : 0, threads = 256 - 64 * first;
+    for (int i = tid - 64 * first; i >= 0 && i < (kChunk / 16) * D; i += threads) {
+        const int g0 = r0 + i / D * 16, ch = i % D;
+        if (g0 >= rb || g0 + 16 <= ra) continue;
+        if (g0 >= ra) {
+            uint32_t w[8];
+#pragma unroll
+            for (int slot = 0; slot < 16; ++slot) {
+                const int row = g0 + 8 * ((slot & 7) >> 2) + 4 * (slot >> 3) + (slot & 3);
+                const uint32_t v = row < rb ? vals[(row - r0) * D + ch] : 0u;
+                w[slot >> 1] = (slot & 1) ? w[slot >> 1] | (v << 16) : v;
+            }
+            u32x4 *dst = (u32x4 *)((bf16_t *)c.V + (((size_t)unit * (c.vrows >> 4) + (g0 >> 4)) * D + ch) * 16);
+            dst[0] = u32x4{w[0], w[1], w[2], w[3]};
+            dst[1] = u32x4{w[4], w[5], w[6], w[7]};
+        } else {
+            for (int row = ra; row < min(g0 + 16, rb); ++row)
+                ((bf16_t *)c.V)[v16_index(unit, c.vrows, D, row, ch)] = vals[(row - r0) * D + ch];
+        }
+    }
+    __syncthreads();
+    if (seals) store_runs<D, 256>(c, unit, chunk, runs, len);
 }
 
 // The inverse of the hand-off, for a prefill that continues a cached sequence: rows 0 .. t0 - 1 of the cache
@@ -197,7 +251,7 @@ __global__ __launch_bounds__(64) void expand_cache_kernel(da_cache c, int t0, in
         uint32_t total = 0, p = 0;
         bf16_t held = 0;
         if (sealed) {
-            p = base + wave_exclusive_scan((uint32_t)__popcll(cm) + 1u, &total);
+            p = base + kHead + wave_exclusive_scan((uint32_t)__popcll(cm) + 1u, &total);
             held = room[p];
         } else if (chunk > 0) {
             held = ((const bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * d + ch];
@@ -214,7 +268,7 @@ __global__ __launch_bounds__(64) void expand_cache_kernel(da_cache c, int t0, in
                 // every load is in bounds whatever the row (ring slot of any position; p stays inside the room), so
                 // none of them is conditional and all of a batch are in flight together
                 kraw[u] = ring[(size_t)(row % c.Wd) * d + ch];
-                p += (bits >> u) & 1u;                                      // p: position of the newest survivor
+                p += sealed ? (bits >> u) & 1u : 0u;                        // p: position of the newest survivor
                 sv[u] = room[p];
             }
 #pragma unroll
@@ -232,8 +286,7 @@ __global__ __launch_bounds__(64) void expand_cache_kernel(da_cache c, int t0, in
                 }
             }
         }
-        base += total;
-        if (c0 == 0 && d > kWave) base = second_half_start(base);
+        base = kHalfRoom;
     }
 }
 
@@ -268,57 +321,57 @@ __device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf1
     if (lane == 0) c.nnz[unit] = (t == 0 ? 0ull : c.nnz[unit]) + fired;
 }
 
-// One decode step: per (run of `nc` consecutive chunks, unit) one wave at head_dim 64, two waves at head_dim
-// 128 that each take 64 of the channels (all query heads of the unit's group either way).
-// A wave walks its chunks in order with flash-style running (max, sum, output) in registers, and asks for
-// the next chunk's mask rows and runs while it works on the current one; a launch is sized so that all of
-// its waves are resident at once (work-group dispatch, not memory, bounds a launch of one chunk per wave).
+// One decode step, one launch: gridDim.x work groups per unit of NW walkers each; a walker is one wave at head_dim 64, two
+// waves at head_dim 128 that each take 64 of the channels (all query heads of the unit's group either way).  Walker w of all
+// the unit's walkers takes chunks w, w + walkers, ... with flash-style running (max, sum, output) in registers, and asks for
+// the next chunk's mask rows and runs while it works on the current one; a launch is sized so that all of its waves are
+// resident at once.
 // Per chunk:
 //   0. the wave that owns the newest row appends it (D1);
-//   1. history chunks (rows left of the decode window): the runs of the wave's 64 channels are copied to LDS;
-//      lane = row j takes, for every channel c, element B_c + #{marked rows <= j of channel c} of the staged
-//      runs, which is the reference value k_hat(j)[c] (Eq. 3) - by telescoping Eq. 4 the history score of
-//      row j is q . k_hat(j).  The column mask of a channel is the wave ballot of that channel's bit in
-//      the lanes' mask rows; the count is one mbcnt pair, B_c a running scalar sum of the ballots'
-//      popcounts.  Reads of one instruction touch at most 65 consecutive elements: no bank conflicts.
-//      Window rows (lane = row again) are 128-bit loads from the raw-key ring, the newest from k_new.
-//   2. a lane now holds 64 channels of a key row; one permlane32 swap per register pair turns that into the
-//      32x32x16 operand order (lane l: row l % 32, channels 16 s + 8 (l / 32)..+7 of contraction step s);
+//   1. history chunks (rows left of the decode window): head and runs of the wave's 64 channels are copied to LDS; the
+//      reference value k_hat(j)[c] (Eq. 3) is element {start of c's run} + #{marked rows <= j of channel c} - by telescoping
+//      Eq. 4 the history score of row j is q . k_hat(j).  The counts come from the matrix cores: column masks as bytes
+//      (64 channels x 64 rows) times a triangle of twos, plus the starts, is the table of byte addresses, exact in int32,
+//      and comes out in the layout that the next product takes its keys in: lane l holds row l % 32 of a half chunk,
+//      channels 8 q + 4 (l / 32)..+3.  That leaves one LDS read per element.  (Counting on the vector ALU - ballot, two
+//      mbcnt, two adds per channel of 64 rows - was 600 instructions a chunk, which one wave issues in 1.6 us and two on a
+//      SIMD in 3: more than the chunk's memory time.)  Window rows are 64-bit loads from the raw-key ring, the newest from k_new;
+//   2. two neighbouring channels to a register: the 32x32x16 operand, with the queries fetched in the same channel order;
 //   3. scores S[row][head] on the matrix cores (heads padded to 32 columns); at head_dim 128 the two waves
 //      exchange their halves of the contraction through LDS and both hold the full scores; softmax update in
 //      the accumulator registers (lane = head, 32 rows per lane, the other 32 in lane + 32);
 //   4. the accumulator registers, rounded to bf16, are the B operand of O^T += V^T P^T as they stand, because
 //      the V cache stores each group of 16 rows in exactly that order; O^T (the wave's 64 channels) keeps
 //      lane = head, so the running rescale needs no cross-lane traffic.
-// The wave's (o, m, l) goes to scratch and a second launch merges the partials of a head - or, with NW > 1
-// (head_dim 64), the waves of the work group hold every row of the unit and merge in LDS.
+// The walkers of a work group merge their (o, m, l) in LDS.  A unit's only work group writes the normalised output; of
+// several, each leaves its partial row in scratch, and the one that finds the others' there merges and writes (a second
+// launch for this cost 4.7 us of a 19 us step at 4 x 5 units of 6000 rows, and its own time on the host).  On this chip every
+// XCD has its own L2, and fences that write it back or drop it cost more than the second launch did; so the partial rows,
+// and nothing else, are stored past it (relaxed device-scope stores), waited for, counted with a device-scope add, and read
+// past it.
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel(da_cache c, const bf16_t *__restrict__ q_new,
                                                                               const bf16_t *__restrict__ k_new,
                                                                               const bf16_t *__restrict__ v_new,
                                                                               bf16_t *__restrict__ o_out,
                                                                               uint32_t *__restrict__ mask_row, int t,
-                                                                              float scale_log2, int nc) {
+                                                                              float scale_log2) {
     constexpr int H = D / 64;                                // waves that share a chunk, 64 channels each
-    static_assert(H == 1 || NW == 1, "the on-chip merge is built for head_dim 64");
-    constexpr int WPR = D / 32;                              // mask words per row
-    constexpr int KS = 4, CT = 2, NK = 32;                   // per wave: contraction steps, output tiles, kreg pairs
-    constexpr int kPieces = ((kChunk + 1) * 64 + 511) / 512; // 1 KiB copies (16 bytes per lane) that cover 64 channels' runs
+    constexpr int KS = 4, CT = 2;                            // per wave: contraction steps, output tiles
+    constexpr int kPieces = (kHalfRoom + 511) / 512;         // 1 KiB copies (16 bytes per lane) that cover 64 channels
     // two staging areas for the runs of a chunk, used in turn: separate arrays, so that reads of one are known
     // not to touch the other while its copy is still in flight
     __shared__ __attribute__((aligned(16))) bf16_t stage_a_all[NW * H][kPieces * 512];
     __shared__ __attribute__((aligned(16))) bf16_t stage_b_all[NW * H][kPieces * 512];
-    __shared__ float ml_all[NW][32][2];
+    __shared__ float ml_all[NW][32][2];                      // [walker][head] maximum, sum
+    __shared__ uint32_t before;                              // work groups of the unit that were done before this one
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave = wv / H, half = wv % H, coff = 64 * half;   // part inside the work group; channel half
     bf16_t *stage_a = stage_a_all[wv], *stage_b = stage_b_all[wv];
-    const int part_i = blockIdx.x * NW + wave, unit = blockIdx.y, lane = threadIdx.x & 63;
+    const int unit = blockIdx.y, lane = threadIdx.x & 63, nparts = gridDim.x;
     const int nchunks = t / kChunk + 1;
-    // the wave's chunks: c_begin, c_begin + c_step, ... below c_end.  Single walkers take nc consecutive chunks;
-    // the NW walkers of one work group take every NW-th chunk, which spreads an uneven chunk count (and the
-    // cheaper window chunks at the end) evenly over the waves and so over the SIMDs
-    const int c_step = NW > 1 ? NW : 1;
-    const int c_begin = NW > 1 ? wave : part_i * nc, c_end = NW > 1 ? nchunks : min(c_begin + nc, nchunks);
+    // (taking every walkers-th chunk spreads an uneven count, and the cheaper window chunks at the end, evenly)
+    const int c_step = NW * nparts, c_begin = (int)blockIdx.x * NW + wave, c_end = nchunks;
     const int g = c.Hq / c.Hkv;                              // <= 32 in this layout
     const int b = unit / c.Hkv, hk = unit % c.Hkv;
     const int n32 = lane & 31, kap = lane >> 5;
@@ -326,44 +379,45 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     // rows of chunk ch left of the decode window (> 0 only for sealed chunks, because Wd >= kChunk)
     auto hist_of = [&](int ch) { return min(max(win_begin - ch * kChunk, 0), min(kChunk, t + 1 - ch * kChunk)); };
 
-    // q operands (B operand of the score contraction): lane l = head l % 32, channels coff + 16 s + 8 (l / 32)..+7
+    // q operands (B operand of the score contraction): lane l = head l % 32, channels coff + 16 s + 4 (l / 32)..+3 and 8 more
     u32x4 qop[KS];
     {
-        const bf16_t *qrow = q_new + ((size_t)b * c.Hq + hk * g + min(n32, g - 1)) * D + coff;
+        const bf16_t *qrow = q_new + ((size_t)b * c.Hq + hk * g + min(n32, g - 1)) * D + coff + 4 * kap;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            qop[s] = *(const u32x4 *)(qrow + 16 * s + 8 * kap);
+            const u32x2 q0 = *(const u32x2 *)(qrow + 16 * s), q1 = *(const u32x2 *)(qrow + 16 * s + 8);
+            qop[s] = u32x4{q0[0], q0[1], q1[0], q1[1]};
             if (n32 >= g) qop[s] = u32x4{0u, 0u, 0u, 0u};
         }
     }
+    // the triangle of twos (B operand, int8): lane l = row l % 32 of a half chunk, byte i of register k = row 16 (l / 32) + 4 k + i
+    i32x4 tri;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w |= (16 * kap + 4 * k + i <= n32 ? 2u : 0u) << (8 * i);
+        tri[k] = (int)w;
+    }
     // History chunk ch: the runs of this wave's channels go straight from global memory to the LDS staging area
     // (128-bit LDS-direct loads: lane i of a copy lands at base + 16 i); its mask rows, lane = row.
-    // cnt: the chunk's packed element counts (elements in the room | start of the runs of channels 64.. << 16).
-    auto copy_runs = [&](int ch, uint32_t cnt, bf16_t *sv) {
-        const uint32_t total = cnt & 0xffffu, second = cnt >> 16;
-        const uint32_t first = half ? second : 0u;                       // where this wave's runs start (a multiple of 8)
-        const uint32_t len = H == 1 ? total : (half ? total - second : second);
+    // cnt: the chunk's element counts (channels 0..63, channels 64.. << 16); pieces `from` .. of the copy.
+    auto copy_runs = [&](int ch, uint32_t cnt, bf16_t *sv, int from) {
+        const uint32_t first = half * kHalfRoom, len = half ? cnt >> 16 : cnt & 0xffffu;   // this wave's runs
         const bf16_t *runs = run_room(c, unit, ch) + first;
 #pragma unroll
         for (int p = 0; p < kPieces; ++p)
-            if ((uint32_t)p * 512u < len && first + p * 512 + lane * 8 + 8 <= (uint32_t)run_room_stride(D))
+            if (p >= from && (uint32_t)p * 512u < len && first + p * 512 + lane * 8 + 8 <= (uint32_t)run_room_stride(D))
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(runs + p * 512 + lane * 8),
                                                  (__attribute__((address_space(3))) void *)(sv + p * 512), 16, 0, 0);
     };
-    auto total_of = [&](int ch) -> uint32_t {
-        return hist_of(ch) > 0 ? __builtin_amdgcn_readfirstlane(c.ccnt[(size_t)unit * c.max_chunks + ch]) : 0u;
-    };
-    uint32_t mk_n[2];
-    auto request_masks = [&](int ch) {
-        if (hist_of(ch) > 0) {
-            const uint32_t *Mp = c.mask + ((size_t)unit * c.max_seq + ch * kChunk + lane) * WPR + 2 * half;
-#pragma unroll
-            for (int w = 0; w < 2; ++w) mk_n[w] = Mp[w];
-        }
-    };
-    if (c_begin < c_end) {
-        copy_runs(c_begin, total_of(c_begin), stage_a);
-        request_masks(c_begin);
+    if (c_begin < c_end && hist_of(c_begin) > 0) {
+        // the first chunk's copy does not wait for its element counts: the pieces that a chunk with two fifths of its entries
+        // fills are copied anyway, the rest when the counts are there
+        constexpr int kSure = 4;
+        const uint32_t cnt = c.ccnt[(size_t)unit * c.max_chunks + c_begin];
+        copy_runs(c_begin, kSure * 512u | (kSure * 512u << 16), stage_a, 0);
+        copy_runs(c_begin, __builtin_amdgcn_readfirstlane(cnt), stage_a, kSure);
     }
     uint32_t tot_v = 0;                                      // element counts of the chunk after the next one's copy
     if (c_begin + c_step < c_end && hist_of(c_begin + c_step) > 0)
@@ -376,19 +430,15 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
         for (int r = 0; r < 16; ++r) o[ct][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;                    // l_run: this lane half's share of the sum
 
-    auto do_chunk = [&](int chunk, bf16_t *sv, bf16_t *sv_next, const bf16_t *sv_partner) {
+    auto do_chunk = [&](int chunk, bf16_t *sv, bf16_t *sv_next, const bf16_t *sv_partner) __attribute__((always_inline)) {
         const bool newest = chunk == nchunks - 1;            // this wave owns row t
         const int r0 = chunk * kChunk;
         const int nrows = min(kChunk, t + 1 - r0);
         const int hist_rows = hist_of(chunk);
         __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this chunk's runs have landed in LDS
-        // the next chunk's runs and mask rows, and the element count of the one after it, fly in meanwhile
-        uint32_t mk[2];
-#pragma unroll
-        for (int w = 0; w < 2; ++w) mk[w] = mk_n[w];
+        // the next chunk's runs, and the element count of the one after it, fly in meanwhile
         if (chunk + c_step < c_end) {
-            copy_runs(chunk + c_step, __builtin_amdgcn_readfirstlane(tot_v), sv_next);
-            request_masks(chunk + c_step);
+            copy_runs(chunk + c_step, __builtin_amdgcn_readfirstlane(tot_v), sv_next, 0);
             tot_v = 0;
             if (chunk + 2 * c_step < c_end && hist_of(chunk + 2 * c_step) > 0)
                 tot_v = c.ccnt[(size_t)unit * c.max_chunks + chunk + 2 * c_step];
@@ -434,59 +484,90 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
             if (half == 0) append_row_runs(c, uo, ln, k_new, v_new, mask_row, tt);
         }
 
-        // 1. 64 channels of one key row per lane
-        uint32_t kreg[NK];
+        // 1., 2. the keys as operands: kop[T][s] = row 32 T + l % 32, channels coff + 16 s + 4 (l / 32)..+3 and 8 more
+        u32x4 kop[2][KS];
         if (hist_rows > 0) {
-            uint32_t run = 0;                                // uniform: survivors of the channels before this one
-            const char *svb = (const char *)sv;
+            const __attribute__((address_space(3))) char *room = (const __attribute__((address_space(3))) char *)sv;
+            const int lds_base = (int)(uintptr_t)room;
+            // starts of the runs, in the layout of the product: register 4 q + e = channel 8 q + 4 (l / 32) + e; column masks
+            i32x4 st[2][4];
+            u32x2 cm[2];
 #pragma unroll
-            for (int ch = 0; ch < 64; ch += 2) {
-                uint32_t val[2];
+            for (int ct = 0; ct < 2; ++ct) {
+                cm[ct] = *(const __attribute__((address_space(3))) u32x2 *)(room + (32 * ct + n32) * 8);
 #pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const uint32_t bit = (mk[(ch + e) >> 5] >> ((ch + e) & 31)) & 1u;
-                    const uint64_t cm = __ballot(bit != 0u);
-                    const uint32_t idx =
-                        __builtin_amdgcn_mbcnt_hi((uint32_t)(cm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)cm, bit));
-                    val[e] = *(const bf16_t *)(svb + ((idx + run) << 1) + 2 * (ch + e));   // run start = run + ch + e
-                    run += (uint32_t)__popcll(cm);
+                for (int qd = 0; qd < 4; ++qd)
+                    st[ct][qd] = *(const __attribute__((address_space(3))) i32x4 *)(room + 512 + (32 * ct + 8 * qd + 4 * kap) * 4);
+            }
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct) {
+                i32x16 start;                                // as LDS addresses
+#pragma unroll
+                for (int r = 0; r < 16; ++r) start[r] = st[ct][r >> 2][r & 3] + lds_base;
+                // column masks, a byte per row: lane l = channel l % 32, rows 32 u + 16 (l / 32) .. + 15
+                i32x4 bytes[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t bits = cm[ct][u] >> (16 * kap);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)              // four bits to four bytes
+                        bytes[u][k] = (int)(__umul24((bits >> (4 * k)) & 15u, 0x204081u) & 0x01010101u);
                 }
-                kreg[ch >> 1] = val[0] | (val[1] << 16);
+                const i32x4 twos = {0x02020202, 0x02020202, 0x02020202, 0x02020202};
+                i32x16 at[2];
+                at[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bytes[0], tri, start, 0, 0, 0);
+                at[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bytes[0], twos, start, 0, 0, 0);
+                at[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(bytes[1], tri, at[1], 0, 0, 0);
+                // (the reads are written out: through a pointer made of an integer they could alias the copy in flight for the
+                // next chunk, and the compiler would wait for that first; so the wait states between a matrix result and
+                // its use as an address - 19 at most - are written out too)
+                asm volatile("s_nop 15\n\ts_nop 3" : "+v"(at[0]), "+v"(at[1]));
+                uint32_t val_of[2][16];
+#pragma unroll
+                for (int T = 0; T < 2; ++T)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) asm volatile("ds_read_u16 %0, %1" : "=v"(val_of[T][r]) : "v"(at[T][r]));
+#pragma unroll
+                for (int T = 0; T < 2; ++T) {
+                    uint32_t *val = val_of[T];
+                    if (T == 0)
+                        asm volatile("s_waitcnt lgkmcnt(15)"
+                                     : "+v"(val[0]), "+v"(val[1]), "+v"(val[2]), "+v"(val[3]), "+v"(val[4]), "+v"(val[5]), "+v"(val[6]),
+                                       "+v"(val[7]), "+v"(val[8]), "+v"(val[9]), "+v"(val[10]), "+v"(val[11]), "+v"(val[12]),
+                                       "+v"(val[13]), "+v"(val[14]), "+v"(val[15]));
+                    else
+                        asm volatile("s_waitcnt lgkmcnt(0)"
+                                     : "+v"(val[0]), "+v"(val[1]), "+v"(val[2]), "+v"(val[3]), "+v"(val[4]), "+v"(val[5]), "+v"(val[6]),
+                                       "+v"(val[7]), "+v"(val[8]), "+v"(val[9]), "+v"(val[10]), "+v"(val[11]), "+v"(val[12]),
+                                       "+v"(val[13]), "+v"(val[14]), "+v"(val[15]));
+#pragma unroll
+                    for (int r = 0; r < 16; r += 2)          // channel 32 ct + 8 (r / 4) + 4 (l / 32) + r % 4 and the next
+                        kop[T][2 * ct + (r >> 3)][(r & 7) >> 1] = val[r] | (val[r + 1] << 16);
+                }
             }
         }
         if (hist_rows < kChunk) {
-            if (lane >= hist_rows) {
-                if (lane < nrows) {
-                    const int row = r0 + lane;
-                    const bf16_t *src = (row == t ? k_new + (size_t)unit * D
-                                                  : (const bf16_t *)c.ring + ((size_t)unit * c.Wd + row % c.Wd) * D) + coff;
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const u32x4 v = *(const u32x4 *)(src + 8 * i);
-                        kreg[4 * i] = v[0];
-                        kreg[4 * i + 1] = v[1];
-                        kreg[4 * i + 2] = v[2];
-                        kreg[4 * i + 3] = v[3];
+            for (int T = 0; T < 2; ++T)
+                if (32 * T + n32 >= hist_rows) {
+                    const int row = r0 + 32 * T + n32;
+                    if (row <= t) {
+                        const bf16_t *src = (row == t ? k_new + (size_t)unit * D
+                                                      : (const bf16_t *)c.ring + ((size_t)unit * c.Wd + row % c.Wd) * D) + coff + 4 * kap;
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) {
+                            const u32x2 x0 = *(const u32x2 *)(src + 16 * s), x1 = *(const u32x2 *)(src + 16 * s + 8);
+                            kop[T][s] = u32x4{x0[0], x0[1], x1[0], x1[1]};
+                        }
+                    } else {
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) kop[T][s] = u32x4{0u, 0u, 0u, 0u};
                     }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < NK; ++i) kreg[i] = 0u;
                 }
-            }
             // the raw rows are awaited here, inside the branch only window chunks take: left to the compiler the
             // wait lands after the join and history chunks would drain their in-flight V and run copies there
             __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
         }
-        // 2. operand order: kop[T][s] = rows 32 T + l % 32, channels coff + 16 s + 8 (l / 32)..+7
-        u32x4 kop[2][KS];
-#pragma unroll
-        for (int s = 0; s < KS; ++s)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const auto sw = __builtin_amdgcn_permlane32_swap(kreg[8 * s + i], kreg[8 * s + 4 + i], false, false);
-                kop[0][s][i] = sw[0];
-                kop[1][s][i] = sw[1];
-            }
         // 3. scores: lane l holds head l % 32 at rows 32 T + 8 (r / 4) + 4 (l / 32) + r % 4
         f32x16 acc[2];
 #pragma unroll
@@ -499,12 +580,11 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
                                                                  __builtin_bit_cast(bf16x8, qop[s]), acc[T], 0, 0, 0);
         }
         if (H == 2) {
-            // the other wave contracted the other 64 channels: the halves meet in the staging areas both waves have
-            // just finished reading (register r of lane l at float 64 r + l: conflict free), and are added in the
-            // same order by both, so both hold the same scores
+            // the other wave contracted the other 64 channels: the halves meet in the staging areas each wave has
+            // just finished reading its own of (register r of lane l at float 64 r + l: conflict free), and are added in
+            // the same order by both, so both hold the same scores
             float *mine = (float *)sv;
             const float *theirs = (const float *)sv_partner;
-            lds_barrier();                                   // both waves are done gathering from these areas
 #pragma unroll
             for (int T = 0; T < 2; ++T)
 #pragma unroll
@@ -565,57 +645,111 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
                                                                     __builtin_bit_cast(bf16x8, pa[T][s2]), o[ct], 0, 0, 0);
     };
     const bf16_t *partner_a = stage_a_all[wv ^ (H - 1)], *partner_b = stage_b_all[wv ^ (H - 1)];
-    for (int chunk = c_begin; chunk < c_end; chunk += 2 * c_step) {
-        do_chunk(chunk, stage_a, stage_b, partner_a);
-        if (chunk + c_step < c_end) do_chunk(chunk + c_step, stage_b, stage_a, partner_b);
+    // Every walker of the work group takes the same number of turns: at head_dim 128 a turn holds two barriers, which a walker
+    // that has run out of chunks passes all the same.
+    auto take = [&](int chunk, bf16_t *sv, bf16_t *sv_next, const bf16_t *sv_partner) __attribute__((always_inline)) {
+        if (chunk < c_end) {
+            do_chunk(chunk, sv, sv_next, sv_partner);
+        } else if (H == 2) {
+            lds_barrier();
+            lds_barrier();
+        }
+    };
+    for (int first = (int)blockIdx.x * NW; first < c_end; first += 2 * c_step) {     // (walker 0's chunk of the turn)
+        take(first + wave, stage_a, stage_b, partner_a);
+        if (first + c_step < c_end) take(first + c_step + wave, stage_b, stage_a, partner_b);
     }
     const float l_all = l_run + __shfl_xor(l_run, 32);
-    if (NW == 1) {
-        // partial (o, m, l) of this wave's rows and channels, merged by a second launch
-        if (n32 < g) {
-            float *out = c.part + (((size_t)b * c.Hq + hk * g + n32) * c.max_chunks + part_i) * part_stride(D);
+    // the walkers' (o, m, l) meet in LDS (a walker without chunks contributes m = -inf, l = 0)
+    if (NW * H > 1) __syncthreads();                         // (the partner may still read this wave's staging area)
+    float *obuf = (float *)stage_a;                          // [g][64] of this wave; its staging areas are idle now
+    if (n32 < g) {
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
+        for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq)
-                    *(f32x4 *)(out + coff + 32 * ct + 8 * rq + 4 * kap) =
-                        f32x4{o[ct][4 * rq], o[ct][4 * rq + 1], o[ct][4 * rq + 2], o[ct][4 * rq + 3]};
-            if (kap == 0 && half == 0) {
-                out[D] = m_run;
-                out[D + 1] = l_all;
-            }
+            for (int rq = 0; rq < 4; ++rq)
+                *(f32x4 *)(obuf + n32 * 64 + 32 * ct + 8 * rq + 4 * kap) =
+                    f32x4{o[ct][4 * rq], o[ct][4 * rq + 1], o[ct][4 * rq + 2], o[ct][4 * rq + 3]};
+        if (kap == 0 && half == 0) {
+            ml_all[wave][n32][0] = m_run;
+            ml_all[wave][n32][1] = l_all;
         }
-    } else {
-        // the work group holds every row of the unit: its waves' (o, m, l) meet in LDS and the normalised
-        // output row of each head is written here (a wave without chunks contributes m = -inf, l = 0)
-        float *obuf = (float *)stage_a;                      // [g][D] of this wave; its staging areas are idle now
-        if (n32 < g) {
+    }
+    __syncthreads();
+    constexpr int kThreads = 64 * NW * H;
+    float *part = c.part + ((size_t)b * c.Hq + hk * g) * c.max_chunks * part_stride(D);   // [head][max_chunks][part_stride]
+    // two channels of a head per thread at a time; a row's last pair is its maximum and sum
+    auto put = [&](int h, int ch, float x, float y) {
+        const uint64_t v = (uint64_t)__float_as_uint(x) | ((uint64_t)__float_as_uint(y) << 32);
+        __hip_atomic_store((uint64_t *)(part + ((size_t)h * c.max_chunks + blockIdx.x) * part_stride(D) + ch), v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto get = [&](int h, int p, int ch) -> f32x2 {
+        const uint64_t v = __hip_atomic_load((const uint64_t *)(part + ((size_t)h * c.max_chunks + p) * part_stride(D) + ch),
+                                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return f32x2{__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32))};
+    };
+    for (int e = threadIdx.x; e < g * (D / 2); e += kThreads) {
+        const int h = e / (D / 2), ch = e % (D / 2) * 2;
+        float M = -INFINITY;
 #pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
+        for (int w = 0; w < NW; ++w) M = fmaxf(M, ml_all[w][h][0]);
+        const float M0 = M == -INFINITY ? 0.f : M;           // (a work group without chunks)
+        float L = 0.f, x = 0.f, y = 0.f;
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq)
-                    *(f32x4 *)(obuf + n32 * D + 32 * ct + 8 * rq + 4 * kap) =
-                        f32x4{o[ct][4 * rq], o[ct][4 * rq + 1], o[ct][4 * rq + 2], o[ct][4 * rq + 3]};
-            if (kap == 0) {
-                ml_all[wave][n32][0] = m_run;
-                ml_all[wave][n32][1] = l_all;
-            }
+        for (int w = 0; w < NW; ++w) {
+            const float f = __builtin_amdgcn_exp2f(ml_all[w][h][0] - M0);
+            const f32x2 v = *(const f32x2 *)((const float *)stage_a_all[w * H + (ch >> 6)] + h * 64 + (ch & 63));
+            L = fmaf(f, ml_all[w][h][1], L);
+            x = fmaf(f, v[0], x);
+            y = fmaf(f, v[1], y);
         }
-        __syncthreads();
-        for (int e = threadIdx.x; e < g * D; e += 64 * NW) {
-            const int h = e / D;
-            float M = -INFINITY;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) M = fmaxf(M, ml_all[w][h][0]);
-            float L = 0.f, O = 0.f;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                const float f = __builtin_amdgcn_exp2f(ml_all[w][h][0] - M);   // wave 0 always has rows: M is finite
-                L = fmaf(f, ml_all[w][h][1], L);
-                O = fmaf(f, ((const float *)stage_a_all[w])[e], O);
-            }
-            o_out[((size_t)b * c.Hq + hk * g) * D + e] = f32_to_bf16(O / L);
+        if (nparts == 1) {
+            const float inv = 1.f / L;
+            *(uint32_t *)(o_out + ((size_t)b * c.Hq + hk * g + h) * D + ch) =
+                (uint32_t)f32_to_bf16(x * inv) | ((uint32_t)f32_to_bf16(y * inv) << 16);
+        } else {
+            put(h, ch, x, y);
+            if (ch == 0) put(h, D, M, L);
         }
+    }
+    if (nparts == 1) return;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's stores have reached memory
+    __syncthreads();
+    if (threadIdx.x == 0) before = __hip_atomic_fetch_add(c.arrived + unit, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (before != (uint32_t)nparts - 1u) return;
+    if (threadIdx.x == 0) __hip_atomic_store(c.arrived + unit, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next step
+    for (int e = threadIdx.x; e < g * (D / 2); e += kThreads) {
+        const int h = e / (D / 2), ch = e % (D / 2) * 2;
+        float M = -INFINITY, L = 0.f, x = 0.f, y = 0.f;
+        constexpr int kB = 8;                                // partial rows fetched together
+        for (int p0 = 0; p0 < nparts; p0 += kB) {
+            f32x2 v[kB], ml[kB];
+#pragma unroll
+            for (int k = 0; k < kB; ++k) {                   // (past the end: the last one again, not used)
+                v[k] = get(h, min(p0 + k, nparts - 1), ch);
+                ml[k] = get(h, min(p0 + k, nparts - 1), D);
+            }
+            float mb = M;
+#pragma unroll
+            for (int k = 0; k < kB; ++k) mb = fmaxf(mb, ml[k][0]);   // (part 0 has rows: finite)
+            const float f = __builtin_amdgcn_exp2f(M - mb);
+            L *= f;
+            x *= f;
+            y *= f;
+#pragma unroll
+            for (int k = 0; k < kB; ++k) {
+                const float w = p0 + k < nparts ? __builtin_amdgcn_exp2f(ml[k][0] - mb) : 0.f;
+                L = fmaf(w, ml[k][1], L);
+                x = fmaf(w, v[k][0], x);
+                y = fmaf(w, v[k][1], y);
+            }
+            M = mb;
+        }
+        const float inv = 1.f / L;
+        *(uint32_t *)(o_out + ((size_t)b * c.Hq + hk * g + h) * D + ch) =
+            (uint32_t)f32_to_bf16(x * inv) | ((uint32_t)f32_to_bf16(y * inv) << 16);
     }
 }
 
@@ -623,12 +757,17 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
 
 namespace da {
 
-void cache_fill_runs(da_cache *c, int t0, int n_k, int ld, const void *Kfull, const void *Vnew, const void *Hfull,
-                     const uint32_t *Mfull, const uint64_t *nnz_new, hipStream_t s) {
-    const int units = c->B * c->Hkv;
-    const int chunks = (n_k + kChunk - 1) / kChunk - t0 / kChunk;
-    hipLaunchKernelGGL(cache_fill_runs_kernel, dim3(chunks, units), dim3(2 * kWave), 0, s, (const bf16_t *)Kfull,
-                       (const bf16_t *)Vnew, (const bf16_t *)Hfull, Mfull, nnz_new, *c, t0, n_k, ld);
+void cache_fill_runs(da_cache *c, int t0, int n_k, const void *Knew, const void *Vnew, const void *Hnew, const uint32_t *Mnew,
+                     const uint64_t *nnz_new, const da_prefix *full, hipStream_t s) {
+    FullRows f = {};
+    if (full) f = FullRows{(bf16_t *)full->k, (bf16_t *)full->v, (bf16_t *)full->h, full->m, c->max_seq};
+    const dim3 grid((n_k + kChunk - 1) / kChunk - t0 / kChunk, c->B * c->Hkv);
+    if (c->d == 64)
+        hipLaunchKernelGGL(cache_fill_runs_kernel<64>, grid, dim3(256), 0, s, (const bf16_t *)Knew, (const bf16_t *)Vnew,
+                           (const bf16_t *)Hnew, Mnew, nnz_new, *c, f, t0, n_k);
+    else
+        hipLaunchKernelGGL(cache_fill_runs_kernel<128>, grid, dim3(256), 0, s, (const bf16_t *)Knew, (const bf16_t *)Vnew,
+                           (const bf16_t *)Hnew, Mnew, nnz_new, *c, f, t0, n_k);
 }
 
 void expand_cache_runs(da_cache *c, int t0, int ld, void *Kfull, void *Hfull, void *Vfull, uint32_t *Mfull,
@@ -638,49 +777,37 @@ void expand_cache_runs(da_cache *c, int t0, int ld, void *Kfull, void *Hfull, vo
                        ld, (bf16_t *)Kfull, (bf16_t *)Hfull, (bf16_t *)Vfull, Mfull);
 }
 
-int decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, void *o, uint32_t *mask_row, int t,
-                     float scale_log2, hipStream_t s) {
+void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, void *o, uint32_t *mask_row, int t,
+                      float scale_log2, hipStream_t s) {
     const int units = c->B * c->Hkv, nchunks = t / kChunk + 1;
-    // A launch is sized so that all of its waves are resident at once: 4 SIMDs per CU, 2 waves per SIMD by the
-    // kernel's registers and LDS.  At head_dim 128 two waves share every chunk, so half as many chunk walkers fit.
     if (c->cus < 1 &&
         (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || c->cus < 1))
         c->cus = 256;
-    const int cus = c->cus;
-    const int slots = (c->plan_slots > 0 ? c->plan_slots : cus * 8) / (c->d == 64 ? 1 : 2);
+    // Work groups of 8 waves - 8 walkers at head_dim 64, 4 at head_dim 128 -, one per compute unit by LDS and registers: as many
+    // per unit as keep the whole launch resident, no more than the last one can merge in a few round trips - or just one,
+    // where meeting across work groups (2 us, about a turn) would take longer than the turns it saves.
+    const int nw = c->d == 64 ? 8 : 4, slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8;
+    auto turns = [&](int parts) { return (nchunks + nw * parts - 1) / (nw * parts); };
+    const int most = std::max(1, std::min(slots / 8 / units, 32)), fewest = turns(most);
+    int parts = 1;
+    if (c->plan_merge != 1 && (fewest + 1 < turns(1) || c->plan_merge == 0))
+        parts = (nchunks + nw * fewest - 1) / (nw * fewest);
+    const dim3 grid(parts, units);
     const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *vv = (const bf16_t *)v;
-    // head_dim 64: one 8-wave work group per unit whose waves split the unit's chunks and merge in LDS (the
-    // normalised output is written by this launch; returns 0: nothing left to merge) pays when its waves fill the
-    // wave slots: measured over 64..512 units with the caches read from HBM, it wins from 3/4 of the slots on and
-    // loses to single-wave work groups (which spread any unit count over every SIMD) below that.
-    if (c->d == 64) {
-        const int nw = 8;
-        const int64_t waves = (int64_t)units * nw;
-        const bool fills = waves * 4 >= (int64_t)slots * 3;
-        if (c->plan_merge == 1 || (c->plan_merge < 0 && fills)) {
-            const int nc = (nchunks + nw - 1) / nw;
-            hipLaunchKernelGGL((decode_step_runs_kernel<64, 8>), dim3(1, units), dim3(64 * nw), 0, s, *c, qq, kk, vv,
-                               (bf16_t *)o, mask_row, t, scale_log2, nc);
-            return 0;
-        }
-    }
-    // otherwise one chunk walker (1 or 2 waves) per work group, as few chunks each as keep the launch resident;
-    // partial rows
-    int nc = (int)(((int64_t)units * nchunks + slots - 1) / max(slots, 1));
-    if (nc < 1) nc = 1;
-    const int nparts = (nchunks + nc - 1) / nc;
-    const dim3 grid(nparts, units);
     if (c->d == 64)
-        hipLaunchKernelGGL((decode_step_runs_kernel<64, 1>), grid, dim3(64), 0, s, *c, qq, kk, vv, (bf16_t *)o, mask_row,
-                           t, scale_log2, nc);
+        hipLaunchKernelGGL((decode_step_runs_kernel<64, 8>), grid, dim3(512), 0, s, *c, qq, kk, vv, (bf16_t *)o, mask_row, t,
+                           scale_log2);
     else
-        hipLaunchKernelGGL((decode_step_runs_kernel<128, 1>), grid, dim3(128), 0, s, *c, qq, kk, vv, (bf16_t *)o,
-                           mask_row, t, scale_log2, nc);
-    return nparts;
+        hipLaunchKernelGGL((decode_step_runs_kernel<128, 4>), grid, dim3(512), 0, s, *c, qq, kk, vv, (bf16_t *)o, mask_row, t,
+                           scale_log2);
 }
 
 void seal_chunk_runs(da_cache *c, int chunk, hipStream_t s) {
-    hipLaunchKernelGGL(seal_from_ring_kernel, dim3(c->B * c->Hkv), dim3(64), 0, s, *c, chunk);
+    const dim3 grid(c->B * c->Hkv);
+    if (c->d == 64)
+        hipLaunchKernelGGL(seal_from_ring_kernel<64>, grid, dim3(256), 0, s, *c, chunk);
+    else
+        hipLaunchKernelGGL(seal_from_ring_kernel<128>, grid, dim3(256), 0, s, *c, chunk);
 }
 
 }  // namespace da

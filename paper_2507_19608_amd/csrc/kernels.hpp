@@ -40,10 +40,6 @@ struct PrefillArgs {
 
 void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s);
 
-// Chunked prefill: rows of the new piece - K, V, H [units][m][d] (bf16) and M [units][m][d/32] - are copied behind
-// row t0 of the whole-sequence arrays [units][ld][...].
-void launch_append_rows(const void *K, const void *V, const void *H, const uint32_t *M, void *Kfull, void *Vfull,
-                        void *Hfull, uint32_t *Mfull, int units, int t0, int m, int ld, int d, hipStream_t s);
 // scratch: delta_scan_scratch_bytes(); init: NULL (row 0 is the basis row), or [units][d], the reference key the rows
 // continue from
 size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d);

@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2507_19608_amd import binding as da
+from test_decode_parity import run_decode
 from test_prefill_parity import run_case
 from util import rand_walk
 
@@ -108,3 +109,25 @@ def test_unaligned_keys_take_the_kernel_that_allows_them():
     a, b = da.delta_attn_prefill(Q, K, V, 0.2, 16), da.delta_attn_prefill(Q, off[0], off[1], 0.2, 16)
     assert torch.equal(a[1], b[1]) and torch.equal(a[2], b[2])
     assert (a[0].float() - b[0].float()).abs().max().item() <= 2e-2
+
+
+@pytest.mark.parametrize("n,steps,d,Hq,theta,plan", [
+    (1535, 3, 64, 8, 0.2, (0, 16)),              # 24, then 25 chunks over the 8 walkers of one work group
+    (1535, 3, 64, 8, 0.2, (0, 32)),              # over 16 of two: every other walker has one more
+    (1535, 3, 64, 1, 0.0, (0, 64)), (900, 2, 64, 32, 5.0, (0, 64)),   # all and none of the entries survive
+    (700, 2, 128, 32, 0.2, (0, 32)),             # 11 chunks over 4 walkers (of two waves) each of two work groups
+    (831, 3, 128, 4, 0.0, (0, 64)), (1300, 2, 128, 8, 0.15, (0, 512)), (257, 2, 128, 2, 0.2, (1, 0)),
+])
+def test_decode_steps_of_several_work_groups(n, steps, d, Hq, theta, plan):
+    """The work groups of a unit meet in memory, the last one merges: uneven walkers, walkers without a chunk, full and
+    empty runs; consecutive steps on one cache find the count of arrivals back at zero."""
+    L = n + steps
+    Q, K, V = rand_walk(91, 2, Hq, L, d), rand_walk(92, 2, 1, L, d), rand_walk(93, 2, 1, L, d, clip=3.5)
+    run_decode(Q, K, V, n, steps, theta, 64, "bf16", plan=plan)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [15, 16, 17, 63, 64, 65, 129, 143])
+def test_hand_off_of_ragged_chunks(d, n):
+    Q, K, V = rand_walk(94, 1, 2, n + 66, d), rand_walk(95, 1, 1, n + 66, d), rand_walk(96, 1, 1, n + 66, d, clip=3.5)
+    run_decode(Q, K, V, n, 66, 0.2, 64, "bf16", check_every=5)
