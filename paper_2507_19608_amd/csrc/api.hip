@@ -19,7 +19,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline size_t elt_size(int dtype) { return dtype == DA_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t khat, scan, scan_total, total;
+    size_t khat, scan, scan_total, queue, total;
 };
 
 // what prefill_mfma_supported reads, for a prefill of p's rows behind `cached` rows
@@ -60,8 +60,10 @@ WsLayout layout(const da_prefill_params *p) {
     w.scan = off;
     off += align_up(delta_scan_scratch_bytes(p->dtype, (int)units, p->seq_len, p->head_dim));
     w.scan_total = off;
-    // Room that no kernel uses: the size a caller asked for has always covered 8 bytes per key element and 4 per row
-    // here, and plans that were sized with it stay comparable.
+    // Room for the attention launch's counters, and else unused: the size a caller asked for has always covered 8 bytes per
+    // key element and 4 per row here, and plans that were sized with it stay comparable.
+    w.queue = off;
+    static_assert(kPrefillQueueBytes <= 64 * 8, "one row of head_dim 64 makes room for it");
     off += align_up(rows * p->head_dim * 8) + align_up(rows * sizeof(uint32_t));
     w.total = off;
     return w;
@@ -161,7 +163,7 @@ da_status delta_attn_delta_scan(const da_prefill_params *p, const void *K, uint3
     char *ws = (char *)workspace;
     (void)hipGetLastError();
     launch_delta_scan(p->dtype, K, k_hat ? k_hat : ws + w.khat, mask_bits, ws + w.scan, nnz,
-                      p->batch * p->n_kv_heads, p->seq_len, p->head_dim, p->theta, s);
+                      p->batch * p->n_kv_heads, p->seq_len, p->head_dim, p->theta, s, nullptr, nullptr);
     return launch_ok("delta_scan") ? DA_OK : DA_ERR_HIP;
 }
 
@@ -218,7 +220,8 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.Hq = p->n_q_heads;
     a.n = p->seq_len;
     stage_begin(kStageScan, s);
-    launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, nnz, units, p->seq_len, p->head_dim, p->theta, s);
+    a.queue = p->head_dim >= 64 ? (uint32_t *)(ws + w.queue) : nullptr;      // (32: another kernel, and less room)
+    launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, nnz, units, p->seq_len, p->head_dim, p->theta, s, nullptr, a.queue);
     stage_end(kStageScan, s);
     if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     a.q_off = 0;
@@ -252,7 +255,7 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
 // workspace of delta_attn_prefill_append: what the scan of the new rows needs (the whole-sequence arrays live in the
 // cache, see da_prefix)
 struct AppendLayout {
-    size_t hnew, scan, total;
+    size_t hnew, scan, queue, total;
 };
 
 AppendLayout append_layout(const da_prefill_params *p) {
@@ -264,6 +267,8 @@ AppendLayout append_layout(const da_prefill_params *p) {
     off += align_up(units * m * d * es);
     w.scan = off;
     off += align_up(delta_scan_scratch_bytes(p->dtype, (int)units, (int)m, (int)d));
+    w.queue = off;
+    off += align_up(kPrefillQueueBytes);
     w.total = off;
     return w;
 }
@@ -346,7 +351,7 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis)
     stage_begin(kStageScan, s);
     launch_delta_scan(p->dtype, K, ws + w.hnew, mask_bits, ws + w.scan, nnz, units, m, d, p->theta, s,
-                      t0 > 0 ? cache->khat : nullptr);
+                      t0 > 0 ? cache->khat : nullptr, (uint32_t *)(ws + w.queue));
     stage_end(kStageScan, s);
     if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     // 3. the new rows join the plain arrays and the cache
@@ -373,6 +378,7 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     a.V = f->v;
     a.Khat = f->h;
     a.O = O;
+    a.queue = (uint32_t *)(ws + w.queue);
     stage_begin(kStageAttn, s);
     launch_prefill_mfma(a, s);                         // (supported: check_append has asked)
     stage_end(kStageAttn, s);

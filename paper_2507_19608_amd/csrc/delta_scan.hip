@@ -254,6 +254,7 @@ struct ScanArgs {
     uint32_t *counts;                    // [units][nseg][groups of 64 channels] fired entries
     unsigned long long *nnz;
     const T *init;
+    uint32_t *zeroed;                    // kPrefillQueueBytes, or NULL
     int n, d, S, nseg, warm, dl;
     float theta;
 };
@@ -293,6 +294,7 @@ __global__ __launch_bounds__(512) void scan_segments_kernel(ScanArgs<T> g) {
             for (int k = 0; k < kIn; ++k) dst[min(i0 + k * threads, pieces - 1)] = v[k];
         }
         if (tid == 0) *cnt = 0;
+        if (g.zeroed && seg == 0 && unit == 0 && blockIdx.z == 0 && tid < kPrefillQueueBytes / 4) g.zeroed[tid] = 0;
         if (g.nseg > 1 && seg == 0 && blockIdx.z == 0 && tid == 0) g.nnz[unit] = 0;   // (scan_settle_kernel adds to it)
     }
     __syncthreads();
@@ -494,11 +496,11 @@ size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d) {
 
 template <typename T>
 static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz,
-                       int units, int n, int d, float theta, const void *init, hipStream_t s) {
+                       int units, int n, int d, float theta, const void *init, uint32_t *zeroed, hipStream_t s) {
     const size_t segs = (size_t)units * p.nseg;
     T *starts = (T *)scratch;
     const ScanArgs<T> a = {(const T *)K, (T *)Khat, mask_bits, starts, starts + segs * d, (uint32_t *)(starts + 2 * segs * d),
-                           (unsigned long long *)nnz, (const T *)init, n, d, p.S, p.nseg, p.warm, p.dl, theta};
+                           (unsigned long long *)nnz, (const T *)init, zeroed, n, d, p.S, p.nseg, p.warm, p.dl, theta};
     const int groups = (d + p.dl - 1) / p.dl;
     const int which = p.dl == 128 ? 2 : p.dl == 64 && d % 64 == 0 ? 1 : 0;
     const auto kernel = which == 2 ? scan_segments_kernel<T, 128> : which == 1 ? scan_segments_kernel<T, 64> : scan_segments_kernel<T, 0>;
@@ -511,12 +513,12 @@ static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *m
 
 // Khat [units][n][d] and scratch (delta_scan_scratch_bytes) are required scratch/outputs.
 void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz, int units,
-                       int n, int d, float theta, hipStream_t s, const void *init) {
+                       int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed) {
     const ScanPlan p = scan_plan(dtype, units, n, d);
     if (dtype == 0)
-        scan_typed<float>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, s);
+        scan_typed<float>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, zeroed, s);
     else
-        scan_typed<bf16_t>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, s);
+        scan_typed<bf16_t>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, zeroed, s);
 }
 
 }  // namespace da

@@ -36,15 +36,17 @@ struct PrefillArgs {
     int sliding;          // 1: exact region is the band i - j < W instead of squares of side W
     const void *Q, *K, *V, *Khat;
     void *O;
+    uint32_t *queue;      // (matrix-core path) kPrefillQueueBytes, zeroed
 };
+constexpr int kPrefillQueueBytes = 512;
 
 void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s);
 
 // scratch: delta_scan_scratch_bytes(); init: NULL (row 0 is the basis row), or [units][d], the reference key the rows
-// continue from
+// continue from; zeroed: NULL, or kPrefillQueueBytes to clear for the attention launch that follows
 size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d);
 void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz, int units,
-                       int n, int d, float theta, hipStream_t s, const void *init = nullptr);
+                       int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed);
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
 // no instantiation.  q_off and ld are not for it.
 bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);

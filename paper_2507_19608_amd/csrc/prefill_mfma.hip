@@ -27,12 +27,15 @@
 // 4 x 8192 tokens, 20 / 5 heads of 128: 1340 -> 1215 us (all waves in step, a barrier per 32 keys, tiles by way of registers
 // and V re-ordered by a launch of its own before); 1 x 4096: 190 -> 115 us, most of it from the order of the tiles below.
 //
-// kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 32 keys, with their own running
-// (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.8 of the time: for launches that would
-// otherwise wait for their longest tile (see launch_d).
+// kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 64 keys, with their own running
+// (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.6 of the time (the same work per wave,
+// twice the loads): for the last, longest rows of a launch that would otherwise wait for them.  A launch cuts its rows into
+// whole and split tiles where that promises to end first (see launch_d) and hands them out longest first from a counter.
+// 2048 tokens, 32 / 8 heads of 64: 41 -> 33 us (blocks of 32 keys for each group before, one work group per tile); pieces of
+// 1024 tokens on 2 x 4096, 20 / 5 heads of 128: 360 -> 328 us a prompt; 2 x 5003 sliding: 301 -> 286 us.
 //
 // Tiles go from global memory to LDS directly (global_load_lds, 16 bytes per lane, no registers), row-major, two blocks ahead
-// in three buffers.  The 16-byte segments of a row are permuted by the row number so that the reads are free of bank
+// in three buffers, or two where every group has its own.  The 16-byte segments of a row are permuted by the row number so that the reads are free of bank
 // conflicts: keys by 128-bit reads down a column of rows, values by transposing reads (ds_read_b64_tr_b16: lane j of 16
 // receives channel j of four key rows whose 8-byte pieces the 16 lanes address), which is why V needs no re-ordering launch.
 //
@@ -62,7 +65,22 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(8))) short s16x8;
 typedef __attribute__((address_space(3))) char lds_char;
 
-constexpr int kSpan = 64;       // keys of one turn of the loop (both groups together where they walk different ones)
+constexpr int KB = 64;          // keys of a block
+constexpr int kQueueStride = kPrefillQueueBytes / 8 / 4;
+
+// n / d for 0 <= n < 2^31 by a divisor known to the host: three scalar instructions, where the division's own two dozen
+// (times nine, one after the other, before the first load can go out) took 0.5 us of every work group
+struct Divisor {
+    uint32_t mul, shift;
+    int d;
+};
+Divisor divisor(int d) {
+    uint32_t l = 0;
+    while (((uint64_t)1 << l) < (uint64_t)d) ++l;
+    return Divisor{(uint32_t)((((uint64_t)1 << (31 + l)) / (uint64_t)d) + 1u), l, d};
+}
+template <typename Div>          // (Divisor, in whichever address space)
+__device__ __forceinline__ int quotient(int n, const Div &d) { return (int)(__umulhi(2u * (uint32_t)n, d.mul) >> d.shift); }
 
 struct MfmaArgs {
     const bf16_t *__restrict__ Q;
@@ -70,16 +88,25 @@ struct MfmaArgs {
     const bf16_t *__restrict__ Khat;
     const bf16_t *__restrict__ V;
     bf16_t *__restrict__ O;
-    int Hq, Hkv, n, W, sliding;
+    int Hq, n, W, sliding;
     int ld;                             // rows of room per unit in K, Khat, V (>= n)
     int q_off, nq;                      // query rows are positions q_off .. q_off + nq - 1 of the n keys
-    int units, GH, RT, tiles, hgroups;  // batch x KV heads, heads per tile, rows per head and tile, row tiles, head chunks per unit
-    int xsplit;                         // > 0: XCD-aware order, every unit split this many ways (see the kernel)
+    int GH;                             // heads per tile
+    struct Kind {
+        int rt_log2, tiles, row0;       // log2 of rows per head and tile, row tiles, first query row
+        int first, end;                 // positions of these tiles in the launch's order
+    } kinds[2];                         // whole tiles, split tiles
+    int g;                              // query heads per KV head
+    Divisor by_hkv, by_hgroups, by_w;   // KV heads, head chunks per unit, window
+    Divisor by_units, by_parts;         // batch x KV heads; what an XCD has of them, or of their parts (see the kernel)
+    int xsplit_log2;                    // >= 0: XCD-aware order, every unit split 2^this many ways
+    int blocks, turn_at;                // tiles of the launch; where their order turns (see prefill_mfma_kernel)
+    uint32_t *queue;                    // [8] counters, kQueueStride apart, zero at the start: tiles handed out beyond the first of each work group
     float scale_log2;
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
 // 64 x 16 bytes from base + the lanes' offsets to LDS bytes lds .. lds + 1023 (wave-uniform), lane after lane.  In asm, so
@@ -90,8 +117,8 @@ __device__ __forceinline__ void load_to_lds(const char *base, uint32_t off, uint
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {                   // until at most N of this wave's loads are in flight
-    static_assert(N < 16, "one field of the count");
-    __builtin_amdgcn_s_waitcnt(0x0F70 | N);
+    static_assert(N < 64, "six bits of the count");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
 }
 // The border between two phases: nothing moves across it, in the compiler either.
 __device__ __forceinline__ void phase_barrier() {
@@ -110,90 +137,112 @@ __device__ __forceinline__ void for_each_index(F f) {
     for_each_index_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// the lane's number, worked out where it is needed once per tile instead of held in a register through the walk
+__device__ __forceinline__ int lane_here() {
+    uint32_t none = 0;
+    asm volatile("" : "+s"(none));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
+}
+
+// The tiles of one kind: those at `pos` and the positions the queue hands out after it; returns the first of these past the
+// kind's end.  a: the kernel's argument, of which the walk keeps a few words in registers.
 template <int D, int kSplit>
-__global__ __launch_bounds__(512) void prefill_mfma_kernel(MfmaArgs a) {
+__device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *lds_raw) {
     constexpr int kRowB = D * 2;                // bytes of a row
     constexpr int kSeg = D / 8;                 // 16-byte segments of a row
-    constexpr int kTile = kSpan * kRowB;        // bytes of a tile (keys or values of one turn)
-    constexpr int kIpw = kTile / 1024 / 8;      // 1 KiB loads per wave that fill a tile
+    constexpr int kTile = KB * kSplit * kRowB;  // bytes of a tile (keys or values of one turn, of both groups)
+    constexpr int kBufs = kSplit == 1 ? 3 : 2;  // tiles of each kind in LDS
+    constexpr int kRows = KB * kSplit / 8;      // rows of a tile that a wave fills
+    constexpr int kIpw = kTile / 1024 / 8;      // by this many 1 KiB loads
     constexpr int kLoads = 2 * kIpw;            // loads per wave and turn
-    constexpr int KB = kSpan / kSplit;          // keys per block
     constexpr int NT = KB / 32;                 // score tiles per block
     constexpr int KS = D / 16;                  // k-steps of Q K^T
     constexpr int MT = D / 32;                  // channel tiles of the output
-    extern __shared__ __attribute__((aligned(1024))) char lds_raw[];   // [3] key tiles, [3] value tiles
+    // LDS: [kBufs] key tiles, [kBufs] value tiles, next tile
+    int *const next_tile = (int *)(lds_raw + 2 * kBufs * kTile);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int grp = wave >> 2;
     const int half = lane >> 5, li = lane & 31;
 
-    // ---- which tile.  Work groups go to the 8 XCDs round-robin by index, and within an XCD they start in order, each on a
-    //      compute unit of the shader engine whose turn it is: a long tile late in the order waits while compute units
-    //      elsewhere are idle, and then runs alone.  So the longest (last) tiles of every unit come first, the
-    //      shortest last.  Every XCD has its own L2, and all tiles of a unit stream the same K, K_hat and V: where the units -
-    //      or, with xsplit, units cut by tile index modulo xsplit - deal out evenly, an XCD keeps to its own.
-    int unit, bid;
-    if (a.xsplit > 0) {
-        const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-        const int parts = a.units * a.xsplit / 8;                // of this XCD: xcd, xcd + 8, ...
-        const int part = xcd + 8 * (slot % parts);
-        unit = part / a.xsplit;
-        bid = slot / parts * a.xsplit + part % a.xsplit;
-    } else {
-        unit = blockIdx.x % a.units;
-        bid = blockIdx.x / a.units;
-    }
-    const int hchunk = bid % a.hgroups;
-    const int tile = a.tiles - 1 - bid / a.hgroups;
-    const int b = unit / a.Hkv, hk = unit % a.Hkv;
-    const int g = a.Hq / a.Hkv;
-    const int head0 = hk * g + hchunk * a.GH;
-    const int n = a.n, W = a.W, RT = a.RT;
-    const int i0 = a.q_off + tile * RT, i_last = min(i0 + RT - 1, n - 1);   // first and last query position
+    const int n = a.n;
+    const int my_sr = 32 * (kSplit == 1 ? wave : wave & 3);     // the wave's first score row
 
-    const char *Kp = (const char *)(a.K + (size_t)unit * a.ld * D);
-    const char *Hp = (const char *)(a.Khat + (size_t)unit * a.ld * D);
-    const char *Vp = (const char *)(a.V + (size_t)unit * a.ld * D);
-
-    // ---- this lane's score row: sr = 32 * (wave, or wave of its group) + li (both lane halves) -> query row i0 + r of head
-    //      head0 + hh.  A wave's 32 rows are consecutive rows of one head (RT is a multiple of 32).
-    const int my_sr = 32 * (kSplit == 1 ? wave : wave & 3) + li;
-    const int my_hh = my_sr / RT, my_r = my_sr - my_hh * RT;
-    const int my_i = i0 + my_r;
-    const bool my_valid = my_i < n;
-    // first exact column of row r: start of its square, or of its band (monotone in r either way)
-    auto win_start = [&](int r) { return a.sliding ? max(r - W + 1, 0) : (r / W) * W; };
-    const int my_win = win_start(min(my_i, n - 1));
-    const int wave_first = __builtin_amdgcn_readfirstlane(my_i);         // rows of this wave: wave_first .. + 31
-    const int wave_win_first = win_start(min(wave_first, n - 1)), wave_win_last = win_start(min(wave_first + 31, n - 1));
-
-    // ---- the list of blocks: n_hat blocks from key 0 on for K_hat, then blocks kb0 .. i_last / KB for K
-    const int win_first = win_start(i0), win_last = win_start(i_last);
-    const int n_hat = (win_last + KB - 1) / KB, kb0 = win_first / KB;
-    const int nv = n_hat + i_last / KB - kb0 + 1;
-    const int turns = (nv + kSplit - 1) / kSplit;
+    // ---- the tile
+    const char *Kp, *Hp, *Vp;
+    const bf16_t *q_rows;                       // where position 0 of the wave's head would be in Q
+    bf16_t *o_rows;                             // ... in O
+    int wave_first, wave_win_first, wave_win_last;              // rows of this wave: wave_first .. + 31, their first exact columns
+    bool wave_past;                             // all of them lie past the end
+    int my_i, my_win;                           // this lane's row (both lane halves) and its first exact column
+    int n_hat, kb0, nv, turns;                  // the list of blocks: n_hat from key 0 on for K_hat, then kb0 .. for K
+    // (what a tile needs of the arguments is read for every tile: kept in registers across the walk, it would not fit)
+    auto open_tile = [&](int pos) __attribute__((always_inline)) {
+        auto *ap = (const __attribute__((address_space(4))) MfmaArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+        asm volatile("" : "+s"(ap));
+        const auto &a = *ap;
+        const auto &kind = a.kinds[kSplit - 1];
+        const int n = a.n, W = a.W, RT = 1 << kind.rt_log2;
+        // first exact column of row r: start of its square, or of its band (monotone in r either way)
+        auto win_start = [&](int r) { return a.sliding ? max(r - W + 1, 0) : quotient(r, a.by_w) * W; };
+        const int at = pos - kind.first;
+        int unit, bid;
+        if (a.xsplit_log2 >= 0) {
+            const int xcd = at & 7, slot = at >> 3;
+            const int turn = quotient(slot, a.by_parts);
+            const int part = xcd + 8 * (slot - turn * a.by_parts.d); // of this XCD's: xcd, xcd + 8, ...
+            unit = part >> a.xsplit_log2;
+            bid = (turn << a.xsplit_log2) + (part & ((1 << a.xsplit_log2) - 1));
+        } else {
+            bid = quotient(at, a.by_units);
+            unit = at - bid * a.by_units.d;
+        }
+        const int row_tile = quotient(bid, a.by_hgroups), hchunk = bid - row_tile * a.by_hgroups.d;
+        const int tile = kind.tiles - 1 - row_tile;
+        const int b = quotient(unit, a.by_hkv), hk = unit - b * a.by_hkv.d;
+        const int i0 = a.q_off + kind.row0 + (tile << kind.rt_log2), i_last = min(i0 + RT - 1, n - 1);   // first and last query position
+        Kp = (const char *)(a.K + (size_t)unit * a.ld * D);
+        Hp = (const char *)(a.Khat + (size_t)unit * a.ld * D);
+        Vp = (const char *)(a.V + (size_t)unit * a.ld * D);
+        // a wave's 32 score rows are consecutive rows of one head (RT is a multiple of 32)
+        const int head = hk * a.g + hchunk * a.GH + (my_sr >> kind.rt_log2);
+        wave_first = i0 + (my_sr & (RT - 1));
+        const size_t row0 = ((size_t)b * a.Hq + head) * a.nq - a.q_off;
+        q_rows = a.Q + row0 * D;
+        o_rows = a.O + row0 * D;
+        my_i = min(wave_first + (lane_here() & 31), n - 1);      // (rows past the end: the last one again)
+        wave_past = wave_first >= n;
+        wave_first = min(wave_first, n - 1);
+        wave_win_first = win_start(wave_first);
+        wave_win_last = win_start(min(wave_first + 31, n - 1));
+        my_win = win_start(my_i);
+        const int win_first = win_start(i0), win_last = win_start(i_last);
+        n_hat = (win_last + KB - 1) / KB;
+        kb0 = win_first / KB;
+        nv = n_hat + i_last / KB - kb0 + 1;
+        turns = (nv + kSplit - 1) / kSplit;
+    };
     auto block_of = [&](int v) { return v < n_hat ? v : kb0 + v - n_hat; };
 
     u32x4 qreg[KS];
-    {
-        const bf16_t *my_q =
-            a.Q + (((size_t)b * a.Hq + head0 + my_hh) * a.nq + (min(my_i, n - 1) - a.q_off)) * D + half * 8;
+    auto load_queries = [&]() {
+        const bf16_t *my_q = q_rows + (ptrdiff_t)my_i * D + (lane_here() >> 5) * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qreg[ks] = *(const u32x4 *)(my_q + ks * 16);
-    }
+    };
 
-    // ---- tile loads: a wave fills 8 rows of the tile (of its own group's block), 1 KiB load i the rows r .. r + 64 / kSeg - 1
+    // ---- tile loads: a wave fills kRows rows of the tile (of its own group's block), 1 KiB load i the rows r .. r + 64 / kSeg - 1
     //      of these, lane = (row, segment as stored); the segment it fetches is the stored one permuted by the row number.
     //      A lane's offset from the load's first row never changes, except where the keys end inside a load.
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char *)lds_raw;
     auto keys_perm = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
     auto vals_perm = [](int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); };
     constexpr int kRpl = 64 / kSeg;                              // rows per load
-    static_assert(kIpw * kRpl == 8, "a wave fills 8 rows");
+    static_assert(kIpw * kRpl == kRows, "a wave's loads fill its rows");
     const int lrow = lane / kSeg, lseg = lane % kSeg;
     auto lane_off = [&](int i, bool keys, int row) -> uint32_t { // row: of the load's rows, clamped to the keys there are
-        const int r = wave * 8 + i * kRpl + lrow;
+        const int r = wave * kRows + i * kRpl + lrow;
         return row * kRowB + ((lseg ^ (keys ? keys_perm(r) : vals_perm(r))) << 4);
     };
     uint32_t k_off[kIpw], v_off[kIpw];
@@ -209,13 +258,13 @@ __global__ __launch_bounds__(512) void prefill_mfma_kernel(MfmaArgs a) {
     };
     auto source_of = [&](int turn) -> Source {
         const int v = min(kSplit == 1 ? turn : turn * kSplit + grp, nv - 1);   // (past the end: the last block again, unread)
-        return {v < n_hat ? Hp : Kp, block_of(v) * KB + (wave * 8) % KB};
+        return {v < n_hat ? Hp : Kp, block_of(v) * KB + (wave * kRows) % KB};
     };
     auto load_tile = [&](const char *src, int row, int buf, bool keys) {
-        const uint32_t to = lds0 + (keys ? 0 : 3 * kTile) + buf * kTile + wave * (8 * kRowB);
+        const uint32_t to = lds0 + (keys ? 0 : kBufs * kTile) + buf * kTile + wave * (kRows * kRowB);
 #pragma unroll
         for (int i = 0; i < kIpw; ++i) {
-            if (row + 8 <= n) {
+            if (row + kRows <= n) {
                 load_to_lds(src + (size_t)(uint32_t)row * kRowB + i * (kRpl * kRowB), keys ? k_off[i] : v_off[i], to + i * 1024);
             } else {
                 const int first = min(row + i * kRpl, n - 1);
@@ -225,12 +274,7 @@ __global__ __launch_bounds__(512) void prefill_mfma_kernel(MfmaArgs a) {
     };
 
     f32x16 oacc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[mt][r] = 0.f;
-    float m_run = -INFINITY;
-    float l_run[4] = {0.f, 0.f, 0.f, 0.f};      // four chains of the running sum, this lane half's share
+    float m_run, l_run[4];                      // maximum; four chains of the running sum, this lane half's share
     f32x16 s[NT];                               // raw scores of the current block
     u32x4 pb[2 * NT];                           // its probabilities, bf16, as P V operands
 
@@ -238,7 +282,7 @@ __global__ __launch_bounds__(512) void prefill_mfma_kernel(MfmaArgs a) {
     // per-lane addresses inside a tile: every read below is one of these, an exclusive-or of a few bits, a constant
     const uint32_t k_lane = lds0 + (row_base + li) * kRowB + ((half ^ keys_perm(li)) << 4);
     const int L = lane & 15, lg = (lane >> 4) & 1;
-    const uint32_t v_lane = lds0 + 3 * kTile + (row_base + 4 * half + (L >> 2)) * kRowB + (vals_perm(L >> 2) << 4) + lg * 32 + (L & 3) * 8;
+    const uint32_t v_lane = lds0 + kBufs * kTile + (row_base + 4 * half + (L >> 2)) * kRowB + (vals_perm(L >> 2) << 4) + lg * 32 + (L & 3) * 8;
 
     // A matrix phase: P V of the turn before (value buffer vb), then the scores of this turn (key buffer kb).  Every matrix
     // instruction takes its first operand fresh from LDS; the reads run kAhead instructions in front, from one product
@@ -338,132 +382,160 @@ __global__ __launch_bounds__(512) void prefill_mfma_kernel(MfmaArgs a) {
             }
     };
 
-    // ---- the walk.  Key tile t lies in buffer t % 3, value tile t too; key tile t + 2 and value tile t + 1 are requested
-    //      in turn t's matrix phase, when no wave reads what those buffers held any more (the other group is at most one
-    //      phase behind), and are waited for two phases later.
-    Source s0 = source_of(0), s1 = source_of(1);                 // sources of turns t and t + 1
-    load_tile(s0.keys, s0.row, 0, true);
-    load_tile(s1.keys, s1.row, 1, true);
-    load_tile(Vp, s0.row, 0, false);
-    wait_loads<kLoads>();                                        // key tile 0
-    // (the queries are waited for here: left to the compiler, the wait would stand at their first use inside the loop and there
-    // drain the tile loads, every turn)
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
-    phase_barrier();
-    if (grp == 1) phase_barrier();                               // group B starts one phase later
+    // ---- the walk.  Tile t lies in buffer t % kBufs.  Key tile t + 2 and value tile t + 1 are requested in turn t's vector
+    //      phase, when no wave reads what those buffers held any more - the other group is at most one phase behind, or, with
+    //      kSplit = 2, has rows of its own in every tile - and are waited for two phases later.
+    Source s1;                                                   // source of turn t + 1
+    auto first_loads = [&]() {
+        const Source s0 = source_of(0);
+        s1 = source_of(1);
+        load_tile(s0.keys, s0.row, 0, true);
+        load_tile(s1.keys, s1.row, 1, true);
+        load_tile(Vp, s0.row, 0, false);
+    };
     constexpr std::true_type yes;
     constexpr std::false_type no;
-    int buf = 0;                                                 // turn % 3
-    auto vector_phase = [&](int turn, int next, int prev) {
-        if (grp == 1) wait_loads<0>();                           // key tile turn + 1, value tile turn
+    int buf;                                                     // turn % kBufs
+    auto after = [](int b) { return b == kBufs - 1 ? 0 : b + 1; };
+    auto vector_phase = [&](int turn) {
+        if (kSplit == 1 && grp == 1) wait_loads<0>();            // key tile turn + 1, value tile turn, which group A is about to read
         phase_barrier();
         __builtin_amdgcn_s_setprio(1);
         const Source s2 = source_of(turn + 2);
-        load_tile(s2.keys, s2.row, prev, true);
-        load_tile(Vp, s1.row, next, false);
+        load_tile(s2.keys, s2.row, after(after(buf)), true);
+        load_tile(Vp, s1.row, after(buf), false);
         s1 = s2;
         softmax(kSplit == 1 ? turn : turn * kSplit + grp);
         __builtin_amdgcn_s_setprio(0);
-        if (grp == 0) wait_loads<kLoads>();
+        if (kSplit > 1 || grp == 0) wait_loads<kLoads>();
         phase_barrier();
     };
-    matrix_phase(no, yes, 0, 0);
-    vector_phase(0, 1, 2);
-    for (int turn = 1; turn < turns; ++turn) {
-        const int prev = buf;
-        buf = buf == 2 ? 0 : buf + 1;
-        const int next = buf == 2 ? 0 : buf + 1;
-        matrix_phase(yes, yes, prev, buf);
-        vector_phase(turn, next, prev);
-    }
-    matrix_phase(yes, no, buf, 0);
-    if (grp == 0) phase_barrier();                               // (group B's last softmax phase)
-    wait_loads<0>();                                             // no load into LDS outlives its wave
-
-    // ---------------------------------------------------------------- epilogue
-    float l_tot = (l_run[0] + l_run[1]) + (l_run[2] + l_run[3]);
-    l_tot += __shfl_xor(l_tot, 32);
-    bf16_t *orow = a.O + (((size_t)b * a.Hq + head0 + my_hh) * a.nq + (my_i - a.q_off)) * D;
-    auto store = [&](int mt, float inv) {
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            u32x2 w;
-            w[0] = pack_bf16x2(oacc[mt][4 * q4 + 0] * inv, oacc[mt][4 * q4 + 1] * inv);
-            w[1] = pack_bf16x2(oacc[mt][4 * q4 + 2] * inv, oacc[mt][4 * q4 + 3] * inv);
-            *(u32x2 *)(orow + mt * 32 + 8 * q4 + 4 * half) = w;
-        }
+    // A tile's outputs are packed, the next tile's loads go out, then the outputs: its first keys are on their way while this
+    // one is stored.  (Next tile, or blocks where there is none: `ticket`.)
+    const int queues = a.xsplit_log2 >= 0 ? 8 : 1, blocks = a.blocks, end = a.kinds[kSplit - 1].end;
+    uint32_t *const queue = a.queue + (pos & (queues - 1)) * kQueueStride;
+    const int handed_out = (int)gridDim.x + (pos & (queues - 1));
+    int ticket = blocks;
+    // (asked for three turns before the tile ends: the answer takes 2 us, and whoever asks first gets the longest tile left)
+    auto ask = [&](int turn) __attribute__((always_inline)) {
+        if (turn == max(turns - 3, 0) && wave == 0 && blocks > (int)gridDim.x && lane_here() == 0)
+            ticket = handed_out + queues * (int)atomicAdd(queue, 1u);
     };
-    if constexpr (kSplit == 1) {
-        if (my_valid) {
+    open_tile(pos);
+    load_queries();
+    first_loads();
+    wait_loads<0>();
+    while (true) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[mt][r] = 0.f;
+        m_run = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) l_run[k] = 0.f;
+        buf = 0;
+        // (the queries are waited for here: left to the compiler, the wait would stand at their first use inside the loop and
+        // there drain the tile loads, every turn)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+        phase_barrier();
+        if (grp == 1) phase_barrier();                           // group B starts one phase later
+        ask(0);
+        matrix_phase(no, yes, 0, 0);
+        vector_phase(0);
+        for (int turn = 1; turn < turns; ++turn) {
+            const int prev = buf;
+            buf = after(buf);
+            ask(turn);
+            matrix_phase(yes, yes, prev, buf);
+            vector_phase(turn);
+        }
+        matrix_phase(yes, no, buf, 0);
+        if (grp == 0) phase_barrier();                           // (group B's last softmax phase)
+        wait_loads<0>();                                         // no load into LDS outlives its tile
+
+        // ------------------------------------------------------------ epilogue
+        float l_tot = (l_run[0] + l_run[1]) + (l_run[2] + l_run[3]);
+        l_tot += __shfl_xor(l_tot, 32);
+        if (wave == 0 && lane_here() == 0) *next_tile = ticket;
+        constexpr int MO = MT / kSplit;                          // channel tiles that this wave stores
+        u32x2 packed[MO][4];
+        auto pack = [&](int mo, const f32x16 &o, float inv) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+                packed[mo][q4] = u32x2{pack_bf16x2(o[4 * q4 + 0] * inv, o[4 * q4 + 1] * inv), pack_bf16x2(o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv)};
+        };
+        __syncthreads();                                         // the tiles are done with
+        pos = __builtin_amdgcn_readfirstlane(*next_tile);
+        const int lane = lane_here();
+        if constexpr (kSplit == 1) {
             const float inv = 1.f / l_tot;
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) store(mt, inv);
-        }
-    } else {
-        // wave w of group A and wave w of group B hold the same rows: each hands the other half of its channels over and
-        // finishes its own half
-        constexpr int MH = MT / 2;
-        float *xo = (float *)lds_raw;                            // [group][wave of the group][MH][16][64]
-        float *xm = xo + 2 * 4 * MH * 16 * 64;                   // [group][wave of the group][64][2] maximum, sum
-        const int w4 = wave & 3;
-        __syncthreads();                                         // the tiles are done with
+            for (int mt = 0; mt < MT; ++mt) pack(mt, oacc[mt], inv);
+        } else {
+            // wave w of group A and wave w of group B hold the same rows: each hands the other half of its channels over and
+            // finishes its own half
+            float *xo = (float *)lds_raw;                        // [group][wave of the group][MO][16][64]
+            float *xm = xo + 2 * 4 * MO * 16 * 64;               // [group][wave of the group][64][2] maximum, sum
+            const int w4 = wave & 3, other = 1 - grp;
 #pragma unroll
-        for (int mh = 0; mh < MH; ++mh)
+            for (int mo = 0; mo < MO; ++mo)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                xo[(((grp * 4 + w4) * MH + mh) * 16 + r) * 64 + lane] = grp == 0 ? oacc[MH + mh][r] : oacc[mh][r];
-        xm[((grp * 4 + w4) * 64 + lane) * 2] = m_run;
-        xm[((grp * 4 + w4) * 64 + lane) * 2 + 1] = l_tot;
-        __syncthreads();
-        const int other = 1 - grp;
-        const float m2 = xm[((other * 4 + w4) * 64 + lane) * 2], l2 = xm[((other * 4 + w4) * 64 + lane) * 2 + 1];
-        const float M = fmaxf(m_run, m2);                        // (a row sees its own key: one of the two is finite)
-        const float f1 = __builtin_amdgcn_exp2f(m_run - M), f2 = __builtin_amdgcn_exp2f(m2 - M);
-        const float inv = 1.f / (l_tot * f1 + l2 * f2);
+                for (int r = 0; r < 16; ++r)
+                    xo[(((grp * 4 + w4) * MO + mo) * 16 + r) * 64 + lane] = grp == 0 ? oacc[MO + mo][r] : oacc[mo][r];
+            xm[((grp * 4 + w4) * 64 + lane) * 2] = m_run;
+            xm[((grp * 4 + w4) * 64 + lane) * 2 + 1] = l_tot;
+            __syncthreads();
+            const float m2 = xm[((other * 4 + w4) * 64 + lane) * 2], l2 = xm[((other * 4 + w4) * 64 + lane) * 2 + 1];
+            const float M = fmaxf(m_run, m2);                    // (a row sees its own key: one of the two is finite)
+            const float f1 = __builtin_amdgcn_exp2f(m_run - M), f2 = __builtin_amdgcn_exp2f(m2 - M);
+            const float inv = 1.f / (l_tot * f1 + l2 * f2);
 #pragma unroll
-        for (int mh = 0; mh < MH; ++mh)
+            for (int mo = 0; mo < MO; ++mo) {
+                f32x16 o;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float x = xo[(((other * 4 + w4) * MH + mh) * 16 + r) * 64 + lane];
-                if (grp == 0)
-                    oacc[mh][r] = oacc[mh][r] * f1 + x * f2;
-                else
-                    oacc[MH + mh][r] = oacc[MH + mh][r] * f1 + x * f2;
+                for (int r = 0; r < 16; ++r) {
+                    const float x = xo[(((other * 4 + w4) * MO + mo) * 16 + r) * 64 + lane];
+                    o[r] = (grp == 0 ? oacc[mo][r] : oacc[MO + mo][r]) * f1 + x * f2;
+                }
+                pack(mo, o, inv);
             }
-        if (my_valid) {
-#pragma unroll
-            for (int mh = 0; mh < MH; ++mh) {
-                if (grp == 0)
-                    store(mh, inv);
-                else
-                    store(MH + mh, inv);
-            }
+            __syncthreads();                                     // the exchange is done with
         }
+        bf16_t *const orow = o_rows + (ptrdiff_t)my_i * D + 4 * (lane >> 5) + (kSplit > 1 ? grp * (D / 2) : 0);
+        const bool more = pos < end, stores = !wave_past;
+        if (more) {
+            open_tile(pos);
+            load_queries();
+            first_loads();
+        }
+        if (stores) {
+#pragma unroll
+            for (int mo = 0; mo < MO; ++mo)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mo * 32 + 8 * q4) = packed[mo][q4];
+            wait_loads<4 * MO>();                                // for all but the stores
+        } else {
+            wait_loads<0>();
+        }
+        if (!more) return pos;
     }
 }
 
-template <int D, int kSplit>
-void launch_tiles(const PrefillArgs &p, MfmaArgs &a, hipStream_t s) {
-    const int units = p.B * p.Hkv, g = p.Hq / p.Hkv;
-    a.GH = (g % 4 == 0) ? 4 : (g % 2 == 0) ? 2 : 1;
-    a.RT = 256 / kSplit / a.GH;
-    a.tiles = (p.nq + a.RT - 1) / a.RT;
-    a.hgroups = g / a.GH;
-    a.units = units;
-    // XCD-aware order needs units * xsplit parts to deal out evenly over 8 XCDs and a unit to split evenly
-    a.xsplit = 0;
-    for (int sp = 1; sp <= 8; sp *= 2)
-        if ((units * sp) % 8 == 0) {
-            if ((a.tiles * a.hgroups) % sp == 0 && sp < 8) a.xsplit = sp;
-            break;
-        }
-    constexpr int lds = 6 * kSpan * D * 2;
-    static_assert(kSplit == 1 || lds >= 2 * 4 * (D / 64) * 16 * 64 * 4 + 2 * 4 * 64 * 2 * 4, "the merge reuses the tiles' room");
-    static std::atomic<uint64_t> lds_set;                        // per instantiation, one bit per device
-    ensure_dynamic_lds((const void *)prefill_mfma_kernel<D, kSplit>, lds, lds_set);
-    const size_t blocks = (size_t)units * a.tiles * a.hgroups;
-    hipLaunchKernelGGL((prefill_mfma_kernel<D, kSplit>), dim3((unsigned)blocks), dim3(512), lds, s, a);
+// Work groups go to the 8 XCDs round-robin by index, and every work group takes further tiles from a counter, in order, so no
+// compute unit is idle while there are tiles: the longest (last) tiles of every unit come first, the shortest last.  (One work
+// group per tile instead is started in order, each on a compute unit of the shader engine whose turn it is, and waits for
+// that one.)  Every XCD has its own L2, and all tiles of a unit stream the same K, K_hat and V: where the units - or
+// units cut by tile index modulo 2^xsplit_log2 - deal out evenly, an XCD keeps to its own, with a counter of its own.
+// Where all tiles are resident at once, two to a compute unit, the second ones come in ascending order, so that short ones share
+// with long ones.
+template <int D>
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(MfmaArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
+    int pos = blockIdx.x;
+    if (pos >= a.turn_at) pos = a.blocks - 8 - ((pos - a.turn_at) & ~7) + (pos & 7);
+    if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2>(a, pos, lds_raw);
+    if (pos < a.kinds[0].end) tiles_of_kind<D, 1>(a, pos, lds_raw);
 }
 
 template <int D>
@@ -475,7 +547,6 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     a.V = (const bf16_t *)p.V;
     a.O = (bf16_t *)p.O;
     a.Hq = p.Hq;
-    a.Hkv = p.Hkv;
     a.n = p.n;
     a.W = p.W;
     a.sliding = p.sliding;
@@ -483,22 +554,61 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     a.q_off = p.q_off;
     a.nq = p.nq;
     a.scale_log2 = p.scale_log2;
-    // Whole or split tiles: a split one has half the rows and takes 0.8 of the time, so splitting shortens the longest tile and
-    // costs 1.6 times the work.  A launch lasts at least as long as its longest tile, as the work per compute unit, and,
-    // with more tiles than compute units, as two of the longest that have to share one (which the pieces of a chunked
-    // prefill, all of about one length, come up against); lengths run evenly from the first row's to the last row's.
-    // Splitting has to promise a tenth.  In units of one whole tile over 64 keys.
-    const int g = p.Hq / p.Hkv, heads = (g % 4 == 0) ? 4 : (g % 2 == 0) ? 2 : 1;
-    const double cus = device_cu_count(), shortest = p.q_off / 64.0, longest = p.n / 64.0;
-    auto lasts = [&](int rows, double per_tile) {
-        const double tiles = (double)p.B * p.Hkv * (g / heads) * ((p.nq + rows - 1) / rows);
-        const double shared = tiles > cus ? 2.0 * (longest - (longest - shortest) * cus / tiles) : 0.0;
-        return per_tile * fmax(fmax(longest, shared), tiles * 0.5 * (shortest + longest) / cus);
-    };
-    if (lasts(128 / heads, 0.8) < 0.9 * lasts(256 / heads, 1.0))
-        launch_tiles<D, 2>(p, a, s);
-    else
-        launch_tiles<D, 1>(p, a, s);
+    a.queue = p.queue;
+    const int units = p.B * p.Hkv, g = p.Hq / p.Hkv;
+    a.GH = (g % 4 == 0) ? 4 : (g % 2 == 0) ? 2 : 1;
+    const int rt = 256 / a.GH, hgroups = g / a.GH;               // rows of a whole tile
+    a.g = g;
+    a.by_hkv = divisor(p.Hkv);
+    a.by_hgroups = divisor(hgroups);
+    a.by_w = divisor(p.W);
+    a.by_units = divisor(units);
+    // as many work groups as are resident at once: one per compute unit, at head_dim 64 two (64 KB of LDS, 128 registers)
+    const int cus = device_cu_count() >= 8 ? device_cu_count() & ~7 : 8, slots = D == 64 ? 2 * cus : cus;
+    // XCD-aware order needs units * 2^xsplit parts to deal out evenly over 8 XCDs and a unit's tiles, of either kind, to split
+    // evenly
+    int xsplit = 0;
+    while ((units << xsplit) % 8 != 0) ++xsplit;
+    auto even = [&](int tiles) { return (tiles * hgroups) % (1 << xsplit) == 0; };
+    // Whole tiles for the first rows, split ones for the rest.  Of the ways to cut, the one that promises to be done first: a
+    // launch lasts at least as long as its longest tile, as the work per compute unit, and, with more tiles than
+    // compute units, as the two that have to share one (which the pieces of a chunked prefill, all of about one length, come
+    // up against).  In units of one whole tile over 64 keys: a tile has kOpen of overhead, a split one takes kSplitTurn for 64 keys.
+    constexpr double kOpen = 2.2, kSplitTurn = 0.6;
+    const int all = (p.nq + rt - 1) / rt, columns = units * hgroups;
+    double best = INFINITY;
+    bool best_even = false;
+    const int step = all > 32 ? (all + 31) / 32 : 1;
+    for (int whole = 0;; whole = min(whole + step, all)) {       // row tiles that stay whole
+        const int rows = min(whole * rt, p.nq), split = (p.nq - rows + rt / 2 - 1) / (rt / 2);
+        auto length = [&](int level) {                           // of the level-th longest row tile
+            return level < split ? kOpen + kSplitTurn * (p.n - level * (rt / 2)) / 64.0
+                                 : kOpen + (p.q_off + rows - (level - split) * rt) / 64.0;
+        };
+        const double work = split * 0.5 * (length(0) + length(split - 1)) + whole * 0.5 * (length(split) + length(split + whole - 1));
+        const int blocks = columns * (whole + split);
+        double lasts = fmax(work * columns / cus, split > 0 ? length(0) : 0.0);
+        if (whole > 0) lasts = fmax(lasts, length(split));
+        if (blocks > cus) lasts = fmax(lasts, length((cus - 1) / columns) + length(cus / columns));
+        const bool ordered = xsplit < 3 && even(whole) && even(split);
+        if (!ordered) lasts *= 1.1;                              // (every XCD streams every unit)
+        if (lasts < best) {
+            best = lasts;
+            best_even = ordered;
+            a.kinds[1] = {__builtin_ctz(rt / 2), split, rows, 0, columns * split};
+            a.kinds[0] = {__builtin_ctz(rt), whole, 0, columns * split, blocks};
+        }
+        if (whole == all) break;
+    }
+    a.blocks = a.kinds[0].end;
+    a.xsplit_log2 = best_even ? xsplit : -1;
+    if (best_even) a.by_parts = divisor((units << xsplit) / 8);
+    a.turn_at = D == 64 && a.blocks > cus && a.blocks <= slots && best_even ? cus : a.blocks;
+    constexpr int lds = 4 * KB * 2 * D * 2 + 16;                 // split tiles take more
+    static_assert(lds >= 6 * KB * D * 2 + 16 && lds >= 2 * 4 * (D / 64) * 16 * 64 * 4 + 2 * 4 * 64 * 2 * 4, "whole tiles, the merge");
+    static std::atomic<uint64_t> lds_set;                        // per instantiation, one bit per device
+    ensure_dynamic_lds((const void *)prefill_mfma_kernel<D>, lds, lds_set);
+    hipLaunchKernelGGL((prefill_mfma_kernel<D>), dim3(a.blocks < slots ? a.blocks : slots), dim3(512), lds, s, a);
 }
 
 }  // namespace

@@ -99,6 +99,26 @@ def test_whole_tiles_of_large_launches(window_mode, d, B, Hq, Hkv, n, W):
     assert df.prefill_worst_error(Q, K, V, khat, W, window_mode == da.DA_WINDOW_SLIDING, [O]) <= 2e-2
 
 
+@pytest.mark.parametrize("d,B,Hq,Hkv,n,W", [(128, 1, 20, 5, 4030, 256), (64, 2, 16, 2, 3001, 100), (64, 5, 12, 6, 700, 64),
+                                            (128, 3, 8, 8, 1100, 55)])
+def test_launches_that_hand_tiles_out(d, B, Hq, Hkv, n, W):
+    """Whole and split tiles in one launch, more tiles than work groups, ragged last ones; and the same rows as chunked
+    prefill, whose second piece starts inside a tile of the first."""
+    import torch
+    import dense_form as df
+    from util import to_dev
+    Q, K, V = (to_dev(x, "bf16") for x in _walks(701, B, Hq, Hkv, n, d, "bf16"))
+    khat, mask = df.reference_keys(K, 0.2)
+    cache = da.Cache(B, Hq, Hkv, d, n, max(W, 64), 0.2, torch.bfloat16)
+    cut = n // 3 + 5
+    pieces = [da.delta_attn_prefill_append(cache, *(x[:, :, r].contiguous() for x in (Q, K, V)), 0.2, W)[0]
+              for r in (slice(0, cut), slice(cut, n))]
+    for O in (da.delta_attn_prefill(Q, K, V, 0.2, W)[0], torch.cat(pieces, 2)):
+        assert torch.isfinite(O).all()
+        assert df.prefill_worst_error(Q, K, V, khat, W, False, [O]) <= 2e-2
+    cache.close()
+
+
 def test_unaligned_keys_take_the_kernel_that_allows_them():
     """K and V one element off 16-byte alignment: same results within rounding."""
     import torch
