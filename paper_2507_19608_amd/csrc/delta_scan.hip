@@ -115,12 +115,12 @@ int timing_collect(double *ms_per_stage, int *calls_per_stage) {
 //       are exact, and a run usually meets its old chain (both fire at the same row) after a few rows, so a round or
 //       two does it.  Reference keys leave LDS in 16-byte pieces.
 //   scan_settle_kernel    prompts of several segments: one work group per unit and 64 channels does the same between
-//       segments - compares every segment's start with its predecessor's end and walks what differs again - and adds
-//       up nnz.
+//       segments - compares every segment's start with its predecessor's end and walks what differs again, in parallel as
+//       long as that settles them, else in order - and adds up nnz.
 //
 // Exact for any input.  The wave ballot of the threshold decision is the mask word itself.
-// 4 x 5 x 8192 rows of 128 (86 MB in and out, 5 % jumps): 62 -> 39 us, of which copying the rows through LDS takes 20; with
-// 1 % jumps and chains that meet late 1247 -> 239 us; 5 x 4096 rows: 31 -> 21 us a call.
+// Against two passes and an ordered repair with row-by-row loads: 20 x 8192 rows of 128 in bf16 (86 MB in and out, 5 % jumps) 62 ->
+// 38 us a call; keys that drift steadily, whose guesses are nearly all wrong, 872 -> 228 us.
 constexpr int kScanLdsMax = 144 * 1024;    // a one-segment prompt: 128 KB of rows, their mask words, the runs' end values
 
 // lane L of (lo, hi) takes the two halves of a wave mask: two instructions, where comparing the lane number and selecting
@@ -391,6 +391,48 @@ __global__ __launch_bounds__(512) void scan_segments_kernel(ScanArgs<T> g) {
 
 constexpr int kSettleWaves = 16;
 
+// The value a segment's rows t0 .. t1 - 1 end on from `held`, without writing anything: once the chain meets the recorded one
+// in every lane (Hp: its reference keys) it ends on the recorded end.  Only the compare and the select of Eq. 2-3 per row, 32
+// rows in flight behind the 32 being walked.
+template <typename T>
+__device__ __forceinline__ float chase(const T *Kp, const T *Hp, int d, int t0, int t1, float held, float end, bool active,
+                                       float theta) {
+    constexpr int N = 32;
+    auto fetch = [&](T (&k)[N + 1], int tb) {                    // (the last row again past the end: it fires once at most)
+#pragma unroll
+        for (int u = 0; u < N; ++u) k[u] = Kp[(size_t)min(tb + u, t1 - 1) * d];
+        k[N] = Hp[(size_t)min(tb + N - 1, t1 - 1) * d];
+    };
+    auto work = [&](const T (&kk)[N + 1], int tb) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const float k = to_f32(kk[u]);
+            held = fabsf(k - held) > theta ? k : held;
+        }
+        if (!__any(active && __float_as_uint(held) != __float_as_uint(to_f32(kk[N])))) {
+            held = end;
+            return false;
+        }
+        return tb + N < t1;
+    };
+    T ka[N + 1], kb[N + 1];
+    fetch(ka, t0);
+    for (int tb = t0;; tb += 2 * N) {
+        fetch(kb, tb + N);
+        if (!work(ka, tb)) break;
+        fetch(ka, tb + 2 * N);
+        if (!work(kb, tb + N)) break;
+    }
+    return held;
+}
+
+// Rounds of walking wrong segments again, in parallel, as long as every round leaves at most three quarters of them (which
+// together is four rounds' work: a steady drift in 63 segments takes 47, 31, 15).  Where channels stay quiet over whole segments a round
+// does not: an end value then travels one segment a round, and rounds until it arrives would make the time
+// quadratic in the number of segments.  So the first wave settles what is left in order - it only chases the end values, each
+// segment once - and one more round, which now has the right starts, writes.
+// 20 units x 8192 rows of 128 in bf16 where nothing fires: 2440 -> 677 us; 5 x 65536: 124.4 -> 5.03 ms; 4 x 16384 in fp32: 14.7 -> 1.13 ms
+// (rounds alone -> this); keys that drift steadily take what they did, 228 us for 20 x 8192.
 template <typename T>
 __global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_kernel(ScanArgs<T> g) {
     __shared__ unsigned long long total;
@@ -407,10 +449,12 @@ __global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_kernel(ScanArgs
     unsigned long long sum = 0;
     for (int s = tid; s < nseg; s += 64 * kSettleWaves) sum += g.counts[((size_t)unit * nseg + s) * gridDim.x + group];
     long long adjust = 0;
-    for (int round = 0; round < nseg; ++round) {
-        bool again = false;
-        constexpr int G = 4;                                     // segments whose boundary values are fetched together
+    constexpr int G = 4;                                         // segments whose boundary values are fetched together
+    bool ordered = false;
+    for (int before = 0x7fffffff;;) {
+        int walked = 0;
         for (int sb = 1 + wave; sb < nseg; sb += G * kSettleWaves) {
+            uint32_t wrong = 0;                                  // bit u: segment sb + u * kSettleWaves
             float st[G], pe[G];
 #pragma unroll
             for (int u = 0; u < G; ++u) {
@@ -419,21 +463,50 @@ __global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_kernel(ScanArgs
                 pe[u] = load_f32(ep, (s - 1) * d);
             }
 #pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const int s = sb + u * kSettleWaves;
-                const bool wrong = s < nseg && active && __float_as_uint(st[u]) != __float_as_uint(pe[u]);
-                if (!__any(wrong)) continue;
-                again = true;
-                const float end = load_f32(ep, (size_t)s * d);
-                const float e = rewalk(Kp, d, Hp, d, Mp, wpr, word + 1 < wpr, s * g.S, min(n, s * g.S + g.S), st[u], pe[u],
-                                       end, active, g.theta, &adjust);
+            for (int u = 0; u < G; ++u)
+                wrong |= (uint32_t)(sb + u * kSettleWaves < nseg && __any(active && __float_as_uint(st[u]) != __float_as_uint(pe[u]))) << u;
+            walked += __popc(wrong);
+            for (; wrong; wrong &= wrong - 1) {
+                const int s = sb + __builtin_ctz(wrong) * kSettleWaves;
+                const float from = load_f32(ep, (size_t)(s - 1) * d);
+                const float e = rewalk(Kp, d, Hp, d, Mp, wpr, word + 1 < wpr, s * g.S, min(n, s * g.S + g.S),
+                                       load_f32(sp, (size_t)s * d), from, load_f32(ep, (size_t)s * d), active, g.theta, &adjust);
                 if (active) {
-                    store_exact(sp, (size_t)s * d, pe[u]);
+                    store_exact(sp, (size_t)s * d, from);
                     store_exact(ep, (size_t)s * d, e);
                 }
             }
         }
-        if (!__syncthreads_or(again)) break;
+        const int all = __syncthreads_count(lane < walked);      // (at most 64 a wave: a lower bound where segments are many)
+        if (all == 0 || ordered) break;
+        if (4ll * all > 3ll * before) {
+            if (wave == 0) {
+                float held = load_f32(ep, 0);                    // (the first segment is exact)
+                for (int sb = 1; sb < nseg; sb += G) {
+                    float st[G], en[G];
+#pragma unroll
+                    for (int u = 0; u < G; ++u) {
+                        const size_t s = min(sb + u, nseg - 1);
+                        st[u] = load_f32(sp, s * d);
+                        en[u] = load_f32(ep, s * d);
+                    }
+#pragma unroll 1
+                    for (int u = 0; u < G && sb + u < nseg; ++u) {
+                        const float start = u == 0 ? st[0] : u == 1 ? st[1] : u == 2 ? st[2] : st[3];
+                        const float end = u == 0 ? en[0] : u == 1 ? en[1] : u == 2 ? en[2] : en[3];
+                        const size_t t0 = (size_t)(sb + u) * g.S;
+                        if (__any(active && __float_as_uint(held) != __float_as_uint(start)))
+                            held = chase(Kp, Hp, d, (int)t0, min(n, (int)t0 + g.S), held, end, active, g.theta);
+                        else
+                            held = end;
+                        if (active) store_exact(ep, (size_t)(sb + u) * d, held);
+                    }
+                }
+            }
+            ordered = true;
+            __syncthreads();
+        }
+        before = all;
     }
     if (lane == 0) sum += (unsigned long long)adjust;
     if (sum) atomicAdd(&total, sum);
