@@ -19,7 +19,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline size_t elt_size(int dtype) { return dtype == DA_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t khat, scan, scan_total, queue, total;
+    size_t khat, scan, scan_total, queue, copies, total;
 };
 
 // what prefill_mfma_supported reads, for a prefill of p's rows behind `cached` rows
@@ -60,10 +60,12 @@ WsLayout layout(const da_prefill_params *p) {
     w.scan = off;
     off += align_up(delta_scan_scratch_bytes(p->dtype, (int)units, p->seq_len, p->head_dim));
     w.scan_total = off;
-    // Room for the attention launch's counters, and else unused: the size a caller asked for has always covered 8 bytes per
-    // key element and 4 per row here, and plans that were sized with it stay comparable.
+    // The attention launch's counters, then room for aligned copies of K and V (4 bytes per key element, launch_copy_aligned).
+    // The size is the 8 bytes per key element and 4 per row that it has been since surviving entries were written out here:
+    // callers size their buffers by it, and what the built-in scratch is too small for does not change.
     w.queue = off;
-    static_assert(kPrefillQueueBytes <= 64 * 8, "one row of head_dim 64 makes room for it");
+    w.copies = off + kPrefillQueueBytes;
+    static_assert(kPrefillQueueBytes + 64 * 4 <= 64 * 8 + kAlign && kPrefillQueueBytes % 16 == 0, "one row of head_dim 64 makes room for them");
     off += align_up(rows * p->head_dim * 8) + align_up(rows * sizeof(uint32_t));
     w.total = off;
     return w;
@@ -236,9 +238,11 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.O = O;
     stage_begin(kStageAttn, s);
     bool launched = true;
-    if (prefill_mfma_supported(a))
+    if (prefill_mfma_supported(a)) {
+        const size_t bytes = (size_t)units * p->seq_len * p->head_dim * 2;
+        launch_copy_aligned(a, ws + w.copies, ws + w.copies + bytes, bytes, s);
         launch_prefill_mfma(a, s);
-    else
+    } else
         launched = launch_prefill_generic(a, s);
     stage_end(kStageAttn, s);
     if (!launched) return DA_ERR_UNSUPPORTED;

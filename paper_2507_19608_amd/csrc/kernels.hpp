@@ -50,8 +50,10 @@ void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
 // no instantiation.  q_off and ld are not for it.
 bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);
-// Matrix-core path: bf16, head_dim 64 or 128, K and V aligned to 16 bytes.
+// Matrix-core path: bf16, head_dim 64 or 128.  K and V have to be aligned to 16 bytes when it is launched.
 bool prefill_mfma_supported(const PrefillArgs &a);
+// K and V that are not are copied to room_k, room_v (`bytes` each, aligned), which take their place in `a`.
+void launch_copy_aligned(PrefillArgs &a, void *room_k, void *room_v, size_t bytes, hipStream_t s);
 void launch_prefill_mfma(const PrefillArgs &a, hipStream_t s);
 // compute units of the current device (256 if it cannot be asked)
 int device_cu_count();
