@@ -27,8 +27,9 @@ struct da_cache {
     int64_t len;          // rows held (all sequences of the batch advance together)
     int device;
     int cus;              // compute units of `device` (0 until the first decode step has asked)
-    int nck;              // checkpoints per unit: max_seq / kChunk + 1
+    int nck;              // checkpoints per unit: max_seq / kChunk + 1, or 1 in the column-run layout
     int max_chunks;       // (max_seq + kChunk - 1) / kChunk
+    int max_parts;        // partial rows per query head that one decode step can leave
     int vrows;            // max_seq rounded up to a whole chunk (row capacity of V)
     int plan_merge;       // launch plan of the column-run layout: -1 auto, 0 spread over work groups, 1 one per unit
     int plan_slots;       // wave slots a launch is sized for, 0 = from the device
@@ -36,34 +37,43 @@ struct da_cache {
                           //    head: the column-run layout below
     // per (batch, KV head) unit, all device memory:
     uint32_t *mask;       // [units][max_seq][d/32]   delta mask bits
-    // Surviving key values (the new reference values at the positions the mask marks), run_room_stride(d)
-    // elements of room per chunk.
-    //   row layout (fast == 0): row after row, channels ascending inside a row, appended one row per step.
+    // Surviving key values (the new reference values at the positions the mask marks).
+    //   row layout (fast == 0): row after row, channels ascending inside a row, appended one row per step; kChunk * d
+    //     elements of room per chunk.
     //   column-run layout (fast == 1): written once per chunk, when its last row has arrived ("sealed"):
     //     for every channel in ascending order one run = the reference value held when the chunk starts,
     //     then the channel's surviving values in row order.  Rows of an unsealed chunk are always inside
     //     the decode window (window >= kChunk, or the whole cache), where raw keys are used, so they need no run.  Every
     //     64 channels have their own part of the room, kRunHalfRoom elements, with their column masks and starts in front.
-    void *surv;           // [units][max_chunks][run_room_stride(d)]
+    void *surv;           // [units][max_chunks][kChunk * d], or [run_room_stride(d)]
     uint32_t *ccnt;       // [units][max_chunks]      row layout: elements stored in the chunk's room; column-run
                           //                          layout: those of channels 0..63 in the low half, those of
                           //                          channels 64.. in the high half
-    void *ck;             // [units][nck][d]          ck[m] = reference key after row m*kChunk - 1 (m >= 1)
+    void *ck;             // fast == 0: [units][nck][d], ck[m] = reference key after row m*kChunk - 1 (m >= 1);
+                          // fast == 1: [units][d], reference key in front of the chunk that is not sealed yet (the sealed
+                          //            ones have theirs in their runs)
     void *khat;           // [units][d]               current reference key
     void *ring;           // [units][Wd][d]           raw key of position p at slot p % Wd
     void *V;              // fast == 0: [units][vrows / 8][d][8], 8 rows interleaved per channel;
                           // fast == 1: [units][vrows / 16][d][16], 16 rows per channel in matrix-core
                           //            accumulator order (slot 8 k + i holds row 8 (i / 4) + 4 k + i % 4)
     uint64_t *nnz;        // [units]
-    float *part;          // [B*Hq][max_chunks][d + 4] partial (o[d], m, l, 2 unused) rows of one decode step
+    float *part;          // [B*Hq][max_parts][d + 4] partial (o[d], m, l, 2 unused) rows of one decode step
     uint32_t *arrived;    // [units] work groups of a unit that have left their partial rows (column-run layout); 0 between steps
     da_prefix *pf;        // host pointer, NULL until delta_attn_prefill_append has run on this cache
 };
 
-// Elements of room per chunk for the surviving values: one per key element and one carried-in value per channel; in the
-// column-run layout also, per 64 channels, their column masks and where their runs start (768 bytes, see decode_runs.hip).
+// Column-run layout: elements of room per chunk - one per key element, one carried-in value per channel and, per 64 channels, their
+// column masks and where their runs start (768 bytes, see decode_runs.hip).  Those are what makes a step's k_hat look-up one
+// matrix product; a cache with few query heads per KV head is larger for them, since the partial rows and checkpoints that this
+// layout does not need weigh less there: 273 -> 279 bytes a row and KV head with one (head_dim 64, 32 K rows), 286 -> 280 with
+// four; 546 -> 558 and 570 -> 559 at head_dim 128.
 constexpr int kRunHalfRoom = 384 + (kChunk + 1) * 64;
-__host__ __device__ inline size_t run_room_stride(int d) { return (size_t)((d + 63) / 64) * kRunHalfRoom; }
+__host__ __device__ inline size_t run_room_stride(int d) { return (size_t)(d / 64) * kRunHalfRoom; }
+// work groups that share a unit in a decode step, at most: what the last of them can merge in a few round trips
+constexpr int kMaxParts = 32;
+// ... and the walkers of each (8 waves, one or two to a walker)
+inline int run_walkers(int d) { return d == 64 ? 8 : 4; }
 
 // floats per partial row: o[d], running maximum, running sum, padded to a 16-byte multiple
 __host__ __device__ inline int part_stride(int d) { return d + 4; }

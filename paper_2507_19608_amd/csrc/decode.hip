@@ -25,10 +25,10 @@ __device__ __forceinline__ size_t v_index(int unit, int vrows, int d, int t, int
     return ((size_t)unit * (vrows >> 3) + (t >> 3)) * ((size_t)d * 8) + (size_t)ch * 8 + (t & 7);
 }
 
-// surviving key values of one chunk of kChunk rows: row after row, channel order, room of (kChunk + 1) * d
+// surviving key values of one chunk of kChunk rows: row after row, channel order, room of kChunk * d
 template <typename T>
 __device__ __forceinline__ T *surv_chunk(const da_cache &c, int unit, int chunk) {
-    return (T *)c.surv + ((size_t)unit * c.max_chunks + chunk) * run_room_stride(c.d);
+    return (T *)c.surv + ((size_t)unit * c.max_chunks + chunk) * ((size_t)kChunk * c.d);
 }
 
 __device__ __forceinline__ float wave_max(float v) {
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(64) void decode_chunk_kernel(da_cache c, const T *_
         __syncthreads();
         pb[lane] = p;
         __syncthreads();
-        float *out = c.part + (((size_t)b * c.Hq + h) * c.max_chunks + chunk) * part_stride(d);
+        float *out = c.part + (((size_t)b * c.Hq + h) * c.max_parts + chunk) * part_stride(d);
         const T *Vp = (const T *)c.V;
         for (int w = 0; w * kWave < d; ++w) {
             const int ch = w * kWave + lane;
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(da_cache c, T *__res
     while (G * 4 < d) G <<= 1;
     const int li = lane & (G - 1), slot = lane / G, slots = kWave / G;
     const bool act = li * 4 < d;
-    const float *part = c.part + (size_t)bh * c.max_chunks * ps;
+    const float *part = c.part + (size_t)bh * c.max_parts * ps;
     float M = -INFINITY, L = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int k0 = 0; k0 < nparts; k0 += slots * kB) {
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(64) void decode_step_bf16_kernel(da_cache c, const 
         l += __shfl_xor(l, 16);
         l += __shfl_xor(l, 32);
         if (lane < gh) {
-            float *out = c.part + (((size_t)b * c.Hq + hk * g + hbase + lane) * c.max_chunks + chunk) * part_stride(d);
+            float *out = c.part + (((size_t)b * c.Hq + hk * g + hbase + lane) * c.max_parts + chunk) * part_stride(d);
             out[d] = m;
             out[d + 1] = l;
         }
@@ -576,7 +576,7 @@ __global__ __launch_bounds__(64) void decode_step_bf16_kernel(da_cache c, const 
             for (int r = 0; r < 4; ++r) {
                 const int h = 4 * lg + r;
                 if (h < gh)
-                    c.part[(((size_t)b * c.Hq + hk * g + hbase + h) * c.max_chunks + chunk) * part_stride(d) + 16 * ct + l16] =
+                    c.part[(((size_t)b * c.Hq + hk * g + hbase + h) * c.max_parts + chunk) * part_stride(d) + 16 * ct + l16] =
                         o[r];
             }
         }
@@ -712,7 +712,6 @@ da_status delta_attn_cache_create(da_cache **out, int32_t batch, int32_t n_q_hea
     c->theta = theta;
     c->scale = scale;
     c->len = 0;
-    c->nck = max_seq / kChunk + 1;
     c->max_chunks = (max_seq + kChunk - 1) / kChunk;
     c->vrows = (max_seq + kChunk - 1) / kChunk * kChunk;
     c->plan_merge = -1;
@@ -721,6 +720,9 @@ da_status delta_attn_cache_create(da_cache **out, int32_t batch, int32_t n_q_hea
     // one chunk, or one that covers the whole cache
     c->fast = dtype == DA_BF16 && (head_dim == 64 || head_dim == 128) && (c->Wd >= kChunk || c->Wd == max_seq) &&
               n_q_heads / n_kv_heads <= 32;
+    const int turns = (c->max_chunks + run_walkers(head_dim) - 1) / run_walkers(head_dim);   // of one work group, at most
+    c->nck = c->fast ? 1 : max_seq / kChunk + 1;
+    c->max_parts = c->fast ? (turns < kMaxParts ? turns : kMaxParts) : c->max_chunks;
     if (hipGetDevice(&c->device) != hipSuccess) {
         delete c;
         return DA_ERR_HIP;
@@ -728,7 +730,7 @@ da_status delta_attn_cache_create(da_cache **out, int32_t batch, int32_t n_q_hea
     const size_t units = (size_t)batch * n_kv_heads, es = elt_size(dtype), d = head_dim;
     bool ok = true;
     ok = ok && hipMalloc((void **)&c->mask, units * max_seq * (d / 32) * 4) == hipSuccess;
-    ok = ok && hipMalloc(&c->surv, units * (size_t)c->max_chunks * run_room_stride(d) * es) == hipSuccess;
+    ok = ok && hipMalloc(&c->surv, units * (size_t)c->max_chunks * (c->fast ? run_room_stride(d) : kChunk * d) * es) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->ccnt, units * (size_t)c->max_chunks * 4) == hipSuccess;
     ok = ok && hipMalloc(&c->ck, units * c->nck * d * es) == hipSuccess;
     ok = ok && hipMalloc(&c->khat, units * d * es) == hipSuccess;
@@ -736,7 +738,7 @@ da_status delta_attn_cache_create(da_cache **out, int32_t batch, int32_t n_q_hea
     ok = ok && hipMalloc(&c->V, units * (size_t)c->vrows * d * es) == hipSuccess;
     if (ok) ok = hipMemset(c->V, 0, units * (size_t)c->vrows * d * es) == hipSuccess;   // rows never written must be finite
     ok = ok && hipMalloc((void **)&c->nnz, units * 8) == hipSuccess;
-    ok = ok && hipMalloc((void **)&c->part, (size_t)batch * n_q_heads * c->max_chunks * part_stride(d) * 4) == hipSuccess;
+    ok = ok && hipMalloc((void **)&c->part, (size_t)batch * n_q_heads * c->max_parts * part_stride(d) * 4) == hipSuccess;
     if (ok) ok = hipMemset(c->nnz, 0, units * 8) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->arrived, units * 4) == hipSuccess;
     if (ok) ok = hipMemset(c->arrived, 0, units * 4) == hipSuccess;

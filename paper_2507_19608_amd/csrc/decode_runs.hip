@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void seal_from_ring_kernel(da_cache c, int chu
     if (tid < kChunk * WPR) mask[tid] = mw;
     __syncthreads();
     if (wave < D / 64) {
-        const bf16_t held = chunk > 0 ? ((const bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * D + tid] : (bf16_t)0;
+        const bf16_t held = chunk > 0 ? ((const bf16_t *)c.ck)[(size_t)unit * D + tid] : (bf16_t)0;
         const uint32_t n = build_runs(keys + 64 * wave, D, mask + 2 * wave, WPR, held, runs + wave * kHalfRoom);
         if ((tid & 63) == 0) len[wave] = n;
     }
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void cache_fill_runs_kernel(const bf16_t *__re
     }
     if (tid == 0 && blockIdx.x == 0) c.nnz[unit] = (t0 == 0 ? 0ull : c.nnz[unit]) + nnz_new[unit];
     if (tid < D) {
-        if (chunk > 0 && r0 >= t0) ((bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * D + tid] = held_of(r0 - 1, tid);
+        if (chunk > 0 && r0 >= t0 && rb - r0 < kChunk) ((bf16_t *)c.ck)[(size_t)unit * D + tid] = held_of(r0 - 1, tid);   // (the last chunk)
         if (rb == n_k) ((bf16_t *)c.khat)[(size_t)unit * D + tid] = held_of(n_k - 1, tid);
     }
     __syncthreads();
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(64) void expand_cache_kernel(da_cache c, int t0, in
             p = base + kHead + wave_exclusive_scan((uint32_t)__popcll(cm) + 1u, &total);
             held = room[p];
         } else if (chunk > 0) {
-            held = ((const bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * d + ch];
+            held = ((const bf16_t *)c.ck)[(size_t)unit * d + ch];
         }
         for (int rb = 0; rb < rows; rb += 16) {
             bf16_t kraw[16], sv[16];
@@ -295,7 +295,6 @@ __global__ __launch_bounds__(64) void expand_cache_kernel(da_cache c, int t0, in
 __device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf16_t *__restrict__ k_new,
                                 const bf16_t *__restrict__ v_new, uint32_t *__restrict__ mask_row, int t) {
     const int d = c.d, wpr = d >> 5;
-    const int chunk = t / kChunk;
     uint32_t fired = 0;
     for (int c0 = 0; c0 < d; c0 += kWave) {
         const int ch = c0 + lane;
@@ -305,7 +304,7 @@ __device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf1
         if (t > 0) {
             const bf16_t hraw = *hp;
             fire = fabsf(bf16_to_f32(kraw) - bf16_to_f32(hraw)) > c.theta;
-            if (t % kChunk == 0) ((bf16_t *)c.ck)[((size_t)unit * c.nck + chunk) * d + ch] = hraw;
+            if (t % kChunk == 0) ((bf16_t *)c.ck)[(size_t)unit * d + ch] = hraw;
         }
         if (fire) *hp = kraw;
         ((bf16_t *)c.ring)[((size_t)unit * c.Wd + t % c.Wd) * d + ch] = kraw;
@@ -677,15 +676,15 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     }
     __syncthreads();
     constexpr int kThreads = 64 * NW * H;
-    float *part = c.part + ((size_t)b * c.Hq + hk * g) * c.max_chunks * part_stride(D);   // [head][max_chunks][part_stride]
+    float *part = c.part + ((size_t)b * c.Hq + hk * g) * c.max_parts * part_stride(D);   // [head][max_parts][part_stride]
     // two channels of a head per thread at a time; a row's last pair is its maximum and sum
     auto put = [&](int h, int ch, float x, float y) {
         const uint64_t v = (uint64_t)__float_as_uint(x) | ((uint64_t)__float_as_uint(y) << 32);
-        __hip_atomic_store((uint64_t *)(part + ((size_t)h * c.max_chunks + blockIdx.x) * part_stride(D) + ch), v, __ATOMIC_RELAXED,
+        __hip_atomic_store((uint64_t *)(part + ((size_t)h * c.max_parts + blockIdx.x) * part_stride(D) + ch), v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     };
     auto get = [&](int h, int p, int ch) -> f32x2 {
-        const uint64_t v = __hip_atomic_load((const uint64_t *)(part + ((size_t)h * c.max_chunks + p) * part_stride(D) + ch),
+        const uint64_t v = __hip_atomic_load((const uint64_t *)(part + ((size_t)h * c.max_parts + p) * part_stride(D) + ch),
                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return f32x2{__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32))};
     };
@@ -786,9 +785,9 @@ void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, 
     // Work groups of 8 waves - 8 walkers at head_dim 64, 4 at head_dim 128 -, one per compute unit by LDS and registers: as many
     // per unit as keep the whole launch resident, no more than the last one can merge in a few round trips - or just one,
     // where meeting across work groups (2 us, about a turn) would take longer than the turns it saves.
-    const int nw = c->d == 64 ? 8 : 4, slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8;
+    const int nw = run_walkers(c->d), slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8;
     auto turns = [&](int parts) { return (nchunks + nw * parts - 1) / (nw * parts); };
-    const int most = std::max(1, std::min(slots / 8 / units, 32)), fewest = turns(most);
+    const int most = std::max(1, std::min(slots / 8 / units, kMaxParts)), fewest = turns(most);
     int parts = 1;
     if (c->plan_merge != 1 && (fewest + 1 < turns(1) || c->plan_merge == 0))
         parts = (nchunks + nw * fewest - 1) / (nw * fewest);
