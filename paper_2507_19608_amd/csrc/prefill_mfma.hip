@@ -111,9 +111,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 // 64 x 16 bytes from base + the lanes' offsets to LDS bytes lds .. lds + 1023 (wave-uniform), lane after lane.  In asm, so
 // that the compiler does not order later LDS reads behind it: whoever reads the tile waits for the count (wait_loads) and
-// then passes a barrier.  (s_nop: m0 may be used by an LDS load one wait state after it was written.)
+// then passes a barrier.  The LDS address goes in m0, which the compiler writes: it may have a use of its own for it in between.
+// (s_nop: m0 may be used by an LDS load one wait state after it was written.)
 __device__ __forceinline__ void load_to_lds(const char *base, uint32_t off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {                   // until at most N of this wave's loads are in flight
