@@ -9,7 +9,9 @@
  *
  * Conventions
  *   - Every tensor pointer is DEVICE memory owned by the caller, contiguous,
- *     last dimension fastest.  The library owns only da_cache objects.
+ *     last dimension fastest.  The library owns only da_cache objects.  The
+ *     Q, K and V of a prefill or a scan may start at any element; a bf16 prefill
+ *     copies K and V first where they are not aligned to 16 bytes.
  *   - hip_stream is a hipStream_t passed as void* (NULL = default stream).  All
  *     work is enqueued on it; only delta_attn_sparsity synchronises.
  *   - Every entry returns a da_status.  Arguments, workspace and cache state are checked before anything is
@@ -44,13 +46,11 @@ typedef enum {
 
 typedef enum { DA_F32 = 0, DA_BF16 = 1 } da_dtype;
 
-/* How scores outside the window are produced.  Both give the same real-number result.
- *   DA_SCORE_GATHER  Eq. 4: a running score per query row, updated per key column.  fp32 inputs and head dims other
- *                    than 64 / 128 add up the surviving (channel, delta) entries one by one; bf16 inputs with head
- *                    dims 64 / 128 take each column's sum in its telescoped form (below) on the matrix cores, where a
- *                    dense product costs a sixth of the surviving entries' multiply-adds on the vector ALU.
- *   DA_SCORE_REBASE  the telescoped form of Eq. 4: sum_{u<=j} dk(u) = k_hat(j), so the
- *                    score is the dense product q . k_hat(j) (no multiply is skipped). */
+/* How scores outside the window are asked for: Eq. 4 as the paper writes it, a running score per query row that every key
+ * column updates (DA_SCORE_GATHER), or its telescoped form, sum_{u<=j} dk(u) = k_hat(j), so that the score is the product
+ * q . k_hat(j) with the held key (DA_SCORE_REBASE).  Both stand for the same number, and every kernel computes it in the
+ * telescoped form, the accumulated sum in binary32 over the channels and nothing carried from column to column: the field is
+ * checked, and a call gives the same results bit for bit with either. */
 typedef enum { DA_SCORE_GATHER = 0, DA_SCORE_REBASE = 1 } da_score_mode;
 
 /* Shape of the prefill's exact region (Sec. III-B).
@@ -91,6 +91,7 @@ const char *delta_attn_last_error(void);
  * A benchmarking aid, off by default: the switch and the event pool are process-wide (guarded by a mutex), so
  * with timing on, calls from several threads are bracketed into one common pool.
  */
+/* DA_STAGE_EMIT: no kernel has this stage any more (surviving entries are not written out); it reads 0 calls. */
 enum { DA_STAGE_SCAN = 0, DA_STAGE_EMIT = 1, DA_STAGE_ATTN = 2, DA_STAGE_CACHE_FILL = 3,
        DA_STAGE_APPEND = 4, DA_STAGE_CHUNK = 5, DA_STAGE_COMBINE = 6, DA_NUM_STAGES = 7 };
 void delta_attn_stage_timing_enable(int32_t on);
@@ -179,7 +180,7 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
                                     void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* Decode cache: per (batch, KV head) the delta matrix in compact form (mask bits + surviving key
- * values), the reference key at the start of every 64 rows, the current reference key, a ring of
+ * values), reference keys at the start of every 64 rows, the current reference key, a ring of
  * the last decode_window raw keys, and V (Sec. III-A last paragraph, Sec. III-C).  All sequences of
  * the batch advance together.  A cache may start empty (the first decoded row is then the basis
  * row) or be filled by delta_attn_prefill.  Allocates device memory on the current device; owned

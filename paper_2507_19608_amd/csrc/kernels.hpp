@@ -20,8 +20,8 @@ const char *last_error_text();
 void set_last_error(const char *fmt, ...) __attribute__((format(printf, 1, 2)));
 
 // Optional per-stage timing with HIP events recorded on the caller's stream (off by default).
-enum Stage { kStageScan = 0, kStageEmit, kStageAttn, kStageCacheFill, kStageAppend, kStageChunk, kStageCombine,
-             kNumStages };
+// Numbered as in the header, whose stage 1 no kernel has any more.
+enum Stage { kStageScan = 0, kStageAttn = 2, kStageCacheFill, kStageAppend, kStageChunk, kStageCombine, kNumStages };
 void stage_begin(int stage, hipStream_t s);   // no-ops unless timing is enabled
 void stage_end(int stage, hipStream_t s);
 void timing_enable(bool on);
