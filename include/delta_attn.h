@@ -197,7 +197,7 @@ const uint32_t *delta_attn_cache_mask(const da_cache *c);
 /* How a decode step on this cache is laid out over the GPU (Sec. III-B decode stage; results do not
  * depend on it).  bf16 caches with head_dim 64 / 128 and decode_window >= min(64, max_seq) split the cached rows of a
  * (batch, KV head) unit into chunks of 64 rows; a wave (head_dim 128: a pair of waves, 64 channels each) walks every
- * n-th of them, and a work group of 8 waves merges its partial results on chip.
+ * n-th of them, and a work group of up to 8 waves merges its partial results on chip.
  *   merge_in_kernel  1: one work group per unit;
  *                    0: as many work groups per unit as the wave slots allow, the last one to finish merges them all;
  *                   -1: chosen per step from the unit count and the wave slots (default).

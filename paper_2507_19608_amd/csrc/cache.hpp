@@ -72,8 +72,8 @@ constexpr int kRunHalfRoom = 384 + (kChunk + 1) * 64;
 __host__ __device__ inline size_t run_room_stride(int d) { return (size_t)(d / 64) * kRunHalfRoom; }
 // work groups that share a unit in a decode step, at most: what the last of them can merge in a few round trips
 constexpr int kMaxParts = 32;
-// ... and the walkers of each (8 waves, one or two to a walker)
-inline int run_walkers(int d) { return d == 64 ? 8 : 4; }
+// ... and the walkers of each, at least
+inline int run_walkers(int d) { return d == 64 ? 8 : 1; }
 
 // floats per partial row: o[d], running maximum, running sum, padded to a 16-byte multiple
 __host__ __device__ inline int part_stride(int d) { return d + 4; }

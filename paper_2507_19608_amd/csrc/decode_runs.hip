@@ -783,22 +783,38 @@ void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, 
         (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess || c->cus < 1))
         c->cus = 256;
     // Work groups of 8 waves - 8 walkers at head_dim 64, 4 at head_dim 128 -, one per compute unit by LDS and registers: as many
-    // per unit as keep the whole launch resident, no more than the last one can merge in a few round trips - or just one,
-    // where meeting across work groups (2 us, about a turn) would take longer than the turns it saves.
-    const int nw = run_walkers(c->d), slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8;
-    auto turns = [&](int parts) { return (nchunks + nw * parts - 1) / (nw * parts); };
-    const int most = std::max(1, std::min(slots / 8 / units, kMaxParts)), fewest = turns(most);
+    // per unit as keep the whole launch resident, no more than the last one can merge in a few round trips, or just one where
+    // that has as few turns (a turn saved is worth the meeting: 20 .. 128 units of 300 rows, head_dim 128, 12.0 .. 14.6 us in two
+    // turns of one work group, 10.0 .. 12.8 in one of two; 8 units of 560 rows, head_dim 64, 10.8 and 10.5).
+    // The walkers of a work group meet at barriers at head_dim 128, and whole work groups of 4 deal out badly to a number of
+    // units that does not divide the compute units: there 2 or 1 are taken where the launch then has fewer turns, and 2 also
+    // where it has as many, but four or more.  2048 rows, us a step with 4 / 2 / 1 walkers: 20 units 12.3 / 13.9 / 18.4 (1 turn), 40
+    // units 15.9 / 17.1 / 20.3 (2), 96 units 27.5 / 24.5 / 25.6 (5 / 4 / 4), 128 units 30.3 / 28.1 / 28.4 (5), 160 units 39.8 /
+    // 32.7 / 32.7 (9 / 6 / 6), 192 units 41.9 / 39.9 / 37.0 (9 / 9 / 7), 512 units, half of whose work groups of 4 are resident at
+    // a time, 89.5 / 77.2 / 79.2 (18 / 17 / 17); 600 rows: 192 units 19.8 / 22.2 / 19.7 (3 / 3 / 2), 256 units 21.9 / 24.0 / 25.1 (3).
+    const int H = c->d / 64, slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8;
+    struct Plan {
+        int nw, most, turns, cost;                           // walkers per work group, work groups per unit, turns of each, in all
+    };
+    auto turns = [&](int nw, int parts) { return (nchunks + nw * parts - 1) / (nw * parts); };
+    auto plan = [&](int nw) {
+        const int resident = std::max(1, slots / (nw * H)), most = std::max(1, std::min(resident / units, kMaxParts));
+        const int t_each = turns(nw, most);
+        return Plan{nw, most, t_each, (int)std::min<int64_t>((int64_t)t_each * (((int64_t)units * most + resident - 1) / resident), 1 << 30)};
+    };
+    Plan p = plan(c->d == 64 ? 8 : 4);
+    if (c->d == 128 && c->plan_merge != 1) {
+        const Plan two = plan(2), one = plan(1);
+        if (two.cost < p.cost || (two.cost == p.cost && two.cost >= 4)) p = two;
+        if (one.cost < p.cost) p = one;
+    }
     int parts = 1;
-    if (c->plan_merge != 1 && (fewest + 1 < turns(1) || c->plan_merge == 0))
-        parts = (nchunks + nw * fewest - 1) / (nw * fewest);
-    const dim3 grid(parts, units);
-    const bf16_t *qq = (const bf16_t *)q, *kk = (const bf16_t *)k, *vv = (const bf16_t *)v;
-    if (c->d == 64)
-        hipLaunchKernelGGL((decode_step_runs_kernel<64, 8>), grid, dim3(512), 0, s, *c, qq, kk, vv, (bf16_t *)o, mask_row, t,
-                           scale_log2);
-    else
-        hipLaunchKernelGGL((decode_step_runs_kernel<128, 4>), grid, dim3(512), 0, s, *c, qq, kk, vv, (bf16_t *)o, mask_row, t,
-                           scale_log2);
+    if (c->plan_merge != 1 && (p.turns < turns(p.nw, 1) || c->plan_merge == 0))
+        parts = (nchunks + p.nw * p.turns - 1) / (p.nw * p.turns);
+    const auto kernel = c->d == 64 ? decode_step_runs_kernel<64, 8> : p.nw == 4 ? decode_step_runs_kernel<128, 4>
+                        : p.nw == 2 ? decode_step_runs_kernel<128, 2> : decode_step_runs_kernel<128, 1>;
+    hipLaunchKernelGGL(kernel, dim3(parts, units), dim3(64 * p.nw * H), 0, s, *c, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,
+                       (bf16_t *)o, mask_row, t, scale_log2);
 }
 
 void seal_chunk_runs(da_cache *c, int chunk, hipStream_t s) {
