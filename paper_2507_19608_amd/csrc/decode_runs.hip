@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void seal_from_ring_kernel(da_cache c, int chu
 // values, reference keys, mask rows.  `full` (chunked prefill): the whole sequence as plain arrays, [units][ld][...]; the new
 // rows are added to them, and the chunk's and its predecessor's old rows are read from them.  Without it t0 is 0.
 // The chunk's rows pass through LDS, whole lines in and out.  (A wave per chunk with a lane per channel that loaded and stored
-// two bytes at a time took 26 us on 1024 rows of 10 units of 128, and a kernel of its own the plain arrays; now 9 us
+// two bytes at a time took 26 us on 1024 rows of 10 units of 128, and a kernel of its own the plain arrays; now 8.7 us
 // together.)
 struct FullRows {
     bf16_t *k, *v, *h;
@@ -333,8 +333,7 @@ __device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf1
 //      (64 channels x 64 rows) times a triangle of twos, plus the starts, is the table of byte addresses, exact in int32,
 //      and comes out in the layout that the next product takes its keys in: lane l holds row l % 32 of a half chunk,
 //      channels 8 q + 4 (l / 32)..+3.  That leaves one LDS read per element.  (Counting on the vector ALU - ballot, two
-//      mbcnt, two adds per channel of 64 rows - was 600 instructions a chunk, which one wave issues in 1.6 us and two on a
-//      SIMD in 3: more than the chunk's memory time.)  Window rows are 64-bit loads from the raw-key ring, the newest from k_new;
+//      mbcnt, two adds per channel of 64 rows - made 702 vector instructions a chunk of the 384 that it takes now.)  Window rows are 64-bit loads from the raw-key ring, the newest from k_new;
 //   2. two neighbouring channels to a register: the 32x32x16 operand, with the queries fetched in the same channel order;
 //   3. scores S[row][head] on the matrix cores (heads padded to 32 columns); at head_dim 128 the two waves
 //      exchange their halves of the contraction through LDS and both hold the full scores; softmax update in
@@ -343,8 +342,8 @@ __device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf1
 //      the V cache stores each group of 16 rows in exactly that order; O^T (the wave's 64 channels) keeps
 //      lane = head, so the running rescale needs no cross-lane traffic.
 // The walkers of a work group merge their (o, m, l) in LDS.  A unit's only work group writes the normalised output; of
-// several, each leaves its partial row in scratch, and the one that finds the others' there merges and writes (a second
-// launch for this cost 4.7 us of a 19 us step at 4 x 5 units of 6000 rows, and its own time on the host).  On this chip every
+// several, each leaves its partial row in scratch, and the one that finds the others' there merges and writes (with a second
+// launch for it a step took 14.1 instead of 12.3 us at 20 units of 2048 rows of 128, and its own time on the host).  On this chip every
 // XCD has its own L2, and fences that write it back or drop it cost more than the second launch did; so the partial rows,
 // and nothing else, are stored past it (relaxed device-scope stores), waited for, counted with a device-scope add, and read
 // past it.

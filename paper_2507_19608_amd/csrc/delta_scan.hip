@@ -542,10 +542,14 @@ void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s) {
                        (unsigned long long)v, n);
 }
 
-// A prompt whose rows fit into LDS is one segment: one work group of 8 waves per unit, one launch.  Longer ones are cut into
-// segments of 128 rows, 64 channels and 4 waves per work group: with the 128 rows before them 35 KB of LDS (bf16), so that
-// four work groups share a compute unit and cover each other's load, walk and store - or of 256 rows, which halves the rows
-// walked twice, where that still leaves every compute unit three work groups.
+// A prompt whose rows fit into LDS is one segment: one work group of 8 waves per unit, one launch (one segment / cut, us a call: 8 x 256
+// rows of 64 12.1 / 14.8, 8 x 512 12.6 / 14.6, 64 x 8 x 1024 43.4 / 50.2; at the line few units would rather be cut: 8 x 1024 16.5 /
+// 15.1).  Longer ones are cut into segments of 128 rows, 64 channels and 4 waves per work group: with the 128 rows before them 35 KB
+// of LDS (bf16), so that four work groups share a compute unit and cover each other's load, walk and store - or of 256 rows,
+// which halves the rows walked twice, where that still leaves every compute unit three work groups (128 / 256 rows, bf16: 8 x 2048
+// rows of 64 15.6 / 18.8, 5 x 4096 of 128 20.2 / 20.7, 20 x 4096 29.5 / 25.6 - below the line already -, 20 x 8192 41.7 / 39.0, 40 x 8192
+// 62.9 / 57.6).  In fp32 a work group of 256 + 128 rows is alone on its compute unit, and 128 rows are as good or better from 16
+// units up (32 x 4000 rows of 128: 52.7 / 56.8), unless most guesses are wrong (32 x 8000 rows of 64 that drift slowly: 328 / 248).
 static ScanPlan scan_plan(int dtype, int units, int n, int d) {
     const int es = dtype == 0 ? 4 : 2;
     ScanPlan p;

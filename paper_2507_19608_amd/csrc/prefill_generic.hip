@@ -9,8 +9,8 @@
 // with its own running (maximum, sum, output), and meet in LDS once at the end.  The calls this kernel sees are small
 // (a numerics user's single head of a few hundred rows), so what bounds it is how many waves there are and how long the
 // longest one walks: a wave per 64 rows that walked every key took 725 us on 256 rows of one head of 64 (4 waves on the
-// chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each, and the whole call
-// takes 28 us (scan included).
+// chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each: 6.7 us, 16.4 for the whole
+// call with the scan.
 //
 // Matrix-core layout (16x16x4, wave64): A lane l holds row l % 16, k = l / 16; B lane l column l % 16, same k; D lane l
 // column l % 16, rows 4 (l / 16) + r.  Scores are taken transposed (keys x query rows): a lane owns one query row, and
@@ -252,8 +252,10 @@ void launch_one(const PrefillArgs &p, hipStream_t s) {
     a.W = p.W;
     a.sliding = p.sliding;
     a.scale_log2 = p.scale_log2;
-    // 32 rows per work group halve the reads of K and V per row; they pay once 16-row work groups would outnumber
-    // the compute units anyway (their merge needs LDS that a larger head_dim does not leave)
+    // 32 rows per work group halve the reads of K and V per row, from two 16-row work groups per compute unit on (their merge
+    // needs LDS that a larger head_dim does not leave).  That pays little there, and less beyond (16 / 32 rows, attention alone):
+    // fp32, 8 heads of 64, 512 tokens (256 work groups of 16 rows) 13.0 / 18.0 us, 1024 tokens 31.7 / 30.4, 2048 tokens 85.3 / 97.6;
+    // 8 heads of 128, 1024 tokens 56.9 / 53.2, 2048 tokens 152 / 182; bf16, 4 x 1000 tokens, 20 / 5 heads of 96: 226 / 344.
     if constexpr (D <= 128) {
         if ((int64_t)((p.n + 15) / 16) * p.Hq * p.B > 2 * device_cu_count()) {
             launch_tiles<T, D, 2>(p, a, s);

@@ -7,8 +7,8 @@
 //   left of the window   the running score of Eq. 4 is, by the telescoped sum of the delta rows up to column j, the
 //                        product of the query with the held key, q . k_hat(j): K_hat Q^T on the matrix cores.
 //                        DA_SCORE_GATHER takes this form too: adding up the surviving entries one by one on the
-//                        vector ALU was bound by instruction issue and LDS at 8.1 ms on 4 x 8192 tokens, 20 / 5 heads
-//                        of 128, 60 % sparsity - the survivors of a block cost about 16 times its dense product.
+//                        vector ALU was bound by instruction issue and LDS, at 8.04 ms on 4 x 8192 tokens, 20 / 5 heads
+//                        of 128, 60 % sparsity, which take 1.28 ms here.
 //   inside the window    exact scores K Q^T.
 //
 // The keys of a tile are walked as one list of blocks: first the blocks with columns left of some row's window (scores
@@ -17,22 +17,26 @@
 // reads is two tiles, keys and values.
 //
 // What bounds it: matrix cores and vector ALU take turns.  A block of 64 keys costs a wave 1024 cycles of matrix work at
-// head_dim 128 (512 at 64) and about 1000 of softmax, so a SIMD is only busy if one of its two waves multiplies while the
+// head_dim 128 (512 at 64) and about 800 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
 // other takes exponentials.  The waves therefore run in two groups half a block apart (waves 0-3 and 4-7, one of each per
 // SIMD), handed from phase to phase by barriers:
 //     A: | PV(b-1) S(b) | softmax(b)   | PV(b) S(b+1) | ...
 //     B:                | PV(b-1) S(b) | softmax(b)   | ...
-// Built like this the card's power limit is what is left on long prompts: products fed from LDS with nothing else going on draw
-// the clock down to 1.7 GHz, and orders of the reads, priorities or row sums that take fewer cycles take as long.
-// 4 x 8192 tokens, 20 / 5 heads of 128: 1340 -> 1215 us (all waves in step, a barrier per 32 keys, tiles by way of registers
-// and V re-ordered by a launch of its own before); 1 x 4096: 190 -> 115 us, most of it from the order of the tiles below.
+// 4 x 8192 tokens, 20 / 5 heads of 128: 1.38 -> 1.28 ms (all waves in step, a barrier per 32 keys, tiles by way of registers and V
+// re-ordered by a launch of its own before); 79 % of the rate of a large library matrix product on the same card (1.38 PFLOP/s).
+// By the counters that is 2.43 M clocks, the same in every run, at 1.69 to 1.80 GHz: the card, good for 2.4, slows down under
+// this load.  Of these clocks the matrix cores are busy 54 %, the vector ALU issues in 50 %, the data path of the LDS is taken 54 % by the
+// operands (at 128 bytes a clock; no bank conflicts, 3 % of the waves' time waiting for it).  A phase lasts 1880 clocks,
+// about the sum of what its two waves have to do on a SIMD (1024 of matrix instructions, 810 of others) and not the larger
+// of the two; why is open.
 //
 // kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 64 keys, with their own running
-// (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.6 of the time (the same work per wave,
-// twice the loads): for the last, longest rows of a launch that would otherwise wait for them.  A launch cuts its rows into
-// whole and split tiles where that promises to end first (see launch_d) and hands them out longest first from a counter.
-// 2048 tokens, 32 / 8 heads of 64: 41 -> 33 us (blocks of 32 keys for each group before, one work group per tile); pieces of
-// 1024 tokens on 2 x 4096, 20 / 5 heads of 128: 360 -> 328 us a prompt; 2 x 5003 sliding: 301 -> 286 us.
+// (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.64 of the time (1.13 instead of 1.76 us for 64
+// keys at head_dim 128, 0.81 instead of 1.31 at 64: the same work per wave, twice the loads): for the last, longest rows of a
+// launch that would otherwise wait for them.  A launch cuts its rows into whole and split tiles where that promises to end first
+// (see launch_d) and hands them out longest first from a counter.  Attention alone, all whole / all split / as cut: 2048 tokens, 32
+// / 8 heads of 64: 46.2 / 33.9 / 34.2 us; 1 x 1024, 20 / 5 heads of 128: 38.4 / 27.5 / 28.4; 4 x 2048: 119 / 131 / 119; 4 x 8192:
+// 1271 / 1435 / 1269.
 //
 // Tiles go from global memory to LDS directly (global_load_lds, 16 bytes per lane, no registers), row-major, two blocks ahead
 // in three buffers, or two where every group has its own.  The 16-byte segments of a row are permuted by the row number so that the reads are free of bank
@@ -600,7 +604,11 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     // Whole tiles for the first rows, split ones for the rest.  Of the ways to cut, the one that promises to be done first: a
     // launch lasts at least as long as its longest tile, as the work per compute unit, and, with more tiles than
     // compute units, as the two that have to share one (which the pieces of a chunked prefill, all of about one length, come
-    // up against).  In units of one whole tile over 64 keys: a tile has kOpen of overhead, a split one takes kSplitTurn for 64 keys.
+    // up against).  In units of one whole tile over 64 keys: a tile has kOpen of overhead, a split one takes kSplitTurn for 64 keys
+    // (measured: 0.62 to 0.64; a launch of one tile per compute unit 5.4 whole and 6.0 split, itself included - a tile that follows
+    // another has its loads out earlier).
+    // Against the best of 13 cuts of each of 15 launches the one chosen is within 2 % on 9; the worst are 4 x 1024 tokens (20 / 5
+    // heads of 128: 53.9 us, all whole 45.4), 16 x 200 (33.8, three of four row tiles whole 28.9) and 1 x 4096 (113, 53 of 64 whole 102).
     constexpr double kOpen = 2.2, kSplitTurn = 0.6;
     const int all = (p.nq + rt - 1) / rt, columns = units * hgroups;
     double best = INFINITY;
@@ -618,7 +626,7 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
         if (whole > 0) lasts = fmax(lasts, length(split));
         if (blocks > cus) lasts = fmax(lasts, length((cus - 1) / columns) + length(cus / columns));
         const bool ordered = xsplit < 3 && even(whole) && even(split);
-        if (!ordered) lasts *= 1.1;                              // (every XCD streams every unit)
+        if (!ordered) lasts *= 1.1;                              // (every XCD streams every unit; timed, 0.96 to 1.03)
         if (lasts < best) {
             best = lasts;
             best_even = ordered;
