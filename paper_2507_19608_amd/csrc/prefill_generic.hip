@@ -5,7 +5,7 @@
 // Scores left of the window are Eq. 4's running sum in telescoped form, q . k_hat(j); a block of keys that straddles
 // a window takes both products and a select per element.
 //
-// Work group = 16 * QT consecutive query rows of one query head; its 8 waves take the blocks of 32 keys in turn, each
+// Work group = 16 consecutive query rows of one query head; its 8 waves take the blocks of 32 keys in turn, each
 // with its own running (maximum, sum, output), and meet in LDS once at the end.  The calls this kernel sees are small
 // (a numerics user's single head of a few hundred rows), so what bounds it is how many waves there are and how long the
 // longest one walks: a wave per 64 rows that walked every key took 725 us on 256 rows of one head of 64 (4 waves on the
@@ -54,12 +54,12 @@ __device__ __forceinline__ f32x2 load2(const bf16_t *p) {
     return f32x2{bf16_to_f32(v[0]), bf16_to_f32(v[1])};
 }
 
-template <typename T, int D, int QT>
+template <typename T, int D>
 __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> a) {
     constexpr int VW = D % 64 == 0 ? 4 : 2;      // channels a lane loads and stores at a time
     constexpr int CG = D / (16 * VW);            // channel groups of the output
     constexpr int KS = D / 16;                   // 16-channel groups of the contraction
-    constexpr int kRowsG = 16 * QT;
+    constexpr int kRowsG = 16;
     extern __shared__ __attribute__((aligned(16))) float lds_g[];
     float *ml = lds_g;                           // [wave][kRowsG][2] running maximum, sum
     float *obuf = lds_g + kWavesG * kRowsG * 2;  // [wave][kRowsG][D + 4] outputs before the merge
@@ -79,92 +79,72 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
     // first exact column of row r: start of its square, or of its band (monotone in r either way)
     auto win_start = [&](int r) { return a.sliding ? max(r - W + 1, 0) : (r / W) * W; };
     const int win_first = win_start(i0), win_last = win_start(i_last);
-    int my_i[QT], my_win[QT];
-    f32x4 q[QT][KS];
+    const int my_i = i0 + l16, my_row = min(my_i, n - 1), my_win = win_start(my_row);
+    f32x4 q[KS];
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-        my_i[t] = i0 + 16 * t + l16;
-        const int i = min(my_i[t], n - 1);
-        my_win[t] = win_start(i);
-#pragma unroll
-        for (int s = 0; s < KS; ++s) q[t][s] = load4(Qp + (size_t)i * D + 16 * s + 4 * lg);
-    }
+    for (int s = 0; s < KS; ++s) q[s] = load4(Qp + (size_t)my_row * D + 16 * s + 4 * lg);
 
-    f32x4 o[QT][CG][VW];
-    float m[QT], l[QT];
+    f32x4 o[CG][VW];
+    float m = -INFINITY, l = 0.f;
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-        m[t] = -INFINITY;
-        l[t] = 0.f;
+    for (int g = 0; g < CG; ++g)
 #pragma unroll
-        for (int g = 0; g < CG; ++g)
-#pragma unroll
-            for (int e = 0; e < VW; ++e) o[t][g][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int e = 0; e < VW; ++e) o[g][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     for (int jb = wave * kKeys; jb <= i_last; jb += kWavesG * kKeys) {
         // scores of the block: X = K, or K_hat where every row has the block left of its window
-        f32x4 s[QT][2];
-        auto scores = [&](const T *X, f32x4 (&acc)[QT][2]) {
+        f32x4 s[2];
+        auto scores = [&](const T *X, f32x4 (&acc)[2]) {
             const T *x0 = X + (size_t)min(jb + l16, n - 1) * D + 4 * lg;
             const T *x1 = X + (size_t)min(jb + 16 + l16, n - 1) * D + 4 * lg;
-#pragma unroll
-            for (int t = 0; t < QT; ++t) acc[t][0] = acc[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+            acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int g = 0; g < KS; ++g) {
                 const f32x4 k0 = load4(x0 + 16 * g), k1 = load4(x1 + 16 * g);
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-#pragma unroll
-                    for (int t = 0; t < QT; ++t) {
-                        acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(k0[e], q[t][g][e], acc[t][0], 0, 0, 0);
-                        acc[t][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k1[e], q[t][g][e], acc[t][1], 0, 0, 0);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(k0[e], q[g][e], acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(k1[e], q[g][e], acc[1], 0, 0, 0);
+                }
             }
         };
         const bool far = jb + kKeys <= win_first;
         scores(far ? Hp : Kp, s);
         if (!far && jb < win_last) {             // some row has part of the block left of its window
-            f32x4 sh[QT][2];
+            f32x4 sh[2];
             scores(Hp, sh);
 #pragma unroll
-            for (int t = 0; t < QT; ++t)
-#pragma unroll
-                for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        s[t][kt][r] = jb + 16 * kt + 4 * lg + r >= my_win[t] ? s[t][kt][r] : sh[t][kt][r];
-        }
-#pragma unroll
-        for (int t = 0; t < QT; ++t) {
-            float bm = -INFINITY;
-#pragma unroll
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool seen = jb + 16 * kt + 4 * lg + r <= my_i[t];
-                    s[t][kt][r] = seen ? s[t][kt][r] * a.scale_log2 : -INFINITY;
-                    bm = fmaxf(bm, s[t][kt][r]);
-                }
-            bm = fmaxf(bm, __shfl_xor(bm, 16));
-            bm = fmaxf(bm, __shfl_xor(bm, 32));
-            const float m_new = fmaxf(m[t], bm);
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // (a row that sees nothing of this wave's keys yet)
-            const float alpha = exp2f(m[t] - m_use);
-            m[t] = m_new;
-            l[t] *= alpha;
-#pragma unroll
-            for (int g = 0; g < CG; ++g)
-#pragma unroll
-                for (int e = 0; e < VW; ++e) o[t][g][e] *= alpha;
-#pragma unroll
-            for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    s[t][kt][r] = exp2f(s[t][kt][r] - m_use);
-                    l[t] += s[t][kt][r];
-                }
+                for (int r = 0; r < 4; ++r) s[kt][r] = jb + 16 * kt + 4 * lg + r >= my_win ? s[kt][r] : sh[kt][r];
         }
+        float bm = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const bool seen = jb + 16 * kt + 4 * lg + r <= my_i;
+                s[kt][r] = seen ? s[kt][r] * a.scale_log2 : -INFINITY;
+                bm = fmaxf(bm, s[kt][r]);
+            }
+        bm = fmaxf(bm, __shfl_xor(bm, 16));
+        bm = fmaxf(bm, __shfl_xor(bm, 32));
+        const float m_new = fmaxf(m, bm);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;    // (a row that sees nothing of this wave's keys yet)
+        const float alpha = exp2f(m - m_use);
+        m = m_new;
+        l *= alpha;
+#pragma unroll
+        for (int g = 0; g < CG; ++g)
+#pragma unroll
+            for (int e = 0; e < VW; ++e) o[g][e] *= alpha;
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                s[kt][r] = exp2f(s[kt][r] - m_use);
+                l += s[kt][r];
+            }
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -181,32 +161,26 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
                         for (int e = 0; e < 2; ++e) vv[e] = x[e];
                     }
 #pragma unroll
-                    for (int e = 0; e < VW; ++e)
-#pragma unroll
-                        for (int t = 0; t < QT; ++t)
-                            o[t][g][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], s[t][kt][r], o[t][g][e], 0, 0, 0);
+                    for (int e = 0; e < VW; ++e) o[g][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vv[e], s[kt][r], o[g][e], 0, 0, 0);
                 }
             }
     }
 
     // the waves' partial results meet: row maxima and sums first, then the outputs at the common maximum
-#pragma unroll
-    for (int t = 0; t < QT; ++t) {
-        l[t] += __shfl_xor(l[t], 16);
-        l[t] += __shfl_xor(l[t], 32);
-        if (lg == 0) {
-            ml[(wave * kRowsG + 16 * t + l16) * 2] = m[t];
-            ml[(wave * kRowsG + 16 * t + l16) * 2 + 1] = l[t];
-        }
-#pragma unroll
-        for (int g = 0; g < CG; ++g)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                float *dst = obuf + (size_t)(wave * kRowsG + 16 * t + l16) * (D + 4) + 16 * VW * g + VW * (4 * lg + r);
-#pragma unroll
-                for (int e = 0; e < VW; ++e) dst[e] = o[t][g][e][r];
-            }
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (lg == 0) {
+        ml[(wave * kRowsG + l16) * 2] = m;
+        ml[(wave * kRowsG + l16) * 2 + 1] = l;
     }
+#pragma unroll
+    for (int g = 0; g < CG; ++g)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float *dst = obuf + (size_t)(wave * kRowsG + l16) * (D + 4) + 16 * VW * g + VW * (4 * lg + r);
+#pragma unroll
+            for (int e = 0; e < VW; ++e) dst[e] = o[g][e][r];
+        }
     __syncthreads();
     for (int idx = threadIdx.x; idx < kRowsG * (D / 4); idx += 64 * kWavesG) {
         const int row = idx / (D / 4), c = (idx % (D / 4)) * 4;
@@ -229,15 +203,6 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
     }
 }
 
-template <typename T, int D, int QT>
-void launch_tiles(const PrefillArgs &p, const KArgs<T> &a, hipStream_t s) {
-    constexpr size_t lds = (size_t)kWavesG * 16 * QT * (D + 6) * sizeof(float);
-    static std::atomic<uint64_t> lds_set;   // per instantiation, one bit per device
-    ensure_dynamic_lds((const void *)prefill_generic_kernel<T, D, QT>, (int)lds, lds_set);
-    dim3 grid((p.n + 16 * QT - 1) / (16 * QT), p.Hq, p.B), block(64 * kWavesG);
-    hipLaunchKernelGGL((prefill_generic_kernel<T, D, QT>), grid, block, lds, s, a);
-}
-
 template <typename T, int D>
 void launch_one(const PrefillArgs &p, hipStream_t s) {
     KArgs<T> a;
@@ -252,17 +217,12 @@ void launch_one(const PrefillArgs &p, hipStream_t s) {
     a.W = p.W;
     a.sliding = p.sliding;
     a.scale_log2 = p.scale_log2;
-    // 32 rows per work group halve the reads of K and V per row, from two 16-row work groups per compute unit on (their merge
-    // needs LDS that a larger head_dim does not leave).  That pays little there, and less beyond (16 / 32 rows, attention alone):
-    // fp32, 8 heads of 64, 512 tokens (256 work groups of 16 rows) 13.0 / 18.0 us, 1024 tokens 31.7 / 30.4, 2048 tokens 85.3 / 97.6;
-    // 8 heads of 128, 1024 tokens 56.9 / 53.2, 2048 tokens 152 / 182; bf16, 4 x 1000 tokens, 20 / 5 heads of 96: 226 / 344.
-    if constexpr (D <= 128) {
-        if ((int64_t)((p.n + 15) / 16) * p.Hq * p.B > 2 * device_cu_count()) {
-            launch_tiles<T, D, 2>(p, a, s);
-            return;
-        }
-    }
-    launch_tiles<T, D, 1>(p, a, s);
+    // (32 rows per work group, which halve the reads of K and V per row, took longer: fp32, 8 heads of 64, 2048 tokens 97.6 us
+    // against 85.3, 8 heads of 128 182 against 152; bf16, 4 x 1000 tokens, 20 / 5 heads of 96 344 against 226.)
+    constexpr size_t lds = (size_t)kWavesG * 16 * (D + 6) * sizeof(float);
+    static std::atomic<uint64_t> lds_set;   // per instantiation, one bit per device
+    ensure_dynamic_lds((const void *)prefill_generic_kernel<T, D>, (int)lds, lds_set);
+    hipLaunchKernelGGL((prefill_generic_kernel<T, D>), dim3((p.n + 15) / 16, p.Hq, p.B), dim3(64 * kWavesG), lds, s, a);
 }
 
 template <typename T>
