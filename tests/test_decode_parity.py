@@ -87,8 +87,8 @@ def test_decode_column_run_layout(n, steps, d, Wd, B, Hq, Hkv, theta):
 @pytest.mark.parametrize("n,steps,d,Hq,Hkv", [(300, 70, 64, 4, 2), (0, 200, 64, 8, 1), (260, 130, 128, 4, 1)])
 def test_decode_launch_plans(plan, n, steps, d, Hq, Hkv):
     """Every way of laying a step out over the GPU gives the same result: one work group per unit whose
-    waves merge on chip (with idle waves while the cache is short), or single-wave work groups that walk
-    several chunks each (2 or 5 wave slots for 2 units force up to all chunks into one wave) + merge launch."""
+    waves merge on chip (with idle waves while the cache is short), or as many as the wave slots hold, the last one to
+    finish merging them (2 or 5 wave slots for 2 units leave one work group each)."""
     B, L = 2, n + steps
     Q, K, V = rand_walk(41, B, Hq, L, d), rand_walk(42, B, Hkv, L, d), rand_walk(43, B, Hkv, L, d, clip=3.5)
     run_decode(Q, K, V, n, steps, 0.2, 64, "bf16", check_every=7, plan=plan)
@@ -363,8 +363,8 @@ def test_chunked_prefill_then_decode(score_mode, window_mode, d, Hq, Hkv, W, Wd,
 @pytest.mark.parametrize("d,Hq,Hkv", [(64, 4, 2), (128, 4, 1)])
 def test_chunked_prefill_between_decode_steps_resets_and_score_modes(d, Hq, Hkv):
     """The cache keeps the sequence as plain arrays between pieces and only adds a piece's rows; whatever else moves
-    the cache on (decode steps, a reset, a one-shot prefill into it) must make the next piece rebuild them, and a
-    piece in gather mode must find the entry lists of columns that earlier telescoped pieces did not write.  Every
+    the cache on (decode steps, a reset, a one-shot prefill into it) must make the next piece rebuild them, in
+    either score mode.  Every
     piece against the same rows of the oracle's prefill over the whole prefix, the final cache through decode."""
     B, W, Wd, theta = 2, 40, 96, 0.2
     G, R = da.DA_SCORE_GATHER, da.DA_SCORE_REBASE

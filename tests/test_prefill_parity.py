@@ -163,9 +163,8 @@ def test_c3_sliding_window_sampled(mode):
 
 
 def test_mid_size_launch_cut_in_two_sampled():
-    """4 x 4096 tokens of C5's head shape with the window of Eq. 5 (W = 204: tiles straddle window squares): 1280 row
-    tiles, five per compute unit - few enough that the gather launch gives every tile two work groups, each on half of
-    its gather blocks, and merges them in a second launch.  Masks and nnz of every unit, sampled output rows."""
+    """4 x 4096 tokens of C5's head shape with the window of Eq. 5 (W = 204: tiles straddle window squares): 1280 whole row
+    tiles, five per compute unit, or some of them as two split ones.  Masks and nnz of every unit, sampled output rows."""
     import dataclasses
     w = dataclasses.replace(wl.C5, seq_len=4096, window=da.delta_attn_window_from_gamma(4096, 0.05, 512),
                             theta=wl.theta_for(wl.C5), target_sparsity=None)
@@ -217,7 +216,7 @@ def test_c5_every_output_element_against_the_dense_form(how):
     either score mode, must equal them bit for bit, and two units of them are also held against the oracle's scan.
     Tolerance as for the oracle.
     Also for the prompt fed in four pieces through the chunked entry point, as `bench.py --chunks 4` times it, and
-    at the two ends of the sparsity sweep (every delta kept: the longest entry lists; 80 % zeroed with bursts)."""
+    at the two ends of the sparsity sweep (every delta kept; 80 % zeroed with bursts)."""
     import dense_form as df
     w = wl.c5(0.0, 0.05) if how == "theta 0" else wl.c5(0.80, 0.20) if how.startswith("80") else wl.C5
     x = _inputs(w)
@@ -254,7 +253,7 @@ def test_c5_every_output_element_against_the_dense_form(how):
 @pytest.mark.parametrize("dtype,d,n,W", [("f32", 64, 1536, 96), ("f32", 256, 700, 33), ("bf16", 96, 2048, 128),
                                          ("bf16", 32, 3000, 7)])
 def test_generic_kernel_every_output_element_against_the_dense_form(dtype, d, n, W):
-    """The vector-ALU kernel (fp32 inputs; head sizes other than 64 / 128) at sizes of a few thousand rows, every
+    """The kernel of binary32 products (fp32 inputs; head sizes other than 64 / 128) at sizes of a few thousand rows, every
     output element of both score modes and both window modes against the same closed form in fp64."""
     import dense_form as df
     B, Hq, Hkv, theta = 2, 6, 2, 0.12
@@ -480,7 +479,7 @@ def test_values_up_to_eight(mode, n, d, W, Hq, Hkv):
 
 @pytest.mark.parametrize("n,d", [(5000, 96), (4097, 64), (130, 32), (63, 128), (1, 64)])
 def test_delta_scan_time_chunks_adversarial(n, d):
-    """The scan is cut into time chunks that start from a guessed state and are repaired afterwards;
+    """The scan is cut into time segments that start from a guessed state and are repaired afterwards;
     these inputs make the repair walk long: keys that never fire, a slow drift that fires every few
     rows at different phases per channel, and a mix with isolated jumps."""
     rng = np.random.default_rng(n + d)
@@ -516,7 +515,7 @@ def test_binding_rejects_bad_arguments():
 
 def test_reruns_are_bit_identical_and_modes_agree():
     """No float atomics anywhere in the output path: two runs give the same bits.  The two score modes
-    evaluate the same real-number function (Eq. 4 vs its telescoped form) and agree to rounding."""
+    stand for the same real-number function (Eq. 4 and its telescoped form)."""
     w = wl.C2
     x = wl.generate(w, batch_ids=[0])
     Qd, Kd, Vd = (to_dev(x[k][:, :, :1024], w.dtype) for k in "QKV")
@@ -592,7 +591,7 @@ def test_all_work_goes_to_the_callers_stream():
 
 
 def test_generic_kernel_matches_on_matrix_core_shapes():
-    """The vector-ALU kernel (fp32 inputs, unusual head dims) and the matrix-core kernel implement the
+    """The kernel of binary32 products (fp32 inputs, unusual head dims) and the bf16 kernel implement the
     same path; run both on a bf16 d = 64 case through the fp32 route by widening the inputs."""
     Q, K, V = rand_walk(21, 1, 4, 200, 64), rand_walk(22, 1, 2, 200, 64), rand_walk(23, 1, 2, 200, 64, clip=3.5)
     theta, W = 0.2, 32
@@ -606,7 +605,7 @@ def test_generic_kernel_matches_on_matrix_core_shapes():
 @pytest.mark.parametrize("mode", MODES)
 def test_prefill_replays_from_a_captured_graph(mode):
     """The prefill entry point allocates nothing and records no memset, so a caller may capture it into a HIP graph
-    (short prompts are launch-bound: six launches per call).  Replays - with eager work and synchronisations between
+    (short prompts are launch-bound).  Replays - with eager work and synchronisations between
     them - must reproduce the eager result bit for bit."""
     B, Hq, Hkv, n, d, W, theta = 2, 4, 2, 200, 64, 16, 0.2
     Q, K, V = rand_walk(81, B, Hq, n, d), rand_walk(82, B, Hkv, n, d), rand_walk(83, B, Hkv, n, d, clip=3.5)
@@ -648,10 +647,8 @@ def test_tiny_sequences(mode, n, d, W, dtype):
 @pytest.mark.parametrize("d,Hq,Hkv,n,W,p_jump,theta", [(128, 4, 1, 900, 64, 0.3, 0.12), (64, 8, 2, 700, 32, 0.5, 0.2),
                                                        (128, 2, 2, 600, 96, 0.15, 0.0), (64, 2, 1, 500, 32, 1.0, 0.3)])
 def test_rebased_full_columns(window_mode, d, Hq, Hkv, n, W, p_jump, theta):
-    """Key streams with many whole-vector jumps (and theta = 0, where every column is full): in blocks with several
-    full columns the gather kernel does not gather those columns but re-bases the running Eq. 4 score there from
-    q . k_hat(j) on the matrix cores - exact by the telescoped sum - so masks, nnz and outputs must still match the
-    oracle, which adds up Eq. 4 column by column."""
+    """Key streams with many whole-vector jumps (and theta = 0, where every entry of every column fires): masks, nnz and outputs
+    must match the oracle, which adds up Eq. 4 column by column where the kernel takes q . k_hat(j)."""
     rng = np.random.default_rng(int(1000 * p_jump) + d)
     Q, V = rand_walk(111, 2, Hq, n, d), rand_walk(113, 2, Hkv, n, d, clip=3.5)
     K = rand_walk(112, 2, Hkv, n, d, step=0.05)
@@ -662,23 +659,22 @@ def test_rebased_full_columns(window_mode, d, Hq, Hkv, n, W, p_jump, theta):
 
 @pytest.mark.parametrize("window_mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
 @pytest.mark.parametrize("B,Hq,Hkv,n,d,W,theta", [
-    (1, 4, 2, 1777, 64, 100, 0.15),     # 28 tiles of 128 rows x 2 heads: cut up to 4 ways, ragged last tile and block
-    (1, 2, 1, 2500, 128, 32, 0.2),      # 10 tiles of 256 rows: up to 8 parts per tile, short first tiles uncut
-    (2, 8, 2, 1100, 128, 300, 0.1),     # windows wider than a part: late tiles have few gather blocks, early ones none
-    (1, 1, 1, 3000, 64, 64, 0.0),       # one head; every column full, so parts also re-base columns inside them
+    (1, 4, 2, 1777, 64, 100, 0.15),     # split tiles of 64 rows x 2 heads, ragged last tile and block
+    (1, 2, 1, 2500, 128, 32, 0.2),      # two heads to a tile
+    (2, 8, 2, 1100, 128, 300, 0.1),     # windows wider than many tiles: late ones have few blocks left of them, early ones none
+    (1, 1, 1, 3000, 64, 64, 0.0),       # one head; every entry fires
 ])
 def test_small_launches_cut_along_the_keys(window_mode, B, Hq, Hkv, n, d, W, theta):
-    """A gather-mode launch with too few row tiles to fill the chip gives every long tile several work groups, each on
-    a range of its key blocks (a part that does not start at key 0 starts its running Eq. 4 score from q . k_hat of
-    the column before, exact by the telescoped sum), and a second launch merges their partial softmax results.  The
-    outputs are still those of the oracle's column-by-column recursion, for every row; masks and nnz bit-exact."""
+    """Launches with too few row tiles to fill the chip take split tiles, whose two halves walk alternate key blocks and merge
+    their softmax results on chip.  The outputs are those of the oracle's column-by-column recursion, for every row; masks
+    and nnz bit-exact."""
     Q, K, V = rand_walk(131, B, Hq, n, d), rand_walk(132, B, Hkv, n, d), rand_walk(133, B, Hkv, n, d, clip=3.5)
     run_case(Q, K, V, theta, W, "bf16", da.DA_SCORE_GATHER, window_mode=window_mode)
 
 
 def test_rebase_is_skipped_for_keys_beyond_fp16():
-    """The re-base tile is taken in fp16; a block whose reference keys do not fit (|k| >= 2^15) keeps gathering its
-    full columns in binary32.  Keys of 5e4 in part of the prompt, every column full (theta = 0): results still match."""
+    """Keys of 5e4, beyond what 16-bit floats with five exponent bits hold, in part of the prompt, every entry fired
+    (theta = 0): results match."""
     n, d = 400, 64
     Q, V = wl.round_to_dtype(rand_walk(121, 1, 2, n, d) * 2.0 ** -14, "bf16"), rand_walk(123, 1, 1, n, d, clip=3.5)
     K = rand_walk(122, 1, 1, n, d)
@@ -693,9 +689,7 @@ def test_rebase_is_skipped_for_keys_beyond_fp16():
 @pytest.mark.parametrize("n,d", [(64, 128), (128, 128), (256, 128), (512, 128), (100, 64), (512, 64), (257, 128)])
 def test_short_prompts_with_the_window_of_eq5(mode, window_mode, n, d):
     """The paper's own regime: prompts of tens to hundreds of tokens with the window of Eq. 5 (gamma = 0.05: W = 3 .. 25).
-    Prompts whose keys fit in LDS (n * head_dim <= 32768) take the fused launch - scan, compaction, V re-order and
-    attention in one kernel, every work group preparing its unit itself - the others a launch per stage; both must
-    match the oracle in masks, nnz, sparsity and every output element."""
+    The scan is one segment here; masks, nnz, sparsity and every output element must match the oracle."""
     W = da.delta_attn_window_from_gamma(n, 0.05, 512)
     assert W == orc.window_from_gamma(n, 0.05, 512) and 3 <= W <= 25
     Q, K, V = rand_walk(131, 2, 8, n, d), rand_walk(132, 2, 2, n, d), rand_walk(133, 2, 2, n, d, clip=3.5)

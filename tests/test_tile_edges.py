@@ -22,7 +22,7 @@ def _walks(seed, B, Hq, Hkv, n, d, dtype):
 @pytest.mark.parametrize("dtype,d,n,W,B,Hq", [
     ("f32", 64, 15, 4, 1, 1), ("f32", 32, 17, 32, 1, 2), ("f32", 96, 33, 7, 2, 1), ("f32", 128, 255, 16, 1, 2),
     ("f32", 64, 257, 40, 1, 1), ("f32", 160, 70, 9, 1, 1), ("f32", 224, 65, 33, 1, 1), ("f32", 256, 289, 64, 1, 1),
-    ("f32", 128, 1055, 52, 1, 8),      # 32-row tiles, ragged
+    ("f32", 128, 1055, 52, 1, 8),      # many tiles, the last one ragged
     ("f32", 64, 513, 512, 4, 8),
     ("bf16", 32, 300, 15, 1, 2), ("bf16", 192, 97, 31, 1, 1), ("bf16", 96, 530, 26, 4, 8),
 ])
@@ -119,8 +119,27 @@ def test_launches_that_hand_tiles_out(d, B, Hq, Hkv, n, W):
     cache.close()
 
 
+@pytest.mark.parametrize("window_mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
+@pytest.mark.parametrize("dtype,d,n,W", [("bf16", 64, 700, 50), ("bf16", 128, 1200, 100), ("bf16", 96, 300, 20), ("f32", 64, 300, 20)])
+def test_score_modes_give_the_same_bits(window_mode, dtype, d, n, W):
+    """One computation stands behind both: in one call, and in two pieces where a cache can take them."""
+    import torch
+    from util import TORCH_DTYPE, to_dev
+    x = [to_dev(t, dtype) for t in _walks(801, 2, 4, 2, n, d, dtype)]
+    runs = []
+    for mode in (da.DA_SCORE_GATHER, da.DA_SCORE_REBASE):
+        runs.append(list(da.delta_attn_prefill(*x, 0.2, W, score_mode=mode, window_mode=window_mode)))
+        if dtype == "bf16" and d in (64, 128):
+            cache = da.Cache(2, 4, 2, d, n, 128, 0.2, TORCH_DTYPE[dtype])
+            for r in (slice(0, n // 3), slice(n // 3, n)):
+                runs[-1] += da.delta_attn_prefill_append(cache, *(t[:, :, r].contiguous() for t in x), 0.2, W, score_mode=mode,
+                                                         window_mode=window_mode)
+            cache.close()
+    assert all(torch.equal(a, b) for a, b in zip(*runs))
+
+
 def test_unaligned_keys_take_the_kernel_that_allows_them():
-    """K and V one element off 16-byte alignment: same results within rounding."""
+    """K and V one element off 16-byte alignment: same results within rounding (bit for bit, see test_unaligned_inputs.py)."""
     import torch
     from util import to_dev
     Q, K, V = (to_dev(x, "bf16") for x in _walks(601, 1, 4, 1, 200, 64, "bf16"))

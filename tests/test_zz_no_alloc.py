@@ -1,8 +1,6 @@
 """delta_attn_prefill_noalloc (the entry point for callers that cannot allocate: its scratch is a buffer built into
-the library's device image) against delta_attn_prefill on the same inputs: same kernels, so masks and nnz must be
-bit-identical and so must the outputs - except where delta_attn_prefill cuts a small launch along the keys and the
-built-in buffer has no room for the parts' results: the two then differ in rounding order, each inside the output
-tolerance of the oracle, against which both calls are held as well.  Two calls in a row share the one buffer - the
+the library's device image) against delta_attn_prefill on the same inputs: same kernels, so masks, nnz and outputs
+are bit-identical, and both calls are held against the oracle as well.  Two calls in a row share the one buffer - the
 second, smaller prompt must not see anything of the first."""
 import numpy as np
 import pytest
@@ -64,8 +62,7 @@ def test_noalloc_replays_from_a_captured_graph(n, d):
     """The callers it is for: captured into a HIP graph (after one eager call that did the one-time set-up), replayed
     with eager work and synchronisations in between; every replay must reproduce the eager call bit for bit (and
     delta_attn_prefill's masks and nnz; its outputs to the tolerance, see above).
-    200 tokens take the fused single launch, 1500 the launch-per-stage path (whose counters are cleared by a fill
-    kernel, not by a memset node)."""
+    200 tokens are one scan segment, 1500 several (whose counters the scan's first launch clears, not a memset node)."""
     B, Hq, Hkv, W, theta = 2, 4, 2, 32, 0.15
     Qd, Kd, Vd = (to_dev(rand_walk(300 + i, B, H, n, d, clip=c), "bf16")
                   for i, (H, c) in enumerate(((Hq, None), (Hkv, None), (Hkv, 3.5))))
