@@ -44,6 +44,21 @@ def test_segments_that_settle_late(kind, dtype, units, n, d):
         assert (nnz == d).all()
 
 
+@pytest.mark.parametrize("kind", ["quiet", "rare", "mixed"])
+@pytest.mark.parametrize("d,cuts", [(64, (0, 1100, 4000)), (128, (0, 40, 2700)), (64, (0, 3001, 3002, 5200))])
+def test_pieces_that_continue_a_cache(kind, d, cuts):
+    """The rows of a piece start from the reference key the cache carries, over several segments."""
+    import dense_form as df
+    n = cuts[-1]
+    K = _keys(kind, n + d, 1, n, d, "bf16")
+    cache = da.Cache(1, 1, 1, d, n, 64, 0.3, torch.bfloat16)
+    bits, counts = zip(*(da.delta_attn_prefill_append(cache, *[K[:, :, a:b].contiguous()] * 3, 0.3, 32)[1:]
+                         for a, b in zip(cuts, cuts[1:])))
+    _, mask = df.reference_keys(K, 0.3)
+    assert (df.unpack_bits(torch.cat(bits, 2), d) == mask).all() and sum(counts).item() == mask.sum().item()
+    cache.close()
+
+
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 128)])
 def test_time_of_quiet_channels_grows_with_the_rows(dtype, d):
     """Four times the rows where nothing fires take four times as long (a fixed part makes it less; the 1.6 is for noise).
