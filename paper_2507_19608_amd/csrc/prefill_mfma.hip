@@ -22,13 +22,14 @@
 // SIMD), handed from phase to phase by barriers:
 //     A: | PV(b-1) S(b) | softmax(b)   | PV(b) S(b+1) | ...
 //     B:                | PV(b-1) S(b) | softmax(b)   | ...
-// 4 x 8192 tokens, 20 / 5 heads of 128: 1.38 -> 1.28 ms (all waves in step, a barrier per 32 keys, tiles by way of registers and V
-// re-ordered by a launch of its own before); 79 % of the rate of a large library matrix product on the same card (1.38 PFLOP/s).
-// By the counters that is 2.43 M clocks, the same in every run, at 1.69 to 1.80 GHz: the card, good for 2.4, slows down under
-// this load.  Of these clocks the matrix cores are busy 54 %, the vector ALU issues in 50 %, the data path of the LDS is taken 54 % by the
-// operands (at 128 bytes a clock; no bank conflicts, 3 % of the waves' time waiting for it).  A phase lasts 1880 clocks,
-// about the sum of what its two waves have to do on a SIMD (1024 of matrix instructions, 810 of others) and not the larger
-// of the two; why is open.
+// A wave in its matrix phase goes first (s_setprio): it issues one instruction in 32 clocks, and every one that has to wait for
+// the other wave's arithmetic lengthens the phase.  By clock stamps inside the kernel a matrix phase takes 1130 clocks alone, a
+// vector phase 1480 (340 of them its tile loads, whose issue is slow), 2960 for the two.  What is added to a matrix phase -
+// addresses, loads, the look at the masks - comes out at more than it saves in the vector phase: its instructions wait in order
+// for whatever is issued between them (loads among the matrix instructions: 2.21 M clocks on 4 x 8192 tokens, here 1.79 M).
+// 4 x 8192 tokens, 20 / 5 heads of 128: 2.46 -> 2.23 M clocks, 1.24 -> 1.17 ms (the clock goes down under this load, to 1.8 of 2.4
+// GHz); 2 x 5003 263 -> 251 us, 1 x 4096 109 -> 101, 2048 tokens of 32 / 8 heads of 64 32.2 -> 29.7 (priority the other way round, a
+// branch and an address for every load, fmaxf, a wait where the next tile is asked for).
 //
 // kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 64 keys, with their own running
 // (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.64 of the time (1.13 instead of 1.76 us for 64
@@ -113,15 +114,18 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
 }
 
-// 64 x 16 bytes from base + the lanes' offsets to LDS bytes lds .. lds + 1023 (wave-uniform), lane after lane.  In asm, so
-// that the compiler does not order later LDS reads behind it: whoever reads the tile waits for the count (wait_loads) and
-// then passes a barrier.  m0 is declared as written: uses of its own that the compiler makes of it must not lie across this (the
+// 64 x 16 bytes from base + at + the lanes' offsets to LDS bytes lds + at .. + 1023 (wave-uniform; `at` is the instruction's own
+// offset, which moves both ends), lane after lane.  In asm, so that the compiler does not order later LDS reads behind it: whoever
+// reads the tile waits for the count (wait_loads) and then passes a barrier.  m0 is declared as written: uses of its own that the compiler makes of it must not lie across this (the
 // warning, that it will not restore a reserved register, is what is wanted; as an operand that the compiler writes it
 // cost 0.6 % on 4 x 8192 tokens).  (s_nop: m0 may be used by an LDS load one wait state after it was written.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
+template <int At>
 __device__ __forceinline__ void load_to_lds(const char *base, uint32_t off, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds))
+    static_assert(At >= 0 && At < 4096, "13 bits, signed");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(off), "s"(base),
+                 "s"(__builtin_amdgcn_readfirstlane(lds)), "n"(At)
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
@@ -249,17 +253,16 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     auto keys_perm = [](int row) { return D == 128 ? row & 15 : (row >> 1) & 7; };
     auto vals_perm = [](int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); };
     constexpr int kRpl = 64 / kSeg;                              // rows per load
-    static_assert(kIpw * kRpl == kRows, "a wave's loads fill its rows");
-    const int lrow = lane / kSeg, lseg = lane % kSeg;
-    auto lane_off = [&](int i, bool keys, int row) -> uint32_t { // row: of the load's rows, clamped to the keys there are
-        const int r = wave * kRows + i * kRpl + lrow;
-        return row * kRowB + ((lseg ^ (keys ? keys_perm(r) : vals_perm(r))) << 4);
+    static_assert(kIpw * kRpl == kRows && kRpl * kRowB == 1024, "a wave's loads fill its rows");
+    auto lane_off = [&](int i, bool keys, int rows) -> uint32_t { // rows: of the load, those that there are
+        const int l = lane_here(), lrow = l / kSeg, r = wave * kRows + i * kRpl + lrow;
+        return min(lrow, rows - 1) * kRowB + (((l % kSeg) ^ (keys ? keys_perm(r) : vals_perm(r))) << 4);
     };
     uint32_t k_off[kIpw], v_off[kIpw];
 #pragma unroll
     for (int i = 0; i < kIpw; ++i) {
-        k_off[i] = lane_off(i, true, lrow);
-        v_off[i] = lane_off(i, false, lrow);
+        k_off[i] = lane_off(i, true, kRpl);
+        v_off[i] = lane_off(i, false, kRpl);
     }
     // first key row that this wave loads of its group's block in a turn, and which rows the scores of that block are taken from
     struct Source {
@@ -270,15 +273,16 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         const int v = min(kSplit == 1 ? turn : turn * kSplit + grp, nv - 1);   // (past the end: the last block again, unread)
         return {v < n_hat ? Hp : Kp, block_of(v) * KB + (wave * kRows) % KB};
     };
-    auto load_tile = [&](const char *src, int row, int buf, bool keys) {
-        const uint32_t to = lds0 + (keys ? 0 : kBufs * kTile) + buf * kTile + wave * (kRows * kRowB);
+    auto lds_of = [&](int buf, bool keys) { return lds0 + (keys ? 0 : kBufs * kTile) + buf * kTile + wave * (kRows * kRowB); };
+    auto load_tile = [&](const char *src, int row, uint32_t to, bool keys) __attribute__((always_inline)) {
+        if (__builtin_expect(row + kRows <= n, true)) {
+            const char *from = src + (size_t)(uint32_t)row * kRowB;
+            for_each_index<kIpw>([&](auto i) { load_to_lds<i * 1024>(from, keys ? k_off[i] : v_off[i], to); });
+        } else {
 #pragma unroll
-        for (int i = 0; i < kIpw; ++i) {
-            if (row + kRows <= n) {
-                load_to_lds(src + (size_t)(uint32_t)row * kRowB + i * (kRpl * kRowB), keys ? k_off[i] : v_off[i], to + i * 1024);
-            } else {
+            for (int i = 0; i < kIpw; ++i) {
                 const int first = min(row + i * kRpl, n - 1);
-                load_to_lds(src + (size_t)(uint32_t)first * kRowB, lane_off(i, keys, min(lrow, n - 1 - first)), to + i * 1024);
+                load_to_lds<0>(src + (size_t)(uint32_t)first * kRowB, lane_off(i, keys, n - first), to + i * 1024);
             }
         }
     };
@@ -338,7 +342,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    // Masks where some row of the tile does not see all of block v, then online softmax: s -> pb.  The running maximum is
+    // Masks where some row of the wave does not see all of the block, then online softmax: s -> pb.  The running maximum is
     // only raised when the block maximum exceeds it by more than 2^8 in the exponent, so probabilities stay <= 256
     // and the accumulator is rarely rescaled.
     auto softmax = [&](int v) {
@@ -355,15 +359,19 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         }
         float bm;
         {
+            // (maximum, three operands to an instruction, and not fmaxf, which quiets every operand with an instruction of its own:
+            // where a score is NaN its row is NaN either way)
+            auto max3 = [](float x, float y, float z) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); };
             float mx[4];                                         // four chains: one would wait for itself
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                mx[k] = fmaxf(fmaxf(s[0][4 * k], s[0][4 * k + 1]), fmaxf(s[0][4 * k + 2], s[0][4 * k + 3]));
-                if (NT == 2) mx[k] = fmaxf(mx[k], fmaxf(fmaxf(s[NT - 1][4 * k], s[NT - 1][4 * k + 1]), fmaxf(s[NT - 1][4 * k + 2], s[NT - 1][4 * k + 3])));
+                mx[k] = max3(s[0][k], s[0][k + 4], s[0][k + 8]);
+                mx[k] = NT == 1 ? __builtin_elementwise_maximum(mx[k], s[0][k + 12]) : max3(mx[k], s[0][k + 12], s[NT - 1][k]);
+                if (NT == 2) mx[k] = __builtin_elementwise_maximum(max3(mx[k], s[NT - 1][k + 4], s[NT - 1][k + 8]), s[NT - 1][k + 12]);
             }
-            bm = fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3]));
+            bm = __builtin_elementwise_maximum(max3(mx[0], mx[1], mx[2]), mx[3]);
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
-            bm = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * a.scale_log2;
+            bm = __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * a.scale_log2;
         }
         if (__any(bm > m_run + 8.f)) {
             const float m_new = fmaxf(m_run, bm);
@@ -394,42 +402,46 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 
     // ---- the walk.  Tile t lies in buffer t % kBufs.  Key tile t + 2 and value tile t + 1 are requested in turn t's vector
     //      phase, when no wave reads what those buffers held any more - the other group is at most one phase behind, or, with
-    //      kSplit = 2, has rows of its own in every tile - and are waited for two phases later.
+    //      kSplit = 2, has rows of its own in every tile - and are waited for two phases later.  (A fourth buffer, and requests a
+    //      turn earlier, changed nothing.)
     Source s1;                                                   // source of turn t + 1
     auto first_loads = [&]() {
         const Source s0 = source_of(0);
         s1 = source_of(1);
-        load_tile(s0.keys, s0.row, 0, true);
-        load_tile(s1.keys, s1.row, 1, true);
-        load_tile(Vp, s0.row, 0, false);
+        load_tile(s0.keys, s0.row, lds_of(0, true), true);
+        load_tile(s1.keys, s1.row, lds_of(1, true), true);
+        load_tile(Vp, s0.row, lds_of(0, false), false);
     };
     constexpr std::true_type yes;
     constexpr std::false_type no;
     int buf;                                                     // turn % kBufs
     auto after = [](int b) { return b == kBufs - 1 ? 0 : b + 1; };
-    auto vector_phase = [&](int turn) {
-        if (kSplit == 1 && grp == 1) wait_loads<0>();            // key tile turn + 1, value tile turn, which group A is about to read
-        phase_barrier();
-        __builtin_amdgcn_s_setprio(1);
-        const Source s2 = source_of(turn + 2);
-        load_tile(s2.keys, s2.row, after(after(buf)), true);
-        load_tile(Vp, s1.row, after(buf), false);
-        s1 = s2;
-        softmax(kSplit == 1 ? turn : turn * kSplit + grp);
-        __builtin_amdgcn_s_setprio(0);
-        if (kSplit > 1 || grp == 0) wait_loads<kLoads>();
-        phase_barrier();
-    };
     // A tile's outputs are packed, the next tile's loads go out, then the outputs: its first keys are on their way while this
     // one is stored.  (Next tile, or blocks where there is none: `ticket`.)
     const int queues = a.xsplit_log2 >= 0 ? 8 : 1, blocks = a.blocks, end = a.kinds[kSplit - 1].end;
     uint32_t *const queue = a.queue + (pos & (queues - 1)) * kQueueStride;
     const int handed_out = (int)gridDim.x + (pos & (queues - 1));
-    int ticket = blocks;
-    // (asked for three turns before the tile ends: the answer takes 2 us, and whoever asks first gets the longest tile left)
+    // Asked for three turns before the tile ends: the answer takes 2 us, and whoever asks first gets the longest tile left.  In
+    // asm, so that nobody waits for it before it is needed.  (Behind the turn's loads: a wait for older ones then does not wait for it.)
+    const bool asks = wave == 0 && blocks > (int)gridDim.x;
+    uint32_t ticket = 0;
     auto ask = [&](int turn) __attribute__((always_inline)) {
-        if (turn == max(turns - 3, 0) && wave == 0 && blocks > (int)gridDim.x && lane_here() == 0)
-            ticket = handed_out + queues * (int)atomicAdd(queue, 1u);
+        if (asks && turn == max(turns - 3, 0) && lane_here() == 0)
+            asm volatile("global_atomic_add %0, %1, %2, %3 sc0" : "+v"(ticket) : "v"(0), "v"(1), "s"(queue) : "memory");
+    };
+    auto vector_phase = [&](int turn) {
+        if (kSplit == 1 && grp == 1) wait_loads<0>();            // key tile turn + 1, value tile turn, which group A is about to read
+        phase_barrier();
+        __builtin_amdgcn_s_setprio(0);
+        const Source s2 = source_of(turn + 2);
+        load_tile(s2.keys, s2.row, lds_of(after(after(buf)), true), true);
+        load_tile(Vp, s1.row, lds_of(after(buf), false), false);
+        s1 = s2;
+        softmax(kSplit == 1 ? turn : turn * kSplit + grp);
+        ask(turn);
+        __builtin_amdgcn_s_setprio(1);                           // (for the matrix phase that follows)
+        if (kSplit > 1 || grp == 0) wait_loads<kLoads>();
+        phase_barrier();
     };
     open_tile(pos);
     load_queries();
@@ -450,13 +462,11 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
         phase_barrier();
         if (grp == 1) phase_barrier();                           // group B starts one phase later
-        ask(0);
         matrix_phase(no, yes, 0, 0);
         vector_phase(0);
         for (int turn = 1; turn < turns; ++turn) {
             const int prev = buf;
             buf = after(buf);
-            ask(turn);
             matrix_phase(yes, yes, prev, buf);
             vector_phase(turn);
         }
@@ -467,7 +477,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         // ------------------------------------------------------------ epilogue
         float l_tot = (l_run[0] + l_run[1]) + (l_run[2] + l_run[3]);
         l_tot += __shfl_xor(l_tot, 32);
-        if (wave == 0 && lane_here() == 0) *next_tile = ticket;
+        if (wave == 0 && lane_here() == 0) *next_tile = asks ? handed_out + queues * (int)ticket : blocks;
         constexpr int MO = MT / kSplit;                          // channel tiles that this wave stores
         u32x2 packed[MO][4];
         auto pack = [&](int mo, const f32x16 &o, float inv) {
