@@ -349,13 +349,20 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         const int jb = block_of(v) * KB;
         const bool hat = v < n_hat, none = kSplit > 1 && v >= nv;        // (none: a turn in which this group has no block)
         if (none || (hat ? jb + KB > wave_win_first : jb < wave_win_last || jb + KB > wave_first + 1)) {
-            const int lo = hat ? 0 : my_win, cnt = none ? 0 : hat ? my_win : my_i - my_win + 1;   // columns lo .. lo + cnt - 1
-            const int j0 = jb + 4 * half - lo;
+            // the row's columns of the block, [from, to), as bits; two instructions a score: a bit spread over the word chooses (a
+            // compare, a select and the wait for the condition between them took 600 clocks a block, half of the softmax itself)
+            const int row = my_i;
+            const int from = min(max((hat ? 0 : my_win) - jb, 0), KB), to = none ? 0 : min(max((hat ? my_win : row + 1) - jb, 0), KB);
+            uint64_t seen = to > 0 ? ~(uint64_t)0 >> (64 - to) : 0;
+            seen = from < 64 ? seen >> from << from : 0;
+            seen >>= 4 * (lane_here() >> 5);                     // (the lane half's first row is column 4)
 #pragma unroll
             for (int T = 0; T < NT; ++T)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    s[T][r] = (uint32_t)(j0 + 32 * T + 8 * (r >> 2) + (r & 3)) < (uint32_t)cnt ? s[T][r] : -INFINITY;
+                for (int r = 0; r < 16; ++r) {
+                    const uint32_t take = (uint32_t)__builtin_amdgcn_sbfe((int)(uint32_t)(seen >> (32 * T)), 8 * (r >> 2) + (r & 3), 1);
+                    s[T][r] = __uint_as_float((__float_as_uint(s[T][r]) & take) | (0xff800000u & ~take));
+                }
         }
         float bm;
         {
