@@ -618,44 +618,74 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     int xsplit = 0;
     while ((units << xsplit) % 8 != 0) ++xsplit;
     auto even = [&](int tiles) { return (tiles * hgroups) % (1 << xsplit) == 0; };
-    // Whole tiles for the first rows, split ones for the rest.  Of the ways to cut, the one that promises to be done first: a
-    // launch lasts at least as long as its longest tile, as the work per compute unit, and, with more tiles than
-    // compute units, as the two that have to share one (which the pieces of a chunked prefill, all of about one length, come
-    // up against).  In units of one whole tile over 64 keys: a tile has kOpen of overhead, a split one takes kSplitTurn for 64 keys
-    // (measured: 0.62 to 0.64; a launch of one tile per compute unit 5.4 whole and 6.0 split, itself included - a tile that follows
-    // another has its loads out earlier).
-    // Against the best of 13 cuts of each of 15 launches the one chosen is within 2 % on 9; the worst are 4 x 1024 tokens (20 / 5
-    // heads of 128: 53.9 us, all whole 45.4), 16 x 200 (33.8, three of four row tiles whole 28.9) and 1 x 4096 (113, 53 of 64 whole 102).
-    constexpr double kOpen = 2.2, kSplitTurn = 0.6;
+    // Whole tiles for the first rows, split ones for the rest.  Of some ways to cut, the one that promises to be done first: with
+    // the tiles in order of length, longest first, a launch on C compute units lasts at least as long as its work / C, and as
+    // the k + 1 shortest of its kC + 1 longest tiles, which some compute unit has to take; the estimate is the largest of these.
+    // In units of a whole tile's turn a tile costs kWhole or kHalf beside its turns, and a split one's turn kHalfTurn (fitted to 250
+    // timed launches of 42 shapes, 8 % off on the average; head_dim 64: work of the two that share a compute unit, where one
+    // alone takes kAlone times as long).  Against the best of up to 13 cuts of each shape the chosen one is 1.0 % slower on the
+    // average at head_dim 128 and 1.1 % at 64, where looking at k = 1 alone was 6.0 and 3.9 %: 1 x 4096 tokens, 20 / 5 heads
+    // of 128, 103 -> 93 us, 2 x 5003 in a sliding window 276 -> 247, 4 x 512 26.7 -> 22.4, 4 x 1024 48.1 -> 43.1.
+    constexpr float kWhole = D == 128 ? 6.5f : 4.2f, kHalf = D == 128 ? 6.5f : 4.4f, kHalfTurn = D == 128 ? 1.22f : 0.93f, kAlone = D == 128 ? 1.f : 1.19f;
     const int all = (p.nq + rt - 1) / rt, columns = units * hgroups;
-    double best = INFINITY;
-    bool best_even = false;
-    const int step = all > 32 ? (all + 31) / 32 : 1;
-    for (int whole = 0;; whole = min(whole + step, all)) {       // row tiles that stay whole
-        const int rows = min(whole * rt, p.nq), split = (p.nq - rows + rt / 2 - 1) / (rt / 2);
-        auto length = [&](int level) {                           // of the level-th longest row tile
-            return level < split ? kOpen + kSplitTurn * (p.n - level * (rt / 2)) / 64.0
-                                 : kOpen + (p.q_off + rows - (level - split) * rt) / 64.0;
+    // turns of a tile of R rows from row i0 on (see open_tile)
+    auto turns = [&](int i0, int R) {
+        auto win_start = [&](int r) {
+            return p.sliding ? (r - p.W + 1 > 0 ? r - p.W + 1 : 0) : (int)(((uint64_t)(2u * (uint32_t)r) * a.by_w.mul >> 32) >> a.by_w.shift) * p.W;
         };
-        const double work = split * 0.5 * (length(0) + length(split - 1)) + whole * 0.5 * (length(split) + length(split + whole - 1));
-        const int blocks = columns * (whole + split);
-        double lasts = fmax(work * columns / cus, split > 0 ? length(0) : 0.0);
-        if (whole > 0) lasts = fmax(lasts, length(split));
-        if (blocks > cus) lasts = fmax(lasts, length((cus - 1) / columns) + length(cus / columns));
-        const bool ordered = xsplit < 3 && even(whole) && even(split);
-        if (!ordered) lasts *= 1.1;                              // (every XCD streams every unit; timed, 0.96 to 1.03)
-        if (lasts < best) {
-            best = lasts;
-            best_even = ordered;
-            a.kinds[1] = {__builtin_ctz(rt / 2), split, rows, 0, columns * split};
-            a.kinds[0] = {__builtin_ctz(rt), whole, 0, columns * split, blocks};
+        i0 += p.q_off;
+        const int last = (i0 + R < p.n ? i0 + R : p.n) - 1;
+        return (win_start(last) + KB - 1) / KB + last / KB - win_start(i0) / KB + 1;
+    };
+    auto cut = [&](int whole, bool ordered) {
+        const int rows = whole * rt < p.nq ? whole * rt : p.nq, split = (p.nq - rows + rt / 2 - 1) / (rt / 2);
+        a.kinds[1] = {__builtin_ctz(rt / 2), split, rows, 0, columns * split};
+        a.kinds[0] = {__builtin_ctz(rt), whole, 0, columns * split, columns * (whole + split)};
+        a.xsplit_log2 = ordered ? xsplit : -1;
+    };
+    constexpr int kMost = 1024;                                  // row tiles that are looked at: with more, all stay whole
+    if (all > kMost) {
+        cut(all, xsplit < 3 && even(all));
+    } else {
+        float whole_cost[kMost], half_cost[2 * kMost];           // of a row tile, and of every half of one
+        const int halves = (p.nq + rt / 2 - 1) / (rt / 2);
+        for (int t = 0; t < all; ++t) whole_cost[t] = kWhole + (float)turns(t * rt, rt);
+        for (int t = 0; t < halves; ++t) half_cost[t] = kHalf + kHalfTurn * (float)((turns(t * (rt / 2), rt / 2) + 1) / 2);
+        // (few ways where there are many tiles to a compute unit: less is at stake)
+        const bool many = (int64_t)all * columns > 8 * (int64_t)cus;
+        const int ways = many ? 32 : 10, step = (all + ways - 1) / ways, fewest = many ? all - 4 * step : 0;
+        float best = INFINITY;
+        for (int whole = all;; whole = whole > step ? (whole - 1) / step * step : 0) {   // row tiles that stay whole
+            float work = 0.f, lasts = 0.f;
+            int64_t tiles = 0, level = 0;                        // tiles so far; the next k
+            for (int w = whole - 1, h = halves - 1; w >= 0 || h >= 2 * whole;) {
+                const bool takes_half = w < 0 || (h >= 2 * whole && half_cost[h] > whole_cost[w]);
+                const float cost = takes_half ? half_cost[h--] : whole_cost[w--];
+                tiles += columns;
+                work += cost * (float)columns;
+                for (; tiles > level * cus; ++level) lasts = fmaxf(lasts, (float)(level + 1) * cost * (level == 0 ? kAlone : 1.f));
+            }
+            lasts = fmaxf(lasts, work / (float)cus);
+            const int split = halves > 2 * whole ? halves - 2 * whole : 0;
+            if (D == 64 && tiles > cus && tiles <= slots) {      // tile j shares with the j-th last one (turn_at)
+                auto cost_at = [&](int at) { return at < split ? half_cost[halves - 1 - at] : whole_cost[whole - 1 - (at - split)]; };
+                for (int j = 0; j < (int)tiles - cus; j += columns > 8 ? columns : 8)
+                    lasts = fmaxf(lasts, cost_at(j / columns) + cost_at(((int)tiles - 1 - j) / columns));
+                lasts = fmaxf(lasts, cost_at(((int)tiles - cus - 1) / columns) + cost_at(cus / columns));
+            }
+            const bool ordered = xsplit < 3 && even(whole) && even(split);
+            if (!ordered) lasts *= 1.02f;                        // (every XCD streams every unit; timed, 0.96 to 1.03)
+            if (lasts <= best) {                                 // (of equals the one with more split tiles: the rest are done earlier)
+                best = lasts;
+                cut(whole, ordered);
+            }
+            if (whole <= fewest || whole == 0) break;
         }
-        if (whole == all) break;
     }
     a.blocks = a.kinds[0].end;
-    a.xsplit_log2 = best_even ? xsplit : -1;
-    if (best_even) a.by_parts = divisor((units << xsplit) / 8);
-    a.turn_at = D == 64 && a.blocks > cus && a.blocks <= slots && best_even ? cus : a.blocks;
+    const bool ordered = a.xsplit_log2 >= 0;
+    if (ordered) a.by_parts = divisor((units << xsplit) / 8);
+    a.turn_at = D == 64 && a.blocks > cus && a.blocks <= slots && ordered ? cus : a.blocks;
     constexpr int lds = 4 * KB * 2 * D * 2 + 16;                 // split tiles take more
     static_assert(lds >= 6 * KB * D * 2 + 16 && lds >= 2 * 4 * (D / 64) * 16 * 64 * 4 + 2 * 4 * 64 * 2 * 4, "whole tiles, the merge");
     static std::atomic<uint64_t> lds_set;                        // per instantiation, one bit per device
