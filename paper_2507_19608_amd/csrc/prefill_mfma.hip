@@ -31,6 +31,11 @@
 // GHz); 2 x 5003 263 -> 251 us, 1 x 4096 109 -> 101, 2048 tokens of 32 / 8 heads of 64 32.2 -> 29.7 (priority the other way round, a
 // branch and an address for every load, fmaxf, a wait where the next tile is asked for).
 //
+// kStream: where many whole tiles, or long ones, follow each other on a compute unit, the next one's first keys and queries are
+// requested, and its first scores taken, while the last one's values are still added up and its outputs stored: 16 to 19 K clocks
+// lie between two tiles otherwise (turns aside).  2 x 5003 tokens 263 -> 250 us, 4 x 8192 2.23 -> 2.02 M clocks, of which the clock takes
+// half back: 1.17 -> 1.14 ms.
+//
 // kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 64 keys, with their own running
 // (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.64 of the time (1.13 instead of 1.76 us for 64
 // keys at head_dim 128, 0.81 instead of 1.31 at 64: the same work per wave, twice the loads): for the last, longest rows of a
@@ -129,6 +134,11 @@ __device__ __forceinline__ void load_to_lds(const char *base, uint32_t off, uint
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
+// 16 bytes a lane that the caller waits for
+template <int At>
+__device__ __forceinline__ void load_in_flight(u32x4 &to, const char *base, uint32_t off) {
+    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "+v"(to) : "v"(off), "s"(base), "n"(At) : "memory");
+}
 template <int N>
 __device__ __forceinline__ void wait_loads() {                   // until at most N of this wave's loads are in flight
     static_assert(N < 64, "six bits of the count");
@@ -160,7 +170,7 @@ __device__ __forceinline__ int lane_here() {
 
 // The tiles of one kind: those at `pos` and the positions the queue hands out after it; returns the first of these past the
 // kind's end.  a: the kernel's argument, of which the walk keeps a few words in registers.
-template <int D, int kSplit>
+template <int D, int kSplit, bool kStream>
 __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *lds_raw) {
     constexpr int kRowB = D * 2;                // bytes of a row
     constexpr int kSeg = D / 8;                 // 16-byte segments of a row
@@ -183,23 +193,40 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     const int n = a.n;
     const int my_sr = 32 * (kSplit == 1 ? wave : wave & 3);     // the wave's first score row
 
-    // ---- the tile
+    // ---- the tile whose keys and values are being requested
     const char *Kp, *Hp, *Vp;
     const bf16_t *q_rows;                       // where position 0 of the wave's head would be in Q
     bf16_t *o_rows;                             // ... in O
-    int wave_first, wave_win_first, wave_win_last;              // rows of this wave: wave_first .. + 31, their first exact columns
-    bool wave_past;                             // all of them lie past the end
-    int my_i, my_win;                           // this lane's row (both lane halves) and its first exact column
+    int first;                                  // rows of this wave: first .. + 31, some or all of which may lie past the end
     int n_hat, kb0, nv, turns;                  // the list of blocks: n_hat from key 0 on for K_hat, then kb0 .. for K
+    // first exact column of row r: start of its square, or of its band (monotone in r either way)
+    auto win_start = [](const auto &a, int r) { return a.sliding ? max(r - a.W + 1, 0) : quotient(r, a.by_w) * a.W; };
     // (what a tile needs of the arguments is read for every tile: kept in registers across the walk, it would not fit)
-    auto open_tile = [&](int pos) __attribute__((always_inline)) {
+    auto arguments = []() __attribute__((always_inline)) {
         auto *ap = (const __attribute__((address_space(4))) MfmaArgs *)__builtin_amdgcn_kernarg_segment_ptr();
         asm volatile("" : "+s"(ap));
-        const auto &a = *ap;
+        return ap;
+    };
+    // ---- the tile whose scores are taken: with kStream a tile is opened while the one before is still worked on
+    int my_win;                                 // this lane's row's first exact column (both lane halves; past the end: the last row again)
+    int wave_first, wave_win_first, wave_win_last;              // first row of the wave, first exact columns of its first and last
+    int at_hat, at_kb0, at_nv, at_turns;        // n_hat .. turns
+    bf16_t *out_rows;
+    auto my_row = [&]() { return min(wave_first + (lane_here() & 31), n - 1); };
+    auto take_rows = [&](const auto &a) __attribute__((always_inline)) {
+        const int last = a.n - 1;
+        wave_first = min(first, last);
+        my_win = win_start(a, min(first + (lane_here() & 31), last));
+        wave_win_first = win_start(a, wave_first);
+        wave_win_last = win_start(a, min(wave_first + 31, last));
+        at_hat = n_hat, at_kb0 = kb0, at_nv = nv, at_turns = turns;
+        out_rows = o_rows;
+    };
+    auto take_tile = [&]() __attribute__((always_inline)) { take_rows(*arguments()); };
+    auto open_tile = [&](int pos) __attribute__((always_inline)) {
+        const auto &a = *arguments();
         const auto &kind = a.kinds[kSplit - 1];
-        const int n = a.n, W = a.W, RT = 1 << kind.rt_log2;
-        // first exact column of row r: start of its square, or of its band (monotone in r either way)
-        auto win_start = [&](int r) { return a.sliding ? max(r - W + 1, 0) : quotient(r, a.by_w) * W; };
+        const int n = a.n, RT = 1 << kind.rt_log2;
         const int at = pos - kind.first;
         int unit, bid;
         if (a.xsplit_log2 >= 0) {
@@ -221,29 +248,27 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         Vp = (const char *)(a.V + (size_t)unit * a.ld * D);
         // a wave's 32 score rows are consecutive rows of one head (RT is a multiple of 32)
         const int head = hk * a.g + hchunk * a.GH + (my_sr >> kind.rt_log2);
-        wave_first = i0 + (my_sr & (RT - 1));
+        first = i0 + (my_sr & (RT - 1));
         const size_t row0 = ((size_t)b * a.Hq + head) * a.nq - a.q_off;
         q_rows = a.Q + row0 * D;
         o_rows = a.O + row0 * D;
-        my_i = min(wave_first + (lane_here() & 31), n - 1);      // (rows past the end: the last one again)
-        wave_past = wave_first >= n;
-        wave_first = min(wave_first, n - 1);
-        wave_win_first = win_start(wave_first);
-        wave_win_last = win_start(min(wave_first + 31, n - 1));
-        my_win = win_start(my_i);
-        const int win_first = win_start(i0), win_last = win_start(i_last);
+        const int win_first = win_start(a, i0), win_last = win_start(a, i_last);
         n_hat = (win_last + KB - 1) / KB;
         kb0 = win_first / KB;
         nv = n_hat + i_last / KB - kb0 + 1;
-        turns = (nv + kSplit - 1) / kSplit;
+        turns = kStream ? max(nv, 2) : (nv + kSplit - 1) / kSplit;
+        if constexpr (!kStream) take_rows(a);
     };
-    auto block_of = [&](int v) { return v < n_hat ? v : kb0 + v - n_hat; };
-
     u32x4 qreg[KS];
-    auto load_queries = [&]() {
-        const bf16_t *my_q = q_rows + (ptrdiff_t)my_i * D + (lane_here() >> 5) * 8;
+    // (the addresses are those of the opened tile; in asm, since the compiler, where it counts these loads, waits for
+    // them at their first use inside the loop and there drains the tile loads, every turn: wait_loads, then have_queries)
+    auto load_queries = [&]() __attribute__((always_inline)) {
+        const uint32_t off = min(first + (lane_here() & 31), n - 1) * kRowB + (lane_here() >> 5) * 16;
+        for_each_index<KS>([&](auto ks) { load_in_flight<ks * 32>(qreg[ks], (const char *)q_rows, off); });
+    };
+    auto have_queries = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) qreg[ks] = *(const u32x4 *)(my_q + ks * 16);
+        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
     };
 
     // ---- tile loads: a wave fills kRows rows of the tile (of its own group's block), 1 KiB load i the rows r .. r + 64 / kSeg - 1
@@ -271,7 +296,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     };
     auto source_of = [&](int turn) -> Source {
         const int v = min(kSplit == 1 ? turn : turn * kSplit + grp, nv - 1);   // (past the end: the last block again, unread)
-        return {v < n_hat ? Hp : Kp, block_of(v) * KB + (wave * kRows) % KB};
+        return {v < n_hat ? Hp : Kp, (v < n_hat ? v : kb0 + v - n_hat) * KB + (wave * kRows) % KB};
     };
     auto lds_of = [&](int buf, bool keys) { return lds0 + (keys ? 0 : kBufs * kTile) + buf * kTile + wave * (kRows * kRowB); };
     auto load_tile = [&](const char *src, int row, uint32_t to, bool keys) __attribute__((always_inline)) {
@@ -335,7 +360,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 }
             }
         };
-        constexpr int kAhead = 5;
+        constexpr int kAhead = D == 64 ? 4 : 5;
         for_each_index<nv + nk + kAhead>([&](auto i) {
             if constexpr (i >= kAhead) multiply(std::integral_constant<int, i - kAhead>{});
             if constexpr (i < nv + nk) read(i);
@@ -346,12 +371,12 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     // only raised when the block maximum exceeds it by more than 2^8 in the exponent, so probabilities stay <= 256
     // and the accumulator is rarely rescaled.
     auto softmax = [&](int v) {
-        const int jb = block_of(v) * KB;
-        const bool hat = v < n_hat, none = kSplit > 1 && v >= nv;        // (none: a turn in which this group has no block)
+        const bool hat = v < at_hat, none = v >= at_nv;          // (none: a turn in which this group has no block)
+        const int jb = (hat ? v : at_kb0 + v - at_hat) * KB;
         if (none || (hat ? jb + KB > wave_win_first : jb < wave_win_last || jb + KB > wave_first + 1)) {
             // the row's columns of the block, [from, to), as bits; two instructions a score: a bit spread over the word chooses (a
             // compare, a select and the wait for the condition between them took 600 clocks a block, half of the softmax itself)
-            const int row = my_i;
+            const int row = my_row();
             const int from = min(max((hat ? 0 : my_win) - jb, 0), KB), to = none ? 0 : min(max((hat ? my_win : row + 1) - jb, 0), KB);
             uint64_t seen = to > 0 ? ~(uint64_t)0 >> (64 - to) : 0;
             seen = from < 64 ? seen >> from << from : 0;
@@ -407,54 +432,31 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             }
     };
 
-    // ---- the walk.  Tile t lies in buffer t % kBufs.  Key tile t + 2 and value tile t + 1 are requested in turn t's vector
-    //      phase, when no wave reads what those buffers held any more - the other group is at most one phase behind, or, with
-    //      kSplit = 2, has rows of its own in every tile - and are waited for two phases later.  (A fourth buffer, and requests a
-    //      turn earlier, changed nothing.)
-    Source s1;                                                   // source of turn t + 1
-    auto first_loads = [&]() {
-        const Source s0 = source_of(0);
-        s1 = source_of(1);
-        load_tile(s0.keys, s0.row, lds_of(0, true), true);
-        load_tile(s1.keys, s1.row, lds_of(1, true), true);
-        load_tile(Vp, s0.row, lds_of(0, false), false);
-    };
+    // ---- the walk.  The tiles of turn t lie in buffers t % kBufs.  The key tile of turn t + 2 and the value tile of turn t + 1 are
+    //      requested in turn t's vector phase, when no wave reads what those buffers held any more - the other group is at
+    //      most one phase behind, or, with kSplit = 2, has rows of its own in every tile - and are waited for two phases later.
+    //      (A fourth buffer, and requests a turn earlier, changed nothing.)
+    const char *values;                                          // whose value rows are requested next
+    int values_row;
     constexpr std::true_type yes;
     constexpr std::false_type no;
-    int buf;                                                     // turn % kBufs
+    int buf = 0;                                                 // turn % kBufs
     auto after = [](int b) { return b == kBufs - 1 ? 0 : b + 1; };
-    // A tile's outputs are packed, the next tile's loads go out, then the outputs: its first keys are on their way while this
-    // one is stored.  (Next tile, or blocks where there is none: `ticket`.)
-    const int queues = a.xsplit_log2 >= 0 ? 8 : 1, blocks = a.blocks, end = a.kinds[kSplit - 1].end;
-    uint32_t *const queue = a.queue + (pos & (queues - 1)) * kQueueStride;
-    const int handed_out = (int)gridDim.x + (pos & (queues - 1));
-    // Asked for three turns before the tile ends: the answer takes 2 us, and whoever asks first gets the longest tile left.  In
-    // asm, so that nobody waits for it before it is needed.  (Behind the turn's loads: a wait for older ones then does not wait for it.)
-    const bool asks = wave == 0 && blocks > (int)gridDim.x;
-    uint32_t ticket = 0;
-    auto ask = [&](int turn) __attribute__((always_inline)) {
-        if (asks && turn == max(turns - 3, 0) && lane_here() == 0)
-            asm volatile("global_atomic_add %0, %1, %2, %3 sc0" : "+v"(ticket) : "v"(0), "v"(1), "s"(queue) : "memory");
+    auto request = [&](int turn, int key_buf, int value_buf) __attribute__((always_inline)) {   // turn: of the opened tile
+        const Source far = source_of(turn);
+        load_tile(far.keys, far.row, lds_of(key_buf, true), true);
+        load_tile(values, values_row, lds_of(value_buf, false), false);
+        values = Vp;
+        values_row = far.row;
     };
-    auto vector_phase = [&](int turn) {
-        if (kSplit == 1 && grp == 1) wait_loads<0>();            // key tile turn + 1, value tile turn, which group A is about to read
-        phase_barrier();
-        __builtin_amdgcn_s_setprio(0);
-        const Source s2 = source_of(turn + 2);
-        load_tile(s2.keys, s2.row, lds_of(after(after(buf)), true), true);
-        load_tile(Vp, s1.row, lds_of(after(buf), false), false);
-        s1 = s2;
-        softmax(kSplit == 1 ? turn : turn * kSplit + grp);
-        ask(turn);
-        __builtin_amdgcn_s_setprio(1);                           // (for the matrix phase that follows)
-        if (kSplit > 1 || grp == 0) wait_loads<kLoads>();
-        phase_barrier();
+    auto first_loads = [&]() __attribute__((always_inline)) {
+        const Source s0 = source_of(0);
+        load_tile(s0.keys, s0.row, lds_of(0, true), true);
+        values = Vp;
+        values_row = s0.row;
+        request(1, 1, 0);
     };
-    open_tile(pos);
-    load_queries();
-    first_loads();
-    wait_loads<0>();
-    while (true) {
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -462,90 +464,247 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         m_run = -INFINITY;
 #pragma unroll
         for (int k = 0; k < 4; ++k) l_run[k] = 0.f;
-        buf = 0;
-        // (the queries are waited for here: left to the compiler, the wait would stand at their first use inside the loop and
-        // there drain the tile loads, every turn)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));
+    };
+    auto row_sum = [&]() {
+        const float l = (l_run[0] + l_run[1]) + (l_run[2] + l_run[3]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+        return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    };
+    auto packed = [](const f32x16 &o, int q4, float inv) {
+        return u32x2{pack_bf16x2(o[4 * q4 + 0] * inv, o[4 * q4 + 1] * inv), pack_bf16x2(o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv)};
+    };
+    const int queues = a.xsplit_log2 >= 0 ? 8 : 1, blocks = a.blocks, end = a.kinds[kSplit - 1].end;
+    uint32_t *const queue = a.queue + (pos & (queues - 1)) * kQueueStride;
+    const int handed_out = (int)gridDim.x + (pos & (queues - 1));
+    const bool asks = blocks > (int)gridDim.x;
+    uint32_t ticket = 0;
+    // Wave 0 asks for the next tile; in asm, so that nobody waits for the answer (2 us) before it is needed.
+    auto ask = [&]() __attribute__((always_inline)) {
+        if (asks && wave == 0 && lane_here() == 0)
+            asm volatile("global_atomic_add %0, %1, %2, %3 sc0" : "+v"(ticket) : "v"(0), "v"(1), "s"(queue) : "memory");
+    };
+    // ... and tells the others, once it has waited for the answer; `blocks`: there is none
+    auto tell = [&]() __attribute__((always_inline)) {
+        if (wave == 0 && lane_here() == 0) *next_tile = asks ? handed_out + queues * (int)ticket : blocks;
+    };
+    auto told = [&]() __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*next_tile); };
+
+    if constexpr (kStream) {
+        // Tile follows tile without a pause: the requests run two turns ahead of the scores, across the end of a tile into the
+        // next one, and the phase that adds up a tile's last values takes the scores of the next one's first keys.  Its
+        // outputs are stored in the vector phase after that.  (Drained and filled again, a tile cost 16 to 19 K clocks beside its
+        // turns of 2960.)  The next tile is asked for so early that its number is there when it is opened, two
+        // turns before the end; hence at least two turns a tile (the second one sees nothing where there is one block).
+        open_tile(pos);
+        load_queries();
+        first_loads();
+        bool early = turns < 4;                                  // (too short to ask on the way)
+        if (early) ask();
+        take_tile();
+        clear();
+        int turn = 0, opened = 2;                                // of the tile that is worked on; requested turns of the opened one
+        bool ahead = false, full = false;                        // the opened tile is the next one; the accumulators hold a finished tile
+        bf16_t *full_rows = nullptr;                             // its rows
+        int full_first = 0, taken = first;
+        bool stored = false;                                     // in the vector phase before
+        wait_loads<0>();
+        have_queries();
+        if (early) tell();
         phase_barrier();
         if (grp == 1) phase_barrier();                           // group B starts one phase later
         matrix_phase(no, yes, 0, 0);
-        vector_phase(0);
-        for (int turn = 1; turn < turns; ++turn) {
+        while (true) {
+            // the key tile of turn + 1 and the value tile of turn, which group A is about to read (loads and stores end in order)
+            if (grp == 1) {
+                if (stored)
+                    wait_loads<4 * MT>();
+                else
+                    wait_loads<0>();
+            }
+            phase_barrier();
+            __builtin_amdgcn_s_setprio(0);
+            const bool last = turn == at_turns - 1;
+            if (last && ahead) load_queries();                   // (nobody multiplies by the old ones any more)
+            if (opened == turns && !ahead) {
+                const int next = told();
+                if (next < end) {
+                    open_tile(next);
+                    ahead = true;
+                    opened = 0;
+                }
+            }
+            request(opened, after(after(buf)), after(buf));
+            const bool asking = opened == turns - 2, telling = opened == turns - 1;
+            if (opened < turns) ++opened;
+            const bool stores = full && full_first < n;
+            if (full) {
+                const float inv = 1.f / row_sum();
+                const int lane = lane_here();
+                if (stores) {
+                    bf16_t *const orow = full_rows + (ptrdiff_t)min(full_first + (lane & 31), n - 1) * D + 4 * (lane >> 5);
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                        for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mt * 32 + 8 * q4) = packed(oacc[mt], q4, inv);
+                }
+                clear();
+            }
+            softmax(turn);
+            __builtin_amdgcn_s_setprio(1);                       // (for the matrix phase that follows)
+            if (grp == 0 || (last && ahead)) {                   // what was asked for in earlier turns, the queries
+                if (stores)
+                    wait_loads<kLoads + 4 * MT>();
+                else
+                    wait_loads<kLoads>();
+            }
+            have_queries();
+            if (telling) tell();
+            if (asking) ask();
+            phase_barrier();
             const int prev = buf;
             buf = after(buf);
+            if (last && !ahead) break;
             matrix_phase(yes, yes, prev, buf);
-            vector_phase(turn);
-        }
-        matrix_phase(yes, no, buf, 0);
-        if (grp == 0) phase_barrier();                           // (group B's last softmax phase)
-        wait_loads<0>();                                         // no load into LDS outlives its tile
-
-        // ------------------------------------------------------------ epilogue
-        float l_tot = (l_run[0] + l_run[1]) + (l_run[2] + l_run[3]);
-        l_tot += __shfl_xor(l_tot, 32);
-        if (wave == 0 && lane_here() == 0) *next_tile = asks ? handed_out + queues * (int)ticket : blocks;
-        constexpr int MO = MT / kSplit;                          // channel tiles that this wave stores
-        u32x2 packed[MO][4];
-        auto pack = [&](int mo, const f32x16 &o, float inv) {
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                packed[mo][q4] = u32x2{pack_bf16x2(o[4 * q4 + 0] * inv, o[4 * q4 + 1] * inv), pack_bf16x2(o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv)};
-        };
-        __syncthreads();                                         // the tiles are done with
-        pos = __builtin_amdgcn_readfirstlane(*next_tile);
-        const int lane = lane_here();
-        if constexpr (kSplit == 1) {
-            const float inv = 1.f / l_tot;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) pack(mt, oacc[mt], inv);
-        } else {
-            // wave w of group A and wave w of group B hold the same rows: each hands the other half of its channels over and
-            // finishes its own half
-            float *xo = (float *)lds_raw;                        // [group][wave of the group][MO][16][64]
-            float *xm = xo + 2 * 4 * MO * 16 * 64;               // [group][wave of the group][64][2] maximum, sum
-            const int w4 = wave & 3, other = 1 - grp;
-#pragma unroll
-            for (int mo = 0; mo < MO; ++mo)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    xo[(((grp * 4 + w4) * MO + mo) * 16 + r) * 64 + lane] = grp == 0 ? oacc[MO + mo][r] : oacc[mo][r];
-            xm[((grp * 4 + w4) * 64 + lane) * 2] = m_run;
-            xm[((grp * 4 + w4) * 64 + lane) * 2 + 1] = l_tot;
-            __syncthreads();
-            const float m2 = xm[((other * 4 + w4) * 64 + lane) * 2], l2 = xm[((other * 4 + w4) * 64 + lane) * 2 + 1];
-            const float M = fmaxf(m_run, m2);                    // (a row sees its own key: one of the two is finite)
-            const float f1 = __builtin_amdgcn_exp2f(m_run - M), f2 = __builtin_amdgcn_exp2f(m2 - M);
-            const float inv = 1.f / (l_tot * f1 + l2 * f2);
-#pragma unroll
-            for (int mo = 0; mo < MO; ++mo) {
-                f32x16 o;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float x = xo[(((other * 4 + w4) * MO + mo) * 16 + r) * 64 + lane];
-                    o[r] = (grp == 0 ? oacc[mo][r] : oacc[MO + mo][r]) * f1 + x * f2;
-                }
-                pack(mo, o, inv);
+            stored = stores;
+            full = last;
+            if (last) {
+                full_rows = out_rows;
+                full_first = taken;
+                taken = first;
+                take_tile();
+                ahead = false;
+                turn = 0;
+            } else {
+                ++turn;
             }
-            __syncthreads();                                     // the exchange is done with
+            // the turns of a tile in which nothing else is to be done: not the first one, which stores, nor the last four
+            for (; turn > 0 && turn + 4 < at_turns; ++turn) {
+                if (grp == 1) wait_loads<0>();
+                phase_barrier();
+                __builtin_amdgcn_s_setprio(0);
+                request(opened++, after(after(buf)), after(buf));
+                softmax(turn);
+                __builtin_amdgcn_s_setprio(1);
+                if (grp == 0) wait_loads<kLoads>();
+                phase_barrier();
+                const int prev = buf;
+                buf = after(buf);
+                matrix_phase(yes, yes, prev, buf);
+                stored = false;
+            }
         }
-        bf16_t *const orow = o_rows + (ptrdiff_t)my_i * D + 4 * (lane >> 5) + (kSplit > 1 ? grp * (D / 2) : 0);
-        const bool more = pos < end, stores = !wave_past;
-        if (more) {
-            open_tile(pos);
-            load_queries();
-            first_loads();
-        }
-        if (stores) {
+        matrix_phase(yes, no, buf == 0 ? kBufs - 1 : buf - 1, 0);
+        if (grp == 0) phase_barrier();                           // (group B's last vector phase)
+        wait_loads<0>();                                         // no load into LDS outlives the work group
+        const float inv = 1.f / row_sum();
+        const int lane = lane_here();
+        if (taken < n) {
+            bf16_t *const orow = out_rows + (ptrdiff_t)my_row() * D + 4 * (lane >> 5);
 #pragma unroll
-            for (int mo = 0; mo < MO; ++mo)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mo * 32 + 8 * q4) = packed[mo][q4];
-            wait_loads<4 * MO>();                                // for all but the stores
-        } else {
-            wait_loads<0>();
+                for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mt * 32 + 8 * q4) = packed(oacc[mt], q4, inv);
         }
-        if (!more) return pos;
+        return blocks;
+    } else {
+        auto vector_phase = [&](int turn) __attribute__((always_inline)) {
+            if (kSplit == 1 && grp == 1) wait_loads<0>();        // key tile turn + 1, value tile turn, which group A is about to read
+            phase_barrier();
+            __builtin_amdgcn_s_setprio(0);
+            request(turn + 2, after(after(buf)), after(buf));
+            softmax(kSplit == 1 ? turn : turn * kSplit + grp);
+            // asked for three turns before the tile ends: whoever asks first gets the longest tile left (behind the turn's
+            // loads: a wait for older ones then does not wait for it)
+            if (turn == max(turns - 3, 0)) ask();
+            __builtin_amdgcn_s_setprio(1);                       // (for the matrix phase that follows)
+            if (kSplit > 1 || grp == 0) wait_loads<kLoads>();
+            phase_barrier();
+        };
+        open_tile(pos);
+        load_queries();
+        first_loads();
+        wait_loads<0>();
+        while (true) {
+            clear();
+            buf = 0;
+            have_queries();
+            phase_barrier();
+            if (grp == 1) phase_barrier();                       // group B starts one phase later
+            matrix_phase(no, yes, 0, 0);
+            vector_phase(0);
+            for (int turn = 1; turn < turns; ++turn) {
+                const int prev = buf;
+                buf = after(buf);
+                matrix_phase(yes, yes, prev, buf);
+                vector_phase(turn);
+            }
+            matrix_phase(yes, no, buf, 0);
+            if (grp == 0) phase_barrier();                       // (group B's last vector phase)
+            wait_loads<0>();                                     // no load into LDS outlives its tile
+            const float l_tot = row_sum();
+            tell();
+            constexpr int MO = MT / kSplit;                      // channel tiles that this wave stores
+            u32x2 words[MO][4];
+            __syncthreads();                                     // the tiles are done with
+            pos = told();
+            const int lane = lane_here();
+            if constexpr (kSplit == 1) {
+                const float inv = 1.f / l_tot;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) words[mt][q4] = packed(oacc[mt], q4, inv);
+            } else {
+                // wave w of group A and wave w of group B hold the same rows: each hands the other half of its channels over and
+                // finishes its own half
+                float *xo = (float *)lds_raw;                    // [group][wave of the group][MO][16][64]
+                float *xm = xo + 2 * 4 * MO * 16 * 64;           // [group][wave of the group][64][2] maximum, sum
+                const int w4 = wave & 3, other = 1 - grp;
+#pragma unroll
+                for (int mo = 0; mo < MO; ++mo)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        xo[(((grp * 4 + w4) * MO + mo) * 16 + r) * 64 + lane] = grp == 0 ? oacc[MO + mo][r] : oacc[mo][r];
+                xm[((grp * 4 + w4) * 64 + lane) * 2] = m_run;
+                xm[((grp * 4 + w4) * 64 + lane) * 2 + 1] = l_tot;
+                __syncthreads();
+                const float m2 = xm[((other * 4 + w4) * 64 + lane) * 2], l2 = xm[((other * 4 + w4) * 64 + lane) * 2 + 1];
+                const float M = fmaxf(m_run, m2);                // (a row sees its own key: one of the two is finite)
+                const float f1 = __builtin_amdgcn_exp2f(m_run - M), f2 = __builtin_amdgcn_exp2f(m2 - M);
+                const float inv = 1.f / (l_tot * f1 + l2 * f2);
+#pragma unroll
+                for (int mo = 0; mo < MO; ++mo) {
+                    f32x16 o;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float x = xo[(((other * 4 + w4) * MO + mo) * 16 + r) * 64 + lane];
+                        o[r] = (grp == 0 ? oacc[mo][r] : oacc[MO + mo][r]) * f1 + x * f2;
+                    }
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) words[mo][q4] = packed(o, q4, inv);
+                }
+                __syncthreads();                                 // the exchange is done with
+            }
+            bf16_t *const orow = out_rows + (ptrdiff_t)my_row() * D + 4 * (lane >> 5) + (kSplit > 1 ? grp * (D / 2) : 0);
+            const bool more = pos < end, stores = first < n;     // (first: still this tile's)
+            // the next tile's loads go out, then the outputs: its first keys are on their way while these are stored
+            if (more) {
+                open_tile(pos);
+                load_queries();
+                first_loads();
+            }
+            if (stores) {
+#pragma unroll
+                for (int mo = 0; mo < MO; ++mo)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mo * 32 + 8 * q4) = words[mo][q4];
+            }
+            if (stores)
+                wait_loads<4 * MO>();                            // for all but the stores
+            else
+                wait_loads<0>();
+            if (!more) return pos;
+        }
     }
 }
 
@@ -556,13 +715,13 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 // units cut by tile index modulo 2^xsplit_log2 - deal out evenly, an XCD keeps to its own, with a counter of its own.
 // Where all tiles are resident at once, two to a compute unit, the second ones come in ascending order, so that short ones share
 // with long ones.
-template <int D>
+template <int D, bool kStream>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(MfmaArgs a) {
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
     int pos = blockIdx.x;
     if (pos >= a.turn_at) pos = a.blocks - 8 - ((pos - a.turn_at) & ~7) + (pos & 7);
-    if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2>(a, pos, lds_raw);
-    if (pos < a.kinds[0].end) tiles_of_kind<D, 1>(a, pos, lds_raw);
+    if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2, false>(a, pos, lds_raw);
+    if (pos < a.kinds[0].end) tiles_of_kind<D, 1, kStream>(a, pos, lds_raw);
 }
 
 // Loads straight into LDS want aligned rows; a tensor that does not start on 16 bytes (a slice of a larger one) is laid out
@@ -688,9 +847,16 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     a.turn_at = D == 64 && a.blocks > cus && a.blocks <= slots && ordered ? cus : a.blocks;
     constexpr int lds = 4 * KB * 2 * D * 2 + 16;                 // split tiles take more
     static_assert(lds >= 6 * KB * D * 2 + 16 && lds >= 2 * 4 * (D / 64) * 16 * 64 * 4 + 2 * 4 * 64 * 2 * 4, "whole tiles, the merge");
-    static std::atomic<uint64_t> lds_set;                        // per instantiation, one bit per device
-    ensure_dynamic_lds((const void *)prefill_mfma_kernel<D>, lds, lds_set);
-    hipLaunchKernelGGL((prefill_mfma_kernel<D>), dim3(a.blocks < slots ? a.blocks : slots), dim3(512), lds, s, a);
+    // Tile after tile without a pause where that many follow each other, or long ones do (head_dim 128, 20 / 5 heads, pausing / not:
+    // 2 x 5003 tokens 263 / 250 us, 1 x 4096 100 / 98, 4 x 6000 638 / 626; 16 / 2 heads, 21 x 965 120 / 114; head_dim 64, 32 / 8 heads, 32 x 2048
+    // 650 / 632, 8 x 1500 116 / 110); for a second tile of few turns what is done beside two groups' turns in turn takes longer than
+    // a pause (20 / 5 heads of 128, 7 x 598 tokens 34 / 39, 4 x 512 23.8 / 25.0; 32 / 8 of 64, 6 x 1472 71 / 74, 8 x 400 22.9 / 24.0).
+    const int64_t whole_tiles = (int64_t)columns * a.kinds[0].tiles;
+    const bool stream = 2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB);
+    const auto kernel = stream ? prefill_mfma_kernel<D, true> : prefill_mfma_kernel<D, false>;
+    static std::atomic<uint64_t> lds_set[2];                     // per instantiation, one bit per device
+    ensure_dynamic_lds((const void *)kernel, lds, lds_set[stream]);
+    hipLaunchKernelGGL(kernel, dim3(a.blocks < slots ? a.blocks : slots), dim3(512), lds, s, a);
 }
 
 }  // namespace
