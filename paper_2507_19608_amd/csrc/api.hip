@@ -19,7 +19,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline size_t elt_size(int dtype) { return dtype == DA_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t khat, scan, scan_total, queue, copies, total;
+    size_t khat, scan, scan_total, queue, copies, counts, total;
 };
 
 // what prefill_mfma_supported reads, for a prefill of p's rows behind `cached` rows
@@ -68,6 +68,8 @@ WsLayout layout(const da_prefill_params *p) {
     static_assert(kPrefillQueueBytes + 64 * 4 <= 64 * 8 + kAlign && kPrefillQueueBytes % 16 == 0, "one row of head_dim 64 makes room for them");
     off += align_up(rows * p->head_dim * 8) + align_up(rows * sizeof(uint32_t));
     w.total = off;
+    w.counts = p->seq_len >= 64 ? off - align_up(units * (p->head_dim / 8) * sizeof(uint32_t)) : 0;   // (0: no room)
+    // (64 rows leave 256 bytes per unit and channel behind the copies, less the counters)
     return w;
 }
 
@@ -164,8 +166,11 @@ da_status delta_attn_delta_scan(const da_prefill_params *p, const void *K, uint3
     hipStream_t s = (hipStream_t)hip_stream;
     char *ws = (char *)workspace;
     (void)hipGetLastError();
-    launch_delta_scan(p->dtype, K, k_hat ? k_hat : ws + w.khat, mask_bits, ws + w.scan, nnz,
-                      p->batch * p->n_kv_heads, p->seq_len, p->head_dim, p->theta, s, nullptr, nullptr);
+    // (where one work group per unit does all of it, that is faster than one launch here and another to add up)
+    const int units = p->batch * p->n_kv_heads;
+    uint32_t *const counts = delta_scan_settles(p->dtype, units, p->seq_len, p->head_dim) ? (uint32_t *)(ws + w.scan) : nullptr;
+    launch_nnz_sum(launch_delta_scan(p->dtype, K, k_hat ? k_hat : ws + w.khat, mask_bits, ws + w.scan, counts, nnz, units, p->seq_len,
+                                     p->head_dim, p->theta, s, nullptr, nullptr), s);
     return launch_ok("delta_scan") ? DA_OK : DA_ERR_HIP;
 }
 
@@ -223,7 +228,8 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.n = p->seq_len;
     stage_begin(kStageScan, s);
     a.queue = p->head_dim >= 64 ? (uint32_t *)(ws + w.queue) : nullptr;      // (32: another kernel, and less room)
-    launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, nnz, units, p->seq_len, p->head_dim, p->theta, s, nullptr, a.queue);
+    a.sum = launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, w.counts ? (uint32_t *)(ws + w.counts) : nullptr, nnz, units,
+                              p->seq_len, p->head_dim, p->theta, s, nullptr, a.queue);
     stage_end(kStageScan, s);
     if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     a.q_off = 0;
@@ -354,13 +360,14 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     if (!kept) expand_cache_runs(cache, t0, ld, f->k, f->h, f->v, f->m, s);
     // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis)
     stage_begin(kStageScan, s);
-    launch_delta_scan(p->dtype, K, ws + w.hnew, mask_bits, ws + w.scan, nnz, units, m, d, p->theta, s,
-                      t0 > 0 ? cache->khat : nullptr, (uint32_t *)(ws + w.queue));
+    // (the scan's counts lie where decode steps leave their partial rows: d + 4 floats per query head at the least)
+    const NnzSum sum = launch_delta_scan(p->dtype, K, ws + w.hnew, mask_bits, ws + w.scan, (uint32_t *)cache->part, nnz, units, m, d,
+                                         p->theta, s, t0 > 0 ? cache->khat : nullptr, (uint32_t *)(ws + w.queue));
     stage_end(kStageScan, s);
     if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     // 3. the new rows join the plain arrays and the cache
     stage_begin(kStageCacheFill, s);
-    cache_fill_runs(cache, t0, nk, K, V, ws + w.hnew, mask_bits, nnz, f, s);
+    cache_fill_runs(cache, t0, nk, K, V, ws + w.hnew, mask_bits, nnz, f, sum, s);
     stage_end(kStageCacheFill, s);
     if (!launch_ok("cache_fill")) return DA_ERR_HIP;
     // 4. attention of the new rows over all nk keys

@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "../../include/delta_attn.h"
+#include "kernels.hpp"
 
 constexpr int kChunk = 64;   // rows per decode chunk; one reference-key checkpoint per chunk
 
@@ -92,7 +93,7 @@ void cache_fill_from_prefill(da_cache *c, const da_prefill_params *p, const void
 // appends rows t0 .. n_k - 1 (t0 = rows already held), given as arrays of these rows alone [units][n_k - t0][...]; with
 // `full` they also join its plain arrays, which hold the rows before t0 (needed where t0 > 0)
 void cache_fill_runs(da_cache *c, int t0, int n_k, const void *Knew, const void *Vnew, const void *Hnew, const uint32_t *Mnew,
-                     const uint64_t *nnz_new, const da_prefix *full, hipStream_t s);
+                     const uint64_t *nnz_new, const da_prefix *full, const NnzSum &sum, hipStream_t s);
 // writes the cached rows 0 .. t0 - 1 out as whole-sequence arrays with ld >= t0 rows of room per unit
 void expand_cache_runs(da_cache *c, int t0, int ld, void *Kfull, void *Hfull, void *Vfull, uint32_t *Mfull,
                        hipStream_t s);

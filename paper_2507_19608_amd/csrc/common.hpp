@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels.hpp"
+
 namespace da {
 
 typedef unsigned short bf16_t;   // raw bfloat16 bits
@@ -57,6 +59,19 @@ __device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t v, uint32_t *to
     }
     *total = __shfl(inc, 63);
     return inc - v;
+}
+
+// up to eight units' counts added up by a whole wave: `unit` is the one of a lane's eight lanes, or sum.units and more for none.  The first of the eight receives the
+// sum and has written it.
+__device__ __forceinline__ uint32_t add_up_nnz(const NnzSum &sum, int unit) {
+    const int lane = threadIdx.x & 7;
+    uint32_t v = 0;
+    if (unit < sum.units)
+        for (int k = lane; k < sum.groups; k += 8) v += sum.counts[(size_t)unit * sum.groups + k];
+#pragma unroll
+    for (int s = 4; s > 0; s >>= 1) v += __shfl_xor(v, s);
+    if (unit < sum.units && lane == 0) sum.nnz[unit] = v;
+    return v;
 }
 
 }  // namespace da

@@ -128,7 +128,7 @@ struct FullRows {
 template <int D>
 __global__ __launch_bounds__(256) void cache_fill_runs_kernel(const bf16_t *__restrict__ Knew, const bf16_t *__restrict__ Vnew,
                                                               const bf16_t *__restrict__ Hnew, const uint32_t *__restrict__ Mnew,
-                                                              const uint64_t *__restrict__ nnz_new, da_cache c, FullRows full,
+                                                              const uint64_t *__restrict__ nnz_new, NnzSum sum, da_cache c, FullRows full,
                                                               int t0, int n_k) {
     constexpr int WPR = D / 32, P = D / 8, kIn = kChunk * P / 256;
     __shared__ __attribute__((aligned(16))) bf16_t keys[kChunk * D];
@@ -181,7 +181,10 @@ __global__ __launch_bounds__(256) void cache_fill_runs_kernel(const bf16_t *__re
             }
         }
     }
-    if (tid == 0 && blockIdx.x == 0) c.nnz[unit] = (t0 == 0 ? 0ull : c.nnz[unit]) + nnz_new[unit];
+    if (blockIdx.x == 0 && wave == 3) {
+        const uint64_t fresh = sum.groups > 0 ? add_up_nnz(sum, lane < 8 ? unit : sum.units) : nnz_new[unit];
+        if (lane == 0) c.nnz[unit] = (t0 == 0 ? 0ull : c.nnz[unit]) + fresh;
+    }
     if (tid < D) {
         if (chunk > 0 && r0 >= t0 && rb - r0 < kChunk) ((bf16_t *)c.ck)[(size_t)unit * D + tid] = held_of(r0 - 1, tid);   // (the last chunk)
         if (rb == n_k) ((bf16_t *)c.khat)[(size_t)unit * D + tid] = held_of(n_k - 1, tid);
@@ -756,16 +759,16 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
 namespace da {
 
 void cache_fill_runs(da_cache *c, int t0, int n_k, const void *Knew, const void *Vnew, const void *Hnew, const uint32_t *Mnew,
-                     const uint64_t *nnz_new, const da_prefix *full, hipStream_t s) {
+                     const uint64_t *nnz_new, const da_prefix *full, const NnzSum &sum, hipStream_t s) {
     FullRows f = {};
     if (full) f = FullRows{(bf16_t *)full->k, (bf16_t *)full->v, (bf16_t *)full->h, full->m, c->max_seq};
     const dim3 grid((n_k + kChunk - 1) / kChunk - t0 / kChunk, c->B * c->Hkv);
     if (c->d == 64)
         hipLaunchKernelGGL(cache_fill_runs_kernel<64>, grid, dim3(256), 0, s, (const bf16_t *)Knew, (const bf16_t *)Vnew,
-                           (const bf16_t *)Hnew, Mnew, nnz_new, *c, f, t0, n_k);
+                           (const bf16_t *)Hnew, Mnew, nnz_new, sum, *c, f, t0, n_k);
     else
         hipLaunchKernelGGL(cache_fill_runs_kernel<128>, grid, dim3(256), 0, s, (const bf16_t *)Knew, (const bf16_t *)Vnew,
-                           (const bf16_t *)Hnew, Mnew, nnz_new, *c, f, t0, n_k);
+                           (const bf16_t *)Hnew, Mnew, nnz_new, sum, *c, f, t0, n_k);
 }
 
 void expand_cache_runs(da_cache *c, int t0, int ld, void *Kfull, void *Hfull, void *Vfull, uint32_t *Mfull,

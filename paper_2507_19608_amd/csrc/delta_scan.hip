@@ -106,6 +106,8 @@ int timing_collect(double *ms_per_stage, int *calls_per_stage) {
 // channel fires: from then on the held value is k(t) whatever it was before.  So time is cut into pieces that are walked in
 // parallel from a guessed incoming state, and pieces whose guess was wrong are walked again from the right one:
 //
+//   scan_whole_kernel     prompts of up to some thousand rows (whole_plan): one work group per unit and few channels, all rows in LDS,
+//       so that nothing is left for a second launch; the counts are added up by the launch that follows anyway.
 //   scan_segments_kernel  one work group per (unit, segment of S rows, group of channels); lane = channel, and the waves of
 //       64 channels cut the segment into runs of rows.  The segment's rows and up to `warm` rows before it are copied to LDS
 //       once (16-byte loads, every one in flight together: row by row from global memory the walk paid a memory round
@@ -389,6 +391,211 @@ __global__ __launch_bounds__(512) void scan_segments_kernel(ScanArgs<T> g) {
     }
 }
 
+// ---- One launch for a prompt of up to some thousand rows: a work group takes a few channels (DL = 8, 16 or 32) of every row of
+// a unit, so that all of a prompt's rows lie in one LDS and nothing has to be settled between work groups, and the channels of
+// one unit still spread over many compute units.  A thread walks one run of L rows in two neighbouring channels (two
+// chains: one alone leaves every other issue slot empty); runs start from the guess "held = the row before", and the ends
+// travel from run to run in rounds as above, but nothing is written in a round: a wrong run of L rows is walked again whole, and
+// one last walk puts the reference keys in the place of the keys.  The mask is what the reference keys say: an entry has fired
+// where a row differs from the one before (it fires only if |k - held| > theta >= 0, and then holds k).
+// A thread then has a row in registers: it goes out with its mask bits.  What bounds it: 50 clocks per row and two channels in the chain,
+// 48 rows of it and a run's own, the rest is latency; 8 x 1024 rows of 64: rows in LDS after 1.2 us, walked after 3.2, settled 3.5, replaced
+// 4.2, out 5.4.
+template <typename T>
+struct WholeArgs {
+    const T *__restrict__ K;
+    T *__restrict__ Khat;
+    uint32_t *__restrict__ mask_bits;
+    uint32_t *counts;                    // [units][groups of DL channels] fired entries
+    const T *init;
+    uint32_t *zeroed;                    // kPrefillQueueBytes, or NULL
+    int units, n, d, L, warm;            // L rows a run, a multiple of 8
+    uint32_t by_l_mul, by_l_shift;       // n / L
+    float theta;
+};
+
+template <typename T> struct TwoRaw;
+template <> struct TwoRaw<bf16_t> { using type = uint32_t; };
+template <> struct TwoRaw<float> { using type = uint2; };
+__device__ __forceinline__ float first_of(uint32_t v) { return __uint_as_float(v << 16); }
+__device__ __forceinline__ float second_of(uint32_t v) { return __uint_as_float(v & 0xffff0000u); }
+__device__ __forceinline__ float first_of(uint2 v) { return __uint_as_float(v.x); }
+__device__ __forceinline__ float second_of(uint2 v) { return __uint_as_float(v.y); }
+__device__ __forceinline__ void both(uint32_t &v, float a, float b) { v = (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u); }
+__device__ __forceinline__ void both(uint2 &v, float a, float b) { v = uint2{__float_as_uint(a), __float_as_uint(b)}; }
+
+// which of 16 (bf16) or 4 (fp32) channels differ between two rows' 16-byte pieces, one bit each
+template <typename T>
+__device__ __forceinline__ uint32_t piece_bits(uint4 x, uint4 y);
+typedef __attribute__((ext_vector_type(2))) unsigned short u16x2_t;
+template <>
+__device__ __forceinline__ uint32_t piece_bits<bf16_t>(uint4 x, uint4 y) {   // 8 channels: even ones in the low half's bits 0, 2, 4, 6
+    const uint32_t w[4] = {x.x ^ y.x, x.y ^ y.y, x.z ^ y.z, x.w ^ y.w};
+    uint32_t m = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const u16x2_t one = __builtin_elementwise_min(__builtin_bit_cast(u16x2_t, w[j]), u16x2_t{1, 1});
+        m |= __builtin_bit_cast(uint32_t, one) << (2 * j);
+    }
+    return (m & 0xffffu) | (m >> 15);                            // odd channels: from bit 16 + 2 j to bit 2 j + 1
+}
+template <>
+__device__ __forceinline__ uint32_t piece_bits<float>(uint4 x, uint4 y) {
+    return min(x.x ^ y.x, 1u) | min(x.y ^ y.y, 1u) << 1 | min(x.z ^ y.z, 1u) << 2 | min(x.w ^ y.w, 1u) << 3;
+}
+
+template <typename T, int DL>
+__global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g) {
+    using Raw = typename TwoRaw<T>::type;
+    constexpr int PR = DL / 2;                                   // threads of a run
+    constexpr int P = DL * (int)sizeof(T) / 16;                  // 16-byte pieces of a row
+    constexpr int kPer = 16 / (int)sizeof(T);                    // channels of a piece
+    extern __shared__ __attribute__((aligned(16))) char lds_w[];
+    // LDS: a row for what the first row continues from, then the runs of L rows with one to spare after each (so that the runs of a
+    // wave, read at the same step, lie in different banks), then the runs' ends
+    const int groups = g.d / DL, n = g.n, L = g.L;
+    const int unit = (int)(blockIdx.x & 7) + 8 * (int)(blockIdx.x / (8 * groups)), group = (int)(blockIdx.x >> 3) % groups;   // (a unit keeps to one XCD)
+    if (unit >= g.units) return;
+    const int tid = threadIdx.x, threads = blockDim.x, ch0 = group * DL;
+    const int runs = (n + L - 1) / L, run = tid / PR, p = tid % PR;
+    const bool works = run < runs;
+    auto run_of = [&](int t) { return (int)(__umulhi(2u * (uint32_t)t, g.by_l_mul) >> g.by_l_shift); };
+    uint4 *const rows = (uint4 *)lds_w + P;                      // piece q of row t: rows[(t + run_of(t)) * P + q]
+    float2 *const E = (float2 *)(rows + (size_t)runs * (L + 1) * P);   // [runs][PR]
+    uint32_t *const flags = (uint32_t *)(E + runs * PR);         // [2] some run was wrong in an even, odd round
+    uint32_t *const total = flags + 2;
+    const T *Kp = g.K + (size_t)unit * n * g.d + ch0;
+    const int gpr = g.d / kPer;                                  // pieces of a row in memory
+    const uint4 *const src = (const uint4 *)Kp;
+    {
+        const int pieces = n * P;
+        constexpr int kIn = 8;
+        for (int i0 = tid; i0 < pieces; i0 += kIn * threads) {
+            uint4 v[kIn];
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) {                      // (pieces past the end are the last one again)
+                const int i = min(i0 + k * threads, pieces - 1);
+                v[k] = src[(size_t)(i / P) * gpr + i % P];
+            }
+#pragma unroll
+            for (int k = 0; k < kIn; ++k) {
+                const int i = min(i0 + k * threads, pieces - 1), t = i / P;
+                rows[(t + run_of(t)) * P + i % P] = v[k];
+            }
+        }
+        // the last run is filled up with its last row again: walked once more it changes nothing
+        for (int i = pieces + tid; i < runs * L * P; i += threads) {
+            const int t = i / P;
+            rows[(t + runs - 1) * P + i % P] = src[(size_t)(n - 1) * gpr + i % P];
+        }
+        if (tid < P) rows[tid - P] = g.init ? ((const uint4 *)(g.init + (size_t)unit * g.d + ch0))[tid] : src[tid];
+        if (tid < 3) flags[tid] = 0;
+        if (g.zeroed && blockIdx.x == 0)
+            for (int i = tid; i < kPrefillQueueBytes / 4; i += threads) g.zeroed[i] = 0;
+    }
+    __syncthreads();
+    const float theta = g.theta;
+    const int a = run * L;
+    constexpr int N = 8;                                         // rows in a batch
+    auto fetch = [&](Raw (&k)[N], int t) {                       // rows t .. t + 7, of one run (t is a multiple of 8)
+        const Raw *r = (const Raw *)(rows + (t + run_of(t)) * P) + p;
+#pragma unroll
+        for (int u = 0; u < N; ++u) k[u] = r[u * PR];
+    };
+    auto step = [&](float2 &held, Raw k) {                       // Eq. 2 in binary32, Eq. 3
+        const float x = first_of(k), y = second_of(k);
+        held.x = fabsf(x - held.x) > theta ? x : held.x;
+        held.y = fabsf(y - held.y) > theta ? y : held.y;
+    };
+    // the rows t .. end - 1 in order from `held`, the next batch's reads issued before this one is worked on
+    auto walk_rows = [&](int t, int end, float2 held) __attribute__((always_inline)) {
+        Raw ka[N], kb[N];
+        if (t < end) fetch(ka, t);
+        for (; t < end; t += 2 * N) {
+            fetch(kb, min(t + N, end - N));
+#pragma unroll
+            for (int u = 0; u < N; ++u) step(held, ka[u]);
+            if (t + N >= end) break;
+            fetch(ka, min(t + 2 * N, end - N));
+#pragma unroll
+            for (int u = 0; u < N; ++u) step(held, kb[u]);
+        }
+        return held;
+    };
+    float2 start = {0.f, 0.f};
+    if (works) {
+        // the row before the first of the warm ones, or, exact, what the first row continues from (basis row or init)
+        const int w = max(a - g.warm, 0);
+        const Raw before = w == 0 ? ((Raw *)(rows - P))[p] : ((Raw *)(rows + (w - 1 + run_of(w - 1)) * P))[p];
+        start = walk_rows(w, a, float2{first_of(before), second_of(before)});
+        E[tid] = walk_rows(a, a + L, start);
+    }
+    __syncthreads();
+    for (int round = 0; round < runs; ++round) {
+        float2 from = start;
+        if (works && run > 0) from = E[tid - PR];
+        const bool wrong = __float_as_uint(from.x) != __float_as_uint(start.x) || __float_as_uint(from.y) != __float_as_uint(start.y);
+        if (__any(wrong) && (tid & 63) == 0) flags[round & 1] = 1;
+        __syncthreads();                                         // (also: every run has read the end of the one before)
+        if (!flags[round & 1]) break;
+        if (tid == 0) flags[(round + 1) & 1] = 0;
+        if (wrong) {
+            start = from;
+            E[tid] = walk_rows(a, a + L, start);
+        }
+        __syncthreads();
+    }
+    if (works) {
+        Raw *r = (Raw *)(rows + (size_t)run * (L + 1) * P) + p;
+        Raw k[N];
+        fetch(k, a);
+        for (int t = a; t < a + L; t += N, r += N * PR) {
+            Raw next[N];
+            fetch(next, min(t + N, a + L - N));
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                step(start, k[u]);
+                both(r[u * PR], start.x, start.y);
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) k[u] = next[u];
+        }
+    }
+    __syncthreads();
+    // a thread per row: reference keys and mask bits out
+    uint32_t fired = 0;
+    T *const Hp = g.Khat + (size_t)unit * n * g.d + ch0;
+    char *const Mp = (char *)g.mask_bits + (size_t)unit * n * (g.d / 8) + ch0 / 8;
+    for (int t = tid; t < n; t += threads) {
+        const int at = t + run_of(t), prev = t == 0 ? -1 : t - 1 + run_of(t - 1);
+        uint32_t bits = 0;
+#pragma unroll
+        for (int q = 0; q < P; ++q) {
+            const uint4 x = rows[at * P + q], y = rows[prev * P + q];
+            ((uint4 *)Hp)[(size_t)t * gpr + q] = x;
+            bits |= piece_bits<T>(x, y) << (kPer * q);
+        }
+        if (t == 0 && !g.init) bits = ~0u >> (32 - DL);          // the basis row is kept whole
+        fired += (uint32_t)__popc(bits);
+        char *const m = Mp + (size_t)t * (g.d / 8);
+        if constexpr (DL == 8)
+            *(uint8_t *)m = (uint8_t)bits;
+        else if constexpr (DL == 16)
+            *(uint16_t *)m = (uint16_t)bits;
+        else
+            *(uint32_t *)m = bits;
+    }
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) fired += __shfl_xor(fired, s);
+    if ((tid & 63) == 0) atomicAdd(total, fired);
+    __syncthreads();
+    if (tid == 0) g.counts[(size_t)unit * groups + group] = *total;
+}
+
+__global__ __launch_bounds__(256) void nnz_sum_kernel(NnzSum sum) {
+    add_up_nnz(sum, (int)(blockIdx.x * 32 + (threadIdx.x >> 3)));
+}
+
 constexpr int kSettleWaves = 16;
 
 // The value a segment's rows t0 .. t1 - 1 end on from `held`, without writing anything: once the chain meets the recorded one
@@ -588,14 +795,85 @@ static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *m
         hipLaunchKernelGGL(scan_settle_kernel<T>, dim3((d + 63) / 64, units), dim3(64 * kSettleWaves), 0, s, a);
 }
 
+// What a launch of scan_whole_kernel looks like; L == 0: the prompt is none for it.
+struct WholePlan {
+    int dl, threads, L, warm;
+    size_t lds;
+};
+// Few channels per work group where there are few units, more where the work groups outnumber the chip (every work group reads
+// whole cache lines); rows of at most 64 KB in LDS, so that two share a compute unit; runs of at most 32 rows up to 2048 rows.
+// The rows a run warms up on save rounds where the chip is idle and are only work where it is not.
+// One launch here / segments, and their settling where there are several, us, without the 1.5 us between these two (5 % jumps): 8 x 333 rows of 64 6.5 / 9.1,
+// 80 x 200 of 128 9.4 / 10.3, 8 x 1024 of 64 9.2 / 13 - 16, 8 x 2048 of 64 11.5 / 14 + 3.9, 10 x 1024 of 128 8.5 / 10 + 3.8, 5 x 4096 of 128
+// 15.7 / 12.5 + 4.8, 20 x 4096 24.5 / 22 + 4.9, 160 x 700 20.9 / 25.6 + 5.4, 256 x 2048 of 64 39.9 / 43.8 + 4.8; fp32, 1 x 256 rows of 64 5.0 / 7.5, 4 x
+// 1000 7.1 / 9.3 + 3.8, 16 x 2000 of 128 15.8 / 13.7 + 4.3.  Beyond, 10 x 5003 rows of 128 (80 KB a work group) 23.5 / 14.6 + 4.8.  With 1 % jumps, where
+// more guesses are wrong, 8 x 2048 of 64 12.7 / 16 + 4 to 19.
+// Where there are about as many units as compute units, and one's rows are 64 to 128 KB, a work group per unit reads whole rows and
+// needs no second wave of work groups: 256 x 700 rows of 64 18.7 here / 17.2 there, 256 x 400 of 128 19.9 / 17.2, 200 x 900 of 64 18.4 / 16.7, 256 x 1000 22.5 /
+// 23.4; but 256 x 400 of 64 13.3 / 19.0, 160 x 500 of 128 16.5 / 17.4.
+static WholePlan whole_plan(int dtype, int units, int n, int d) {
+    const int es = dtype == 0 ? 4 : 2;
+    WholePlan p = {8, 256, 0, 0, 0};
+    if (n < 64 || (int64_t)n * p.dl * es > 64 * 1024) return p;
+    if (units >= 192 && (int64_t)n * d * es > 64 * 1024 && (int64_t)n * d * es <= 128 * 1024) return p;
+    const auto groups = [&](int dl) { return (int64_t)units * (d / dl); };
+    if (groups(8) > 512) p.dl = 16;
+    if ((int64_t)n * p.dl * es > 64 * 1024) return p;            // (8 channels at a time read lines too often there: 88 x 2958 of 128 55 / 46)
+    if (p.dl == 16 && groups(16) > 512 && n <= 512) p.dl = 32;
+    p.threads = n > 32 * (256 / (p.dl / 2)) ? 512 : 256;
+    const int runs = p.threads / (p.dl / 2);
+    p.L = ((n + runs - 1) / runs + 7) / 8 * 8;
+    p.warm = groups(p.dl) <= 256 ? 48 : 32;
+    const int used = (n + p.L - 1) / p.L;
+    p.lds = (size_t)(used * (p.L + 1) + 1) * p.dl * es + (size_t)used * p.dl * 4 + 16;
+    return p;
+}
+
+template <typename T, int DL>
+static void whole_typed(const WholeArgs<T> &a, const WholePlan &p, hipStream_t s) {
+    static std::atomic<uint64_t> lds_set;                        // per instantiation, one bit per device
+    ensure_dynamic_lds((const void *)scan_whole_kernel<T, DL>, kScanLdsMax, lds_set);
+    const int64_t blocks = (int64_t)8 * (a.d / DL) * ((a.units + 7) / 8);
+    hipLaunchKernelGGL((scan_whole_kernel<T, DL>), dim3((unsigned)blocks), dim3(p.threads), p.lds, s, a);
+}
+template <typename T>
+static void whole_scan(const WholePlan &p, const void *K, void *Khat, uint32_t *mask_bits, uint32_t *counts, int units, int n, int d,
+                       float theta, const void *init, uint32_t *zeroed, hipStream_t s) {
+    uint32_t l = 0;
+    while ((1u << l) < (uint32_t)p.L) ++l;
+    const WholeArgs<T> a = {(const T *)K, (T *)Khat, mask_bits, counts, (const T *)init, zeroed, units, n, d, p.L, p.warm,
+                            (uint32_t)((((uint64_t)1 << (31 + l)) / (uint64_t)p.L) + 1u), l, theta};
+    if (p.dl == 8)
+        whole_typed<T, 8>(a, p, s);
+    else if (p.dl == 16)
+        whole_typed<T, 16>(a, p, s);
+    else
+        whole_typed<T, 32>(a, p, s);
+}
+
 // Khat [units][n][d] and scratch (delta_scan_scratch_bytes) are required scratch/outputs.
-void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz, int units,
-                       int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed) {
+NnzSum launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint32_t *counts, uint64_t *nnz,
+                         int units, int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed) {
+    const WholePlan w = whole_plan(dtype, units, n, d);
+    if (counts && w.L > 0) {
+        if (dtype == 0)
+            whole_scan<float>(w, K, Khat, mask_bits, counts, units, n, d, theta, init, zeroed, s);
+        else
+            whole_scan<bf16_t>(w, K, Khat, mask_bits, counts, units, n, d, theta, init, zeroed, s);
+        return NnzSum{counts, nnz, d / w.dl, units};
+    }
     const ScanPlan p = scan_plan(dtype, units, n, d);
     if (dtype == 0)
         scan_typed<float>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, zeroed, s);
     else
         scan_typed<bf16_t>(p, K, Khat, mask_bits, scratch, nnz, units, n, d, theta, init, zeroed, s);
+    return NnzSum{};
 }
+
+void launch_nnz_sum(const NnzSum &sum, hipStream_t s) {
+    if (sum.groups > 0) hipLaunchKernelGGL(nnz_sum_kernel, dim3((sum.units + 31) / 32), dim3(256), 0, s, sum);
+}
+
+bool delta_scan_settles(int dtype, int units, int n, int d) { return scan_plan(dtype, units, n, d).nseg > 1; }
 
 }  // namespace da

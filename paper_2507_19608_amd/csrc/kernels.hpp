@@ -27,6 +27,14 @@ void stage_end(int stage, hipStream_t s);
 void timing_enable(bool on);
 int timing_collect(double *ms_per_stage, int *calls_per_stage);
 
+// Fired entries that a scan has left per unit and group of channels, [units][groups] (at most 64 groups), for the launch that follows
+// it to add up into nnz [units].  groups == 0: nnz has been written.
+struct NnzSum {
+    const uint32_t *counts = nullptr;
+    uint64_t *nnz = nullptr;
+    int groups = 0, units = 0;
+};
+
 struct PrefillArgs {
     int dtype;            // 0 f32, 1 bf16
     int B, Hq, Hkv, d, n, W;   // n = number of key rows
@@ -37,16 +45,20 @@ struct PrefillArgs {
     const void *Q, *K, *V, *Khat;
     void *O;
     uint32_t *queue;      // (matrix-core path) kPrefillQueueBytes, zeroed
+    NnzSum sum;           // to be added up on the way
 };
 constexpr int kPrefillQueueBytes = 512;
 
 void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s);
 
-// scratch: delta_scan_scratch_bytes(); init: NULL (row 0 is the basis row), or [units][d], the reference key the rows
-// continue from; zeroed: NULL, or kPrefillQueueBytes to clear for the attention launch that follows
+// scratch: delta_scan_scratch_bytes(); counts: NULL, or room for units * d / 8 words, which may then be left for the caller to
+// add up (NnzSum; launch_nnz_sum, where no other launch takes it along); init: NULL (row 0 is the basis row), or [units][d], the
+// reference key the rows continue from; zeroed: NULL, or kPrefillQueueBytes to clear for the attention launch that follows
 size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d);
-void launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint64_t *nnz, int units,
-                       int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed);
+NnzSum launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint32_t *counts, uint64_t *nnz,
+                         int units, int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed);
+void launch_nnz_sum(const NnzSum &sum, hipStream_t s);
+bool delta_scan_settles(int dtype, int units, int n, int d);   // without `counts` a second launch follows
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
 // no instantiation.  q_off and ld are not for it.
 bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);

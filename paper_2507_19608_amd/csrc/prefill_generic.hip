@@ -41,6 +41,7 @@ struct KArgs {
     T *__restrict__ O;
     int Hq, Hkv, n, W, sliding;
     float scale_log2;
+    NnzSum sum;
 };
 
 __device__ __forceinline__ f32x4 load4(const float *p) { return *(const f32x4 *)p; }
@@ -71,6 +72,8 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
     const int i0 = tile * kRowsG, i_last = min(n - 1, i0 + kRowsG - 1);
     const int h = blockIdx.y, b = blockIdx.z;
     const int unit = b * a.Hkv + h / (a.Hq / a.Hkv);
+    if (wave == kWavesG - 1 && tile == 0 && h % (a.Hq / a.Hkv) == 0 && a.sum.groups > 0)      // (the shortest rows)
+        add_up_nnz(a.sum, lane < 8 ? unit : a.sum.units);
     const T *Qp = a.Q + (size_t)(b * a.Hq + h) * n * D;
     const T *Kp = a.K + (size_t)unit * n * D;
     const T *Vp = a.V + (size_t)unit * n * D;
@@ -217,6 +220,7 @@ void launch_one(const PrefillArgs &p, hipStream_t s) {
     a.W = p.W;
     a.sliding = p.sliding;
     a.scale_log2 = p.scale_log2;
+    a.sum = p.sum;
     // (32 rows per work group, which halve the reads of K and V per row, took longer: fp32, 8 heads of 64, 2048 tokens 97.6 us
     // against 85.3, 8 heads of 128 182 against 152; bf16, 4 x 1000 tokens, 20 / 5 heads of 96 344 against 226.)
     constexpr size_t lds = (size_t)kWavesG * 16 * (D + 6) * sizeof(float);

@@ -113,6 +113,7 @@ struct MfmaArgs {
     int blocks, turn_at;                // tiles of the launch; where their order turns (see prefill_mfma_kernel)
     uint32_t *queue;                    // [8] counters, kQueueStride apart, zero at the start: tiles handed out beyond the first of each work group
     float scale_log2;
+    NnzSum sum;
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -476,6 +477,16 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     const int queues = a.xsplit_log2 >= 0 ? 8 : 1, blocks = a.blocks, end = a.kinds[kSplit - 1].end;
     uint32_t *const queue = a.queue + (pos & (queues - 1)) * kQueueStride;
     const int handed_out = (int)gridDim.x + (pos & (queues - 1));
+    // the counts that the scan has left, by a wave that waits for its first loads meanwhile (positions from the queue are larger), and
+    // first by the last work groups, which have the least to do where all of them are there at once
+    auto add_up = [&]() __attribute__((always_inline)) {
+        if (wave != 7 || pos >= (int)gridDim.x) return;
+        const auto &a = *arguments();
+        const NnzSum sum = {a.sum.counts, a.sum.nnz, a.sum.groups, a.sum.units};
+        if (sum.groups == 0) return;
+        for (int u = (int)(gridDim.x - 1 - blockIdx.x); u < sum.units; u += 8 * (int)gridDim.x)
+            add_up_nnz(sum, u + (lane >> 3) * (int)gridDim.x);
+    };
     const bool asks = blocks > (int)gridDim.x;
     uint32_t ticket = 0;
     // Wave 0 asks for the next tile; in asm, so that nobody waits for the answer (2 us) before it is needed.
@@ -500,6 +511,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         first_loads();
         bool early = turns < 4;                                  // (too short to ask on the way)
         if (early) ask();
+        add_up();
         take_tile();
         clear();
         int turn = 0, opened = 2;                                // of the tile that is worked on; requested turns of the opened one
@@ -623,6 +635,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         open_tile(pos);
         load_queries();
         first_loads();
+        add_up();
         wait_loads<0>();
         while (true) {
             clear();
@@ -762,6 +775,7 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     a.nq = p.nq;
     a.scale_log2 = p.scale_log2;
     a.queue = p.queue;
+    a.sum = p.sum;
     const int units = p.B * p.Hkv, g = p.Hq / p.Hkv;
     a.GH = (g % 4 == 0) ? 4 : (g % 2 == 0) ? 2 : 1;
     const int rt = 256 / a.GH, hgroups = g / a.GH;               // rows of a whole tile
