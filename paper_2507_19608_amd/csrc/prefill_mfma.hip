@@ -130,8 +130,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 template <int At>
 __device__ __forceinline__ void load_to_lds(const char *base, uint32_t off, uint32_t lds) {
     static_assert(At >= 0 && At < 4096, "13 bits, signed");
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(off), "s"(base),
-                 "s"(__builtin_amdgcn_readfirstlane(lds)), "n"(At)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)), "n"(At)
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
