@@ -74,7 +74,7 @@ __host__ __device__ inline size_t run_room_stride(int d) { return (size_t)(d / 6
 // work groups that share a unit in a decode step, at most: what the last of them can merge in a few round trips
 constexpr int kMaxParts = 32;
 // ... and the walkers of each, at least
-inline int run_walkers(int d) { return d == 64 ? 8 : 1; }
+inline int run_walkers(int d) { return d == 64 ? 4 : 1; }
 
 // floats per partial row: o[d], running maximum, running sum, padded to a 16-byte multiple
 __host__ __device__ inline int part_stride(int d) { return d + 4; }

@@ -293,35 +293,45 @@ __global__ __launch_bounds__(64) void expand_cache_kernel(da_cache c, int t0, in
     }
 }
 
-// D1: delta of the new key against the carried reference key (Eq. 2-3).  One wave per unit.  The
+// D1: delta of the new key against the carried reference key (Eq. 2-3), by one wave per unit.  The
 // surviving values themselves are already in the raw-key ring; the run is built when the chunk is sealed.
-__device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf16_t *__restrict__ k_new,
-                                const bf16_t *__restrict__ v_new, uint32_t *__restrict__ mask_row, int t) {
-    const int d = c.d, wpr = d >> 5;
-    uint32_t fired = 0;
-    for (int c0 = 0; c0 < d; c0 += kWave) {
-        const int ch = c0 + lane;
-        const bf16_t kraw = k_new[(size_t)unit * d + ch];
-        bf16_t *hp = (bf16_t *)c.khat + (size_t)unit * d + ch;
-        bool fire = true;   // basis row
-        if (t > 0) {
-            const bf16_t hraw = *hp;
-            fire = fabsf(bf16_to_f32(kraw) - bf16_to_f32(hraw)) > c.theta;
-            if (t % kChunk == 0) ((bf16_t *)c.ck)[(size_t)unit * d + ch] = hraw;
+// What it reads is asked for when the step begins and stored from at its end: nothing of the step waits for it.
+template <int D>
+struct NewRow {
+    bf16_t k[D / kWave], h[D / kWave], v[D / kWave];
+    uint64_t nnz;
+    __device__ __forceinline__ void load(const da_cache &c, int unit, int lane, const bf16_t *__restrict__ k_new,
+                                         const bf16_t *__restrict__ v_new) {
+#pragma unroll
+        for (int i = 0; i < D / kWave; ++i) {
+            const size_t at = (size_t)unit * D + kWave * i + lane;
+            k[i] = k_new[at];
+            h[i] = ((const bf16_t *)c.khat)[at];
+            v[i] = v_new[at];
         }
-        if (fire) *hp = kraw;
-        ((bf16_t *)c.ring)[((size_t)unit * c.Wd + t % c.Wd) * d + ch] = kraw;
-        ((bf16_t *)c.V)[v16_index(unit, c.vrows, d, t, ch)] = v_new[(size_t)unit * d + ch];
-        const uint64_t b = __ballot(fire);
-        if ((lane & 31) == 0) {
-            const uint32_t w = (uint32_t)(b >> (lane & 32));
-            c.mask[((size_t)unit * c.max_seq + t) * wpr + (ch >> 5)] = w;
-            if (mask_row) mask_row[(size_t)unit * wpr + (ch >> 5)] = w;
-        }
-        fired += __popcll(b);
+        nnz = c.nnz[unit];
     }
-    if (lane == 0) c.nnz[unit] = (t == 0 ? 0ull : c.nnz[unit]) + fired;
-}
+    __device__ __forceinline__ void append(const da_cache &c, int unit, int lane, uint32_t *__restrict__ mask_row, int t) const {
+        uint32_t fired = 0;
+#pragma unroll
+        for (int i = 0; i < D / kWave; ++i) {
+            const int ch = kWave * i + lane;
+            const bool fire = t == 0 || fabsf(bf16_to_f32(k[i]) - bf16_to_f32(h[i])) > c.theta;   // (t == 0: basis row)
+            if (t > 0 && t % kChunk == 0) ((bf16_t *)c.ck)[(size_t)unit * D + ch] = h[i];
+            if (fire) ((bf16_t *)c.khat)[(size_t)unit * D + ch] = k[i];
+            ((bf16_t *)c.ring)[((size_t)unit * c.Wd + t % c.Wd) * D + ch] = k[i];
+            ((bf16_t *)c.V)[v16_index(unit, c.vrows, D, t, ch)] = v[i];
+            const uint64_t b = __ballot(fire);
+            if ((lane & 31) == 0) {
+                const uint32_t w = (uint32_t)(b >> (lane & 32));
+                c.mask[((size_t)unit * c.max_seq + t) * (D / 32) + (ch >> 5)] = w;
+                if (mask_row) mask_row[(size_t)unit * (D / 32) + (ch >> 5)] = w;
+            }
+            fired += __popcll(b);
+        }
+        if (lane == 0) c.nnz[unit] = (t == 0 ? 0ull : nnz) + fired;
+    }
+};
 
 // One decode step, one launch: gridDim.x work groups per unit of NW walkers each; a walker is one wave at head_dim 64, two
 // waves at head_dim 128 that each take 64 of the channels (all query heads of the unit's group either way).  Walker w of all
@@ -329,17 +339,19 @@ __device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf1
 // the next chunk's mask rows and runs while it works on the current one; a launch is sized so that all of its waves are
 // resident at once.
 // Per chunk:
-//   0. the wave that owns the newest row appends it (D1);
 //   1. history chunks (rows left of the decode window): head and runs of the wave's 64 channels are copied to LDS; the
 //      reference value k_hat(j)[c] (Eq. 3) is element {start of c's run} + #{marked rows <= j of channel c} - by telescoping
 //      Eq. 4 the history score of row j is q . k_hat(j).  The counts come from the matrix cores: column masks as bytes
 //      (64 channels x 64 rows) times a triangle of twos, plus the starts, is the table of byte addresses, exact in int32,
 //      and comes out in the layout that the next product takes its keys in: lane l holds row l % 32 of a half chunk,
 //      channels 8 q + 4 (l / 32)..+3.  That leaves one LDS read per element.  (Counting on the vector ALU - ballot, two
-//      mbcnt, two adds per channel of 64 rows - made 702 vector instructions a chunk of the 384 that it takes now.)  Window rows are 64-bit loads from the raw-key ring, the newest from k_new;
+//      mbcnt, two adds per channel of 64 rows - made 702 vector instructions a chunk of the 384 that it takes now.)
+//      Window rows are 64-bit loads from the raw-key ring, the newest from k_new, asked for before the history rows of a chunk
+//      that has both are worked on;
 //   2. two neighbouring channels to a register: the 32x32x16 operand, with the queries fetched in the same channel order;
 //   3. scores S[row][head] on the matrix cores (heads padded to 32 columns); at head_dim 128 the two waves
-//      exchange their halves of the contraction through LDS and both hold the full scores; softmax update in
+//      exchange their halves of the contraction through LDS and both hold the full scores (they wait for each other alone, by a
+//      word of LDS each: barriers made all walkers of a work group wait for the slowest copy in every turn); softmax update in
 //      the accumulator registers (lane = head, 32 rows per lane, the other 32 in lane + 32);
 //   4. the accumulator registers, rounded to bf16, are the B operand of O^T += V^T P^T as they stand, because
 //      the V cache stores each group of 16 rows in exactly that order; O^T (the wave's 64 channels) keeps
@@ -350,6 +362,10 @@ __device__ void append_row_runs(const da_cache &c, int unit, int lane, const bf1
 // XCD has its own L2, and fences that write it back or drop it cost more than the second launch did; so the partial rows,
 // and nothing else, are stored past it (relaxed device-scope stores), waited for, counted with a device-scope add, and read
 // past it.
+// What bounds a step of few chunks is the chain launch - counts and runs - keys - scores - merge - meeting, 8 units of 512 rows of 64: 1.2
+// us until all is asked for, 0.7 until it is there, 0.9 keys, 0.5 softmax, 0.4 P V, 1.2 merge, 2.2 meeting, before the order of the
+// requests, the append at the end and work groups of 4 walkers: 7.95 -> 7.1 us a step together; 8 units of 200 rows 6.5 -> 5.8; 20 of 6000 rows of
+// 128 17.1 -> 16.4; 256 of 2048 rows of 64, which the memory bounds, 21.6 -> 19.9.  (V a chunk ahead took longer in every one of them.)
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel(da_cache c, const bf16_t *__restrict__ q_new,
                                                                               const bf16_t *__restrict__ k_new,
@@ -365,6 +381,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     __shared__ __attribute__((aligned(16))) bf16_t stage_a_all[NW * H][kPieces * 512];
     __shared__ __attribute__((aligned(16))) bf16_t stage_b_all[NW * H][kPieces * 512];
     __shared__ float ml_all[NW][32][2];                      // [walker][head] maximum, sum
+    __shared__ int done_by[NW * H];
     __shared__ uint32_t before;                              // work groups of the unit that were done before this one
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave = wv / H, half = wv % H, coff = 64 * half;   // part inside the work group; channel half
@@ -380,26 +397,6 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     // rows of chunk ch left of the decode window (> 0 only for sealed chunks, because Wd >= kChunk)
     auto hist_of = [&](int ch) { return min(max(win_begin - ch * kChunk, 0), min(kChunk, t + 1 - ch * kChunk)); };
 
-    // q operands (B operand of the score contraction): lane l = head l % 32, channels coff + 16 s + 4 (l / 32)..+3 and 8 more
-    u32x4 qop[KS];
-    {
-        const bf16_t *qrow = q_new + ((size_t)b * c.Hq + hk * g + min(n32, g - 1)) * D + coff + 4 * kap;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            const u32x2 q0 = *(const u32x2 *)(qrow + 16 * s), q1 = *(const u32x2 *)(qrow + 16 * s + 8);
-            qop[s] = u32x4{q0[0], q0[1], q1[0], q1[1]};
-            if (n32 >= g) qop[s] = u32x4{0u, 0u, 0u, 0u};
-        }
-    }
-    // the triangle of twos (B operand, int8): lane l = row l % 32 of a half chunk, byte i of register k = row 16 (l / 32) + 4 k + i
-    i32x4 tri;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        uint32_t w = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w |= (16 * kap + 4 * k + i <= n32 ? 2u : 0u) << (8 * i);
-        tri[k] = (int)w;
-    }
     // History chunk ch: the runs of this wave's channels go straight from global memory to the LDS staging area
     // (128-bit LDS-direct loads: lane i of a copy lands at base + 16 i); its mask rows, lane = row.
     // cnt: the chunk's element counts (channels 0..63, channels 64.. << 16); pieces `from` .. of the copy.
@@ -412,17 +409,43 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(runs + p * 512 + lane * 8),
                                                  (__attribute__((address_space(3))) void *)(sv + p * 512), 16, 0, 0);
     };
-    if (c_begin < c_end && hist_of(c_begin) > 0) {
-        // the first chunk's copy does not wait for its element counts: the pieces that a chunk with two fifths of its entries
-        // fills are copied anyway, the rest when the counts are there
-        constexpr int kSure = 4;
-        const uint32_t cnt = c.ccnt[(size_t)unit * c.max_chunks + c_begin];
+    // Everything a walker begins with is asked for before anything is waited for.  The first chunk's copy does not wait for its element
+    // counts: the pieces that a chunk with two fifths of its entries fills are copied anyway, the rest when the counts are there.
+    constexpr int kSure = 4;
+    const bool begins_with_runs = c_begin < c_end && hist_of(c_begin) > 0;
+    uint32_t first_count = 0, tot_v = 0;                     // tot_v: element counts of the chunk after the next one's copy
+    if (begins_with_runs) {
+        int none = 0;                                        // (as a vector load: a scalar one would be waited for with the next arguments)
+        asm("" : "+v"(none));
+        first_count = c.ccnt[(size_t)unit * c.max_chunks + c_begin + none];
         copy_runs(c_begin, kSure * 512u | (kSure * 512u << 16), stage_a, 0);
-        copy_runs(c_begin, __builtin_amdgcn_readfirstlane(cnt), stage_a, kSure);
     }
-    uint32_t tot_v = 0;                                      // element counts of the chunk after the next one's copy
     if (c_begin + c_step < c_end && hist_of(c_begin + c_step) > 0)
         tot_v = c.ccnt[(size_t)unit * c.max_chunks + c_begin + c_step];
+    const bool appends = half == 0 && (nchunks - 1) % c_step == c_begin;   // this wave owns row t
+    NewRow<D> row_t;
+    if (appends) row_t.load(c, unit, lane, k_new, v_new);
+    // q operands (B operand of the score contraction): lane l = head l % 32, channels coff + 16 s + 4 (l / 32)..+3 and 8 more
+    // (columns past the last head repeat it: their results go nowhere)
+    u32x4 qop[KS];
+    {
+        const bf16_t *qrow = q_new + ((size_t)b * c.Hq + hk * g + min(n32, g - 1)) * D + coff + 4 * kap;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const u32x2 q0 = *(const u32x2 *)(qrow + 16 * s), q1 = *(const u32x2 *)(qrow + 16 * s + 8);
+            qop[s] = u32x4{q0[0], q0[1], q1[0], q1[1]};
+        }
+    }
+    // the triangle of twos (B operand, int8): lane l = row l % 32 of a half chunk, byte i of register k = row 16 (l / 32) + 4 k + i
+    i32x4 tri;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        uint32_t w = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w |= (16 * kap + 4 * k + i <= n32 ? 2u : 0u) << (8 * i);
+        tri[k] = (int)w;
+    }
+    if (begins_with_runs) copy_runs(c_begin, __builtin_amdgcn_readfirstlane(first_count), stage_a, kSure);
 
     f32x16 o[CT];                                            // O^T: lane = head, register r of tile ct =
 #pragma unroll                                               // channel coff + 32 ct + 8 (r / 4) + 4 (l / 32) + r % 4
@@ -430,6 +453,23 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[ct][r] = 0.f;
     float m_run = -INFINITY, l_run = 0.f;                    // l_run: this lane half's share of the sum
+
+    // The two waves of a walker at head_dim 128 wait for each other, and for nobody else: what each has done, in steps of two a turn.
+    // (They are of one work group, so both are there, and take the same chunks; LDS accesses of a wave are carried out in order.)
+    int turn = 0;
+    auto tell = [&](int done) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (lane == 0) __hip_atomic_store(&done_by[wv], done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto await = [&](int done) __attribute__((always_inline)) {
+        while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&done_by[wv ^ (H - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < done)
+            __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+    };
+    if (H == 2) {
+        if (lane == 0) done_by[wv] = 0;
+        lds_barrier();
+    }
 
     auto do_chunk = [&](int chunk, bf16_t *sv, bf16_t *sv_next, const bf16_t *sv_partner) __attribute__((always_inline)) {
         const bool newest = chunk == nchunks - 1;            // this wave owns row t
@@ -439,6 +479,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
         __builtin_amdgcn_s_waitcnt(0x0F70);                  // vmcnt(0): this chunk's runs have landed in LDS
         // the next chunk's runs, and the element count of the one after it, fly in meanwhile
         if (chunk + c_step < c_end) {
+            if (H == 2) await(2 * turn);                     // (the partner is done with the scores that lie where they go)
             copy_runs(chunk + c_step, __builtin_amdgcn_readfirstlane(tot_v), sv_next, 0);
             tot_v = 0;
             if (chunk + 2 * c_step < c_end && hist_of(chunk + 2 * c_step) > 0)
@@ -457,36 +498,29 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
                     vop[ct][T][s2] = *(const u32x4 *)((const bf16_t *)c.V +
                                                       (((size_t)unit * (c.vrows >> 4) + (row16 >> 4)) * D + ch) * 16 + 8 * kap);
                 }
-        if (newest) {
-            // position, unit and lane are made opaque here so that the select conditions and the addresses of the
-            // append are worked out inside this branch, once per step, instead of being kept in registers across
-            // the whole chunk loop
-            int tt = t, uo = unit, ln = lane;
-            asm volatile("" : "+s"(tt), "+s"(uo), "+v"(ln));
-            const int pt = tt & 15;
-            const int kap_t = (pt >> 2) & 1, i_t = 4 * (pt >> 3) + (pt & 3);
-            const int Tn = (tt >> 5) & 1, sn = (tt >> 4) & 1;
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                const uint32_t vn = v_new[(size_t)uo * D + coff + 32 * ct + (ln & 31)];
-#pragma unroll
-                for (int TT = 0; TT < 2; ++TT)
-#pragma unroll
-                    for (int ss = 0; ss < 2; ++ss)
-#pragma unroll
-                        for (int w = 0; w < 4; ++w) {
-                            const bool hit = TT == Tn && ss == sn && w == (i_t >> 1) && kap == kap_t;
-                            const uint32_t old = vop[ct][TT][ss][w];
-                            const uint32_t pat = (i_t & 1) ? ((old & 0xffffu) | (vn << 16)) : ((old & 0xffff0000u) | vn);
-                            vop[ct][TT][ss][w] = hit ? pat : old;
-                        }
-            }
-            // 0. the new row goes into the cache (other waves of this launch never read what is written here)
-            if (half == 0) append_row_runs(c, uo, ln, k_new, v_new, mask_row, tt);
-        }
-
         // 1., 2. the keys as operands: kop[T][s] = row 32 T + l % 32, channels coff + 16 s + 4 (l / 32)..+3 and 8 more
-        u32x4 kop[2][KS];
+        u32x4 kop[2][KS], raw[2][KS];
+        uint32_t v_last[CT];
+        if (hist_rows < kChunk) {                            // window rows, asked for before the history rows are worked on
+#pragma unroll
+            for (int T = 0; T < 2; ++T) {
+                const int row = r0 + 32 * T + n32;
+#pragma unroll
+                for (int s = 0; s < KS; ++s) raw[T][s] = u32x4{0u, 0u, 0u, 0u};
+                if (32 * T + n32 >= hist_rows && row <= t) {
+                    const bf16_t *src = (row == t ? k_new + (size_t)unit * D
+                                                  : (const bf16_t *)c.ring + ((size_t)unit * c.Wd + row % c.Wd) * D) + coff + 4 * kap;
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) {
+                        const u32x2 x0 = *(const u32x2 *)(src + 16 * s), x1 = *(const u32x2 *)(src + 16 * s + 8);
+                        raw[T][s] = u32x4{x0[0], x0[1], x1[0], x1[1]};
+                    }
+                }
+            }
+            if (newest)
+#pragma unroll
+                for (int ct = 0; ct < CT; ++ct) v_last[ct] = v_new[(size_t)unit * D + coff + 32 * ct + n32];
+        }
         if (hist_rows > 0) {
             const __attribute__((address_space(3))) char *room = (const __attribute__((address_space(3))) char *)sv;
             const int lds_base = (int)(uintptr_t)room;
@@ -550,21 +584,10 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
         if (hist_rows < kChunk) {
 #pragma unroll
             for (int T = 0; T < 2; ++T)
-                if (32 * T + n32 >= hist_rows) {
-                    const int row = r0 + 32 * T + n32;
-                    if (row <= t) {
-                        const bf16_t *src = (row == t ? k_new + (size_t)unit * D
-                                                      : (const bf16_t *)c.ring + ((size_t)unit * c.Wd + row % c.Wd) * D) + coff + 4 * kap;
 #pragma unroll
-                        for (int s = 0; s < KS; ++s) {
-                            const u32x2 x0 = *(const u32x2 *)(src + 16 * s), x1 = *(const u32x2 *)(src + 16 * s + 8);
-                            kop[T][s] = u32x4{x0[0], x0[1], x1[0], x1[1]};
-                        }
-                    } else {
+                for (int s = 0; s < KS; ++s)
 #pragma unroll
-                        for (int s = 0; s < KS; ++s) kop[T][s] = u32x4{0u, 0u, 0u, 0u};
-                    }
-                }
+                    for (int k = 0; k < 4; ++k) kop[T][s][k] = 32 * T + n32 >= hist_rows ? raw[T][s][k] : kop[T][s][k];
             // the raw rows are awaited here, inside the branch only window chunks take: left to the compiler the
             // wait lands after the join and history chunks would drain their in-flight V and run copies there
             __builtin_amdgcn_s_waitcnt(0x0F70);              // vmcnt(0)
@@ -582,23 +605,27 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
         }
         if (H == 2) {
             // the other wave contracted the other 64 channels: the halves meet in the staging areas each wave has
-            // just finished reading its own of (register r of lane l at float 64 r + l: conflict free), and are added in
+            // just finished reading its own of (registers 4 q .. 4 q + 3 of lane l at four floats 64 q + l: conflict free), and are added in
             // the same order by both, so both hold the same scores
-            float *mine = (float *)sv;
-            const float *theirs = (const float *)sv_partner;
+            f32x4 *mine = (f32x4 *)sv;
+            const f32x4 *theirs = (const f32x4 *)sv_partner;
 #pragma unroll
             for (int T = 0; T < 2; ++T)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) mine[(16 * T + r) * 64 + lane] = acc[T][r];
-            lds_barrier();
+                for (int q = 0; q < 4; ++q)
+                    mine[(4 * T + q) * 64 + lane] = f32x4{acc[T][4 * q], acc[T][4 * q + 1], acc[T][4 * q + 2], acc[T][4 * q + 3]};
+            tell(2 * turn + 1);
+            await(2 * turn + 1);
 #pragma unroll
             for (int T = 0; T < 2; ++T)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float x = theirs[(16 * T + r) * 64 + lane];
-                    acc[T][r] = half ? x + acc[T][r] : acc[T][r] + x;
+                for (int q = 0; q < 4; ++q) {
+                    const f32x4 x = theirs[(4 * T + q) * 64 + lane];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[T][4 * q + e] = half ? x[e] + acc[T][4 * q + e] : acc[T][4 * q + e] + x[e];
                 }
-            lds_barrier();                                   // the areas may be copied into again
+            tell(2 * turn + 2);                              // (what was read of the partner's area has arrived)
+            ++turn;
         }
         if (nrows < kChunk) {                                // only the newest chunk has rows that do not exist yet
             const int lim = nrows - 4 * kap;                     // compared with constants: nothing to keep in registers
@@ -635,6 +662,30 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
                 l_run = __builtin_amdgcn_fdot2_f32_bf16(pk, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run, false);
                 pa[T][r >> 3][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
             }
+        if (newest) {
+            // the position is made opaque here so that the select conditions are worked out inside this branch, once per step,
+            // instead of being kept in registers across the whole chunk loop
+            int tt = t;
+            asm volatile("" : "+s"(tt));
+            const int pt = tt & 15;
+            const int kap_t = (pt >> 2) & 1, i_t = 4 * (pt >> 3) + (pt & 3);
+            const int Tn = (tt >> 5) & 1, sn = (tt >> 4) & 1;
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) {
+                const uint32_t vn = v_last[ct];
+#pragma unroll
+                for (int TT = 0; TT < 2; ++TT)
+#pragma unroll
+                    for (int ss = 0; ss < 2; ++ss)
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) {
+                            const bool hit = TT == Tn && ss == sn && w == (i_t >> 1) && kap == kap_t;
+                            const uint32_t old = vop[ct][TT][ss][w];
+                            const uint32_t pat = (i_t & 1) ? ((old & 0xffffu) | (vn << 16)) : ((old & 0xffff0000u) | vn);
+                            vop[ct][TT][ss][w] = hit ? pat : old;
+                        }
+            }
+        }
         // 4. O^T += V^T P^T: channels x heads, contraction over the chunk's 64 rows in accumulator order
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct)
@@ -646,23 +697,18 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
                                                                     __builtin_bit_cast(bf16x8, pa[T][s2]), o[ct], 0, 0, 0);
     };
     const bf16_t *partner_a = stage_a_all[wv ^ (H - 1)], *partner_b = stage_b_all[wv ^ (H - 1)];
-    // Every walker of the work group takes the same number of turns: at head_dim 128 a turn holds two barriers, which a walker
-    // that has run out of chunks passes all the same.
     auto take = [&](int chunk, bf16_t *sv, bf16_t *sv_next, const bf16_t *sv_partner) __attribute__((always_inline)) {
-        if (chunk < c_end) {
-            do_chunk(chunk, sv, sv_next, sv_partner);
-        } else if (H == 2) {
-            lds_barrier();
-            lds_barrier();
-        }
+        if (chunk < c_end) do_chunk(chunk, sv, sv_next, sv_partner);
     };
     for (int first = (int)blockIdx.x * NW; first < c_end; first += 2 * c_step) {     // (walker 0's chunk of the turn)
         take(first + wave, stage_a, stage_b, partner_a);
         if (first + c_step < c_end) take(first + c_step + wave, stage_b, stage_a, partner_b);
     }
+    // the new row goes into the cache (other waves of this launch never read what is written here)
+    if (appends) row_t.append(c, unit, lane, mask_row, t);
     const float l_all = l_run + __shfl_xor(l_run, 32);
     // the walkers' (o, m, l) meet in LDS (a walker without chunks contributes m = -inf, l = 0)
-    if (NW * H > 1) __syncthreads();                         // (the partner may still read this wave's staging area)
+    if (H > 1) __syncthreads();                              // (the partner may still read this wave's staging area)
     float *obuf = (float *)stage_a;                          // [g][64] of this wave; its staging areas are idle now
     if (n32 < g) {
 #pragma unroll
@@ -786,15 +832,23 @@ void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, 
         c->cus = 256;
     // Work groups of 8 waves - 8 walkers at head_dim 64, 4 at head_dim 128 -, one per compute unit by LDS and registers: as many
     // per unit as keep the whole launch resident, no more than the last one can merge in a few round trips, or just one where
-    // that has as few turns (a turn saved is worth the meeting: 20 .. 128 units of 300 rows, head_dim 128, 12.0 .. 14.6 us in two
-    // turns of one work group, 10.0 .. 12.8 in one of two; 8 units of 560 rows, head_dim 64, 10.8 and 10.5).
-    // The walkers of a work group meet at barriers at head_dim 128, and whole work groups of 4 deal out badly to a number of
-    // units that does not divide the compute units: there 2 or 1 are taken where the launch then has fewer turns, and 2 also
-    // where it has as many, but four or more.  2048 rows, us a step with 4 / 2 / 1 walkers: 20 units 12.3 / 13.9 / 18.4 (1 turn), 40
-    // units 15.9 / 17.1 / 20.3 (2), 96 units 27.5 / 24.5 / 25.6 (5 / 4 / 4), 128 units 30.3 / 28.1 / 28.4 (5), 160 units 39.8 /
-    // 32.7 / 32.7 (9 / 6 / 6), 192 units 41.9 / 39.9 / 37.0 (9 / 9 / 7), 512 units, half of whose work groups of 4 are resident at
-    // a time, 89.5 / 77.2 / 79.2 (18 / 17 / 17); 600 rows: 192 units 19.8 / 22.2 / 19.7 (3 / 3 / 2), 256 units 21.9 / 24.0 / 25.1 (3).
-    const int H = c->d / 64, slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8;
+    // that has as few turns (a turn saved is worth the meeting: 20 .. 80 units of 300 rows, head_dim 128, 9.9 .. 10.1 us in two
+    // turns of one work group, 9.5 .. 9.9 in one of two; 16 units of 500 rows, head_dim 64, 7.4 and 7.7).
+    // Smaller ones, us a step:
+    //  - half the walkers, where all work groups still have a compute unit each and a unit no more than 16: a SIMD then has one wave to
+    //    serve.  head_dim 64, 8 / 4 walkers: 8 units of 512 rows 7.7 / 7.1, of 2000 9.0 / 7.9, 16 of 1000 8.4 / 7.5, 60 of 876 9.9 / 8.5 (but 32 work
+    //    groups a unit, 8 units of 8000 rows: 9.5 / 10.6); head_dim 128, 4 / 2 walkers: 20 units of 300 rows 9.5 / 8.8, of 500 9.8 / 8.9, 5 of 2000
+    //    10.1 / 9.5.  Likewise where there are only so many chunks (head_dim 64, 4 of them: 6.0 / 5.8).
+    //  - more units than compute units: two work groups of 4 walkers of head_dim 64 fit one.  300 units of 200 rows 10.2 / 7.3, of 800 18.9 / 15.3,
+    //    512 of 2000 37.8 / 36.0.
+    //  - head_dim 64, nearly as many units as compute units, long: 256 units of 1000 rows 13.2 / 13.4, 1500 16.5 / 16.5, 2000 21.3 / 19.9, 4000 36.5 / 35.3; 224 of 2000
+    //    18.7 / 18.6; but 192 of 2000 17.1 / 18.1.
+    //  - head_dim 128, whole work groups of 4 deal out badly to a number of units that does not divide the compute units: 2 or 1 are
+    //    taken where the launch then has fewer turns, and 2 also where it has as many, but four or more; not where one work group of 4 per unit
+    //    uses three quarters of the compute units, or half of them for few turns.  4 / 2 / 1: 2000 rows, 20 units 10.8 / 11.8 / 13.8, 60 units 15.2 / 16.0
+    //    / 17.1, 96 units 20.1 / 20.0 / 18.9, 140 units 29.2 / 26.2 / 25.5, 192 units 30.2 / 32.0 / 30.7, 256 units 37.4 / 38.3 / 38.2; 300 rows, 160 units 10.4 / 11.5 / 11.9,
+    //    192 units 10.3 / 12.0 / 12.6; 1000 rows, 160 units 19.2 / 18.9 / 19.2, 320 units 37.6 / 32.8 / 30.5, 512 units 42.6 / 38.0 / 40.1.
+    const int H = c->d / 64, slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8, cus = std::max(1, slots / 8);
     struct Plan {
         int nw, most, turns, cost;                           // walkers per work group, work groups per unit, turns of each, in all
     };
@@ -804,17 +858,31 @@ void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, 
         const int t_each = turns(nw, most);
         return Plan{nw, most, t_each, (int)std::min<int64_t>((int64_t)t_each * (((int64_t)units * most + resident - 1) / resident), 1 << 30)};
     };
-    Plan p = plan(c->d == 64 ? 8 : 4);
-    if (c->d == 128 && c->plan_merge != 1) {
-        const Plan two = plan(2), one = plan(1);
-        if (two.cost < p.cost || (two.cost == p.cost && two.cost >= 4)) p = two;
-        if (one.cost < p.cost) p = one;
+    auto parts_of = [&](const Plan &p) { return (nchunks + p.nw * p.turns - 1) / (p.nw * p.turns); };
+    Plan p = plan(8 / H);
+    bool one_each = c->plan_merge == 1;                      // one work group per unit
+    if (!one_each) {
+        const bool free = c->plan_merge < 0;
+        const Plan half = plan(4 / H);
+        if (c->d == 64 && (nchunks <= 4 || (units > cus && half.cost <= p.cost))) {
+            p = half;
+        } else if (c->d == 64 && free && units <= cus && 8 * (int64_t)units >= 7 * (int64_t)cus && nchunks >= 24) {
+            p = half;
+            one_each = true;
+        } else if (c->d == 128 && free && units <= cus && (4 * (int64_t)units >= 3 * (int64_t)cus || (2 * (int64_t)units > cus && turns(4, 1) <= 4))) {
+            one_each = true;
+        } else if (free && p.turns < turns(p.nw, 1) && half.turns == p.turns && parts_of(half) <= 16 && (int64_t)units * parts_of(half) <= cus) {
+            p = half;
+        } else if (c->d == 128) {
+            const Plan one = plan(1);
+            if (half.cost < p.cost || (half.cost == p.cost && half.cost >= 4)) p = half;
+            if (one.cost < p.cost) p = one;
+        }
     }
     int parts = 1;
-    if (c->plan_merge != 1 && (p.turns < turns(p.nw, 1) || c->plan_merge == 0))
-        parts = (nchunks + p.nw * p.turns - 1) / (p.nw * p.turns);
-    const auto kernel = c->d == 64 ? decode_step_runs_kernel<64, 8> : p.nw == 4 ? decode_step_runs_kernel<128, 4>
-                        : p.nw == 2 ? decode_step_runs_kernel<128, 2> : decode_step_runs_kernel<128, 1>;
+    if (!one_each && (p.turns < turns(p.nw, 1) || c->plan_merge == 0)) parts = parts_of(p);
+    const auto kernel = c->d == 64 ? (p.nw == 8 ? decode_step_runs_kernel<64, 8> : decode_step_runs_kernel<64, 4>)
+                        : p.nw == 4 ? decode_step_runs_kernel<128, 4> : p.nw == 2 ? decode_step_runs_kernel<128, 2> : decode_step_runs_kernel<128, 1>;
     hipLaunchKernelGGL(kernel, dim3(parts, units), dim3(64 * p.nw * H), 0, s, *c, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,
                        (bf16_t *)o, mask_row, t, scale_log2);
 }

@@ -40,3 +40,34 @@ def test_plans_of_many_units_agree(B, Hq, Hkv, n):
             assert (o.float() - o2.float()).abs().max().item() <= 4 * (2 ** -8 + 2 ** -9) / 2 + 2 ** -8
     for cache in caches:
         cache.close()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n", [(1, 8, 8, 255), (1, 32, 8, 256), (3, 8, 2, 511), (2, 32, 8, 575), (2, 4, 1, 4090), (2, 4, 1, 4095), (16, 5, 5, 640),
+                                        (28, 8, 8, 1470), (28, 8, 8, 1534), (33, 8, 8, 200), (37, 20, 5, 500), (40, 16, 8, 700)])
+def test_plans_of_four_walkers_agree(B, Hq, Hkv, n):
+    """The same at head_dim 64, where work groups of 4 walkers take over: 4 and 5 chunks, 8 and 9, 64 and 65 (16 and 17 work groups
+    a unit), 23 and 24 chunks of nearly as many units as compute units, and more units than those."""
+    steps, d, theta = 3, 64, 0.2
+    x = [to_dev(rand_walk(s, B, H, n + steps, d, clip=c), "bf16") for s, H, c in ((5, Hq, None), (6, Hkv, None), (7, Hkv, 3.5))]
+    caches = [da.Cache(B, Hq, Hkv, d, n + steps, 64, theta, torch.bfloat16) for _ in range(3)]
+    for cache, merge in zip(caches, (-1, 0, 1)):
+        cache.set_launch_plan(merge, 0)
+        da.delta_attn_prefill(*(t[:, :, :n].contiguous() for t in x), theta, 64, cache=cache)
+    for i in range(n, n + steps):
+        row = [t[:, :, i].contiguous() for t in x]
+        (o, m), *others = [da.delta_attn_decode(cache, *row) for cache in caches]
+        assert torch.isfinite(o).all()
+        for o2, m2 in others:
+            assert torch.equal(m, m2)
+            assert (o.float() - o2.float()).abs().max().item() <= 4 * (2 ** -8 + 2 ** -9) / 2 + 2 ** -8
+    for cache in caches:
+        cache.close()
+
+
+@pytest.mark.parametrize("slots", [8, 64, 256])
+@pytest.mark.parametrize("n,steps,Hq,theta", [(62, 4, 4, 0.2), (255, 3, 1, 0.0), (640, 3, 32, 0.2), (1151, 2, 8, 5.0)])
+def test_plans_of_four_walkers_against_the_oracle(slots, n, steps, Hq, theta):
+    """1 .. 19 chunks of 2 units; chunks that are window and history, and the newest row's, on the way."""
+    L = n + steps
+    Q, K, V = rand_walk(81, 2, Hq, L, 64), rand_walk(82, 2, 1, L, 64), rand_walk(83, 2, 1, L, 64, clip=3.5)
+    run_decode(Q, K, V, n, steps, theta, 100, "bf16", plan=(-1, slots))
