@@ -829,25 +829,42 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
         const int ways = many ? 32 : 10, step = (all + ways - 1) / ways, fewest = many ? all - 4 * step : 0;
         float best = INFINITY;
         for (int whole = all;; whole = whole > step ? (whole - 1) / step * step : 0) {   // row tiles that stay whole
-            float work = 0.f, lasts = 0.f;
-            int64_t tiles = 0, level = 0;                        // tiles so far; the next k
-            for (int w = whole - 1, h = halves - 1; w >= 0 || h >= 2 * whole;) {
-                const bool takes_half = w < 0 || (h >= 2 * whole && half_cost[h] > whole_cost[w]);
-                const float cost = takes_half ? half_cost[h--] : whole_cost[w--];
-                tiles += columns;
-                work += cost * (float)columns;
-                for (; tiles > level * cus; ++level) lasts = fmaxf(lasts, (float)(level + 1) * cost * (level == 0 ? kAlone : 1.f));
-            }
-            lasts = fmaxf(lasts, work / (float)cus);
             const int split = halves > 2 * whole ? halves - 2 * whole : 0;
-            if (D == 64 && tiles > cus && tiles <= slots) {      // tile j shares with the j-th last one (turn_at)
+            // on `some` compute units, of which those of a row tile's columns that `of` says come
+            auto estimate = [&](int some, auto of) {
+                float work = 0.f, lasts = 0.f;
+                int64_t tiles = 0, level = 0;                    // tiles so far; the next k
+                for (int w = whole - 1, h = halves - 1; w >= 0 || h >= 2 * whole;) {
+                    const bool takes_half = w < 0 || (h >= 2 * whole && half_cost[h] > whole_cost[w]);
+                    const int n = of(takes_half ? halves - 1 - h : whole - 1 - w);
+                    const float cost = takes_half ? half_cost[h--] : whole_cost[w--];
+                    tiles += n;
+                    work += cost * (float)n;
+                    for (; tiles > level * some; ++level) lasts = fmaxf(lasts, (float)(level + 1) * cost * (level == 0 ? kAlone : 1.f));
+                }
+                return fmaxf(lasts, work / (float)some);
+            };
+            // In XCD-aware order the XCDs that take tiles 0, 2^xsplit, ... of their units, the longest, are done last; in the other one
+            // every XCD streams every unit, which costs 2 % (timed, -4 to 4).  20 / 5 heads of 128, in XCD-aware order wherever the parts deal out /
+            // as chosen: 14 x 200 tokens 36 / 27, 10 x 1000 93 / 84, 2 x 2500 85 / 78, 6 x 2500 220 / 208; 32 / 8 of 64 stay as they are.
+            const int64_t tiles = (int64_t)columns * (whole + split);
+            const bool paired = D == 64 && tiles > cus && tiles <= slots, orders = xsplit < 3 && even(whole) && even(split);
+            float lasts = 1.02f * estimate(cus, [&](int) { return columns; });
+            bool ordered = false;
+            if (orders) {
+                const int mine = (units << xsplit) / 8, part = (1 << xsplit) - 1;
+                const float as = estimate(cus / 8, [&](int tile) {
+                    return mine * ((tile * hgroups + hgroups + part) / (part + 1) - (tile * hgroups + part) / (part + 1));
+                });
+                ordered = paired || as <= lasts;
+                if (ordered) lasts = as;
+            }
+            if (paired) {                                        // tile j shares with the j-th last one (turn_at)
                 auto cost_at = [&](int at) { return at < split ? half_cost[halves - 1 - at] : whole_cost[whole - 1 - (at - split)]; };
                 for (int j = 0; j < (int)tiles - cus; j += columns > 8 ? columns : 8)
                     lasts = fmaxf(lasts, cost_at(j / columns) + cost_at(((int)tiles - 1 - j) / columns));
                 lasts = fmaxf(lasts, cost_at(((int)tiles - cus - 1) / columns) + cost_at(cus / columns));
             }
-            const bool ordered = xsplit < 3 && even(whole) && even(split);
-            if (!ordered) lasts *= 1.02f;                        // (every XCD streams every unit; timed, 0.96 to 1.03)
             if (lasts <= best) {                                 // (of equals the one with more split tiles: the rest are done earlier)
                 best = lasts;
                 cut(whole, ordered);

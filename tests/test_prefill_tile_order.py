@@ -33,6 +33,7 @@ def test_tile_after_tile(B, Hq, Hkv, d, n, W, mode):
 @pytest.mark.parametrize("mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
 @pytest.mark.parametrize("B,Hq,Hkv,d,n,W", [
     (1, 20, 5, 128, 3500, 175), (3, 12, 3, 128, 2500, 100), (1, 32, 8, 64, 4650, 64), (7, 20, 5, 128, 598, 256), (4, 8, 8, 64, 1700, 85),
+    (14, 20, 5, 128, 200, 10), (6, 20, 5, 128, 1000, 50), (14, 12, 6, 64, 300, 15), (2, 12, 6, 64, 2400, 120), (10, 24, 2, 128, 500, 25),
 ])
 def test_cuts_and_long_tiles(B, Hq, Hkv, d, n, W, mode):
     _check(B, Hq, Hkv, d, n, W, mode)
