@@ -135,10 +135,12 @@ __device__ __forceinline__ void load_to_lds(const char *base, uint32_t off, uint
                  : "memory", "m0");
 }
 #pragma clang diagnostic pop
-// 16 bytes a lane that the caller waits for
+// 16 bytes a lane that the caller waits for.  (s_nop: a scalar register that a vector instruction has just written - a readlane, or a
+// spilled one read back - may be used as an address five wait states later, which the compiler does not look after inside asm.  The
+// tile loads above do without: their rows are scalar arithmetic, and nothing in these kernels is spilled.)
 template <int At>
 __device__ __forceinline__ void load_in_flight(u32x4 &to, const char *base, uint32_t off) {
-    asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "+v"(to) : "v"(off), "s"(base), "n"(At) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_dwordx4 %0, %1, %2 offset:%3" : "+v"(to) : "v"(off), "s"(base), "n"(At) : "memory");
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {                   // until at most N of this wave's loads are in flight
@@ -492,7 +494,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     // Wave 0 asks for the next tile; in asm, so that nobody waits for the answer (2 us) before it is needed.
     auto ask = [&]() __attribute__((always_inline)) {
         if (asks && wave == 0 && lane_here() == 0)
-            asm volatile("global_atomic_add %0, %1, %2, %3 sc0" : "+v"(ticket) : "v"(0), "v"(1), "s"(queue) : "memory");
+            asm volatile("s_nop 4\n\tglobal_atomic_add %0, %1, %2, %3 sc0" : "+v"(ticket) : "v"(0), "v"(1), "s"(queue) : "memory");
     };
     // ... and tells the others, once it has waited for the answer; `blocks`: there is none
     auto tell = [&]() __attribute__((always_inline)) {
