@@ -311,7 +311,7 @@ struct NewRow {
         }
         nnz = c.nnz[unit];
     }
-    __device__ __forceinline__ void append(const da_cache &c, int unit, int lane, uint32_t *__restrict__ mask_row, int t) const {
+    __device__ __forceinline__ void append(const da_cache &c, int unit, int lane, uint32_t *__restrict__ mask_row, int t, int slot) const {
         uint32_t fired = 0;
 #pragma unroll
         for (int i = 0; i < D / kWave; ++i) {
@@ -319,7 +319,7 @@ struct NewRow {
             const bool fire = t == 0 || fabsf(bf16_to_f32(k[i]) - bf16_to_f32(h[i])) > c.theta;   // (t == 0: basis row)
             if (t > 0 && t % kChunk == 0) ((bf16_t *)c.ck)[(size_t)unit * D + ch] = h[i];
             if (fire) ((bf16_t *)c.khat)[(size_t)unit * D + ch] = k[i];
-            ((bf16_t *)c.ring)[((size_t)unit * c.Wd + t % c.Wd) * D + ch] = k[i];
+            ((bf16_t *)c.ring)[((size_t)unit * c.Wd + slot) * D + ch] = k[i];
             ((bf16_t *)c.V)[v16_index(unit, c.vrows, D, t, ch)] = v[i];
             const uint64_t b = __ballot(fire);
             if ((lane & 31) == 0) {
@@ -362,17 +362,19 @@ struct NewRow {
 // XCD has its own L2, and fences that write it back or drop it cost more than the second launch did; so the partial rows,
 // and nothing else, are stored past it (relaxed device-scope stores), waited for, counted with a device-scope add, and read
 // past it.
-// What bounds a step of few chunks is the chain launch - counts and runs - keys - scores - merge - meeting, 8 units of 512 rows of 64: 1.2
-// us until all is asked for, 0.7 until it is there, 0.9 keys, 0.5 softmax, 0.4 P V, 1.2 merge, 2.2 meeting, before the order of the
-// requests, the append at the end and work groups of 4 walkers: 7.95 -> 7.1 us a step together; 8 units of 200 rows 6.5 -> 5.8; 20 of 6000 rows of
-// 128 17.1 -> 16.4; 256 of 2048 rows of 64, which the memory bounds, 21.6 -> 19.9.  (V a chunk ahead took longer in every one of them.)
+// What bounds a step of few chunks is the chain launch - counts and runs - keys - scores - merge - meeting; 8 units of 512 rows of 64, before what
+// follows: 1.2 us until all is asked for, 0.7 until it is there, 0.9 keys, 0.5 softmax, 0.4 P V, 1.2 merge, 2.2 meeting.  Requests in one go and
+// before anything else, no division and no constant worked out in their way or after their wait, the append at the end, work groups
+// of 4 walkers: 7.95 -> 6.65 us a step together; 8 units of 200 rows 6.5 -> 5.6; 20 of 6000 rows of 128 17.1 -> 15.5, 40 of 3000 17.4 -> 16.2; 256 of 2048 rows of
+// 64, which the memory bounds, 21.6 -> 21.0.  (V a chunk ahead took longer in every one of them; one copy of a turn's code
+// instead of two changed nothing.)
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel(da_cache c, const bf16_t *__restrict__ q_new,
                                                                               const bf16_t *__restrict__ k_new,
                                                                               const bf16_t *__restrict__ v_new,
                                                                               bf16_t *__restrict__ o_out,
-                                                                              uint32_t *__restrict__ mask_row, int t,
-                                                                              float scale_log2) {
+                                                                              uint32_t *__restrict__ mask_row, int t, int g, int nparts,
+                                                                              int slot, float scale_log2) {
     constexpr int H = D / 64;                                // waves that share a chunk, 64 channels each
     constexpr int KS = 4, CT = 2;                            // per wave: contraction steps, output tiles
     constexpr int kPieces = (kHalfRoom + 511) / 512;         // 1 KiB copies (16 bytes per lane) that cover 64 channels
@@ -386,12 +388,14 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wave = wv / H, half = wv % H, coff = 64 * half;   // part inside the work group; channel half
     bf16_t *stage_a = stage_a_all[wv], *stage_b = stage_b_all[wv];
-    const int unit = blockIdx.y, lane = threadIdx.x & 63, nparts = gridDim.x;
+    const int unit = blockIdx.y, lane = threadIdx.x & 63;
+    // (all arguments that the first requests need are read together: one after the other, each is a wait before them)
+    asm volatile("" ::"s"(q_new), "s"(k_new), "s"(v_new), "s"(c.khat), "s"(c.nnz), "s"(c.surv), "s"(c.ccnt), "s"(c.max_chunks), "s"(c.Wd), "s"(t), "s"(g),
+                 "s"(nparts));
     const int nchunks = t / kChunk + 1;
     // (taking every walkers-th chunk spreads an uneven count, and the cheaper window chunks at the end, evenly)
     const int c_step = NW * nparts, c_begin = (int)blockIdx.x * NW + wave, c_end = nchunks;
-    const int g = c.Hq / c.Hkv;                              // <= 32 in this layout
-    const int b = unit / c.Hkv, hk = unit % c.Hkv;
+    const int first_head = unit * g;                         // of the batch's; g = Hq / Hkv <= 32 in this layout; slot = t % Wd
     const int n32 = lane & 31, kap = lane >> 5;
     const int win_begin = t + 1 - c.Wd;
     // rows of chunk ch left of the decode window (> 0 only for sealed chunks, because Wd >= kChunk)
@@ -400,9 +404,11 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     // History chunk ch: the runs of this wave's channels go straight from global memory to the LDS staging area
     // (128-bit LDS-direct loads: lane i of a copy lands at base + 16 i); its mask rows, lane = row.
     // cnt: the chunk's element counts (channels 0..63, channels 64.. << 16); pieces `from` .. of the copy.
+    const bf16_t *const rooms = (const bf16_t *)c.surv + (size_t)unit * c.max_chunks * run_room_stride(D);
+    const uint32_t *const counts = c.ccnt + (size_t)unit * c.max_chunks;
     auto copy_runs = [&](int ch, uint32_t cnt, bf16_t *sv, int from) {
         const uint32_t first = half * kHalfRoom, len = half ? cnt >> 16 : cnt & 0xffffu;   // this wave's runs
-        const bf16_t *runs = run_room(c, unit, ch) + first;
+        const bf16_t *runs = rooms + (size_t)ch * run_room_stride(D) + first;
 #pragma unroll
         for (int p = 0; p < kPieces; ++p)
             if (p >= from && (uint32_t)p * 512u < len && first + p * 512 + lane * 8 + 8 <= (uint32_t)run_room_stride(D))
@@ -417,11 +423,11 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     if (begins_with_runs) {
         int none = 0;                                        // (as a vector load: a scalar one would be waited for with the next arguments)
         asm("" : "+v"(none));
-        first_count = c.ccnt[(size_t)unit * c.max_chunks + c_begin + none];
+        first_count = counts[c_begin + none];
         copy_runs(c_begin, kSure * 512u | (kSure * 512u << 16), stage_a, 0);
     }
     if (c_begin + c_step < c_end && hist_of(c_begin + c_step) > 0)
-        tot_v = c.ccnt[(size_t)unit * c.max_chunks + c_begin + c_step];
+        tot_v = counts[c_begin + c_step];
     const bool appends = half == 0 && (nchunks - 1) % c_step == c_begin;   // this wave owns row t
     NewRow<D> row_t;
     if (appends) row_t.load(c, unit, lane, k_new, v_new);
@@ -429,7 +435,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     // (columns past the last head repeat it: their results go nowhere)
     u32x4 qop[KS];
     {
-        const bf16_t *qrow = q_new + ((size_t)b * c.Hq + hk * g + min(n32, g - 1)) * D + coff + 4 * kap;
+        const bf16_t *qrow = q_new + (size_t)(first_head + min(n32, g - 1)) * D + coff + 4 * kap;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             const u32x2 q0 = *(const u32x2 *)(qrow + 16 * s), q1 = *(const u32x2 *)(qrow + 16 * s + 8);
@@ -445,30 +451,37 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
         for (int i = 0; i < 4; ++i) w |= (16 * kap + 4 * k + i <= n32 ? 2u : 0u) << (8 * i);
         tri[k] = (int)w;
     }
-    if (begins_with_runs) copy_runs(c_begin, __builtin_amdgcn_readfirstlane(first_count), stage_a, kSure);
-
     f32x16 o[CT];                                            // O^T: lane = head, register r of tile ct =
 #pragma unroll                                               // channel coff + 32 ct + 8 (r / 4) + 4 (l / 32) + r % 4
     for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[ct][r] = 0.f;
+    // (worked out here, while the first loads are on their way: the compiler would do it when they have landed)
+    asm volatile("" : "+v"(tri), "+v"(o[0]), "+v"(o[1]));
+    if (begins_with_runs) copy_runs(c_begin, __builtin_amdgcn_readfirstlane(first_count), stage_a, kSure);
+
     float m_run = -INFINITY, l_run = 0.f;                    // l_run: this lane half's share of the sum
 
     // The two waves of a walker at head_dim 128 wait for each other, and for nobody else: what each has done, in steps of two a turn.
-    // (They are of one work group, so both are there, and take the same chunks; LDS accesses of a wave are carried out in order.)
+    // (They are of one work group, so both are there, and take the same chunks; LDS accesses of a wave are carried out in order.  In asm:
+    // as ordinary accesses they would wait for the copies into LDS that are on their way.)
     int turn = 0;
+    const uint32_t done_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int *)done_by;
     auto tell = [&](int done) __attribute__((always_inline)) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (lane == 0) __hip_atomic_store(&done_by[wv], done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\tds_write_b32 %0, %1" ::"v"(done_at + 4 * wv), "v"(done) : "memory");
     };
     auto await = [&](int done) __attribute__((always_inline)) {
-        while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(&done_by[wv ^ (H - 1)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < done)
+        while (true) {
+            int by;
+            asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(by) : "v"(done_at + 4 * (wv ^ (H - 1))) : "memory");
+            if (__builtin_amdgcn_readfirstlane(by) >= done) break;
             __builtin_amdgcn_s_sleep(1);
-        asm volatile("" ::: "memory");
+        }
     };
     if (H == 2) {
-        if (lane == 0) done_by[wv] = 0;
-        lds_barrier();
+        tell(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
     }
 
     auto do_chunk = [&](int chunk, bf16_t *sv, bf16_t *sv_next, const bf16_t *sv_partner) __attribute__((always_inline)) {
@@ -483,7 +496,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
             copy_runs(chunk + c_step, __builtin_amdgcn_readfirstlane(tot_v), sv_next, 0);
             tot_v = 0;
             if (chunk + 2 * c_step < c_end && hist_of(chunk + 2 * c_step) > 0)
-                tot_v = c.ccnt[(size_t)unit * c.max_chunks + chunk + 2 * c_step];
+                tot_v = counts[chunk + 2 * c_step];
         }
         // V operands of the chunk (needed last, requested first): lane l = channel coff + 32 ct + l % 32, rows of
         // lane half l / 32 of each 16-row group; the newest row is patched in from v_new
@@ -508,8 +521,9 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
 #pragma unroll
                 for (int s = 0; s < KS; ++s) raw[T][s] = u32x4{0u, 0u, 0u, 0u};
                 if (32 * T + n32 >= hist_rows && row <= t) {
+                    const int back = slot - (t - row);           // (of the last Wd rows: one turn of the ring at most)
                     const bf16_t *src = (row == t ? k_new + (size_t)unit * D
-                                                  : (const bf16_t *)c.ring + ((size_t)unit * c.Wd + row % c.Wd) * D) + coff + 4 * kap;
+                                                  : (const bf16_t *)c.ring + ((size_t)unit * c.Wd + (back < 0 ? back + c.Wd : back)) * D) + coff + 4 * kap;
 #pragma unroll
                     for (int s = 0; s < KS; ++s) {
                         const u32x2 x0 = *(const u32x2 *)(src + 16 * s), x1 = *(const u32x2 *)(src + 16 * s + 8);
@@ -705,7 +719,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
         if (first + c_step < c_end) take(first + c_step + wave, stage_b, stage_a, partner_b);
     }
     // the new row goes into the cache (other waves of this launch never read what is written here)
-    if (appends) row_t.append(c, unit, lane, mask_row, t);
+    if (appends) row_t.append(c, unit, lane, mask_row, t, slot);
     const float l_all = l_run + __shfl_xor(l_run, 32);
     // the walkers' (o, m, l) meet in LDS (a walker without chunks contributes m = -inf, l = 0)
     if (H > 1) __syncthreads();                              // (the partner may still read this wave's staging area)
@@ -724,7 +738,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
     }
     __syncthreads();
     constexpr int kThreads = 64 * NW * H;
-    float *part = c.part + ((size_t)b * c.Hq + hk * g) * c.max_parts * part_stride(D);   // [head][max_parts][part_stride]
+    float *part = c.part + (size_t)first_head * c.max_parts * part_stride(D);   // [head][max_parts][part_stride]
     // two channels of a head per thread at a time; a row's last pair is its maximum and sum
     auto put = [&](int h, int ch, float x, float y) {
         const uint64_t v = (uint64_t)__float_as_uint(x) | ((uint64_t)__float_as_uint(y) << 32);
@@ -753,7 +767,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
         }
         if (nparts == 1) {
             const float inv = 1.f / L;
-            *(uint32_t *)(o_out + ((size_t)b * c.Hq + hk * g + h) * D + ch) =
+            *(uint32_t *)(o_out + (size_t)(first_head + h) * D + ch) =
                 (uint32_t)f32_to_bf16(x * inv) | ((uint32_t)f32_to_bf16(y * inv) << 16);
         } else {
             put(h, ch, x, y);
@@ -795,7 +809,7 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
             M = mb;
         }
         const float inv = 1.f / L;
-        *(uint32_t *)(o_out + ((size_t)b * c.Hq + hk * g + h) * D + ch) =
+        *(uint32_t *)(o_out + (size_t)(first_head + h) * D + ch) =
             (uint32_t)f32_to_bf16(x * inv) | ((uint32_t)f32_to_bf16(y * inv) << 16);
     }
 }
@@ -884,7 +898,7 @@ void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, 
     const auto kernel = c->d == 64 ? (p.nw == 8 ? decode_step_runs_kernel<64, 8> : decode_step_runs_kernel<64, 4>)
                         : p.nw == 4 ? decode_step_runs_kernel<128, 4> : p.nw == 2 ? decode_step_runs_kernel<128, 2> : decode_step_runs_kernel<128, 1>;
     hipLaunchKernelGGL(kernel, dim3(parts, units), dim3(64 * p.nw * H), 0, s, *c, (const bf16_t *)q, (const bf16_t *)k, (const bf16_t *)v,
-                       (bf16_t *)o, mask_row, t, scale_log2);
+                       (bf16_t *)o, mask_row, t, c->Hq / c->Hkv, parts, t % c->Wd, scale_log2);
 }
 
 void seal_chunk_runs(da_cache *c, int chunk, hipStream_t s) {
