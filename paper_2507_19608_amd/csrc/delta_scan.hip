@@ -755,17 +755,21 @@ void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s) {
 // of LDS (bf16), so that four work groups share a compute unit and cover each other's load, walk and store - or of 256 rows,
 // which halves the rows walked twice, where that still leaves every compute unit three work groups (128 / 256 rows, bf16: 8 x 2048
 // rows of 64 15.6 / 18.8, 5 x 4096 of 128 20.2 / 20.7, 20 x 4096 29.5 / 25.6 - below the line already -, 20 x 8192 41.7 / 39.0, 40 x 8192
-// 62.9 / 57.6).  In fp32 a work group of 256 + 128 rows is alone on its compute unit, and 128 rows are as good or better from 16
+// 62.9 / 57.6), or of 384 rows and 8 waves where that still holds and the settling waves have a segment each (256 / 384: 20 x 8192 36.7 /
+// 34.3, with 1 % jumps 47 / 42.5 and, where most guesses are wrong, 245 / 206; 20 x 16384 58.3 / 54.2; 40 x 8192 of 64 36.3 / 34.4; shorter ones lose what
+// settling then takes longer, 128 x 3000 of 64 127 / 143).  In fp32 a work group of 256 + 128 rows is alone on its compute unit, and 128 rows are as good or better from 16
 // units up (32 x 4000 rows of 128: 52.7 / 56.8), unless most guesses are wrong (32 x 8000 rows of 64 that drift slowly: 328 / 248).
 static ScanPlan scan_plan(int dtype, int units, int n, int d) {
     const int es = dtype == 0 ? 4 : 2;
     ScanPlan p;
     const bool one = (int64_t)n * d * es <= 128 * 1024;
     p.warm = 128;
-    p.S = one ? n : (int64_t)units * ((d + 63) / 64) * (n / 256) >= 3 * device_cu_count() ? 256 : 128;
+    const int64_t columns = (int64_t)units * ((d + 63) / 64), cus = device_cu_count();
+    const bool longest = !one && es == 2 && columns * (n / 384) >= 3 * cus && n >= 384 * kSettleWaves;
+    p.S = one ? n : longest ? 384 : columns * (n / 256) >= 3 * cus ? 256 : 128;
     p.nseg = (n + p.S - 1) / p.S;
     p.dl = one ? d : 64;
-    p.waves = one ? 8 : 4;
+    p.waves = one || longest ? 8 : 4;
     const int dl = p.dl < d ? p.dl : d, TW = p.waves / ((dl + kWave - 1) / kWave);
     const size_t rows = one ? n : p.S + p.warm;
     p.lds = rows * dl * es + (size_t)p.S * (dl / 32) * 4 + (size_t)TW * dl * 4 + 16;
@@ -774,7 +778,9 @@ static ScanPlan scan_plan(int dtype, int units, int n, int d) {
 
 size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d) {
     const ScanPlan p = scan_plan(dtype, units, n, d);
-    const size_t segs = (size_t)units * p.nseg;
+    // (room as for segments of 256 rows where they are longer: callers size their buffers by it, and it has been that)
+    const int S = p.S > 256 ? 256 : p.S;
+    const size_t segs = (size_t)units * ((n + S - 1) / S);
     return p.nseg == 1 ? 0 : 2 * segs * d * (dtype == 0 ? 4 : 2) + segs * ((d + 63) / 64) * 4;
 }
 

@@ -51,3 +51,14 @@ def test_pieces(kind, d, cuts):
         assert (c == mask[:, :, a:b].sum(dim=(2, 3))).all()
     assert (cache.nnz() == mask.sum(dim=(2, 3))).all()
     cache.close()
+
+
+@pytest.mark.parametrize("units,n,d", [(48, 6144, 64), (47, 6144, 64), (24, 6143, 128), (40, 6560, 96)])
+def test_segments_of_384_rows(units, n, d):
+    """The longest segments, at the line where they begin, with whole ones and a remainder at the end."""
+    for kind in ("quiet", "mixed", "drift"):
+        K = _keys(kind, n + d, units, n, d, "bf16")
+        bits, nnz, khat = da.delta_attn_delta_scan(K, 0.3, want_khat=True)
+        ref_khat, ref_mask = df.reference_keys(K, 0.3)
+        assert (khat.double() == ref_khat).all() and (df.unpack_bits(bits, d) == ref_mask).all(), kind
+        assert (nnz == ref_mask.sum(dim=(2, 3))).all(), kind
