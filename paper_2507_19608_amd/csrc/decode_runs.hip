@@ -855,11 +855,11 @@ void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, 
     //    10.1 / 9.5.  Likewise where there are only so many chunks (head_dim 64, 4 of them: 6.0 / 5.8).
     //  - more units than compute units: two work groups of 4 walkers of head_dim 64 fit one.  300 units of 200 rows 10.2 / 7.3, of 800 18.9 / 15.3,
     //    512 of 2000 37.8 / 36.0.
-    //  - head_dim 64, nearly as many units as compute units, long: 256 units of 1000 rows 13.2 / 13.4, 1500 16.5 / 16.5, 2000 21.3 / 19.9, 4000 36.5 / 35.3; 224 of 2000
-    //    18.7 / 18.6; but 192 of 2000 17.1 / 18.1.
+    //    (256 units of 2048 rows, 8 / 4 walkers: 20.3 / 20.8, and 24.0 / 25.9 where other caches are stepped in between.)
     //  - head_dim 128, whole work groups of 4 deal out badly to a number of units that does not divide the compute units: 2 or 1 are
     //    taken where the launch then has fewer turns, and 2 also where it has as many, but four or more; not where one work group of 4 per unit
-    //    uses three quarters of the compute units, or half of them for few turns.  4 / 2 / 1: 2000 rows, 20 units 10.8 / 11.8 / 13.8, 60 units 15.2 / 16.0
+    //    uses three quarters of the compute units, or half of them for few turns (2048 rows, other caches in between, 192 units 41.9 -> 37.0,
+    //    256 units 50.9 -> 46.8).  4 / 2 / 1: 2000 rows, 20 units 10.8 / 11.8 / 13.8, 60 units 15.2 / 16.0
     //    / 17.1, 96 units 20.1 / 20.0 / 18.9, 140 units 29.2 / 26.2 / 25.5, 192 units 30.2 / 32.0 / 30.7, 256 units 37.4 / 38.3 / 38.2; 300 rows, 160 units 10.4 / 11.5 / 11.9,
     //    192 units 10.3 / 12.0 / 12.6; 1000 rows, 160 units 19.2 / 18.9 / 19.2, 320 units 37.6 / 32.8 / 30.5, 512 units 42.6 / 38.0 / 40.1.
     const int H = c->d / 64, slots = c->plan_slots > 0 ? c->plan_slots : c->cus * 8, cus = std::max(1, slots / 8);
@@ -880,9 +880,6 @@ void decode_step_runs(da_cache *c, const void *q, const void *k, const void *v, 
         const Plan half = plan(4 / H);
         if (c->d == 64 && (nchunks <= 4 || (units > cus && half.cost <= p.cost))) {
             p = half;
-        } else if (c->d == 64 && free && units <= cus && 8 * (int64_t)units >= 7 * (int64_t)cus && nchunks >= 24) {
-            p = half;
-            one_each = true;
         } else if (c->d == 128 && free && units <= cus && (4 * (int64_t)units >= 3 * (int64_t)cus || (2 * (int64_t)units > cus && turns(4, 1) <= 4))) {
             one_each = true;
         } else if (free && p.turns < turns(p.nw, 1) && half.turns == p.turns && parts_of(half) <= 16 && (int64_t)units * parts_of(half) <= cus) {

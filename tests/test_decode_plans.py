@@ -46,7 +46,7 @@ def test_plans_of_many_units_agree(B, Hq, Hkv, n):
                                         (28, 8, 8, 1470), (28, 8, 8, 1534), (33, 8, 8, 200), (37, 20, 5, 500), (40, 16, 8, 700)])
 def test_plans_of_four_walkers_agree(B, Hq, Hkv, n):
     """The same at head_dim 64, where work groups of 4 walkers take over: 4 and 5 chunks, 8 and 9, 64 and 65 (16 and 17 work groups
-    a unit), 23 and 24 chunks of nearly as many units as compute units, and more units than those."""
+    a unit), nearly as many units as compute units, and more units than those."""
     steps, d, theta = 3, 64, 0.2
     x = [to_dev(rand_walk(s, B, H, n + steps, d, clip=c), "bf16") for s, H, c in ((5, Hq, None), (6, Hkv, None), (7, Hkv, 3.5))]
     caches = [da.Cache(B, Hq, Hkv, d, n + steps, 64, theta, torch.bfloat16) for _ in range(3)]
