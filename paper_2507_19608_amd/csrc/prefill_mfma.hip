@@ -8,7 +8,7 @@
 //                        product of the query with the held key, q . k_hat(j): K_hat Q^T on the matrix cores.
 //                        DA_SCORE_GATHER takes this form too: adding up the surviving entries one by one on the
 //                        vector ALU was bound by instruction issue and LDS, at 8.04 ms on 4 x 8192 tokens, 20 / 5 heads
-//                        of 128, 60 % sparsity, which take 1.28 ms here.
+//                        of 128, 60 % sparsity, which take 1.14 ms here.
 //   inside the window    exact scores K Q^T.
 //
 // The keys of a tile are walked as one list of blocks: first the blocks with columns left of some row's window (scores
@@ -17,7 +17,7 @@
 // reads is two tiles, keys and values.
 //
 // What bounds it: matrix cores and vector ALU take turns.  A block of 64 keys costs a wave 1024 cycles of matrix work at
-// head_dim 128 (512 at 64) and about 800 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
+// head_dim 128 (512 at 64) and about 690 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
 // other takes exponentials.  The waves therefore run in two groups half a block apart (waves 0-3 and 4-7, one of each per
 // SIMD), handed from phase to phase by barriers:
 //     A: | PV(b-1) S(b) | softmax(b)   | PV(b) S(b+1) | ...
@@ -41,8 +41,8 @@
 // keys at head_dim 128, 0.81 instead of 1.31 at 64: the same work per wave, twice the loads): for the last, longest rows of a
 // launch that would otherwise wait for them.  A launch cuts its rows into whole and split tiles where that promises to end first
 // (see launch_d) and hands them out longest first from a counter.  Attention alone, all whole / all split / as cut: 2048 tokens, 32
-// / 8 heads of 64: 46.2 / 33.9 / 34.2 us; 1 x 1024, 20 / 5 heads of 128: 38.4 / 27.5 / 28.4; 4 x 2048: 119 / 131 / 119; 4 x 8192:
-// 1271 / 1435 / 1269.
+// / 8 heads of 64: 42.5 / 30.7 / 31.2 us; 1 x 1024, 20 / 5 heads of 128: 35.5 / 24.2 / 24.8; 16 x 200: 27.5 / 32.8 / 28.4; 4 x 2048: 109 / 119 /
+// 110; 1 x 4096: 104 / 99.5 / 97.9.
 //
 // Tiles go from global memory to LDS directly (global_load_lds, 16 bytes per lane, no registers), row-major, two blocks ahead
 // in three buffers, or two where every group has its own.  The 16-byte segments of a row are permuted by the row number so that the reads are free of bank
