@@ -185,8 +185,10 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     constexpr int NT = KB / 32;                 // score tiles per block
     constexpr int KS = D / 16;                  // k-steps of Q K^T
     constexpr int MT = D / 32;                  // channel tiles of the output
-    // LDS: [kBufs] key tiles, [kBufs] value tiles, next tile
-    int *const next_tile = (int *)(lds_raw + 2 * kBufs * kTile);
+    // LDS: [kBufs] key tiles, [kBufs] value tiles, at the end the next tile; where a tile begins, its queries lie behind the first value
+    // tile
+    constexpr int kRoom = 4 * KB * 2 * kRowB;   // of everything but the next tile's number
+    int *const next_tile = (int *)(lds_raw + kRoom);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -292,6 +294,27 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         k_off[i] = lane_off(i, true, kRpl);
         v_off[i] = lane_off(i, false, kRpl);
     }
+    // The queries of a tile before which the matrix cores have nothing to do come through LDS, in whole rows: as operands, 32 rows by 32 bytes
+    // an instruction, the eight waves' 64 KB went through an L1 of 32 in pieces of its lines (16 x 200 tokens of 20 / 5 heads of 128: 2.3 us until
+    // all was asked for, of 16 that a tile took).  Both groups hold the same rows of a split tile: each loads half.  Operands / rows: 16 x 200
+    // 28.3 / 27.2 us, 4 x 512 22.4 / 21.5, 1 x 1024 23.9 / 22.8, 4 x 1024 43.7 / 42.8; 32 / 8 heads of 64, 333 tokens 11.8 / 11.5, 2048 32.6 / 32.0.
+    constexpr int kQWave = 32 * kRowB, kQLoads = kQWave / 1024 / kSplit;
+    const uint32_t lds_q = lds0 + (kBufs + 1) * kTile + my_sr * kRowB;
+    static_assert((kBufs + 1) * kTile + (kSplit == 1 ? 8 : 4) * kQWave <= kRoom, "queries");
+    auto stage_queries = [&]() __attribute__((always_inline)) {
+        const int l = lane_here();
+#pragma unroll
+        for (int i = 0; i < kQLoads; ++i) {
+            const int at = (kSplit == 1 ? 0 : grp * kQLoads) + i, r = at * kRpl + l / kSeg;
+            load_to_lds<0>((const char *)q_rows, min(first + r, n - 1) * kRowB + (((l % kSeg) ^ keys_perm(r)) << 4), lds_q + at * 1024);
+        }
+    };
+    auto staged_queries = [&]() __attribute__((always_inline)) {   // behind a barrier; the area is free behind the next one
+        const int l = lane_here(), r = l & 31;
+        typedef const __attribute__((address_space(3))) u32x4 *lds_vec;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qreg[ks] = *(lds_vec)(uintptr_t)(lds_q + r * kRowB + (((2 * ks + (l >> 5)) ^ keys_perm(r)) << 4));
+    };
     // first key row that this wave loads of its group's block in a turn, and which rows the scores of that block are taken from
     struct Source {
         const char *keys;
@@ -508,8 +531,12 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         // outputs are stored in the vector phase after that.  (Drained and filled again, a tile cost 16 to 19 K clocks beside its
         // turns of 2960.)  The next tile is asked for so early that its number is there when it is opened, two
         // turns before the end; hence at least two turns a tile (the second one sees nothing where there is one block).
+        constexpr bool kStaged = D == 128;                       // (at 64: 8 x 1500 tokens 115.6 us instead of 114.3; 128: 32 x 700 167 instead of 169)
         open_tile(pos);
-        load_queries();
+        if constexpr (kStaged)
+            stage_queries();
+        else
+            load_queries();
         first_loads();
         bool early = turns < 4;                                  // (too short to ask on the way)
         if (early) ask();
@@ -522,9 +549,10 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         int full_first = 0, taken = first;
         bool stored = false;                                     // in the vector phase before
         wait_loads<0>();
-        have_queries();
+        if constexpr (!kStaged) have_queries();
         if (early) tell();
         phase_barrier();
+        if constexpr (kStaged) staged_queries();
         if (grp == 1) phase_barrier();                           // group B starts one phase later
         matrix_phase(no, yes, 0, 0);
         while (true) {
@@ -635,15 +663,15 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             phase_barrier();
         };
         open_tile(pos);
-        load_queries();
+        stage_queries();
         first_loads();
         add_up();
-        wait_loads<0>();
+        wait_loads<kLoads>();                                    // the queries and the first keys; the rest like any turn's
         while (true) {
             clear();
             buf = 0;
-            have_queries();
             phase_barrier();
+            staged_queries();
             if (grp == 1) phase_barrier();                       // group B starts one phase later
             matrix_phase(no, yes, 0, 0);
             vector_phase(0);
@@ -705,7 +733,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             // the next tile's loads go out, then the outputs: its first keys are on their way while these are stored
             if (more) {
                 open_tile(pos);
-                load_queries();
+                stage_queries();
                 first_loads();
             }
             if (stores) {
@@ -715,9 +743,9 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                     for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mo * 32 + 8 * q4) = words[mo][q4];
             }
             if (stores)
-                wait_loads<4 * MO>();                            // for all but the stores
+                wait_loads<4 * MO + kLoads>();                   // the queries and the first keys
             else
-                wait_loads<0>();
+                wait_loads<kLoads>();
             if (!more) return pos;
         }
     }
