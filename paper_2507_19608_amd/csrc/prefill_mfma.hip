@@ -728,7 +728,28 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 }
                 __syncthreads();                                 // the exchange is done with
             }
-            bf16_t *const orow = out_rows + (ptrdiff_t)my_row() * D + 4 * (lane >> 5) + (kSplit > 1 ? grp * (D / 2) : 0);
+            // The outputs turn in LDS, each wave its own, from 8 bytes of 32 rows a store to whole rows: 16 pieces of 16 bytes a row were 4096
+            // writes of partial lines from a work group at head_dim 128, 1.8 us at the end of its tile (8 bytes / rows: 20 / 5 heads of 128, 16 x
+            // 200 tokens 27.1 / 25.1 us, 4 x 512 21.6 / 19.4, 4 x 1024 42.2 / 38.5, 64 x 64 26.1 / 22.1; 32 / 8 heads of 64, 2048 tokens 31.8 / 31.0).
+            constexpr int kOSeg = D / kSplit / 8, kORow = kOSeg * 16, kOStores = 32 * kORow / 1024;   // 16-byte segments of a row here
+            typedef __attribute__((address_space(3))) u32x2 *lds_pair;
+            typedef const __attribute__((address_space(3))) u32x4 *lds_vec;
+            const uint32_t o_lds = lds0 + wave * (32 * kORow);
+            const int o_row = lane & 31, o_seg = lane % kOSeg;
+#pragma unroll
+            for (int mo = 0; mo < MO; ++mo)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    *(lds_pair)(uintptr_t)(o_lds + o_row * kORow + (((4 * mo + q4) ^ (o_row & (kOSeg - 1))) << 4) + 8 * (lane >> 5)) = words[mo][q4];
+            u32x4 rows[kOStores];
+#pragma unroll
+            for (int k = 0; k < kOStores; ++k) {
+                const int r = k * (64 / kOSeg) + lane / kOSeg;
+                rows[k] = *(lds_vec)(uintptr_t)(o_lds + r * kORow + ((o_seg ^ (r & (kOSeg - 1))) << 4));
+            }
+            lds_barrier();                                       // all have turned theirs: the next tile's loads may come, of either kind
+            bf16_t *const o_to = out_rows + (kSplit > 1 ? grp * (D / 2) : 0) + o_seg * 8;
+            const int o_first = wave_first + lane / kOSeg;
             const bool more = pos < end, stores = first < n;     // (first: still this tile's)
             // the next tile's loads go out, then the outputs: its first keys are on their way while these are stored
             if (more) {
@@ -738,12 +759,10 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             }
             if (stores) {
 #pragma unroll
-                for (int mo = 0; mo < MO; ++mo)
-#pragma unroll
-                    for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mo * 32 + 8 * q4) = words[mo][q4];
+                for (int k = 0; k < kOStores; ++k) *(u32x4 *)(o_to + (ptrdiff_t)min(o_first + k * (64 / kOSeg), n - 1) * D) = rows[k];
             }
             if (stores)
-                wait_loads<4 * MO + kLoads>();                   // the queries and the first keys
+                wait_loads<kOStores + kLoads>();                 // the queries and the first keys
             else
                 wait_loads<kLoads>();
             if (!more) return pos;
