@@ -526,6 +526,30 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     auto told = [&]() __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*next_tile); };
 
     if constexpr (kStream) {
+        // A finished tile's outputs, from row `from` on, turned in LDS behind the tiles into whole rows, each wave its own, half of the
+        // channels at a time (that is the room).  As 8 bytes of 32 rows a store they kept a vector phase waiting: 20 / 5 heads of 128, 64 x
+        // 512 tokens 212 / 192 us, 256 x 64 58.4 / 49.1, 4 x 2048 110.6 / 106.0; 32 / 8 heads of 64, 8 x 1500 109.2 / 107.4, 32 x 2048 634 / 624.
+        constexpr int kHSeg = D / 16, kHStores = 32 * kHSeg * 16 / 1024;
+        auto store_rows = [&](bf16_t *to, int from, float inv) __attribute__((always_inline)) {
+            typedef __attribute__((address_space(3))) u32x2 *lds_pair;
+            typedef const __attribute__((address_space(3))) u32x4 *lds_vec;
+            const int l = lane_here(), row = l & 31, seg = l % kHSeg;
+            const uint32_t at = lds0 + 2 * kBufs * kTile + wave * (32 * kHSeg * 16);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int c = 0; c < kHSeg; ++c)
+                    *(lds_pair)(uintptr_t)(at + row * (kHSeg * 16) + ((c ^ (row & (kHSeg - 1))) << 4) + 8 * (l >> 5)) =
+                        packed(oacc[h * (MT / 2) + (c >> 2)], c & 3, inv);
+#pragma unroll
+                for (int k = 0; k < kHStores; ++k) {
+                    const int r = k * (64 / kHSeg) + l / kHSeg;
+                    *(u32x4 *)(to + (ptrdiff_t)min(from + r, n - 1) * D + h * (D / 2) + seg * 8) =
+                        *(lds_vec)(uintptr_t)(at + r * (kHSeg * 16) + ((seg ^ (r & (kHSeg - 1))) << 4));
+                }
+            }
+        };
+        static_assert(2 * kBufs * kTile + 8 * 32 * kHSeg * 16 <= kRoom, "outputs");
         // Tile follows tile without a pause: the requests run two turns ahead of the scores, across the end of a tile into the
         // next one, and the phase that adds up a tile's last values takes the scores of the next one's first keys.  Its
         // outputs are stored in the vector phase after that.  (Drained and filled again, a tile cost 16 to 19 K clocks beside its
@@ -559,7 +583,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             // the key tile of turn + 1 and the value tile of turn, which group A is about to read (loads and stores end in order)
             if (grp == 1) {
                 if (stored)
-                    wait_loads<4 * MT>();
+                    wait_loads<2 * kHStores>();
                 else
                     wait_loads<0>();
             }
@@ -581,21 +605,14 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             const bool stores = full && full_first < n;
             if (full) {
                 const float inv = 1.f / row_sum();
-                const int lane = lane_here();
-                if (stores) {
-                    bf16_t *const orow = full_rows + (ptrdiff_t)min(full_first + (lane & 31), n - 1) * D + 4 * (lane >> 5);
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mt * 32 + 8 * q4) = packed(oacc[mt], q4, inv);
-                }
+                if (stores) store_rows(full_rows, full_first, inv);
                 clear();
             }
             softmax(turn);
             __builtin_amdgcn_s_setprio(1);                       // (for the matrix phase that follows)
             if (grp == 0 || (last && ahead)) {                   // what was asked for in earlier turns, the queries
                 if (stores)
-                    wait_loads<kLoads + 4 * MT>();
+                    wait_loads<kLoads + 2 * kHStores>();
                 else
                     wait_loads<kLoads>();
             }
@@ -639,14 +656,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         if (grp == 0) phase_barrier();                           // (group B's last vector phase)
         wait_loads<0>();                                         // no load into LDS outlives the work group
         const float inv = 1.f / row_sum();
-        const int lane = lane_here();
-        if (taken < n) {
-            bf16_t *const orow = out_rows + (ptrdiff_t)my_row() * D + 4 * (lane >> 5);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) *(u32x2 *)(orow + mt * 32 + 8 * q4) = packed(oacc[mt], q4, inv);
-        }
+        if (taken < n) store_rows(out_rows, wave_first, inv);
         return blocks;
     } else {
         auto vector_phase = [&](int turn) __attribute__((always_inline)) {
