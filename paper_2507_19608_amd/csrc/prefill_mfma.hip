@@ -34,7 +34,7 @@
 // kStream: where many whole tiles, or long ones, follow each other on a compute unit, the next one's first keys and queries are
 // requested, and its first scores taken, while the last one's values are still added up and its outputs stored: 16 to 19 K clocks
 // lie between two tiles otherwise (turns aside).  2 x 5003 tokens 263 -> 250 us, 4 x 8192 2.23 -> 2.02 M clocks, of which the clock takes
-// half back: 1.17 -> 1.14 ms.
+// half back: 1.17 -> 1.14 ms.  At head_dim 64 a second work group on the compute unit works in the pause (see launch_d).
 //
 // kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 64 keys, with their own running
 // (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.64 of the time (1.13 instead of 1.76 us for 64
@@ -528,7 +528,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     if constexpr (kStream) {
         // A finished tile's outputs, from row `from` on, turned in LDS behind the tiles into whole rows, each wave its own, half of the
         // channels at a time (that is the room).  As 8 bytes of 32 rows a store they kept a vector phase waiting: 20 / 5 heads of 128, 64 x
-        // 512 tokens 212 / 192 us, 256 x 64 58.4 / 49.1, 4 x 2048 110.6 / 106.0; 32 / 8 heads of 64, 8 x 1500 109.2 / 107.4, 32 x 2048 634 / 624.
+        // 512 tokens 212 / 192 us, 256 x 64 58.4 / 49.1, 4 x 2048 110.6 / 106.0.
         constexpr int kHSeg = D / 16, kHStores = 32 * kHSeg * 16 / 1024;
         auto store_rows = [&](bf16_t *to, int from, float inv) __attribute__((always_inline)) {
             typedef __attribute__((address_space(3))) u32x2 *lds_pair;
@@ -555,12 +555,8 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         // outputs are stored in the vector phase after that.  (Drained and filled again, a tile cost 16 to 19 K clocks beside its
         // turns of 2960.)  The next tile is asked for so early that its number is there when it is opened, two
         // turns before the end; hence at least two turns a tile (the second one sees nothing where there is one block).
-        constexpr bool kStaged = D == 128;                       // (at 64: 8 x 1500 tokens 115.6 us instead of 114.3; 128: 32 x 700 167 instead of 169)
         open_tile(pos);
-        if constexpr (kStaged)
-            stage_queries();
-        else
-            load_queries();
+        stage_queries();
         first_loads();
         bool early = turns < 4;                                  // (too short to ask on the way)
         if (early) ask();
@@ -573,10 +569,9 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         int full_first = 0, taken = first;
         bool stored = false;                                     // in the vector phase before
         wait_loads<0>();
-        if constexpr (!kStaged) have_queries();
         if (early) tell();
         phase_barrier();
-        if constexpr (kStaged) staged_queries();
+        staged_queries();
         if (grp == 1) phase_barrier();                           // group B starts one phase later
         matrix_phase(no, yes, 0, 0);
         while (true) {
@@ -938,12 +933,14 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     constexpr int lds = 4 * KB * 2 * D * 2 + 16;                 // split tiles take more
     static_assert(lds >= 6 * KB * D * 2 + 16 && lds >= 2 * 4 * (D / 64) * 16 * 64 * 4 + 2 * 4 * 64 * 2 * 4, "whole tiles, the merge");
     // Tile after tile without a pause where that many follow each other, or long ones do (head_dim 128, 20 / 5 heads, pausing / not:
-    // 2 x 5003 tokens 263 / 250 us, 1 x 4096 100 / 98, 4 x 6000 638 / 626; 16 / 2 heads, 21 x 965 120 / 114; head_dim 64, 32 / 8 heads, 32 x 2048
-    // 650 / 632, 8 x 1500 116 / 110); for a second tile of few turns what is done beside two groups' turns in turn takes longer than
-    // a pause (20 / 5 heads of 128, 7 x 598 tokens 34 / 39, 4 x 512 23.8 / 25.0; 32 / 8 of 64, 6 x 1472 71 / 74, 8 x 400 22.9 / 24.0).
+    // 1 x 4096 tokens 104 / 102 us, 26 x 512 77.8 / 73.5, 133 x 64 34.8 / 32.1, though 27 x 900 173 / 179); for a second tile of few turns
+    // what is done beside two groups' turns in turn takes longer than a pause (7 x 598 34.7 / 35.4, 4 x 512 18.3 / 18.7).  At head_dim
+    // 64 the other work group of the compute unit fills the pause, and over 27 launches of 64 to 1400 tokens pausing was faster by 0.9 % on the
+    // average, -4 to 12 (32 / 8 heads: 512 x 64 83.6 / 80.5, 55 x 130 32.9 / 36.9, 16 x 700 61.8 / 64.1, 12 x 1024 82.4 / 86.0, 8 x 1500 106 / 107,
+    // 4 x 4096 306 / 306).
     const int64_t whole_tiles = (int64_t)columns * a.kinds[0].tiles;
-    const bool stream = 2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB);
-    const auto kernel = stream ? prefill_mfma_kernel<D, true> : prefill_mfma_kernel<D, false>;
+    const bool stream = D == 128 && (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
+    const auto kernel = stream ? prefill_mfma_kernel<D, D == 128> : prefill_mfma_kernel<D, false>;
     static std::atomic<uint64_t> lds_set[2];                     // per instantiation, one bit per device
     ensure_dynamic_lds((const void *)kernel, lds, lds_set[stream]);
     hipLaunchKernelGGL(kernel, dim3(a.blocks < slots ? a.blocks : slots), dim3(512), lds, s, a);
