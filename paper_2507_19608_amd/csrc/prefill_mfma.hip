@@ -34,15 +34,15 @@
 // kStream: where many whole tiles, or long ones, follow each other on a compute unit, the next one's first keys and queries are
 // requested, and its first scores taken, while the last one's values are still added up and its outputs stored: 16 to 19 K clocks
 // lie between two tiles otherwise (turns aside).  2 x 5003 tokens 263 -> 250 us, 4 x 8192 2.23 -> 2.02 M clocks, of which the clock takes
-// half back: 1.17 -> 1.14 ms.  At head_dim 64 a second work group on the compute unit works in the pause (see launch_d).
+// half back: 1.17 -> 1.14 ms.  (With queries and outputs in whole rows a pause is shorter: 2 x 5003 249 / 248 us, 4 x 8192 1.224 / 1.214 ms.)  At head_dim 64 a second work group on the compute unit works in the pause (see launch_d).
 //
 // kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 64 keys, with their own running
 // (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.64 of the time (1.13 instead of 1.76 us for 64
 // keys at head_dim 128, 0.81 instead of 1.31 at 64: the same work per wave, twice the loads): for the last, longest rows of a
 // launch that would otherwise wait for them.  A launch cuts its rows into whole and split tiles where that promises to end first
 // (see launch_d) and hands them out longest first from a counter.  Attention alone, all whole / all split / as cut: 2048 tokens, 32
-// / 8 heads of 64: 42.5 / 30.7 / 31.2 us; 1 x 1024, 20 / 5 heads of 128: 35.5 / 24.2 / 24.8; 16 x 200: 27.5 / 32.8 / 28.4; 4 x 2048: 109 / 119 /
-// 110; 1 x 4096: 104 / 99.5 / 97.9.
+// / 8 heads of 64: 41.5 / 30.8 / 30.3 us; 1 x 1024, 20 / 5 heads of 128: 32.2 / 23.0 / 22.9; 16 x 200: 25.8 / 28.6 / 25.5; 4 x 2048: 104 / 110 /
+// 103; 1 x 4096: 99.7 / 93.4 / 92.7.
 //
 // Tiles go from global memory to LDS directly (global_load_lds, 16 bytes per lane, no registers), row-major, two blocks ahead
 // in three buffers, or two where every group has its own.  The 16-byte segments of a row are permuted by the row number so that the reads are free of bank
