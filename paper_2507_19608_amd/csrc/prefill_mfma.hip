@@ -793,7 +793,8 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(Mfma
 
 // Loads straight into LDS want aligned rows; a tensor that does not start on 16 bytes (a slice of a larger one) is laid out
 // anew in front of the launch.  (The kernel of binary32 products needs no alignment, but took 1148 instead of 154 us on 1 x 4096
-// tokens, 20 / 5 heads of 128, 14.7 instead of 1.30 ms on 4 x 8192; with the copies 160 us and 1.25 ms.)
+// tokens, 20 / 5 heads of 128, 14.7 instead of 1.30 ms on 4 x 8192; with the copies 160 us and 1.25 ms.  Queries and outputs, which move once, start
+// anywhere: 16 bytes of global memory a lane at any address, bit for bit the same.)
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 struct CopyPair {
     const u32x4_any *src[2];

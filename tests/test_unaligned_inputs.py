@@ -37,6 +37,19 @@ def test_prefill_of_moved_tensors(window_mode, by, B, Hq, Hkv, n, d, W):
         c.close()
 
 
+# split tiles, whole ones that end before the next begins, tile after tile without a pause: queries and outputs off 16 bytes
+@pytest.mark.parametrize("by", [1, 4])
+@pytest.mark.parametrize("B,Hq,Hkv,n,d", [(1, 4, 2, 333, 64), (70, 12, 6, 130, 64), (2, 4, 1, 300, 128), (16, 20, 5, 200, 128), (128, 20, 5, 65, 128)])
+def test_queries_and_outputs_moved(by, B, Hq, Hkv, n, d):
+    x = [to_dev(rand_walk(s, B, H, n, d, "bf16"), "bf16") for s, H in ((1, Hq), (2, Hkv), (3, Hkv))]
+    want = da.delta_attn_prefill(*x, 0.2, 16)
+    room = torch.full((want[0].numel() + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+    out = (room[by:by + want[0].numel()].view(want[0].shape), torch.empty_like(want[1]), torch.empty_like(want[2]))
+    da.delta_attn_prefill(_moved(x[0], by), x[1], x[2], 0.2, 16, out=out)
+    assert all(torch.equal(s, t) for s, t in zip(out, want))
+    assert (room[:by] == 7).all() and (room[by + want[0].numel():] == 7).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_chunked_prefill_and_scan_of_moved_tensors(d):
     B, Hq, Hkv, n, cut = 1, 4, 2, 300, 130
