@@ -806,30 +806,31 @@ struct WholePlan {
     int dl, threads, L, warm;
     size_t lds;
 };
-// Few channels per work group where there are few units, more where the work groups outnumber the chip (every work group reads
+// Few channels per work group where there are few units, more where the work groups would not all be resident (every work group reads
 // whole cache lines); rows of at most 64 KB in LDS, so that two share a compute unit; runs of at most 32 rows up to 2048 rows.
-// The rows a run warms up on save rounds where the chip is idle and are only work where it is not.
+// The rows a run warms up on save rounds where every work group has a compute unit to itself and are only work where it has not.
 // One launch here / segments, and their settling where there are several, us, without the 1.5 us between these two (5 % jumps): 8 x 333 rows of 64 6.5 / 9.1,
 // 80 x 200 of 128 9.4 / 10.3, 8 x 1024 of 64 9.2 / 13 - 16, 8 x 2048 of 64 11.5 / 14 + 3.9, 10 x 1024 of 128 8.5 / 10 + 3.8, 5 x 4096 of 128
 // 15.7 / 12.5 + 4.8, 20 x 4096 24.5 / 22 + 4.9, 160 x 700 20.9 / 25.6 + 5.4, 256 x 2048 of 64 39.9 / 43.8 + 4.8; fp32, 1 x 256 rows of 64 5.0 / 7.5, 4 x
 // 1000 7.1 / 9.3 + 3.8, 16 x 2000 of 128 15.8 / 13.7 + 4.3.  Beyond, 10 x 5003 rows of 128 (80 KB a work group) 23.5 / 14.6 + 4.8.  With 1 % jumps, where
 // more guesses are wrong, 8 x 2048 of 64 12.7 / 16 + 4 to 19.
-// Where there are about as many units as compute units, and one's rows are 64 to 128 KB, a work group per unit reads whole rows and
+// Where there are about as many units as compute units (three quarters and more), and one's rows are 64 to 128 KB, a work group per unit reads whole rows and
 // needs no second wave of work groups: 256 x 700 rows of 64 18.7 here / 17.2 there, 256 x 400 of 128 19.9 / 17.2, 200 x 900 of 64 18.4 / 16.7, 256 x 1000 22.5 /
 // 23.4; but 256 x 400 of 64 13.3 / 19.0, 160 x 500 of 128 16.5 / 17.4.
 static WholePlan whole_plan(int dtype, int units, int n, int d) {
     const int es = dtype == 0 ? 4 : 2;
+    const int64_t cus = device_cu_count();
     WholePlan p = {8, 256, 0, 0, 0};
     if (n < 64 || (int64_t)n * p.dl * es > 64 * 1024) return p;
-    if (units >= 192 && (int64_t)n * d * es > 64 * 1024 && (int64_t)n * d * es <= 128 * 1024) return p;
+    if (4 * (int64_t)units >= 3 * cus && (int64_t)n * d * es > 64 * 1024 && (int64_t)n * d * es <= 128 * 1024) return p;
     const auto groups = [&](int dl) { return (int64_t)units * (d / dl); };
-    if (groups(8) > 512) p.dl = 16;
+    if (groups(8) > 2 * cus) p.dl = 16;
     if ((int64_t)n * p.dl * es > 64 * 1024) return p;            // (8 channels at a time read lines too often there: 88 x 2958 of 128 55 / 46)
-    if (p.dl == 16 && groups(16) > 512 && n <= 512) p.dl = 32;
+    if (p.dl == 16 && groups(16) > 2 * cus && n <= 512) p.dl = 32;
     p.threads = n > 32 * (256 / (p.dl / 2)) ? 512 : 256;
     const int runs = p.threads / (p.dl / 2);
     p.L = ((n + runs - 1) / runs + 7) / 8 * 8;
-    p.warm = groups(p.dl) <= 256 ? 48 : 32;
+    p.warm = groups(p.dl) <= cus ? 48 : 32;
     const int used = (n + p.L - 1) / p.L;
     p.lds = (size_t)(used * (p.L + 1) + 1) * p.dl * es + (size_t)used * p.dl * 4 + 16;
     return p;
