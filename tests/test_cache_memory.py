@@ -17,7 +17,7 @@ def _needed(units, heads, d, L, Wd, es, runs):
     if runs:
         # survivors and carried-in values, 512 bytes of column masks and 256 of starts per 64 channels; one checkpoint
         per_unit += chunks * ((CHUNK + 1) * d * es + d // 64 * 768) + d * es + 4
-        parts = min(32, -(-chunks // (8 if d == 64 else 1)))
+        parts = min(32, -(-chunks // (4 if d == 64 else 1)))   # of the smallest work groups
     else:
         per_unit += chunks * CHUNK * d * es + (L // CHUNK + 1) * d * es + 4                # survivors; a checkpoint per chunk
         parts = chunks

@@ -689,7 +689,7 @@ def test_rebase_is_skipped_for_keys_beyond_fp16():
 @pytest.mark.parametrize("n,d", [(64, 128), (128, 128), (256, 128), (512, 128), (100, 64), (512, 64), (257, 128)])
 def test_short_prompts_with_the_window_of_eq5(mode, window_mode, n, d):
     """The paper's own regime: prompts of tens to hundreds of tokens with the window of Eq. 5 (gamma = 0.05: W = 3 .. 25).
-    The scan is one segment here; masks, nnz, sparsity and every output element must match the oracle."""
+    The scan is one launch here, and its counts are added up by the attention's; masks, nnz, sparsity and every output element must match the oracle."""
     W = da.delta_attn_window_from_gamma(n, 0.05, 512)
     assert W == orc.window_from_gamma(n, 0.05, 512) and 3 <= W <= 25
     Q, K, V = rand_walk(131, 2, 8, n, d), rand_walk(132, 2, 2, n, d), rand_walk(133, 2, 2, n, d, clip=3.5)

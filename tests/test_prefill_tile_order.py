@@ -1,4 +1,4 @@
-"""Launches of the matrix-core prefill whose tiles follow each other without a pause, and cuts into whole and split tiles: every
+"""Launches of the matrix-core prefill whose tiles follow each other, without a pause (head_dim 128) or with one, and cuts into whole and split tiles: every
 output element against the closed form, masks bit-exact; rows that hold NaN."""
 import pytest
 
@@ -17,7 +17,7 @@ def _check(B, Hq, Hkv, d, n, W, mode):
     assert df.prefill_worst_error(Q, K, V, khat, W, mode == da.DA_WINDOW_SLIDING, [O]) <= 2e-2
 
 
-# whole tiles that outnumber the work groups by far: of one turn (the first row tile, window a multiple of 64), two, three, four,
+# whole tiles that outnumber the work groups by far (128: no pause, 64: pauses between tiles): of one turn (the first row tile, window a multiple of 64), two, three, four,
 # five and more; ragged ones, waves and whole row tiles' ends past the last row, several head chunks per unit
 @pytest.mark.parametrize("mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
 @pytest.mark.parametrize("B,Hq,Hkv,d,n,W", [

@@ -1,5 +1,5 @@
-"""The delta scan where segments cannot settle from their neighbours at once: channels that stay quiet over whole segments,
-chains that meet late or never.  Bit-exact against the row-by-row recurrence, and in time linear in the rows."""
+"""The delta scan where segments (or the runs of the one-launch form) cannot settle from their neighbours at once: channels that stay
+quiet over whole segments, chains that meet late or never.  Bit-exact against the row-by-row recurrence, and in time linear in the rows."""
 import numpy as np
 import pytest
 import torch
@@ -32,6 +32,8 @@ def _keys(kind, seed, units, n, d, dtype):
     ("bf16", 1, 1025, 64), ("bf16", 2, 2049, 64), ("bf16", 1, 128 * 17 + 1, 128), ("bf16", 1, 128 * 33 - 1, 64),
     ("bf16", 1, 128 * 65 + 40, 128), ("bf16", 1, 3000, 96), ("bf16", 1, 5000, 32), ("bf16", 200, 1400, 64),
     ("f32", 1, 128 * 18, 64), ("f32", 1, 4100, 160), ("f32", 2, 128 * 40 + 3, 32),
+    # (of those above, up to 64 KB of rows in 8 channels are one launch)  17 and 33 segments; 9 of 256 rows; half a group of channels
+    ("f32", 1, 2049, 64), ("bf16", 20, 4097, 128), ("bf16", 100, 2100, 64), ("bf16", 1, 4100, 96),
 ])
 def test_segments_that_settle_late(kind, dtype, units, n, d):
     import dense_form as df
@@ -45,9 +47,9 @@ def test_segments_that_settle_late(kind, dtype, units, n, d):
 
 
 @pytest.mark.parametrize("kind", ["quiet", "rare", "mixed"])
-@pytest.mark.parametrize("d,cuts", [(64, (0, 1100, 4000)), (128, (0, 40, 2700)), (64, (0, 3001, 3002, 5200))])
+@pytest.mark.parametrize("d,cuts", [(64, (0, 1100, 4000)), (128, (0, 40, 2700)), (64, (0, 3001, 3002, 5200)), (128, (0, 300, 4500))])
 def test_pieces_that_continue_a_cache(kind, d, cuts):
-    """The rows of a piece start from the reference key the cache carries, over several segments."""
+    """The rows of a piece start from the reference key the cache carries: in one launch, and over several segments (the last case)."""
     import dense_form as df
     n = cuts[-1]
     K = _keys(kind, n + d, 1, n, d, "bf16")

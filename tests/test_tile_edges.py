@@ -35,10 +35,13 @@ def test_binary32_products_kernel(window_mode, dtype, d, n, W, B, Hq):
     ("bf16", 64, (1, 7, 8, 9, 1023, 1024, 1025, 1280)), ("bf16", 128, (5, 511, 512, 513, 640, 641)),
     ("bf16", 32, (2048, 2049)), ("bf16", 96, (682, 683, 897)), ("bf16", 256, (256, 257, 321)), ("f32", 32, (1024, 1025)),
     ("f32", 64, (512, 513, 769)), ("f32", 128, (255, 256, 257, 321)), ("f32", 160, (205, 300)), ("f32", 256, (128, 129, 193)),
+    # several segments (of 128 rows): from more rows on than 64 KB hold in 8 channels
+    ("bf16", 32, (4097, 4224)), ("bf16", 64, (4097, 4225)), ("bf16", 96, (4100,)), ("bf16", 128, (4223,)), ("bf16", 256, (4097,)),
+    ("f32", 32, (2049, 2176)), ("f32", 64, (2049, 2177)), ("f32", 160, (2050,)), ("f32", 256, (2175,)),
 ])
 def test_scan_segments(dtype, d, sizes):
-    """One segment or several, ragged last ones, runs of a few rows or none: bursty and slow keys, so that some guesses of
-    the time-parallel walk hold and some do not."""
+    """One segment, few channels of every row in one launch, or several segments; ragged last ones, runs of a few rows or none:
+    bursty and slow keys, so that some guesses of the time-parallel walk hold and some do not."""
     import torch
     import dense_form as df
     from paper_2507_19608_amd import workloads as wl
@@ -58,12 +61,12 @@ def test_scan_segments(dtype, d, sizes):
         torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("units", [64, 1100])
-def test_scan_of_many_short_rows(units):
-    """The 256-row segments that only launches of many units take, and the same rows in 128-row ones."""
+@pytest.mark.parametrize("units,n", [(64, 1100), (1100, 1100), (65, 2100), (100, 2100), (300, 2049)])
+def test_scan_of_many_short_rows(units, n):
+    """One launch of 8 and of 16 channels a work group; 128-row segments, and the 256-row ones that only launches of many units take."""
     import dense_form as df
     from util import to_dev
-    Kd = to_dev(rand_walk(17, units, 1, 1100, 64, "bf16", 0.03), "bf16")
+    Kd = to_dev(rand_walk(17, units, 1, n, 64, "bf16", 0.03), "bf16")
     bits, nnz, khat = da.delta_attn_delta_scan(Kd, 0.1, want_khat=True)
     ref_khat, ref_mask = df.reference_keys(Kd, 0.1)
     assert (df.unpack_bits(bits, 64) == ref_mask).all() and (nnz == ref_mask.sum(dim=(2, 3))).all()

@@ -57,12 +57,13 @@ def test_noalloc_rejects_a_prompt_beyond_its_scratch():
     assert e.value.status == 3 and str(da.NOALLOC_SCRATCH_BYTES) in str(e.value)
 
 
-@pytest.mark.parametrize("n,d", [(200, 64), (1500, 128)])
+@pytest.mark.parametrize("n,d", [(200, 64), (1500, 128), (4200, 64)])
 def test_noalloc_replays_from_a_captured_graph(n, d):
     """The callers it is for: captured into a HIP graph (after one eager call that did the one-time set-up), replayed
     with eager work and synchronisations in between; every replay must reproduce the eager call bit for bit (and
     delta_attn_prefill's masks and nnz; its outputs to the tolerance, see above).
-    200 tokens are one scan segment, 1500 several (whose counters the scan's first launch clears, not a memset node)."""
+    200 and 1500 tokens are scanned in one launch, 4200 in several segments (in either form the first launch clears what the later
+    ones count in, not a memset node)."""
     B, Hq, Hkv, W, theta = 2, 4, 2, 32, 0.15
     Qd, Kd, Vd = (to_dev(rand_walk(300 + i, B, H, n, d, clip=c), "bf16")
                   for i, (H, c) in enumerate(((Hq, None), (Hkv, None), (Hkv, 3.5))))
