@@ -755,9 +755,11 @@ void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s) {
 // of LDS (bf16), so that four work groups share a compute unit and cover each other's load, walk and store - or of 256 rows,
 // which halves the rows walked twice, where that still leaves every compute unit three work groups (128 / 256 rows, bf16: 8 x 2048
 // rows of 64 15.6 / 18.8, 5 x 4096 of 128 20.2 / 20.7, 20 x 4096 29.5 / 25.6 - below the line already -, 20 x 8192 41.7 / 39.0, 40 x 8192
-// 62.9 / 57.6), or of 384 rows and 8 waves where that still holds and the settling waves have a segment each (256 / 384: 20 x 8192 36.7 /
-// 34.3, with 1 % jumps 47 / 42.5 and, where most guesses are wrong, 245 / 206; 20 x 16384 58.3 / 54.2; 40 x 8192 of 64 36.3 / 34.4; shorter ones lose what
-// settling then takes longer, 128 x 3000 of 64 127 / 143).  In fp32 a work group of 256 + 128 rows is alone on its compute unit, and 128 rows are as good or better from 16
+// 62.9 / 57.6), or of 384 rows and 8 waves where that still holds and the settling waves have a segment each.  256 / 384, two builds in
+// turn, medians of 12, each within 1 %: 20 x 8192 36.6 / 34.6, 20 x 16384 56.2 / 52.3, 40 x 8192 of 64 37.4 / 34.7, 24 x 6144 33.9 / 32.4, 5 x 65536
+// 59.6 / 55.8; over 144 launches (12 shapes, 1 / 5 / 20 % jumps, thresholds 0.06 to 0.23) 5.5 % faster on the geometric mean.  Where nearly all
+// guesses hold that is 3 to 9 %; where many segments are walked again the time hangs on which ones happen to be wrong, -17 to +39 %; keys that never
+// fire -13 (64 x 6144) to +4 %.  Shorter prompts lose what settling then takes longer, 128 x 3000 of 64 127 / 143.  In fp32 a work group of 256 + 128 rows is alone on its compute unit, and 128 rows are as good or better from 16
 // units up (32 x 4000 rows of 128: 52.7 / 56.8), unless most guesses are wrong (32 x 8000 rows of 64 that drift slowly: 328 / 248).
 static ScanPlan scan_plan(int dtype, int units, int n, int d) {
     const int es = dtype == 0 ? 4 : 2;
@@ -813,7 +815,9 @@ struct WholePlan {
 // 80 x 200 of 128 9.4 / 10.3, 8 x 1024 of 64 9.2 / 13 - 16, 8 x 2048 of 64 11.5 / 14 + 3.9, 10 x 1024 of 128 8.5 / 10 + 3.8, 5 x 4096 of 128
 // 15.7 / 12.5 + 4.8, 20 x 4096 24.5 / 22 + 4.9, 160 x 700 20.9 / 25.6 + 5.4, 256 x 2048 of 64 39.9 / 43.8 + 4.8; fp32, 1 x 256 rows of 64 5.0 / 7.5, 4 x
 // 1000 7.1 / 9.3 + 3.8, 16 x 2000 of 128 15.8 / 13.7 + 4.3.  Beyond, 10 x 5003 rows of 128 (80 KB a work group) 23.5 / 14.6 + 4.8.  With 1 % jumps, where
-// more guesses are wrong, 8 x 2048 of 64 12.7 / 16 + 4 to 19.
+// more guesses are wrong, 8 x 2048 of 64 12.7 / 16 + 4 to 19.  There is no walk in order here for ends that travel one run a round (up to 128
+// rounds): where nothing fires for the whole prompt 8 x 2048 of 64 takes 84 / 18 + 141, 5 x 4096 of 128 179 / 23 + 294, 256 x 2048 of 64 228 / 101 + 168,
+// 100 x 1500 of 128 174 / 69 + 130; keys that drift 20 / 18 + 33, 28 / 23 + 51, 65 / 84 + 29, 57 / 52 + 29.
 // Where there are about as many units as compute units (three quarters and more), and one's rows are 64 to 128 KB, a work group per unit reads whole rows and
 // needs no second wave of work groups: 256 x 700 rows of 64 18.7 here / 17.2 there, 256 x 400 of 128 19.9 / 17.2, 200 x 900 of 64 18.4 / 16.7, 256 x 1000 22.5 /
 // 23.4; but 256 x 400 of 64 13.3 / 19.0, 160 x 500 of 128 16.5 / 17.4.
