@@ -366,7 +366,7 @@ struct NewRow {
 // follows: 1.2 us until all is asked for, 0.7 until it is there, 0.9 keys, 0.5 softmax, 0.4 P V, 1.2 merge, 2.2 meeting.  Requests in one go and
 // before anything else, no division and no constant worked out in their way or after their wait, the append at the end, work groups
 // of 4 walkers: 7.95 -> 6.65 us a step together; 8 units of 200 rows 6.5 -> 5.6; 20 of 6000 rows of 128 17.1 -> 15.5, 40 of 3000 17.4 -> 16.2; 256 of 2048 rows of
-// 64, which the memory bounds, 21.6 -> 21.0.  (V a chunk ahead took longer in every one of them; one copy of a turn's code
+// 64, which the memory bounds, 21.6 -> 20.7.  (V a chunk ahead took longer in every one of them; one copy of a turn's code
 // instead of two changed nothing.)
 template <int D, int NW>
 __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel(da_cache c, const bf16_t *__restrict__ q_new,

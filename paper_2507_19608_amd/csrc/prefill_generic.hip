@@ -9,7 +9,7 @@
 // with its own running (maximum, sum, output), and meet in LDS once at the end.  The calls this kernel sees are small
 // (a numerics user's single head of a few hundred rows), so what bounds it is how many waves there are and how long the
 // longest one walks: a wave per 64 rows that walked every key took 725 us on 256 rows of one head of 64 (4 waves on the
-// chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each: 6.7 us, 16.4 for the whole
+// chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each: 6.8 us, 16.0 for the whole
 // call with the scan.
 //
 // Matrix-core layout (16x16x4, wave64): A lane l holds row l % 16, k = l / 16; B lane l column l % 16, same k; D lane l

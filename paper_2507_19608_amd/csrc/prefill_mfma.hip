@@ -8,7 +8,7 @@
 //                        product of the query with the held key, q . k_hat(j): K_hat Q^T on the matrix cores.
 //                        DA_SCORE_GATHER takes this form too: adding up the surviving entries one by one on the
 //                        vector ALU was bound by instruction issue and LDS, at 8.04 ms on 4 x 8192 tokens, 20 / 5 heads
-//                        of 128, 60 % sparsity, which take 1.14 ms here.
+//                        of 128, 60 % sparsity, which take 1.14 to 1.24 ms here (the clock differs from card to card).
 //   inside the window    exact scores K Q^T.
 //
 // The keys of a tile are walked as one list of blocks: first the blocks with columns left of some row's window (scores
@@ -23,18 +23,17 @@
 //     A: | PV(b-1) S(b) | softmax(b)   | PV(b) S(b+1) | ...
 //     B:                | PV(b-1) S(b) | softmax(b)   | ...
 // A wave in its matrix phase goes first (s_setprio): it issues one instruction in 32 clocks, and every one that has to wait for
-// the other wave's arithmetic lengthens the phase.  By clock stamps inside the kernel a matrix phase takes 1130 clocks alone, a
-// vector phase 1480 (340 of them its tile loads, whose issue is slow), 2960 for the two.  What is added to a matrix phase -
-// addresses, loads, the look at the masks - comes out at more than it saves in the vector phase: its instructions wait in order
-// for whatever is issued between them (loads among the matrix instructions: 2.21 M clocks on 4 x 8192 tokens, here 1.79 M).
-// 4 x 8192 tokens, 20 / 5 heads of 128: 2.46 -> 2.23 M clocks, 1.24 -> 1.17 ms (the clock goes down under this load, to 1.8 of 2.4
-// GHz); 2 x 5003 263 -> 251 us, 1 x 4096 109 -> 101, 2048 tokens of 32 / 8 heads of 64 32.2 -> 29.7 (priority the other way round, a
-// branch and an address for every load, fmaxf, a wait where the next tile is asked for).
+// the other wave's arithmetic lengthens the phase.  What is added to a matrix phase - addresses, loads, the look at the masks -
+// comes out at more than it saves in the vector phase: its instructions wait in order for whatever is issued between them.
+// Counters on 4 x 8192 tokens, 20 / 5 heads of 128: 2.08 M clocks a launch, 1610 a phase, of which one wave's matrix instructions
+// fill 1024 and the other wave's vector instructions 692.  With the priority the other way round, a branch and an address for every
+// load, fmaxf, a wait where the next tile is asked for, a pause between tiles and queries and outputs in pieces it was 2.43 M; of 15 %
+// fewer clocks 7 % are left in time (1344 -> 1256 us a call, in turn on one card): the clock goes down under this load, to 1.7 of 2.4 GHz.
 //
 // kStream: where many whole tiles, or long ones, follow each other on a compute unit, the next one's first keys and queries are
-// requested, and its first scores taken, while the last one's values are still added up and its outputs stored: 16 to 19 K clocks
-// lie between two tiles otherwise (turns aside).  2 x 5003 tokens 263 -> 250 us, 4 x 8192 2.23 -> 2.02 M clocks, of which the clock takes
-// half back: 1.17 -> 1.14 ms.  (With queries and outputs in whole rows a pause is shorter: 2 x 5003 249 / 248 us, 4 x 8192 1.224 / 1.214 ms.)  At head_dim 64 a second work group on the compute unit works in the pause (see launch_d).
+// requested, and its first scores taken, while the last one's values are still added up and its outputs stored.  Pausing / not: 1 x 4096
+// tokens 104 / 102 us, 4 x 8192 1224 / 1214, 26 x 512 77.8 / 73.5.  At head_dim 64 a second work group on the compute unit works in the
+// pause (see launch_d).
 //
 // kSplit = 2: a tile has 128 score rows and the two groups walk alternate blocks of 64 keys, with their own running
 // (maximum, sum, output), and meet in LDS at the end.  Twice the tiles, each done in 0.64 of the time (1.13 instead of 1.76 us for 64
@@ -552,8 +551,8 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         static_assert(2 * kBufs * kTile + 8 * 32 * kHSeg * 16 <= kRoom, "outputs");
         // Tile follows tile without a pause: the requests run two turns ahead of the scores, across the end of a tile into the
         // next one, and the phase that adds up a tile's last values takes the scores of the next one's first keys.  Its
-        // outputs are stored in the vector phase after that.  (Drained and filled again, a tile cost 16 to 19 K clocks beside its
-        // turns of 2960.)  The next tile is asked for so early that its number is there when it is opened, two
+        // outputs are stored in the vector phase after that.  (Drained and filled again, and with queries and outputs in
+        // pieces, a tile cost 16 to 19 K clocks beside its turns of 3.2 K.)  The next tile is asked for so early that its number is there when it is opened, two
         // turns before the end; hence at least two turns a tile (the second one sees nothing where there is one block).
         open_tile(pos);
         stage_queries();
