@@ -742,6 +742,8 @@ da_status delta_attn_cache_create(da_cache **out, int32_t batch, int32_t n_q_hea
     if (ok) ok = hipMemset(c->nnz, 0, units * 8) == hipSuccess;
     ok = ok && hipMalloc((void **)&c->arrived, units * 4) == hipSuccess;
     if (ok) ok = hipMemset(c->arrived, 0, units * 4) == hipSuccess;
+    // (hipMemset returns before the memory is cleared, on the null stream, which a caller's non-blocking stream does not wait for)
+    ok = ok && hipStreamSynchronize(nullptr) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
         free_all(c);
