@@ -293,15 +293,18 @@ da_status ensure_prefix(da_cache *c) {
     }
     da_prefix *f = c->pf;
     const size_t units = (size_t)c->B * c->Hkv, d = c->d, ld = c->max_seq;
-    bool ok = true;
+    bool ok = true, fresh = false;
     auto room = [&](void **ptr, size_t bytes) {
         if (!ok || *ptr) return;
         ok = hipMalloc(ptr, bytes) == hipSuccess && hipMemset(*ptr, 0, bytes) == hipSuccess;
+        fresh = true;
     };
     room(&f->k, units * ld * d * 2);
     room(&f->h, units * ld * d * 2);
     room(&f->v, units * ld * d * 2);
     room((void **)&f->m, units * ld * (d / 32) * 4);
+    // (hipMemset returns before the memory is cleared, on the null stream, which the caller's stream need not wait for)
+    if (fresh && ok) ok = hipStreamSynchronize(nullptr) == hipSuccess;
     if (!ok) {
         (void)launch_ok("prefill_append: room for the cached sequence as plain arrays");   // records the error text
         return DA_ERR_HIP;

@@ -35,3 +35,26 @@ def test_new_cache():
     with torch.cuda.stream(torch.cuda.Stream()):
         got = _fill_and_step(x, 130, LONG, False)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def _two_pieces(x, cut, max_seq, wait):
+    cache = da.Cache(B, HQ, HKV, D, max_seq, 64, THETA, torch.bfloat16)
+    n = x[0].shape[2]
+    got = []
+    for r in (slice(0, cut), slice(cut, n)):
+        got += da.delta_attn_prefill_append(cache, *(t[:, :, r].contiguous() for t in x), THETA, W)
+        if wait:
+            torch.cuda.synchronize()
+    torch.cuda.current_stream().synchronize()
+    cache.close()
+    return got
+
+
+def test_first_piece_of_a_chunked_prefill():
+    """The first piece allocates and clears the cache's plain arrays and writes its rows there; the second one reads them."""
+    x = _rows(200)
+    want = _two_pieces(x, 90, 200, True)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.Stream()):
+        got = _two_pieces(x, 90, LONG, False)
+    assert all(torch.equal(a, b) for a, b in zip(got, want))
