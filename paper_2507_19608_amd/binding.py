@@ -261,15 +261,16 @@ def _qkv_params(Q, K, V, window, theta, scale, score_mode, window_mode):
 
 
 def _hip_copy(dst: int, src: int, nbytes: int):
-    """Device-to-device copy through the HIP runtime (plumbing for the cache accessors)."""
+    """Device-to-device copy through the HIP runtime (plumbing for the cache accessors), on the current stream: hipMemcpy runs on the
+    null stream and returns before the copy is done, and whoever reads the result on another stream does not wait for it."""
     global _hip
     if _hip is None:
         _hip = ctypes.CDLL("libamdhip64.so")
-        _hip.hipMemcpy.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int]
-        _hip.hipMemcpy.restype = ctypes.c_int
-    rc = _hip.hipMemcpy(dst, src, nbytes, 3)   # hipMemcpyDeviceToDevice
+        _hip.hipMemcpyAsync.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_void_p]
+        _hip.hipMemcpyAsync.restype = ctypes.c_int
+    rc = _hip.hipMemcpyAsync(dst, src, nbytes, 3, _stream())   # hipMemcpyDeviceToDevice
     if rc != 0:
-        raise RuntimeError(f"hipMemcpy failed with {rc}")
+        raise RuntimeError(f"hipMemcpyAsync failed with {rc}")
 
 
 def _mask_and_counts(B, Hkv, n, d, device):

@@ -58,3 +58,16 @@ def test_first_piece_of_a_chunked_prefill():
     with torch.cuda.stream(torch.cuda.Stream()):
         got = _two_pieces(x, 90, LONG, False)
     assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_mask_and_counts_of_a_cache():
+    """Copied out on another stream and read there at once, a cache's mask rows and counts are those of the calls that filled it."""
+    n = 130
+    x = _rows(n)
+    cache = da.Cache(B, HQ, HKV, D, LONG, 64, THETA, torch.bfloat16)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        _, bits, nnz = da.delta_attn_prefill(*x, THETA, W, cache=cache)
+        got = cache.mask_rows().clone(), cache.nnz().clone()
+        torch.cuda.current_stream().synchronize()
+    assert torch.equal(got[0], bits) and torch.equal(got[1], nnz)
+    cache.close()
