@@ -169,7 +169,7 @@ da_status delta_attn_prefill_noalloc(const da_prefill_params *p, const void *Q, 
  *             are invalid), 256-byte aligned
  * The cache keeps the sequence so far as the plain arrays the prefill kernels read (keys, reference keys, values,
  * mask rows), with max_seq rows of room: about 6 * head_dim + 4 * head_dim / 32 bytes per (KV head, row).
- * The first call on a cache allocates them (hipMalloc + hipMemset, released by delta_attn_cache_destroy; DA_ERR_HIP if that fails; make that call outside graph capture); a call that follows
+ * The first call on a cache allocates them (hipMalloc + hipMemset and a wait for it, released by delta_attn_cache_destroy; DA_ERR_HIP if that fails; make that call outside graph capture); a call that follows
  * another such call, or delta_attn_cache_reset, then only adds its own rows.  After decode steps or a one-shot
  * delta_attn_prefill into the cache the arrays are rebuilt from the cache by the next call, at a cost proportional to
  * the cache length.
@@ -183,8 +183,8 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
  * values), reference keys at the start of every 64 rows, the current reference key, a ring of
  * the last decode_window raw keys, and V (Sec. III-A last paragraph, Sec. III-C).  All sequences of
  * the batch advance together.  A cache may start empty (the first decoded row is then the basis
- * row) or be filled by delta_attn_prefill.  Allocates device memory on the current device; owned
- * by the library until delta_attn_cache_destroy. */
+ * row) or be filled by delta_attn_prefill.  Allocates device memory on the current device (cleared where it has to be
+ * when the call returns, so that any stream may use the cache at once); owned by the library until delta_attn_cache_destroy. */
 da_status delta_attn_cache_create(da_cache **out, int32_t batch, int32_t n_q_heads, int32_t n_kv_heads,
                                   int32_t head_dim, int32_t max_seq, int32_t decode_window, float theta,
                                   float scale, int32_t dtype);
