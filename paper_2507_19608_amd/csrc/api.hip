@@ -226,12 +226,6 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.Hkv = p->n_kv_heads;
     a.Hq = p->n_q_heads;
     a.n = p->seq_len;
-    stage_begin(kStageScan, s);
-    a.queue = p->head_dim >= 64 ? (uint32_t *)(ws + w.queue) : nullptr;      // (32: another kernel, and less room)
-    a.sum = launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, w.counts ? (uint32_t *)(ws + w.counts) : nullptr, nnz, units,
-                              p->seq_len, p->head_dim, p->theta, s, nullptr, a.queue);
-    stage_end(kStageScan, s);
-    if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     a.q_off = 0;
     a.nq = p->seq_len;
     a.W = p->window;
@@ -242,12 +236,24 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.V = V;
     a.Khat = khat;
     a.O = O;
+    const bool in_one = prefill_short_supported(a);
+    if (!in_one) {
+        stage_begin(kStageScan, s);
+        a.queue = p->head_dim >= 64 ? (uint32_t *)(ws + w.queue) : nullptr;  // (32: another kernel, and less room)
+        a.sum = launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, w.counts ? (uint32_t *)(ws + w.counts) : nullptr, nnz, units,
+                                  p->seq_len, p->head_dim, p->theta, s, nullptr, a.queue);
+        stage_end(kStageScan, s);
+        if (!launch_ok("delta_scan")) return DA_ERR_HIP;
+    }
     stage_begin(kStageAttn, s);
     bool launched = true;
-    if (prefill_mfma_supported(a)) {
+    if (in_one || prefill_mfma_supported(a)) {
         const size_t bytes = (size_t)units * p->seq_len * p->head_dim * 2;
         launch_copy_aligned(a, ws + w.copies, ws + w.copies + bytes, bytes, s);
-        launch_prefill_mfma(a, s);
+        if (in_one)
+            launch_prefill_short(a, p->theta, cache ? khat : nullptr, mask_bits, nnz, s);
+        else
+            launch_prefill_mfma(a, s);
     } else
         launched = launch_prefill_generic(a, s);
     stage_end(kStageAttn, s);

@@ -67,6 +67,10 @@ bool prefill_mfma_supported(const PrefillArgs &a);
 // K and V that are not are copied to room_k, room_v (`bytes` each, aligned), which take their place in `a`.
 void launch_copy_aligned(PrefillArgs &a, void *room_k, void *room_v, size_t bytes, hipStream_t s);
 void launch_prefill_mfma(const PrefillArgs &a, hipStream_t s);
+// Scan and attention in one launch, of prompts whose rows fit into LDS: bf16, head_dim 64 or 128.  K and V have to be aligned to 16
+// bytes when it is launched.  khat: NULL, or [units][n][d] for the reference keys; a.Khat, a.queue and a.sum are not for it.
+bool prefill_short_supported(const PrefillArgs &a);
+void launch_prefill_short(const PrefillArgs &a, float theta, void *khat, uint32_t *mask_bits, uint64_t *nnz, hipStream_t s);
 // compute units of the current device (256 if it cannot be asked)
 int device_cu_count();
 
