@@ -260,7 +260,9 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     };
 
     f32x16 oacc[MT];
-    float m_run, l_run[4];                      // maximum; four chains of the running sum, this lane half's share
+    float limit;                                // of a block's sum; -1 as long as there is no maximum
+    constexpr int kSums = D == 64 ? 4 : 1;
+    float m_run, l_run[kSums];                  // maximum; running sum, this lane half's share (head_dim 64: in the four chains it is added up in)
     f32x16 s[NT];                               // raw scores of the current block
     u32x4 pb[2 * NT];                           // its probabilities, bf16, as P V operands
 
@@ -315,8 +317,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         });
     };
     // Masks where some row of the wave does not see all of the block, then online softmax: s -> pb.  The running maximum is
-    // only raised when the block maximum exceeds it by more than 2^8 in the exponent, so probabilities stay <= 256
-    // and the accumulator is rarely rescaled.
+    // only raised where a block goes far beyond it, so the accumulator is rarely rescaled.
     auto softmax = [&](int v) {
         const bool hat = v < at_hat, none = v >= at_nv;          // (none: a turn in which this group has no block)
         const int jb = (hat ? v : at_kb0 + v - at_hat) * KB;
@@ -336,9 +337,32 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                     s[T][r] = __uint_as_float((__float_as_uint(s[T][r]) & take) | (0xff800000u & ~take));
                 }
         }
-        float bm;
-        {
-            // (maximum, three operands to an instruction, and not fmaxf, which quiets every operand with an instruction of its own:
+        auto exponentials = [&]() __attribute__((always_inline)) {
+            const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
+            // The row sum is taken over the probabilities as rounded to bf16, i.e. over the very weights that P V uses:
+            // the output is then an exact weighted mean of the value rows, and the rounding of the weights cannot bias it
+            // (summing the unrounded ones does, by up to 2^-9 relative when many weights are equal).
+            float sum[4] = {0.f, 0.f, 0.f, 0.f};                 // four chains: one would wait for itself
+            if constexpr (D == 64)
+                for (int k = 0; k < 4; ++k) sum[k] = l_run[k];
+#pragma unroll
+            for (int T = 0; T < NT; ++T)
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) {
+                    f32x2 p;                                     // bare v_exp_f32: tiny results may flush to 0
+                    p[0] = __builtin_amdgcn_exp2f(fmaf(s[T][r], a.scale_log2, neg_m));
+                    p[1] = __builtin_amdgcn_exp2f(fmaf(s[T][r + 1], a.scale_log2, neg_m));
+                    const bf16x2 pk = __builtin_convertvector(p, bf16x2);
+                    pb[2 * T + (r >> 3)][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
+                    sum[(r >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pk, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, sum[(r >> 1) & 3], false);
+                }
+            if constexpr (D == 64)
+                for (int k = 0; k < 4; ++k) l_run[k] = sum[k];
+            return (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        };
+        // the block's maximum, in log2 units
+        auto block_max = [&]() __attribute__((always_inline)) {
+            // (three operands to an instruction, and not fmaxf, which quiets every operand with an instruction of its own:
             // where a score is NaN its row is NaN either way)
             auto max3 = [](float x, float y, float z) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); };
             float mx[4];                                         // four chains: one would wait for itself
@@ -348,35 +372,43 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 mx[k] = NT == 1 ? __builtin_elementwise_maximum(mx[k], s[0][k + 12]) : max3(mx[k], s[0][k + 12], s[NT - 1][k]);
                 if (NT == 2) mx[k] = __builtin_elementwise_maximum(max3(mx[k], s[NT - 1][k + 4], s[NT - 1][k + 8]), s[NT - 1][k + 12]);
             }
-            bm = __builtin_elementwise_maximum(max3(mx[0], mx[1], mx[2]), mx[3]);
+            const float bm = __builtin_elementwise_maximum(max3(mx[0], mx[1], mx[2]), mx[3]);
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
-            bm = __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * a.scale_log2;
-        }
-        if (__any(bm > m_run + 8.f)) {
+            return __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * a.scale_log2;
+        };
+        auto raise = [&](float bm) __attribute__((always_inline)) {
             const float m_new = fmaxf(m_run, bm);
             const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
             m_run = m_new;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) l_run[k] *= alpha;
+            for (int k = 0; k < kSums; ++k) l_run[k] *= alpha;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) oacc[mt] *= alpha;
-        }
-        const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-        // The row sum is taken over the probabilities as rounded to bf16, i.e. over the very weights that P V uses:
-        // the output is then an exact weighted mean of the value rows, and the rounding of the weights cannot bias it
-        // (summing the unrounded ones does, by up to 2^-9 relative when many weights are equal).
-#pragma unroll
-        for (int T = 0; T < NT; ++T)
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                f32x2 p;                                         // bare v_exp_f32: tiny results may flush to 0
-                p[0] = __builtin_amdgcn_exp2f(fmaf(s[T][r], a.scale_log2, neg_m));
-                p[1] = __builtin_amdgcn_exp2f(fmaf(s[T][r + 1], a.scale_log2, neg_m));
-                const bf16x2 pk = __builtin_convertvector(p, bf16x2);
-                pb[2 * T + (r >> 3)][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
-                l_run[(r >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pk, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run[(r >> 1) & 3], false);
+        };
+        if constexpr (D == 64) {
+            // the running maximum is only raised when the block's exceeds it by more than 2^8, so that probabilities stay <= 256
+            const float bm = block_max();
+            if (__any(bm > m_run + 8.f)) raise(bm);
+            exponentials();
+        } else {
+            // The exponentials are taken against the maximum as it stands, and the block's sum says whether that was high enough: a block's
+            // maximum is only looked for where some row of the wave has none yet, or a sum beyond 2^60 (then they are taken again; sums
+            // and outputs have 2^67 left).  That is 22 of the phase's 173 instructions: 4 x 8192 tokens of 20 / 5 heads 1159 -> 1129 us a call,
+            // 1 x 4096 108.5 -> 106.2, 2 x 5003 in a band 261 -> 255.  At head_dim 64 the scores, kept for that, do not fit into the registers.
+            float sum = 0.f;
+            bool look = __any(limit < 0.f);
+            if (!look) {
+                sum = exponentials();
+                look = __any(sum > limit);
             }
+            if (__builtin_expect(look, false)) {
+                raise(block_max());
+                limit = m_run == -INFINITY ? -1.f : 0x1p60f;
+                sum = exponentials();
+            }
+            l_run[0] += sum;
+        }
     };
 
     // ---- the walk.  The tiles of turn t lie in buffers t % kBufs.  The key tile of turn t + 2 and the value tile of turn t + 1 are
@@ -409,11 +441,12 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[mt][r] = 0.f;
         m_run = -INFINITY;
+        limit = -1.f;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) l_run[k] = 0.f;
+        for (int k = 0; k < kSums; ++k) l_run[k] = 0.f;
     };
     auto row_sum = [&]() {
-        const float l = (l_run[0] + l_run[1]) + (l_run[2] + l_run[3]);
+        const float l = kSums == 1 ? l_run[0] : (l_run[0] + l_run[1]) + (l_run[kSums - 2] + l_run[kSums - 1]);
         const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
         return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     };
