@@ -261,8 +261,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 
     f32x16 oacc[MT];
     float limit;                                // of a block's sum; -1 as long as there is no maximum
-    constexpr int kSums = D == 64 ? 4 : 1;
-    float m_run, l_run[kSums];                  // maximum; running sum, this lane half's share (head_dim 64: in the four chains it is added up in)
+    float m_run, l_run;                         // maximum; running sum, this lane half's share
     f32x16 s[NT];                               // raw scores of the current block
     u32x4 pb[2 * NT];                           // its probabilities, bf16, as P V operands
 
@@ -321,30 +320,31 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     auto softmax = [&](int v) {
         const bool hat = v < at_hat, none = v >= at_nv;          // (none: a turn in which this group has no block)
         const int jb = (hat ? v : at_kb0 + v - at_hat) * KB;
-        if (none || (hat ? jb + KB > wave_win_first : jb < wave_win_last || jb + KB > wave_first + 1)) {
-            // the row's columns of the block, [from, to), as bits; two instructions a score: a bit spread over the word chooses (a
-            // compare, a select and the wait for the condition between them took 600 clocks a block, half of the softmax itself)
-            const int row = my_row();
-            const int from = min(max((hat ? 0 : my_win) - jb, 0), KB), to = none ? 0 : min(max((hat ? my_win : row + 1) - jb, 0), KB);
-            uint64_t seen = to > 0 ? ~(uint64_t)0 >> (64 - to) : 0;
-            seen = from < 64 ? seen >> from << from : 0;
-            seen >>= 4 * (lane_here() >> 5);                     // (the lane half's first row is column 4)
+        auto mask = [&]() __attribute__((always_inline)) {
+            if (none || (hat ? jb + KB > wave_win_first : jb < wave_win_last || jb + KB > wave_first + 1)) {
+                // the row's columns of the block, [from, to), as bits; two instructions a score: a bit spread over the word chooses (a
+                // compare, a select and the wait for the condition between them took 600 clocks a block, half of the softmax itself)
+                const int row = my_row();
+                const int from = min(max((hat ? 0 : my_win) - jb, 0), KB), to = none ? 0 : min(max((hat ? my_win : row + 1) - jb, 0), KB);
+                uint64_t seen = to > 0 ? ~(uint64_t)0 >> (64 - to) : 0;
+                seen = from < 64 ? seen >> from << from : 0;
+                seen >>= 4 * (lane_here() >> 5);                 // (the lane half's first row is column 4)
 #pragma unroll
-            for (int T = 0; T < NT; ++T)
+                for (int T = 0; T < NT; ++T)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const uint32_t take = (uint32_t)__builtin_amdgcn_sbfe((int)(uint32_t)(seen >> (32 * T)), 8 * (r >> 2) + (r & 3), 1);
-                    s[T][r] = __uint_as_float((__float_as_uint(s[T][r]) & take) | (0xff800000u & ~take));
-                }
-        }
+                    for (int r = 0; r < 16; ++r) {
+                        const uint32_t take = (uint32_t)__builtin_amdgcn_sbfe((int)(uint32_t)(seen >> (32 * T)), 8 * (r >> 2) + (r & 3), 1);
+                        s[T][r] = __uint_as_float((__float_as_uint(s[T][r]) & take) | (0xff800000u & ~take));
+                    }
+            }
+        };
+        mask();
         auto exponentials = [&]() __attribute__((always_inline)) {
             const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
             // The row sum is taken over the probabilities as rounded to bf16, i.e. over the very weights that P V uses:
             // the output is then an exact weighted mean of the value rows, and the rounding of the weights cannot bias it
             // (summing the unrounded ones does, by up to 2^-9 relative when many weights are equal).
             float sum[4] = {0.f, 0.f, 0.f, 0.f};                 // four chains: one would wait for itself
-            if constexpr (D == 64)
-                for (int k = 0; k < 4; ++k) sum[k] = l_run[k];
 #pragma unroll
             for (int T = 0; T < NT; ++T)
 #pragma unroll
@@ -356,8 +356,6 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                     pb[2 * T + (r >> 3)][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
                     sum[(r >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pk, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, sum[(r >> 1) & 3], false);
                 }
-            if constexpr (D == 64)
-                for (int k = 0; k < 4; ++k) l_run[k] = sum[k];
             return (sum[0] + sum[1]) + (sum[2] + sum[3]);
         };
         // the block's maximum, in log2 units
@@ -381,34 +379,44 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
             m_run = m_new;
-#pragma unroll
-            for (int k = 0; k < kSums; ++k) l_run[k] *= alpha;
+            l_run *= alpha;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) oacc[mt] *= alpha;
         };
-        if constexpr (D == 64) {
-            // the running maximum is only raised when the block's exceeds it by more than 2^8, so that probabilities stay <= 256
-            const float bm = block_max();
-            if (__any(bm > m_run + 8.f)) raise(bm);
-            exponentials();
-        } else {
-            // The exponentials are taken against the maximum as it stands, and the block's sum says whether that was high enough: a block's
-            // maximum is only looked for where some row of the wave has none yet, or a sum beyond 2^60 (then they are taken again; sums
-            // and outputs have 2^67 left).  That is 22 of the phase's 173 instructions: 4 x 8192 tokens of 20 / 5 heads 1159 -> 1129 us a call,
-            // 1 x 4096 108.5 -> 106.2, 2 x 5003 in a band 261 -> 255.  At head_dim 64 the scores, kept for that, do not fit into the registers.
-            float sum = 0.f;
-            bool look = __any(limit < 0.f);
-            if (!look) {
-                sum = exponentials();
-                look = __any(sum > limit);
+        // At head_dim 64 the scores, kept until their sum is known, would not fit into the registers: where they are wanted again they are taken
+        // again, from keys in memory (the next but one tile may be on its way to where they lay in LDS).
+        auto scores_again = [&]() __attribute__((always_inline)) {
+            const bf16_t *keys = (const bf16_t *)(hat || none ? Hp : Kp);
+#pragma unroll
+            for (int T = 0; T < NT; ++T) {
+                const u32x4 *row = (const u32x4 *)(keys + (size_t)min(jb + 32 * T + (lane_here() & 31), n - 1) * D);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[T][r] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks)
+                    s[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, row[2 * ks + (lane_here() >> 5)]),
+                                                                  __builtin_bit_cast(bf16x8, qreg[ks]), s[T], 0, 0, 0);
             }
-            if (__builtin_expect(look, false)) {
-                raise(block_max());
-                limit = m_run == -INFINITY ? -1.f : 0x1p60f;
-                sum = exponentials();
-            }
-            l_run[0] += sum;
+            mask();
+        };
+        // The exponentials are taken against the maximum as it stands, and the block's sum says whether that was high enough: a block's
+        // maximum is only looked for where some row of the wave has none yet, or a sum beyond 2^60 (then they are taken again; sums
+        // and outputs have 2^67 left).  That is 22 of the phase's 173 instructions.  us a call, maximum of every block / where needed: 20 / 5 heads of
+        // 128, 4 x 8192 tokens 1159 / 1129, 1 x 4096 108.5 / 106.2, 2 x 5003 in a band 261 / 255; 32 / 8 heads of 64, 1 x 2048 37.7 / 35.5,
+        // 32 x 2048 690 / 674, 4 x 4096 305 / 301, 8 x 1500 in a band 123 / 118.
+        float sum = 0.f;
+        bool look = __any(limit < 0.f), taken = false;
+        if (!look) {
+            sum = exponentials();
+            look = taken = __any(sum > limit);
         }
+        if (__builtin_expect(look, false)) {
+            if (D == 64 && taken) scores_again();
+            raise(block_max());
+            limit = m_run == -INFINITY ? -1.f : 0x1p60f;
+            sum = exponentials();
+        }
+        l_run += sum;
     };
 
     // ---- the walk.  The tiles of turn t lie in buffers t % kBufs.  The key tile of turn t + 2 and the value tile of turn t + 1 are
@@ -442,12 +450,10 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             for (int r = 0; r < 16; ++r) oacc[mt][r] = 0.f;
         m_run = -INFINITY;
         limit = -1.f;
-#pragma unroll
-        for (int k = 0; k < kSums; ++k) l_run[k] = 0.f;
+        l_run = 0.f;
     };
     auto row_sum = [&]() {
-        const float l = kSums == 1 ? l_run[0] : (l_run[0] + l_run[1]) + (l_run[kSums - 2] + l_run[kSums - 1]);
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
         return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     };
     auto packed = [](const f32x16 &o, int q4, float inv) {

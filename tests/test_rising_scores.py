@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # 2^60 is 41 in the exponent, the largest float 88: below, between, beyond, and down again; split tiles, whole ones, tile after tile
 @pytest.mark.parametrize("window_mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
-@pytest.mark.parametrize("d,B,Hq,Hkv,n", [(128, 1, 4, 1, 500), (64, 1, 4, 1, 500), (128, 30, 16, 4, 330), (128, 20, 20, 5, 260)])
+@pytest.mark.parametrize("d,B,Hq,Hkv,n", [(128, 1, 4, 1, 500), (64, 1, 4, 1, 500), (64, 64, 16, 4, 450), (128, 30, 16, 4, 330), (128, 20, 20, 5, 260)])
 def test_rising_scores(window_mode, d, B, Hq, Hkv, n):
     rng = np.random.default_rng(n + d)
     Q = np.abs(rand_walk(1, B, Hq, n, d)) * 0 + 1.0 + 0.1 * rng.standard_normal((B, Hq, n, d))
