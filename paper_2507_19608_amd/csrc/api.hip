@@ -246,20 +246,27 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
         if (!launch_ok("delta_scan")) return DA_ERR_HIP;
     }
     stage_begin(kStageAttn, s);
-    bool launched = true;
+    bool launched = true, filled = false;                        // filled: the attention launch takes the cache's part along
     if (in_one || prefill_mfma_supported(a)) {
         const size_t bytes = (size_t)units * p->seq_len * p->head_dim * 2;
         launch_copy_aligned(a, ws + w.copies, ws + w.copies + bytes, bytes, s);
-        if (in_one)
+        if (in_one) {
             launch_prefill_short(a, p->theta, cache ? khat : nullptr, mask_bits, nnz, s);
-        else
-            launch_prefill_mfma(a, s);
+        } else {
+            CacheFill fill = {};
+            if (cache && cache->fast) fill = cache_fill(cache, 0, p->seq_len, p->seq_len, a.K, a.V, khat, mask_bits, nullptr, nnz, a.sum);
+            filled = fill.items > 0 && prefill_takes_fill(a, fill);
+            if (filled) a.sum = NnzSum{};                            // (the hand-off adds up)
+            launch_prefill_mfma(a, filled ? &fill : nullptr, s);
+        }
     } else
         launched = launch_prefill_generic(a, s);
     stage_end(kStageAttn, s);
     if (!launched) return DA_ERR_UNSUPPORTED;
     if (!launch_ok("prefill attention")) return DA_ERR_HIP;
-    if (cache) {
+    if (filled) {
+        cache->len = p->seq_len;
+    } else if (cache) {
         stage_begin(kStageCacheFill, s);
         cache_fill_from_prefill(cache, p, K, V, khat, mask_bits, nnz, s);
         stage_end(kStageCacheFill, s);
@@ -271,18 +278,14 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
 // workspace of delta_attn_prefill_append: what the scan of the new rows needs (the whole-sequence arrays live in the
 // cache, see da_prefix)
 struct AppendLayout {
-    size_t hnew, scan, queue, total;
+    size_t scan, queue, total;
 };
 
 AppendLayout append_layout(const da_prefill_params *p) {
-    const size_t units = (size_t)p->batch * p->n_kv_heads, d = p->head_dim, es = elt_size(p->dtype);
-    const size_t m = p->seq_len;
     AppendLayout w;
     size_t off = 0;
-    w.hnew = off;
-    off += align_up(units * m * d * es);
     w.scan = off;
-    off += align_up(delta_scan_scratch_bytes(p->dtype, (int)units, (int)m, (int)d));
+    off += align_up(delta_scan_scratch_bytes(p->dtype, p->batch * p->n_kv_heads, p->seq_len, p->head_dim));
     w.queue = off;
     off += align_up(kPrefillQueueBytes);
     w.total = off;
@@ -367,19 +370,17 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     const bool kept = f->rows == t0;
     f->rows = -1;                                   // in flux until this call has gone through
     if (!kept) expand_cache_runs(cache, t0, ld, f->k, f->h, f->v, f->m, s);
-    // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis)
+    // 2. Eq. 2-3 over the new rows, continuing from the cache's reference key (row 0 of an empty cache is the basis); keys, values and
+    //    reference keys join the plain arrays
     stage_begin(kStageScan, s);
+    auto row_of = [&](void *array) { return (char *)array + (size_t)t0 * d * 2; };
+    const RowCopy copy = {{K, V}, {row_of(f->k), row_of(f->v)}, units, m, ld, d / 8};
     // (the scan's counts lie where decode steps leave their partial rows: d + 4 floats per query head at the least)
-    const NnzSum sum = launch_delta_scan(p->dtype, K, ws + w.hnew, mask_bits, ws + w.scan, (uint32_t *)cache->part, nnz, units, m, d,
-                                         p->theta, s, t0 > 0 ? cache->khat : nullptr, (uint32_t *)(ws + w.queue));
+    const NnzSum sum = launch_delta_scan(p->dtype, K, row_of(f->h), mask_bits, ws + w.scan, (uint32_t *)cache->part, nnz, units, m, d,
+                                         p->theta, s, t0 > 0 ? cache->khat : nullptr, (uint32_t *)(ws + w.queue), &copy);
     stage_end(kStageScan, s);
     if (!launch_ok("delta_scan")) return DA_ERR_HIP;
-    // 3. the new rows join the plain arrays and the cache
-    stage_begin(kStageCacheFill, s);
-    cache_fill_runs(cache, t0, nk, K, V, ws + w.hnew, mask_bits, nnz, f, sum, s);
-    stage_end(kStageCacheFill, s);
-    if (!launch_ok("cache_fill")) return DA_ERR_HIP;
-    // 4. attention of the new rows over all nk keys
+    // 3. attention of the new rows over all nk keys; the new rows join the cache
     PrefillArgs a;
     a.dtype = p->dtype;
     a.B = p->batch;
@@ -399,10 +400,18 @@ da_status delta_attn_prefill_append(const da_prefill_params *p, const void *Q, c
     a.Khat = f->h;
     a.O = O;
     a.queue = (uint32_t *)(ws + w.queue);
+    const CacheFill fill = cache_fill(cache, t0, nk, ld, f->k, f->v, f->h, mask_bits, f->m, nnz, sum);
+    const bool filled = prefill_takes_fill(a, fill);
     stage_begin(kStageAttn, s);
-    launch_prefill_mfma(a, s);                         // (supported: check_append has asked)
+    launch_prefill_mfma(a, filled ? &fill : nullptr, s);   // (supported: check_append has asked)
     stage_end(kStageAttn, s);
     if (!launch_ok("prefill_append attention")) return DA_ERR_HIP;
+    if (!filled) {
+        stage_begin(kStageCacheFill, s);
+        launch_cache_fill(fill, s);
+        stage_end(kStageCacheFill, s);
+        if (!launch_ok("cache_fill")) return DA_ERR_HIP;
+    }
     cache->len = nk;
     f->rows = nk;
     return DA_OK;

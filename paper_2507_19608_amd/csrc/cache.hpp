@@ -90,10 +90,20 @@ void cache_fill_from_prefill(da_cache *c, const da_prefill_params *p, const void
                              const void *Khat, const uint32_t *mask_bits,
                              const uint64_t *nnz, hipStream_t s);
 // column-run layout (fast == 1)
-// appends rows t0 .. n_k - 1 (t0 = rows already held), given as arrays of these rows alone [units][n_k - t0][...]; with
-// `full` they also join its plain arrays, which hold the rows before t0 (needed where t0 > 0)
-void cache_fill_runs(da_cache *c, int t0, int n_k, const void *Knew, const void *Vnew, const void *Hnew, const uint32_t *Mnew,
-                     const uint64_t *nnz_new, const da_prefix *full, const NnzSum &sum, hipStream_t s);
+// Rows t0 .. n_k - 1 of a sequence on their way into a cache that holds rows 0 .. t0 - 1 (kernels: cache_fill.hpp).
+struct CacheFill {
+    const unsigned short *K, *V, *H;     // [units][ld][d] keys, values, reference keys, from row 0 on
+    const uint32_t *Mnew;                // [units][n_k - t0][d/32] mask rows from t0 on
+    uint32_t *Mall;                      // [units][ld][d/32] mask rows from row 0 on, to which the new ones are added; NULL where t0 == 0 and nobody wants them
+    const uint64_t *nnz_new;             // [units], or, where sum.groups > 0, to be added up
+    NnzSum sum;
+    da_cache cache;
+    int ld, t0, n_k;
+    int units, items;                    // chunks with new rows of all units
+};
+CacheFill cache_fill(const da_cache *c, int t0, int n_k, int ld, const void *K, const void *V, const void *H, const uint32_t *Mnew, uint32_t *Mall,
+                     const uint64_t *nnz_new, const NnzSum &sum);
+void launch_cache_fill(const CacheFill &f, hipStream_t s);
 // writes the cached rows 0 .. t0 - 1 out as whole-sequence arrays with ld >= t0 rows of room per unit
 void expand_cache_runs(da_cache *c, int t0, int ld, void *Kfull, void *Hfull, void *Vfull, uint32_t *Mfull,
                        hipStream_t s);

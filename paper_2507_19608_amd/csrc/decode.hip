@@ -669,7 +669,7 @@ void cache_fill_from_prefill(da_cache *c, const da_prefill_params *p, const void
                              const uint64_t *nnz, hipStream_t s) {
     const int units = c->B * c->Hkv, n = p->seq_len;
     if (c->fast) {
-        da::cache_fill_runs(c, 0, n, K, V, Khat, mask_bits, nnz, nullptr, da::NnzSum{}, s);
+        da::launch_cache_fill(da::cache_fill(c, 0, n, n, K, V, Khat, mask_bits, nullptr, nnz, da::NnzSum{}), s);
         c->len = n;
         return;
     }

@@ -7,82 +7,18 @@
 #include <algorithm>
 
 #include "cache.hpp"
+#include "cache_fill.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
+#include "mfma.hpp"
 
 using namespace da;
 
 namespace {
 
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(16))) int i32x16;
-
-// V cache, column-run layout: 16 rows per channel, [unit][t / 16][channel][16].  Inside a group of 16 the
-// slot of row p is 8 k + i with k = (p / 4) % 2 and i = 4 (p / 8) + p % 4: the order in which the 32x32
-// matrix-core accumulator hands 8 consecutive registers of lane half k to the next contraction.
-__device__ __forceinline__ size_t v16_index(int unit, int vrows, int d, int t, int ch) {
-    const int p = t & 15;
-    const int slot = 8 * ((p >> 2) & 1) + 4 * (p >> 3) + (p & 3);
-    return (((size_t)unit * (vrows >> 4) + (t >> 4)) * d + ch) * 16 + slot;
-}
-
-__device__ __forceinline__ bf16_t *run_room(const da_cache &c, int unit, int chunk) {
-    return (bf16_t *)c.surv + ((size_t)unit * c.max_chunks + chunk) * run_room_stride(c.d);
-}
-
-// A sealed chunk's room holds, per 64 channels (kHalfRoom elements apart): the column masks (64 x 8 bytes: bit r = the
-// channel's mask bit of row r), where each channel's run starts (64 x 4 bytes: byte offset from the head), then the runs.
-constexpr int kHead = 256 + 128;                             // elements of masks and starts
-constexpr int kHalfRoom = kRunHalfRoom;
-static_assert(kHalfRoom == kHead + (kChunk + 1) * 64 && kHalfRoom % 8 == 0, "16-byte pieces");
-
-// Seals 64 channels of one chunk, by one wave (lane = channel): head and runs - for every channel in ascending order
-// {reference value held before the chunk, then its surviving values in row order}.  From the chunk's keys (row stride d) and
-// mask rows in LDS into LDS; returns the number of elements.
-__device__ __forceinline__ uint32_t build_runs(const bf16_t *keys, int d, const uint32_t *mask, int wpr, bf16_t held, bf16_t *room) {
-    const int lane = threadIdx.x & (kWave - 1);
-    uint32_t lo = 0, hi = 0;                                     // the channel's mask bits of rows 0..31, 32..63
-#pragma unroll 16
-    for (int r = 0; r < 32; ++r) {
-        lo |= ((mask[r * wpr + (lane >> 5)] >> (lane & 31)) & 1u) << r;
-        hi |= ((mask[(r + 32) * wpr + (lane >> 5)] >> (lane & 31)) & 1u) << r;
-    }
-    uint32_t total;
-    uint32_t p = kHead + wave_exclusive_scan((uint32_t)__popc(lo) + (uint32_t)__popc(hi) + 1u, &total);
-    ((uint32_t *)room)[2 * lane] = lo;
-    ((uint32_t *)room)[2 * lane + 1] = hi;
-    ((uint32_t *)room)[128 + lane] = 2u * p;
-    room[p++] = held;
-    for (int rb = 0; rb < kChunk; rb += 16) {                    // 16 keys at a time: reads first
-        bf16_t kv[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) kv[u] = keys[(rb + u) * d + lane];
-        const uint32_t bits = (rb < 32 ? lo : hi) >> (rb & 31);
-#pragma unroll
-        for (int u = 0; u < 16; ++u)
-            if ((bits >> u) & 1u) room[p++] = kv[u];
-    }
-    return kHead + total;
-}
-
-// sealed channels in LDS [D / 64][kHalfRoom] -> the chunk's room, 16-byte pieces (the last one may carry a few elements nobody
-// reads)
-template <int D, int NT>
-__device__ __forceinline__ void store_runs(const da_cache &c, int unit, int chunk, const bf16_t *runs, const uint32_t *len) {
-    for (int h = 0; h < D / 64; ++h) {
-        u32x4 *dst = (u32x4 *)(run_room(c, unit, chunk) + h * kHalfRoom);
-        const u32x4 *src = (const u32x4 *)(runs + h * kHalfRoom);
-        for (int i = threadIdx.x; i < (int)(len[h] + 7) / 8; i += NT) dst[i] = src[i];
-    }
-    if (threadIdx.x == 0) c.ccnt[(size_t)unit * c.max_chunks + chunk] = len[0] | (D > 64 ? len[1] << 16 : 0u);
-}
 
 // Seal from the raw-key ring: runs right after the step that appended the chunk's last row.
 template <int D>
@@ -113,114 +49,11 @@ __global__ __launch_bounds__(256) void seal_from_ring_kernel(da_cache c, int chu
     store_runs<D, 256>(c, unit, chunk, runs, len);
 }
 
-// Hand-off of prefilled rows to the cache (Sec. III-C): rows t0 .. n_k - 1 (t0 = rows the cache already holds) are appended,
-// one work group of 4 waves per (chunk that contains such a row, unit).  K, V, H [units][n_k - t0][D], M: the new rows - keys,
-// values, reference keys, mask rows.  `full` (chunked prefill): the whole sequence as plain arrays, [units][ld][...]; the new
-// rows are added to them, and the chunk's and its predecessor's old rows are read from them.  Without it t0 is 0.
-// The chunk's rows pass through LDS, whole lines in and out.  (A wave per chunk with a lane per channel that loaded and stored
-// two bytes at a time took 26 us on 1024 rows of 10 units of 128, and a kernel of its own the plain arrays; now 8.7 us
-// together.)
-struct FullRows {
-    bf16_t *k, *v, *h;
-    uint32_t *m;
-    int ld;
-};
+// Hand-off of prefilled rows to the cache where no attention launch takes it along (cache_fill.hpp).
 template <int D>
-__global__ __launch_bounds__(256) void cache_fill_runs_kernel(const bf16_t *__restrict__ Knew, const bf16_t *__restrict__ Vnew,
-                                                              const bf16_t *__restrict__ Hnew, const uint32_t *__restrict__ Mnew,
-                                                              const uint64_t *__restrict__ nnz_new, NnzSum sum, da_cache c, FullRows full,
-                                                              int t0, int n_k) {
-    constexpr int WPR = D / 32, P = D / 8, kIn = kChunk * P / 256;
-    __shared__ __attribute__((aligned(16))) bf16_t keys[kChunk * D];
-    __shared__ __attribute__((aligned(16))) bf16_t vals[kChunk * D];
-    __shared__ __attribute__((aligned(16))) bf16_t runs[(D / 64) * kHalfRoom];
-    __shared__ uint32_t mask[kChunk * WPR], len[2];
-    const int chunk = blockIdx.x + t0 / kChunk, unit = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int m = n_k - t0, r0 = chunk * kChunk;
-    const int ra = max(r0, t0), rb = min(r0 + kChunk, n_k);      // new rows of this chunk
-    const size_t new0 = (size_t)unit * m, full0 = (size_t)unit * full.ld, cache0 = (size_t)unit * c.max_seq;
-    // a row of an array: the new rows' own, or (rows before t0) the whole sequence's
-    auto piece = [&](const bf16_t *fresh, const bf16_t *old, int row, int p) {
-        return row >= t0 ? ((const u32x4 *)fresh)[(new0 + row - t0) * P + p] : ((const u32x4 *)old)[(full0 + row) * P + p];
-    };
-    auto held_of = [&](int row, int ch) { return row >= t0 ? Hnew[(new0 + row - t0) * D + ch] : full.h[(full0 + row) * D + ch]; };
-    // 1. keys (the chunk's old rows included), values and mask rows into LDS; new rows join the plain arrays
-    {
-        u32x4 kk[kIn], vv[kIn], hh[kIn];
-#pragma unroll
-        for (int i = 0; i < kIn; ++i) {                          // (rows past the end are the last one again)
-            const int idx = tid + i * 256, row = min(r0 + idx / P, rb - 1), p = idx % P;
-            kk[i] = piece(Knew, full.k, row, p);
-            vv[i] = ((const u32x4 *)Vnew)[(new0 + max(row, ra) - t0) * P + p];
-            hh[i] = ((const u32x4 *)Hnew)[(new0 + max(row, ra) - t0) * P + p];
-        }
-        uint32_t mw = 0;
-        const int mrow = min(r0 + tid / WPR, rb - 1);
-        if (tid < kChunk * WPR)
-            mw = mrow >= t0 ? Mnew[(new0 + mrow - t0) * WPR + tid % WPR] : full.m[(full0 + mrow) * WPR + tid % WPR];
-#pragma unroll
-        for (int i = 0; i < kIn; ++i) {
-            const int idx = tid + i * 256, row = r0 + idx / P, p = idx % P;
-            ((u32x4 *)keys)[idx] = kk[i];
-            ((u32x4 *)vals)[idx] = vv[i];
-            if (row >= ra && row < rb) {
-                if (full.k) {
-                    ((u32x4 *)full.k)[(full0 + row) * P + p] = kk[i];
-                    ((u32x4 *)full.v)[(full0 + row) * P + p] = vv[i];
-                    ((u32x4 *)full.h)[(full0 + row) * P + p] = hh[i];
-                }
-                if (row >= n_k - c.Wd) ((u32x4 *)c.ring)[((size_t)unit * c.Wd + row % c.Wd) * P + p] = kk[i];
-            }
-        }
-        if (tid < kChunk * WPR) {
-            const int row = r0 + tid / WPR;
-            mask[tid] = mw;
-            if (row >= ra && row < rb) {
-                c.mask[(cache0 + row) * WPR + tid % WPR] = mw;
-                if (full.k) full.m[(full0 + row) * WPR + tid % WPR] = mw;
-            }
-        }
-    }
-    if (blockIdx.x == 0 && wave == 3) {
-        const uint64_t fresh = sum.groups > 0 ? add_up_nnz(sum, lane < 8 ? unit : sum.units) : nnz_new[unit];
-        if (lane == 0) c.nnz[unit] = (t0 == 0 ? 0ull : c.nnz[unit]) + fresh;
-    }
-    if (tid < D) {
-        if (chunk > 0 && r0 >= t0 && rb - r0 < kChunk) ((bf16_t *)c.ck)[(size_t)unit * D + tid] = held_of(r0 - 1, tid);   // (the last chunk)
-        if (rb == n_k) ((bf16_t *)c.khat)[(size_t)unit * D + tid] = held_of(n_k - 1, tid);
-    }
-    __syncthreads();
-    // 2. a chunk completed by these rows is sealed, by the first wave of every 64 channels; the others start on the values
-    const bool seals = rb - r0 == kChunk;
-    if (seals && wave < D / 64) {
-        const bf16_t held = chunk > 0 ? held_of(r0 - 1, 64 * wave + lane) : (bf16_t)0;
-        const uint32_t n = build_runs(keys + 64 * wave, D, mask + 2 * wave, WPR, held, runs + wave * kHalfRoom);
-        if (lane == 0) len[wave] = n;
-    }
-    // 3. values: 16 rows of one channel are contiguous, in slot order (v16_index).  A group that starts with a new row is
-    //    written whole (rows past the end as zeros), one that starts with old rows only gets its new slots
-    const int first = seals ? D / 64 : 0, threads = 256 - 64 * first;
-    for (int i = tid - 64 * first; i >= 0 && i < (kChunk / 16) * D; i += threads) {
-        const int g0 = r0 + i / D * 16, ch = i % D;
-        if (g0 >= rb || g0 + 16 <= ra) continue;
-        if (g0 >= ra) {
-            uint32_t w[8];
-#pragma unroll
-            for (int slot = 0; slot < 16; ++slot) {
-                const int row = g0 + 8 * ((slot & 7) >> 2) + 4 * (slot >> 3) + (slot & 3);
-                const uint32_t v = row < rb ? vals[(row - r0) * D + ch] : 0u;
-                w[slot >> 1] = (slot & 1) ? w[slot >> 1] | (v << 16) : v;
-            }
-            u32x4 *dst = (u32x4 *)((bf16_t *)c.V + (((size_t)unit * (c.vrows >> 4) + (g0 >> 4)) * D + ch) * 16);
-            dst[0] = u32x4{w[0], w[1], w[2], w[3]};
-            dst[1] = u32x4{w[4], w[5], w[6], w[7]};
-        } else {
-            for (int row = ra; row < min(g0 + 16, rb); ++row)
-                ((bf16_t *)c.V)[v16_index(unit, c.vrows, D, row, ch)] = vals[(row - r0) * D + ch];
-        }
-    }
-    __syncthreads();
-    if (seals) store_runs<D, 256>(c, unit, chunk, runs, len);
+__global__ __launch_bounds__(256) void cache_fill_runs_kernel(CacheFill f) {
+    __shared__ __attribute__((aligned(16))) char lds[kFillLds<D>];
+    fill_chunk<D, 256>(f, (int)blockIdx.x, lds);
 }
 
 // The inverse of the hand-off, for a prefill that continues a cached sequence: rows 0 .. t0 - 1 of the cache
@@ -818,17 +651,19 @@ __global__ __launch_bounds__(64 * NW * (D / 64), 2) void decode_step_runs_kernel
 
 namespace da {
 
-void cache_fill_runs(da_cache *c, int t0, int n_k, const void *Knew, const void *Vnew, const void *Hnew, const uint32_t *Mnew,
-                     const uint64_t *nnz_new, const da_prefix *full, const NnzSum &sum, hipStream_t s) {
-    FullRows f = {};
-    if (full) f = FullRows{(bf16_t *)full->k, (bf16_t *)full->v, (bf16_t *)full->h, full->m, c->max_seq};
-    const dim3 grid((n_k + kChunk - 1) / kChunk - t0 / kChunk, c->B * c->Hkv);
-    if (c->d == 64)
-        hipLaunchKernelGGL(cache_fill_runs_kernel<64>, grid, dim3(256), 0, s, (const bf16_t *)Knew, (const bf16_t *)Vnew,
-                           (const bf16_t *)Hnew, Mnew, nnz_new, sum, *c, f, t0, n_k);
+CacheFill cache_fill(const da_cache *c, int t0, int n_k, int ld, const void *K, const void *V, const void *H, const uint32_t *Mnew, uint32_t *Mall,
+                     const uint64_t *nnz_new, const NnzSum &sum) {
+    CacheFill f = {(const bf16_t *)K, (const bf16_t *)V, (const bf16_t *)H, Mnew, Mall, nnz_new, sum, *c, ld, t0, n_k, 0, 0};
+    f.units = c->B * c->Hkv;
+    f.items = ((n_k + kChunk - 1) / kChunk - t0 / kChunk) * f.units;
+    return f;
+}
+
+void launch_cache_fill(const CacheFill &f, hipStream_t s) {
+    if (f.cache.d == 64)
+        hipLaunchKernelGGL(cache_fill_runs_kernel<64>, dim3(f.items), dim3(256), 0, s, f);
     else
-        hipLaunchKernelGGL(cache_fill_runs_kernel<128>, grid, dim3(256), 0, s, (const bf16_t *)Knew, (const bf16_t *)Vnew,
-                           (const bf16_t *)Hnew, Mnew, nnz_new, sum, *c, f, t0, n_k);
+        hipLaunchKernelGGL(cache_fill_runs_kernel<128>, dim3(f.items), dim3(256), 0, s, f);
 }
 
 void expand_cache_runs(da_cache *c, int t0, int ld, void *Kfull, void *Hfull, void *Vfull, uint32_t *Mfull,

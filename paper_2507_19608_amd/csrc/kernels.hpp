@@ -47,7 +47,16 @@ struct PrefillArgs {
     uint32_t *queue;      // (matrix-core path) kPrefillQueueBytes, zeroed
     NnzSum sum;           // to be added up on the way
 };
+struct CacheFill;         // (cache.hpp)
 constexpr int kPrefillQueueBytes = 512;
+
+// Rows of a piece of a longer sequence that join arrays with `ld` rows of room per unit: src[k] [units][rows][..] to dst[k], which points at the first
+// unit's first new row.  In pieces of 16 bytes, `pieces` a row; sources may start anywhere.
+struct RowCopy {
+    const void *src[2];
+    void *dst[2];
+    int units, rows, ld, pieces;
+};
 
 void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s);
 
@@ -55,8 +64,9 @@ void launch_fill_u64(uint64_t *p, uint64_t v, int n, hipStream_t s);
 // add up (NnzSum; launch_nnz_sum, where no other launch takes it along); init: NULL (row 0 is the basis row), or [units][d], the
 // reference key the rows continue from; zeroed: NULL, or kPrefillQueueBytes to clear for the attention launch that follows
 size_t delta_scan_scratch_bytes(int dtype, int units, int n, int d);
+// copy: rows that the launch copies beside the scan, and Khat's room (NULL: none, n rows)
 NnzSum launch_delta_scan(int dtype, const void *K, void *Khat, uint32_t *mask_bits, void *scratch, uint32_t *counts, uint64_t *nnz,
-                         int units, int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed);
+                         int units, int n, int d, float theta, hipStream_t s, const void *init, uint32_t *zeroed, const RowCopy *copy = nullptr);
 void launch_nnz_sum(const NnzSum &sum, hipStream_t s);
 bool delta_scan_settles(int dtype, int units, int n, int d);   // without `counts` a second launch follows
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
@@ -66,7 +76,9 @@ bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);
 bool prefill_mfma_supported(const PrefillArgs &a);
 // K and V that are not are copied to room_k, room_v (`bytes` each, aligned), which take their place in `a`.
 void launch_copy_aligned(PrefillArgs &a, void *room_k, void *room_v, size_t bytes, hipStream_t s);
-void launch_prefill_mfma(const PrefillArgs &a, hipStream_t s);
+// fill: NULL, or a hand-off whose items the launch takes along; not where prefill_takes_fill says that a launch of its own is faster.
+void launch_prefill_mfma(const PrefillArgs &a, const CacheFill *fill, hipStream_t s);
+bool prefill_takes_fill(const PrefillArgs &a, const CacheFill &fill);
 // Scan and attention in one launch, of prompts whose rows fit into LDS: bf16, head_dim 64 or 128.  K and V have to be aligned to 16
 // bytes when it is launched.  khat: NULL, or [units][n][d] for the reference keys; a.Khat, a.queue and a.sum are not for it.
 bool prefill_short_supported(const PrefillArgs &a);

@@ -57,6 +57,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "cache_fill.hpp"
 #include "common.hpp"
 #include "kernels.hpp"
 #include "mfma.hpp"
@@ -87,6 +88,7 @@ struct MfmaArgs {
     Divisor by_units, by_parts;         // batch x KV heads; what an XCD has of them, or of their parts (see the kernel)
     int xsplit_log2;                    // >= 0: XCD-aware order, every unit split 2^this many ways
     int blocks, turn_at;                // tiles of the launch; where their order turns (see prefill_mfma_kernel)
+    int total;                          // tiles and, behind them, items of a hand-off to a cache
     uint32_t *queue;                    // [8] counters, kQueueStride apart, zero at the start: tiles handed out beyond the first of each work group
     float scale_log2;
     NnzSum sum;
@@ -459,7 +461,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     auto packed = [](const f32x16 &o, int q4, float inv) {
         return u32x2{pack_bf16x2(o[4 * q4 + 0] * inv, o[4 * q4 + 1] * inv), pack_bf16x2(o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv)};
     };
-    const int queues = a.xsplit_log2 >= 0 ? 8 : 1, blocks = a.blocks, end = a.kinds[kSplit - 1].end;
+    const int queues = a.xsplit_log2 >= 0 ? 8 : 1, total = a.total, end = a.kinds[kSplit - 1].end;
     uint32_t *const queue = a.queue + (pos & (queues - 1)) * kQueueStride;
     const int handed_out = (int)gridDim.x + (pos & (queues - 1));
     // the counts that the scan has left, by a wave that waits for its first loads meanwhile (positions from the queue are larger), and
@@ -472,16 +474,16 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         for (int u = (int)(gridDim.x - 1 - blockIdx.x); u < sum.units; u += 8 * (int)gridDim.x)
             add_up_nnz(sum, u + (lane >> 3) * (int)gridDim.x);
     };
-    const bool asks = blocks > (int)gridDim.x;
+    const bool asks = total > (int)gridDim.x;
     uint32_t ticket = 0;
     // Wave 0 asks for the next tile; in asm, so that nobody waits for the answer (2 us) before it is needed.
     auto ask = [&]() __attribute__((always_inline)) {
         if (asks && wave == 0 && lane_here() == 0)
             asm volatile("s_nop 4\n\tglobal_atomic_add %0, %1, %2, %3 sc0" : "+v"(ticket) : "v"(0), "v"(1), "s"(queue) : "memory");
     };
-    // ... and tells the others, once it has waited for the answer; `blocks`: there is none
+    // ... and tells the others, once it has waited for the answer; `total`: there is none
     auto tell = [&]() __attribute__((always_inline)) {
-        if (wave == 0 && lane_here() == 0) *next_tile = asks ? handed_out + queues * (int)ticket : blocks;
+        if (wave == 0 && lane_here() == 0) *next_tile = asks ? handed_out + queues * (int)ticket : total;
     };
     auto told = [&]() __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*next_tile); };
 
@@ -612,7 +614,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         wait_loads<0>();                                         // no load into LDS outlives the work group
         const float inv = 1.f / row_sum();
         if (taken < n) store_rows(out_rows, wave_first, inv);
-        return blocks;
+        return told();
     } else {
         auto vector_phase = [&](int turn) __attribute__((always_inline)) {
             if (kSplit == 1 && grp == 1) wait_loads<0>();        // key tile turn + 1, value tile turn, which group A is about to read
@@ -742,13 +744,35 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 // units cut by tile index modulo 2^xsplit_log2 - deal out evenly, an XCD keeps to its own, with a counter of its own.
 // Where all tiles are resident at once, two to a compute unit, the second ones come in ascending order, so that short ones share
 // with long ones.
-template <int D, bool kStream>
-__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(MfmaArgs a) {
+// Behind the tiles come the chunks that a cache is handed (fill_chunk), for whoever is done with the tiles or has none: a piece of a
+// prompt, or a short one, leaves compute units idle, and the hand-off's own launch took 9 us of each.
+// (kernels of their own: with the look for such a chunk at its end every other launch took 0.5 to 1 us longer.)
+template <int D, bool kStream, typename... Fill>                 // Fill: CacheFill, or nothing
+__global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(MfmaArgs a, Fill...) {
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
     int pos = blockIdx.x;
-    if (pos >= a.turn_at) pos = a.blocks - 8 - ((pos - a.turn_at) & ~7) + (pos & 7);
+    if (pos >= a.turn_at && pos < a.blocks) pos = a.blocks - 8 - ((pos - a.turn_at) & ~7) + (pos & 7);
     if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2, false>(a, pos, lds_raw);
-    if (pos < a.kinds[0].end) tiles_of_kind<D, 1, kStream>(a, pos, lds_raw);
+    if (pos < a.kinds[0].end) pos = tiles_of_kind<D, 1, kStream>(a, pos, lds_raw);
+    if constexpr (sizeof...(Fill) == 0) return;
+    // (the arguments of what follows are read here: in registers from the start on they would push others out across the walk)
+    typedef const __attribute__((address_space(4))) char arg_char;
+    auto *args = (arg_char *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(args));
+    const auto &b = *(const __attribute__((address_space(4))) MfmaArgs *)args;
+    static_assert(sizeof(MfmaArgs) % alignof(CacheFill) == 0, "the second argument follows the first");
+    const auto &fill = *(const __attribute__((address_space(4))) CacheFill *)(args + sizeof(MfmaArgs));
+    static_assert(kFillLds<D> <= 4 * KB * 2 * D * 2, "the room of the tiles");
+    int *const next = (int *)(lds_raw + 4 * KB * 2 * D * 2);
+    while (pos < b.total) {
+        __syncthreads();                                         // the LDS is free
+        if (threadIdx.x == 0) {
+            const int queues = b.xsplit_log2 >= 0 ? 8 : 1, mine = pos & (queues - 1);
+            *next = b.total > (int)gridDim.x ? (int)gridDim.x + mine + queues * (int)atomicAdd(b.queue + mine * kQueueStride, 1u) : b.total;
+        }
+        fill_chunk<D, 512>(fill, pos - b.blocks, lds_raw);
+        pos = *next;
+    }
 }
 
 // Loads straight into LDS want aligned rows; a tensor that does not start on 16 bytes (a slice of a larger one) is laid out
@@ -773,8 +797,14 @@ __global__ __launch_bounds__(256) void copy_aligned_kernel(CopyPair c, size_t pi
         if (i0 + k * 256 < pieces) dst[i0 + k * 256] = v[k];
 }
 
+// as many work groups as are resident at once: one per compute unit, at head_dim 64 two (64 KB of LDS, 128 registers)
+int resident(int d) {
+    const int cus = device_cu_count() >= 8 ? device_cu_count() & ~7 : 8;
+    return d == 64 ? 2 * cus : cus;
+}
+
 template <int D>
-void launch_d(const PrefillArgs &p, hipStream_t s) {
+void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     MfmaArgs a;
     a.Q = (const bf16_t *)p.Q;
     a.K = (const bf16_t *)p.K;
@@ -799,8 +829,7 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     a.by_hgroups = divisor(hgroups);
     a.by_w = divisor(p.W);
     a.by_units = divisor(units);
-    // as many work groups as are resident at once: one per compute unit, at head_dim 64 two (64 KB of LDS, 128 registers)
-    const int cus = device_cu_count() >= 8 ? device_cu_count() & ~7 : 8, slots = D == 64 ? 2 * cus : cus;
+    const int slots = resident(D), cus = D == 64 ? slots / 2 : slots;
     // XCD-aware order needs units * 2^xsplit parts to deal out evenly over 8 XCDs and a unit's tiles, of either kind, to split
     // evenly
     int xsplit = 0;
@@ -888,6 +917,7 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
         }
     }
     a.blocks = a.kinds[0].end;
+    a.total = a.blocks + (fill ? fill->items : 0);
     const bool ordered = a.xsplit_log2 >= 0;
     if (ordered) a.by_parts = divisor((units << xsplit) / 8);
     a.turn_at = D == 64 && a.blocks > cus && a.blocks <= slots && ordered ? cus : a.blocks;
@@ -901,10 +931,17 @@ void launch_d(const PrefillArgs &p, hipStream_t s) {
     // 4 x 4096 306 / 306).
     const int64_t whole_tiles = (int64_t)columns * a.kinds[0].tiles;
     const bool stream = D == 128 && (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
+    const dim3 grid(a.total < slots ? a.total : slots), block(512);
+    static std::atomic<uint64_t> lds_set[4];                     // per instantiation, one bit per device
+    if (fill) {
+        const auto kernel = stream ? prefill_mfma_kernel<D, D == 128, CacheFill> : prefill_mfma_kernel<D, false, CacheFill>;
+        ensure_dynamic_lds((const void *)kernel, lds, lds_set[2 + stream]);
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, a, *fill);
+        return;
+    }
     const auto kernel = stream ? prefill_mfma_kernel<D, D == 128> : prefill_mfma_kernel<D, false>;
-    static std::atomic<uint64_t> lds_set[2];                     // per instantiation, one bit per device
     ensure_dynamic_lds((const void *)kernel, lds, lds_set[stream]);
-    hipLaunchKernelGGL(kernel, dim3(a.blocks < slots ? a.blocks : slots), dim3(512), lds, s, a);
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, a);
 }
 
 }  // namespace
@@ -930,11 +967,18 @@ void launch_copy_aligned(PrefillArgs &a, void *room_k, void *room_v, size_t byte
     hipLaunchKernelGGL(copy_aligned_kernel, dim3((unsigned)((pieces + 1023) / 1024), count), dim3(256), 0, s, c, pieces);
 }
 
-void launch_prefill_mfma(const PrefillArgs &p, hipStream_t s) {
+void launch_prefill_mfma(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     if (p.d == 64)
-        launch_d<64>(p, s);
+        launch_d<64>(p, fill, s);
     else
-        launch_d<128>(p, s);
+        launch_d<128>(p, fill, s);
 }
+
+// A chunk by an attention launch's work groups, two of which at most share a compute unit, takes longer than by six small ones of a launch of its own; what
+// that launch costs is its start and end.  In that launch / this one, us a call (prompt, hand-off, one decode step) at items per resident work group:
+// 32 / 8 heads of 64, 1 x 512 tokens 0.1 31.3 / 25.9, 4 x 512 0.5 39.0 / 36.7, 2 x 8192 of 16 / 2 1 338 / 326, 16 x 600 2.5 77.3 / 76.1, 32 x 1024 8 242 / 254; 20 / 5 heads
+// of 128, 1 x 512 0.2 36.7 / 30.1, 8 x 500 1.3 55.5 / 49.8, 4 x 2048 2.5 135 / 129, 1 x 8192 2.5 352 / 340, 32 x 300 of 8 / 8 heads 3.1 89.9 / 95.3, 16 x 1024 5 168 / 170, 4 x
+// 6000 7.3 676 / 682.
+bool prefill_takes_fill(const PrefillArgs &p, const CacheFill &fill) { return 2 * (int64_t)fill.items <= 5 * (int64_t)resident(p.d); }
 
 }  // namespace da
