@@ -236,8 +236,8 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
     a.V = V;
     a.Khat = khat;
     a.O = O;
-    const bool in_one = prefill_short_supported(a);
-    if (!in_one) {
+    const bool in_one = prefill_short_supported(a), scans = !in_one && !cache && prefill_generic_scans(a);   // (a cache wants the reference keys)
+    if (!in_one && !scans) {
         stage_begin(kStageScan, s);
         a.queue = p->head_dim >= 64 ? (uint32_t *)(ws + w.queue) : nullptr;  // (32: another kernel, and less room)
         a.sum = launch_delta_scan(p->dtype, K, khat, mask_bits, ws + w.scan, w.counts ? (uint32_t *)(ws + w.counts) : nullptr, nnz, units,
@@ -259,8 +259,10 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
             if (filled) a.sum = NnzSum{};                            // (the hand-off adds up)
             launch_prefill_mfma(a, filled ? &fill : nullptr, s);
         }
-    } else
-        launched = launch_prefill_generic(a, s);
+    } else {
+        const PrefillScan scan = {mask_bits, nnz, p->theta};
+        launched = launch_prefill_generic(a, scans ? &scan : nullptr, s);
+    }
     stage_end(kStageAttn, s);
     if (!launched) return DA_ERR_UNSUPPORTED;
     if (!launch_ok("prefill attention")) return DA_ERR_HIP;

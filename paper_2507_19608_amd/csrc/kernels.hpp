@@ -71,7 +71,15 @@ void launch_nnz_sum(const NnzSum &sum, hipStream_t s);
 bool delta_scan_settles(int dtype, int units, int n, int d);   // without `counts` a second launch follows
 // Generic path: any head_dim in {32, 64, ..., 256}, both dtypes, binary32 products.  Returns false if the head_dim has
 // no instantiation.  q_off and ld are not for it.
-bool launch_prefill_generic(const PrefillArgs &a, hipStream_t s);
+// scan: NULL, or what the scan of the keys is to write, which the launch then does itself (a.Khat and a.sum are not for it); only where
+// prefill_generic_scans says so.
+struct PrefillScan {
+    uint32_t *mask_bits;
+    uint64_t *nnz;
+    float theta;
+};
+bool prefill_generic_scans(const PrefillArgs &a);
+bool launch_prefill_generic(const PrefillArgs &a, const PrefillScan *scan, hipStream_t s);
 // Matrix-core path: bf16, head_dim 64 or 128.  K and V have to be aligned to 16 bytes when it is launched.
 bool prefill_mfma_supported(const PrefillArgs &a);
 // K and V that are not are copied to room_k, room_v (`bytes` each, aligned), which take their place in `a`.

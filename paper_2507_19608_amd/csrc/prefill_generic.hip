@@ -10,7 +10,11 @@
 // (a numerics user's single head of a few hundred rows), so what bounds it is how many waves there are and how long the
 // longest one walks: a wave per 64 rows that walked every key took 725 us on 256 rows of one head of 64 (4 waves on the
 // chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each: 6.8 us, 16.0 for the whole
-// call with the scan.
+// call with a scan in front, which two launches on the host bound, and 12.7 where it is part of the launch.
+//
+// kScans: the keys left of a work group's windows fit into its LDS, so it takes them in and makes them reference keys there for itself
+// (Eq. 2-3), and no launch and no pass through memory comes in front; one more work group per unit writes the mask.  (A block's values
+// and window keys asked for in front of the scan: 11.6 / 11.6 us at 256 rows of 64, 13.4 / 15.0 at 128 of 128, which then spills.)
 //
 // Matrix-core layout (16x16x4, wave64): A lane l holds row l % 16, k = l / 16; B lane l column l % 16, same k; D lane l
 // column l % 16, rows 4 (l / 16) + r.  Scores are taken transposed (keys x query rows): a lane owns one query row, and
@@ -42,6 +46,9 @@ struct KArgs {
     int Hq, Hkv, n, W, sliding;
     float scale_log2;
     NnzSum sum;
+    uint32_t *__restrict__ mask_bits;            // from here on: kScans
+    uint64_t *__restrict__ nnz;
+    float theta;
 };
 
 __device__ __forceinline__ f32x4 load4(const float *p) { return *(const f32x4 *)p; }
@@ -55,7 +62,116 @@ __device__ __forceinline__ f32x2 load2(const bf16_t *p) {
     return f32x2{bf16_to_f32(v[0]), bf16_to_f32(v[1])};
 }
 
-template <typename T, int D>
+// LDS of a work group that scans n rows: these, four floats apart so that 16 rows' reads of one segment lie in different banks; what the runs end
+// on; three words
+constexpr size_t scan_lds(int n, int d) { return ((size_t)n * (d + 4) + 2 * 64 * kWavesG + 4) * sizeof(float); }
+
+// The reference keys of a unit's rows 0 .. n - 1, in LDS [n][D + 4].  A thread walks a run of rows in two neighbouring channels, from the guess "held
+// = the row before" kWarm rows earlier; runs whose start is not what the run before has ended on walk again, in rounds, and one last walk puts reference
+// keys in the place of keys (as scan_whole_kernel does).
+template <int D>
+__device__ __forceinline__ void scan_rows(const float *__restrict__ K, int n, float theta, float *rows) {
+    constexpr int S = D + 4, PR = D / 2, kRuns = 64 * kWavesG / PR, kWarm = 48, N = 8;
+    float2 *const E = (float2 *)(rows + (size_t)n * S);
+    int *const flags = (int *)(E + 64 * kWavesG);                // [2] some run was wrong in an even, odd round
+    const int tid = threadIdx.x;
+    {
+        const int pieces = n * (D / 4);
+        for (int i0 = tid; i0 < pieces; i0 += N * 64 * kWavesG) {
+            f32x4 v[N];
+#pragma unroll
+            for (int k = 0; k < N; ++k) v[k] = load4(K + 4 * (size_t)min(i0 + k * 64 * kWavesG, pieces - 1));
+#pragma unroll
+            for (int k = 0; k < N; ++k) {                        // (pieces past the end are the last one again)
+                const int i = min(i0 + k * 64 * kWavesG, pieces - 1);
+                *(f32x4 *)(rows + i / (D / 4) * S + i % (D / 4) * 4) = v[k];
+            }
+        }
+        if (tid < 2) flags[tid] = 0;
+    }
+    __syncthreads();
+    const int run = tid / PR, p = tid % PR, L = (n + kRuns - 1) / kRuns;
+    const int a = run * L, b = min(a + L, n);
+    const bool works = a < n;
+    float *const mine = rows + 2 * p;
+    // rows t .. end - 1 in order from `held`; with `write` they become what is held
+    auto walk = [&](int t, int end, float2 held, bool write) __attribute__((always_inline)) {
+        float2 k[N], next[N];
+        auto fetch = [&](float2 (&x)[N], int from) {
+#pragma unroll
+            for (int u = 0; u < N; ++u) x[u] = *(const float2 *)(mine + min(from + u, n - 1) * S);
+        };
+        fetch(k, t);
+        for (; t < end; t += N) {
+            fetch(next, t + N);
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const bool here = t + u < end;
+                held.x = here && fabsf(k[u].x - held.x) > theta ? k[u].x : held.x;          // Eq. 2 in binary32, Eq. 3
+                held.y = here && fabsf(k[u].y - held.y) > theta ? k[u].y : held.y;
+                if (write && here) *(float2 *)(mine + (t + u) * S) = held;
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) k[u] = next[u];
+        }
+        return held;
+    };
+    float2 start = {0.f, 0.f};
+    if (works) {
+        const int w = max(a - kWarm, 0);                         // (row 0 is the basis row: exact)
+        start = walk(w, a, *(const float2 *)(mine + max(w - 1, 0) * S), false);
+        E[tid] = walk(a, b, start, false);
+    }
+    __syncthreads();
+    for (int round = 0; round < kRuns; ++round) {
+        float2 from = start;
+        if (works && run > 0) from = E[tid - PR];
+        const bool wrong = __float_as_uint(from.x) != __float_as_uint(start.x) || __float_as_uint(from.y) != __float_as_uint(start.y);
+        if (__any(wrong) && (tid & 63) == 0) flags[round & 1] = 1;
+        __syncthreads();                                         // (also: every run has read the end of the one before)
+        if (!flags[round & 1]) break;
+        if (tid == 0) flags[(round + 1) & 1] = 0;
+        if (wrong) {
+            start = from;
+            E[tid] = walk(a, b, start, false);
+        }
+        __syncthreads();
+    }
+    if (works) walk(a, b, start, true);
+    __syncthreads();
+}
+
+// Mask words and count of a unit whose reference keys lie in LDS: an entry has fired where a row differs from the one before (it fires only if |k -
+// held| > theta >= 0, and then holds k).
+template <int D>
+__device__ __forceinline__ void write_mask(const float *rows, int n, uint32_t *__restrict__ mask, uint64_t *__restrict__ nnz) {
+    constexpr int S = D + 4, WPR = D / 32;
+    uint32_t *const total = (uint32_t *)(rows + (size_t)n * S + 2 * 64 * kWavesG) + 2;
+    if (threadIdx.x == 0) *total = 0;
+    __syncthreads();
+    uint32_t fired = 0;
+    for (int i = threadIdx.x; i < n * WPR; i += 64 * kWavesG) {
+        const int t = i / WPR, w = i % WPR;
+        const float *x = rows + t * S + 32 * w, *y = x - (t > 0 ? S : 0);
+        uint32_t bits = 0;
+#pragma unroll
+        for (int c = 0; c < 32; c += 4) {
+            const f32x4 u = *(const f32x4 *)(x + c), v = *(const f32x4 *)(y + c);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bits |= (uint32_t)(__float_as_uint(u[e]) != __float_as_uint(v[e])) << (c + e);
+        }
+        if (t == 0) bits = ~0u;                                  // the basis row is kept whole
+        mask[i] = bits;
+        fired += (uint32_t)__popc(bits);
+    }
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) fired += __shfl_xor(fired, s);
+    if ((threadIdx.x & 63) == 0) atomicAdd(total, fired);
+    __syncthreads();
+    if (threadIdx.x == 0) *nnz = *total;
+}
+
+template <typename T, int D, bool kScans>
 __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> a) {
     constexpr int VW = D % 64 == 0 ? 4 : 2;      // channels a lane loads and stores at a time
     constexpr int CG = D / (16 * VW);            // channel groups of the output
@@ -68,11 +184,19 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l16 = lane & 15, lg = lane >> 4;
     const int n = a.n, W = a.W;
-    const int tile = (int)gridDim.x - 1 - (int)blockIdx.x;       // longest rows first
+    const int tile = (int)gridDim.x - 1 - (int)blockIdx.x;       // longest rows first; kScans: in front of them the mask
     const int i0 = tile * kRowsG, i_last = min(n - 1, i0 + kRowsG - 1);
     const int h = blockIdx.y, b = blockIdx.z;
     const int unit = b * a.Hkv + h / (a.Hq / a.Hkv);
-    if (wave == kWavesG - 1 && tile == 0 && h % (a.Hq / a.Hkv) == 0 && a.sum.groups > 0)      // (the shortest rows)
+    if constexpr (kScans) {
+        if (i0 >= n) {
+            if (h % (a.Hq / a.Hkv) != 0) return;
+            scan_rows<D>(a.K + (size_t)unit * n * D, n, a.theta, lds_g);
+            write_mask<D>(lds_g, n, a.mask_bits + (size_t)unit * n * (D / 32), a.nnz + unit);
+            return;
+        }
+    }
+    if (!kScans && wave == kWavesG - 1 && tile == 0 && h % (a.Hq / a.Hkv) == 0 && a.sum.groups > 0)      // (the shortest rows)
         add_up_nnz(a.sum, lane < 8 ? unit : a.sum.units);
     const T *Qp = a.Q + (size_t)(b * a.Hq + h) * n * D;
     const T *Kp = a.K + (size_t)unit * n * D;
@@ -87,6 +211,11 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
 #pragma unroll
     for (int s = 0; s < KS; ++s) q[s] = load4(Qp + (size_t)my_row * D + 16 * s + 4 * lg);
 
+    if constexpr (kScans)
+        if (win_last > 0) scan_rows<D>(Kp, win_last, a.theta, lds_g);
+    const int hat_rows = kScans ? win_last : n, hat_stride = kScans ? D + 4 : D;
+    const T *const hats = kScans ? (const T *)lds_g : Hp;
+
     f32x4 o[CG][VW];
     float m = -INFINITY, l = 0.f;
 #pragma unroll
@@ -97,9 +226,9 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
     for (int jb = wave * kKeys; jb <= i_last; jb += kWavesG * kKeys) {
         // scores of the block: X = K, or K_hat where every row has the block left of its window
         f32x4 s[2];
-        auto scores = [&](const T *X, f32x4 (&acc)[2]) {
-            const T *x0 = X + (size_t)min(jb + l16, n - 1) * D + 4 * lg;
-            const T *x1 = X + (size_t)min(jb + 16 + l16, n - 1) * D + 4 * lg;
+        auto scores = [&](const T *X, int rows, int stride, f32x4 (&acc)[2]) __attribute__((always_inline)) {
+            const T *x0 = X + (size_t)min(jb + l16, rows - 1) * stride + 4 * lg;
+            const T *x1 = X + (size_t)min(jb + 16 + l16, rows - 1) * stride + 4 * lg;
             acc[0] = acc[1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int g = 0; g < KS; ++g) {
@@ -112,10 +241,17 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
             }
         };
         const bool far = jb + kKeys <= win_first;
-        scores(far ? Hp : Kp, s);
+        if constexpr (kScans) {                  // (from different memories)
+            if (far)
+                scores((const T *)lds_g, hat_rows, hat_stride, s);
+            else
+                scores(Kp, n, D, s);
+        } else {
+            scores(far ? Hp : Kp, n, D, s);
+        }
         if (!far && jb < win_last) {             // some row has part of the block left of its window
             f32x4 sh[2];
-            scores(Hp, sh);
+            scores(hats, hat_rows, hat_stride, sh);
 #pragma unroll
             for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
@@ -170,6 +306,7 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
     }
 
     // the waves' partial results meet: row maxima and sums first, then the outputs at the common maximum
+    if constexpr (kScans) __syncthreads();       // (the reference keys lay there)
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
     if (lg == 0) {
@@ -207,8 +344,11 @@ __global__ __launch_bounds__(64 * kWavesG) void prefill_generic_kernel(KArgs<T> 
 }
 
 template <typename T, int D>
-void launch_one(const PrefillArgs &p, hipStream_t s) {
-    KArgs<T> a;
+constexpr size_t merge_lds = (size_t)kWavesG * 16 * (D + 6) * sizeof(float);
+
+template <typename T, int D>
+void launch_one(const PrefillArgs &p, const PrefillScan *scan, hipStream_t s) {
+    KArgs<T> a = {};
     a.Q = (const T *)p.Q;
     a.K = (const T *)p.K;
     a.V = (const T *)p.V;
@@ -221,33 +361,54 @@ void launch_one(const PrefillArgs &p, hipStream_t s) {
     a.sliding = p.sliding;
     a.scale_log2 = p.scale_log2;
     a.sum = p.sum;
+    if constexpr (sizeof(T) == 4 && (D == 64 || D == 128)) {
+        if (scan) {
+            a.mask_bits = scan->mask_bits;
+            a.nnz = scan->nnz;
+            a.theta = scan->theta;
+            const size_t rows = scan_lds(p.n, D), lds = rows > merge_lds<T, D> ? rows : merge_lds<T, D>;
+            static std::atomic<uint64_t> set;   // one bit per device
+            ensure_dynamic_lds((const void *)prefill_generic_kernel<T, D, true>, 160 * 1024, set);
+            static_assert(scan_lds(32768 / D, D) <= 160 * 1024, "prefill_generic_scans");
+            hipLaunchKernelGGL((prefill_generic_kernel<T, D, true>), dim3((p.n + 15) / 16 + 1, p.Hq, p.B), dim3(64 * kWavesG), lds, s, a);
+            return;
+        }
+    }
     // (32 rows per work group, which halve the reads of K and V per row, took longer: fp32, 8 heads of 64, 2048 tokens 97.6 us
     // against 85.3, 8 heads of 128 182 against 152; bf16, 4 x 1000 tokens, 20 / 5 heads of 96 344 against 226.)
-    constexpr size_t lds = (size_t)kWavesG * 16 * (D + 6) * sizeof(float);
     static std::atomic<uint64_t> lds_set;   // per instantiation, one bit per device
-    ensure_dynamic_lds((const void *)prefill_generic_kernel<T, D>, (int)lds, lds_set);
-    hipLaunchKernelGGL((prefill_generic_kernel<T, D>), dim3((p.n + 15) / 16, p.Hq, p.B), dim3(64 * kWavesG), lds, s, a);
+    ensure_dynamic_lds((const void *)prefill_generic_kernel<T, D, false>, (int)merge_lds<T, D>, lds_set);
+    hipLaunchKernelGGL((prefill_generic_kernel<T, D, false>), dim3((p.n + 15) / 16, p.Hq, p.B), dim3(64 * kWavesG), (merge_lds<T, D>), s, a);
 }
 
 template <typename T>
-bool launch_by_dim(const PrefillArgs &p, hipStream_t s) {
+bool launch_by_dim(const PrefillArgs &p, const PrefillScan *scan, hipStream_t s) {
     switch (p.d) {
-        case 32: launch_one<T, 32>(p, s); return true;
-        case 64: launch_one<T, 64>(p, s); return true;
-        case 96: launch_one<T, 96>(p, s); return true;
-        case 128: launch_one<T, 128>(p, s); return true;
-        case 160: launch_one<T, 160>(p, s); return true;
-        case 192: launch_one<T, 192>(p, s); return true;
-        case 224: launch_one<T, 224>(p, s); return true;
-        case 256: launch_one<T, 256>(p, s); return true;
+        case 32: launch_one<T, 32>(p, scan, s); return true;
+        case 64: launch_one<T, 64>(p, scan, s); return true;
+        case 96: launch_one<T, 96>(p, scan, s); return true;
+        case 128: launch_one<T, 128>(p, scan, s); return true;
+        case 160: launch_one<T, 160>(p, scan, s); return true;
+        case 192: launch_one<T, 192>(p, scan, s); return true;
+        case 224: launch_one<T, 224>(p, scan, s); return true;
+        case 256: launch_one<T, 256>(p, scan, s); return true;
         default: return false;
     }
 }
 
 }  // namespace
 
-bool launch_prefill_generic(const PrefillArgs &p, hipStream_t s) {
-    return p.dtype == 0 ? launch_by_dim<float>(p, s) : launch_by_dim<bf16_t>(p, s);
+// Every work group then scans the keys of its unit anew, beside the others as long as each has a compute unit; the scan's own launch spreads over more of them.
+// fp32, a scan in front / in the same launch, us a call: 1 head of 64, 64 tokens 11.0 / 9.8, 256 12.6 / 11.5 (buffers left to the binding, which the host
+// bounds, 16.0 / 12.7), 400 15.4 / 15.2, 580 18.7 / 19.1; 2 x 200, 4 heads 13.1 / 12.2; 2 x 256, 8 heads (272 work groups) 13.4 / 18.2; 1 head of 128, 128
+// tokens 14.5 / 13.4, 290 21.3 / 21.2; 8 x 200 of 8 / 8 heads 40 / 63.
+bool prefill_generic_scans(const PrefillArgs &p) {
+    return p.dtype == 0 && (p.d == 64 || p.d == 128) && (int64_t)p.n * p.d <= 32768 &&
+           (int64_t)p.B * p.Hq * ((p.n + 15) / 16 + 1) <= device_cu_count();
+}
+
+bool launch_prefill_generic(const PrefillArgs &p, const PrefillScan *scan, hipStream_t s) {
+    return p.dtype == 0 ? launch_by_dim<float>(p, scan, s) : launch_by_dim<bf16_t>(p, scan, s);
 }
 
 }  // namespace da
