@@ -31,7 +31,7 @@ static_assert(kHalfRoom == kHead + (kChunk + 1) * 64 && kHalfRoom % 8 == 0, "16-
 // {reference value held before the chunk, then its surviving values in row order}.  From the chunk's keys (row stride d) and
 // mask rows in LDS into LDS; returns the number of elements.
 __device__ __forceinline__ uint32_t build_runs(const bf16_t *keys, int d, const uint32_t *mask, int wpr, bf16_t held, bf16_t *room) {
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = lane_id();
     uint32_t lo = 0, hi = 0;                                     // the channel's mask bits of rows 0..31, 32..63
 #pragma unroll 16
     for (int r = 0; r < 32; ++r) {
@@ -59,13 +59,13 @@ __device__ __forceinline__ uint32_t build_runs(const bf16_t *keys, int d, const 
 // sealed channels in LDS [D / 64][kHalfRoom] -> the chunk's room, 16-byte pieces (the last one may carry a few elements nobody
 // reads)
 template <int D, int NT, typename Cache>
-__device__ __forceinline__ void store_runs(const Cache &c, int unit, int chunk, const bf16_t *runs, const uint32_t *len) {
+__device__ __forceinline__ void store_runs(const Cache &c, int unit, int chunk, const bf16_t *runs, const uint32_t *len, int tid) {
     for (int h = 0; h < D / 64; ++h) {
         u32x4 *dst = (u32x4 *)(run_room(c, unit, chunk) + h * kHalfRoom);
         const u32x4 *src = (const u32x4 *)(runs + h * kHalfRoom);
-        for (int i = threadIdx.x; i < (int)(len[h] + 7) / 8; i += NT) dst[i] = src[i];
+        for (int i = tid; i < (int)(len[h] + 7) / 8; i += NT) dst[i] = src[i];
     }
-    if (threadIdx.x == 0) c.ccnt[(size_t)unit * c.max_chunks + chunk] = len[0] | (D > 64 ? len[1] << 16 : 0u);
+    if (tid == 0) c.ccnt[(size_t)unit * c.max_chunks + chunk] = len[0] | (D > 64 ? len[1] << 16 : 0u);
 }
 
 // One chunk of one unit of a hand-off, by NT threads: rows t0 .. n_k - 1 (t0 = rows the cache already holds) are appended, item by item those
@@ -75,7 +75,7 @@ __device__ __forceinline__ void store_runs(const Cache &c, int unit, int chunk, 
 template <int D>
 constexpr int kFillLds = 2 * kChunk * D * 2 + D / 64 * kRunHalfRoom * 2 + kChunk * (D / 32) * 4 + 16;
 template <int D, int NT, typename Fill>                       // (CacheFill, in whichever address space)
-__device__ __forceinline__ void fill_chunk(const Fill &f, int item, char *lds) {
+__device__ __forceinline__ void fill_chunk(const Fill &f, int item, char *lds, int tid) {
     constexpr int WPR = D / 32, P = D / 8, kIn = kChunk * P / NT;
     bf16_t *const keys = (bf16_t *)lds, *const vals = keys + kChunk * D, *const runs = vals + kChunk * D;
     uint32_t *const mask = (uint32_t *)(runs + D / 64 * kHalfRoom), *const len = mask + kChunk * WPR;
@@ -83,7 +83,7 @@ __device__ __forceinline__ void fill_chunk(const Fill &f, int item, char *lds) {
     const auto &c = f.cache;
     const int t0 = f.t0, n_k = f.n_k, m = n_k - t0;
     const int at = item / f.units, unit = item - at * f.units, chunk = at + t0 / kChunk, r0 = chunk * kChunk;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int wave = tid >> 6, lane = tid & 63;
     const int ra = max(r0, t0), rb = min(r0 + kChunk, n_k);      // new rows of this chunk
     const size_t row0 = (size_t)unit * f.ld, new0 = (size_t)unit * m, cache0 = (size_t)unit * c.max_seq;
     auto held_of = [&](int row, int ch) { return f.H[(row0 + row) * D + ch]; };
@@ -156,7 +156,7 @@ __device__ __forceinline__ void fill_chunk(const Fill &f, int item, char *lds) {
         }
     }
     __syncthreads();
-    if (seals) store_runs<D, NT>(c, unit, chunk, runs, len);
+    if (seals) store_runs<D, NT>(c, unit, chunk, runs, len, tid);
 }
 
 }  // namespace da

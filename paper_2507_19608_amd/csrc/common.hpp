@@ -48,9 +48,12 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// the lane's number without the thread's, which a kernel then need not keep
+__device__ __forceinline__ int lane_id() { return (int)lanes_below(~0ull); }
+
 // exclusive prefix sum over the 64 lanes; *total receives the wave sum
 __device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t v, uint32_t *total) {
-    const int lane = threadIdx.x & 63;
+    const int lane = lane_id();
     uint32_t inc = v;
 #pragma unroll
     for (int s = 1; s < 64; s <<= 1) {
@@ -64,7 +67,7 @@ __device__ __forceinline__ uint32_t wave_exclusive_scan(uint32_t v, uint32_t *to
 // up to eight units' counts added up by a whole wave: `unit` is the one of a lane's eight lanes, or sum.units and more for none.  The first of the eight receives the
 // sum and has written it.
 __device__ __forceinline__ uint32_t add_up_nnz(const NnzSum &sum, int unit) {
-    const int lane = threadIdx.x & 7;
+    const int lane = lane_id() & 7;
     uint32_t v = 0;
     if (unit < sum.units)
         for (int k = lane; k < sum.groups; k += 8) v += sum.counts[(size_t)unit * sum.groups + k];

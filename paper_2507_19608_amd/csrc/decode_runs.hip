@@ -16,7 +16,6 @@ using namespace da;
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(16))) int i32x16;
 
@@ -46,14 +45,14 @@ __global__ __launch_bounds__(256) void seal_from_ring_kernel(da_cache c, int chu
         if ((tid & 63) == 0) len[wave] = n;
     }
     __syncthreads();
-    store_runs<D, 256>(c, unit, chunk, runs, len);
+    store_runs<D, 256>(c, unit, chunk, runs, len, tid);
 }
 
 // Hand-off of prefilled rows to the cache where no attention launch takes it along (cache_fill.hpp).
 template <int D>
 __global__ __launch_bounds__(256) void cache_fill_runs_kernel(CacheFill f) {
     __shared__ __attribute__((aligned(16))) char lds[kFillLds<D>];
-    fill_chunk<D, 256>(f, (int)blockIdx.x, lds);
+    fill_chunk<D, 256>(f, (int)blockIdx.x, lds, (int)threadIdx.x);
 }
 
 // The inverse of the hand-off, for a prefill that continues a cached sequence: rows 0 .. t0 - 1 of the cache

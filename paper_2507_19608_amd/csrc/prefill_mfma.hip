@@ -17,7 +17,7 @@
 // reads is two tiles, keys and values.
 //
 // What bounds it: matrix cores and vector ALU take turns.  A block of 64 keys costs a wave 1024 cycles of matrix work at
-// head_dim 128 (512 at 64) and about 690 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
+// head_dim 128 (512 at 64) and about 560 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
 // other takes exponentials.  The waves therefore run in two groups half a block apart (waves 0-3 and 4-7, one of each per
 // SIMD), handed from phase to phase by barriers:
 //     A: | PV(b-1) S(b) | softmax(b)   | PV(b) S(b+1) | ...
@@ -25,8 +25,9 @@
 // A wave in its matrix phase goes first (s_setprio): it issues one instruction in 32 clocks, and every one that has to wait for
 // the other wave's arithmetic lengthens the phase.  What is added to a matrix phase - addresses, loads, the look at the masks -
 // comes out at more than it saves in the vector phase: its instructions wait in order for whatever is issued between them.
-// Counters on 4 x 8192 tokens, 20 / 5 heads of 128: 2.08 M clocks a launch, 1610 a phase, of which one wave's matrix instructions
-// fill 1024 and the other wave's vector instructions 692.  With the priority the other way round, a branch and an address for every
+// Counters on 4 x 8192 tokens, 20 / 5 heads of 128: 1.92 M clocks a launch, 1490 a phase, of which one wave's matrix instructions
+// fill 1088 and the other wave's vector instructions 560; with row sums by dot products on the vector ALU and the maximum of every block 2.08 M and 1610
+// (692 of issue).  Before that, with the priority the other way round, a branch and an address for every
 // load, fmaxf, a wait where the next tile is asked for, a pause between tiles and queries and outputs in pieces it was 2.43 M; of 15 %
 // fewer clocks 7 % are left in time (1344 -> 1256 us a call, in turn on one card): the clock goes down under this load, to 1.7 of 2.4 GHz.
 //
@@ -95,7 +96,8 @@ struct MfmaArgs {
 };
 
 // The tiles of one kind: those at `pos` and the positions the queue hands out after it; returns the first of these past the
-// kind's end.  a: the kernel's argument, of which the walk keeps a few words in registers.
+// kind's end.  a: the kernel's argument, of which the walk keeps a few words in registers.  None of these kernels
+// may spill: a ticket of the queue is on its way into its register while other things are done, and a copy of that would be one of the old value.
 template <int D, int kSplit, bool kStream>
 __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *lds_raw) {
     constexpr int kRowB = D * 2;                // bytes of a row
@@ -139,6 +141,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     int my_win;                                 // this lane's row's first exact column (both lane halves; past the end: the last row again)
     int wave_first, wave_win_first, wave_win_last;              // first row of the wave, first exact columns of its first and last
     int at_hat, at_kb0, at_nv, at_turns;        // n_hat .. turns
+    int at_steady;                              // (kStream) turns up to here, in which the wave masks nothing and requests K_hat two turns ahead
     bf16_t *out_rows;
     auto my_row = [&]() { return min(wave_first + (lane_here() & 31), n - 1); };
     auto take_rows = [&](const auto &a) __attribute__((always_inline)) {
@@ -148,6 +151,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         wave_win_first = win_start(a, wave_first);
         wave_win_last = win_start(a, min(wave_first + 31, last));
         at_hat = n_hat, at_kb0 = kb0, at_nv = nv, at_turns = turns;
+        at_steady = min(min(wave_win_first / KB, turns - 4), min(n_hat, a.n / KB) - 2);
         out_rows = o_rows;
     };
     auto take_tile = [&]() __attribute__((always_inline)) { take_rows(*arguments()); };
@@ -262,8 +266,10 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     };
 
     f32x16 oacc[MT];
-    float limit;                                // of a block's sum; -1 as long as there is no maximum
-    float m_run, l_run;                         // maximum; running sum, this lane half's share
+    constexpr bool kMatrixSums = D == 128;      // row sums on the matrix cores
+    constexpr float kRaise = 8.f;               // in log2 units: by what a block's maximum has to exceed the running one for that to be raised
+    constexpr int kSums = kMatrixSums ? 1 : 4;
+    float m_run, l_run[kSums];                  // kMatrixSums: maximum + kRaise - 1, sum; else maximum, this lane half's share of the sum in four chains
     f32x16 s[NT];                               // raw scores of the current block
     u32x4 pb[2 * NT];                           // its probabilities, bf16, as P V operands
 
@@ -272,6 +278,16 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     const uint32_t k_lane = lds0 + (row_base + li) * kRowB + ((half ^ keys_perm(li)) << 4);
     const int L = lane & 15, lg = (lane >> 4) & 1;
     const uint32_t v_lane = lds0 + kBufs * kTile + (row_base + 4 * half + (L >> 2)) * kRowB + (vals_perm(L >> 2) << 4) + lg * 32 + (L & 3) * 8;
+
+    // The row sum is taken over the probabilities as rounded to bf16, i.e. over the very weights that P V uses: the output is then an exact
+    // weighted mean of the value rows, and the rounding of the weights cannot bias it (summing the unrounded ones does, by up to 2^-9
+    // relative when many weights are equal).  At head_dim 128 on the matrix cores, while a phase's first operands are on their way from LDS: as a
+    // 16 x 16 x 32 operand the probabilities of score rows c and c + 16 lie in the same column, of which these ones and zeros take the lanes of
+    // one.  A v_dot2c_f32_bf16 waits for a turn of the matrix cores behind the other wave's products: with 16 of them a block a vector phase
+    // took 1360 clocks, and no instruction less in it made it shorter; now 1060, the matrix phase 1200.  (4 x 4 x 4 products, of which every lane has its own
+    // column, 4 x 8192 tokens 1125 / 1136 us.  At head_dim 64, where the vector ALU is what there is least of and other waves fill such waits, 32 x 2048
+    // tokens took 672 / 682 us in this way.)
+    const uint32_t one = ((lane >> 2) ^ (lane >> 4)) & 1 ? 0u : 0x3f803f80u;
 
     // A matrix phase: P V of the turn before (value buffer vb), then the scores of this turn (key buffer kb).  Every matrix
     // instruction takes its first operand fresh from LDS; the reads run kAhead instructions in front, from one product
@@ -311,54 +327,53 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             }
         };
         constexpr int kAhead = D == 64 ? 4 : 5;
+        const u32x4 ones = {one, one, one, one};
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};                        // (the lane's row, in every register)
         for_each_index<nv + nk + kAhead>([&](auto i) {
             if constexpr (i >= kAhead) multiply(std::integral_constant<int, i - kAhead>{});
             if constexpr (i < nv + nk) read(i);
+            if constexpr (kMatrixSums && nv > 0 && i < 2 * NT)
+                sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ones), __builtin_bit_cast(bf16x8, pb[i]), sum, 0, 0, 0);
+            if constexpr (kMatrixSums && nv > 0 && i == 2 * NT + 2) l_run[0] += sum[0];
             __builtin_amdgcn_sched_barrier(0);
         });
     };
-    // Masks where some row of the wave does not see all of the block, then online softmax: s -> pb.  The running maximum is
-    // only raised where a block goes far beyond it, so the accumulator is rarely rescaled.
-    auto softmax = [&](int v) {
+    // Masks where some row of the wave does not see all of the block, then online softmax: s -> pb.
+    auto softmax = [&](int v, auto masks) __attribute__((always_inline)) {   // masks: some row may not see all of the block
         const bool hat = v < at_hat, none = v >= at_nv;          // (none: a turn in which this group has no block)
         const int jb = (hat ? v : at_kb0 + v - at_hat) * KB;
-        auto mask = [&]() __attribute__((always_inline)) {
-            if (none || (hat ? jb + KB > wave_win_first : jb < wave_win_last || jb + KB > wave_first + 1)) {
-                // the row's columns of the block, [from, to), as bits; two instructions a score: a bit spread over the word chooses (a
-                // compare, a select and the wait for the condition between them took 600 clocks a block, half of the softmax itself)
-                const int row = my_row();
-                const int from = min(max((hat ? 0 : my_win) - jb, 0), KB), to = none ? 0 : min(max((hat ? my_win : row + 1) - jb, 0), KB);
-                uint64_t seen = to > 0 ? ~(uint64_t)0 >> (64 - to) : 0;
-                seen = from < 64 ? seen >> from << from : 0;
-                seen >>= 4 * (lane_here() >> 5);                 // (the lane half's first row is column 4)
+        if (masks && (none || (hat ? jb + KB > wave_win_first : jb < wave_win_last || jb + KB > wave_first + 1))) {
+            // the row's columns of the block, [from, to), as bits; two instructions a score: a bit spread over the word chooses (a
+            // compare, a select and the wait for the condition between them took 600 clocks a block, half of the softmax itself)
+            const int row = my_row();
+            const int from = min(max((hat ? 0 : my_win) - jb, 0), KB), to = none ? 0 : min(max((hat ? my_win : row + 1) - jb, 0), KB);
+            uint64_t seen = to > 0 ? ~(uint64_t)0 >> (64 - to) : 0;
+            seen = from < 64 ? seen >> from << from : 0;
+            seen >>= 4 * (lane_here() >> 5);                 // (the lane half's first row is column 4)
 #pragma unroll
-                for (int T = 0; T < NT; ++T)
+            for (int T = 0; T < NT; ++T)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const uint32_t take = (uint32_t)__builtin_amdgcn_sbfe((int)(uint32_t)(seen >> (32 * T)), 8 * (r >> 2) + (r & 3), 1);
-                        s[T][r] = __uint_as_float((__float_as_uint(s[T][r]) & take) | (0xff800000u & ~take));
-                    }
-            }
-        };
-        mask();
-        auto exponentials = [&]() __attribute__((always_inline)) {
-            const float neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-            // The row sum is taken over the probabilities as rounded to bf16, i.e. over the very weights that P V uses:
-            // the output is then an exact weighted mean of the value rows, and the rounding of the weights cannot bias it
-            // (summing the unrounded ones does, by up to 2^-9 relative when many weights are equal).
-            float sum[4] = {0.f, 0.f, 0.f, 0.f};                 // four chains: one would wait for itself
+                for (int r = 0; r < 16; ++r) {
+                    const uint32_t take = (uint32_t)__builtin_amdgcn_sbfe((int)(uint32_t)(seen >> (32 * T)), 8 * (r >> 2) + (r & 3), 1);
+                    s[T][r] = __uint_as_float((__float_as_uint(s[T][r]) & take) | (0xff800000u & ~take));
+                }
+        }
+        // s -> pb, against m.  kMatrixSums: returns the words of pb or-ed together; else adds them up.
+        auto exponentials = [&](float m) __attribute__((always_inline)) {
+            uint32_t any = 0;
 #pragma unroll
             for (int T = 0; T < NT; ++T)
 #pragma unroll
                 for (int r = 0; r < 16; r += 2) {
                     f32x2 p;                                     // bare v_exp_f32: tiny results may flush to 0
-                    p[0] = __builtin_amdgcn_exp2f(fmaf(s[T][r], a.scale_log2, neg_m));
-                    p[1] = __builtin_amdgcn_exp2f(fmaf(s[T][r + 1], a.scale_log2, neg_m));
+                    p[0] = __builtin_amdgcn_exp2f(fmaf(s[T][r], a.scale_log2, -m));
+                    p[1] = __builtin_amdgcn_exp2f(fmaf(s[T][r + 1], a.scale_log2, -m));
                     const bf16x2 pk = __builtin_convertvector(p, bf16x2);
-                    pb[2 * T + (r >> 3)][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
-                    sum[(r >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pk, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, sum[(r >> 1) & 3], false);
+                    any |= pb[2 * T + (r >> 3)][(r & 7) >> 1] = __builtin_bit_cast(uint32_t, pk);
+                    if constexpr (!kMatrixSums)                  // (four chains: one would wait for itself)
+                        l_run[(r >> 1) & 3] = __builtin_amdgcn_fdot2_f32_bf16(pk, bf16x2{(__bf16)1.0f, (__bf16)1.0f}, l_run[(r >> 1) & 3], false);
                 }
-            return (sum[0] + sum[1]) + (sum[2] + sum[3]);
+            return any;
         };
         // the block's maximum, in log2 units
         auto block_max = [&]() __attribute__((always_inline)) {
@@ -377,48 +392,43 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             return __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * a.scale_log2;
         };
         auto raise = [&](float bm) __attribute__((always_inline)) {
-            const float m_new = fmaxf(m_run, bm);
+            const float m_new = fmaxf(m_run, kMatrixSums ? bm + (kRaise - 1.f) : bm);
             const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
             m_run = m_new;
-            l_run *= alpha;
+#pragma unroll
+            for (int k = 0; k < kSums; ++k) l_run[k] *= alpha;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) oacc[mt] *= alpha;
         };
-        // At head_dim 64 the scores, kept until their sum is known, would not fit into the registers: where they are wanted again they are taken
-        // again, from keys in memory (the next but one tile may be on its way to where they lay in LDS).
-        auto scores_again = [&]() __attribute__((always_inline)) {
-            const bf16_t *keys = (const bf16_t *)(hat || none ? Hp : Kp);
+        // The running maximum is only raised where a block's exceeds it by 2^kRaise: the accumulator is rarely rescaled, and a row's largest
+        // weight mostly stays the power of two that bf16 holds exactly.  (Raised beyond 2^60 only, errors against 64 bits are up to 0.5 % larger.)
+        if constexpr (kMatrixSums) {
+            // The exponentials say themselves whether there is one: they are taken against the maximum as it stands, with m_run so far above it
+            // that then, and only then, one is 2 or more and has a bit of its exponent that no smaller one has.  A block's maximum is only looked for
+            // where that is so, or some row has none yet, and they are taken again.  With the sums on the matrix cores, and no masks and addresses in
+            // most turns, us a call, before / now: 20 / 5 heads of 128, 4 x 8192 tokens 1171 / 1128, 1 x 4096 107.1 / 103.9, 2 x 5003 in a band 263 /
+            // 256, 2 x 4096 in pieces of 1024 257 / 251 (the sums alone).
+            uint32_t large = 0x40004000u;
+            if (!__any(m_run == -INFINITY)) large &= exponentials(m_run);
+            if (__builtin_expect(__any(large != 0), false)) {
+                const float bm = block_max();
+                raise(bm);
+                exponentials(m_run == -INFINITY ? 0.f : m_run);
+                // (a NaN among them, which has that bit too, must not meet the zeros of the row whose column it shares: this row's sum is NaN from here on)
+                const uint32_t take = bm < INFINITY ? ~0u : 0u;
 #pragma unroll
-            for (int T = 0; T < NT; ++T) {
-                const u32x4 *row = (const u32x4 *)(keys + (size_t)min(jb + 32 * T + (lane_here() & 31), n - 1) * D);
+                for (int k = 0; k < 2 * NT; ++k)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[T][r] = 0.f;
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks)
-                    s[T] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, row[2 * ks + (lane_here() >> 5)]),
-                                                                  __builtin_bit_cast(bf16x8, qreg[ks]), s[T], 0, 0, 0);
+                    for (int j = 0; j < 4; ++j) pb[k][j] &= take;
+                l_run[0] = bm < INFINITY ? l_run[0] : __builtin_nanf("");
             }
-            mask();
-        };
-        // The exponentials are taken against the maximum as it stands, and the block's sum says whether that was high enough: a block's
-        // maximum is only looked for where some row of the wave has none yet, or a sum beyond 2^60 (then they are taken again; sums
-        // and outputs have 2^67 left).  That is 22 of the phase's 173 instructions.  us a call, maximum of every block / where needed: 20 / 5 heads of
-        // 128, 4 x 8192 tokens 1159 / 1129, 1 x 4096 108.5 / 106.2, 2 x 5003 in a band 261 / 255; 32 / 8 heads of 64, 1 x 2048 37.7 / 35.5,
-        // 32 x 2048 690 / 674, 4 x 4096 305 / 301, 8 x 1500 in a band 123 / 118.
-        float sum = 0.f;
-        bool look = __any(limit < 0.f), taken = false;
-        if (!look) {
-            sum = exponentials();
-            look = taken = __any(sum > limit);
+        } else {
+            // (at head_dim 64 the scores, kept until that is known, would not fit into the registers)
+            const float bm = block_max();
+            if (__any(bm > m_run + kRaise)) raise(bm);
+            exponentials(m_run == -INFINITY ? 0.f : m_run);
         }
-        if (__builtin_expect(look, false)) {
-            if (D == 64 && taken) scores_again();
-            raise(block_max());
-            limit = m_run == -INFINITY ? -1.f : 0x1p60f;
-            sum = exponentials();
-        }
-        l_run += sum;
     };
 
     // ---- the walk.  The tiles of turn t lie in buffers t % kBufs.  The key tile of turn t + 2 and the value tile of turn t + 1 are
@@ -451,11 +461,13 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[mt][r] = 0.f;
         m_run = -INFINITY;
-        limit = -1.f;
-        l_run = 0.f;
+#pragma unroll
+        for (int k = 0; k < kSums; ++k) l_run[k] = 0.f;
     };
     auto row_sum = [&]() {
-        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
+        if constexpr (kMatrixSums) return l_run[0];
+        const float l = (l_run[0] + l_run[kSums / 4]) + (l_run[kSums / 2] + l_run[kSums - 1]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l), __float_as_uint(l), false, false);
         return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
     };
     auto packed = [](const f32x16 &o, int q4, float inv) {
@@ -565,7 +577,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 if (stores) store_rows(full_rows, full_first, inv);
                 clear();
             }
-            softmax(turn);
+            softmax(turn, yes);
             __builtin_amdgcn_s_setprio(1);                       // (for the matrix phase that follows)
             if (grp == 0 || (last && ahead)) {                   // what was asked for in earlier turns, the queries
                 if (stores)
@@ -593,19 +605,31 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             } else {
                 ++turn;
             }
-            // the turns of a tile in which nothing else is to be done: not the first one, which stores, nor the last four
-            for (; turn > 0 && turn + 4 < at_turns; ++turn) {
-                if (grp == 1) wait_loads<0>();
-                phase_barrier();
-                __builtin_amdgcn_s_setprio(0);
-                request(opened++, after(after(buf)), after(buf));
-                softmax(turn);
-                __builtin_amdgcn_s_setprio(1);
-                if (grp == 0) wait_loads<kLoads>();
-                phase_barrier();
-                const int prev = buf;
-                buf = after(buf);
-                matrix_phase(yes, yes, prev, buf);
+            // most turns of a long tile: the blocks left of all windows, one array after the other, nothing masked, nothing past the end, and
+            // nothing else to be done - not the first one, which stores, nor the last four
+            if (turn > 0 && turn < at_steady) {
+                const char *keys = Hp + (size_t)(uint32_t)(opened * KB + wave * kRows) * kRowB;
+                const char *vals = Vp + (size_t)(uint32_t)values_row * kRowB;
+                const int from = turn;
+                for (; turn < at_steady; ++turn) {
+                    if (grp == 1) wait_loads<0>();
+                    phase_barrier();
+                    __builtin_amdgcn_s_setprio(0);
+                    const int prev = buf, far = after(after(buf));
+                    buf = after(buf);
+                    loads_to_lds(keys, k_off, lds_of(far, true));
+                    loads_to_lds(vals, v_off, lds_of(buf, false));
+                    keys += KB * kRowB;
+                    vals += KB * kRowB;
+                    softmax(turn, no);
+                    __builtin_amdgcn_s_setprio(1);
+                    if (grp == 0) wait_loads<kLoads>();
+                    phase_barrier();
+                    matrix_phase(yes, yes, prev, buf);
+                }
+                opened += turn - from;
+                values_row += (turn - from) * KB;
+                values = Vp;
                 stored = false;
             }
         }
@@ -621,7 +645,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             phase_barrier();
             __builtin_amdgcn_s_setprio(0);
             request(turn + 2, after(after(buf)), after(buf));
-            softmax(kSplit == 1 ? turn : turn * kSplit + grp);
+            softmax(kSplit == 1 ? turn : turn * kSplit + grp, yes);
             // asked for three turns before the tile ends: whoever asks first gets the longest tile left (behind the turn's
             // loads: a wait for older ones then does not wait for it)
             if (turn == max(turns - 3, 0)) ask();
@@ -764,13 +788,14 @@ __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(Mfma
     const auto &fill = *(const __attribute__((address_space(4))) CacheFill *)(args + sizeof(MfmaArgs));
     static_assert(kFillLds<D> <= 4 * KB * 2 * D * 2, "the room of the tiles");
     int *const next = (int *)(lds_raw + 4 * KB * 2 * D * 2);
+    const int tid = (int)threadIdx.x;
     while (pos < b.total) {
         __syncthreads();                                         // the LDS is free
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             const int queues = b.xsplit_log2 >= 0 ? 8 : 1, mine = pos & (queues - 1);
             *next = b.total > (int)gridDim.x ? (int)gridDim.x + mine + queues * (int)atomicAdd(b.queue + mine * kQueueStride, 1u) : b.total;
         }
-        fill_chunk<D, 512>(fill, pos - b.blocks, lds_raw);
+        fill_chunk<D, 512>(fill, pos - b.blocks, lds_raw, tid);
         pos = *next;
     }
 }

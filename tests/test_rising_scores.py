@@ -22,3 +22,24 @@ def test_rising_scores(window_mode, d, B, Hq, Hkv, n):
     K = (level / np.sqrt(d))[None, None, :, None] + 0.05 * rng.standard_normal((B, Hkv, n, d))
     Q, K = (wl.round_to_dtype(x, "bf16") for x in (Q, K))
     run_case(Q, K, V, 0.03, 40, "bf16", da.DA_SCORE_GATHER, window_mode=window_mode, q_heads=[0, Hq - 1])
+
+
+@pytest.mark.parametrize("d,B,Hq,Hkv,n", [(128, 1, 4, 1, 500), (128, 30, 16, 4, 330), (128, 1, 4, 1, 2000), (64, 1, 4, 1, 500)])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_not_a_number_stays_in_the_rows_that_see_it(value, d, B, Hq, Hkv, n):
+    """A key with such an entry, from the middle of the prompt on: rows before it are what they are without it, to the bit where no row of their wave sees
+    it; rows from it on, whose window it lies in, are NaN in every channel (it is in the reference keys of later rows too)."""
+    import torch
+    Q, K, V = (torch.from_numpy(np.ascontiguousarray(rand_walk(s, B, H, n, d, "bf16", clip=3.5))).to(torch.bfloat16).cuda() for s, H in ((17, Hq), (18, Hkv), (19, Hkv)))
+    at, W = n // 2 + 3, 40
+    clean, _, _ = da.delta_attn_prefill(Q, K, V, 0.2, W)
+    Q2 = Q.clone()
+    Q2[..., 3] = Q2[..., 3].abs() + 0.25
+    clean, _, _ = da.delta_attn_prefill(Q2, K, V, 0.2, W)
+    K2 = K.clone()
+    K2[:, :, at, 3] = value
+    O, _, _ = da.delta_attn_prefill(Q2, K2, V, 0.2, W)
+    assert torch.isfinite(O[:, :, :at].float()).all()
+    assert (O[:, :, :at].float() - clean[:, :, :at].float()).abs().max().item() <= 2e-2
+    end = min(n, (at // W + 1) * W)                              # of the window the key lies in
+    assert torch.isnan(O[:, :, at:end]).all()
