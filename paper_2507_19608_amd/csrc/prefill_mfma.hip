@@ -416,12 +416,14 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 raise(bm);
                 exponentials(m_run == -INFINITY ? 0.f : m_run);
                 // (a NaN among them, which has that bit too, must not meet the zeros of the row whose column it shares: this row's sum is NaN from here on)
-                const uint32_t take = bm < INFINITY ? ~0u : 0u;
+                if (__builtin_expect(__any(!(bm < INFINITY)), false)) {
+                    const uint32_t take = bm < INFINITY ? ~0u : 0u;
 #pragma unroll
-                for (int k = 0; k < 2 * NT; ++k)
+                    for (int k = 0; k < 2 * NT; ++k)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) pb[k][j] &= take;
-                l_run[0] = bm < INFINITY ? l_run[0] : __builtin_nanf("");
+                        for (int j = 0; j < 4; ++j) pb[k][j] &= take;
+                    l_run[0] = bm < INFINITY ? l_run[0] : __builtin_nanf("");
+                }
             }
         } else {
             // (at head_dim 64 the scores, kept until that is known, would not fit into the registers)
