@@ -8,7 +8,7 @@
 //                        product of the query with the held key, q . k_hat(j): K_hat Q^T on the matrix cores.
 //                        DA_SCORE_GATHER takes this form too: adding up the surviving entries one by one on the
 //                        vector ALU was bound by instruction issue and LDS, at 8.04 ms on 4 x 8192 tokens, 20 / 5 heads
-//                        of 128, 60 % sparsity, which take 1.14 to 1.24 ms here (the clock differs from card to card).
+//                        of 128, 60 % sparsity, which take 1.10 to 1.20 ms here (the clock differs from card to card).
 //   inside the window    exact scores K Q^T.
 //
 // The keys of a tile are walked as one list of blocks: first the blocks with columns left of some row's window (scores
@@ -16,8 +16,8 @@
 // the list twice, each time with the other part masked: there is one loop and one kind of block, and what a block
 // reads is two tiles, keys and values.
 //
-// What bounds it: matrix cores and vector ALU take turns.  A block of 64 keys costs a wave 1024 cycles of matrix work at
-// head_dim 128 (512 at 64) and about 560 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
+// What bounds it: matrix cores and vector ALU take turns.  A block of 64 keys costs a wave 1088 cycles of matrix work at
+// head_dim 128 (512 at 64) and about 590 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
 // other takes exponentials.  The waves therefore run in two groups half a block apart (waves 0-3 and 4-7, one of each per
 // SIMD), handed from phase to phase by barriers:
 //     A: | PV(b-1) S(b) | softmax(b)   | PV(b) S(b+1) | ...
@@ -25,8 +25,8 @@
 // A wave in its matrix phase goes first (s_setprio): it issues one instruction in 32 clocks, and every one that has to wait for
 // the other wave's arithmetic lengthens the phase.  What is added to a matrix phase - addresses, loads, the look at the masks -
 // comes out at more than it saves in the vector phase: its instructions wait in order for whatever is issued between them.
-// Counters on 4 x 8192 tokens, 20 / 5 heads of 128: 1.92 M clocks a launch, 1490 a phase, of which one wave's matrix instructions
-// fill 1088 and the other wave's vector instructions 560; with row sums by dot products on the vector ALU and the maximum of every block 2.08 M and 1610
+// Counters on 4 x 8192 tokens, 20 / 5 heads of 128: 1.96 M clocks a launch, 1520 a phase, of which one wave's matrix instructions
+// fill 1088 and the other wave's vector instructions 586; with row sums by dot products on the vector ALU and the maximum of every block 2.08 M and 1610
 // (692 of issue).  Before that, with the priority the other way round, a branch and an address for every
 // load, fmaxf, a wait where the next tile is asked for, a pause between tiles and queries and outputs in pieces it was 2.43 M; of 15 %
 // fewer clocks 7 % are left in time (1344 -> 1256 us a call, in turn on one card): the clock goes down under this load, to 1.7 of 2.4 GHz.
