@@ -392,7 +392,8 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             return __builtin_elementwise_maximum(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * a.scale_log2;
         };
         auto raise = [&](float bm) __attribute__((always_inline)) {
-            const float m_new = fmaxf(m_run, kMatrixSums ? bm + (kRaise - 1.f) : bm);
+            // (the maximum of a row with a NaN score is NaN at head_dim 128)
+            const float m_new = kMatrixSums ? __builtin_elementwise_maximum(m_run, bm + (kRaise - 1.f)) : fmaxf(m_run, bm);
             const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);
             m_run = m_new;
@@ -414,15 +415,25 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             if (__builtin_expect(__any(large != 0), false)) {
                 const float bm = block_max();
                 raise(bm);
-                exponentials(m_run == -INFINITY ? 0.f : m_run);
-                // (a NaN among them, which has that bit too, must not meet the zeros of the row whose column it shares: this row's sum is NaN from here on)
-                if (__builtin_expect(__any(!(bm < INFINITY)), false)) {
-                    const uint32_t take = bm < INFINITY ? ~0u : 0u;
+                const float m = m_run == -INFINITY ? 0.f : m_run;
+                exponentials(m);
+                // An infinity or a NaN among them must not meet the zeros of the row whose column it shares: its own row's sum is NaN from here on.  (A NaN
+                // score makes the maximum one.)  Finite scores give an infinity too: from 2^31 on half a step of the maximum is 128 or more, by which
+                // the exponent, rounded once, can exceed it; below 2^30 an exponent stays below 64.
+                if (__builtin_expect(__any(!(fabsf(m) < 0x1p30f)), false)) {
+                    uint32_t full = 0;                           // bit 15, 31: an exponent of all ones
+#pragma unroll
+                    for (int k = 0; k < 2 * NT; ++k)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) full |= (pb[k][j] & 0x7f807f80u) + 0x00800080u;
+                    const auto both = __builtin_amdgcn_permlane32_swap(full, full, false, false);
+                    const bool none = ((both[0] | both[1]) & 0x80008000u) == 0;
+                    const uint32_t take = none ? ~0u : 0u;
 #pragma unroll
                     for (int k = 0; k < 2 * NT; ++k)
 #pragma unroll
                         for (int j = 0; j < 4; ++j) pb[k][j] &= take;
-                    l_run[0] = bm < INFINITY ? l_run[0] : __builtin_nanf("");
+                    l_run[0] = none ? l_run[0] : __builtin_nanf("");
                 }
             }
         } else {

@@ -41,3 +41,21 @@ def test_not_a_number_stays_in_the_rows_that_see_it(value, d, B, Hq, Hkv, n):
     assert (O[:, :, :at].float() - clean[:, :, :at].float()).abs().max().item() <= 2e-2
     end = min(n, (at // W + 1) * W)                              # of the window the key lies in
     assert torch.isnan(O[:, :, at:end]).all()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n", [(1, 4, 1, 300), (30, 16, 4, 330), (64, 20, 5, 260)])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_huge_scores_stay_in_their_row(sign, B, Hq, Hkv, n):
+    """Queries whose scores are beyond 2^31, where a probability against the rounded maximum can be infinite: the rows 16 further on and 16 before, whose sums are
+    taken in the same column of a matrix product, are within the rounding of the outputs what they are without them.  (head_dim 128: split tiles, whole ones,
+    tile after tile.)"""
+    import torch
+    Q, K, V = (torch.from_numpy(np.ascontiguousarray(rand_walk(s, B, H, n, 128, "bf16", clip=3.5))).to(torch.bfloat16).cuda() for s, H in ((27, Hq), (28, Hkv), (29, Hkv)))
+    K[..., 3] = sign * (K[..., 3].abs() + 0.25)
+    clean, _, _ = da.delta_attn_prefill(Q, K, V, 0.2, 40)
+    huge = torch.arange(n, device="cuda") % 64 < 16              # rows 0 .. 15 and, in other heads, 16 .. 31 of every 64
+    hit = torch.stack([huge.roll(16 * (h % 2)) for h in range(Hq)])
+    Q2 = Q.clone()
+    Q2[..., 3] = torch.where(hit[None], torch.full_like(Q[..., 3], 3e11), Q[..., 3])
+    O, _, _ = da.delta_attn_prefill(Q2, K, V, 0.2, 40)
+    assert (O.float() - clean.float())[:, ~hit].abs().max().item() <= 2e-2
