@@ -270,7 +270,7 @@ da_status prefill_checked(const da_prefill_params *p, const WsLayout &w, const v
         cache->len = p->seq_len;
     } else if (cache) {
         stage_begin(kStageCacheFill, s);
-        cache_fill_from_prefill(cache, p, K, V, khat, mask_bits, nnz, s);
+        cache_fill_from_prefill(cache, p, a.K, a.V, khat, mask_bits, nnz, s);   // (K and V, or their aligned copies)
         stage_end(kStageCacheFill, s);
         if (!launch_ok("cache_fill")) return DA_ERR_HIP;
     }

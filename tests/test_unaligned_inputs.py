@@ -16,10 +16,11 @@ def _moved(x, by):
     return y
 
 
+# (the hand-off to the cache in the attention launch, and in one of its own: short prompts, many chunks)
 @pytest.mark.parametrize("window_mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
 @pytest.mark.parametrize("by", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (0, 3, 5), (7, 7, 4), (0, 8, 8)])
 @pytest.mark.parametrize("B,Hq,Hkv,n,d,W", [(1, 1, 1, 1, 64, 1), (1, 2, 1, 2, 64, 2), (2, 4, 2, 257, 64, 16), (1, 4, 1, 1500, 128, 100),
-                                            (3, 2, 2, 129, 128, 32)])
+                                            (3, 2, 2, 129, 128, 32), (24, 8, 8, 450, 64, 20)])
 def test_prefill_of_moved_tensors(window_mode, by, B, Hq, Hkv, n, d, W):
     x = [to_dev(rand_walk(s, B, H, n, d, "bf16"), "bf16") for s, H in ((1, Hq), (2, Hkv), (3, Hkv))]
     y = [_moved(t, b) for t, b in zip(x, by)]
