@@ -16,11 +16,10 @@ def _moved(x, by):
     return y
 
 
-# (the hand-off to the cache in the attention launch, and in one of its own: short prompts, many chunks)
 @pytest.mark.parametrize("window_mode", [da.DA_WINDOW_BLOCK, da.DA_WINDOW_SLIDING])
 @pytest.mark.parametrize("by", [(1, 0, 0), (0, 1, 0), (0, 0, 1), (0, 3, 5), (7, 7, 4), (0, 8, 8)])
 @pytest.mark.parametrize("B,Hq,Hkv,n,d,W", [(1, 1, 1, 1, 64, 1), (1, 2, 1, 2, 64, 2), (2, 4, 2, 257, 64, 16), (1, 4, 1, 1500, 128, 100),
-                                            (3, 2, 2, 129, 128, 32), (24, 8, 8, 450, 64, 20)])
+                                            (3, 2, 2, 129, 128, 32)])
 def test_prefill_of_moved_tensors(window_mode, by, B, Hq, Hkv, n, d, W):
     x = [to_dev(rand_walk(s, B, H, n, d, "bf16"), "bf16") for s, H in ((1, Hq), (2, Hkv), (3, Hkv))]
     y = [_moved(t, b) for t, b in zip(x, by)]
@@ -36,6 +35,20 @@ def test_prefill_of_moved_tensors(window_mode, by, B, Hq, Hkv, n, d, W):
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     for c in caches:
         c.close()
+
+
+@pytest.mark.parametrize("by", [1, 5])
+def test_moved_tensors_into_a_cache_of_many_chunks(by):
+    """The hand-off to the cache in a launch of its own."""
+    B, Hq, Hkv, n, d = 24, 8, 8, 450, 64
+    x = [to_dev(rand_walk(s, B, H, n, d, "bf16"), "bf16") for s, H in ((1, Hq), (2, Hkv), (3, Hkv))]
+    step = [to_dev(rand_walk(40 + s, B, H, 1, d, "bf16"), "bf16")[:, :, 0].contiguous() for s, H in ((0, Hq), (9, Hkv), (18, Hkv))]
+    found = []
+    for y in (x, [_moved(t, by) for t in x]):
+        cache = da.Cache(B, Hq, Hkv, d, n + 1, 64, 0.2, torch.bfloat16)
+        found.append(da.delta_attn_prefill(*y, 0.2, 20, cache=cache) + da.delta_attn_decode(cache, *step) + (cache.nnz().clone(),))
+        cache.close()
+    assert all(torch.equal(s, t) for s, t in zip(*found))
 
 
 # split tiles, whole ones that end before the next begins, tile after tile without a pause: queries and outputs off 16 bytes
