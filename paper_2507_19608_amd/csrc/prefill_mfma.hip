@@ -97,7 +97,8 @@ struct MfmaArgs {
 
 // The tiles of one kind: those at `pos` and the positions the queue hands out after it; returns the first of these past the
 // kind's end.  a: the kernel's argument, of which the walk keeps a few words in registers.  None of these kernels
-// may spill: a ticket of the queue is on its way into its register while other things are done, and a copy of that would be one of the old value.
+// may spill: a ticket of the queue is on its way into its register while other things are done, and a copy of that would be one of the old value
+// (a build in which one does fails).
 template <int D, int kSplit, bool kStream>
 __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *lds_raw) {
     constexpr int kRowB = D * 2;                // bytes of a row
