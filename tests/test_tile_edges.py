@@ -81,7 +81,8 @@ def test_scan_of_many_short_rows(units, n):
 ])
 def test_matrix_core_tiles(window_mode, d, n, W, B, Hq, Hkv):
     """Blocks that lie left of some rows' windows and inside others', tiles that end in the middle, waves without rows,
-    turns for which one of the two groups has no block."""
+    turns for which one of the two groups has no block.  (Up to 416 rows of 64 and 200 of 128 the short prompts' kernel; the tile-by-tile one on such
+    sizes, by pieces: test_short_prompts.py.)"""
     Q, K, V = _walks(401, B, Hq, Hkv, n, d, "bf16")
     run_case(Q, K, V, 0.2, W, "bf16", da.DA_SCORE_GATHER, window_mode=window_mode)
 
@@ -90,7 +91,7 @@ def test_matrix_core_tiles(window_mode, d, n, W, B, Hq, Hkv):
 @pytest.mark.parametrize("d,B,Hq,Hkv,n,W", [(64, 33, 32, 8, 300, 50), (128, 16, 20, 5, 900, 128), (64, 70, 8, 8, 520, 26),
                                             (128, 24, 16, 2, 777, 64)])
 def test_whole_tiles_of_large_launches(window_mode, d, B, Hq, Hkv, n, W):
-    """The 256-row tiles that only launches of many tiles take: every output against the closed form, masks too."""
+    """The 256-row tiles that only launches of many tiles take (300 rows of 64 are for the short prompts' kernel): every output against the closed form, masks too."""
     import torch
     import dense_form as df
     from util import to_dev

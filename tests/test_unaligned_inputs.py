@@ -51,9 +51,11 @@ def test_moved_tensors_into_a_cache_of_many_chunks(by):
     assert all(torch.equal(s, t) for s, t in zip(*found))
 
 
-# split tiles, whole ones that end before the next begins, tile after tile without a pause: queries and outputs off 16 bytes
+# short prompts in one launch, items of one wave and of several; split tiles, whole ones that end before the next begins, tile after tile without a pause: queries and
+# outputs off 16 bytes
 @pytest.mark.parametrize("by", [1, 4])
-@pytest.mark.parametrize("B,Hq,Hkv,n,d", [(1, 4, 2, 333, 64), (70, 12, 6, 130, 64), (2, 4, 1, 300, 128), (16, 20, 5, 200, 128), (128, 20, 5, 65, 128)])
+@pytest.mark.parametrize("B,Hq,Hkv,n,d", [(1, 4, 2, 333, 64), (70, 12, 6, 130, 64), (2, 4, 1, 300, 128), (16, 20, 5, 200, 128), (128, 20, 5, 65, 128),
+                                          (1, 4, 2, 450, 64), (70, 12, 6, 430, 64), (16, 20, 5, 260, 128), (48, 20, 5, 333, 128)])
 def test_queries_and_outputs_moved(by, B, Hq, Hkv, n, d):
     x = [to_dev(rand_walk(s, B, H, n, d, "bf16"), "bf16") for s, H in ((1, Hq), (2, Hkv), (3, Hkv))]
     want = da.delta_attn_prefill(*x, 0.2, 16)
