@@ -66,6 +66,15 @@ def outside_rows(n, W, sliding=False):
     return np.maximum(0, n - np.minimum(n, (j // W + 1) * W))
 
 
+def timed_kernel(stages, pieces, graph):
+    """What kernel_ms of a prefill is the time of: a stage with fewer launches than the attention was done in some of these."""
+    if graph:
+        return "whole step, replayed from a graph"
+    fused = lambda stage: stages[stage][1] < stages["attn"][1]
+    beside = ["scan"] * fused("scan") + ["hand-off to the cache"] * (pieces > 1 and fused("cache_fill"))
+    return "prefill attention" + (f" with {' and '.join(beside)} in the same launch" if beside else "")
+
+
 def prefill_bench(args, da, wl, torch, np, mode_name, data=None, workload=None):
     w = workload or {"C5": wl.c5(args.sparsity, args.p_jump), "C3": wl.C3, "C2": wl.C2}[args.workload]
     mode = da.DA_SCORE_GATHER if mode_name == "gather" else da.DA_SCORE_REBASE
@@ -132,7 +141,7 @@ def prefill_bench(args, da, wl, torch, np, mode_name, data=None, workload=None):
     tokens_per_s = B * n / (dt / args.steps)
     s_m, s_c = da.delta_attn_sparsity(out[2], n, d, w.window)
 
-    # algorithmic work of the attention kernel (dominant kernel)
+    # algorithmic work of the attention (dominant kernel; what else its launch does is not counted)
     mask = (out[1] if pieces == 1 else cache.mask_rows()).cpu().numpy().view(np.uint32)
     nnz_col = np.bitwise_count(mask).sum(axis=-1).astype(np.int64)   # [B, Hkv, n]
     rows_out = outside_rows(n, w.window, args.window_mode == "sliding")
@@ -157,7 +166,7 @@ def prefill_bench(args, da, wl, torch, np, mode_name, data=None, workload=None):
                  if args.window_mode == "block" and pieces == 1 else None,
                  "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE)",
                  "traffic_from": f"profiles/{os.path.basename(PROFILE_TRAFFIC)} at commit {TRAFFIC_FROM_COMMIT}",
-                 "kernel": "prefill attention", "kernel_ms": attn_ms,
+                 "kernel": timed_kernel(stages, pieces, use_graph), "kernel_ms": attn_ms,
                  "algorithmic_sparse_gmac": sparse_macs / 1e9, "row_weighted_density": sparse_macs / max(outside_pairs * d, 1),
                  "mfma_tflops": mfma_flops / (attn_ms * 1e-3) / 1e12,
                  "mfma_frac": mfma_flops / (attn_ms * 1e-3) / 1e12 / PEAK_MFMA_BF16_TFLOPS,

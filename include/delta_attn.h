@@ -91,7 +91,10 @@ const char *delta_attn_last_error(void);
  * A benchmarking aid, off by default: the switch and the event pool are process-wide (guarded by a mutex), so
  * with timing on, calls from several threads are bracketed into one common pool.
  */
-/* DA_STAGE_EMIT: no kernel has this stage any more (surviving entries are not written out); it reads 0 calls. */
+/* DA_STAGE_EMIT: no kernel has this stage any more (surviving entries are not written out); it reads 0 calls.
+ * A launch that does the work of several stages counts as DA_STAGE_ATTN alone: short prompts (bf16, head_dim 64 up to 416 rows,
+ * 128 up to 200; small fp32 ones without a cache) are scanned in the attention launch, and DA_STAGE_SCAN has no call; rows that
+ * join a cache may be handed over in it, and DA_STAGE_CACHE_FILL has none. */
 enum { DA_STAGE_SCAN = 0, DA_STAGE_EMIT = 1, DA_STAGE_ATTN = 2, DA_STAGE_CACHE_FILL = 3,
        DA_STAGE_APPEND = 4, DA_STAGE_CHUNK = 5, DA_STAGE_COMBINE = 6, DA_NUM_STAGES = 7 };
 void delta_attn_stage_timing_enable(int32_t on);

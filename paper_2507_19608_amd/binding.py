@@ -110,7 +110,7 @@ def delta_attn_window_from_gamma(n: int, gamma: float, w_max: int) -> int:
     return int(lib().delta_attn_window_from_gamma(n, gamma, w_max))
 
 
-# as numbered in the header ("emit": no kernel has this stage any more)
+# as numbered in the header ("emit": no kernel has this stage any more; a launch that scans or fills a cache beside the attention is "attn" alone)
 STAGES = ("scan", "emit", "attn", "cache_fill", "append", "chunk", "combine")
 
 

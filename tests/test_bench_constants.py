@@ -38,3 +38,12 @@ def test_traffic_constants_are_those_of_the_profile_summary():
 def test_published_peaks():
     assert bench.PEAK_HBM_GBS == 8000.0 and bench.PEAK_MFMA_BF16_TFLOPS == 2500.0
     assert bench.PEAK_VALU_F32_TFLOPS == 157.3 and abs(bench.FMA_MIX_ISSUE_TFLOPS - 157.3 / 2) < 0.06
+
+
+def test_a_launch_that_does_more_than_attention_says_so():
+    calls = lambda scan, fill: {"scan": (0.1, scan), "attn": (1.0, 4), "cache_fill": (0.1, fill)}
+    assert bench.timed_kernel(calls(4, 0), 1, False) == "prefill attention"
+    assert bench.timed_kernel(calls(0, 0), 1, False) == "prefill attention with scan in the same launch"
+    assert bench.timed_kernel(calls(4, 4), 4, False) == "prefill attention"
+    assert bench.timed_kernel(calls(4, 0), 4, False) == "prefill attention with hand-off to the cache in the same launch"
+    assert "step" in bench.timed_kernel(calls(0, 0), 1, True)

@@ -101,3 +101,29 @@ def test_tile_by_tile_kernel_on_short_prompts(window_mode, d, n, W, B, Hq, Hkv):
                                             (128, 257, 20, 1, 1, 1), (128, 289, 33, 2, 8, 2), (128, 321, 320, 1, 12, 6)])
 def test_tile_by_tile_kernel_beyond_short_prompts(window_mode, d, n, W, B, Hq, Hkv):
     run_case(*_walks(402, B, Hq, Hkv, n, d), 0.2, W, "bf16", da.DA_SCORE_GATHER, window_mode=window_mode)
+
+
+# (prompt's rows, pieces, stages with a call): one launch; two; the hand-off in the attention's; short prompts and fp32 into a cache
+@pytest.mark.parametrize("dtype,n,pieces,stages", [
+    ("bf16", 333, 0, {"attn"}), ("bf16", 500, 0, {"scan", "attn"}), ("f32", 200, 0, {"attn"}), ("f32", 600, 0, {"scan", "attn"}),
+    ("bf16", 333, 1, {"attn", "cache_fill"}), ("bf16", 500, 1, {"scan", "attn"}), ("f32", 200, 1, {"scan", "attn", "cache_fill"}), ("bf16", 500, 2, {"scan", "attn"}),
+])
+def test_stages_that_are_timed(dtype, n, pieces, stages):
+    """What the header says of launches that do the work of several stages."""
+    Hq, Hkv, d = 4, 2, 64
+    x = [to_dev(t, dtype) for t in _walks(21, 1, Hq, Hkv, n, d)]
+    cache = da.Cache(1, Hq, Hkv, d, n, 64, 0.2, x[0].dtype) if pieces else None
+    torch.cuda.synchronize()
+    da.delta_attn_stage_timing_enable(True)
+    da.delta_attn_stage_timing_read()
+    if pieces < 2:
+        da.delta_attn_prefill(*x, 0.2, 16, cache=cache)
+    else:
+        for r in (slice(0, n // 2), slice(n // 2, n)):
+            da.delta_attn_prefill_append(cache, *(t[:, :, r].contiguous() for t in x), 0.2, 16)
+    torch.cuda.synchronize()
+    read = da.delta_attn_stage_timing_read()
+    da.delta_attn_stage_timing_enable(False)
+    if cache:
+        cache.close()
+    assert {name for name, (_, calls) in read.items() if calls} == stages
