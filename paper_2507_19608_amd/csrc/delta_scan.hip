@@ -835,9 +835,9 @@ static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *m
     const int which = p.dl == 128 ? 2 : p.dl == 64 && d % 64 == 0 ? 1 : 0;
     static std::atomic<uint64_t> lds_set[6];                     // per instantiation, one bit per device
     const dim3 block(64 * p.waves);
-    if constexpr (sizeof(T) == 2) {                              // (what is fed in pieces is bf16)
-        if (copy) {
-            const auto kernel = which == 2 ? scan_segments_kernel<T, 128, RowCopy> : which == 1 ? scan_segments_kernel<T, 64, RowCopy> : scan_segments_kernel<T, 0, RowCopy>;
+    if constexpr (sizeof(T) == 2) {
+        if (copy) {                                              // (what is fed in pieces is bf16, of 64 or 128 channels)
+            const auto kernel = which == 2 ? scan_segments_kernel<T, 128, RowCopy> : scan_segments_kernel<T, 64, RowCopy>;
             ensure_dynamic_lds((const void *)kernel, kScanLdsMax, lds_set[3 + which]);
             hipLaunchKernelGGL(kernel, dim3(p.nseg, units, groups + 1), block, p.lds, s, a, *copy);
         }

@@ -49,16 +49,12 @@ __device__ __forceinline__ void load_to_lds(const char *base, uint32_t off, uint
                  "global_load_lds_dwordx4 %0, %1 offset:%3" ::"v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds)), "n"(At)
                  : "memory", "m0");
 }
-// N of them, 1 KiB apart
-template <int N>
-__device__ __forceinline__ void loads_to_lds(const char *base, const uint32_t (&off)[N], uint32_t lds) {
-    if constexpr (N == 2)
-        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
-                     "global_load_lds_dwordx4 %0, %2\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:1024" ::"v"(off[0]), "v"(off[1]), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds))
-                     : "memory", "m0");
-    else
-        load_to_lds<0>(base, off[0], lds);
+// two of them, 1 KiB apart
+__device__ __forceinline__ void loads_to_lds(const char *base, const uint32_t (&off)[2], uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %0, %2\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:1024" ::"v"(off[0]), "v"(off[1]), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds))
+                 : "memory", "m0");
 }
 #pragma clang diagnostic pop
 // 16 bytes a lane that the caller waits for.  (s_nop: a scalar register that a vector instruction has just written - a readlane, or a

@@ -109,6 +109,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     constexpr int kIpw = kTile / 1024 / 8;      // by this many 1 KiB loads
     constexpr int kLoads = 2 * kIpw;            // loads per wave and turn
     constexpr int NT = KB / 32;                 // score tiles per block
+    static_assert(NT == 2, "the block's maximum");
     constexpr int KS = D / 16;                  // k-steps of Q K^T
     constexpr int MT = D / 32;                  // channel tiles of the output
     // LDS: [kBufs] key tiles, [kBufs] value tiles, at the end the next tile; where a tile begins, its queries lie behind the first value
@@ -385,8 +386,8 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 mx[k] = max3(s[0][k], s[0][k + 4], s[0][k + 8]);
-                mx[k] = NT == 1 ? __builtin_elementwise_maximum(mx[k], s[0][k + 12]) : max3(mx[k], s[0][k + 12], s[NT - 1][k]);
-                if (NT == 2) mx[k] = __builtin_elementwise_maximum(max3(mx[k], s[NT - 1][k + 4], s[NT - 1][k + 8]), s[NT - 1][k + 12]);
+                mx[k] = max3(mx[k], s[0][k + 12], s[1][k]);
+                mx[k] = __builtin_elementwise_maximum(max3(mx[k], s[1][k + 4], s[1][k + 8]), s[1][k + 12]);
             }
             const float bm = __builtin_elementwise_maximum(max3(mx[0], mx[1], mx[2]), mx[3]);
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bm), __float_as_uint(bm), false, false);
