@@ -44,6 +44,9 @@
 // / 8 heads of 64: 41.5 / 30.8 / 30.3 us; 1 x 1024, 20 / 5 heads of 128: 32.2 / 23.0 / 22.9; 16 x 200: 25.8 / 28.6 / 25.5; 4 x 2048: 104 / 110 /
 // 103; 1 x 4096: 99.7 / 93.4 / 92.7.
 //
+// Figures here and below for up to 416 rows of 64 or 200 of 128 (16 x 200, 14 x 200, 64 x 64, 133 x 64, 512 x 64, 55 x 130, 1 x 333 tokens) were taken when
+// prompts of such lengths still came here in one call.  These have a kernel of their own now (prefill_short.hip); pieces of a prompt of such lengths come here.
+//
 // Tiles go from global memory to LDS directly (global_load_lds, 16 bytes per lane, no registers), row-major, two blocks ahead
 // in three buffers, or two where every group has its own.  The 16-byte segments of a row are permuted by the row number so that the reads are free of bank
 // conflicts: keys by 128-bit reads down a column of rows, values by transposing reads (ds_read_b64_tr_b16: lane j of 16

@@ -4,11 +4,12 @@
 // once, builds the reference keys there and walks its share of the score rows with no barrier and no load between: neither K_hat
 // nor a second launch goes through memory.  Several work groups share a unit's score rows; each scans the unit's keys for itself.
 //
-// What bounds it is latency: at 16 x 200 tokens, 20 / 5 heads of 128, a work group has its rows after 2.6 us, the reference keys after 3 more,
-// and its longest item (of 32 score rows) takes 4.5; matrix instructions fill two thirds of that last part.  Calls in a
-// graph, us, against the two launches of delta_scan.hip and prefill_mfma.hip: 32 / 8 heads of 64, 1 x 64 tokens 11.8 / 6.5, 1 x 333 18.5 / 10, 64 x
-// 200 69 / 42, 32 x 400 65 / 46; 20 / 5 heads of 128, 1 x 200 18.1 / 11.4, 16 x 200 31.5 / 18.2, 256 x 200 301 / 182; over 76 shapes of 1 to
-// 416 tokens, 1 to 256 prompts and six kinds of heads 1.04 to 2.4 times as fast, 1.75 on the geometric mean: there is no line inside the range.
+// What bounds it is latency.  16 x 200 tokens, 20 / 5 heads of 128, us after the first work group's start: all have their keys at 1.8, have walked their runs at
+// 6.1, have their reference keys at 7.0, the first items end at 10.4 to 15.1 (4.0 to 8.4 each: the two waves of a SIMD share its matrix cores), second ones
+// at 13.6, masks and the launch at 15.8.  Times here and below: calls in a graph, 5 % jumps, theta 0.1113, mean of six inputs.  Two launches (delta_scan.hip,
+// prefill_mfma.hip) / this one: 32 / 8 heads of 64, 1 x 64 tokens 12.0 / 6.6, 1 x 333 16.0 / 9.7, 64 x 200 68.8 / 41.2, 32 x 400 70.9 / 47.5; 20 / 5 heads of 128, 1 x
+// 200 18.2 / 11.3, 16 x 200 31.5 / 17.2, 256 x 200 301 / 173; over 76 shapes of 1 to 416 tokens, 1 to 256 prompts and six kinds of heads (an earlier
+// build, one input each) 1.04 to 2.4 times as fast, 1.75 on the geometric mean: there is no line inside the range.
 #include <math.h>
 
 #include "common.hpp"
@@ -23,7 +24,7 @@ typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 typedef __attribute__((address_space(3))) uint32_t *lds_word;
 
 constexpr int NW = 8;                    // waves of a work group
-constexpr int kScanWaves = 4;            // of these walk keys (one a SIMD: eight waves and shorter runs take as long, 16 x 200 18.2 / 18.3 us)
+constexpr int kScanWaves = 4;            // of these walk keys (one a SIMD: eight waves and shorter runs took as long at 16 x 200 tokens, within 1 %)
 template <int D> constexpr int kMostRows = D == 64 ? 416 : 200;              // so that three arrays fit (short_lds)
 
 struct ShortArgs {
@@ -507,12 +508,15 @@ size_t short_lds(int n, int d) {
 }
 
 // One work group to a compute unit (its LDS).  A wave takes an item of 32 score rows, kSplit of them one together where compute units
-// are idle and the longest item has that many blocks (1 / 2 / 4, us a call in a graph: 32 / 8 heads of 64, 1 x 64 tokens 6.2 / 7.0 / 6.9, 1 x 200
-// 9.5 / 9.3 / 8.8, 1 x 333 13.4 / 12.1 / 11.3; 20 / 5 of 128, 1 x 200 14.0 / 13.0 / 11.6).  Else a unit is cut so that every wave has one item and one
+// are idle and the longest item has that many blocks (1 / 2 / 4, us: 32 / 8 heads of 64, 1 x 64 tokens 6.6 / 7.3 / 7.2, 1 x 200
+// 9.9 / 9.2 / 8.6, 1 x 333 11.8 / 10.6 / 9.7; 20 / 5 of 128, 1 x 200 13.7 / 12.5 / 11.4).  Else a unit is cut so that every wave has one item and one
 // wave is left for the mask, or into as many work groups as are resident: more would each scan the unit again (16 x 200 tokens of 20 / 5
-// heads of 128, cut in 1 / 2 / 3 / 4: 28 / 20 / 18 / 31 us).
-// Rows that runs warm up on save rounds: 16 / 32 / 48 / 64 of them 12.5 / 11.3 / 11.1 / 11.4 at 1 x 400 tokens of 64, 15.0 / 15.5 / 14.2 / 14.6 at 16 x
-// 200, 18.3 / 18.2 / 17.8 / 17.8 at 16 x 200 of 128, 15.0 / 13.5 / 11.6 / 9.8 at 1 x 333: which guesses hold is chance.
+// heads of 128, cut in 1 / 2 / 3 / 4: 27.2 / 19.3 / 17.3 / 25.8 us).
+// Rows that runs warm up on save rounds, where the rows that the keys' guesses need are not there anyway.  Geometric mean over 13 shapes and 9 kinds of keys:
+// 16 / 32 / 48 / 64 / 96 of them 12.00 / 11.95 / 12.01 / 12.15 / 12.50 us at jumps of 1 to 20 %, theta 0.03 to 0.22, three inputs each; 32 / 48 / 64 12.15 / 12.04 /
+// 12.05 at 2 to 10 %, 0.08 to 0.16, twelve inputs each.  Fewer are faster where entries fire often (theta 0.03 10.4 .. 12.2), more where they
+// fire rarely (1 %, 0.22 16.5 .. 14.6), and the slowest call gets shorter (26.4 / 25.5 / 24.8 / 24.2 / 22.7): 64 is within 1.7 % of the best mean, and
+// ahead at the rates of the 60 % points (5 %, 0.1113: 12.05 / 11.80 / 11.78).
 ShortPlan short_plan(const PrefillArgs &p) {
     ShortPlan s = {};
     if (p.dtype != 1 || (p.d != 64 && p.d != 128)) return s;
