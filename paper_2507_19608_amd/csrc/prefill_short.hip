@@ -4,9 +4,9 @@
 // once, builds the reference keys there and walks its share of the score rows with no barrier and no load between: neither K_hat
 // nor a second launch goes through memory.  Several work groups share a unit's score rows; each scans the unit's keys for itself.
 //
-// What bounds it is latency.  16 x 200 tokens, 20 / 5 heads of 128, us after the first work group's start: all have their keys at 1.8, have walked their runs at
-// 6.1, have their reference keys at 7.0, the first items end at 10.4 to 15.1 (4.0 to 8.4 each: the two waves of a SIMD share its matrix cores), second ones
-// at 13.6, masks and the launch at 15.8.  Times here and below: calls in a graph, 5 % jumps, theta 0.1113, mean of six inputs.  Two launches (delta_scan.hip,
+// What bounds it is latency.  16 x 200 tokens, 20 / 5 heads of 128, us after the first work group's start: all have their keys at 2.3, have walked their runs at
+// 6.4, have their reference keys at 7.1, the first items end at 9.7 to 14.5 (4.0 to 7.8 each: the two waves of a SIMD share its matrix cores), second ones
+// at 13.4, masks and the launch at 15.3.  Times here and below: calls in a graph, 5 % jumps, theta 0.1113, mean of six inputs.  Two launches (delta_scan.hip,
 // prefill_mfma.hip) / this one: 32 / 8 heads of 64, 1 x 64 tokens 12.0 / 6.6, 1 x 333 16.0 / 9.7, 64 x 200 68.8 / 41.2, 32 x 400 70.9 / 47.5; 20 / 5 heads of 128, 1 x
 // 200 18.2 / 11.3, 16 x 200 31.5 / 17.2, 256 x 200 301 / 173; over 76 shapes of 1 to 416 tokens, 1 to 256 prompts and six kinds of heads (an earlier
 // build, one input each) 1.04 to 2.4 times as fast, 1.75 on the geometric mean: there is no line inside the range.
