@@ -23,6 +23,7 @@
  *   - Threshold decision: fabsf((float)k - (float)held) > theta in IEEE binary32,
  *     strict inequality (Eq. 2); the first row of a sequence is the basis and is
  *     kept whole.  NaN keys never fire (not checked).
+ *   - Scores (scale and log2(e) included) of more than 2^31 can make their row of a bf16 prefill NaN; no other row.
  */
 #ifndef DELTA_ATTN_H
 #define DELTA_ATTN_H
