@@ -6,6 +6,7 @@ or no GPU is present, calls raise.
 """
 import ctypes
 import os
+import struct
 from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -133,11 +134,12 @@ def _check(st: int, where: str):
 
 _torch_mod = None
 _raw_stream = None
+_marshal = None        # the compiled way from a call's objects to the library, or None (it is built beside the library)
 
 
 def _torch():
     """torch, once a GPU has been seen (asked anew as long as there is none)."""
-    global _torch_mod, _raw_stream
+    global _torch_mod, _raw_stream, _marshal
     if _torch_mod is None:
         import torch
         if not torch.cuda.is_available():
@@ -145,6 +147,14 @@ def _torch():
         # The current stream's handle without a Stream object around it (2.5 us a call, a quarter of a decode step's host
         # time); torch's own compiled code asks in this way, and without it the public call does.
         of, device = (getattr(torch._C, f, None) for f in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+        try:
+            from . import _marshal as m                      # (links to torch's libraries, which are loaded by now)
+        except ImportError:
+            m = None
+        if m is not None:
+            m.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+                lib().delta_attn_prefill, lib().delta_attn_prefill_workspace_bytes, lib().delta_attn_decode)))
+            _marshal = m
         _raw_stream = (lambda: of(device())) if of and device else lambda: torch.cuda.current_stream().cuda_stream
         _torch_mod = torch
     return _torch_mod
@@ -199,6 +209,7 @@ class Cache:
         self.shape = (batch, n_q_heads, n_kv_heads, head_dim, max_seq)
         self.dtype = dtype
         self._row_shapes = (batch, n_q_heads, head_dim), (batch, n_kv_heads, head_dim)   # of a decode step's q, and k and v
+        self._packed = struct.pack("P6i", h.value, batch, n_q_heads, n_kv_heads, head_dim, code, 0)   # (CacheOf in csrc/marshal.cpp)
 
     def __len__(self):
         return int(lib().delta_attn_cache_length(self.handle))
@@ -234,7 +245,7 @@ class Cache:
     def close(self):
         if self.handle is not None:
             lib().delta_attn_cache_destroy(self.handle)
-            self.handle = None
+            self.handle = self._packed = None
 
     def __del__(self):
         try:
@@ -300,6 +311,14 @@ def delta_attn_prefill(Q, K, V, theta: float, window: int, scale: float = 0.0, s
     """Returns (O, mask_bits int32 [B, Hkv, n, d/32], nnz int64 [B, Hkv]).  Buffers may be passed in
     (workspace: uint8 tensor, out: (O, mask_bits, nnz)) so a timing loop allocates nothing."""
     torch = _torch()
+    if _marshal is not None:
+        done = _marshal.prefill(Q, K, V, theta, window, scale, score_mode, window_mode,
+                                0 if cache is None or cache.handle is None else cache.handle.value, workspace, out)
+        if done is not None:
+            if type(done) is int:
+                raise DeltaAttnError(done, "delta_attn_prefill")
+            return done
+    # what is not in order, or of other types than the usual: said, or done, here
     p = _qkv_params(Q, K, V, window, theta, scale, score_mode, window_mode)
     if workspace is None:
         workspace = torch.empty(max(delta_attn_prefill_workspace_bytes(p), 1), dtype=torch.uint8, device=Q.device)
@@ -357,6 +376,12 @@ def delta_attn_prefill_append(cache: Cache, Q, K, V, theta: float, window: int, 
 def delta_attn_decode(cache: Cache, q_new, k_new, v_new, out=None, mask_row=None):
     """One decode step.  q_new [B, Hq, d], k_new/v_new [B, Hkv, d].  Returns (o, mask_row)."""
     _torch()
+    if _marshal is not None:
+        done = _marshal.decode(cache._packed, q_new, k_new, v_new, out, mask_row)
+        if done is not None:
+            if type(done) is int:
+                raise DeltaAttnError(done, "delta_attn_decode")
+            return done
     for t, name in ((q_new, "q_new"), (k_new, "k_new"), (v_new, "v_new")):
         if not (t.is_cuda and t.is_contiguous()):
             _dev(t, name)

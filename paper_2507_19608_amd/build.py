@@ -1,15 +1,18 @@
-"""Build libdelta_attn.so (HIP, gfx950) in-tree with hipcc.  No GPU is needed to compile."""
+"""Build libdelta_attn.so (HIP, gfx950) in-tree with hipcc, and the binding's compiled part with g++.  No GPU is needed to compile."""
 import glob
+import importlib.util
 import os
 import re
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_obj")
 LIB = os.path.join(HERE, "libdelta_attn.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 # packed fp32 instructions are switched off for every device compile (hipcc's host pass warns
 # that it does not know the feature; harmless)
@@ -45,11 +48,30 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def build_marshal(force: bool) -> None:
+    """The binding's compiled part.  It calls the library through addresses that it is given, and links to torch alone."""
+    src = os.path.join(CSRC, "marshal.cpp")
+    deps = [src] + glob.glob(os.path.join(HERE, "..", "include", "*.h"))
+    if not force and os.path.exists(MARSHAL) and all(os.path.getmtime(MARSHAL) >= os.path.getmtime(d) for d in deps):
+        return
+    torch = os.path.dirname(importlib.util.find_spec("torch").origin)
+    include = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
+               sysconfig.get_paths()["include"]]
+    r = subprocess.run(["g++", "-O2", "-shared", "-fPIC", "-std=c++17", "-Wall", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
+                       + [a for d in include for a in ("-isystem", d)] + [src, "-o", MARSHAL, "-L" + os.path.join(torch, "lib")]
+                       + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for {src}:\n{r.stderr}")
+    sys.stderr.write(r.stderr)
+
+
 def build(force: bool = True, jobs: int = 8) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(build_marshal, force)
         objs = list(ex.map(lambda s: _compile(s, force), srcs))
+        marshal.result()
     if force or not os.path.exists(LIB) or any(os.path.getmtime(o) > os.path.getmtime(LIB) for o in objs):
         subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, check=True)
     return LIB
