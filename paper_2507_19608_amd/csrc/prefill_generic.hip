@@ -14,13 +14,15 @@
 //
 // kScans: the keys left of a work group's windows fit into its LDS, so it takes them in and makes them reference keys there for itself
 // (Eq. 2-3), and no launch and no pass through memory comes in front; one more work group per unit writes the mask.  (A block's values
-// and window keys asked for in front of the scan: 11.6 / 11.6 us at 256 rows of 64, 13.4 / 15.0 at 128 of 128, which then spills.)
+// and window keys asked for in front of the scan, when that took 2 us more: 11.6 / 11.6 us at 256 rows of 64, 13.4 / 15.0 at 128 of 128, which then spills.)
 //
 // Matrix-core layout (16x16x4, wave64): A lane l holds row l % 16, k = l / 16; B lane l column l % 16, same k; D lane l
 // column l % 16, rows 4 (l / 16) + r.  Scores are taken transposed (keys x query rows): a lane owns one query row, and
 // register r of a score tile is the B operand of a P V step whose k-th key is 4 k + r.  The contraction over channels runs
 // in the order that lets every operand be a 16-byte load of a row (step e of group s: channel 16 s + 4 (l / 16) + e), and
 // output tile e of a channel group covers the channels VW m + e, so that a lane loads and stores VW consecutive ones.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -62,65 +64,83 @@ __device__ __forceinline__ f32x2 load2(const bf16_t *p) {
     return f32x2{bf16_to_f32(v[0]), bf16_to_f32(v[1])};
 }
 
-// LDS of a work group that scans n rows: these, four floats apart so that 16 rows' reads of one segment lie in different banks; what the runs end
+// A scan of n rows: 2 * 64 * kWavesG / d runs of so many rows each (a multiple of a batch), and the rows of all of them, which end with the last row again
+constexpr int kBatch = 8;
+__host__ __device__ constexpr int run_rows(int n, int d) {
+    const int runs = 2 * 64 * kWavesG / d;
+    return ((n + runs - 1) / runs + kBatch - 1) / kBatch * kBatch;
+}
+__host__ __device__ constexpr int scan_room(int n, int d) { return (n + run_rows(n, d) - 1) / run_rows(n, d) * run_rows(n, d); }
+// LDS of a work group that scans n rows, or fewer: these, four floats apart so that 16 rows' reads of one segment lie in different banks; what the runs end
 // on; three words
-constexpr size_t scan_lds(int n, int d) { return ((size_t)n * (d + 4) + 2 * 64 * kWavesG + 4) * sizeof(float); }
+constexpr size_t scan_lds(int n, int d) { return ((size_t)scan_room(n, d) * (d + 4) + 2 * 64 * kWavesG + 4) * sizeof(float); }
 
-// The reference keys of a unit's rows 0 .. n - 1, in LDS [n][D + 4].  A thread walks a run of rows in two neighbouring channels, from the guess "held
+// The reference keys of a unit's rows 0 .. n - 1, in LDS [scan_room][D + 4].  A thread walks a run of rows in two neighbouring channels, from the guess "held
 // = the row before" kWarm rows earlier; runs whose start is not what the run before has ended on walk again, in rounds, and one last walk puts reference
-// keys in the place of keys (as scan_whole_kernel does).
+// keys in the place of keys (as scan_whole_kernel does).  Runs are whole batches, so that a row costs its read and the three operations of each channel:
+// with the last run's end looked for in every row, 1 head of 64, 256 rows
+// took 11.6 us a call, now 9.8.
 template <int D>
 __device__ __forceinline__ void scan_rows(const float *__restrict__ K, int n, float theta, float *rows) {
-    constexpr int S = D + 4, PR = D / 2, kRuns = 64 * kWavesG / PR, kWarm = 48, N = 8;
-    float2 *const E = (float2 *)(rows + (size_t)n * S);
+    constexpr int S = D + 4, PR = D / 2, kRuns = 64 * kWavesG / PR, kWarm = 48, N = kBatch;
+    const int L = run_rows(n, D), room = scan_room(n, D);
+    float2 *const E = (float2 *)(rows + (size_t)room * S);
     int *const flags = (int *)(E + 64 * kWavesG);                // [2] some run was wrong in an even, odd round
     const int tid = threadIdx.x;
     {
-        const int pieces = n * (D / 4);
-        for (int i0 = tid; i0 < pieces; i0 += N * 64 * kWavesG) {
+        const int pieces = n * (D / 4), all = room * (D / 4);
+        for (int i0 = tid; i0 < all; i0 += N * 64 * kWavesG) {
             f32x4 v[N];
 #pragma unroll
-            for (int k = 0; k < N; ++k) v[k] = load4(K + 4 * (size_t)min(i0 + k * 64 * kWavesG, pieces - 1));
+            for (int k = 0; k < N; ++k) {                        // (rows past the end are the last one again: walked once more it changes nothing)
+                const int i = min(i0 + k * 64 * kWavesG, all - 1);
+                v[k] = load4(K + 4 * (size_t)(i < pieces ? i : pieces - D / 4 + i % (D / 4)));
+            }
 #pragma unroll
-            for (int k = 0; k < N; ++k) {                        // (pieces past the end are the last one again)
-                const int i = min(i0 + k * 64 * kWavesG, pieces - 1);
+            for (int k = 0; k < N; ++k) {
+                const int i = min(i0 + k * 64 * kWavesG, all - 1);
                 *(f32x4 *)(rows + i / (D / 4) * S + i % (D / 4) * 4) = v[k];
             }
         }
         if (tid < 2) flags[tid] = 0;
     }
     __syncthreads();
-    const int run = tid / PR, p = tid % PR, L = (n + kRuns - 1) / kRuns;
-    const int a = run * L, b = min(a + L, n);
+    const int run = tid / PR, p = tid % PR, a = run * L;
     const bool works = a < n;
     float *const mine = rows + 2 * p;
-    // rows t .. end - 1 in order from `held`; with `write` they become what is held
-    auto walk = [&](int t, int end, float2 held, bool write) __attribute__((always_inline)) {
-        float2 k[N], next[N];
+    // rows t .. end - 1 (whole batches) in order from `held`, the next batch's reads issued before this one is worked on; with `write` they become what is held
+    auto walk = [&](int t, int end, float2 held, auto write) __attribute__((always_inline)) {
+        float2 k[2][N];
         auto fetch = [&](float2 (&x)[N], int from) {
+            const float *const r = mine + from * S;
 #pragma unroll
-            for (int u = 0; u < N; ++u) x[u] = *(const float2 *)(mine + min(from + u, n - 1) * S);
+            for (int u = 0; u < N; ++u) x[u] = *(const float2 *)(r + u * S);
         };
-        fetch(k, t);
-        for (; t < end; t += N) {
-            fetch(next, t + N);
+        auto work = [&](const float2 (&x)[N]) {
+            float *const r = mine + t * S;
 #pragma unroll
             for (int u = 0; u < N; ++u) {
-                const bool here = t + u < end;
-                held.x = here && fabsf(k[u].x - held.x) > theta ? k[u].x : held.x;          // Eq. 2 in binary32, Eq. 3
-                held.y = here && fabsf(k[u].y - held.y) > theta ? k[u].y : held.y;
-                if (write && here) *(float2 *)(mine + (t + u) * S) = held;
+                held.x = fabsf(x[u].x - held.x) > theta ? x[u].x : held.x;                  // Eq. 2 in binary32, Eq. 3
+                held.y = fabsf(x[u].y - held.y) > theta ? x[u].y : held.y;
+                if (write) *(float2 *)(r + u * S) = held;
             }
-#pragma unroll
-            for (int u = 0; u < N; ++u) k[u] = next[u];
+            t += N;
+        };
+        if (t < end) fetch(k[0], t);
+        while (t < end) {
+            fetch(k[1], min(t + N, end - N));
+            work(k[0]);
+            if (t >= end) break;
+            fetch(k[0], min(t + N, end - N));
+            work(k[1]);
         }
         return held;
     };
     float2 start = {0.f, 0.f};
     if (works) {
         const int w = max(a - kWarm, 0);                         // (row 0 is the basis row: exact)
-        start = walk(w, a, *(const float2 *)(mine + max(w - 1, 0) * S), false);
-        E[tid] = walk(a, b, start, false);
+        start = walk(w, a, *(const float2 *)(mine + max(w - 1, 0) * S), std::false_type{});
+        E[tid] = walk(a, a + L, start, std::false_type{});
     }
     __syncthreads();
     for (int round = 0; round < kRuns; ++round) {
@@ -133,11 +153,11 @@ __device__ __forceinline__ void scan_rows(const float *__restrict__ K, int n, fl
         if (tid == 0) flags[(round + 1) & 1] = 0;
         if (wrong) {
             start = from;
-            E[tid] = walk(a, b, start, false);
+            E[tid] = walk(a, a + L, start, std::false_type{});
         }
         __syncthreads();
     }
-    if (works) walk(a, b, start, true);
+    if (works) walk(a, a + L, start, std::true_type{});
     __syncthreads();
 }
 
@@ -146,7 +166,7 @@ __device__ __forceinline__ void scan_rows(const float *__restrict__ K, int n, fl
 template <int D>
 __device__ __forceinline__ void write_mask(const float *rows, int n, uint32_t *__restrict__ mask, uint64_t *__restrict__ nnz) {
     constexpr int S = D + 4, WPR = D / 32;
-    uint32_t *const total = (uint32_t *)(rows + (size_t)n * S + 2 * 64 * kWavesG) + 2;
+    uint32_t *const total = (uint32_t *)(rows + (size_t)scan_room(n, D) * S + 2 * 64 * kWavesG) + 2;
     if (threadIdx.x == 0) *total = 0;
     __syncthreads();
     uint32_t fired = 0;

@@ -23,6 +23,15 @@ def test_small_fp32_prompts(window_mode, d, B, Hq, Hkv, n, W):
     run_case(Q, K, V, 0.15, W, "f32", da.DA_SCORE_GATHER, window_mode=window_mode)
 
 
+@pytest.mark.parametrize("d,n", [(64, n) for n in (7, 8, 9, 127, 128, 129, 383, 384, 385)] + [(128, n) for n in (8, 63, 64, 65, 191, 192, 193)])
+def test_runs_of_whole_batches(d, n):
+    """Runs of 8, 16, .. rows that end with the prompt, one row before and one behind: the same masks and counts as the scan's own entry point."""
+    Kd = to_dev(rand_walk(n, 1, 1, n, d), "f32")
+    mask, nnz, _ = da.delta_attn_delta_scan(Kd, 0.2)
+    _, mask2, nnz2 = da.delta_attn_prefill(Kd, Kd, Kd, 0.2, 1)
+    assert torch.equal(mask, mask2) and torch.equal(nnz, nnz2)
+
+
 @pytest.mark.parametrize("kind", ["still", "drift", "jumps", "zeros", "nan"])
 @pytest.mark.parametrize("d,n", [(64, 300), (128, 200)])
 def test_the_same_mask_as_the_scan_alone(kind, d, n):
