@@ -19,17 +19,21 @@
 // What bounds it: matrix cores and vector ALU take turns.  A block of 64 keys costs a wave 1088 cycles of matrix work at
 // head_dim 128 (512 at 64) and about 590 of issue for softmax and addresses, so a SIMD is only busy if one of its two waves multiplies while the
 // other takes exponentials.  The waves therefore run in two groups half a block apart (waves 0-3 and 4-7, one of each per
-// SIMD), handed from phase to phase by barriers:
-//     A: | PV(b-1) S(b) | softmax(b)   | PV(b) S(b+1) | ...
-//     B:                | PV(b-1) S(b) | softmax(b)   | ...
+// SIMD), with one barrier for every block (|), group A's before its matrix phase and group B's before its vector phase:
+//     A: | PV(b-1) S(b)   softmax(b)    | PV(b) S(b+1) softmax(b+1) |
+//     B: | softmax(b-1)   PV(b-1) S(b)  | softmax(b)   PV(b) S(b+1) |
+// Between two barriers a wave goes from phase to phase by itself: a block takes the sum of its two phases, not twice the longer one, as it did with
+// a barrier between them (4 x 8192 tokens, 20 / 5 heads of 128: 2590 -> 2480 clocks a block and pair of waves; 38 shapes 1.00 to 1.07 times as
+// fast, 1.03 on the geometric mean).  What the tiles need for that: three of each kind, requested up to two turns ahead.  Where every group has its own
+// there is room for two, and the next ones can only be requested behind the barrier, by all waves at once; see kLate.
 // A wave in its matrix phase goes first (s_setprio): it issues one instruction in 32 clocks, and every one that has to wait for
-// the other wave's arithmetic lengthens the phase.  What is added to a matrix phase - addresses, loads, the look at the masks -
+// the other wave's arithmetic lengthens the phase (without it 5 % more clocks).  What is added to a matrix phase - addresses, loads, the look at the masks -
 // comes out at more than it saves in the vector phase: its instructions wait in order for whatever is issued between them.
-// Counters on 4 x 8192 tokens, 20 / 5 heads of 128: 1.96 M clocks a launch, 1520 a phase, of which one wave's matrix instructions
+// Counters on 4 x 8192 tokens, 20 / 5 heads of 128, with the barrier between the phases: 1.96 M clocks a launch, 1520 a phase, of which one wave's matrix instructions
 // fill 1088 and the other wave's vector instructions 586; with row sums by dot products on the vector ALU and the maximum of every block 2.08 M and 1610
 // (692 of issue).  Before that, with the priority the other way round, a branch and an address for every
 // load, fmaxf, a wait where the next tile is asked for, a pause between tiles and queries and outputs in pieces it was 2.43 M; of 15 %
-// fewer clocks 7 % are left in time (1344 -> 1256 us a call, in turn on one card): the clock goes down under this load, to 1.7 of 2.4 GHz.
+// fewer clocks 7 % are left in time (1344 -> 1256 us a call, in turn on one card): the clock goes down under this load, to 1.6 of 2.4 GHz.
 //
 // kStream: where many whole tiles, or long ones, follow each other on a compute unit, the next one's first keys and queries are
 // requested, and its first scores taken, while the last one's values are still added up and its outputs stored.  Pausing / not: 1 x 4096
@@ -47,7 +51,7 @@
 // Figures here and below for up to 416 rows of 64 or 200 of 128 (16 x 200, 14 x 200, 64 x 64, 133 x 64, 512 x 64, 55 x 130, 1 x 333 tokens) were taken when
 // prompts of such lengths still came here in one call.  These have a kernel of their own now (prefill_short.hip); pieces of a prompt of such lengths come here.
 //
-// Tiles go from global memory to LDS directly (global_load_lds, 16 bytes per lane, no registers), row-major, two blocks ahead
+// Tiles go from global memory to LDS directly (global_load_lds, 16 bytes per lane, no registers), row-major, up to two blocks ahead
 // in three buffers, or two where every group has its own.  The 16-byte segments of a row are permuted by the row number so that the reads are free of bank
 // conflicts: keys by 128-bit reads down a column of rows, values by transposing reads (ds_read_b64_tr_b16: lane j of 16
 // receives channel j of four key rows whose 8-byte pieces the 16 lanes address), which is why V needs no re-ordering launch.
@@ -102,7 +106,7 @@ struct MfmaArgs {
 // kind's end.  a: the kernel's argument, of which the walk keeps a few words in registers.  None of these kernels
 // may spill: a ticket of the queue is on its way into its register while other things are done, and a copy of that would be one of the old value
 // (a build in which one does fails).
-template <int D, int kSplit, bool kStream>
+template <int D, int kSplit, bool kStream, bool kLate>
 __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *lds_raw) {
     constexpr int kRowB = D * 2;                // bytes of a row
     constexpr int kSeg = D / 8;                 // 16-byte segments of a row
@@ -331,7 +335,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 }
             }
         };
-        constexpr int kAhead = D == 64 ? 4 : 5;
+        constexpr int kAhead = D == 64 ? 3 : 4;
         const u32x4 ones = {one, one, one, one};
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};                        // (the lane's row, in every register)
         for_each_index<nv + nk + kAhead>([&](auto i) {
@@ -450,9 +454,11 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
     };
 
     // ---- the walk.  The tiles of turn t lie in buffers t % kBufs.  The key tile of turn t + 2 and the value tile of turn t + 1 are
-    //      requested in turn t's vector phase, when no wave reads what those buffers held any more - the other group is at
-    //      most one phase behind, or, with kSplit = 2, has rows of its own in every tile - and are waited for two phases later.
-    //      (A fourth buffer, and requests a turn earlier, changed nothing.)
+    //      requested in turn t's vector phase.  With three buffers nobody reads what those held any more: it was last read in turn t - 1's matrix
+    //      phase, and a barrier lies between.  They have landed before the barrier in front of turn t + 2: group A waits for them at the end of turn t + 1's vector phase, group B
+    //      at its beginning, in front of the same barrier.  (A fourth buffer, and requests a turn earlier, changed nothing.)
+    //      With kSplit = 2 a group reads rows of its own, in two buffers: a barrier more, between matrix and vector phase, frees them, or (kLate) the
+    //      requests wait for the turn's one.
     const char *values;                                          // whose value rows are requested next
     int values_row;
     constexpr std::true_type yes;
@@ -511,11 +517,12 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         if (asks && wave == 0 && lane_here() == 0)
             asm volatile("s_nop 4\n\tglobal_atomic_add %0, %1, %2, %3 sc0" : "+v"(ticket) : "v"(0), "v"(1), "s"(queue) : "memory");
     };
+    int flip = 0;                               // (kStream) two words in turn: wave 0 may be about to write one while group B still reads the other
     // ... and tells the others, once it has waited for the answer; `total`: there is none
     auto tell = [&]() __attribute__((always_inline)) {
-        if (wave == 0 && lane_here() == 0) *next_tile = asks ? handed_out + queues * (int)ticket : total;
+        if (wave == 0 && lane_here() == 0) next_tile[flip] = asks ? handed_out + queues * (int)ticket : total;
     };
-    auto told = [&]() __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(*next_tile); };
+    auto told = [&]() __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(next_tile[flip]); };
 
     if constexpr (kStream) {
         // A finished tile's outputs, from row `from` on, turned in LDS behind the tiles into whole rows, each wave its own, half of the
@@ -564,17 +571,17 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         if (early) tell();
         phase_barrier();
         staged_queries();
-        if (grp == 1) phase_barrier();                           // group B starts one phase later
+        phase_barrier();                                         // (their area is free)
         matrix_phase(no, yes, 0, 0);
         while (true) {
-            // the key tile of turn + 1 and the value tile of turn, which group A is about to read (loads and stores end in order)
+            // the key tile of turn + 1 and the value tile of turn (loads and stores end in order)
             if (grp == 1) {
                 if (stored)
                     wait_loads<2 * kHStores>();
                 else
                     wait_loads<0>();
+                phase_barrier();
             }
-            phase_barrier();
             __builtin_amdgcn_s_setprio(0);
             const bool last = turn == at_turns - 1;
             if (last && ahead) load_queries();                   // (nobody multiplies by the old ones any more)
@@ -584,6 +591,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                     open_tile(next);
                     ahead = true;
                     opened = 0;
+                    flip ^= 1;
                 }
             }
             request(opened, after(after(buf)), after(buf));
@@ -606,7 +614,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             have_queries();
             if (telling) tell();
             if (asking) ask();
-            phase_barrier();
+            if (grp == 0) phase_barrier();
             const int prev = buf;
             buf = after(buf);
             if (last && !ahead) break;
@@ -630,8 +638,10 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 const char *vals = Vp + (size_t)(uint32_t)values_row * kRowB;
                 const int from = turn;
                 for (; turn < at_steady; ++turn) {
-                    if (grp == 1) wait_loads<0>();
-                    phase_barrier();
+                    if (grp == 1) {
+                        wait_loads<0>();
+                        phase_barrier();
+                    }
                     __builtin_amdgcn_s_setprio(0);
                     const int prev = buf, far = after(after(buf));
                     buf = after(buf);
@@ -641,8 +651,10 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                     vals += KB * kRowB;
                     softmax(turn, no);
                     __builtin_amdgcn_s_setprio(1);
-                    if (grp == 0) wait_loads<kLoads>();
-                    phase_barrier();
+                    if (grp == 0) {
+                        wait_loads<kLoads>();
+                        phase_barrier();
+                    }
                     matrix_phase(yes, yes, prev, buf);
                 }
                 opened += turn - from;
@@ -652,24 +664,42 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             }
         }
         matrix_phase(yes, no, buf == 0 ? kBufs - 1 : buf - 1, 0);
-        if (grp == 0) phase_barrier();                           // (group B's last vector phase)
         wait_loads<0>();                                         // no load into LDS outlives the work group
         const float inv = 1.f / row_sum();
         if (taken < n) store_rows(out_rows, wave_first, inv);
         return told();
     } else {
+        // kLate: one barrier a turn with two tiles of each kind, the next ones requested behind it.  A work group that has its compute unit for itself is done
+        // sooner (32 / 8 heads of 64, 2048 tokens: 2711 -> 2567 clocks a turn); of two that share one the first is not so far ahead of the second any
+        // more (1.53 and 2.9 us a turn -> 1.75 and 2.7), see launch_d.  At head_dim 128 64 KB at once take the address path longer than is saved (3046 -> 3430).
+        static_assert(!kLate || kSplit > 1, "whole tiles have the room");
         auto vector_phase = [&](int turn) __attribute__((always_inline)) {
-            if (kSplit == 1 && grp == 1) wait_loads<0>();        // key tile turn + 1, value tile turn, which group A is about to read
-            phase_barrier();
+            auto ends_turn = [&]() __attribute__((always_inline)) {
+                wait_loads<0>();                                 // key tile turn + 1, value tile turn
+                phase_barrier();
+            };
+            auto requests = [&]() __attribute__((always_inline)) { request(turn + 2, after(after(buf)), after(buf)); };
+            if (kSplit == 1 || kLate) {
+                if (grp == 1) ends_turn();
+            } else {
+                phase_barrier();
+            }
             __builtin_amdgcn_s_setprio(0);
-            request(turn + 2, after(after(buf)), after(buf));
+            if (!kLate || grp == 1) requests();
             softmax(kSplit == 1 ? turn : turn * kSplit + grp, yes);
             // asked for three turns before the tile ends: whoever asks first gets the longest tile left (behind the turn's
             // loads: a wait for older ones then does not wait for it)
             if (turn == max(turns - 3, 0)) ask();
             __builtin_amdgcn_s_setprio(1);                       // (for the matrix phase that follows)
-            if (kSplit > 1 || grp == 0) wait_loads<kLoads>();
-            phase_barrier();
+            if constexpr (kLate) {
+                if (grp == 0) {
+                    ends_turn();
+                    requests();
+                }
+            } else if (kSplit > 1 || grp == 0) {
+                wait_loads<kLoads>();
+                phase_barrier();
+            }
         };
         open_tile(pos);
         stage_queries();
@@ -681,7 +711,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             buf = 0;
             phase_barrier();
             staged_queries();
-            if (grp == 1) phase_barrier();                       // group B starts one phase later
+            if (kSplit == 1 || (!kLate && grp == 1)) phase_barrier();   // (the area is free; group B starts one phase later)
             matrix_phase(no, yes, 0, 0);
             vector_phase(0);
             for (int turn = 1; turn < turns; ++turn) {
@@ -691,7 +721,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
                 vector_phase(turn);
             }
             matrix_phase(yes, no, buf, 0);
-            if (grp == 0) phase_barrier();                       // (group B's last vector phase)
+            if (kSplit > 1 && !kLate && grp == 0) phase_barrier();   // (group B's last vector phase)
             wait_loads<0>();                                     // no load into LDS outlives its tile
             const float l_tot = row_sum();
             tell();
@@ -789,13 +819,13 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 // Behind the tiles come the chunks that a cache is handed (fill_chunk), for whoever is done with the tiles or has none: a piece of a
 // prompt, or a short one, leaves compute units idle, and the hand-off's own launch took 9 us of each.
 // (kernels of their own: with the look for such a chunk at its end every other launch took 0.5 to 1 us longer.)
-template <int D, bool kStream, typename... Fill>                 // Fill: CacheFill, or nothing
+template <int D, bool kStream, typename... Fill>                 // kStream: at head_dim 64 kLate; Fill: CacheFill, or nothing
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(MfmaArgs a, Fill...) {
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
     int pos = blockIdx.x;
     if (pos >= a.turn_at && pos < a.blocks) pos = a.blocks - 8 - ((pos - a.turn_at) & ~7) + (pos & 7);
-    if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2, false>(a, pos, lds_raw);
-    if (pos < a.kinds[0].end) pos = tiles_of_kind<D, 1, kStream>(a, pos, lds_raw);
+    if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2, false, kStream && D == 64>(a, pos, lds_raw);
+    if (pos < a.kinds[0].end) pos = tiles_of_kind<D, 1, kStream && D == 128, false>(a, pos, lds_raw);
     if constexpr (sizeof...(Fill) == 0) return;
     // (the arguments of what follows are read here: in registers from the start on they would push others out across the walk)
     typedef const __attribute__((address_space(4))) char arg_char;
@@ -973,16 +1003,22 @@ void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     // average, -4 to 12 (32 / 8 heads: 512 x 64 83.6 / 80.5, 55 x 130 32.9 / 36.9, 16 x 700 61.8 / 64.1, 12 x 1024 82.4 / 86.0, 8 x 1500 106 / 107,
     // 4 x 4096 306 / 306).
     const int64_t whole_tiles = (int64_t)columns * a.kinds[0].tiles;
-    const bool stream = D == 128 && (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
+    // At head_dim 64 instead: one barrier a turn for split tiles, too (kLate), where all tiles are resident at once, or so many follow that it does not matter which
+    // of the two work groups of a compute unit is done first; between that the longest tiles, which came first, would end last.  Two barriers / one: 512 tiles,
+    // 1 x 2048 tokens of 32 / 8 heads 41.1 / 40.1 us, 1 x 4096 of 16 / 2 63.3 / 61.9, 1 x 8192 of 8 / 8 115 / 112; 532, 1 x 5000 of 16 / 2 90.9 / 86.5; 552, 1 x 6000 113 / 115;
+    // 592, 1 x 3000 of 32 / 8 67.0 / 68.9; 624, 3 x 4000 of 8 / 8 92.6 / 106; 816, 1 x 8192 of 16 / 2 189 / 211; 925, 1 x 8000 of 20 / 5 205 / 221; 1010, 2 x 5003
+    // 175 / 171; 1024, 1 x 6000 of 32 / 8 206 / 200.
+    const bool stream = D == 64 ? 20 * (int64_t)a.blocks <= 21 * slots || 20 * (int64_t)a.blocks >= 39 * slots
+                                : (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
     const dim3 grid(a.total < slots ? a.total : slots), block(512);
     static std::atomic<uint64_t> lds_set[4];                     // per instantiation, one bit per device
     if (fill) {
-        const auto kernel = stream ? prefill_mfma_kernel<D, D == 128, CacheFill> : prefill_mfma_kernel<D, false, CacheFill>;
+        const auto kernel = stream ? prefill_mfma_kernel<D, true, CacheFill> : prefill_mfma_kernel<D, false, CacheFill>;
         ensure_dynamic_lds((const void *)kernel, lds, lds_set[2 + stream]);
         hipLaunchKernelGGL(kernel, grid, block, lds, s, a, *fill);
         return;
     }
-    const auto kernel = stream ? prefill_mfma_kernel<D, D == 128> : prefill_mfma_kernel<D, false>;
+    const auto kernel = stream ? prefill_mfma_kernel<D, true> : prefill_mfma_kernel<D, false>;
     ensure_dynamic_lds((const void *)kernel, lds, lds_set[stream]);
     hipLaunchKernelGGL(kernel, grid, block, lds, s, a);
 }
