@@ -71,3 +71,24 @@ def test_plans_of_four_walkers_against_the_oracle(slots, n, steps, Hq, theta):
     L = n + steps
     Q, K, V = rand_walk(81, 2, Hq, L, 64), rand_walk(82, 2, 1, L, 64), rand_walk(83, 2, 1, L, 64, clip=3.5)
     run_decode(Q, K, V, n, steps, theta, 100, "bf16", plan=(-1, slots))
+
+
+@pytest.mark.parametrize("d,Hq", [(64, 6), (64, 16), (128, 2), (128, 6), (128, 16)])
+@pytest.mark.parametrize("parts", [2, 4, 5, 8, 9, 16, 17, 32])
+def test_parts_of_a_unit_agree(d, Hq, parts):
+    """Work groups of a unit, as many as a batch of the last one's reads takes, one more, and the most there are: each has one
+    turn of its walkers, the last one a chunk of few rows."""
+    Hkv, steps, theta, walkers = 2, 2, 0.2, 512 // d
+    n = 64 * (walkers * (parts - 1) + 1) + 5
+    x = [to_dev(rand_walk(s, 1, H, n + steps, d, clip=c), "bf16") for s, H, c in ((5, Hq, None), (6, Hkv, None), (7, Hkv, 3.5))]
+    caches = [da.Cache(1, Hq, Hkv, d, n + steps, 64, theta, torch.bfloat16) for _ in range(2)]
+    for cache, merge in zip(caches, (0, 1)):
+        cache.set_launch_plan(merge, 8 * Hkv * parts)
+        da.delta_attn_prefill(*(t[:, :, :n].contiguous() for t in x), theta, 64, cache=cache)
+    for i in range(n, n + steps):
+        row = [t[:, :, i].contiguous() for t in x]
+        (o, m), (o1, m1) = [da.delta_attn_decode(cache, *row) for cache in caches]
+        assert torch.isfinite(o).all() and torch.equal(m, m1)
+        assert (o.float() - o1.float()).abs().max().item() <= 4 * (2 ** -8 + 2 ** -9) / 2 + 2 ** -8
+    for cache in caches:
+        cache.close()
