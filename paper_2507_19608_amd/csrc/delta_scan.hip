@@ -425,13 +425,15 @@ __global__ __launch_bounds__(512) void scan_segments_kernel(ScanArgs<T> g, Copy.
 // ---- One launch for a prompt of up to some thousand rows: a work group takes a few channels (DL = 8, 16 or 32) of every row of
 // a unit, so that all of a prompt's rows lie in one LDS and nothing has to be settled between work groups, and the channels of
 // one unit still spread over many compute units.  A thread walks one run of L rows in two neighbouring channels (two
-// chains: one alone leaves every other issue slot empty); runs start from the guess "held = the row before", and the ends
-// travel from run to run in rounds as above, but nothing is written in a round: a wrong run of L rows is walked again whole, and
-// one last walk puts the reference keys in the place of the keys.  The mask is what the reference keys say: an entry has fired
+// chains: one alone leaves every other issue slot empty); runs start from the guess "held = the row before".  The ends travel from run to run,
+// at first in rounds as above, but nothing is written in a round: a wrong run of L rows is walked again whole.  A round moves a chain on by one run and lasts as long as
+// 32 rows' walk, also where few chains are wrong, so that after one round or none a wave per channel takes them in order.  One last walk puts the reference keys in
+// the place of the keys.  The mask is what the reference keys say: an entry has fired
 // where a row differs from the one before (it fires only if |k - held| > theta >= 0, and then holds k).
 // A thread then has a row in registers: it goes out with its mask bits.  What bounds it: 50 clocks per row and two channels in the chain,
 // 48 rows of it and a run's own, the rest is latency; 8 x 1024 rows of 64: rows in LDS after 1.2 us, walked after 3.2, settled 3.5, replaced
-// 4.2, out 5.4.
+// 4.2, out 5.4.  Rounds alone / this, the scan's launches of 8 x 2048 rows of 64 back to back: 5 % jumps 13.3 / 12.0, threshold 0.2 17.8 / 13.9, 1 % 15.4 / 12.6,
+// 1 % and 0.2 31.2 / 17.8, 20 % 11.2 / 11.1; 5 x 4096 of 128 17.8 / 17.4, 21.2 / 19.2, 19.1 / 17.9, 30.7 / 23.8, 16.7 / 16.7.
 template <typename T>
 struct WholeArgs {
     const T *__restrict__ K;
@@ -445,6 +447,7 @@ struct WholeArgs {
     float theta;
     int ld;                              // rows of room per unit in Khat
     int blocks;                          // work groups that scan
+    int rounds;                          // before the rest settles in order
 };
 
 template <typename T> struct TwoRaw;
@@ -499,7 +502,8 @@ __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy...
     auto run_of = [&](int t) { return (int)(__umulhi(2u * (uint32_t)t, g.by_l_mul) >> g.by_l_shift); };
     uint4 *const rows = (uint4 *)lds_w + P;                      // piece q of row t: rows[(t + run_of(t)) * P + q]
     float2 *const E = (float2 *)(rows + (size_t)runs * (L + 1) * P);   // [runs][PR]
-    uint32_t *const flags = (uint32_t *)(E + runs * PR);         // [2] some run was wrong in an even, odd round
+    float2 *const S = E + runs * PR;                             // [runs][PR] what the runs have been walked from
+    uint32_t *const flags = (uint32_t *)(S + runs * PR);         // [2] some run was wrong in an even, odd round
     uint32_t *const total = flags + 2;
     const T *Kp = g.K + (size_t)unit * n * g.d + ch0;
     const int gpr = g.d / kPer;                                  // pieces of a row in memory
@@ -568,19 +572,57 @@ __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy...
         E[tid] = walk_rows(a, a + L, start);
     }
     __syncthreads();
-    for (int round = 0; round < runs; ++round) {
+    bool settled = false;
+    for (int round = 0; round < g.rounds; ++round) {
         float2 from = start;
         if (works && run > 0) from = E[tid - PR];
         const bool wrong = __float_as_uint(from.x) != __float_as_uint(start.x) || __float_as_uint(from.y) != __float_as_uint(start.y);
         if (__any(wrong) && (tid & 63) == 0) flags[round & 1] = 1;
         __syncthreads();                                         // (also: every run has read the end of the one before)
-        if (!flags[round & 1]) break;
+        settled = !flags[round & 1];
+        if (settled) break;
         if (tid == 0) flags[(round + 1) & 1] = 0;
         if (wrong) {
             start = from;
             E[tid] = walk_rows(a, a + L, start);
         }
         __syncthreads();
+    }
+    // What is left, in order, a wave per channel: its lanes hold the rows of a run and say which of them fire, so that a row that does not fire costs
+    // nothing (60 clocks a row that does, 60 a run; in a round 50 a row of the longest chain's run, and two barriers).
+    if (!settled) {
+        if (works) S[tid] = start;
+        __syncthreads();
+        float *const ends = (float *)E;                          // [runs][DL]
+        const float *const starts = (const float *)S;
+        const int lane = tid & 63;
+        for (int c = __builtin_amdgcn_readfirstlane(tid >> 6); c < DL; c += threads >> 6) {
+            for (int r0 = 1; r0 < runs; r0 += 64) {
+                const int mine = min(r0 + lane, runs - 1);       // a lane per run: what it should start from, and did
+                int from = __float_as_int(ends[(mine - 1) * DL + c]);
+                const int guess = __float_as_int(starts[mine * DL + c]);
+                uint64_t wrong = __ballot(r0 + lane < runs && from != guess);
+                while (wrong) {
+                    const int i = __builtin_ctzll(wrong), r = r0 + i;
+                    wrong &= wrong - 1;
+                    const float k = load_f32((const T *)(rows + (size_t)r * (L + 1) * P), (size_t)(min(lane, L - 1) * DL + c));
+                    int held = __builtin_amdgcn_readlane(from, i);
+                    uint64_t fires = __ballot(lane < L && fabsf(k - __int_as_float(held)) > theta);
+                    while (fires) {
+                        const int t = __builtin_ctzll(fires);
+                        held = __builtin_amdgcn_readlane(__float_as_int(k), t);
+                        fires = __ballot(lane < L && fabsf(k - __int_as_float(held)) > theta) & (~1ull << t);
+                    }
+                    if (lane == 0) ends[r * DL + c] = __int_as_float(held);
+                    if (i < 63 && r + 1 < runs) {                // (the 64 runs behind these ask for their starts themselves)
+                        from = lane == i + 1 ? held : from;
+                        wrong = (wrong & ~(2ull << i)) | (held != __builtin_amdgcn_readlane(guess, i + 1) ? 2ull << i : 0ull);
+                    }
+                }
+            }
+        }
+        __syncthreads();
+        if (works && run > 0) start = E[tid - PR];
     }
     if (works) {
         Raw *r = (Raw *)(rows + (size_t)run * (L + 1) * P) + p;
@@ -853,7 +895,7 @@ static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *m
 
 // What a launch of scan_whole_kernel looks like; L == 0: the prompt is none for it.
 struct WholePlan {
-    int dl, threads, L, warm;
+    int dl, threads, L, warm, rounds;
     size_t lds;
 };
 // Few channels per work group where there are few units, more where the work groups would not all be resident (every work group reads
@@ -872,7 +914,7 @@ struct WholePlan {
 static WholePlan whole_plan(int dtype, int units, int n, int d) {
     const int es = dtype == 0 ? 4 : 2;
     const int64_t cus = device_cu_count();
-    WholePlan p = {8, 256, 0, 0, 0};
+    WholePlan p = {8, 256, 0, 0, 0, 0};
     if (n < 64 || (int64_t)n * p.dl * es > 64 * 1024) return p;
     if (4 * (int64_t)units >= 3 * cus && (int64_t)n * d * es > 64 * 1024 && (int64_t)n * d * es <= 128 * 1024) return p;
     const auto groups = [&](int dl) { return (int64_t)units * (d / dl); };
@@ -883,8 +925,13 @@ static WholePlan whole_plan(int dtype, int units, int n, int d) {
     const int runs = p.threads / (p.dl / 2);
     p.L = ((n + runs - 1) / runs + 7) / 8 * 8;
     p.warm = groups(p.dl) <= cus ? 48 : 32;
+    // (A wave per channel settles, where it takes no other work group's time: a batch of 150 x 700 rows of 128 74.5 us a call with 4 waves, 77 with 8.)
+    if (p.dl == 8 && groups(8) <= cus) p.threads = 512;
+    // One round first / none: 8 x 2048 rows of 64 12.5 / 12.0 (1 % jumps 13.0 / 12.6, and threshold 0.2 17.0 / 17.8), 10 x 1024 of 128 30.4 / 30.5 a call; where a wave has
+    // many runs or channels, 5 x 4096 of 128 17.5 / 17.3 (17.9 / 17.8, 23.8 / 27.1), 150 x 700 of 128 74.5 / 77.4 a call.
+    p.rounds = groups(p.dl) > cus || n > 2048;
     const int used = (n + p.L - 1) / p.L;
-    p.lds = (size_t)(used * (p.L + 1) + 1) * p.dl * es + (size_t)used * p.dl * 4 + 16;
+    p.lds = (size_t)(used * (p.L + 1) + 1) * p.dl * es + (size_t)used * p.dl * 8 + 16;
     return p;
 }
 
@@ -909,7 +956,7 @@ static void whole_scan(const WholePlan &p, const void *K, void *Khat, uint32_t *
     while ((1u << l) < (uint32_t)p.L) ++l;
     const WholeArgs<T> a = {(const T *)K, (T *)Khat, mask_bits, counts, (const T *)init, zeroed, units, n, d, p.L, p.warm,
                             (uint32_t)((((uint64_t)1 << (31 + l)) / (uint64_t)p.L) + 1u), l, theta,
-                            copy ? copy->ld : n, 8 * (d / p.dl) * ((units + 7) / 8)};
+                            copy ? copy->ld : n, 8 * (d / p.dl) * ((units + 7) / 8), p.rounds};
     if (p.dl == 8)
         whole_typed<T, 8>(a, p, copy, s);
     else if (p.dl == 16)

@@ -62,3 +62,19 @@ def test_segments_of_384_rows(units, n, d):
         ref_khat, ref_mask = df.reference_keys(K, 0.3)
         assert (khat.double() == ref_khat).all() and (df.unpack_bits(bits, d) == ref_mask).all(), kind
         assert (nnz == ref_mask.sum(dim=(2, 3))).all(), kind
+
+
+@pytest.mark.parametrize("dtype,units,d", [("bf16", 3, 64), ("f32", 1, 32), ("bf16", 40, 128)])
+@pytest.mark.parametrize("runs", [2, 3, 64, 65, 66, 128])
+def test_runs_in_order(dtype, units, d, runs):
+    """Runs of 32 rows whose ends travel in order, 64 of them at a time: the first run of the next 64, and of those behind; channels that never
+    meet their guess, that meet it in most runs and that fire in every one; with and without a round in front."""
+    n = 32 * runs - 5
+    if n * 8 * (2 if dtype == "bf16" else 4) > 64 * 1024 or n < 64:
+        n = 64 if n < 64 else 2048
+    for kind, theta in (("quiet", 0.3), ("mixed", 0.3), ("drift", 0.3), ("drift", 0.02)):
+        K = _keys(kind, n + d, units, n, d, dtype)
+        _, bits, nnz = da.delta_attn_prefill(K, K, K, theta, 32)
+        _, ref_mask = df.reference_keys(K, theta)
+        assert (df.unpack_bits(bits, d) == ref_mask).all(), (kind, theta)
+        assert (nnz == ref_mask.sum(dim=(2, 3))).all(), (kind, theta)
