@@ -904,10 +904,10 @@ struct WholePlan {
 // One launch here / segments, and their settling where there are several, us, without the 1.5 us between these two (5 % jumps): 8 x 333 rows of 64 6.5 / 9.1,
 // 80 x 200 of 128 9.4 / 10.3, 8 x 1024 of 64 9.2 / 13 - 16, 8 x 2048 of 64 11.5 / 14 + 3.9, 10 x 1024 of 128 8.5 / 10 + 3.8, 5 x 4096 of 128
 // 15.7 / 12.5 + 4.8, 20 x 4096 24.5 / 22 + 4.9, 160 x 700 20.9 / 25.6 + 5.4, 256 x 2048 of 64 39.9 / 43.8 + 4.8; fp32, 1 x 256 rows of 64 5.0 / 7.5, 4 x
-// 1000 7.1 / 9.3 + 3.8, 16 x 2000 of 128 15.8 / 13.7 + 4.3.  Beyond, 10 x 5003 rows of 128 (80 KB a work group) 23.5 / 14.6 + 4.8.  With 1 % jumps, where
-// more guesses are wrong, 8 x 2048 of 64 12.7 / 16 + 4 to 19.  There is no walk in order here for ends that travel one run a round (up to 128
-// rounds): where nothing fires for the whole prompt 8 x 2048 of 64 takes 84 / 18 + 141, 5 x 4096 of 128 179 / 23 + 294, 256 x 2048 of 64 228 / 101 + 168,
-// 100 x 1500 of 128 174 / 69 + 130; keys that drift 20 / 18 + 33, 28 / 23 + 51, 65 / 84 + 29, 57 / 52 + 29.
+// 1000 7.1 / 9.3 + 3.8, 16 x 2000 of 128 15.8 / 13.7 + 4.3.  Beyond, 10 x 5003 rows of 128 (80 KB a work group) 23.5 / 14.6 + 4.8.  Where more guesses are wrong, calls with scans in rounds
+// alone / settling in order, us: 1 % jumps and threshold 0.2, 8 x 2048 of 64 68.0 / 44.0, 10 x 1024 of 128 49.5 / 37.3, 20 x 4096 145 / 135, 160 x 700 98 / 88, 256 x 2048 of
+// 64 274 / 254; where nothing fires for the whole prompt 143 / 44, 77 / 38, 311 / 130, 101 / 74, 391 / 244; keys that drift 113 / 49, 80 / 49, 354 / 179,
+// 122 / 119, 424 / 293.
 // Where there are about as many units as compute units (three quarters and more), and one's rows are 64 to 128 KB, a work group per unit reads whole rows and
 // needs no second wave of work groups: 256 x 700 rows of 64 18.7 here / 17.2 there, 256 x 400 of 128 19.9 / 17.2, 200 x 900 of 64 18.4 / 16.7, 256 x 1000 22.5 /
 // 23.4; but 256 x 400 of 64 13.3 / 19.0, 160 x 500 of 128 16.5 / 17.4.
