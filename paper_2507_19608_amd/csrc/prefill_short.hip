@@ -22,9 +22,10 @@ namespace {
 
 typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 typedef __attribute__((address_space(3))) uint32_t *lds_word;
+typedef __attribute__((address_space(3))) uint16_t *lds_half;
 
 constexpr int NW = 8;                    // waves of a work group
-constexpr int kScanWaves = 4;            // of these walk keys (one a SIMD: eight waves and shorter runs took as long at 16 x 200 tokens, within 1 %)
+constexpr int kScanWaves = 4;            // of these walk keys, one a SIMD (eight waves and shorter runs took as long at 16 x 200 tokens, within 1 %)
 template <int D> constexpr int kMostRows = D == 64 ? 416 : 200;              // so that three arrays fit (short_lds)
 
 struct ShortArgs {
@@ -40,7 +41,7 @@ struct ShortArgs {
     int rt_log2;                         // an item is this many rows of 32 >> rt_log2 heads
     int row_groups, items;               // of a unit
     int parts, mask_part;                // work groups that share a unit's items; the one that writes its mask
-    int L, warm;                         // rows of a run of the scan, and before it: multiples of 8
+    int L0, L, warm;                     // rows of the scan's first run, of a later one, and before that: multiples of 8
     Divisor by_units, by_hkv, by_hgroups, by_w;
     float scale_log2, theta;
 };
@@ -64,7 +65,7 @@ template <int D, int kSplit>
 __global__ __launch_bounds__(64 * NW, 2) void prefill_short_kernel(ShortArgs a) {
     constexpr int kRowB = 2 * D, kSeg = D / 8, kRpl = 64 / kSeg;    // bytes and 16-byte segments of a row; rows of a 1 KiB load
     constexpr int KS = D / 16, MT = D / 32;
-    constexpr int kPairs = D / 2, kRuns = kScanWaves * 64 / kPairs;   // threads of a run of the scan, runs
+    constexpr int kRuns = kScanWaves * 64 / D;                   // runs of the scan
     constexpr uint32_t kDist = kMostRows<D> * kRowB;             // from a key to its reference key (an instruction's own offset)
     constexpr int kGroups = NW / kSplit;                         // of waves that take an item
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
@@ -118,25 +119,23 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_short_kernel(ShortArgs a) 
     const int at_first = wave / kSplit;
     if (tid < 4) words[tid] = tid == 2 ? kGroups : 0;
 
-    // ---- Eq. 2-3.  A thread walks one run of L rows in two neighbouring channels.  Runs after the first start from the guess "held =
-    //      the row before" some rows earlier; one whose guess was wrong walks again, until it meets what it has written.
+    // ---- Eq. 2-3.  A thread walks one run of rows in one channel.  Runs after the first start from the guess "held =
+    //      the row before" some rows earlier; one whose guess was wrong walks again, until it meets what it has written.  (Two neighbouring channels a thread and
+    //      twice the runs, of equal length, walk more warm rows than others: 16 x 200 tokens of 20 / 5 heads of 128 17.9 / 17.2 us, 1 x 333 of 32 / 8 of 64
+    //      10.7 / 10.1, 14 shapes and five kinds of keys 1.066 on the geometric mean, the least at 416 rows that fire often, 10.76 / 10.87.)
     {
         wait_loads_but(v_loads);
         lds_barrier();
         if (at_first < count) open(at_first);                    // (these have the scan's time to come)
         const float theta = a.theta;
-        const int run = tid / kPairs, pair = tid % kPairs;
-        const int r0 = run * a.L, r1 = min(r0 + a.L, nk);
+        const int run = tid / D, ch = tid % D;
+        const int r0 = run == 0 ? 0 : a.L0 + (run - 1) * a.L, r1 = min(run == 0 ? a.L0 : r0 + a.L, nk);
         const bool works = run < kRuns && r0 < n;
         const lds_word ends = (lds_word)(uintptr_t)e_at;
-        auto first_of = [](uint32_t v) { return __uint_as_float(v << 16); };
-        auto second_of = [](uint32_t v) { return __uint_as_float(v & 0xffff0000u); };
-        auto both = [](float x, float y) { return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u); };
-        auto at_row = [&](int t) { return k_at + (uint32_t)(t * kRowB + (((pair >> 2) ^ keys_perm(t)) << 4) + (pair & 3) * 4); };
+        auto at_row = [&](int t) { return k_at + (uint32_t)(t * kRowB + (((ch >> 3) ^ keys_perm(t)) << 4) + (ch & 7) * 2); };
+        auto load = [](uint32_t at) { return (uint32_t)*(lds_half)(uintptr_t)at << 16; };
         constexpr int B = 8;                                     // rows in a batch (the permutation of rows repeats after two)
-        float x, y;
-        // rows t .. end - 1 (multiples of 8) from (x, y), the next batch's reads issued before this one is walked.  kWrites: the reference keys are
-        // written; kMeets: until they are in every lane what stands there already.
+        float x;
         auto walk = [&](auto writes, auto meets, int t, int end) __attribute__((always_inline)) {
             uint32_t at[2][B], key[2][B], base = at_row(t);
             // row u of a batch: the segment's permutation is the batch's and, exclusive, u's
@@ -144,7 +143,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_short_kernel(ShortArgs a) 
 #pragma unroll
                 for (int u = 0; u < B; ++u) {
                     at[h][u] = base ^ (keys_perm(u) << 4);
-                    key[h][u] = *(lds_word)(uintptr_t)(at[h][u] + u * kRowB);
+                    key[h][u] = *(lds_half)(uintptr_t)(at[h][u] + u * kRowB);
                 }
                 base = (base ^ (keys_perm(B) << 4)) + B * kRowB;
                 asm volatile("" ::: "memory");                   // (here, and not where they are used)
@@ -152,19 +151,23 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_short_kernel(ShortArgs a) 
             };
             auto work = [&](int h) __attribute__((always_inline)) {
                 uint32_t old = 0;
-                if (meets) old = *(lds_word)(uintptr_t)(at[h][B - 1] + (B - 1) * kRowB + kDist);
+                if (meets) old = load(at[h][B - 1] + (B - 1) * kRowB + kDist);
+                auto put = [&](int u) __attribute__((always_inline)) { *(lds_half)(uintptr_t)(at[h][u] + u * kRowB + kDist) = (uint16_t)(__float_as_uint(x) >> 16); };
+                float kx = __uint_as_float(key[h][0] << 16), kn = 0.f;
 #pragma unroll
                 for (int u = 0; u < B; ++u) {
-                    // Eq. 2 in binary32, Eq. 3 (in this order: one channel after the other waits two states for each mask)
-                    const float kx = first_of(key[h][u]), ky = second_of(key[h][u]);
-                    const bool fx = fabsf(kx - x) > theta, fy = fabsf(ky - y) > theta;
+                    // Eq. 2 in binary32, Eq. 3 (the select waits two states for its mask: what else there is to do comes between, 1.02)
+                    const bool f = fabsf(kx - x) > theta;
                     __builtin_amdgcn_sched_barrier(0);
-                    x = fx ? kx : x;
-                    y = fy ? ky : y;
-                    if (writes) *(lds_word)(uintptr_t)(at[h][u] + u * kRowB + kDist) = both(x, y);
+                    if (u + 1 < B) kn = __uint_as_float(key[h][u + 1] << 16);
+                    if (writes && u > 0) put(u - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    x = f ? kx : x;
+                    kx = kn;
                 }
+                if (writes) put(B - 1);
                 t += B;
-                return t < end && !(meets && !__any(both(x, y) != old));
+                return t < end && !(meets && !__any(__float_as_uint(x) != old));
             };
             read(0);
             while (true) {
@@ -177,31 +180,29 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_short_kernel(ShortArgs a) 
         };
         constexpr std::true_type yes;
         constexpr std::false_type no;
-        uint32_t start = 0;
+        float start = 0.f;
         if (works) {
             const int w = max(r0 - a.warm, 0);
-            start = *(lds_word)(uintptr_t)at_row(max(w - 1, 0));
-            x = first_of(start), y = second_of(start);
+            start = x = __uint_as_float(load(at_row(max(w - 1, 0))));
             if (w < r0) {
                 walk(no, no, w, r0);
-                start = both(x, y);
+                start = x;
             }
             walk(yes, no, r0, r1);
-            ends[tid] = both(x, y);
+            ends[tid] = __float_as_uint(x);
         }
         lds_barrier();
         for (int round = 0; round < kRuns; ++round) {
-            uint32_t from = start;
-            if (works && run > 0) from = ends[tid - kPairs];
-            const bool wrong = from != start;
+            float from = start;
+            if (works && run > 0) from = __uint_as_float(ends[tid - D]);
+            const bool wrong = __float_as_uint(from) != __float_as_uint(start);
             if (__any(wrong) && lane == 0) words[round & 1] = 1;
             lds_barrier();
             if (!words[round & 1]) break;
             if (tid == 0) words[(round + 1) & 1] = 0;
             if (__any(wrong) && works) {
-                start = from;
-                x = first_of(from), y = second_of(from);
-                if (walk(yes, yes, r0, r1) >= r1) ends[tid] = both(x, y);
+                start = x = from;
+                if (walk(yes, yes, r0, r1) >= r1) ends[tid] = __float_as_uint(x);
             }
             lds_barrier();
         }
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(64 * NW, 2) void prefill_short_kernel(ShortArgs a) 
 
 // what a launch looks like; L == 0: the prompt is none for it
 struct ShortPlan {
-    int split, parts, L, warm;
+    int split, parts, L, L0, warm;
     size_t lds;
 };
 
@@ -512,22 +513,23 @@ size_t short_lds(int n, int d) {
 // 9.9 / 9.2 / 8.6, 1 x 333 11.8 / 10.6 / 9.7; 20 / 5 of 128, 1 x 200 13.7 / 12.5 / 11.4).  Else a unit is cut so that every wave has one item and one
 // wave is left for the mask, or into as many work groups as are resident: more would each scan the unit again (16 x 200 tokens of 20 / 5
 // heads of 128, cut in 1 / 2 / 3 / 4: 27.2 / 19.3 / 17.3 / 25.8 us).
-// Rows that runs warm up on save rounds, where the rows that the keys' guesses need are not there anyway.  Geometric mean over 13 shapes and 9 kinds of keys:
-// 16 / 32 / 48 / 64 / 96 of them 12.00 / 11.95 / 12.01 / 12.15 / 12.50 us at jumps of 1 to 20 %, theta 0.03 to 0.22, three inputs each; 32 / 48 / 64 12.15 / 12.04 /
-// 12.05 at 2 to 10 %, 0.08 to 0.16, twelve inputs each.  Fewer are faster where entries fire often (theta 0.03 10.4 .. 12.2), more where they
-// fire rarely (1 %, 0.22 16.5 .. 14.6), and the slowest call gets shorter (26.4 / 25.5 / 24.8 / 24.2 / 22.7): 64 is within 1.7 % of the best mean, and
-// ahead at the rates of the 60 % points (5 %, 0.1113: 12.05 / 11.80 / 11.78).
+// Rows that runs warm up on save rounds, where the rows that the keys' guesses need are not there anyway.  Geometric mean over 14 shapes and five kinds of keys (jumps of 1 to 20 %, theta
+// 0.11 to 0.2), four inputs each, times as fast as 64 of them and runs of equal length: 48 / 56 / 64 / 72 rows 1.060 / 1.066 / 1.067 / 1.067; the worst, 1 x 416 rows of 64 that fire often
+// (20 %, 0.15), 10.66 / 10.87 / 11.04 / 11.07 us for 10.76.
 ShortPlan short_plan(const PrefillArgs &p) {
     ShortPlan s = {};
     if (p.dtype != 1 || (p.d != 64 && p.d != 128)) return s;
-    const int g = p.Hq / p.Hkv, runs = kScanWaves * 128 / p.d;
+    const int g = p.Hq / p.Hkv, runs = kScanWaves * 64 / p.d;
     if (p.n > (p.d == 64 ? kMostRows<64> : kMostRows<128>)) return s;
     const int GH = g % 4 == 0 ? 4 : g % 2 == 0 ? 2 : 1, rt = 32 / GH;
     const int64_t units = (int64_t)p.B * p.Hkv, items = (int64_t)((p.n + rt - 1) / rt) * (g / GH), slots = device_cu_count();
     // (a unit's queries are addressed by 32 bits, work groups and items are counted by 31)
     if ((int64_t)g * p.n * p.d * 2 >= (int64_t)1 << 31 || units * 32 >= (int64_t)1 << 31 || items >= (int64_t)1 << 28) return s;
-    s.L = ((p.n + runs - 1) / runs + 7) & ~7;
-    s.warm = 64;
+    s.warm = 56;
+    const int later = (p.n - s.warm + runs - 1) / runs;          // the first run has no rows to warm up on and takes as many more
+    s.L = later > 8 ? (later + 7) & ~7 : 8;
+    s.L0 = ((p.n + 7) & ~7) - (runs - 1) * s.L;
+    if (s.L0 < 8) s.L0 = 8;
     s.lds = short_lds(p.n, p.d);
     s.split = 1;
     for (int k = 4; k > 1; k /= 2)
@@ -582,6 +584,7 @@ void launch_prefill_short(const PrefillArgs &p, float theta, void *khat, uint32_
     a.parts = s.parts;
     a.mask_part = s.split > 1 ? s.parts : s.parts - 1;
     a.L = s.L;
+    a.L0 = s.L0;
     a.warm = s.warm;
     a.by_units = divisor(a.units);
     a.by_hkv = divisor(p.Hkv);

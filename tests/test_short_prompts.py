@@ -42,6 +42,19 @@ def test_masks_and_counts(kind, theta, units, n, d):
     assert (df.unpack_bits(bits, d) == mask).all() and (nnz == mask.sum(dim=(2, 3))).all()
 
 
+@pytest.mark.parametrize("kind", ["quiet", "mixed", "drift"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [2, 55, 56, 57, 73, 80, 88, 89, 121, 194, 200])
+def test_runs_of_unequal_length(kind, d, n):
+    """The scan's first run, longer by the rows that the later ones warm up on: prompts of about as many rows, later runs of 8 and of 16, a last one of
+    a few rows or none."""
+    K = _keys(kind, n + d, 3, n, d, "bf16")
+    _, bits, nnz = da.delta_attn_prefill(K, K, K, 0.3, 8)
+    _, mask = df.reference_keys(K, 0.3)
+    assert (df.unpack_bits(bits, d) == mask).all()
+    assert (nnz == mask.sum(dim=(2, 3))).all()
+
+
 @pytest.mark.parametrize("d,B,n", [(64, 1, 416), (64, 50, 100), (128, 1, 200), (128, 60, 70)])
 def test_prompt_into_a_cache(d, B, n):
     """The reference keys that the cache is filled from: decode steps on what one launch has left against a prompt that came in pieces."""
