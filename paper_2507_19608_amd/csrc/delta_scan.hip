@@ -572,15 +572,15 @@ __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy...
         E[tid] = walk_rows(a, a + L, start);
     }
     __syncthreads();
-    bool settled = false;
-    for (int round = 0; round < g.rounds; ++round) {
+    bool settled;
+    for (int round = 0;; ++round) {
         float2 from = start;
         if (works && run > 0) from = E[tid - PR];
         const bool wrong = __float_as_uint(from.x) != __float_as_uint(start.x) || __float_as_uint(from.y) != __float_as_uint(start.y);
         if (__any(wrong) && (tid & 63) == 0) flags[round & 1] = 1;
         __syncthreads();                                         // (also: every run has read the end of the one before)
         settled = !flags[round & 1];
-        if (settled) break;
+        if (settled || round == g.rounds) break;
         if (tid == 0) flags[(round + 1) & 1] = 0;
         if (wrong) {
             start = from;
@@ -926,10 +926,11 @@ static WholePlan whole_plan(int dtype, int units, int n, int d) {
     p.L = ((n + runs - 1) / runs + 7) / 8 * 8;
     p.warm = groups(p.dl) <= cus ? 48 : 32;
     // (A wave per channel settles, where it takes no other work group's time: a batch of 150 x 700 rows of 128 74.5 us a call with 4 waves, 77 with 8.)
-    if (p.dl == 8 && groups(8) <= cus) p.threads = 512;
+    if (p.dl == 8 && n > 64 && groups(8) <= cus) p.threads = 512;
     // One round first / none: 8 x 2048 rows of 64 12.5 / 12.0 (1 % jumps 13.0 / 12.6, and threshold 0.2 17.0 / 17.8), 10 x 1024 of 128 30.4 / 30.5 a call; where a wave has
-    // many runs or channels, 5 x 4096 of 128 17.5 / 17.3 (17.9 / 17.8, 23.8 / 27.1), 150 x 700 of 128 74.5 / 77.4 a call.
-    p.rounds = groups(p.dl) > cus || n > 2048;
+    // many runs or channels, 5 x 4096 of 128 17.5 / 17.3 (17.9 / 17.8, 23.8 / 27.1), 150 x 700 of 128 74.5 / 77.4 a call.  Rounds alone where they are short
+    // and a wave would have 4 or 8 channels (appends, rounds / one and in order: 162 x 64 rows of 64 20.3 / 21.9, 72 x 80 of 128 41.8 / 45.3, 80 x 119 of 64 54.0 / 54.7; but 55 x 226 of 128 120.5 / 115.8).
+    p.rounds = p.dl == 32 || n <= (p.dl == 16 ? 128 : 64) ? runs : groups(p.dl) > cus || n > 2048;
     const int used = (n + p.L - 1) / p.L;
     p.lds = (size_t)(used * (p.L + 1) + 1) * p.dl * es + (size_t)used * p.dl * 8 + 16;
     return p;
