@@ -9,8 +9,8 @@
 // with its own running (maximum, sum, output), and meet in LDS once at the end.  The calls this kernel sees are small
 // (a numerics user's single head of a few hundred rows), so what bounds it is how many waves there are and how long the
 // longest one walks: a wave per 64 rows that walked every key took 725 us on 256 rows of one head of 64 (4 waves on the
-// chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each: 6.8 us, 16.0 for the whole
-// call with a scan in front, which two launches on the host bound, and 12.7 where it is part of the launch.
+// chip, operands by scalar loads); rows by 16 and keys by 8 give 128 waves of one or two blocks each: 6.8 us, 12.6 for the whole
+// call with a scan in front and 9.8 where it is part of the launch.
 //
 // kScans: the keys left of a work group's windows fit into its LDS, so it takes them in and makes them reference keys there for itself
 // (Eq. 2-3), and no launch and no pass through memory comes in front; one more work group per unit writes the mask.  (A block's values
@@ -419,8 +419,8 @@ bool launch_by_dim(const PrefillArgs &p, const PrefillScan *scan, hipStream_t s)
 }  // namespace
 
 // Every work group then scans the keys of its unit anew, beside the others as long as each has a compute unit; the scan's own launch spreads over more of them.
-// fp32, a scan in front / in the same launch, us a call: 1 head of 64, 64 tokens 11.0 / 9.8, 256 12.6 / 11.5 (buffers left to the binding, which the host
-// bounds, 16.0 / 12.7), 400 15.4 / 15.2, 580 18.7 / 19.1; 2 x 200, 4 heads 13.1 / 12.2; 2 x 256, 8 heads (272 work groups) 13.4 / 18.2; 1 head of 128, 128
+// fp32, a scan in front / in the same launch, us a call: 1 head of 64, 64 tokens 11.0 / 9.8, 256 12.6 / 11.5 (since runs are whole batches
+// 9.8), 400 15.4 / 15.2, 580 18.7 / 19.1; 2 x 200, 4 heads 13.1 / 12.2; 2 x 256, 8 heads (272 work groups) 13.4 / 18.2; 1 head of 128, 128
 // tokens 14.5 / 13.4, 290 21.3 / 21.2; 8 x 200 of 8 / 8 heads 40 / 63.
 bool prefill_generic_scans(const PrefillArgs &p) {
     return p.dtype == 0 && (p.d == 64 || p.d == 128) && (int64_t)p.n * p.d <= 32768 &&

@@ -29,7 +29,7 @@
 // A wave in its matrix phase goes first (s_setprio): it issues one instruction in 32 clocks, and every one that has to wait for
 // the other wave's arithmetic lengthens the phase (without it 5 % more clocks).  What is added to a matrix phase - addresses, loads, the look at the masks -
 // comes out at more than it saves in the vector phase: its instructions wait in order for whatever is issued between them.
-// Counters on 4 x 8192 tokens, 20 / 5 heads of 128, with the barrier between the phases: 1.96 M clocks a launch, 1520 a phase, of which one wave's matrix instructions
+// Counters on 4 x 8192 tokens, 20 / 5 heads of 128, with the barrier between the phases: 1.96 M clocks a launch (without it 1.85), 1520 a phase, of which one wave's matrix instructions
 // fill 1088 and the other wave's vector instructions 586; with row sums by dot products on the vector ALU and the maximum of every block 2.08 M and 1610
 // (692 of issue).  Before that, with the priority the other way round, a branch and an address for every
 // load, fmaxf, a wait where the next tile is asked for, a pause between tiles and queries and outputs in pieces it was 2.43 M; of 15 %
