@@ -116,13 +116,12 @@ int timing_collect(double *ms_per_stage, int *calls_per_stage) {
 //       the value the run before ended on and walk again, in parallel, until all agree: after round i the first i + 1 runs
 //       are exact, and a run usually meets its old chain (both fire at the same row) after a few rows, so a round or
 //       two does it.  Reference keys leave LDS in 16-byte pieces.
-//   scan_settle_kernel    prompts of several segments: one work group per unit and 64 channels does the same between
-//       segments - compares every segment's start with its predecessor's end and walks what differs again, in parallel as
-//       long as that settles them, else in order - and adds up nnz.
+//   scan_settle_kernel    prompts of several segments: one work group per unit and 16 channels takes every segment's start from its predecessor's
+//       end, in order, walks what differs again, in parallel, and adds up nnz.
 //
 // Exact for any input.  The wave ballot of the threshold decision is the mask word itself.
 // Against two passes and an ordered repair with row-by-row loads: 20 x 8192 rows of 128 in bf16 (86 MB in and out, 5 % jumps) 62 ->
-// 38 us a call; keys that drift steadily, whose guesses are nearly all wrong, 872 -> 228 us.
+// 38 us a call.
 constexpr int kScanLdsMax = 144 * 1024;    // a one-segment prompt: 128 KB of rows, their mask words, the runs' end values
 
 // lane L of (lo, hi) takes the two halves of a wave mask: two instructions, where comparing the lane number and selecting
@@ -422,6 +421,47 @@ __global__ __launch_bounds__(512) void scan_segments_kernel(ScanArgs<T> g, Copy.
     }
 }
 
+// The value that a lane's row per lane - `rows` of them, at most 64 - ends on from `held`, bits of a float: the lanes vote on which fire.
+__device__ __forceinline__ int fired_in(float k, int rows, int held, float theta) {
+    const int lane = threadIdx.x & 63;
+    uint64_t fires = __ballot(lane < rows && fabsf(k - __int_as_float(held)) > theta);   // Eq. 2 in binary32
+    while (fires) {
+        const int t = __builtin_ctzll(fires);
+        held = __builtin_amdgcn_readlane(__float_as_int(k), t);                          // Eq. 3
+        fires = __ballot(lane < rows && fabsf(k - __int_as_float(held)) > theta) & (~1ull << t);
+    }
+    return held;
+}
+
+// One channel's runs (or segments) 1 .. count - 1 by one wave: those whose start is not what the one before ends on are walked from that, in order.
+// walk(run, start's bits): what it ends on, in every lane.  Returns whether there was one.
+template <typename End, typename Start, typename Put, typename Walk>
+__device__ __forceinline__ bool runs_in_order(int count, End end_of, Start start_of, Put put_end, Walk walk) {
+    const int lane = threadIdx.x & 63;
+    bool found = false;
+    int held = 0, last = 0;                                      // (what the run `last` ends on now)
+    for (int r0 = 1; r0 < count; r0 += 64) {
+        const int mine = min(r0 + lane, count - 1);              // a lane per run: what it should start from, and did
+        int from = __float_as_int(end_of(mine - 1));
+        const int start = __float_as_int(start_of(mine));
+        if (lane == 0 && last == r0 - 1 && last > 0) from = held;
+        uint64_t wrong = __ballot(r0 + lane < count && from != start);
+        found = found || wrong;
+        while (wrong) {
+            const int i = __builtin_ctzll(wrong), r = r0 + i;
+            wrong &= wrong - 1;
+            held = walk(r, __builtin_amdgcn_readlane(from, i));
+            last = r;
+            if (lane == 0) put_end(r, __int_as_float(held));
+            if (i < 63 && r + 1 < count) {
+                from = lane == i + 1 ? held : from;
+                wrong = (wrong & ~(2ull << i)) | (held != __builtin_amdgcn_readlane(start, i + 1) ? 2ull << i : 0ull);
+            }
+        }
+    }
+    return found;
+}
+
 // ---- One launch for a prompt of up to some thousand rows: a work group takes a few channels (DL = 8, 16 or 32) of every row of
 // a unit, so that all of a prompt's rows lie in one LDS and nothing has to be settled between work groups, and the channels of
 // one unit still spread over many compute units.  A thread walks one run of L rows in two neighbouring channels (two
@@ -596,31 +636,12 @@ __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy...
         float *const ends = (float *)E;                          // [runs][DL]
         const float *const starts = (const float *)S;
         const int lane = tid & 63;
-        for (int c = __builtin_amdgcn_readfirstlane(tid >> 6); c < DL; c += threads >> 6) {
-            for (int r0 = 1; r0 < runs; r0 += 64) {
-                const int mine = min(r0 + lane, runs - 1);       // a lane per run: what it should start from, and did
-                int from = __float_as_int(ends[(mine - 1) * DL + c]);
-                const int guess = __float_as_int(starts[mine * DL + c]);
-                uint64_t wrong = __ballot(r0 + lane < runs && from != guess);
-                while (wrong) {
-                    const int i = __builtin_ctzll(wrong), r = r0 + i;
-                    wrong &= wrong - 1;
-                    const float k = load_f32((const T *)(rows + (size_t)r * (L + 1) * P), (size_t)(min(lane, L - 1) * DL + c));
-                    int held = __builtin_amdgcn_readlane(from, i);
-                    uint64_t fires = __ballot(lane < L && fabsf(k - __int_as_float(held)) > theta);
-                    while (fires) {
-                        const int t = __builtin_ctzll(fires);
-                        held = __builtin_amdgcn_readlane(__float_as_int(k), t);
-                        fires = __ballot(lane < L && fabsf(k - __int_as_float(held)) > theta) & (~1ull << t);
-                    }
-                    if (lane == 0) ends[r * DL + c] = __int_as_float(held);
-                    if (i < 63 && r + 1 < runs) {                // (the 64 runs behind these ask for their starts themselves)
-                        from = lane == i + 1 ? held : from;
-                        wrong = (wrong & ~(2ull << i)) | (held != __builtin_amdgcn_readlane(guess, i + 1) ? 2ull << i : 0ull);
-                    }
-                }
-            }
-        }
+        for (int c = __builtin_amdgcn_readfirstlane(tid >> 6); c < DL; c += threads >> 6)
+            runs_in_order(
+                runs, [&](int r) { return ends[r * DL + c]; }, [&](int r) { return starts[r * DL + c]; }, [&](int r, float end) { ends[r * DL + c] = end; },
+                [&](int r, int held) {
+                    return fired_in(load_f32((const T *)(rows + (size_t)r * (L + 1) * P), (size_t)(min(lane, L - 1) * DL + c)), L, held, theta);
+                });
         __syncthreads();
         if (works && run > 0) start = E[tid - PR];
     }
@@ -675,124 +696,97 @@ __global__ __launch_bounds__(256) void nnz_sum_kernel(NnzSum sum) {
     add_up_nnz(sum, (int)(blockIdx.x * 32 + (threadIdx.x >> 3)));
 }
 
-constexpr int kSettleWaves = 16;
+constexpr int kSettleWaves = 16;                                 // a channel each
+constexpr int kMostSegment = 384;                                // rows of a segment (scan_plan)
 
-// The value a segment's rows t0 .. t1 - 1 end on from `held`, without writing anything: once the chain meets the recorded one
-// in every lane (Hp: its reference keys) it ends on the recorded end.  Only the compare and the select of Eq. 2-3 per row, 32
-// rows in flight behind the 32 being walked.
+// The reference keys, masks and counts of up to four segments of 16 channels again, one segment to 16 lanes: rows from t0 on (t1 - t0 are a segment's, `most` any one's) from `held`, where those
+// there are from `spec`; `mine`: this lane's segment is one of them.  Until the two chains have met in every lane.  Returns the value the segment ends on.
 template <typename T>
-__device__ __forceinline__ float chase(const T *Kp, const T *Hp, int d, int t0, int t1, float held, float end, bool active,
-                                       float theta) {
-    constexpr int N = 32;
-    auto fetch = [&](T (&k)[N + 1], int tb) {                    // (the last row again past the end: it fires once at most)
+__device__ __forceinline__ float rewalk_four(const T *Kp, T *Hp, uint16_t *Mp, int d, int t0, int t1, int most, float spec, float held, float end, bool mine, float theta,
+                                             long long *adjust) {
+    const int lane = threadIdx.x & 63, sub = lane >> 4, at = lane & 15;
+    bool synced = !mine || __float_as_uint(spec) == __float_as_uint(held);
+    auto fetch = [&](T (&k)[U], int tb) {                        // rows past the end are clamped and not worked on
 #pragma unroll
-        for (int u = 0; u < N; ++u) k[u] = Kp[(size_t)min(tb + u, t1 - 1) * d];
-        k[N] = Hp[(size_t)min(tb + N - 1, t1 - 1) * d];
+        for (int u = 0; u < U; ++u) k[u] = Kp[(size_t)min(t0 + tb + u, t1 - 1) * d];
     };
-    auto work = [&](const T (&kk)[N + 1], int tb) {
-#pragma unroll
-        for (int u = 0; u < N; ++u) {
+    auto work = [&](const T (&kk)[U], int tb) {
+        uint32_t bits = 0;                                       // lane u of a segment's keeps the mask of its row tb + u
+        for_batch([&](auto u) {
+            const bool here = mine && t0 + tb + u < t1;
             const float k = to_f32(kk[u]);
-            held = fabsf(k - held) > theta ? k : held;
-        }
-        if (!__any(active && __float_as_uint(held) != __float_as_uint(to_f32(kk[N])))) {
-            held = end;
-            return false;
-        }
-        return tb + N < t1;
+            const bool fs = here && fabsf(k - spec) > theta, ft = here && fabsf(k - held) > theta;
+            spec = fs ? k : spec;
+            held = ft ? k : held;
+            const uint64_t bt = __ballot(ft);
+            *adjust += (long long)__popcll(bt) - (long long)__popcll(__ballot(fs));
+            bits = at == u ? (sub & 2 ? (uint32_t)(bt >> 32) : (uint32_t)bt) >> (16 * (sub & 1)) : bits;
+            if (here) store_exact(Hp, (size_t)(t0 + tb + u) * d, held);
+        });
+        synced = synced || __float_as_uint(spec) == __float_as_uint(held);   // (chains that have met stay together)
+        if (mine && at < U && t0 + tb + at < t1) Mp[(size_t)(t0 + tb + at) * (d >> 4)] = (uint16_t)bits;
+        return tb + U < most && __any(!synced);
     };
-    T ka[N + 1], kb[N + 1];
-    fetch(ka, t0);
-    for (int tb = t0;; tb += 2 * N) {
-        fetch(kb, tb + N);
+    T ka[U], kb[U];
+    fetch(ka, 0);
+    for (int tb = 0;; tb += 2 * U) {
+        fetch(kb, tb + U);
         if (!work(ka, tb)) break;
-        fetch(ka, tb + 2 * N);
-        if (!work(kb, tb + N)) break;
+        fetch(ka, tb + 2 * U);
+        if (!work(kb, tb + U)) break;
     }
-    return held;
+    return synced ? end : held;
 }
 
-// Rounds of walking wrong segments again, in parallel, as long as every round leaves at most three quarters of them (which
-// together is four rounds' work: a steady drift in 63 segments takes 47, 31, 15).  Where channels stay quiet over whole segments a round
-// does not: an end value then travels one segment a round, and rounds until it arrives would make the time
-// quadratic in the number of segments.  So the first wave settles what is left in order - it only chases the end values, each
-// segment once - and one more round, which now has the right starts, writes.
-// 20 units x 8192 rows of 128 in bf16 where nothing fires: 2440 -> 677 us; 5 x 65536: 124.4 -> 5.03 ms; 4 x 16384 in fp32: 14.7 -> 1.13 ms
-// (rounds alone -> this); keys that drift steadily take what they did, 228 us for 20 x 8192.
+// What segments end on travels in order, a wave per channel (runs_in_order), 16 channels to a work group; then every segment whose start was another is
+// walked again once, until it meets what stands there.  What bounds it is that walk's rows in a chain and, where most segments are wrong, the lines that the waves
+// read one channel of.  Against rounds of walking 64 channels of a segment again, each up to 384 rows with their stores, and one wave that chased the ends where rounds
+// did not help, scans back to back, us: 20 x 8192 rows of 128 34.3 / 33.7, at threshold 0.2 51.7 / 49.2, 1 % jumps 41.4 / 39.6, and 0.2 142.5 / 141.5, drift
+// 451 / 230, nothing fires 637 / 251; 10 x 5003 21.7 / 21.2, 35.8 / 33.4, 30.9 / 29.0, 141 / 67, 382 / 101, 379 / 84; 5 x 65536, nothing fires, 5396 / 1528.
 template <typename T>
 __global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_kernel(ScanArgs<T> g) {
     __shared__ unsigned long long total;
     const int group = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = g.n, d = g.d, nseg = g.nseg, wpr = d >> 5;
-    const int c = group * kWave + lane, cs = min(c, d - 1), word = group * 2;
-    const bool active = c < d;
-    const T *Kp = g.K + (size_t)unit * n * d + cs;
-    T *Hp = g.Khat + (size_t)unit * g.ld * d + cs;
-    uint32_t *Mp = g.mask_bits + (size_t)unit * n * wpr + word;
-    T *sp = g.starts + (size_t)unit * nseg * d + cs, *ep = g.ends + (size_t)unit * nseg * d + cs;
+    const int n = g.n, d = g.d, nseg = g.nseg, columns = (d + 63) / 64;
+    const T *const Ku = g.K + (size_t)unit * n * d + group * 16;
+    const T *const Hu = g.Khat + (size_t)unit * g.ld * d + group * 16;
+    T *const su = g.starts + (size_t)unit * nseg * d + group * 16, *const eu = g.ends + (size_t)unit * nseg * d + group * 16;
     if (tid == 0) total = 0;
     unsigned long long sum = 0;
-    for (int s = tid; s < nseg; s += 64 * kSettleWaves) sum += g.counts[((size_t)unit * nseg + s) * gridDim.x + group];
+    if (group < columns)
+        for (int s = tid; s < nseg; s += 64 * kSettleWaves) sum += g.counts[((size_t)unit * nseg + s) * columns + group];
+    const bool found = runs_in_order(
+        nseg, [&](int s) { return load_f32(eu, (size_t)s * d + wave); }, [&](int s) { return load_f32(su, (size_t)s * d + wave); },
+        [&](int s, float end) { store_exact(eu, (size_t)s * d + wave, end); },
+        [&](int s, int held) {
+            // (two blocks of 64 rows first: most chains meet what stands there, which every round here pays for with 64 lines a block)
+            const int t0 = s * g.S, rows = min(n - t0, g.S);
+            const float stands = load_f32(Hu, (size_t)(t0 + min(127, rows - 1)) * d + wave), end = load_f32(eu, (size_t)s * d + wave);
+            auto blocks = [&](auto from, auto to) __attribute__((always_inline)) {
+                float k[to - from];
+#pragma unroll
+                for (int b = from; b < to; ++b) k[b - from] = load_f32(Ku, (size_t)(t0 + min(64 * b + lane, rows - 1)) * d + wave);
+#pragma unroll
+                for (int b = from; b < to; ++b) held = fired_in(k[b - from], rows - 64 * b, held, g.theta);
+            };
+            blocks(std::integral_constant<int, 0>{}, std::integral_constant<int, 2>{});
+            if (held == __float_as_int(stands)) return __float_as_int(end);
+            if (rows > 128) blocks(std::integral_constant<int, 2>{}, std::integral_constant<int, kMostSegment / 64>{});
+            return held;
+        });
     long long adjust = 0;
-    constexpr int G = 4;                                         // segments whose boundary values are fetched together
-    bool ordered = false;
-    for (int before = 0x7fffffff;;) {
-        int walked = 0;
-        for (int sb = 1 + wave; sb < nseg; sb += G * kSettleWaves) {
-            uint32_t wrong = 0;                                  // bit u: segment sb + u * kSettleWaves
-            float st[G], pe[G];
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                const size_t s = min(sb + u * kSettleWaves, nseg - 1);
-                st[u] = load_f32(sp, s * d);
-                pe[u] = load_f32(ep, (s - 1) * d);
-            }
-#pragma unroll
-            for (int u = 0; u < G; ++u)
-                wrong |= (uint32_t)(sb + u * kSettleWaves < nseg && __any(active && __float_as_uint(st[u]) != __float_as_uint(pe[u]))) << u;
-            walked += __popc(wrong);
-            for (; wrong; wrong &= wrong - 1) {
-                const int s = sb + __builtin_ctz(wrong) * kSettleWaves;
-                const float from = load_f32(ep, (size_t)(s - 1) * d);
-                const float e = rewalk(Kp, d, Hp, d, Mp, wpr, word + 1 < wpr, s * g.S, min(n, s * g.S + g.S),
-                                       load_f32(sp, (size_t)s * d), from, load_f32(ep, (size_t)s * d), active, g.theta, &adjust);
-                if (active) {
-                    store_exact(sp, (size_t)s * d, from);
-                    store_exact(ep, (size_t)s * d, e);
-                }
-            }
+    if (__syncthreads_or(found)) {
+        const int sub = lane >> 4, c = lane & 15;
+        T *const Hp = g.Khat + (size_t)unit * g.ld * d + group * 16 + c;
+        uint16_t *const Mp = (uint16_t *)(g.mask_bits + (size_t)unit * n * (d >> 5)) + group;
+        for (int s0 = 1 + wave; s0 < nseg; s0 += 4 * kSettleWaves) {
+            const int s = min(s0 + sub * kSettleWaves, nseg - 1);
+            const float st = load_f32(su, (size_t)s * d + c), from = load_f32(eu, (size_t)(s - 1) * d + c), end = load_f32(eu, (size_t)s * d + c);
+            const uint64_t wrong = __ballot(s0 + sub * kSettleWaves < nseg && __float_as_uint(st) != __float_as_uint(from));
+            if (wrong)
+                rewalk_four(Ku + c, Hp, Mp, d, s * g.S, min(n, s * g.S + g.S), g.S, st, from, end, (wrong >> (16 * sub) & 0xffff) != 0, g.theta, &adjust);
         }
-        const int all = __syncthreads_count(lane < walked);      // (at most 64 a wave: a lower bound where segments are many)
-        if (all == 0 || ordered) break;
-        if (4ll * all > 3ll * before) {
-            if (wave == 0) {
-                float held = load_f32(ep, 0);                    // (the first segment is exact)
-                for (int sb = 1; sb < nseg; sb += G) {
-                    float st[G], en[G];
-#pragma unroll
-                    for (int u = 0; u < G; ++u) {
-                        const size_t s = min(sb + u, nseg - 1);
-                        st[u] = load_f32(sp, s * d);
-                        en[u] = load_f32(ep, s * d);
-                    }
-#pragma unroll 1
-                    for (int u = 0; u < G && sb + u < nseg; ++u) {
-                        const float start = u == 0 ? st[0] : u == 1 ? st[1] : u == 2 ? st[2] : st[3];
-                        const float end = u == 0 ? en[0] : u == 1 ? en[1] : u == 2 ? en[2] : en[3];
-                        const size_t t0 = (size_t)(sb + u) * g.S;
-                        if (__any(active && __float_as_uint(held) != __float_as_uint(start)))
-                            held = chase(Kp, Hp, d, (int)t0, min(n, (int)t0 + g.S), held, end, active, g.theta);
-                        else
-                            held = end;
-                        if (active) store_exact(ep, (size_t)(sb + u) * d, held);
-                    }
-                }
-            }
-            ordered = true;
-            __syncthreads();
-        }
-        before = all;
     }
     if (lane == 0) sum += (unsigned long long)adjust;
     if (sum) atomicAdd(&total, sum);
@@ -890,7 +884,7 @@ static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *m
         hipLaunchKernelGGL(kernel, dim3(p.nseg, units, groups), block, p.lds, s, a);
     }
     if (p.nseg > 1)
-        hipLaunchKernelGGL(scan_settle_kernel<T>, dim3((d + 63) / 64, units), dim3(64 * kSettleWaves), 0, s, a);
+        hipLaunchKernelGGL(scan_settle_kernel<T>, dim3(d / 16, units), dim3(64 * kSettleWaves), 0, s, a);
 }
 
 // What a launch of scan_whole_kernel looks like; L == 0: the prompt is none for it.

@@ -46,6 +46,20 @@ def test_segments_that_settle_late(kind, dtype, units, n, d):
         assert (nnz == d).all()
 
 
+@pytest.mark.parametrize("kind", ["quiet", "rare", "drift", "mixed"])
+@pytest.mark.parametrize("dtype,units,n,d", [("bf16", 1, 128 * 64 + 1, 32), ("bf16", 1, 128 * 129 + 2, 64), ("f32", 1, 128 * 65, 32), ("bf16", 24, 6144 + 1, 128),
+                                             ("bf16", 24, 384 * 16 + 129, 128)])
+def test_segments_in_order(kind, dtype, units, n, d):
+    """64 segments whose ends travel together and one more, twice that; a last segment of one or two rows, whole, and of one row more than the two
+    blocks that are looked at first."""
+    import dense_form as df
+    K = _keys(kind, n + 7, units, n, d, dtype)
+    bits, nnz, khat = da.delta_attn_delta_scan(K, 0.3, want_khat=True)
+    ref_khat, ref_mask = df.reference_keys(K, 0.3)
+    assert (khat.double() == ref_khat).all() and (df.unpack_bits(bits, d) == ref_mask).all()
+    assert (nnz == ref_mask.sum(dim=(2, 3))).all()
+
+
 @pytest.mark.parametrize("kind", ["quiet", "rare", "mixed"])
 @pytest.mark.parametrize("d,cuts", [(64, (0, 1100, 4000)), (128, (0, 40, 2700)), (64, (0, 3001, 3002, 5200)), (128, (0, 300, 4500))])
 def test_pieces_that_continue_a_cache(kind, d, cuts):
