@@ -117,7 +117,8 @@ int timing_collect(double *ms_per_stage, int *calls_per_stage) {
 //       are exact, and a run usually meets its old chain (both fire at the same row) after a few rows, so a round or
 //       two does it.  Reference keys leave LDS in 16-byte pieces.
 //   scan_settle_kernel    prompts of several segments: one work group per unit and 16 channels takes every segment's start from its predecessor's
-//       end, in order, walks what differs again, in parallel, and adds up nnz.
+//       end, in order, walks what differs again, in parallel, and adds up nnz.  Where units are many, scan_settle_rounds_kernel: one of 64 channels, which walks
+//       what differs in rounds as long as that settles it, else in order.
 //
 // Exact for any input.  The wave ballot of the threshold decision is the mask word itself.
 // Against two passes and an ordered repair with row-by-row loads: 20 x 8192 rows of 128 in bf16 (86 MB in and out, 5 % jumps) 62 ->
@@ -794,6 +795,130 @@ __global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_kernel(ScanArgs
     if (tid == 0) atomicAdd(g.nnz + unit, total);
 }
 
+// The value a segment's rows t0 .. t1 - 1 end on from `held`, without writing anything: once the chain meets the recorded one
+// in every lane (Hp: its reference keys) it ends on the recorded end.  Only the compare and the select of Eq. 2-3 per row, 32
+// rows in flight behind the 32 being walked.
+template <typename T>
+__device__ __forceinline__ float chase(const T *Kp, const T *Hp, int d, int t0, int t1, float held, float end, bool active,
+                                       float theta) {
+    constexpr int N = 32;
+    auto fetch = [&](T (&k)[N + 1], int tb) {                    // (the last row again past the end: it fires once at most)
+#pragma unroll
+        for (int u = 0; u < N; ++u) k[u] = Kp[(size_t)min(tb + u, t1 - 1) * d];
+        k[N] = Hp[(size_t)min(tb + N - 1, t1 - 1) * d];
+    };
+    auto work = [&](const T (&kk)[N + 1], int tb) {
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const float k = to_f32(kk[u]);
+            held = fabsf(k - held) > theta ? k : held;
+        }
+        if (!__any(active && __float_as_uint(held) != __float_as_uint(to_f32(kk[N])))) {
+            held = end;
+            return false;
+        }
+        return tb + N < t1;
+    };
+    T ka[N + 1], kb[N + 1];
+    fetch(ka, t0);
+    for (int tb = t0;; tb += 2 * N) {
+        fetch(kb, tb + N);
+        if (!work(ka, tb)) break;
+        fetch(ka, tb + 2 * N);
+        if (!work(kb, tb + N)) break;
+    }
+    return held;
+}
+
+// Where units are many and work groups of 16 channels would not all be resident: one of 64 channels per unit.
+// Rounds of walking wrong segments again, in parallel, as long as every round leaves at most three quarters of them (which
+// together is four rounds' work: a steady drift in 63 segments takes 47, 31, 15).  Where channels stay quiet over whole segments a round
+// does not: an end value then travels one segment a round, and rounds until it arrives would make the time
+// quadratic in the number of segments.  So the first wave settles what is left in order - it only chases the end values, each
+// segment once - and one more round, which now has the right starts, writes.
+// 20 units x 8192 rows of 128 in bf16 where nothing fires: 2440 -> 677 us; 5 x 65536: 124.4 -> 5.03 ms; 4 x 16384 in fp32: 14.7 -> 1.13 ms
+// (rounds alone -> this); keys that drift steadily take what they did, 228 us for 20 x 8192.
+template <typename T>
+__global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_rounds_kernel(ScanArgs<T> g) {
+    __shared__ unsigned long long total;
+    const int group = blockIdx.x, unit = blockIdx.y, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = g.n, d = g.d, nseg = g.nseg, wpr = d >> 5;
+    const int c = group * kWave + lane, cs = min(c, d - 1), word = group * 2;
+    const bool active = c < d;
+    const T *Kp = g.K + (size_t)unit * n * d + cs;
+    T *Hp = g.Khat + (size_t)unit * g.ld * d + cs;
+    uint32_t *Mp = g.mask_bits + (size_t)unit * n * wpr + word;
+    T *sp = g.starts + (size_t)unit * nseg * d + cs, *ep = g.ends + (size_t)unit * nseg * d + cs;
+    if (tid == 0) total = 0;
+    unsigned long long sum = 0;
+    for (int s = tid; s < nseg; s += 64 * kSettleWaves) sum += g.counts[((size_t)unit * nseg + s) * gridDim.x + group];
+    long long adjust = 0;
+    constexpr int G = 4;                                         // segments whose boundary values are fetched together
+    bool ordered = false;
+    for (int before = 0x7fffffff;;) {
+        int walked = 0;
+        for (int sb = 1 + wave; sb < nseg; sb += G * kSettleWaves) {
+            uint32_t wrong = 0;                                  // bit u: segment sb + u * kSettleWaves
+            float st[G], pe[G];
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                const size_t s = min(sb + u * kSettleWaves, nseg - 1);
+                st[u] = load_f32(sp, s * d);
+                pe[u] = load_f32(ep, (s - 1) * d);
+            }
+#pragma unroll
+            for (int u = 0; u < G; ++u)
+                wrong |= (uint32_t)(sb + u * kSettleWaves < nseg && __any(active && __float_as_uint(st[u]) != __float_as_uint(pe[u]))) << u;
+            walked += __popc(wrong);
+            for (; wrong; wrong &= wrong - 1) {
+                const int s = sb + __builtin_ctz(wrong) * kSettleWaves;
+                const float from = load_f32(ep, (size_t)(s - 1) * d);
+                const float e = rewalk(Kp, d, Hp, d, Mp, wpr, word + 1 < wpr, s * g.S, min(n, s * g.S + g.S),
+                                       load_f32(sp, (size_t)s * d), from, load_f32(ep, (size_t)s * d), active, g.theta, &adjust);
+                if (active) {
+                    store_exact(sp, (size_t)s * d, from);
+                    store_exact(ep, (size_t)s * d, e);
+                }
+            }
+        }
+        const int all = __syncthreads_count(lane < walked);      // (at most 64 a wave: a lower bound where segments are many)
+        if (all == 0 || ordered) break;
+        if (4ll * all > 3ll * before) {
+            if (wave == 0) {
+                float held = load_f32(ep, 0);                    // (the first segment is exact)
+                for (int sb = 1; sb < nseg; sb += G) {
+                    float st[G], en[G];
+#pragma unroll
+                    for (int u = 0; u < G; ++u) {
+                        const size_t s = min(sb + u, nseg - 1);
+                        st[u] = load_f32(sp, s * d);
+                        en[u] = load_f32(ep, s * d);
+                    }
+#pragma unroll 1
+                    for (int u = 0; u < G && sb + u < nseg; ++u) {
+                        const float start = u == 0 ? st[0] : u == 1 ? st[1] : u == 2 ? st[2] : st[3];
+                        const float end = u == 0 ? en[0] : u == 1 ? en[1] : u == 2 ? en[2] : en[3];
+                        const size_t t0 = (size_t)(sb + u) * g.S;
+                        if (__any(active && __float_as_uint(held) != __float_as_uint(start)))
+                            held = chase(Kp, Hp, d, (int)t0, min(n, (int)t0 + g.S), held, end, active, g.theta);
+                        else
+                            held = end;
+                        if (active) store_exact(ep, (size_t)(sb + u) * d, held);
+                    }
+                }
+            }
+            ordered = true;
+            __syncthreads();
+        }
+        before = all;
+    }
+    if (lane == 0) sum += (unsigned long long)adjust;
+    if (sum) atomicAdd(&total, sum);
+    __syncthreads();
+    if (tid == 0) atomicAdd(g.nnz + unit, total);
+}
+
 __global__ void fill_u64_kernel(unsigned long long *p, unsigned long long v, int n) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -883,8 +1008,13 @@ static void scan_typed(const ScanPlan &p, const void *K, void *Khat, uint32_t *m
         ensure_dynamic_lds((const void *)kernel, kScanLdsMax, lds_set[which]);
         hipLaunchKernelGGL(kernel, dim3(p.nseg, units, groups), block, p.lds, s, a);
     }
-    if (p.nseg > 1)
+    // In order with 16 channels a work group while each has a compute unit / in rounds with 64 beyond, scans back to back, us: 64 x 6144 rows of 64 37.6 / 38.4, at
+    // threshold 0.2 67.9 / 73.0; 33 x 8192 of 128 (264 work groups) 49.6 / 48.2 and 72.4 / 75.4, 96 x 5304 of 64 48.7 / 47.6 and 69.5 / 71.6, 300 x 2100 59.1 / 55.4 and
+    // 91.6 / 89.9.  (In order with 64 a work group 57.0 and 114.9 there.)
+    if (p.nseg > 1 && (int64_t)units * (d / 16) <= device_cu_count())
         hipLaunchKernelGGL(scan_settle_kernel<T>, dim3(d / 16, units), dim3(64 * kSettleWaves), 0, s, a);
+    else if (p.nseg > 1)
+        hipLaunchKernelGGL(scan_settle_rounds_kernel<T>, dim3((d + 63) / 64, units), dim3(64 * kSettleWaves), 0, s, a);
 }
 
 // What a launch of scan_whole_kernel looks like; L == 0: the prompt is none for it.

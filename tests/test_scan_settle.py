@@ -48,10 +48,10 @@ def test_segments_that_settle_late(kind, dtype, units, n, d):
 
 @pytest.mark.parametrize("kind", ["quiet", "rare", "drift", "mixed"])
 @pytest.mark.parametrize("dtype,units,n,d", [("bf16", 1, 128 * 64 + 1, 32), ("bf16", 1, 128 * 129 + 2, 64), ("f32", 1, 128 * 65, 32), ("bf16", 24, 6144 + 1, 128),
-                                             ("bf16", 24, 384 * 16 + 129, 128)])
+                                             ("bf16", 24, 384 * 16 + 129, 128), ("bf16", 64, 4100, 64), ("bf16", 65, 4100, 64)])
 def test_segments_in_order(kind, dtype, units, n, d):
     """64 segments whose ends travel together and one more, twice that; a last segment of one or two rows, whole, and of one row more than the two
-    blocks that are looked at first."""
+    blocks that are looked at first; the most units that settle in order, and one more."""
     import dense_form as df
     K = _keys(kind, n + 7, units, n, d, dtype)
     bits, nnz, khat = da.delta_attn_delta_scan(K, 0.3, want_khat=True)
