@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libdelta_attn.so: argument marshalling only.
+"""Binding of libdelta_attn.so: argument marshalling only, by ctypes and, for the two short calls, by compiled code (csrc/marshal.cpp).
 
 Every step of the path runs in the library's HIP kernels; torch is used for device
 memory and the current stream.  There is no CPU fallback: if the library is missing
@@ -7,6 +7,7 @@ or no GPU is present, calls raise.
 import ctypes
 import os
 import struct
+import warnings
 from typing import Optional
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -137,6 +138,20 @@ _raw_stream = None
 _marshal = None        # the compiled way from a call's objects to the library, or None (it is built beside the library)
 
 
+def _load_marshal(torch):
+    """The compiled marshalling, where it was built for this Python and this torch; else None, and a warning that says why."""
+    try:
+        from . import _marshal as m                              # (links to torch's libraries, which are loaded by now)
+        if getattr(m, "built_for", None) == torch.__version__:
+            return m
+        why = f"it is built for torch {getattr(m, 'built_for', '?')}, this is {torch.__version__}"
+    except ImportError as e:
+        why = str(e)
+    warnings.warn(f"delta_attn's compiled marshalling is not used, a short call takes 3 us more: {why}; "
+                  "`python -m paper_2507_19608_amd.build` builds it", RuntimeWarning, stacklevel=4)
+    return None
+
+
 def _torch():
     """torch, once a GPU has been seen (asked anew as long as there is none)."""
     global _torch_mod, _raw_stream, _marshal
@@ -147,10 +162,7 @@ def _torch():
         # The current stream's handle without a Stream object around it (2.5 us a call, a quarter of a decode step's host
         # time); torch's own compiled code asks in this way, and without it the public call does.
         of, device = (getattr(torch._C, f, None) for f in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
-        try:
-            from . import _marshal as m                      # (links to torch's libraries, which are loaded by now)
-        except ImportError:
-            m = None
+        m = _load_marshal(torch)
         if m is not None:
             m.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
                 lib().delta_attn_prefill, lib().delta_attn_prefill_workspace_bytes, lib().delta_attn_decode)))

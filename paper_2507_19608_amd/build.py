@@ -1,7 +1,6 @@
 """Build libdelta_attn.so (HIP, gfx950) in-tree with hipcc, and, where there are torch and g++, the binding's compiled part.  No GPU is
 needed to compile."""
 import glob
-import importlib.util
 import os
 import re
 import subprocess
@@ -13,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_obj")
 LIB = os.path.join(HERE, "libdelta_attn.so")
-MARSHAL = os.path.join(HERE, "_marshal.so")
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))   # (another Python does not find it)
 
 # packed fp32 instructions are switched off for every device compile (hipcc's host pass warns
 # that it does not know the feature; harmless)
@@ -50,23 +49,29 @@ def _compile(src: str, force: bool) -> str:
 
 
 def build_marshal(force: bool) -> None:
-    """The binding's compiled part.  It calls the library through addresses that it is given, and links to torch alone."""
-    src = os.path.join(CSRC, "marshal.cpp")
+    """The binding's compiled part.  It calls the library through addresses that it is given, and links to torch alone: the one that it
+    is built for, which it keeps the name of (the binding takes it for no other)."""
+    try:
+        import torch
+    except ImportError as e:
+        raise RuntimeError(f"there is no torch ({e})")
+    src, built_for = os.path.join(CSRC, "marshal.cpp"), os.path.join(OBJ, "marshal.built_for")
     deps = [src] + glob.glob(os.path.join(HERE, "..", "include", "*.h"))
-    if not force and os.path.exists(MARSHAL) and all(os.path.getmtime(MARSHAL) >= os.path.getmtime(d) for d in deps):
+    if not force and os.path.exists(MARSHAL) and all(os.path.getmtime(MARSHAL) >= os.path.getmtime(d) for d in deps) \
+            and os.path.exists(built_for) and open(built_for).read() == torch.__version__:
         return
-    spec = importlib.util.find_spec("torch")
-    if spec is None or not spec.origin:
-        raise RuntimeError("torch is not installed")
-    torch = os.path.dirname(spec.origin)
-    include = [os.path.join(torch, "include"), os.path.join(torch, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
+    at = os.path.dirname(torch.__file__)
+    include = [os.path.join(at, "include"), os.path.join(at, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
                sysconfig.get_paths()["include"]]
-    r = subprocess.run(["g++", "-O2", "-shared", "-fPIC", "-std=c++17", "-Wall", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
-                       + [a for d in include for a in ("-isystem", d)] + [src, "-o", MARSHAL, "-L" + os.path.join(torch, "lib")]
+    r = subprocess.run(["g++", "-O2", "-shared", "-fPIC", "-std=c++17", "-Wall", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                        f'-DBUILT_FOR="{torch.__version__}"']
+                       + [a for d in include for a in ("-isystem", d)] + [src, "-o", MARSHAL, "-L" + os.path.join(at, "lib")]
                        + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"g++ failed for {src}:\n{r.stderr}")
     sys.stderr.write(r.stderr)
+    with open(built_for, "w") as f:
+        f.write(torch.__version__)
 
 
 def build(force: bool = True, jobs: int = 8) -> str:

@@ -211,4 +211,11 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, n
 
 }  // namespace
 
-extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal() { return PyModule_Create(&module); }
+extern "C" __attribute__((visibility("default"))) PyObject *PyInit__marshal() {
+    PyObject *const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", BUILT_FOR) < 0) {   // torch.__version__
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}
