@@ -60,6 +60,12 @@ int dtype_of(const at::Tensor &t) {
     return t.scalar_type() == at::kFloat ? DA_F32 : t.scalar_type() == at::kBFloat16 ? DA_BF16 : -1;
 }
 void *stream() { return (void *)c10::hip::getCurrentHIPStream().stream(); }
+// The interpreter's lock is given back while one of these lives: an allocation may wait for the device, and so for a host function on a
+// stream that wants the lock.
+struct Unlocked {
+    PyThreadState *const state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
 
 // prefill(Q, K, V, theta, window, scale, score_mode, window_mode, cache's handle, workspace, out)
 PyObject *prefill(PyObject *, PyObject *const *args, Py_ssize_t count) {
@@ -96,26 +102,23 @@ PyObject *prefill(PyObject *, PyObject *const *args, Py_ssize_t count) {
     const at::Tensor *workspace = nullptr;
     if (args[9] != Py_None && !(workspace = buffer(args[9]))) return not_here();
     at::Tensor room, O, mask, nnz;
-    if (!workspace) {
-        const size_t bytes = workspace_entry(&p);
-        room = at::empty({(int64_t)(bytes ? bytes : 1)}, Q->options().dtype(at::kByte));
-        workspace = &room;
-    }
-    if (made) {
-        O = at::empty(Q->sizes(), Q->options());
-        mask = at::empty({p.batch, p.n_kv_heads, p.seq_len, p.head_dim / 32}, Q->options().dtype(at::kInt));
-        nnz = at::empty({p.batch, p.n_kv_heads}, Q->options().dtype(at::kLong));
-        out[0] = &O, out[1] = &mask, out[2] = &nnz;
-    }
-    void *const q = Q->data_ptr(), *const k = K->data_ptr(), *const v = V->data_ptr(), *const o = out[0]->data_ptr(), *const ws = workspace->data_ptr();
-    uint32_t *const m = (uint32_t *)out[1]->data_ptr();
-    uint64_t *const c = (uint64_t *)out[2]->data_ptr();
-    const size_t bytes = (size_t)workspace->numel();
-    void *const on = stream();
     da_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = prefill_entry(&p, q, k, v, o, m, c, cache, ws, bytes, on);
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked unlocked;
+        if (!workspace) {
+            const size_t bytes = workspace_entry(&p);
+            room = at::empty({(int64_t)(bytes ? bytes : 1)}, Q->options().dtype(at::kByte));
+            workspace = &room;
+        }
+        if (made) {
+            O = at::empty(Q->sizes(), Q->options());
+            mask = at::empty({p.batch, p.n_kv_heads, p.seq_len, p.head_dim / 32}, Q->options().dtype(at::kInt));
+            nnz = at::empty({p.batch, p.n_kv_heads}, Q->options().dtype(at::kLong));
+            out[0] = &O, out[1] = &mask, out[2] = &nnz;
+        }
+        st = prefill_entry(&p, Q->data_ptr(), K->data_ptr(), V->data_ptr(), out[0]->data_ptr(), (uint32_t *)out[1]->data_ptr(),
+                           (uint64_t *)out[2]->data_ptr(), cache, workspace->data_ptr(), (size_t)workspace->numel(), stream());
+    }
     if (st != DA_OK) return PyLong_FromLong((long)st);
     PyObject *const result = PyTuple_New(3);
     if (!result) return nullptr;
@@ -163,21 +166,19 @@ PyObject *decode(PyObject *, PyObject *const *args, Py_ssize_t count) {
         return not_here();
     }
     if (args[5] != Py_None && !(row = buffer(args[5]))) return not_here();
-    if (!out) {
-        new_out = at::empty(q->sizes(), q->options());
-        out = &new_out;
-    }
-    if (!row) {
-        new_row = at::empty({c.batch, c.n_kv_heads, c.head_dim / 32}, q->options().dtype(at::kInt));
-        row = &new_row;
-    }
-    void *const qp = q->data_ptr(), *const kp = k->data_ptr(), *const vp = v->data_ptr(), *const op = out->data_ptr();
-    uint32_t *const mp = (uint32_t *)row->data_ptr();
-    void *const on = stream();
     da_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = decode_entry(c.handle, qp, kp, vp, op, mp, on);
-    Py_END_ALLOW_THREADS
+    {
+        const Unlocked unlocked;
+        if (!out) {
+            new_out = at::empty(q->sizes(), q->options());
+            out = &new_out;
+        }
+        if (!row) {
+            new_row = at::empty({c.batch, c.n_kv_heads, c.head_dim / 32}, q->options().dtype(at::kInt));
+            row = &new_row;
+        }
+        st = decode_entry(c.handle, q->data_ptr(), k->data_ptr(), v->data_ptr(), out->data_ptr(), (uint32_t *)row->data_ptr(), stream());
+    }
     if (st != DA_OK) return PyLong_FromLong((long)st);
     PyObject *const a = out == &new_out ? THPVariable_Wrap(std::move(new_out)) : (Py_INCREF(args[4]), args[4]);
     PyObject *const b = row == &new_row ? THPVariable_Wrap(std::move(new_row)) : (Py_INCREF(args[5]), args[5]);

@@ -1,4 +1,10 @@
 """The binding's compiled calls: the same results, refusals and objects as its Python code, which takes whatever is not in order."""
+import gc
+import struct
+import sys
+import threading
+import time
+
 import pytest
 import torch
 
@@ -105,3 +111,43 @@ def test_decode_both_ways(monkeypatch):
         got.append(rows)
     for a, b in zip(*got):
         assert a == b if isinstance(a, str) else torch.equal(a, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("asks_for", ["a prefill's workspace", "a prefill's output", "a decode step's output"])
+def test_other_threads_run_while_memory_is_asked_for(asks_for):
+    """Memory that torch has to ask the driver for takes long, and waits for the device where others' is freed first: no other Python thread may stand
+    still for it.  There is none left here: each call ends where it asks for it, with nothing launched.  Threads are only switched where one gives the
+    interpreter up, so that the count moves only if the call does."""
+    assert da._torch() and da._marshal is not None
+    if asks_for == "a decode step's output":                       # (no cache: a step that came as far as the library would be refused)
+        q, k, v = (torch.empty(4096, h, 128, dtype=torch.bfloat16, device="cuda") for h in (64, 1, 1))
+        args = da._marshal.decode, struct.pack("P6i", 0, 4096, 64, 1, 128, da.DA_BF16, 0), q, k, v, None, None
+    else:
+        q, k, v = (torch.empty(1, h, 1 << 16, 64, dtype=torch.bfloat16, device="cuda") for h in (32, 1, 1))
+        ws = None if asks_for == "a prefill's workspace" else torch.empty(16, dtype=torch.uint8, device="cuda")
+        args = da._marshal.prefill, q, k, v, 0.1, 64, 0.0, 0, 0, 0, ws, None
+    count, stop = [0], threading.Event()
+
+    def others():
+        while not stop.is_set():
+            count[0] += 1
+            time.sleep(1e-5)
+    thread, moved, interval = threading.Thread(target=others), 0, sys.getswitchinterval()
+    gc.collect()                                                   # (tensors that an earlier test's exceptions still hold)
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(1e-6)
+    thread.start()
+    sys.setswitchinterval(1000)
+    try:
+        for _ in range(100):
+            before = count[0]
+            with pytest.raises(torch.OutOfMemoryError):
+                args[0](*args[1:])
+            moved += count[0] != before
+    finally:
+        sys.setswitchinterval(interval)
+        stop.set()
+        thread.join()
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert moved
