@@ -521,6 +521,9 @@ __device__ __forceinline__ uint32_t piece_bits<float>(uint4 x, uint4 y) {
     return min(x.x ^ y.x, 1u) | min(x.y ^ y.y, 1u) << 1 | min(x.z ^ y.z, 1u) << 2 | min(x.w ^ y.w, 1u) << 3;
 }
 
+// 32 channels a work group: rounds alone (whole_plan)
+template <int DL> constexpr bool kInOrder = DL < 32;
+
 template <typename T, int DL, typename... Copy>                  // Copy: RowCopy, for the work groups behind those that scan, or nothing
 __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy... copy) {
     using Raw = typename TwoRaw<T>::type;
@@ -543,8 +546,8 @@ __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy...
     auto run_of = [&](int t) { return (int)(__umulhi(2u * (uint32_t)t, g.by_l_mul) >> g.by_l_shift); };
     uint4 *const rows = (uint4 *)lds_w + P;                      // piece q of row t: rows[(t + run_of(t)) * P + q]
     float2 *const E = (float2 *)(rows + (size_t)runs * (L + 1) * P);   // [runs][PR]
-    float2 *const S = E + runs * PR;                             // [runs][PR] what the runs have been walked from
-    uint32_t *const flags = (uint32_t *)(S + runs * PR);         // [2] some run was wrong in an even, odd round
+    float2 *const S = E + runs * PR;                             // [runs][PR] what the runs have been walked from, where they settle in order
+    uint32_t *const flags = (uint32_t *)(kInOrder<DL> ? S + runs * PR : S);   // [2] some run was wrong in an even, odd round
     uint32_t *const total = flags + 2;
     const T *Kp = g.K + (size_t)unit * n * g.d + ch0;
     const int gpr = g.d / kPer;                                  // pieces of a row in memory
@@ -613,7 +616,7 @@ __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy...
         E[tid] = walk_rows(a, a + L, start);
     }
     __syncthreads();
-    bool settled;
+    bool settled;                                                // (DL == 32: in as many rounds as there are runs it always is)
     for (int round = 0;; ++round) {
         float2 from = start;
         if (works && run > 0) from = E[tid - PR];
@@ -631,20 +634,23 @@ __global__ __launch_bounds__(512) void scan_whole_kernel(WholeArgs<T> g, Copy...
     }
     // What is left, in order, a wave per channel: its lanes hold the rows of a run and say which of them fire, so that a row that does not fire costs
     // nothing (60 clocks a row that does, 60 a run; in a round 50 a row of the longest chain's run, and two barriers).
-    if (!settled) {
-        if (works) S[tid] = start;
-        __syncthreads();
-        float *const ends = (float *)E;                          // [runs][DL]
-        const float *const starts = (const float *)S;
-        const int lane = tid & 63;
-        for (int c = __builtin_amdgcn_readfirstlane(tid >> 6); c < DL; c += threads >> 6)
-            runs_in_order(
-                runs, [&](int r) { return ends[r * DL + c]; }, [&](int r) { return starts[r * DL + c]; }, [&](int r, float end) { ends[r * DL + c] = end; },
-                [&](int r, int held) {
-                    return fired_in(load_f32((const T *)(rows + (size_t)r * (L + 1) * P), (size_t)(min(lane, L - 1) * DL + c)), L, held, theta);
-                });
-        __syncthreads();
-        if (works && run > 0) start = E[tid - PR];
+    if constexpr (kInOrder<DL>) {
+        if (!settled) {
+            if (works) S[tid] = start;
+            __syncthreads();
+            float *const ends = (float *)E;                      // [runs][DL]
+            const float *const starts = (const float *)S;
+            const int lane = tid & 63;
+            for (int c = __builtin_amdgcn_readfirstlane(tid >> 6); c < DL; c += threads >> 6)
+                runs_in_order(
+                    runs, [&](int r) { return ends[r * DL + c]; }, [&](int r) { return starts[r * DL + c]; },
+                    [&](int r, float end) { ends[r * DL + c] = end; },
+                    [&](int r, int held) {
+                        return fired_in(load_f32((const T *)(rows + (size_t)r * (L + 1) * P), (size_t)(min(lane, L - 1) * DL + c)), L, held, theta);
+                    });
+            __syncthreads();
+            if (works && run > 0) start = E[tid - PR];
+        }
     }
     if (works) {
         Raw *r = (Raw *)(rows + (size_t)run * (L + 1) * P) + p;
@@ -701,10 +707,10 @@ constexpr int kSettleWaves = 16;                                 // a channel ea
 constexpr int kMostSegment = 384;                                // rows of a segment (scan_plan)
 
 // The reference keys, masks and counts of up to four segments of 16 channels again, one segment to 16 lanes: rows from t0 on (t1 - t0 are a segment's, `most` any one's) from `held`, where those
-// there are from `spec`; `mine`: this lane's segment is one of them.  Until the two chains have met in every lane.  Returns the value the segment ends on.
+// there are from `spec`; `mine`: this lane's segment is one of them.  Until the two chains have met in every lane.
 template <typename T>
-__device__ __forceinline__ float rewalk_four(const T *Kp, T *Hp, uint16_t *Mp, int d, int t0, int t1, int most, float spec, float held, float end, bool mine, float theta,
-                                             long long *adjust) {
+__device__ __forceinline__ void rewalk_four(const T *Kp, T *Hp, uint16_t *Mp, int d, int t0, int t1, int most, float spec, float held, bool mine, float theta,
+                                            long long *adjust) {
     const int lane = threadIdx.x & 63, sub = lane >> 4, at = lane & 15;
     bool synced = !mine || __float_as_uint(spec) == __float_as_uint(held);
     auto fetch = [&](T (&k)[U], int tb) {                        // rows past the end are clamped and not worked on
@@ -736,7 +742,6 @@ __device__ __forceinline__ float rewalk_four(const T *Kp, T *Hp, uint16_t *Mp, i
         fetch(ka, tb + 2 * U);
         if (!work(kb, tb + U)) break;
     }
-    return synced ? end : held;
 }
 
 // What segments end on travels in order, a wave per channel (runs_in_order), 16 channels to a work group; then every segment whose start was another is
@@ -783,10 +788,10 @@ __global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_kernel(ScanArgs
         uint16_t *const Mp = (uint16_t *)(g.mask_bits + (size_t)unit * n * (d >> 5)) + group;
         for (int s0 = 1 + wave; s0 < nseg; s0 += 4 * kSettleWaves) {
             const int s = min(s0 + sub * kSettleWaves, nseg - 1);
-            const float st = load_f32(su, (size_t)s * d + c), from = load_f32(eu, (size_t)(s - 1) * d + c), end = load_f32(eu, (size_t)s * d + c);
+            const float st = load_f32(su, (size_t)s * d + c), from = load_f32(eu, (size_t)(s - 1) * d + c);
             const uint64_t wrong = __ballot(s0 + sub * kSettleWaves < nseg && __float_as_uint(st) != __float_as_uint(from));
             if (wrong)
-                rewalk_four(Ku + c, Hp, Mp, d, s * g.S, min(n, s * g.S + g.S), g.S, st, from, end, (wrong >> (16 * sub) & 0xffff) != 0, g.theta, &adjust);
+                rewalk_four(Ku + c, Hp, Mp, d, s * g.S, min(n, s * g.S + g.S), g.S, st, from, (wrong >> (16 * sub) & 0xffff) != 0, g.theta, &adjust);
         }
     }
     if (lane == 0) sum += (unsigned long long)adjust;
@@ -1056,7 +1061,7 @@ static WholePlan whole_plan(int dtype, int units, int n, int d) {
     // and a wave would have 4 or 8 channels (appends, rounds / one and in order: 162 x 64 rows of 64 20.3 / 21.9, 72 x 80 of 128 41.8 / 45.3, 80 x 119 of 64 54.0 / 54.7; but 55 x 226 of 128 120.5 / 115.8).
     p.rounds = p.dl == 32 || n <= (p.dl == 16 ? 128 : 64) ? runs : groups(p.dl) > cus || n > 2048;
     const int used = (n + p.L - 1) / p.L;
-    p.lds = (size_t)(used * (p.L + 1) + 1) * p.dl * es + (size_t)used * p.dl * 8 + 16;
+    p.lds = (size_t)(used * (p.L + 1) + 1) * p.dl * es + (size_t)used * p.dl * (p.dl == 32 ? 4 : 8) + 16;   // (kInOrder)
     return p;
 }
 
