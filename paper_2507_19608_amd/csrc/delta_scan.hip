@@ -704,7 +704,8 @@ __global__ __launch_bounds__(256) void nnz_sum_kernel(NnzSum sum) {
 }
 
 constexpr int kSettleWaves = 16;                                 // a channel each
-constexpr int kMostSegment = 384;                                // rows of a segment (scan_plan)
+constexpr int kMostSegment = 384;                                // rows of a segment, where there are several, at most (scan_plan)
+static_assert(kMostSegment % 64 == 0, "whole blocks of a wave's lanes");
 
 // The reference keys, masks and counts of up to four segments of 16 channels again, one segment to 16 lanes: rows from t0 on (t1 - t0 are a segment's, `most` any one's) from `held`, where those
 // there are from `spec`; `mine`: this lane's segment is one of them.  Until the two chains have met in every lane.
@@ -970,8 +971,8 @@ static ScanPlan scan_plan(int dtype, int units, int n, int d) {
     const bool one = (int64_t)n * d * es <= 128 * 1024;
     p.warm = 128;
     const int64_t columns = (int64_t)units * ((d + 63) / 64), cus = device_cu_count();
-    const bool longest = !one && es == 2 && columns * (n / 384) >= 3 * cus && n >= 384 * kSettleWaves;
-    p.S = one ? n : longest ? 384 : columns * (n / 256) >= 3 * cus ? 256 : 128;
+    const bool longest = !one && es == 2 && columns * (n / kMostSegment) >= 3 * cus && n >= kMostSegment * kSettleWaves;
+    p.S = one ? n : longest ? kMostSegment : columns * (n / 256) >= 3 * cus ? 256 : 128;
     p.nseg = (n + p.S - 1) / p.S;
     p.dl = one ? d : 64;
     p.waves = one || longest ? 8 : 4;
@@ -1028,7 +1029,8 @@ struct WholePlan {
     size_t lds;
 };
 // Few channels per work group where there are few units, more where the work groups would not all be resident (every work group reads
-// whole cache lines); rows of at most 64 KB in LDS, so that two share a compute unit; runs of at most 32 rows up to 2048 rows.
+// whole cache lines); rows of at most 64 KB in LDS, so that two share a compute unit; runs of at most kMostRun rows, in
+// twice the threads where 256 would have longer ones.
 // The rows a run warms up on save rounds where every work group has a compute unit to itself and are only work where it has not.
 // One launch here / segments, and their settling where there are several, us, without the 1.5 us between these two (5 % jumps): 8 x 333 rows of 64 6.5 / 9.1,
 // 80 x 200 of 128 9.4 / 10.3, 8 x 1024 of 64 9.2 / 13 - 16, 8 x 2048 of 64 11.5 / 14 + 3.9, 10 x 1024 of 128 8.5 / 10 + 3.8, 5 x 4096 of 128
@@ -1040,6 +1042,8 @@ struct WholePlan {
 // Where there are about as many units as compute units (three quarters and more), and one's rows are 64 to 128 KB, a work group per unit reads whole rows and
 // needs no second wave of work groups: 256 x 700 rows of 64 18.7 here / 17.2 there, 256 x 400 of 128 19.9 / 17.2, 200 x 900 of 64 18.4 / 16.7, 256 x 1000 22.5 /
 // 23.4; but 256 x 400 of 64 13.3 / 19.0, 160 x 500 of 128 16.5 / 17.4.
+constexpr int kMostRun = 32;
+static_assert(kMostRun <= kWave, "where runs settle in order the lanes of a wave hold one's rows (fired_in)");
 static WholePlan whole_plan(int dtype, int units, int n, int d) {
     const int es = dtype == 0 ? 4 : 2;
     const int64_t cus = device_cu_count();
@@ -1050,7 +1054,7 @@ static WholePlan whole_plan(int dtype, int units, int n, int d) {
     if (groups(8) > 2 * cus) p.dl = 16;
     if ((int64_t)n * p.dl * es > 64 * 1024) return p;            // (8 channels at a time read lines too often there: 88 x 2958 of 128 55 / 46)
     if (p.dl == 16 && groups(16) > 2 * cus && n <= 512) p.dl = 32;
-    p.threads = n > 32 * (256 / (p.dl / 2)) ? 512 : 256;
+    p.threads = n > kMostRun * (256 / (p.dl / 2)) ? 512 : 256;      // (64 KB are 4096 rows of 8 channels at most: 128 runs)
     const int runs = p.threads / (p.dl / 2);
     p.L = ((n + runs - 1) / runs + 7) / 8 * 8;
     p.warm = groups(p.dl) <= cus ? 48 : 32;
