@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import dense_form as df
+import scan_plans
 from paper_2507_19608_amd import binding as da
 from test_scan_settle import _keys
 from util import TORCH_DTYPE
@@ -64,17 +65,23 @@ def test_segments_of_384_rows(units, n, d):
         assert (nnz == ref_mask.sum(dim=(2, 3))).all(), kind
 
 
-@pytest.mark.parametrize("dtype,units,d", [("bf16", 3, 64), ("f32", 1, 32), ("bf16", 40, 128)])
-@pytest.mark.parametrize("runs", [2, 3, 64, 65, 66, 128])
-def test_runs_in_order(dtype, units, d, runs):
-    """Runs of 32 rows whose ends travel in order, 64 of them at a time: the first run of the next 64, and of those behind; channels that never
-    meet their guess, that meet it in most runs and that fire in every one; with and without a round in front."""
-    n = 32 * runs - 5
-    if n * 8 * (2 if dtype == "bf16" else 4) > 64 * 1024 or n < 64:
-        n = 64 if n < 64 else 2048
+# (of the rules, more than 64 runs are 86 or more: 2049 rows of 8 channels)
+@pytest.mark.parametrize("dtype,units,d,n,runs", [
+    ("bf16", 3, 64, 65, 9), ("bf16", 3, 64, 512, 64), ("bf16", 3, 64, 1031, 43), ("bf16", 3, 64, 2043, 64), ("bf16", 3, 64, 2049, 86), ("bf16", 3, 64, 3067, 128),
+    ("bf16", 3, 64, 3073, 97), ("bf16", 3, 64, 4096, 128), ("f32", 1, 32, 65, 9), ("f32", 1, 32, 2043, 64),
+    ("bf16", 40, 128, 129, 17), ("bf16", 40, 128, 1019, 32), ("bf16", 40, 128, 1025, 43), ("bf16", 40, 128, 2043, 64),
+])
+def test_runs_in_order(dtype, units, d, n, runs):
+    """Runs whose ends travel in order, 64 of them at a time: the fewest, as many as travel together, those and some more, and twice that; of 8 and of 32 rows; channels
+    that never meet their guess, that meet it in most runs and that fire in every one; with and without a round in front."""
+    plan = scan_plans.whole(dtype, units, n, d)
+    assert plan.runs == runs and plan.rounds == (n > 2048 or units == 40)
     for kind, theta in (("quiet", 0.3), ("mixed", 0.3), ("drift", 0.3), ("drift", 0.02)):
         K = _keys(kind, n + d, units, n, d, dtype)
-        _, bits, nnz = da.delta_attn_prefill(K, K, K, theta, 32)
-        _, ref_mask = df.reference_keys(K, theta)
+        ref_khat, ref_mask = df.reference_keys(K, theta)
+        bits, nnz, khat = da.delta_attn_delta_scan(K, theta, want_khat=True)
+        assert (khat.double() == ref_khat).all() and (df.unpack_bits(bits, d) == ref_mask).all(), (kind, theta)
+        assert (nnz == ref_mask.sum(dim=(2, 3))).all(), (kind, theta)
+        _, bits, nnz = da.delta_attn_prefill(K, K, K, theta, 32)       # (short prompts and small ones of fp32 scan in the attention's launch)
         assert (df.unpack_bits(bits, d) == ref_mask).all(), (kind, theta)
         assert (nnz == ref_mask.sum(dim=(2, 3))).all(), (kind, theta)
