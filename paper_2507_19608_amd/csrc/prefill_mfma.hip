@@ -687,14 +687,16 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             __builtin_amdgcn_s_setprio(0);
             if (!kLate || grp == 1) requests();
             softmax(kSplit == 1 ? turn : turn * kSplit + grp, yes);
-            // asked for three turns before the tile ends: whoever asks first gets the longest tile left (behind the turn's
-            // loads: a wait for older ones then does not wait for it)
-            if (turn == max(turns - 3, 0)) ask();
+            // asked for three turns before the tile ends: whoever asks first gets the longest tile left.  Behind the turn's loads, where a wait for
+            // older ones does not wait for it, and kLate behind the turn's barrier, where none comes before the next turn's.
+            const bool asks_now = turn == max(turns - 3, 0);
+            if (!kLate && asks_now) ask();
             __builtin_amdgcn_s_setprio(1);                       // (for the matrix phase that follows)
             if constexpr (kLate) {
                 if (grp == 0) {
                     ends_turn();
                     requests();
+                    if (asks_now) ask();                         // (wave 0 is one of these)
                 }
             } else if (kSplit > 1 || grp == 0) {
                 wait_loads<kLoads>();

@@ -121,3 +121,49 @@ def test_the_search_finds_a_copy(between, found):
     text = "0000000000000100 <kernel>:\n" + "".join(f"\t{l} // {256 + 8 * i:012X}: 00000000\n" for i, l in enumerate(lines))
     (code,) = _kernels(text).values()
     assert len(code) == 5 and _touched_in_flight(code)[0] == 1 and len(_touched_in_flight(code)[1]) == found
+
+
+def _waited_for_at_once(code):
+    """(tickets asked for, [instruction that waits for one with no product in between])"""
+    index = {at: i for i, (at, _, _, _) in enumerate(code)}
+    target = lambda i: index[code[0][0] + code[i][3]]
+    tickets, waits = 0, set()
+    for i in range(1, len(code)):
+        if code[i - 1][1:3] != ("s_nop", "4") or code[i][1] != "global_atomic_add":
+            continue
+        tickets += 1
+        seen, todo = set(), [(i + 1, 0)]
+        while todo:
+            j, later = todo.pop()
+            while (j, later) not in seen:
+                seen.add((j, later))
+                _, op, operands, _ = code[j]
+                if op == "s_endpgm" or op.startswith("v_mfma"):
+                    break
+                wait = re.search(r"vmcnt\((\d+)\)", operands) if op == "s_waitcnt" else None
+                if wait and int(wait.group(1)) <= later:
+                    waits.add((code[j][0], operands))
+                    break
+                later = min(later + op.startswith(("global_", "buffer_load", "buffer_store", "scratch_", "flat_")), 63)
+                if op.startswith("s_cbranch"):
+                    todo.append((target(j), later))
+                j = target(j) if op == "s_branch" else j + 1
+    return tickets, waits
+
+
+def test_nobody_waits_for_a_ticket_at_once(tmp_path):
+    """A ticket takes 2 us to come.  Wave 0 has a phase of products to do before it waits for it: a wait in front of the turn's barrier would hold all waves.  (The kernel
+    that does not pause between tiles may ask in front of its first one, whose loads it has to wait for anyway.)"""
+    dev = _device_code("prefill_mfma.hip", tmp_path)
+    text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", dev], check=True, capture_output=True, text=True).stdout
+    found = {name: _waited_for_at_once(code) for name, code in _kernels(text).items() if "kernelILi64E" in name or "kernelILi128ELb0E" in name}
+    assert len(found) == 6 and all(tickets >= 2 and not waits for tickets, waits in found.values()), found
+
+
+@pytest.mark.parametrize("between,found", [([], 1), (["v_mfma_f32_32x32x16_bf16 v[8:11], v[12:13], v[14:15], 0"], 0), (["s_waitcnt vmcnt(1)"], 1),
+                                           (["global_load_lds_dwordx4 v[2:3], off", "s_waitcnt vmcnt(1)", "v_mfma_f32_32x32x16_bf16 v[8:11], v[12:13], v[14:15], 0"], 1)])
+def test_the_search_finds_a_wait(between, found):
+    lines = ["s_nop 4", "global_atomic_add v5, v1, v2, s[2:3] sc0", *between, "s_waitcnt vmcnt(0)", "s_endpgm"]
+    text = "0000000000000100 <kernel>:\n" + "".join(f"\t{l} // {256 + 8 * i:012X}: 00000000\n" for i, l in enumerate(lines))
+    (code,) = _kernels(text).values()
+    assert _waited_for_at_once(code)[0] == 1 and len(_waited_for_at_once(code)[1]) == found
