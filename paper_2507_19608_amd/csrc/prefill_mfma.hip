@@ -1005,13 +1005,16 @@ void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     // average, -4 to 12 (32 / 8 heads: 512 x 64 83.6 / 80.5, 55 x 130 32.9 / 36.9, 16 x 700 61.8 / 64.1, 12 x 1024 82.4 / 86.0, 8 x 1500 106 / 107,
     // 4 x 4096 306 / 306).
     const int64_t whole_tiles = (int64_t)columns * a.kinds[0].tiles;
-    // At head_dim 64 instead: one barrier a turn for split tiles, too (kLate), where all tiles are resident at once, or so many follow that it does not matter which
-    // of the two work groups of a compute unit is done first; between that the longest tiles, which came first, would end last.  Two barriers / one: 512 tiles,
-    // 1 x 2048 tokens of 32 / 8 heads 41.1 / 40.1 us, 1 x 4096 of 16 / 2 63.3 / 61.9, 1 x 8192 of 8 / 8 115 / 112; 532, 1 x 5000 of 16 / 2 90.9 / 86.5; 552, 1 x 6000 113 / 115;
-    // 592, 1 x 3000 of 32 / 8 67.0 / 68.9; 624, 3 x 4000 of 8 / 8 92.6 / 106; 816, 1 x 8192 of 16 / 2 189 / 211; 925, 1 x 8000 of 20 / 5 205 / 221; 1010, 2 x 5003
-    // 175 / 171; 1024, 1 x 6000 of 32 / 8 206 / 200.
-    const bool stream = D == 64 ? 20 * (int64_t)a.blocks <= 21 * slots || 20 * (int64_t)a.blocks >= 39 * slots
-                                : (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
+    // At head_dim 64 instead: one barrier a turn for split tiles, too (kLate), where most tiles are split and about all of them are resident at once, or so many follow
+    // that it does not matter which of the two work groups of a compute unit is done first; between that the longest tiles, which came first, would end
+    // last.  Times as fast with it over 219 launches of 440 to 2832 tiles: up to 537 tiles, three quarters of them split or more 1.04 on the geometric
+    // mean (1.013 to 1.067), 70 to 75 % 0.997, fewer 0.986 (0.963 to 1.009); 538 to 997 tiles 1.00 (0.89 to 1.07, gains where nearly all of at most 560 are split); more, a third or more
+    // split 1.024 (0.99 to 1.057), fewer 0.997 (0.978 to 1.018; whole tiles alone 0.991 on one card and 1.006 on another).  Two barriers / one, us a call, of 16 / 2 heads:
+    // 1 x 4716 tokens, 464 of 528 tiles split, 85.4 / 80.2, 2 x 3070, 288 of 528, 73.0 / 75.2, 2 x 8138, 1000 of 1520, 334 / 325; of 8 / 8, 3 x 5004, 576 of
+    // 768, 133 / 149.
+    const int64_t tiles64 = a.blocks;
+    const bool late = 20 * tiles64 <= 21 * slots ? 4 * (int64_t)a.kinds[1].end >= 3 * tiles64 : 20 * tiles64 >= 39 * slots;
+    const bool stream = D == 64 ? late : (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
     const dim3 grid(a.total < slots ? a.total : slots), block(512);
     static std::atomic<uint64_t> lds_set[4];                     // per instantiation, one bit per device
     if (fill) {
