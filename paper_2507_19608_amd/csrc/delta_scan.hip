@@ -842,8 +842,8 @@ __device__ __forceinline__ float chase(const T *Kp, const T *Hp, int d, int t0, 
 // does not: an end value then travels one segment a round, and rounds until it arrives would make the time
 // quadratic in the number of segments.  So the first wave settles what is left in order - it only chases the end values, each
 // segment once - and one more round, which now has the right starts, writes.
-// 20 units x 8192 rows of 128 in bf16 where nothing fires: 2440 -> 677 us; 5 x 65536: 124.4 -> 5.03 ms; 4 x 16384 in fp32: 14.7 -> 1.13 ms
-// (rounds alone -> this); keys that drift steadily take what they did, 228 us for 20 x 8192.
+// Scans, us, 5 % jumps / keys that drift steadily / nothing fires: 33 units x 8192 rows of 128 in bf16 44 .. 48 / 488 / 692 .. 716, 96 x 5304 of 64 47 / 461 / 450 .. 465, 300 x 2100 of 64
+// 55 / 462 / 450 .. 462.  (Against rounds alone, on units so few that they settle in order now: where nothing fires, 20 x 8192 of 128, 64 segments, 2440 -> 677.)
 template <typename T>
 __global__ __launch_bounds__(64 * kSettleWaves) void scan_settle_rounds_kernel(ScanArgs<T> g) {
     __shared__ unsigned long long total;

@@ -77,9 +77,8 @@ constexpr size_t scan_lds(int n, int d) { return ((size_t)scan_room(n, d) * (d +
 
 // The reference keys of a unit's rows 0 .. n - 1, in LDS [scan_room][D + 4].  A thread walks a run of rows in two neighbouring channels, from the guess "held
 // = the row before" kWarm rows earlier; runs whose start is not what the run before has ended on walk again, in rounds, and one last walk puts reference
-// keys in the place of keys (as scan_whole_kernel does).  Runs are whole batches, so that a row costs its read and the three operations of each channel:
-// with the last run's end looked for in every row, 1 head of 64, 256 rows
-// took 11.6 us a call, now 9.8.
+// keys in the place of keys (as scan_whole_kernel does).  Runs are whole batches, so that a row costs its read and the three operations of each channel: with the last
+// run's end looked for in every row, 1 head of 64, 256 rows took 11.6 us a call, now 9.8.
 template <int D>
 __device__ __forceinline__ void scan_rows(const float *__restrict__ K, int n, float theta, float *rows) {
     constexpr int S = D + 4, PR = D / 2, kRuns = 64 * kWavesG / PR, kWarm = 48, N = kBatch;
@@ -419,9 +418,10 @@ bool launch_by_dim(const PrefillArgs &p, const PrefillScan *scan, hipStream_t s)
 }  // namespace
 
 // Every work group then scans the keys of its unit anew, beside the others as long as each has a compute unit; the scan's own launch spreads over more of them.
-// fp32, a scan in front / in the same launch, us a call: 1 head of 64, 64 tokens 11.0 / 9.8, 256 12.6 / 11.5 (since runs are whole batches
-// 9.8), 400 15.4 / 15.2, 580 18.7 / 19.1; 2 x 200, 4 heads 13.1 / 12.2; 2 x 256, 8 heads (272 work groups) 13.4 / 18.2; 1 head of 128, 128
-// tokens 14.5 / 13.4, 290 21.3 / 21.2; 8 x 200 of 8 / 8 heads 40 / 63.
+// fp32, a scan in front / in the same launch, us a call: 1 head of 64, 64 tokens 9.4 / 7.5, 256 12.6 / 9.8, 400 15.2 / 13.1, 512 16.4 / 14.2 (more rows are not tried: at 588
+// of 64 the LDS is full); 2 x 200, 4 heads 12.3 / 9.9; 1 head of 128, 128 tokens 12.6 / 10.6, 256 16.4 / 14.3; up to 256 work groups: 4 x 64, 8 heads 10.0 / 7.8, 480, 8 heads 17.3 / 14.4, 2 x 200, 8 heads
+// of 128 17.8 / 14.3.  Not taken: 264, 512, 8 / 1 heads 16.5 / 14.5; 272, 2 x 256, 8 heads 13.7 / 14.9 and 1 x 256, 16 / 4 heads 12.8 / 14.9; 288, 128, 32 / 8 heads 10.7 / 11.1; 896, 8 x 200, 8
+// heads 23.3 / 25.1.
 bool prefill_generic_scans(const PrefillArgs &p) {
     return p.dtype == 0 && (p.d == 64 || p.d == 128) && (int64_t)p.n * p.d <= 32768 &&
            (int64_t)p.B * p.Hq * ((p.n + 15) / 16 + 1) <= device_cu_count();

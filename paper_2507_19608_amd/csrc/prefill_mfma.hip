@@ -23,8 +23,8 @@
 //     A: | PV(b-1) S(b)   softmax(b)    | PV(b) S(b+1) softmax(b+1) |
 //     B: | softmax(b-1)   PV(b-1) S(b)  | softmax(b)   PV(b) S(b+1) |
 // Between two barriers a wave goes from phase to phase by itself: a block takes the sum of its two phases, not twice the longer one, as it did with
-// a barrier between them (4 x 8192 tokens, 20 / 5 heads of 128: 2590 -> 2480 clocks a block and pair of waves; 38 shapes 1.00 to 1.07 times as
-// fast, 1.03 on the geometric mean).  What the tiles need for that: three of each kind, requested up to two turns ahead.  Where every group has its own
+// a barrier between them (4 x 8192 tokens, 20 / 5 heads of 128, by the counters: 2960 to 3040 -> 2840 to 2870 clocks a block and pair of waves; 38 shapes 1.00 to 1.07 times as
+// fast, 1.03 on the geometric mean, with the shorter read-ahead of the operands and, at head_dim 64, kLate).  What the tiles need for that: three of each kind, requested up to two turns ahead.  Where every group has its own
 // there is room for two, and the next ones can only be requested behind the barrier, by all waves at once; see kLate.
 // A wave in its matrix phase goes first (s_setprio): it issues one instruction in 32 clocks, and every one that has to wait for
 // the other wave's arithmetic lengthens the phase (without it 5 % more clocks).  What is added to a matrix phase - addresses, loads, the look at the masks -
@@ -915,8 +915,9 @@ void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     // the k + 1 shortest of its kC + 1 longest tiles, which some compute unit has to take; the estimate is the largest of these.
     // In units of a whole tile's turn a tile costs kWhole or kHalf beside its turns, and a split one's turn kHalfTurn (fitted to 250
     // timed launches of 42 shapes, 8 % off on the average; head_dim 64: work of the two that share a compute unit, where one
-    // alone takes kAlone times as long).  Against the best of up to 13 cuts of each shape the chosen one is 1.0 % slower on the
-    // average at head_dim 128 and 1.1 % at 64, where looking at k = 1 alone was 6.0 and 3.9 %: 1 x 4096 tokens, 20 / 5 heads
+    // alone takes kAlone times as long).  That was with two barriers a turn in all tiles, and a whole tile's turn is shorter since; with the present
+    // kernels, 26 shapes, the chosen cut is 0.7 % slower on the average than the best of up to 11 at head_dim 128 (the worst 3 x 1436 tokens of 32 / 8 heads, 81.8 / 78.8 us) and
+    // 0.6 % at 64 (3 x 2500 of 16 / 2 in a sliding window, 68.5 / 66.8); before, of up to 13, 1.0 and 1.1 %, where looking at k = 1 alone was 6.0 and 3.9 %: 1 x 4096 tokens, 20 / 5 heads
     // of 128, 103 -> 93 us, 2 x 5003 in a sliding window 276 -> 247, 4 x 512 26.7 -> 22.4, 4 x 1024 48.1 -> 43.1.
     constexpr float kWhole = D == 128 ? 6.5f : 4.2f, kHalf = D == 128 ? 6.5f : 4.4f, kHalfTurn = D == 128 ? 1.22f : 0.93f, kAlone = D == 128 ? 1.f : 1.19f;
     const int all = (p.nq + rt - 1) / rt, columns = units * hgroups;
@@ -1000,7 +1001,9 @@ void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     static_assert(lds >= 6 * KB * D * 2 + 16 && lds >= 2 * 4 * (D / 64) * 16 * 64 * 4 + 2 * 4 * 64 * 2 * 4, "whole tiles, the merge");
     // Tile after tile without a pause where that many follow each other, or long ones do (head_dim 128, 20 / 5 heads, pausing / not:
     // 1 x 4096 tokens 104 / 102 us, 26 x 512 77.8 / 73.5, 133 x 64 34.8 / 32.1, though 27 x 900 173 / 179); for a second tile of few turns
-    // what is done beside two groups' turns in turn takes longer than a pause (7 x 598 34.7 / 35.4, 4 x 512 18.3 / 18.7).  At head_dim
+    // what is done beside two groups' turns in turn takes longer than a pause (7 x 598 34.7 / 35.4, 4 x 512 18.3 / 18.7).  (Those with two barriers a turn.  With one,
+    // calls of 25 shapes, pausing / not: taken 1 x 5390 of 20 / 5 heads 160.5 / 157.3, 1 x 5487 of 32 / 8 254.6 / 250.2, 4 x 8319 of 8 / 8 575 / 565, the least 4 x 3718 of 8 / 8 158.2 / 159.9; not
+    // taken 6 x 527 of 32 / 8 44.9 / 45.8, 3 x 1409 of 16 / 2 47.7 / 49.0, the most 1 x 2138 of 32 / 8 61.0 / 60.2.)  At head_dim
     // 64 the other work group of the compute unit fills the pause, and over 27 launches of 64 to 1400 tokens pausing was faster by 0.9 % on the
     // average, -4 to 12 (32 / 8 heads: 512 x 64 83.6 / 80.5, 55 x 130 32.9 / 36.9, 16 x 700 61.8 / 64.1, 12 x 1024 82.4 / 86.0, 8 x 1500 106 / 107,
     // 4 x 4096 306 / 306).
