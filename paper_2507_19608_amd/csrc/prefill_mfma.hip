@@ -106,7 +106,7 @@ struct MfmaArgs {
 // kind's end.  a: the kernel's argument, of which the walk keeps a few words in registers.  None of these kernels
 // may spill: a ticket of the queue is on its way into its register while other things are done, and a copy of that would be one of the old value
 // (a build in which one does fails).
-template <int D, int kSplit, bool kStream, bool kLate>
+template <int D, int kSplit, bool kStream, bool kLate, bool kQueue>   // kQueue: there may be tiles beyond those of the grid
 __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *lds_raw) {
     constexpr int kRowB = D * 2;                // bytes of a row
     constexpr int kSeg = D / 8;                 // 16-byte segments of a row
@@ -510,7 +510,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         for (int u = (int)(gridDim.x - 1 - blockIdx.x); u < sum.units; u += 8 * (int)gridDim.x)
             add_up_nnz(sum, u + (lane >> 3) * (int)gridDim.x);
     };
-    const bool asks = total > (int)gridDim.x;
+    const bool asks = kQueue && total > (int)gridDim.x;
     uint32_t ticket = 0;
     // Wave 0 asks for the next tile; in asm, so that nobody waits for the answer (2 us) before it is needed.
     auto ask = [&]() __attribute__((always_inline)) {
@@ -673,6 +673,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         // sooner (32 / 8 heads of 64, 2048 tokens: 2711 -> 2567 clocks a turn); of two that share one the first is not so far ahead of the second any
         // more (1.53 and 2.9 us a turn -> 1.75 and 2.7), see launch_d.  At head_dim 128 64 KB at once take the address path longer than is saved (3046 -> 3430).
         static_assert(!kLate || kSplit > 1, "whole tiles have the room");
+        int asks_at = -1;                                        // (kLate) the turn, for the wave that does: two instructions in front of a matrix phase
         auto vector_phase = [&](int turn) __attribute__((always_inline)) {
             auto ends_turn = [&]() __attribute__((always_inline)) {
                 wait_loads<0>();                                 // key tile turn + 1, value tile turn
@@ -689,14 +690,13 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
             softmax(kSplit == 1 ? turn : turn * kSplit + grp, yes);
             // asked for three turns before the tile ends: whoever asks first gets the longest tile left.  Behind the turn's loads, where a wait for
             // older ones does not wait for it, and kLate behind the turn's barrier, where none comes before the next turn's.
-            const bool asks_now = turn == max(turns - 3, 0);
-            if (!kLate && asks_now) ask();
+            if (!kLate && turn == max(turns - 3, 0)) ask();
             __builtin_amdgcn_s_setprio(1);                       // (for the matrix phase that follows)
             if constexpr (kLate) {
                 if (grp == 0) {
                     ends_turn();
                     requests();
-                    if (asks_now) ask();                         // (wave 0 is one of these)
+                    if (turn == asks_at) ask();                  // (wave 0 is one of these)
                 }
             } else if (kSplit > 1 || grp == 0) {
                 wait_loads<kLoads>();
@@ -711,6 +711,7 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
         while (true) {
             clear();
             buf = 0;
+            if constexpr (kLate) asks_at = asks && wave == 0 ? max(turns - 3, 0) : -1;
             phase_barrier();
             staged_queries();
             if (kSplit == 1 || (!kLate && grp == 1)) phase_barrier();   // (the area is free; group B starts one phase later)
@@ -821,13 +822,14 @@ __device__ __forceinline__ int tiles_of_kind(const MfmaArgs &a, int pos, char *l
 // Behind the tiles come the chunks that a cache is handed (fill_chunk), for whoever is done with the tiles or has none: a piece of a
 // prompt, or a short one, leaves compute units idle, and the hand-off's own launch took 9 us of each.
 // (kernels of their own: with the look for such a chunk at its end every other launch took 0.5 to 1 us longer.)
-template <int D, bool kStream, typename... Fill>                 // kStream: at head_dim 64 kLate; Fill: CacheFill, or nothing
+// kForm 1: kStream at head_dim 128, kLate at 64; 2: kLate where every work group has one tile and none asks for another.  Fill: CacheFill, or nothing
+template <int D, int kForm, typename... Fill>
 __global__ __launch_bounds__(512, D == 64 ? 4 : 2) void prefill_mfma_kernel(MfmaArgs a, Fill...) {
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
     int pos = blockIdx.x;
     if (pos >= a.turn_at && pos < a.blocks) pos = a.blocks - 8 - ((pos - a.turn_at) & ~7) + (pos & 7);
-    if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2, false, kStream && D == 64>(a, pos, lds_raw);
-    if (pos < a.kinds[0].end) pos = tiles_of_kind<D, 1, kStream && D == 128, false>(a, pos, lds_raw);
+    if (pos < a.kinds[1].end) pos = tiles_of_kind<D, 2, false, kForm != 0 && D == 64, kForm != 2>(a, pos, lds_raw);
+    if (pos < a.kinds[0].end) pos = tiles_of_kind<D, 1, kForm != 0 && D == 128, false, kForm != 2>(a, pos, lds_raw);
     if constexpr (sizeof...(Fill) == 0) return;
     // (the arguments of what follows are read here: in registers from the start on they would push others out across the walk)
     typedef const __attribute__((address_space(4))) char arg_char;
@@ -1019,15 +1021,18 @@ void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     const bool late = 20 * tiles64 <= 21 * slots ? 4 * (int64_t)a.kinds[1].end >= 3 * tiles64 : 20 * tiles64 >= 39 * slots;
     const bool stream = D == 64 ? late : (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
     const dim3 grid(a.total < slots ? a.total : slots), block(512);
-    static std::atomic<uint64_t> lds_set[4];                     // per instantiation, one bit per device
+    // (kLate with the look for the turn to ask in: 0.5 % slower in launches that need none, 1 x 2048 tokens of 32 / 8 heads 36.1 / 36.3 us)
+    constexpr int kResident = D == 64 ? 2 : 1;
+    const int form = stream ? (a.total <= slots ? kResident : 1) : 0;
+    static std::atomic<uint64_t> lds_set[6];                     // per instantiation, one bit per device
     if (fill) {
-        const auto kernel = stream ? prefill_mfma_kernel<D, true, CacheFill> : prefill_mfma_kernel<D, false, CacheFill>;
-        ensure_dynamic_lds((const void *)kernel, lds, lds_set[2 + stream]);
+        const auto kernel = form == 0 ? prefill_mfma_kernel<D, 0, CacheFill> : form == 1 ? prefill_mfma_kernel<D, 1, CacheFill> : prefill_mfma_kernel<D, kResident, CacheFill>;
+        ensure_dynamic_lds((const void *)kernel, lds, lds_set[3 + form]);
         hipLaunchKernelGGL(kernel, grid, block, lds, s, a, *fill);
         return;
     }
-    const auto kernel = stream ? prefill_mfma_kernel<D, true> : prefill_mfma_kernel<D, false>;
-    ensure_dynamic_lds((const void *)kernel, lds, lds_set[stream]);
+    const auto kernel = form == 0 ? prefill_mfma_kernel<D, 0> : form == 1 ? prefill_mfma_kernel<D, 1> : prefill_mfma_kernel<D, kResident>;
+    ensure_dynamic_lds((const void *)kernel, lds, lds_set[form]);
     hipLaunchKernelGGL(kernel, grid, block, lds, s, a);
 }
 

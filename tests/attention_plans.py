@@ -35,7 +35,7 @@ def _rule():
             piece("mfma.hpp", r"struct Divisor \{", r"\};"), piece("mfma.hpp", r"inline Divisor divisor\(", r"\}$"),
             piece("prefill_mfma.hip", r"constexpr int KB\b", r"constexpr int kQueueStride").rsplit("\n", 1)[0],
             piece("prefill_mfma.hip", r"struct MfmaArgs \{", r"\};"),
-            "template <int D, bool kStream, typename... Fill> static void prefill_mfma_kernel(MfmaArgs, Fill...) {}",
+            "template <int D, int kForm, typename... Fill> static void prefill_mfma_kernel(MfmaArgs, Fill...) {}",
             piece("prefill_mfma.hip", r"int resident\(", r"\}$"), piece("prefill_mfma.hip", r"template <int D>\nvoid launch_d\(", r"\}$"),
             """extern "C" void plan(int B, int Hq, int Hkv, int d, int n, int nq, int W, int sliding, int64_t *o) {
     PrefillArgs p = {};

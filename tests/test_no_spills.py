@@ -156,8 +156,9 @@ def test_nobody_waits_for_a_ticket_at_once(tmp_path):
     that does not pause between tiles may ask in front of its first one, whose loads it has to wait for anyway.)"""
     dev = _device_code("prefill_mfma.hip", tmp_path)
     text = subprocess.run([f"{LLVM}/llvm-objdump", "-d", dev], check=True, capture_output=True, text=True).stdout
-    found = {name: _waited_for_at_once(code) for name, code in _kernels(text).items() if "kernelILi64E" in name or "kernelILi128ELb0E" in name}
-    assert len(found) == 6 and all(tickets >= 2 and not waits for tickets, waits in found.values()), found
+    found = {name: _waited_for_at_once(code) for name, code in _kernels(text).items() if re.search("prefill_mfma_kernelILi(64ELi[012]|128ELi0)E", name)}
+    assert len(found) == 8 and not any(waits for _, waits in found.values()), found
+    assert all((tickets == 0) == ("ILi64ELi2E" in name) for name, (tickets, _) in found.items()), found
 
 
 @pytest.mark.parametrize("between,found", [([], 1), (["v_mfma_f32_32x32x16_bf16 v[8:11], v[12:13], v[14:15], 0"], 0), (["s_waitcnt vmcnt(1)"], 1),
