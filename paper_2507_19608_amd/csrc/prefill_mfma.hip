@@ -1012,11 +1012,10 @@ void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     const int64_t whole_tiles = (int64_t)columns * a.kinds[0].tiles;
     // At head_dim 64 instead: one barrier a turn for split tiles, too (kLate), where most tiles are split and about all of them are resident at once, or so many follow
     // that it does not matter which of the two work groups of a compute unit is done first; between that the longest tiles, which came first, would end
-    // last.  Times as fast with it over 219 launches of 440 to 2832 tiles: up to 537 tiles, three quarters of them split or more 1.04 on the geometric
-    // mean (1.013 to 1.067), 70 to 75 % 0.997, fewer 0.986 (0.963 to 1.009); 538 to 997 tiles 1.00 (0.89 to 1.07, gains where nearly all of at most 560 are split); more, a third or more
-    // split 1.024 (0.99 to 1.057), fewer 0.997 (0.978 to 1.018; whole tiles alone 0.991 on one card and 1.006 on another).  Two barriers / one, us a call, of 16 / 2 heads:
-    // 1 x 4716 tokens, 464 of 528 tiles split, 85.4 / 80.2, 2 x 3070, 288 of 528, 73.0 / 75.2, 2 x 8138, 1000 of 1520, 334 / 325; of 8 / 8, 3 x 5004, 576 of
-    // 768, 133 / 149.
+    // last.  Times as fast with it over 190 launches of 440 to 3024 tiles: up to 537 tiles, three quarters of them split or more 1.037 on the geometric
+    // mean (0.943 to 1.085), fewer 0.984 (0.949 to 1.007; 70 to 75 % of an earlier build 0.997); 538 to 997 tiles 1.00 (0.85 to 1.09, gains where nearly all of at most 560 are split); more, a
+    // third or more split 1.033 (1.003 to 1.066), fewer 1.005 (0.985 to 1.023; whole tiles alone 1.000).  Two barriers / one, us a call, of 16 / 2 heads: 1 x 4672 tokens, 456
+    // of 520 tiles split, 83.2 / 77.2, 2 x 3099, 296 of 536, 72.8 / 74.3, 1 x 8201, 508 of 768, 177 / 209, 3 x 6923, 1020 of 1812, 338 / 330.
     const int64_t tiles64 = a.blocks;
     const bool late = 20 * tiles64 <= 21 * slots ? 4 * (int64_t)a.kinds[1].end >= 3 * tiles64 : 20 * tiles64 >= 39 * slots;
     const bool stream = D == 64 ? late : (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
