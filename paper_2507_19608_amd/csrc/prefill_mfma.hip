@@ -1020,7 +1020,7 @@ void launch_d(const PrefillArgs &p, const CacheFill *fill, hipStream_t s) {
     const bool late = 20 * tiles64 <= 21 * slots ? 4 * (int64_t)a.kinds[1].end >= 3 * tiles64 : 20 * tiles64 >= 39 * slots;
     const bool stream = D == 64 ? late : (2 * whole_tiles >= 5 * slots || (whole_tiles > slots && p.q_off + a.kinds[0].tiles * rt / 2 >= 24 * KB));
     const dim3 grid(a.total < slots ? a.total : slots), block(512);
-    // (kLate with the look for the turn to ask in: 0.5 % slower in launches that need none, 1 x 2048 tokens of 32 / 8 heads 36.1 / 36.3 us)
+    // (kLate with / without the look for the turn to ask in, launches that need none: 1 x 2048 tokens of 32 / 8 heads 36.4 / 36.0 us, 1 x 3000 of 16 / 2 46.3 / 45.7, 4 x 2048 of 8 / 8 42.3 / 42.1)
     constexpr int kResident = D == 64 ? 2 : 1;
     const int form = stream ? (a.total <= slots ? kResident : 1) : 0;
     static std::atomic<uint64_t> lds_set[6];                     // per instantiation, one bit per device
